@@ -84,8 +84,14 @@ struct ImageBarrier {
   unsigned int arrived;
   int failed;
 };
+// Device-scope store: written through the XCD's L2.
+__device__ __forceinline__ void store_through(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 constexpr long long kBarrierLimitTicks = 200000000LL;   // 2 s, the default of `limit_ticks`
 
+// WRITE_BACK = false: everything the workgroup hands on went out in store_through() and is at the coherence point once
+// the stores are acknowledged, so the caches need no write-back.
+template <bool WRITE_BACK = true>
 __device__ __forceinline__ bool image_barrier_wait(ImageBarrier* bar, unsigned int target, int* s_flag, long long limit_ticks) {
   // Every wave first waits until its own stores have been acknowledged by the L2 (vmcnt counts loads and
   // stores on this architecture); the cache maintenance itself acts on the CU's L1 and the XCD's L2, not on a
@@ -94,19 +100,21 @@ __device__ __forceinline__ bool image_barrier_wait(ImageBarrier* bar, unsigned i
   __syncthreads();
   if (threadIdx.x == 0) {
     int ok = 1;
-    __threadfence();
-    __hip_atomic_fetch_add(&bar->arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    // one write-back, then relaxed polling, then one invalidate: an acquire per poll would invalidate the caches
+    // under the workgroups that are still at work, a release on the counter would write them back a second time
+    if (WRITE_BACK) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __hip_atomic_fetch_add(&bar->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const long long t0 = wall_clock64();
-    while (__hip_atomic_load(&bar->arrived, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
+    while (__hip_atomic_load(&bar->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
       if (__hip_atomic_load(&bar->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
           wall_clock64() - t0 > limit_ticks) {
         ok = 0;
         break;
       }
-      __builtin_amdgcn_s_sleep(4);
+      __builtin_amdgcn_s_sleep(1);
     }
     if (!ok) __hip_atomic_store(&bar->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     *s_flag = ok;
   }
   __syncthreads();
