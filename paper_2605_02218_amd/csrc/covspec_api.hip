@@ -367,24 +367,18 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
   if (q.lr == COVSPEC_LR_ENERGY_TOPK) {
     float* c = c_out ? c_out : at<float>(ws, q.c);
     marks.mark(COVSPEC_STAGE_LOWRANK);
-    if (q.P > 0) {
-      // r dominant eigenpairs by block subspace iteration; images whose residual check fails fall back to
-      // the full Jacobi solve (which leaves the others untouched)
-      int* ok = at<int>(ws, q.ok);
-      const double* Ut = nullptr;
-      HIPCHK(launch_subspace_eigen(A, q.B, q.M, q.nP, q.r, q.P, kSubspaceIters, kSubspaceMoreIters, at<void>(ws, q.sub), at<void>(ws, q.ctl),
-                                   at<double>(ws, q.lam), ok, &Ut, img_status, marks.ev ? marks.ev[COVSPEC_PROBE_BEGIN] : nullptr,
-                                   marks.ev ? marks.ev[COVSPEC_PROBE_END] : nullptr, st));
-      probed = true;
-      HIPCHK(launch_jacobi_eigen(A, q.B, q.M, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, img_status, st));
-      marks.mark(COVSPEC_STAGE_KEEP);
-      HIPCHK(launch_subspace_energy(Ut, q.B, q.P, q.M, q.nP, (long)q.P * q.nP, q.r, at<double>(ws, q.lam), c, ok, 1, st));
-      HIPCHK(launch_subspace_energy(A, q.B, q.M, q.M, q.nP, (long)q.nP * q.nP, q.r, at<double>(ws, q.lam), c, ok, 0, st));
-    } else {
-      HIPCHK(launch_jacobi_eigen(A, q.B, q.M, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), nullptr, nullptr, img_status, st));
-      marks.mark(COVSPEC_STAGE_KEEP);
-      HIPCHK(launch_subspace_energy(A, q.B, q.M, q.M, q.nP, (long)q.nP * q.nP, q.r, at<double>(ws, q.lam), c, nullptr, 0, st));
+    // energies in the r-dominant subspace; images whose residual check fails (or whose matrix is neither large enough
+    // for a block nor small enough for a direct split) take the full Jacobi solve, which leaves the others untouched
+    int* ok = nullptr;
+    if (q.P > 0 || split_direct(q.nP)) {
+      ok = at<int>(ws, q.ok);
+      HIPCHK(launch_subspace_eigen(A, q.B, q.M, q.nP, q.r, q.P, kSubspaceIters, kSubspaceMoreIters, at<void>(ws, q.sub), ok, c, img_status,
+                                   marks.ev ? marks.ev[COVSPEC_PROBE_BEGIN] : nullptr, marks.ev ? marks.ev[COVSPEC_PROBE_END] : nullptr, st));
+      probed = q.P > 0;
     }
+    HIPCHK(launch_jacobi_eigen(A, q.B, q.M, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, img_status, st));
+    marks.mark(COVSPEC_STAGE_KEEP);
+    HIPCHK(launch_subspace_energy(A, q.B, q.M, q.M, q.nP, (long)q.nP * q.nP, q.r, at<double>(ws, q.lam), c, ok, 0, st));
     HIPCHK(launch_select_top(c, q.B, q.M, q.k, idxm, idx_out, st));
   } else {
     int32_t* order = at<int32_t>(ws, q.order);
@@ -844,18 +838,14 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
     float* c = c_out ? c_out : at<float>(ws, q.c);
     HIPCHK(hipMemcpyAsync(A, Gc, (size_t)q.B * gstride * 8, hipMemcpyDeviceToDevice, st));   // the solve may overwrite its input
     const int P = subspace_block(nC, q.r);
-    if (P > 0) {
-      int* ok = at<int>(ws, q.ok);
-      const double* Ut = nullptr;
-      HIPCHK(launch_subspace_eigen(A, q.B, nC, q.nP, q.r, P, kSubspaceIters, kSubspaceMoreIters, at<void>(ws, q.sub), at<void>(ws, q.ctl),
-                                   at<double>(ws, q.lam), ok, &Ut, nullptr, nullptr, nullptr, st));
-      HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, nullptr, st));
-      HIPCHK(launch_subspace_energy(Ut, q.B, P, nC, q.nP, (long)P * q.nP, q.r, at<double>(ws, q.lam), c, ok, 1, st));
-      HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, ok, 0, st));
-    } else {
-      HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), nullptr, nullptr, nullptr, st));
-      HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, nullptr, 0, st));
+    int* ok = nullptr;
+    if (P > 0 || split_direct(q.nP)) {
+      ok = at<int>(ws, q.ok);
+      HIPCHK(launch_subspace_eigen(A, q.B, nC, q.nP, q.r, P, kSubspaceIters, kSubspaceMoreIters, at<void>(ws, q.sub), ok, c, nullptr, nullptr,
+                                   nullptr, st));
     }
+    HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, st));
+    HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, ok, 0, st));
     int32_t* selw = at<int32_t>(ws, q.sel);
     HIPCHK(launch_select_top(c, q.B, nC, q.k, nullptr, selw, st));
     sel = selw;

@@ -36,7 +36,7 @@ __device__ __forceinline__ int regroup_xcd(int bid, int nblocks) {
   return (bid < (per << 3)) ? (bid & 7) * per + (bid >> 3) : bid;
 }
 
-template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ>
+template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ, bool DUAL = false>
 __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr int TM = 32 * MI, TN = 32 * NJ;
   constexpr int SA = TM / 16, SBn = TN / 16;       // staged elements per thread and operand
@@ -108,6 +108,16 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 
   double ra_[SA], rb_[SBn];
   auto fetch = [&](int k0) {
+    if (DUAL && k0 >= g.K) {       // second pair of operands, subtracted (K % TK == 0, checked by the launcher)
+      k0 -= g.K;
+      const TA* __restrict__ A2 = (const TA*)g.A2 + (long)bo * g.strideA;
+      const TB* __restrict__ B2 = (const TB*)g.B2 + (long)bo * g.strideB;
+#pragma unroll
+      for (int s = 0; s < SA; ++s) ra_[s] = aok[s] ? -as_f64(A2[aoff[s] + k0]) : 0.0;
+#pragma unroll
+      for (int s = 0; s < SBn; ++s) rb_[s] = bok[s] ? as_f64(B2[boff[s] + (TRANSB ? (long)k0 * g.ldb : (long)k0)]) : 0.0;
+      return;
+    }
     if (WIDE_T && wide) {
       const u32x4_t z = {0u, 0u, 0u, 0u};
       const bf16_t* P = wop ? (const bf16_t*)B : (const bf16_t*)A;
@@ -158,7 +168,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
     for (int j = 0; j < NJ; ++j) acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 
   const int i16 = lane & 15, kq = lane >> 4;
-  const int nt = (g.K + TK - 1) / TK;
+  const int nt = (DUAL ? 2 : 1) * ((g.K + TK - 1) / TK);
   fetch(0);
   park(0);
   __syncthreads();
@@ -182,7 +192,10 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
     __syncthreads();
   }
 
-  if (EPI == EPI_STORE_F64 || EPI == EPI_SUB_F64) {
+  if (EPI == EPI_STORE_F64 || EPI == EPI_SUB_F64 || EPI == EPI_STORE_DOT) {
+    double dot[NJ];                // EPI_STORE_DOT: this lane's part of the column sums of C * D
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) dot[j] = 0.0;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -195,10 +208,23 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
             double* out = (double*)g.C + coff + (long)r * g.ldc + c;
             if (EPI == EPI_SUB_F64) *out -= acc[i][j][v];
             else *out = acc[i][j][v];
+            if (EPI == EPI_STORE_DOT) dot[j] = fma(acc[i][j][v], ((const double*)g.D)[coff + (long)r * g.ldc + c], dot[j]);
             // lanes of equal i16 hold four consecutive rows r: the transposed store goes out in 32-byte pieces
             if (EPI == EPI_STORE_F64 && g.mirror && tn != tm) ((double*)g.C)[coff + (long)c * g.ldc + r] = acc[i][j][v];
           }
         }
+    if (EPI == EPI_STORE_DOT) {
+      double* red = smem;          // [2][TN], as below
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        double s = dot[j];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (kq == 0) red[wm * TN + wn * NJ * 16 + j * 16 + i16] = s;
+      }
+      __syncthreads();
+      if (tid < TN && col0 + tid < g.N) g.dots[((long)bidx * tiles_m + tm) * g.N + col0 + tid] = red[tid] + red[TN + tid];
+    }
   } else {  // EPI_ROWNORM2: per-row sum over this tile's columns of C^2 (fp64)
     double* red = smem;   // [2][TM], reuses the operand buffers (all reads of them are behind the last barrier)
 #pragma unroll
@@ -220,7 +246,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
   }
 }
 
-template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ>
+template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ, bool DUAL = false>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream) {
   constexpr int TM = 32 * MI, TN = 32 * NJ;
   const int tiles_m = (g.M + TM - 1) / TM, tiles_n = (g.N + TN - 1) / TN;
@@ -228,7 +254,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream) {
   if (nblocks <= 0) return hipSuccess;
   if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
   const size_t lds = (size_t)2 * (TM + TN) * PITCH * sizeof(double);
-  auto kern = gemm64_kernel<TA, TB, EPI, GATHER, TRANSB, MI, NJ>;
+  auto kern = gemm64_kernel<TA, TB, EPI, GATHER, TRANSB, MI, NJ, DUAL>;
   if (lds > 64 * 1024) {
     static PerDeviceInt raised;   // per instantiation
     const hipError_t e = ensure_dynamic_lds(raised, (const void*)kern, lds);
@@ -272,6 +298,16 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
 }  // namespace
 
 int gemm64_tiles_n(int N) { return (N + 63) / 64; }   // ROWNORM2 always runs with 64-column tiles
+
+hipError_t launch_gemm64_store_dot(const GemmArgs& g, hipStream_t stream) {
+  if (!g.transB || !g.D || !g.dots || g.gatherA || g.gatherB) return hipErrorInvalidValue;
+  return launch_cfg<double, double, EPI_STORE_DOT, false, true, 2, 2>(g, stream);
+}
+
+hipError_t launch_gemm64_rownorm_dual(const GemmArgs& g, hipStream_t stream) {
+  if (!g.transB || !g.A2 || !g.B2 || g.gatherA || g.gatherB || g.K % TK != 0) return hipErrorInvalidValue;
+  return launch_cfg<double, double, EPI_ROWNORM2, false, true, 2, 2, true>(g, stream);
+}
 
 hipError_t launch_gemm64_bf16(const GemmArgs& g, hipStream_t stream) { return launch_ab<bf16_t, bf16_t>(g, stream); }
 

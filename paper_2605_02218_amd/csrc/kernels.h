@@ -16,6 +16,7 @@ enum GemmEpilogue {
   EPI_ROWNORM2 = 1,   // C fp32 [M, tiles_n]: per-tile sums over columns of C^2 (C itself is not stored)
   EPI_STORE_F64 = 2,  // C fp64 [M,N]; the fp32 accumulators are flushed into fp64 every 256 k
   EPI_SUB_F64 = 3,    // C fp64 [M,N] -= A*B^T (fp64 kernel only)
+  EPI_STORE_DOT = 4,  // EPI_STORE_F64, and the column sums of C * D per row tile (fp64 kernel only)
 };
 
 struct GemmArgs {
@@ -39,6 +40,10 @@ struct GemmArgs {
   bool transB = false;                         // B is stored [K][N] (row pitch ldb), i.e. C = A * B
   const int* skip = nullptr;                   // per outer batch: the work is skipped while skip[b] > skip_if
   int skip_if = 1;
+  const void* A2 = nullptr;                    // launch_gemm64_rownorm_dual: second operands, laid out like A and B
+  const void* B2 = nullptr;
+  const void* D = nullptr;                     // launch_gemm64_store_dot: laid out like C
+  double* dots = nullptr;                      // [batch][ceil(M / 64)][N]
 };
 int gemm_tiles_n(int N);
 hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream);
@@ -48,6 +53,10 @@ hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream);
 // Epilogues: EPI_STORE_F64, EPI_ROWNORM2 (fp64 partials, one per 64-column tile).
 int gemm64_tiles_n(int N);
 hipError_t launch_gemm64_nt(const GemmArgs& g, bool a_is_f64, bool b_is_f64, hipStream_t stream);
+// C = A * B (B stored [K][N]), and g.dots: per 64-row tile the column sums of C * D, elementwise.
+hipError_t launch_gemm64_store_dot(const GemmArgs& g, hipStream_t stream);
+// Squared row lengths, one partial per 64-column tile (EPI_ROWNORM2), of A * B - A2 * B2 (B stored [K][N]; K % 16 == 0).
+hipError_t launch_gemm64_rownorm_dual(const GemmArgs& g, hipStream_t stream);
 // Both operands bf16: products of bf16 values are exact in fp64 and the sum is fp64, so the result is the
 // exactly rounded contraction to ~1e-16 (used where differences of Gram entries decide a ranking).
 hipError_t launch_gemm64_bf16(const GemmArgs& g, hipStream_t stream);
@@ -126,15 +135,8 @@ int jacobi_pitch(int n);      // row pitch (and padded order) the solver needs: 
 // preset_done (optional, [B]): images whose entry is non-zero are left untouched.
 // img_status (optional, [B]): set to 1 for an image whose workgroups gave up waiting for one another (its rows
 // are then NaN); never cleared here.
-// band (optional, [B]): largest super-block distance (32 rows each) whose pairs are visited, for matrices whose rows
-// only couple to near neighbours (see launch_band_limit); nullptr or an entry that saves no rounds: every pair.
 hipError_t launch_jacobi_eigen(double* A, int B, int n, int nP, int r, void* ctl, double* len2, const int* preset_done,
-                               const int* band, int* img_status, hipStream_t stream);
-// dmax[b] = largest distance between 32-row super-blocks at which rows of the symmetric n x n matrix H[b] couple with a
-// weight of at least tol, given S[b] = H[b]^2 (pitch n, lower triangle read); n % 32 == 0.
-// skip (optional, [B]): images with a non-zero entry are left out.
-hipError_t launch_band_limit(const double* S, int B, int n, double tol, int* dmax, const int* skip, hipStream_t stream);
-hipError_t launch_row_lengths(const double* A, int B, int rows, int pitch, long img_stride, double* lam, hipStream_t stream);
+                               int* img_status, hipStream_t stream);
 // Subspace energy (paper energy equation) from rows of the form lambda_k v_k^T: c[b,i] = sum over the r
 // longest of the `rows` rows of A[b] of A[k][i]^2 / |row k|, i < n.  A[b] starts at b*img_stride, rows have
 // `pitch` doubles.  `lam` is scratch of B*rows doubles.  Images with flag[b] != run_if are skipped
@@ -142,19 +144,36 @@ hipError_t launch_row_lengths(const double* A, int B, int rows, int pitch, long 
 hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int pitch, long img_stride, int r, double* lam,
                                   float* c, const int* flag, int run_if, hipStream_t stream);
 
+// ---------------------------------------------------------------- split.hip
+// Projector onto the span of the r dominant eigenvectors of the symmetric positive semidefinite H[b] (P x P, pitch P,
+// P % 64 == 0, r < P), left in Y[b]; X0, X1 are scratch of the same size.  ordered: the rows of H are ordered like its
+// eigenvalues (a block iteration's); required for P > 128 (split_direct).  `scratch`: split_scratch_bytes(B, P) bytes, read
+// again by the two launchers below.  skip (optional, [B]): images with a non-zero entry are left out.  img_status as
+// for launch_jacobi_eigen.  Where the eigenvalues at the cut cannot be told apart the image gets no projector.
+size_t split_scratch_bytes(int B, int P);
+bool split_direct(int nP);
+hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
+                                 const int* skip, int* img_status, hipStream_t stream);
+// Residual check and energies of a block iteration, see split.hip.
+hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
+                               int P, int n, int nP, int r, double tol, const void* scratch, int* ok, int pass_no, float* c,
+                               hipStream_t stream);
+// c[b][i] = (Pi G)_ii, i < n, from the projector of G[b] itself; done[b] = 1 where there is one, else 0 and c[b] untouched.
+hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n, int nP, int r, const void* scratch, int* done, float* c,
+                                hipStream_t stream);
+
 // ---------------------------------------------------------------- subspace.hip
-// Block subspace iteration for the r dominant eigenpairs of G[b] (fp64, n x n, pitch nP, left untouched).
-// subspace_block: block size P for (n, r), 0 when the full solve is the better choice.
-// On return ok[b] = 1 where the residual check passed; then the P rows of (*ut)[b] (pitch nP) are
-// theta_k u_k^T with the r longest converged.  jacobi_ctl / jacobi_len2 as for launch_jacobi_eigen.
+// Energies c[b, i], i < n, in the span of the r dominant eigenvectors of G[b] (fp64, n x n, pitch nP, left untouched) by
+// block subspace iteration; for P == 0 and nP <= 128 by the projector of G itself.
+// subspace_block: block size P for (n, r), 0 when the matrix is better split (nP <= 128) or solved as a whole.
+// On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second.
 int subspace_block(int n, int r);
 size_t subspace_workspace_bytes(int B, int n, int nP, int P);
 // probe_begin / probe_end (optional): recorded around the first of the subspace_product_launches(iters)
 // equal launches of the product Yt G (P x nP x nP per image).
 int subspace_product_launches(int iters);
-hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, int iters, int more_iters, void* ws, void* jacobi_ctl,
-                                 double* jacobi_len2, int* ok, const double** ut, int* img_status, hipEvent_t probe_begin,
-                                 hipEvent_t probe_end, hipStream_t stream);
+hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, int iters, int more_iters, void* ws, int* ok,
+                                 float* c, int* img_status, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t stream);
 
 // ---------------------------------------------------------------- greedy.hip
 // Greedy residual picks (variant): pivoted Cholesky of G[b] (fp64, pitch nP; G may be overwritten with the residual

@@ -1,0 +1,614 @@
+// Spectral split of a symmetric matrix H at its r-th eigenvalue: the orthogonal projector Pi onto the span of the
+// r dominant eigenvectors (paper Sec. III-A.3: the energies c_i need the rank-r subspace, not its eigenvectors:
+// c_i = (Pi G)_ii).
+//
+// Pi = (I + sign(H - mu I)) / 2 with mu between the r-th and the (r+1)-th eigenvalue.  Two kernels:
+//   split_kernel finds mu.  The rows of H are ordered like its eigenvalues (block iteration, subspace.hip), so the
+//     two eigenvalues at the cut are those of a 128 x 128 window of rows around r: what the rows outside couple to it
+//     enters an eigenvalue squared.  The window is brought to tridiagonal form by Householder reflections with the
+//     matrix in the registers of one workgroup, and the two eigenvalues are cut out of it by Sturm counts, 128 trial
+//     points per pass and eigenvalue.  A matrix of order <= 128 is its own window, whatever the order of its rows.
+//   sign_kernel iterates X <- 1.5 s X - 0.5 s^3 X^3 from X = (H - mu I) / |H - mu I| (Newton-Schulz; s is the factor
+//     for which the image of [l, 1] has the largest lower end, l the known lower bound on |eigenvalues of X|: a step
+//     then multiplies a small l by 2.6, against 1.5 without), two symmetric products per step on the fp64 MFMA, until
+//     X no longer changes.  12 to 21 steps for the spectra of the token matrices.
+// Before: the P x P problem was diagonalised by block Jacobi (six sweeps of P/32 - 1 rounds of 32 dependent rotation
+// steps each).  An eigen-decomposition orders every pair of rows; the energies only ask which side of the cut a
+// direction is on, and the products that answer that are matrix-core work without a serial chain of rotations.
+// Jacobi against split + sign, us: one matrix of order 128 2727 -> 143 + 168, one of 192 1482 -> 144 + 292, four of 192
+// 1769 -> 144 + 262, eight of 384 3551 -> 144 + 366, sixty-four of 256 3894 -> 144 + 1530.
+//
+// Leading rows [0, a) of an ordered H that do not couple to the rows around and beyond the cut (kLeadFar) and whose
+// eigenvalues are above mu by their diagonal (row sums of the scaled couplings below 1/2: no eigenvalue of the block is
+// below half its smallest diagonal entry) are wanted as they are: the iteration then runs on the trailing block only,
+// which is smaller and, without the largest eigenvalues, needs fewer steps.  What it leaves out shows in the residual
+// check of the caller.
+#include "common.h"
+#include "host_cache.h"
+#include "kernels.h"
+
+namespace covspec {
+
+namespace {
+
+constexpr int SN = 128;              // order of the window
+constexpr int kMaxSignSteps = 40;    // 25 take the smallest admitted l to 1 / 2.6, a handful more to 1
+constexpr double kMinGap = 1e-10;    // smallest half gap at the cut, relative to the norm, that is iterated on
+// Couplings |H_pq| / H_rr below which a leading row p is left out of the iteration: to rows beyond the cut (they go into
+// the residual as they are, in quadrature over the rows left out) and to the 32 rows before it (they meet the unwanted
+// directions only through these directions' tails).
+constexpr double kLeadFar = 2e-11, kLeadNear = 1e-6;
+
+struct SplitCtl {
+  unsigned long long dev[kMaxSignSteps + 2];   // per step: bits of the largest change of an entry of X
+  ImageBarrier bar;
+  unsigned int ticket;                         // ctl[0] only: next (image, slot) to hand to a starting workgroup
+  int state;                                   // 0: to be iterated, 1: left alone (no usable gap, or not asked for), 2: projector valid, 3: gave up
+  int first;                                   // a: rows before it are wanted as they are
+  double mu, inv_norm, l0, theta;              // cut, 1 / norm, lower bound on |eigenvalues of X|, r-th eigenvalue
+};
+
+// sum over the 16 lanes of a DPP row, the same in all of them
+__device__ __forceinline__ double row16_sum(double v) {
+#define COVSPEC_ROR_ADD(n)                                                                                  \
+  {                                                                                                         \
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + (n), 0xf, 0xf, false);         \
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + (n), 0xf, 0xf, false);         \
+    v += __hiloint2double(hi, lo);                                                                          \
+  }
+  COVSPEC_ROR_ADD(8)
+  COVSPEC_ROR_ADD(4)
+  COVSPEC_ROR_ADD(2)
+  COVSPEC_ROR_ADD(1)
+#undef COVSPEC_ROR_ADD
+  return v;
+}
+
+// Per row p of H: off[p] = sum over q != p of |H_pq|, and link[p] = the largest coupling to the rows from r - 32 on as a
+// multiple of what kLeadFar / kLeadNear admit; 1 where the |H_pq| / sqrt(H_pp H_qq) of the row sum to more than 1/2 (no
+// candidate for being left out of the iteration).  One wave per row, 16 rows per workgroup (the diagonal is read once for them).
+__global__ __launch_bounds__(256) void row_profile_kernel(const double* __restrict__ H, int P, long stride, int r, double* __restrict__ off,
+                                                          double* __restrict__ link, const int* __restrict__ skip) {
+  __shared__ double rd[4096];                        // reciprocal square roots of the diagonal, 0 for rows of length zero
+  const int b = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (skip && skip[b]) return;
+  const double* Hb = H + b * stride;
+  const double hrr = Hb[(long)(r - 1) * P + r - 1];
+  for (int q = threadIdx.x; q < P; q += 256) {
+    const double d = Hb[(long)q * P + q];
+    rd[q] = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int x = 0; x < 4; ++x) {
+    const int p = blockIdx.x * 16 + 4 * x + wv;      // P % 16 == 0
+    const double rp = rd[p];
+    double s = 0.0, t = 0.0, m = 0.0;
+    const double far = 1.0 / (kLeadFar * hrr), near = 1.0 / (kLeadNear * hrr);
+#pragma unroll 4
+    for (int q = lane; q < P; q += 64) {
+      const double h = q == p ? 0.0 : fabs(Hb[(long)p * P + q]);
+      const double w = h * rp * rd[q];
+      s += h;
+      t += w;
+      if (q >= r - 32 && q > p) m = fmax(m, h * (q >= r ? far : near));
+    }
+    s = wave_sum(s);
+    t = wave_sum(t);
+    m = wave_max(m);
+    if (lane == 0) {
+      off[(long)b * P + p] = s;
+      link[(long)b * P + p] = t < 0.5 && rp > 0.0 && m < 1.0 ? m : 1.0;      // NaN: 1
+    }
+  }
+}
+
+// Reflections 16 a0 .. 16 a0 + 15 (to 125) of the Householder reduction of split_kernel's window.  Reflection k takes row k
+// beyond the diagonal to one entry; rows and columns up to k are done.  a0 is a compile-time constant, so that finished
+// blocks of 16 cost nothing and the elements stay in registers.
+template <int a0>
+__device__ __forceinline__ void reflect_block(double (&A)[8][8], double* xs, double* ps, double* dv, double* es) {
+  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+  const int kend = a0 == 7 ? 14 : 16;           // k <= 125
+#pragma unroll 1
+  for (int kk = 0; kk < kend; ++kk) {
+    const int k = 16 * a0 + kk;
+    if (ti == kk) {                             // the owners of row k
+#pragma unroll
+      for (int y = a0; y < 8; ++y) {
+        const int j = tj + 16 * y;
+        if (j == k) dv[k] = A[a0][y];
+        xs[j] = j <= k ? 0.0 : A[a0][y];
+      }
+    }
+    __syncthreads();
+    double v[8], vi[8], p[8], ss = 0.0;
+#pragma unroll
+    for (int y = a0; y < 8; ++y) { v[y] = xs[tj + 16 * y]; vi[y] = xs[ti + 16 * y]; }
+    const double alpha = xs[k + 1];
+#pragma unroll
+    for (int y = a0; y < 8; ++y) ss = fma(v[y], v[y], ss);
+    ss = row16_sum(ss);
+    const double nrm = sqrt(ss);
+    const double den = fma(fabs(alpha), nrm, ss);
+    const double hinv = den > 1e-280 ? 1.0 / den : 0.0;      // a row that is zero already needs no reflection
+    const double v1 = alpha + copysign(nrm, alpha);
+    if (tid == 0) es[k] = ss;
+#pragma unroll
+    for (int y = a0; y < (a0 + 2 < 8 ? a0 + 2 : 8); ++y) {
+      if (tj + 16 * y == k + 1) v[y] = v1;
+      if (ti + 16 * y == k + 1) vi[y] = v1;
+    }
+#pragma unroll
+    for (int x = a0; x < 8; ++x) {
+      double s = 0.0;
+#pragma unroll
+      for (int y = a0; y < 8; ++y) s = fma(A[x][y], v[y], s);
+      s = row16_sum(s);
+      p[x] = ti + 16 * x > k ? s * hinv : 0.0;
+      if (tj == 0) ps[ti + 16 * x] = p[x];
+    }
+    __syncthreads();
+    double q[8], dot = 0.0;
+#pragma unroll
+    for (int y = a0; y < 8; ++y) { q[y] = ps[tj + 16 * y]; dot = fma(q[y], v[y], dot); }
+    dot = 0.5 * hinv * row16_sum(dot);
+#pragma unroll
+    for (int y = a0; y < 8; ++y) { q[y] = fma(-dot, v[y], q[y]); p[y] = fma(-dot, vi[y], p[y]); }
+#pragma unroll
+    for (int x = a0; x < 8; ++x)
+#pragma unroll
+      for (int y = a0; y < 8; ++y) A[x][y] = fma(-p[x], v[y], fma(-vi[x], q[y], A[x][y]));
+  }
+}
+
+// See the head of the file.  One workgroup of 256 threads per image: thread (ti, tj) = (tid / 16, tid % 16) holds the
+// elements (ti + 16 x, tj + 16 y) of the window, x, y < 8, in registers; a sum over a row is then 16 lanes of one DPP
+// row.  Two barriers per reflection.  Bound by latency (126 dependent reflections, then the Sturm recurrences).
+__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int r, const double* __restrict__ off,
+                                                    const double* __restrict__ link, bool ordered, SplitCtl* ctl,
+                                                    const int* __restrict__ skip) {
+  __shared__ double xs[SN], ps[SN], dv[SN], es[SN];   // es: squared off-diagonals
+  __shared__ double red[4];
+  __shared__ int cnt[2][4];
+  const int b = blockIdx.x, tid = threadIdx.x, ti = tid >> 4, tj = tid & 15, lane = tid & 63, wv = tid >> 6;
+  SplitCtl* cb = ctl + b;
+  if (b == 0 && tid == 0) ctl[0].ticket = 0u;
+  for (int k = tid; k < kMaxSignSteps + 2; k += 256) cb->dev[k] = 0ull;
+  if (tid == 0) {
+    cb->bar.arrived = 0u;
+    cb->bar.failed = 0;
+    cb->state = 1;
+    cb->first = 0;
+  }
+  if (skip && skip[b]) return;
+  const double* Hb = H + b * stride;
+  const int w0 = P <= SN ? 0 : (r - SN / 2 < 0 ? 0 : (r - SN / 2 > P - SN ? P - SN : r - SN / 2));
+  const int nw = P - w0 < SN ? P - w0 : SN;
+
+  double A[8][8];
+  double big = 0.0;
+#pragma unroll
+  for (int x = 0; x < 8; ++x)
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+      const int i = ti + 16 * x, j = tj + 16 * y;
+      A[x][y] = (i < nw && j < nw) ? Hb[(long)(w0 + i) * P + w0 + j] : 0.0;
+    }
+#pragma unroll
+  for (int x = 0; x < 8; ++x)
+    if (ti == tj) big = fmax(big, A[x][x]);       // H is positive semidefinite: no entry exceeds the largest diagonal entry
+  big = wave_max(big);
+  if (lane == 0) red[wv] = big;
+  __syncthreads();
+  big = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  if (!(big > 0.0) || !(big < 1e300)) return;     // zero matrix, infinities, NaN: left to the caller's fallback
+  const double scale = 1.0 / big;
+#pragma unroll
+  for (int x = 0; x < 8; ++x)
+#pragma unroll
+    for (int y = 0; y < 8; ++y) A[x][y] *= scale;
+
+  // ---- Householder reduction
+  reflect_block<0>(A, xs, ps, dv, es);
+  reflect_block<1>(A, xs, ps, dv, es);
+  reflect_block<2>(A, xs, ps, dv, es);
+  reflect_block<3>(A, xs, ps, dv, es);
+  reflect_block<4>(A, xs, ps, dv, es);
+  reflect_block<5>(A, xs, ps, dv, es);
+  reflect_block<6>(A, xs, ps, dv, es);
+  reflect_block<7>(A, xs, ps, dv, es);
+  if (ti >= 14 && tj >= 14) {
+    if (ti == tj) dv[112 + ti] = A[7][7];
+    else if (ti == 14) es[126] = A[7][7] * A[7][7];
+  }
+  if (tid == 0) es[127] = 0.0;
+  __syncthreads();
+
+  // ---- the m-th and (m+1)-th largest eigenvalue of the window, m = r - w0, by Sturm counts.  Threads 0..127 narrow
+  //      the interval of the first, the others that of the second, until both are known to 2 % of what separates them.
+  double top = 0.0;
+  if (tid < SN) top = dv[tid] + sqrt(es[tid]) + (tid > 0 ? sqrt(es[tid - 1]) : 0.0);
+  top = wave_max(top);
+  if (lane == 0) red[wv] = top;
+  __syncthreads();
+  top = fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) * 1.0001 + 1e-12;
+  double lo[2] = {-1e-3 * top, -1e-3 * top}, hi[2] = {top, top};
+  const int g = tid >> 7, m = r - w0 + g;
+#pragma unroll 1
+  for (int pass = 0; pass < 8; ++pass) {
+    const double l_ = g ? lo[1] : lo[0], h_ = g ? hi[1] : hi[0];
+    const double x = l_ + (h_ - l_) * ((double)((tid & 127) + 1) * (1.0 / 129.0));
+    double q = dv[0] - x;
+    int neg = q < 0.0 ? 1 : 0;
+#pragma unroll 8
+    for (int i = 1; i < SN; ++i) {
+      if (!(fabs(q) > 1e-200)) q = -1e-200;
+      double rq = __builtin_amdgcn_rcp(q);
+      rq = fma(rq, fma(-q, rq, 1.0), rq);
+      q = fma(-es[i - 1], rq, dv[i] - x);
+      neg += q < 0.0 ? 1 : 0;
+    }
+    // SN - neg eigenvalues lie at x or above: the m-th largest does where that is at least m
+    const unsigned long long yes = __ballot(SN - neg >= m);
+    if (lane == 0) cnt[pass & 1][wv] = __popcll(yes);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int t = cnt[pass & 1][2 * e] + cnt[pass & 1][2 * e + 1];
+      const double w = hi[e] - lo[e], l0 = lo[e], h0 = hi[e];
+      if (t > 0) lo[e] = l0 + w * ((double)t * (1.0 / 129.0));
+      if (t < SN) hi[e] = fmin(h0, l0 + w * ((double)(t + 1) * (1.0 / 129.0)));
+    }
+    const double gap = lo[0] - hi[1];
+    if (fmax(hi[0] - lo[0], hi[1] - lo[1]) <= 0.02 * gap) break;      // the same in every thread
+  }
+  const double gap = (lo[0] - hi[1]) * big;
+  const double mu = 0.25 * (lo[0] + hi[0] + lo[1] + hi[1]) * big;
+
+  // ---- rows that are wanted as they are, and the norm of the rest
+  const double* offb = off + (long)b * P;
+  const double* linkb = link + (long)b * P;
+  int bad = 0x7fffffff;                            // first row that couples across the cut
+  for (int p = tid; p < r; p += 256)
+    if (!(linkb[p] < 1.0 && 0.5 * Hb[(long)p * P + p] > mu)) bad = p < bad ? p : bad;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { const int t = __shfl_xor(bad, o, 64); bad = t < bad ? t : bad; }
+  __syncthreads();
+  if (lane == 0) cnt[0][wv] = bad;
+  __syncthreads();
+  bad = min(min(cnt[0][0], cnt[0][1]), min(cnt[0][2], cnt[0][3]));
+  if (bad > r - 32) bad = r - 32;
+  const int a = !ordered || bad < 64 ? 0 : bad / 64 * 64;
+  double nrm = 0.0;
+  for (int p = a + tid; p < P; p += 256) nrm = fmax(nrm, fabs(Hb[(long)p * P + p] - mu) + offb[p]);
+  nrm = wave_max(nrm);
+  if (lane == 0) red[wv] = nrm;
+  __syncthreads();
+  nrm = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  if (tid == 0) {
+    const double l0 = 0.45 * gap / nrm;            // a tenth off the half gap for what the window leaves out
+    cb->first = a;
+    cb->mu = mu;
+    cb->inv_norm = 1.0 / nrm;
+    cb->l0 = l0;
+    cb->theta = lo[0] * big;
+    cb->state = l0 > kMinGap && nrm < 1e300 ? 0 : 1;
+  }
+}
+
+constexpr int ST = 32;            // tile of a wave in the sign iteration
+constexpr int STP = ST + 1;
+
+// Tile (r0, c0), 32 x 32, of X Z for symmetric X, Z (pitch P), k over [k0, k0 + kn), kn % 16 == 0: one wave, operands
+// straight from global memory in 128-byte pieces of a row, DEPTH groups of 16 k in flight; the result goes to `out` (LDS).
+template <int DEPTH>
+__device__ __forceinline__ void tile_product(const double* X, const double* Z, int P, int k0, int kn, int r0, int c0, double* out) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+  const double* xr = X + (long)(r0 + i16) * P + k0 + 4 * kq;
+  const double* zr = Z + (long)(c0 + i16) * P + k0 + 4 * kq;
+  const long step = 16 * (long)P;
+  f64x4_t acc[2][2], fx[DEPTH][2], fz[DEPTH][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  const int nc = kn >> 4;
+  auto load = [&](int s, int c) {
+    if (c < nc) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        fx[s][x] = *(const f64x4_t*)(xr + x * step + 16 * c);
+        fz[s][x] = *(const f64x4_t*)(zr + x * step + 16 * c);
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < DEPTH; ++s) load(s, s);
+#pragma unroll 1
+  for (int c = 0; c < nc; c += DEPTH) {
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) {
+      if (c + s < nc) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx[s][x][k], fz[s][y][k], acc[x][y], 0, 0, 0);
+        load(s, c + s + DEPTH);
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(16 * x + 4 * v + kq) * STP + 16 * y + i16] = acc[x][y][v];
+}
+
+__device__ __forceinline__ void tile_of(int t, int& i, int& j) {      // t-th tile on or below the diagonal, row by row
+  int q = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while ((q + 1) * (q + 2) / 2 <= t) ++q;
+  while (q * (q + 1) / 2 > t) --q;
+  i = q;
+  j = t - q * (q + 1) / 2;
+}
+
+// The whole iteration of all images: workgroup (image, slot) owns the tiles slot, slot + W, ... on and below the
+// diagonal and stores each also transposed; the workgroups of an image meet after every product.  (Image, slot)
+// pairs are handed out by a ticket counter, so that resident workgroups always form whole images plus at most one
+// partial image whose missing workgroups start next; every wait is bounded.
+// X0, X1, Y: P x P per image; the projector is left in Y.
+// What the workgroups hand one another is stored through the L2 (store_through), which spares the write-back of a whole L2
+// at every meeting: eight images of order 192 to 320 took 553 us with write-backs and 366 us without (a single image of
+// order 192: 259 and 292 us, sixty-four of order 256: 1.70 and 1.53 ms).
+// WIDE = false: a workgroup's tile is 32 x 32, its waves take a quarter of k each; WIDE = true: the tile is 64 x 64, a
+// wave takes a quadrant of it and all of k (a quarter of the workgroups: sixty-four images of order 256 took 3.7 ms on
+// small tiles, whose workgroups the device holds only a quarter of at a time, and 1.7 ms on wide ones).
+// Everything is kept symmetric to the bit (the elements above the diagonal are those below it): rounding that differs
+// between the two would be a skew perturbation, which the iteration magnifies by 1 / l0.
+template <bool WIDE>
+__global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
+                                                                 int W, SplitCtl* ctl, int* img_status, long long limit_ticks) {
+  constexpr int TT = WIDE ? 2 * ST : ST;             // tile of the workgroup
+  constexpr int ES = WIDE ? 64 : 256;                // threads that store one 32 x 32 tile
+  __shared__ double part[4 * ST * STP];
+  __shared__ int s_flag;
+  __shared__ double s_dev[4];
+  const int tid = threadIdx.x, wv = tid >> 6;
+  if (tid == 0) s_flag = (int)atomicAdd(&ctl[0].ticket, 1u);
+  __syncthreads();
+  const int ticket = s_flag;
+  __syncthreads();                                   // s_flag is reused by the barriers
+  const int b = ticket / W, slot = ticket - b * W;
+  SplitCtl* cb = ctl + b;
+  if (cb->state != 0) return;                        // set before the launch; nobody of this image writes it before all have read it
+  const int a = cb->first;
+  const int ns = (P - a) / TT, ntiles = ns * (ns + 1) / 2;
+  const int nact = ntiles < W ? ntiles : W;
+  if (slot >= nact) return;
+  const double mu = cb->mu, inv = cb->inv_norm;
+  double l = cb->l0;
+  const long pp = (long)P * P;
+  const double* Hb = H + b * pp;
+  double *X = X0 + b * pp, *Xn = X1 + b * pp, *Yb = Y + b * pp;
+  unsigned int target = 0;
+  bool alive = true, done = false;
+  auto meet = [&]() {
+    target += nact;
+    alive = image_barrier_wait<false>(&cb->bar, target, &s_flag, limit_ticks);
+  };
+  // fn(r0, c0, first element, its LDS tile) on the 32 x 32 tile on or below the diagonal that this thread helps to store
+  auto for_tiles = [&](auto fn) {
+    for (int t = slot; t < ntiles; t += W) {
+      int ti, tj;
+      tile_of(t, ti, tj);
+      if (WIDE) {
+        const int qi = wv >> 1, qj = wv & 1;
+        fn(a + TT * ti + ST * qi, a + TT * tj + ST * qj, tid & 63, ti == tj && qj > qi);
+      } else {
+        fn(a + TT * ti, a + TT * tj, tid, false);
+      }
+    }
+  };
+  // the same with the tile's product X Z in LDS first
+  auto product = [&](const double* Z, auto fn) {
+    for_tiles([&](int r0, int c0, int e0, bool above) {
+      double* mine = part + wv * (ST * STP);
+      const int kn = WIDE ? P - a : (P - a) >> 2;     // P - a is a multiple of 64
+      if (!above) tile_product<WIDE ? 2 : 3>(X, Z, P, WIDE ? a : a + wv * kn, kn, r0, c0, mine);
+      __syncthreads();
+      auto sum = [&](int i, int j) {
+        const double* q = (WIDE ? mine : part) + i * STP + j;
+        return WIDE ? q[0] : (q[0] + q[ST * STP]) + (q[2 * ST * STP] + q[3 * ST * STP]);
+      };
+      if (!above)
+        for (int e = e0; e < ST * ST; e += ES) fn(r0, c0, e >> 5, e & 31, sum);
+      __syncthreads();
+    });
+  };
+  for_tiles([&](int r0, int c0, int e0, bool above) {
+    if (above) return;
+    for (int e = e0; e < ST * ST; e += ES) {
+      const int i = e >> 5, j = e & 31;
+      const long lo = r0 == c0 && j > i ? (long)(r0 + j) * P + c0 + i : (long)(r0 + i) * P + c0 + j;
+      store_through(&X[(long)(r0 + i) * P + c0 + j], (Hb[lo] - (r0 + i == c0 + j ? mu : 0.0)) * inv);
+      if (r0 != c0) store_through(&X[(long)(c0 + i) * P + r0 + j], Hb[(long)(r0 + j) * P + c0 + i] * inv);
+    }
+  });
+  meet();
+  int step = 0;
+#pragma unroll 1
+  for (; alive && !done && step < kMaxSignSteps; ++step) {
+    const double s = sqrt(3.0 / (1.0 + l + l * l)), c1 = 1.5 * s, c3 = -0.5 * s * s * s;
+    product(X, [&](int r0, int c0, int i, int j, auto sum) {            // Y = X X
+      store_through(&Yb[(long)(r0 + i) * P + c0 + j], sum(i, j));    // a diagonal tile: the same products in the same order
+      if (r0 != c0) store_through(&Yb[(long)(c0 + i) * P + r0 + j], sum(j, i));
+    });
+    meet();
+    if (!alive) break;
+    double dev = 0.0;
+    product(Yb, [&](int r0, int c0, int i, int j, auto sum) {           // Xn = c1 X + c3 X Y
+      const double x = X[(long)(r0 + i) * P + c0 + j];
+      const double xn = fma(c3, r0 == c0 && j > i ? sum(j, i) : sum(i, j), c1 * x);
+      store_through(&Xn[(long)(r0 + i) * P + c0 + j], xn);
+      const double d = fabs(xn - x);
+      dev = d > dev || !(d == d) ? (d == d ? d : INFINITY) : dev;
+      if (r0 != c0) store_through(&Xn[(long)(c0 + i) * P + r0 + j], fma(c3, sum(j, i), c1 * X[(long)(c0 + i) * P + r0 + j]));
+    });
+    dev = wave_max(dev);
+    if ((tid & 63) == 0) s_dev[wv] = dev;
+    __syncthreads();
+    if (tid == 0) {
+      const double m = fmax(fmax(s_dev[0], s_dev[1]), fmax(s_dev[2], s_dev[3]));
+      atomicMax(&cb->dev[step], (unsigned long long)__double_as_longlong(m));
+    }
+    meet();
+    if (!alive) break;
+    l = fmin(1.0, c1 * l + c3 * l * l * l);
+    const double change =
+        __longlong_as_double((long long)__hip_atomic_load(&cb->dev[step], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    // near its limit the iteration squares the error: an entry that moved by 1e-7 is 1e-14 away afterwards
+    done = l > 1.0 - 1e-6 && change < 1e-7;
+    double* tmp = X; X = Xn; Xn = tmp;
+  }
+  if (done) {
+    for_tiles([&](int r0, int c0, int e0, bool above) {
+      if (above) return;
+      for (int e = e0; e < ST * ST; e += ES) {
+        const int i = e >> 5, j = e & 31;
+        Yb[(long)(r0 + i) * P + c0 + j] = 0.5 * (X[(long)(r0 + i) * P + c0 + j] + (r0 + i == c0 + j ? 1.0 : 0.0));
+        if (r0 != c0) Yb[(long)(c0 + i) * P + r0 + j] = 0.5 * X[(long)(c0 + i) * P + r0 + j];
+      }
+    });
+    for (int p = slot; p < P; p += nact)             // the rows and columns before a: identity
+      for (int q = tid; q < (p < a ? P : a); q += 256) Yb[(long)p * P + q] = p == q ? 1.0 : 0.0;
+  }
+  if (slot == 0 && tid == 0) cb->state = done ? 2 : 3;   // every workgroup of the image has read it (behind a barrier, or gave up)
+  if (!alive && img_status && tid == 0) img_status[b] = 1;
+}
+
+// A workgroup that gave up has not stored its part, whatever slot 0 went on to report.
+__device__ __forceinline__ bool projector_valid(const SplitCtl* cb) { return cb->state == 2 && cb->bar.failed == 0; }
+
+// |trace(Pi) - r| tells whether the cut really has r eigenvalues above it.
+__device__ __forceinline__ double trace_minus(const double* Pi, int P, int r, double* red, int threads) {
+  double t = 0.0;
+  for (int p = threadIdx.x; p < P; p += threads) t += Pi[(long)p * P + p];
+  t = wave_sum(t);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+  __syncthreads();
+  t = 0.0;
+  for (int w = 0; w < threads / 64; ++w) t += red[w];
+  return fabs(t - (double)r);
+}
+
+// Residual check of the dominant subspace and, where it holds, the energies.  With Q the orthonormal rows of the block,
+// U = Pi Q and R = Pi Q G - H U (zero where the rows of U span an invariant subspace of G), rnorm holds the squared
+// lengths of R's rows, one partial sum per column tile.  Row p of the block carries eigenvalues of about H_pp, so
+// |R_p| <= tol max(H_pp, theta_r) is the relative residual of the eigenpairs in it.  ok[b] = pass_no, else 0.
+// c[b][i] = sum over the row tiles of cpart: the products of column i of U with column i of Q G.
+__global__ __launch_bounds__(1024) void split_finish_kernel(const double* __restrict__ H, const double* __restrict__ Pi,
+                                                            const double* __restrict__ rnorm, int rparts, const double* __restrict__ cpart,
+                                                            int cparts, int P, int n, int nP, int r, double tol,
+                                                            const SplitCtl* __restrict__ ctl, int* ok, int pass_no, float* __restrict__ c) {
+  __shared__ double red[16];
+  __shared__ int bad;
+  const int b = blockIdx.x;
+  if (pass_no > 1 && ok[b]) return;                  // passed an earlier check; its energies are in place
+  if (threadIdx.x == 0) bad = 0;
+  __syncthreads();
+  const bool valid = projector_valid(ctl + b);
+  const double theta = ctl[b].theta;
+  if (valid) {
+    const double off = trace_minus(Pi + (long)b * P * P, P, r, red, 1024);
+    if (threadIdx.x == 0 && !(off < 1e-3)) bad = 1;
+    for (int p = threadIdx.x; p < P; p += 1024) {
+      const double* rp = rnorm + ((long)b * P + p) * rparts;
+      double s = 0.0;
+      for (int t = 0; t < rparts; ++t) s += rp[t];
+      const double ref = fmax(H[((long)b * P + p) * P + p], theta);
+      if (!(sqrt(s) <= tol * ref)) bad = 1;          // also catches NaN
+    }
+  }
+  __syncthreads();
+  const bool good = valid && bad == 0;
+  if (threadIdx.x == 0) ok[b] = good ? pass_no : 0;
+  if (!good) return;
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    double s = 0.0;
+    for (int t = 0; t < cparts; ++t) s += cpart[((long)b * cparts + t) * nP + i];
+    c[(long)b * n + i] = (float)s;
+  }
+}
+
+// c[b][i] = (Pi G)_ii for a projector of the Gram matrix itself; done[b] = 1 where the projector is valid.  One wave per row.
+__global__ __launch_bounds__(256) void direct_energy_kernel(const double* __restrict__ G, const double* __restrict__ Pi, int n, int nP, int r,
+                                                            const SplitCtl* __restrict__ ctl, int* __restrict__ done, float* __restrict__ c) {
+  __shared__ double red[4];
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
+  const long base = (long)b * nP * nP;
+  bool good = projector_valid(ctl + b);              // uniform
+  if (good) good = trace_minus(Pi + base, nP, r, red, 256) < 1e-3;
+  if (blockIdx.x == 0 && threadIdx.x == 0) done[b] = good ? 1 : 0;
+  if (!good) return;
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= n) return;
+  double s = 0.0;
+  for (int j = lane; j < nP; j += 64) s = fma(G[base + (long)i * nP + j], Pi[base + (long)i * nP + j], s);
+  s = wave_sum(s);
+  if (lane == 0) c[(long)b * n + i] = (float)s;
+}
+
+}  // namespace
+
+size_t split_scratch_bytes(int B, int P) { return (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256 + 2 * (size_t)B * P * 8; }
+
+hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
+                                 const int* skip, int* img_status, hipStream_t st) {
+  if (P < 64 || P % 64 != 0 || P > 4096 || r < 1 || r >= P || (!ordered && P > SN)) return hipErrorInvalidValue;
+  SplitCtl* ctl = (SplitCtl*)scratch;
+  double* off = (double*)((char*)scratch + (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256);
+  double* link = off + (size_t)B * P;
+  static PerDeviceInt cache_narrow, cache_wide;
+  int cap_narrow = 0, cap_wide = 0;
+  hipError_t e = resident_workgroups(cache_narrow, sign_kernel<false>, 256, 0, &cap_narrow);
+  if (e != hipSuccess) return e;
+  if ((e = resident_workgroups(cache_wide, sign_kernel<true>, 256, 0, &cap_wide)) != hipSuccess) return e;
+  const long n32 = P / 32, n64 = P / 64;
+  const long t32 = n32 * (n32 + 1) / 2, t64 = n64 * (n64 + 1) / 2;
+  // small tiles while the device holds the workgroups of all images at once
+  const bool wide = B * t32 > 2 * cap_narrow;
+  const int capacity = wide ? cap_wide : cap_narrow;
+  // An image of more tiles than its workgroups deals them out.  Its workgroups are an eighth of those the device holds at
+  // most, so that the partial images of eight concurrent calls never hold all of it while they wait for the rest of theirs.
+  const long most = capacity / 8, tiles = wide ? t64 : t32;
+  const long W = tiles < most ? tiles : most;
+  if (W < 1) return hipErrorInvalidValue;
+  const long stride = (long)P * P;
+  hipLaunchKernelGGL(row_profile_kernel, dim3(P / 16, B), dim3(256), 0, st, H, P, stride, r, off, link, skip);
+  hipLaunchKernelGGL(split_kernel, dim3(B), dim3(256), 0, st, H, P, stride, r, (const double*)off, (const double*)link, ordered, ctl,
+                     skip);
+  hipLaunchKernelGGL(wide ? sign_kernel<true> : sign_kernel<false>, dim3((unsigned)(B * W)), dim3(256), 0, st, H, X0, Y, X1, P, (int)W, ctl,
+                     img_status, barrier_limit_ticks());
+  return hipGetLastError();
+}
+
+hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
+                               int P, int n, int nP, int r, double tol, const void* scratch, int* ok, int pass_no, float* c, hipStream_t st) {
+  hipLaunchKernelGGL(split_finish_kernel, dim3(B), dim3(1024), 0, st, H, Pi, rnorm, rparts, cpart, cparts, P, n, nP, r, tol,
+                     (const SplitCtl*)scratch, ok, pass_no, c);
+  return hipGetLastError();
+}
+
+bool split_direct(int nP) { return nP <= SN; }
+
+hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n, int nP, int r, const void* scratch, int* done, float* c,
+                                hipStream_t st) {
+  hipLaunchKernelGGL(direct_energy_kernel, dim3((n + 3) / 4, B), dim3(256), 0, st, G, Pi, n, nP, r, (const SplitCtl*)scratch, done, c);
+  return hipGetLastError();
+}
+
+}  // namespace covspec

@@ -4,8 +4,8 @@
 // Only the r dominant eigenpairs of G = Z_M^T Z_M enter the energies, so instead of
 // diagonalising all of G, a block of P > r vectors is iterated:
 //     Y <- G Y,  Y <- orthonormalise(Y)          (P = r + 64..127; error shrinks by lambda_{P+1}/lambda_r per step)
-// and the r dominant Ritz pairs of the P x P projection Q^T G Q are taken (Rayleigh-Ritz, solved by
-// the block Jacobi kernel).  All products are fp64 MFMA GEMMs; the cost scales with r, not with M.
+// and the P x P projection Q^T G Q is split at its r-th eigenvalue (split.hip): U = Pi Q^T spans the dominant subspace and
+// c_i = (U (Q^T G))_ii.  All products are fp64 MFMA GEMMs; the cost scales with r, not with M.
 //
 // Storage is transposed (vectors are rows, Yt is P x nP) so that every product is in the
 // K-contiguous "NT" form of the GEMM kernel: (G Y)^T = Yt G^T = Yt G.
@@ -13,8 +13,8 @@
 // panels, trailing update on the MFMA), Yt <- L^-1 Yt (blocked forward substitution).
 // The start block is Omega G with a fixed +-1 pattern Omega, so exact duplicate tokens (equal rows of
 // G) cannot make it rank deficient.
-// After the Ritz step the residuals |G u - theta u| of the r dominant Ritz pairs are checked; images
-// that fail (slow decay, P too small) fall back to the full block Jacobi solve of G.
+// The residual of the dominant subspace, Pi Q^T G - H U, is checked; images that fail (slow decay, P too small, no gap
+// at the cut) take four more steps and, if they fail again, the full block Jacobi solve of G.
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"
@@ -25,19 +25,14 @@ namespace {
 
 constexpr int NB = 64;        // panel width of Cholesky / substitution
 constexpr int NBP = NB + 1;   // LDS pitch
-// Relative residual |G u - theta u| / theta accepted for the r dominant Ritz pairs.  The Jacobi solve of the
-// projected problem stops at an admixture weight that leaves the energies good to ~1e-8, and a residual of
-// 1e-9 perturbs an energy by at most 1e-9 / (relative gap at r) relative, the same order; converged blocks
-// sit at 1e-11..1e-13, unconverged ones orders above.
+// Relative residual accepted for the dominant subspace, row by row (split_finish_kernel).  It perturbs an energy by at
+// most 1e-9 / (relative gap at r) relative; converged blocks sit at 1e-11..1e-13, unconverged ones orders above.
 constexpr double kRitzTol = 1e-9;
 // see the end of chol_kernel
 constexpr double kPivotNear = 0.25;   // smallest scaled pivot above this: rows nearly orthogonal, blocks of three steps
 constexpr double kPivotFar = 1e-3;    // above this: blocks of two steps
 constexpr double kGradeDigits = 14.0; // decimal digits a block's grading (lambda_1 / lambda_P)^steps may use up
 constexpr int kMaxBlockSteps = 3;
-// Couplings between rows of the projected matrix below this weight are left out of the first, banded sweeps of the
-// Ritz solve (its last sweeps visit every pair).
-constexpr double kBandTol = 1e-9;
 constexpr double kPivotOnePass = 0.01; // final step: above this one Cholesky-QR pass leaves the rows orthonormal to ~1e-14
 constexpr size_t kCholLdsFixed = (size_t)(2 * NB * NBP + NB) * sizeof(double);   // plus P doubles: the diagonal of S
 
@@ -376,55 +371,6 @@ __global__ void mask_passed_kernel(const int* __restrict__ ok, int* __restrict__
   last_orth[b] = -1;
 }
 
-// Residual check of the r dominant Ritz pairs.  Ut rows are theta_k u_k^T, Rt = Ut G.  ok[b] = 1 (2 in the second pass) when
-// |Rt_k - theta_k Ut_k| <= tol * theta_k^2 for each of them (theta_k = |Ut_k|, so this is the relative
-// residual |G u - theta u| / theta).
-__global__ __launch_bounds__(1024) void ritz_check_kernel(const double* __restrict__ Ut, const double* __restrict__ Rt,
-                                                           const double* __restrict__ lam, int P, int n, int nP, int r,
-                                                           double tol, int* ok, int only_failed) {
-  __shared__ double slam[4096];
-  __shared__ unsigned char sel[4096];
-  __shared__ int bad;
-  const int b = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (only_failed && ok[b]) return;      // passed an earlier check; its rows were not touched since (uniform)
-  const double* lb = lam + (long)b * P;
-  for (int k = threadIdx.x; k < P; k += 1024) slam[k] = lb[k];
-  if (threadIdx.x == 0) bad = 0;
-  __syncthreads();
-  for (int k = threadIdx.x; k < P; k += 1024) {
-    const double v = slam[k];
-    int rank = 0;
-    for (int j = 0; j < P; ++j) { const double u = slam[j]; rank += (u > v || (u == v && j < k)) ? 1 : 0; }
-    sel[k] = rank < r;
-  }
-  __syncthreads();
-  // one wave per row, four pairs of loads in flight per lane
-  for (int k = w; k < P; k += 16) {
-    if (!sel[k]) continue;
-    const double th = slam[k];
-    const double* u = Ut + ((long)b * P + k) * nP;
-    const double* rr = Rt + ((long)b * P + k) * nP;
-    double s0 = 0.0, s1 = 0.0;
-    int j = lane;
-    for (; j + 192 < n; j += 256) {
-      double a[4], c[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { a[q] = rr[j + 64 * q]; c[q] = u[j + 64 * q]; }
-#pragma unroll
-      for (int q = 0; q < 4; q += 2) {
-        const double d0 = a[q] - th * c[q], d1 = a[q + 1] - th * c[q + 1];
-        s0 = fma(d0, d0, s0);
-        s1 = fma(d1, d1, s1);
-      }
-    }
-    for (; j < n; j += 64) { const double d = rr[j] - th * u[j]; s0 = fma(d, d, s0); }
-    const double s = wave_sum(s0 + s1);
-    if (lane == 0 && !(sqrt(s) <= tol * th * th)) bad = 1;   // also catches NaN
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) ok[b] = bad ? 0 : (only_failed ? 2 : 1);    // 1: first pass, 2: second pass
-}
-
 }  // namespace
 
 int subspace_block(int n, int r) {
@@ -436,44 +382,53 @@ int subspace_block(int n, int r) {
 }
 
 size_t subspace_workspace_bytes(int B, int n, int nP, int P) {
-  if (P <= 0) return 0;
+  if (P <= 0) return split_direct(nP) ? 3 * (size_t)B * nP * nP * 8 + split_scratch_bytes(B, nP) + 256 : 0;
   const size_t blk = (size_t)B * P * nP * 8;
-  return 2 * blk + (size_t)P * nP * 8 + 2 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + (size_t)B * P * 8 + 1024 + (size_t)B * 4 +
-         (size_t)B * 4 + (size_t)B * 4 /* band limits */ + 256 + (size_t)B * nP * nP * 8 /* G^2 */ + 256;
+  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 + (size_t)B * 4 +
+         (size_t)B * 4 + 256 + (size_t)B * nP * nP * 8 /* G^2 */ + 256;
 }
 
-// Runs the iteration on G[b] (n x n, pitch nP, untouched).  On return, for images with ok[b] = 1, rows
-// k of (*ut)[b] (P rows, pitch nP, inside ws) are theta_k u_k^T with the r longest rows converged.
 // The first pass makes iters steps of the iteration as iters / 3 products with G^2 followed by iters / 3 with G.
-// Launches of the probed shape: start block, the products of the first pass, residuals.
-int subspace_product_launches(int iters) { return 2 * (iters / 3) + 2; }
+// Launches of the probed shape: start block and the products of the first pass.
+int subspace_product_launches(int iters) { return 2 * (iters / 3) + 1; }
 
-hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, int iters, int more_iters, void* ws_, void* jacobi_ctl,
-                                 double* jacobi_len2, int* ok, const double** ut, int* img_status, hipEvent_t probe_begin,
-                                 hipEvent_t probe_end, hipStream_t st) {
+hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, int iters, int more_iters, void* ws_, int* ok,
+                                 float* c, int* img_status, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t st) {
+  if (P == 0) {
+    // the whole matrix is the window
+    if (!split_direct(nP)) return hipErrorInvalidValue;
+    const size_t sq = (size_t)B * nP * nP;
+    double* X0 = (double*)ws_;
+    double *Y = X0 + sq, *X1 = Y + sq;
+    void* scratch = (void*)(((uintptr_t)(X1 + sq) + 255) & ~(uintptr_t)255);
+    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, img_status, st);
+    return ed != hipSuccess ? ed : launch_direct_energy(G, Y, B, n, nP, r, scratch, ok, c, st);
+  }
   hipError_t e0;
   if (P <= 0 || P % NB != 0 || P > n || P > 4096 || nP % NB != 0) return hipErrorInvalidValue;
-  // every pass makes an even number of products, so that the rows of the images that passed the first check are
-  // in the block that is returned (the two blocks swap roles per product)
-  if (iters < 3 || iters % 3 != 0 || more_iters < 2 || (more_iters & 1)) return hipErrorInvalidValue;
+  if (iters < 3 || iters % 3 != 0 || more_iters < 1) return hipErrorInvalidValue;
   {
     static PerDeviceInt raised;
     if ((e0 = ensure_dynamic_lds(raised, (const void*)chol_kernel, kCholLdsFixed + 4096 * sizeof(double))) != hipSuccess) return e0;
   }
   char* ws = (char*)ws_;
   const size_t blk = (size_t)B * P * nP * 8;
-  double* Yt = (double*)ws;                 // after the call: Ut
+  double* Yt = (double*)ws;
   double* Zt = (double*)(ws + blk);
   double* Om = (double*)(ws + 2 * blk);
   double* S = (double*)(ws + 2 * blk + (size_t)P * nP * 8);
   double* H = S + (size_t)B * P * P;
   double* D = H + (size_t)B * P * P;
-  double* lam = D + (size_t)B * P * NB;
-  int* skip_until = (int*)(((uintptr_t)(lam + (size_t)B * P) + 255) & ~(uintptr_t)255);   // [B] next step that orthonormalises
+  double* Pi = D + (size_t)B * P * NB;                                                      // [B][P][P] the projector
+  void* scratch = (void*)(((uintptr_t)(Pi + (size_t)B * P * P) + 255) & ~(uintptr_t)255);
+  int* skip_until = (int*)((char*)scratch + split_scratch_bytes(B, P));                     // [B] next step that orthonormalises
   int* last_orth = skip_until + B;                                                          // [B] step of the last one
-  int* band = last_orth + B;                                                                // [B] see launch_band_limit
-  double* G2 = (double*)(((uintptr_t)(band + B) + 255) & ~(uintptr_t)255);                  // [B][nP][nP] G squared
-  const int nblk = P / NB;
+  double* G2 = (double*)(((uintptr_t)(last_orth + B) + 255) & ~(uintptr_t)255);             // [B][nP][nP] G squared
+  // after the products with G^2 its place is free: one of the iterates of the split (P <= nP), then U, its partial energies
+  // and the partial row lengths of the residual: nP (P + P / 64 + P / 64) <= nP^2 doubles per image, as P <= 3/4 n
+  double* U = G2;
+  double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 64][nP]
+  double* rnorm = cpart + (size_t)B * (P / NB) * nP;                                        // [B][P][nP / 64]
   hipError_t e;
 
   // Second pass: images that passed the first check take no further part; the kernels see them as skip_until ==
@@ -511,14 +466,14 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   double* cur = Yt;
   double* oth = Zt;
   // `steps` products from the block in `cur` (each preceded by an orthonormalisation where the image's schedule
-  // asks for one), then Rayleigh-Ritz and the residual check.  steps is even, so `cur` is the same buffer after it.
+  // asks for one), then the split, the residual check and the energies.
   // The first n_sq products multiply by G^2: two steps of the iteration at the cost of one (the same subspace as
   // two products with G and an orthonormalisation between them).  G^2 as formed is off by about 1e-16 |G|^2, which
   // is a fixed perturbation of the operator of relative size 1e-16 (lambda_1 / lambda_r)^2 at the r-th eigenvalue
   // (1e-8 for a spectrum that falls by 1e4 down to r); the products with G itself that follow contract that error
   // like any other, and a CPU model of the workloads' matrices needs three to four of them.  The last product
   // feeds the Rayleigh-Ritz step and is with G in any case.
-  auto pass = [&](int n_sq, int n_plain) -> hipError_t {
+  auto pass = [&](int n_sq, int n_plain, int pass_no) -> hipError_t {
     const int steps = n_sq + n_plain;
     for (int it = 0; it < steps; ++it) {
       // the block of step 0 is not (orthonormal) x G, so its factor says nothing about the next step (the kernel
@@ -529,7 +484,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       if ((e = gemm_yt_g(cur, oth, w == 2 ? G2 : G)) != hipSuccess) return e;   // last: oth = Q^T G
       double* t = cur; cur = oth; oth = t;
     }
-    // now oth = Q^T (orthonormal rows), cur = Q^T G.  Rayleigh-Ritz: H = (Q^T G) Q
+    // now oth = Q^T (orthonormal rows), cur = Q^T G.  H = (Q^T G) Q
     {
       GemmArgs g;
       g.A = cur; g.B = oth; g.C = H; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
@@ -540,33 +495,24 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       mask(g);
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    // The rows of the block are ordered like the eigenvalues, so H only couples neighbouring rows: measure how far
-    // (on H^2, the Gram matrix of the rows the solve rotates; S is free by now) and let the solve leave the rest out
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, G2, scratch, masked ? (const int*)ok : nullptr, img_status, st)) != hipSuccess) return e;
+    // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;
-      g.A = H; g.B = H; g.C = S; g.M = P; g.N = P; g.K = P; g.lda = P; g.ldb = P; g.ldc = P;
-      g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * P; g.strideC = (long)P * P;
-      g.epilogue = EPI_STORE_F64;
-      g.lower_only = true;
-      mask(g);
-      if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
-      if ((e = launch_band_limit(S, B, P, kBandTol, band, masked ? (const int*)ok : nullptr, st)) != hipSuccess) return e;
-    }
-    if ((e = launch_jacobi_eigen(H, B, P, P, r, jacobi_ctl, jacobi_len2, masked ? (const int*)ok : nullptr, band, img_status, st)) != hipSuccess) return e;
-    // rows of H are now theta_k w_k^T; Ut = H Q^T has rows theta_k u_k^T
-    {
-      GemmArgs g;
-      g.A = H; g.B = oth; g.C = cur; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP; g.transB = true;
+      g.A = Pi; g.B = oth; g.C = U; g.D = cur; g.dots = cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP; g.transB = true;
       g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * nP;
-      g.epilogue = EPI_STORE_F64;
       mask(g);
-      if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
+      if ((e = launch_gemm64_store_dot(g, st)) != hipSuccess) return e;
     }
-    // residuals: Rt = Ut G
-    if ((e = gemm_yt_g(cur, oth, G)) != hipSuccess) return e;
-    if ((e = launch_row_lengths(cur, B, P, nP, (long)P * nP, lam, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(ritz_check_kernel, dim3(B), dim3(1024), 0, st, cur, oth, lam, P, n, nP, r, kRitzTol, ok, masked ? 1 : 0);
-    return hipGetLastError();
+    // row lengths of the residual Pi Q^T G - H U
+    {
+      GemmArgs g;
+      g.A = Pi; g.B = cur; g.A2 = H; g.B2 = U; g.C = rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / NB; g.transB = true;
+      g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * (nP / NB);
+      mask(g);
+      if ((e = launch_gemm64_rownorm_dual(g, st)) != hipSuccess) return e;
+    }
+    return launch_split_finish(H, Pi, rnorm, nP / NB, cpart, P / NB, B, P, n, nP, r, kRitzTol, scratch, ok, pass_no, c, st);
   };
 
   // G^2 (symmetric: tiles on and below the diagonal, mirrored)
@@ -591,14 +537,12 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   }
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
   if ((e = launch_fill_int(skip_until, 2 * B, -1, st)) != hipSuccess) return e;
-  if ((e = pass(iters / 3, iters / 3)) != hipSuccess) return e;
-  // images whose Ritz pairs are not there yet (slower spectral decay than the first pass allows for) go on from
-  // their Ritz vectors for a few more steps; for the others every kernel of this pass returns at once
+  if ((e = pass(iters / 3, iters / 3, 1)) != hipSuccess) return e;
+  // images whose subspace is not there yet (slower spectral decay than the first pass allows for) go on from Q^T G
+  // for a few more steps; for the others every kernel of this pass returns at once
   masked = true;
   hipLaunchKernelGGL(mask_passed_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, (const int*)ok, skip_until, last_orth, B);
-  if ((e = pass(0, more_iters)) != hipSuccess) return e;
-  *ut = cur;
-  return hipGetLastError();
+  return pass(0, more_iters, 2);
 }
 
 }  // namespace covspec

@@ -1,0 +1,66 @@
+"""The spectral split behind the energies (split.hip): energies against the fp64 oracle at the edges of its ranges."""
+import numpy as np
+import pytest
+
+import covspec_inputs as I
+from oracle import covspec_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def C():
+    import paper_2605_02218_amd as C
+    C.load_library()
+    return C
+
+
+# batch, tokens, width, rank, decay of the singular values per index; what is at its edge
+CASES = {
+    "smallest": (1, 2, 16, 1, 0.3),
+    "one-tile": (3, 64, 96, 63, 0.05),            # direct, every row but one wanted
+    "direct-padded": (2, 65, 96, 20, 0.05),       # direct on a padded order of 128
+    "direct-largest": (1, 128, 160, 127, 0.05),
+    "direct-rank1": (2, 128, 160, 1, 0.05),
+    "full-solve": (1, 129, 160, 64, 0.05),        # too large for a direct split, block would be most of the matrix
+    "smallest-block": (1, 171, 192, 3, 0.05),     # block of 128 of 171: the whole block is the window
+    "window-inside": (2, 400, 420, 180, 0.04),    # block of 256, window in its middle
+    "leading-rows": (1, 600, 640, 250, 0.06),     # leading rows that no longer couple are left out of the iteration
+    "eleven-images": (11, 171, 192, 40, 0.05),
+    "wide-tiles": (110, 128, 160, 30, 0.05),      # more tiles than the device holds workgroups
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_energies_match_the_oracle(C, name):
+    import torch
+    B, n, d, r, decay = CASES[name]
+    sigma = np.exp(-decay * np.arange(min(n, d)))
+    X = np.stack([I.make_spectrum_tokens(n, d, sigma, seed=b, dtype=I.FP32) for b in range(B)])
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    k = max(1, n // 3)
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=k, preselect_m=n, rank_r=r)
+    out = C.select(p, torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda())
+    c, idx = out["c"].cpu().numpy().astype(np.float64), out["idx"].cpu().numpy()
+    op = O.Params(preselect_m=n, rank_r=r, keep_k=k)
+    for b in range(B) if B <= 16 else (0, 7, 8, 63, B - 1):
+        ref = O.select(X[b].astype(np.float64), sf[b], op)
+        # c is rounded to fp32 (6e-8); a residual of 1e-9 enters an energy at most as 1e-9 / relative gap (>= 0.07 here),
+        # twice; energies far below the largest carry its rounding
+        err = np.abs(c[b] - ref["c"]) / np.maximum(ref["c"], 1e-6 * ref["c"].max())
+        assert err.max() < 2e-7, "%s image %d: %g" % (name, b, err.max())
+        np.testing.assert_array_equal(idx[b], ref["idx"])
+
+
+def test_equal_eigenvalues_at_the_cut_still_give_a_result(C):
+    """Orthogonal tokens of equal length: no rank-r subspace is better than another, the split has no gap to use and the
+    full solve answers.  Every energy lies between 0 and the squared length, and they sum to r of it."""
+    import torch
+    for n, d in ((96, 128), (256, 256)):
+        X = torch.zeros(1, n, d)
+        X[0, torch.arange(n), torch.arange(n)] = 2.0
+        p = C.Params(batch=1, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=10, preselect_m=n, rank_r=20)
+        out = C.select(p, X.cuda(), torch.rand(1, n, generator=torch.Generator().manual_seed(0)).cuda())
+        c = out["c"].cpu().double()
+        assert c.min() > -1e-6 and c.max() < 4.0 + 1e-5 and abs(c.sum() - 80.0) < 1e-4, (n, c.sum())
+        assert len(set(out["idx"][0].tolist())) == 10
