@@ -46,126 +46,152 @@ __global__ void omega_kernel(double* __restrict__ om, int P, int n, int nP) {
 }
 
 // value of `v` in lane `l` (compile-time lane), uniform across the wave
-template <typename = void>
 __device__ __forceinline__ double lane_value(double v, int l) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
   return __hiloint2double(hi, lo);
 }
 
-// Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle) in one wave: lane i holds row i.  The factor
-// goes to `fac` (lower triangle, zeros above).  Pivots are floored at `floor_`.  Column k: pivot from lane k, scaled
-// column l_ik = a_ik / sqrt(a_kk) (lane i), then a_ij -= l_ik l_jk.  The l_jk of the other lanes come through
-// `col` (64 doubles of LDS): every lane posts its l_ik and reads the column back as broadcast loads, two values
-// per load (a wave's LDS accesses complete in order, so no barrier is needed; reading them lane by lane with
-// v_readlane took two such instructions and their wait states per value and ran at twice the time).  Not inlined,
-// so that the 64 row registers do not compete with the caller's.
-__device__ __noinline__ void potrf_wave(const double* a, double* fac, double* col, double floor_) {
-  const int lane = threadIdx.x & 63;
-  double row[NB];
+// Everything a wave has written to LDS before is read back by it after (its LDS accesses complete in order; this only
+// keeps the compiler from moving one across the other).
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle: a = L L^T) and inverts the factor, in one wave: inv(L) goes
+// to `inv` (its tiles above the diagonal are zero already), the diagonal of L to dl.  Pivots are floored at `floor_`.
+// By 16 x 16 tiles.  A diagonal tile is eliminated together with a unit matrix, lane = column (lanes 0..15 the tile,
+// 16..31 the unit matrix): step k subtracts a_ik / a_kk times row k from row i, the a_ik being the scalars of lane k, and
+// leaves the inverse of the unit-diagonal factor in the right half, no exchange through LDS and no column to wait for.  The
+// tiles below and the rest of the block follow on the MFMA, then the inverse tile by tile, inv_ts = -inv_tt sum L_tu inv_us:
+// the sum comes out of the MFMA in the layout its B operand wants.  A column by column factorisation by one wave with the
+// inversion after it by the workgroup took 23 + 14 us of a panel, this takes 11.
+__device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* dl, double floor_) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4, c = lane & 31;
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    double x[16];
 #pragma unroll
-  for (int k = 0; k < NB; ++k) row[k] = a[lane * NBP + k];
-#pragma unroll
-  for (int k = 0; k < NB; ++k) {
-    const double akk = fmax(lane_value(row[k], k), floor_);
-    double rs = __builtin_amdgcn_rsq(akk);
-    rs = rs * fma(-0.5 * akk, rs * rs, 1.5);
-    rs = rs * fma(-0.5 * akk, rs * rs, 1.5);
-    const double lk = (lane == k) ? akk * rs : row[k] * rs;
-    row[k] = lk;
-    if (k + 1 < NB) {
-      col[lane] = lk;
-#pragma unroll
-      for (int j = k + 1; j < NB; ++j) row[j] = fma(-lk, col[j], row[j]);
+    for (int i = 0; i < 16; ++i) {
+      const int hi = i > i16 ? i : i16, lo = i > i16 ? i16 : i;
+      const double v = a[(16 * s + hi) * NBP + 16 * s + lo];
+      x[i] = c < 16 ? v : (c - 16 == i ? 1.0 : 0.0);
     }
-  }
+    double mine = 0.0;
 #pragma unroll
-  for (int k = 0; k < NB; ++k) fac[lane * NBP + k] = (k <= lane) ? row[k] : 0.0;
+    for (int k = 0; k < 16; ++k) {
+      const double piv = fmax(lane_value(x[k], k), floor_);
+      double rp = __builtin_amdgcn_rcp(piv);
+      rp = fma(rp, fma(-piv, rp, 1.0), rp);
+      rp = fma(rp, fma(-piv, rp, 1.0), rp);
+      const double row = x[k] * rp;
+#pragma unroll
+      for (int i = k + 1; i < 16; ++i) x[i] = fma(-lane_value(x[i], k), row, x[i]);
+      double rs = __builtin_amdgcn_rsq(piv);
+      rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
+      rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
+      x[k] *= rs;                                  // lanes 16..31: row k of inv(L_ss)
+      if (lane == k) mine = piv * rs;
+    }
+    if (lane < 16) dl[16 * s + lane] = mine;
+    if (lane >= 16 && lane < 32) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) inv[(16 * s + k) * NBP + 16 * s + i16] = i16 <= k ? x[k] : 0.0;
+    }
+    wave_lds_fence();
+    double wf[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) wf[j] = inv[(16 * s + i16) * NBP + 16 * s + 4 * j + kq];
+#pragma unroll 1
+    for (int t = s + 1; t < 4; ++t) {              // L_ts = A_ts inv(L_ss)^T
+      f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * s + 4 * j + kq], wf[j], o, 0, 0, 0);
+      wave_lds_fence();
+#pragma unroll
+      for (int v = 0; v < 4; ++v) a[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
+    }
+    wave_lds_fence();
+#pragma unroll 1
+    for (int t = s + 1; t < 4; ++t)                // A_tu -= L_ts L_us^T
+#pragma unroll 1
+      for (int u = s + 1; u <= t; ++u) {
+        f64x4_t o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = a[(16 * t + 4 * v + kq) * NBP + 16 * u + i16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          o = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[(16 * t + i16) * NBP + 16 * s + 4 * j + kq], a[(16 * u + i16) * NBP + 16 * s + 4 * j + kq], o, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a[(16 * t + 4 * v + kq) * NBP + 16 * u + i16] = o[v];
+      }
+    wave_lds_fence();
+  }
+#pragma unroll 1
+  for (int d = 1; d < 4; ++d) {
+#pragma unroll 1
+    for (int t = d; t < 4; ++t) {
+      const int s = t - d;
+      f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0}, o = sum;
+#pragma unroll 1
+      for (int u = s; u < t; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          sum = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * u + 4 * j + kq], inv[(16 * u + 4 * j + kq) * NBP + 16 * s + i16], sum, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(-inv[(16 * t + i16) * NBP + 16 * t + 4 * j + kq], sum[j], o, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) inv[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
+    }
+    wave_lds_fence();
+  }
 }
 
 // Cholesky factorisation S[b] = L L^T (P x P, pitch P, P % 64 == 0; only the lower triangle is read), one
 // 512-thread workgroup per image, right-looking over 64-wide panels:
-//   diagonal block: factored in LDS, then inverted in LDS; the inverse goes to Dinv[b][J] (64 x 64);
+//   diagonal block: factored and inverted by one wave (factor_invert_wave); the inverse goes to Dinv[b][J] (64 x 64);
 //   panel below:    X = S[I,J] inv(L_JJ)^T on the MFMA, in place (these blocks are L[I,J]);
-//   trailing part:  S[I,I'] -= X_I X_I'^T for I' <= I on the MFMA, 16 x 64 units dealt round-robin to the waves.
+//   next diagonal block: updated by all waves, into LDS; then one wave factors it while the others do the
+//   trailing part:  S[I,I'] -= X_I X_I'^T for I' <= I on the MFMA, 16 x 32 units.
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
 // Pivots are floored at 1e-28 * trace(first block) so that a numerically rank-deficient block cannot
 // produce NaNs (the residual check afterwards decides whether the result is usable).
+// Bound by the chain of panels (and, from order 384 on, by one compute unit's MFMA rate in the trailing part).  One image of
+// order 192 168 -> 76 us, eight of 384 448 -> 220, sixty-four of 256 257 -> 115 (before: the block factored column by column,
+// its inverse formed by the workgroup, the next diagonal block updated by the wave that factors it, spilled registers).
 // Dynamic LDS: 2 * 64 * 65 + 64 + P doubles.
 __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, int* skip_until, int* last_orth, int step,
                                                    int last_free_step, int next_weight) {
   extern __shared__ double lds[];
-  double* a = lds;                  // [64][65] diagonal block, later the inverse of its factor
-  double* fac = lds + NB * NBP;     // [64][65] the factor (lower triangle) and scratch (upper triangle)
-  double* col = lds + 2 * NB * NBP;     // [64] column exchange of the one-wave factorisation
-  double* diag0 = col + NB;             // [P] the diagonal of S before any update: squared row lengths
+  double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert_wave (tiles below the diagonal)
+  double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor
+  double* dl = lds + 2 * NB * NBP;  // [64] diagonal of the factor
+  double* diag0 = dl + NB;          // [P] the diagonal of S before any update: squared row lengths
   const int b = blockIdx.x;
   if (skip_until && skip_until[b] > step) return;   // this image does not orthonormalise at this step
   double* Sb = S + (long)b * P * P;
-  double dmin = 1e300, dmax = 0.0, pmin = 1.0;   // extremes of the factor's diagonal, smallest scaled pivot (thread 0)
+  double dmin = 1e300, dmax = 0.0, pmin = 1.0;   // extremes of the factor's diagonal, smallest scaled pivot (wave 0, by lane)
   const int nblk = P / NB;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
-  double floor_ = 0.0;
   for (int k = tid; k < P; k += 512) diag0[k] = Sb[(long)k * P + k];
-
-  // The diagonal block of the first panel: factored by ONE wave, row i of the block in the registers of lane i (no
-  // barrier and no LDS traffic per column; with the whole workgroup a column cost a barrier and a round trip through
-  // LDS, and the factorisation is a chain of 64 dependent columns).  Column k: pivot from lane k, scaled column
-  // l_ik = a_ik / sqrt(a_kk), then a_ij -= l_ik l_jk with l_jk read from lane j.  Lanes also carry the (unused)
-  // entries above the diagonal; they stay finite and never feed an entry below it.
   for (int e = tid; e < NB * NB; e += 512) {
     const int i = e >> 6, j = e & 63;
     a[i * NBP + j] = (j <= i) ? Sb[(long)i * P + j] : 0.0;
+    inv[i * NBP + j] = 0.0;
   }
   __syncthreads();
-  {
-    double tr = 0.0;
-    for (int i = 0; i < NB; ++i) tr += a[i * NBP + i];   // same value in every thread
-    floor_ = 1e-300 + 1e-28 * tr;
-  }
-  if (w == 0) potrf_wave(a, fac, col, floor_);
+  double floor_ = 0.0;
+  for (int i = 0; i < NB; ++i) floor_ += diag0[i];       // the same value in every thread
+  floor_ = 1e-300 + 1e-28 * floor_;
+  if (w == 0) factor_invert_wave(a, inv, dl, floor_);
   __syncthreads();
 
   for (int J = 0; J < nblk; ++J) {
     const int j0 = J * NB;
-    // here `fac` holds the factor of diagonal block J (for J > 0 wave 0 formed it during the trailing update of panel J - 1)
-    if (tid == 0)
-      for (int k = 0; k < NB; ++k) {
-        const double d = fac[k * NBP + k];
-        dmin = fmin(dmin, d);
-        dmax = fmax(dmax, d);
-        const double s0 = diag0[j0 + k];
-        if (s0 > 0.0) pmin = fmin(pmin, d * d / s0);
-      }
-    // ---- inverse of the factor into `a`, by doubling: with L = [A 0; C D], inv(L) = [inv(A) 0; -inv(D) C inv(A) inv(D)].
-    //      Level s joins the inverses of the s x s diagonal blocks pairwise; the intermediate C inv(A) is parked,
-    //      transposed, in the unused upper triangle of `fac`.
-    for (int e = tid; e < NB * NB; e += 512) {
-      const int i = e >> 6, j = e & 63;
-      a[i * NBP + j] = (i == j) ? 1.0 / fac[i * NBP + i] : 0.0;
+    // here `inv` holds the inverse of the factor of diagonal block J
+    if (w == 0) {
+      const double d = dl[lane], s0 = diag0[j0 + lane];
+      dmin = fmin(dmin, d);
+      dmax = fmax(dmax, d);
+      if (s0 > 0.0) pmin = fmin(pmin, d * d / s0);
     }
-    __syncthreads();
-    for (int s_ = 1, ls = 0; s_ < NB; s_ <<= 1, ++ls) {
-      // 32 * s_ elements per level: element e -> block pair m, row i, column j
-      for (int e = tid; e < 32 * s_; e += 512) {
-        const int m = e >> (2 * ls), i = (e >> ls) & (s_ - 1), j = e & (s_ - 1);
-        const int base = 2 * s_ * m;
-        double t1 = 0.0;   // (C inv(A))[i][j], inv(A) lower triangular
-#pragma unroll 8
-        for (int t = j; t < s_; ++t) t1 = fma(fac[(base + s_ + i) * NBP + base + t], a[(base + t) * NBP + base + j], t1);
-        fac[(base + j) * NBP + base + s_ + i] = t1;
-      }
-      __syncthreads();
-      for (int e = tid; e < 32 * s_; e += 512) {
-        const int m = e >> (2 * ls), i = (e >> ls) & (s_ - 1), j = e & (s_ - 1);
-        const int base = 2 * s_ * m;
-        double x = 0.0;    // (inv(D) T1)[i][j], inv(D) lower triangular
-#pragma unroll 8
-        for (int u = 0; u <= i; ++u) x = fma(a[(base + s_ + i) * NBP + base + s_ + u], fac[(base + j) * NBP + base + s_ + u], x);
-        a[(base + s_ + i) * NBP + base + j] = -x;
-      }
-      __syncthreads();
-    }
-    double* inv = a;
     {
       double* Db = Dinv + ((long)b * nblk + J) * NB * NB;
       // stored with the columns of every group of 16 permuted, 16x + 4v + q -> 16x + 4q + v: trsm_kernel's lane
@@ -175,7 +201,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
         Db[(e & ~63) | (c & 48) | ((c & 3) << 2) | ((c >> 2) & 3)] = inv[(e >> 6) * NBP + c];
       }
     }
-    // ---- panel: X = S[I,J] inv^T, 16-row tiles dealt to the waves
+    // ---- panel: X = S[I,J] inv^T, 16-row tiles dealt to the waves; inv is lower triangular
     const int below = P - j0 - NB;
     for (int t = w; t < below / 16; t += 8) {
       const long rb = j0 + NB + 16 * t;
@@ -186,7 +212,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
       for (int y = 0; y < 4; ++y) {
         out[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c <= y; ++c)
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj)
             out[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[c][jj], inv[(16 * y + i16) * NBP + 16 * c + 4 * kq + jj], out[y], 0, 0, 0);
@@ -196,79 +222,91 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
 #pragma unroll
         for (int v = 0; v < 4; ++v) Sb[(rb + 4 * v + kq) * P + j0 + 16 * y + i16] = out[y][v];
     }
-    __syncthreads();     // the panel is complete in global memory and `a`, `fac` are free
+    __syncthreads();     // the panel is complete in global memory and `a`, `inv` are free
     if (below == 0) break;
-    // ---- trailing update, unit = 16 rows of block I x the 64 columns of block I' <= I.  The four units of the
-    //      next diagonal block go to wave 0, which writes them to LDS instead of global memory and factors the
-    //      block at once (look-ahead: the chain of 64 dependent columns runs beside the rest of the update instead
-    //      of after it); the other waves share the remaining units in contiguous ranges, so that consecutive units
-    //      mostly share I' and its fragments stay in registers.  All loads of a unit are issued before its MFMAs.
-    {
+    // ---- the next diagonal block, into LDS: its ten 16 x 16 tiles on and below the diagonal
+    for (int t = w; t < 10; t += 8) {
+      const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
+      const long ra = j0 + NB + 16 * x, rc = j0 + NB + 16 * y;
+      f64x4_t fa[4], fb[4], cc, acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        fa[c] = *(const f64x4_t*)(Sb + (ra + i16) * P + j0 + 16 * c + 4 * kq);
+        fb[c] = *(const f64x4_t*)(Sb + (rc + i16) * P + j0 + 16 * c + 4 * kq);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cc[v] = Sb[(ra + 4 * v + kq) * P + rc + i16];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[c][jj], fb[c][jj], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) a[(16 * x + 4 * v + kq) * NBP + 16 * y + i16] = cc[v] - acc[v];
+    }
+    __syncthreads();
+    // ---- trailing update by waves 1..7, unit = 16 rows of block I x 32 columns of block I' <= I, in contiguous
+    //      ranges, so that consecutive units mostly share the columns and their fragments stay in registers (64 columns
+    //      would not fit the registers).  Wave 0 factors the next diagonal block meanwhile.
+    if (w == 0) {
+      factor_invert_wave(a, inv, dl, floor_);
+    } else {
       const int nb = below / NB;
-      const int units = 2 * nb * (nb + 1);            // 4 * nb (nb + 1) / 2; units 0..3 are the next diagonal block
-      int u0, u1;
-      if (w == 0) { u0 = 0; u1 = 4; }
-      else { u0 = 4 + (int)((long)(units - 4) * (w - 1) / 7); u1 = 4 + (int)((long)(units - 4) * w / 7); }
-      // unit u -> pair index u / 4 -> (I, I2) with I (I + 1) / 2 + I2 = pair index
+      const int units = 4 * nb * (nb + 1);            // 8 * nb (nb + 1) / 2; units 0..7 are the next diagonal block
+      const int u0 = 8 + (int)((long)(units - 8) * (w - 1) / 7), u1 = 8 + (int)((long)(units - 8) * w / 7);
+      // unit u -> pair index u / 8 -> (I, I2) with I (I + 1) / 2 + I2 = pair index
       int I = 0, I2 = 0;
       {
-        int pi = u0 >> 2;
+        int pi = u0 >> 3;
         while ((I + 1) * (I + 2) / 2 <= pi) ++I;
         I2 = pi - I * (I + 1) / 2;
       }
-      f64x4_t fb[4][4];
+      f64x4_t fb[2][4];
       int have = -1;
+#pragma unroll 1
       for (int u = u0; u < u1; ++u) {
-        const int q = u & 3;
+        const int q = u & 3, h = (u >> 2) & 1;
         const long ra = j0 + NB + (long)I * NB + 16 * q;
-        const long rc = j0 + NB + (long)I2 * NB;
-        f64x4_t fa[4], cc[4];
+        const long rc = j0 + NB + (long)I2 * NB + 32 * h;
+        const int ylim = I == I2 ? q - 2 * h : 1;     // a diagonal block: no tile above the diagonal
+        if (ylim >= 0) {
+          f64x4_t fa[4], cc[2], acc[2];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) fa[c] = *(const f64x4_t*)(Sb + (ra + i16) * P + j0 + 16 * c + 4 * kq);
-        if (have != I2) {
+          for (int c = 0; c < 4; ++c) fa[c] = *(const f64x4_t*)(Sb + (ra + i16) * P + j0 + 16 * c + 4 * kq);
+          if (have != 2 * I2 + h) {
 #pragma unroll
-          for (int y = 0; y < 4; ++y)
+            for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) fb[y][c] = *(const f64x4_t*)(Sb + (rc + 16 * y + i16) * P + j0 + 16 * c + 4 * kq);
-          have = I2;
+              for (int c = 0; c < 4; ++c) fb[y][c] = *(const f64x4_t*)(Sb + (rc + 16 * y + i16) * P + j0 + 16 * c + 4 * kq);
+            have = 2 * I2 + h;
+          }
+#pragma unroll
+          for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) cc[y][v] = Sb[(ra + 4 * v + kq) * P + rc + 16 * y + i16];
+#pragma unroll
+          for (int y = 0; y < 2; ++y) {
+            acc[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+            if (y <= ylim) {
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[c][jj], fb[y][c][jj], acc[y], 0, 0, 0);
+#pragma unroll
+              for (int v = 0; v < 4; ++v) Sb[(ra + 4 * v + kq) * P + rc + 16 * y + i16] = cc[y][v] - acc[y][v];
+            }
+          }
         }
-        f64x4_t acc[4];
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-          for (int y = 0; y < 4; ++y)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[c][jj], fb[y][c][jj], acc[y], 0, 0, 0);
-#pragma unroll
-        for (int y = 0; y < 4; ++y)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) cc[y][v] = Sb[(ra + 4 * v + kq) * P + rc + 16 * y + i16];
-        if (w == 0) {
-          // the next diagonal block (every entry of it is kept up to date, above the diagonal too): into LDS
-#pragma unroll
-          for (int y = 0; y < 4; ++y)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) a[(16 * q + 4 * v + kq) * NBP + 16 * y + i16] = cc[y][v] - acc[y][v];
-        } else {
-#pragma unroll
-          for (int y = 0; y < 4; ++y)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) Sb[(ra + 4 * v + kq) * P + rc + 16 * y + i16] = cc[y][v] - acc[y][v];
-        }
-        if (q == 3) {   // next pair
+        if ((u & 7) == 7) {   // next pair
           if (I2 == I) { ++I; I2 = 0; } else ++I2;
         }
       }
-      if (w == 0) {
-        // one wave wrote the block and one wave reads it: its LDS writes are complete once the counter says so
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        __builtin_amdgcn_wave_barrier();
-        potrf_wave(a, fac, col, floor_);
-      }
     }
     __syncthreads();
+  }
+  if (w == 0) {
+    dmin = wave_min(dmin);
+    dmax = wave_max(dmax);
+    pmin = wave_min(pmin);
   }
   // How many steps (products with G) the image may take before it orthonormalises again.  Two things limit a
   // block of m steps.  (1) Cholesky-QR needs the SCALED Gram matrix (unit diagonal) to be well conditioned; the raw
