@@ -154,9 +154,9 @@ size_t split_scratch_bytes(int B, int P);
 bool split_direct(int nP);
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
                                  const int* skip, int* img_status, hipStream_t stream);
-// Residual check and energies of a block iteration, see split.hip.
+// Residual check and energies of a block iteration, see split.hip.  slow[b] != 0: the image was left out of the split.
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
-                               int P, int n, int nP, int r, double tol, const void* scratch, int* ok, int pass_no, float* c,
+                               int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,
                                hipStream_t stream);
 // c[b][i] = (Pi G)_ii, i < n, from the projector of G[b] itself; done[b] = 1 where there is one, else 0 and c[b] untouched.
 hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n, int nP, int r, const void* scratch, int* done, float* c,

@@ -513,11 +513,16 @@ __device__ __forceinline__ double trace_minus(const double* Pi, int P, int r, do
 __global__ __launch_bounds__(1024) void split_finish_kernel(const double* __restrict__ H, const double* __restrict__ Pi,
                                                             const double* __restrict__ rnorm, int rparts, const double* __restrict__ cpart,
                                                             int cparts, int P, int n, int nP, int r, double tol,
-                                                            const SplitCtl* __restrict__ ctl, int* ok, int pass_no, float* __restrict__ c) {
+                                                            const SplitCtl* __restrict__ ctl, const int* __restrict__ slow, int* ok, int pass_no,
+                                                            float* __restrict__ c) {
   __shared__ double red[16];
   __shared__ int bad;
   const int b = blockIdx.x;
   if (pass_no > 1 && ok[b]) return;                  // passed an earlier check; its energies are in place
+  if (slow[b]) {                                     // not split in this pass
+    if (threadIdx.x == 0) ok[b] = 0;
+    return;
+  }
   if (threadIdx.x == 0) bad = 0;
   __syncthreads();
   const bool valid = projector_valid(ctl + b);
@@ -597,9 +602,10 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
 }
 
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
-                               int P, int n, int nP, int r, double tol, const void* scratch, int* ok, int pass_no, float* c, hipStream_t st) {
+                               int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,
+                               hipStream_t st) {
   hipLaunchKernelGGL(split_finish_kernel, dim3(B), dim3(1024), 0, st, H, Pi, rnorm, rparts, cpart, cparts, P, n, nP, r, tol,
-                     (const SplitCtl*)scratch, ok, pass_no, c);
+                     (const SplitCtl*)scratch, slow, ok, pass_no, c);
   return hipGetLastError();
 }
 

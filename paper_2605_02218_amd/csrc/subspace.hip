@@ -33,6 +33,7 @@ constexpr double kPivotNear = 0.25;   // smallest scaled pivot above this: rows 
 constexpr double kPivotFar = 1e-3;    // above this: blocks of two steps
 constexpr double kGradeDigits = 14.0; // decimal digits a block's grading (lambda_1 / lambda_P)^steps may use up
 constexpr int kMaxBlockSteps = 3;
+constexpr double kPlanTol = 2e-10;     // residual that the planned number of steps has to promise (checked: kRitzTol)
 constexpr double kPivotOnePass = 0.01; // final step: above this one Cholesky-QR pass leaves the rows orthonormal to ~1e-14
 constexpr size_t kCholLdsFixed = (size_t)(2 * NB * NBP + NB) * sizeof(double);   // plus P doubles: the diagonal of S
 
@@ -158,7 +159,7 @@ __device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* 
 // its inverse formed by the workgroup, the next diagonal block updated by the wave that factors it, spilled registers).
 // Dynamic LDS: 2 * 64 * 65 + 64 + P doubles.
 __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, int* skip_until, int* last_orth, int step,
-                                                   int last_free_step, int next_weight) {
+                                                   int last_free_step, int next_weight, int r, int n_sq, int* hold, int* slow) {
   extern __shared__ double lds[];
   double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert_wave (tiles below the diagonal)
   double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor
@@ -168,6 +169,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
   if (skip_until && skip_until[b] > step) return;   // this image does not orthonormalise at this step
   double* Sb = S + (long)b * P * P;
   double dmin = 1e300, dmax = 0.0, pmin = 1.0;   // extremes of the factor's diagonal, smallest scaled pivot (wave 0, by lane)
+  double d0 = 0.0, dr = 0.0, dP = 0.0;           // diagonal of the factor at rows 0, r - 1 and P - 1 (wave 0)
   const int nblk = P / NB;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
   for (int k = tid; k < P; k += 512) diag0[k] = Sb[(long)k * P + k];
@@ -191,6 +193,9 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
       dmin = fmin(dmin, d);
       dmax = fmax(dmax, d);
       if (s0 > 0.0) pmin = fmin(pmin, d * d / s0);
+      if (J == (r - 1) / NB) dr = __shfl(d, (r - 1) % NB, 64);
+      if (J == 0) d0 = __shfl(d, 0, 64);
+      if (J == nblk - 1) dP = __shfl(d, NB - 1, 64);
     }
     {
       double* Db = Dinv + ((long)b * nblk + J) * NB * NB;
@@ -315,10 +320,11 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
   // the rows like the eigenvectors, and once it has, they stay nearly orthogonal over several steps.  (2) Within a
   // row the wanted direction must not drown in rounding noise along the dominant one: (lambda_1 / lambda_P)^m has
   // to stay well inside the 16 digits; the diagonal of L spans that ratio for the steps of the block just closed.
-  if (tid == 0 && skip_until) {
+  if (tid == 0) {
     int m = 1;
+    const int begun = hold[b] > last_orth[b] ? hold[b] : last_orth[b];    // first product of the block just factored
     if (step >= 1 && dmin > 0.0) {
-      const int closed = step - last_orth[b];                       // steps in the block just factored (>= 1)
+      const int closed = step - begun;                              // steps in the block just factored (>= 1)
       const double digits_per_step = log10(fmax(dmax / dmin, 10.0)) / (double)(closed < 1 ? 1 : closed);
       const int by_grade = (int)(kGradeDigits / digits_per_step);
       const int by_pivot = pmin > kPivotNear ? kMaxBlockSteps : (pmin > kPivotFar ? 2 : 1);
@@ -333,6 +339,29 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     // The final step is followed by a second pass (step + 1) that makes the rows orthonormal to rounding; the
     // error of one pass is about 1e-16 times the scaled condition number, so with large pivots it is not needed.
     if (step == last_free_step) next = pmin > kPivotOnePass ? step + 2 : step + 1;
+    // How many steps are needed.  The block just closed multiplied orthonormal rows by G^(2 closed), and the rows are
+    // ordered: the diagonal of L holds lambda_k^(2 closed), which gives the contraction rho = lambda_P / lambda_r and the
+    // grading lambda_1 / lambda_r (within a quarter of the true rho at step 2 on all workloads).  A first pass of s steps
+    // leaves a residual of about 2 rho^s; what the G^2 as formed is off by, 1e-16 (lambda_1 / lambda_r)^2, is contracted by
+    // the g steps with G itself behind it.  With the rows orthonormal an image may wait out an even number of products (the
+    // two blocks swap roles per product) and go on where the pass ends: a decay of 0.01 per step needs 6 steps of the 12.
+    if (n_sq > 0 && step >= 2 && step <= n_sq && last_orth[b] >= 1 && hold[b] < 0) {
+      const double per = 0.5 / (double)(step - begun);
+      const double est = pow(fmax(dP, 1e-300) / fmax(dr, 1e-300), per), grade = pow(d0 / fmax(dr, 1e-300), per);
+      const double rho = fmin(1.25 * est, 1.0);
+      const int total = last_free_step + 1;
+      for (int t = (last_free_step - step) / 2 * 2 + step; t > step; t -= 2) {    // resume at product t
+        const int with_sq = n_sq - t > 0 ? n_sq - t : 0, g = total - (t > n_sq ? t : n_sq);
+        const int steps = 2 * (step + with_sq) + g;
+        if (2.0 * pow(rho, (double)steps) + 1e-16 * grade * grade * pow(rho, (double)g) < kPlanTol) {
+          hold[b] = t;
+          next = t + 1 < last_free_step ? t + 1 : last_free_step;
+          break;
+        }
+      }
+      // an image that this pass cannot bring down to the tolerance skips the split and goes on in the second pass
+      if (2.0 * pow(est, (double)(2 * n_sq + total - n_sq)) > 4.0 * kRitzTol) slow[b] = 1;
+    }
     skip_until[b] = next;
     last_orth[b] = step;
   }
@@ -401,12 +430,15 @@ __global__ __launch_bounds__(256) void trsm_kernel(double* Yt, const double* __r
   }
 }
 
-// skip_until[b] = ok[b] ? INT_MAX : -1 (images that passed take no further part), last_orth[b] = -1
-__global__ void mask_passed_kernel(const int* __restrict__ ok, int* __restrict__ skip_until, int* __restrict__ last_orth, int B) {
+// skip_until[b] = ok[b] ? INT_MAX : -1 (images that passed take no further part), last_orth[b] = hold[b] = -1, slow[b] = 0
+__global__ void mask_passed_kernel(const int* __restrict__ ok, int* __restrict__ skip_until, int* __restrict__ last_orth, int* __restrict__ hold,
+                                   int* __restrict__ slow, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   skip_until[b] = ok[b] ? 0x7fffffff : -1;
   last_orth[b] = -1;
+  hold[b] = -1;
+  slow[b] = 0;
 }
 
 }  // namespace
@@ -422,8 +454,7 @@ int subspace_block(int n, int r) {
 size_t subspace_workspace_bytes(int B, int n, int nP, int P) {
   if (P <= 0) return split_direct(nP) ? 3 * (size_t)B * nP * nP * 8 + split_scratch_bytes(B, nP) + 256 : 0;
   const size_t blk = (size_t)B * P * nP * 8;
-  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 + (size_t)B * 4 +
-         (size_t)B * 4 + 256 + (size_t)B * nP * nP * 8 /* G^2 */ + 256;
+  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 + 4 * (size_t)B * 4 + 256 + (size_t)B * nP * nP * 8 /* G^2 */ + 256;
 }
 
 // The first pass makes iters steps of the iteration as iters / 3 products with G^2 followed by iters / 3 with G.
@@ -461,7 +492,9 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   void* scratch = (void*)(((uintptr_t)(Pi + (size_t)B * P * P) + 255) & ~(uintptr_t)255);
   int* skip_until = (int*)((char*)scratch + split_scratch_bytes(B, P));                     // [B] next step that orthonormalises
   int* last_orth = skip_until + B;                                                          // [B] step of the last one
-  double* G2 = (double*)(((uintptr_t)(last_orth + B) + 255) & ~(uintptr_t)255);             // [B][nP][nP] G squared
+  int* hold = last_orth + B;                                                                // [B] products before this one are left out
+  int* slow = hold + B;                                                                     // [B] no split at the end of the first pass
+  double* G2 = (double*)(((uintptr_t)(slow + B) + 255) & ~(uintptr_t)255);             // [B][nP][nP] G squared
   // after the products with G^2 its place is free: one of the iterates of the split (P <= nP), then U, its partial energies
   // and the partial row lengths of the residual: nP (P + P / 64 + P / 64) <= nP^2 doubles per image, as P <= 3/4 n
   double* U = G2;
@@ -474,19 +507,21 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   bool masked = false;
   auto mask = [&](GemmArgs& g) {
     if (masked) { g.skip = skip_until; g.skip_if = 0x7ffffffe; }
+    else { g.skip = slow; g.skip_if = 0; }
   };
-  auto gemm_yt_g = [&](const double* X, double* out, const double* Gop) {   // out = X Gop  (P x nP), Gop = G or G^2
+  auto gemm_yt_g = [&](const double* X, double* out, const double* Gop, int it) {   // out = X Gop  (P x nP), Gop = G or G^2; product `it`
     GemmArgs g;
     g.A = X; g.B = Gop; g.C = out; g.M = P; g.N = nP; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = nP;
     g.batch = B; g.strideA = (long)P * nP; g.strideB = (long)nP * nP; g.strideC = (long)P * nP;
     g.epilogue = EPI_STORE_F64;
-    mask(g);
+    if (masked) mask(g);
+    else { g.skip = hold; g.skip_if = it; }
     return launch_gemm64_nt(g, true, true, st);
   };
   // X <- L^-1 X with X X^T = L L^T.  Images with skip_until[b] > step leave X alone, and the factorisation decides
   // how many steps the image takes before the next one (never beyond last_free_step).
   const size_t chol_lds = kCholLdsFixed + (size_t)P * sizeof(double);
-  auto cholqr = [&](double* X, int step, int last_free_step, int next_weight) -> hipError_t {
+  auto cholqr = [&](double* X, int step, int last_free_step, int next_weight, int n_sq) -> hipError_t {
     GemmArgs g;
     g.A = X; g.B = X; g.C = S; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
     g.batch = B; g.strideA = (long)P * nP; g.strideB = (long)P * nP; g.strideC = (long)P * P;
@@ -496,7 +531,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     g.skip_if = step;
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(chol_kernel, dim3((unsigned)B), dim3(512), chol_lds, st, S, D, P, skip_until, last_orth, step, last_free_step,
-                       next_weight);
+                       next_weight, r, n_sq, hold, slow);
     hipLaunchKernelGGL(trsm_kernel, dim3((unsigned)(B * (nP / NB))), dim3(256), 0, st, X, (const double*)S, (const double*)D, P, nP,
                        nP / NB, (const int*)last_orth, step);
     return hipGetLastError();
@@ -517,9 +552,9 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       // the block of step 0 is not (orthonormal) x G, so its factor says nothing about the next step (the kernel
       // takes one step after it); the last step always orthonormalises, twice where its pivots ask for it
       const int w = it < n_sq ? 2 : 1;
-      if ((e = cholqr(cur, it, steps - 1, w)) != hipSuccess) return e;
-      if (it + 1 == steps && (e = cholqr(cur, it + 1, steps - 1, 1)) != hipSuccess) return e;
-      if ((e = gemm_yt_g(cur, oth, w == 2 ? G2 : G)) != hipSuccess) return e;   // last: oth = Q^T G
+      if ((e = cholqr(cur, it, steps - 1, w, n_sq)) != hipSuccess) return e;
+      if (it + 1 == steps && (e = cholqr(cur, it + 1, steps - 1, 1, 0)) != hipSuccess) return e;
+      if ((e = gemm_yt_g(cur, oth, w == 2 ? G2 : G, it)) != hipSuccess) return e;   // last: oth = Q^T G
       double* t = cur; cur = oth; oth = t;
     }
     // now oth = Q^T (orthonormal rows), cur = Q^T G.  H = (Q^T G) Q
@@ -533,7 +568,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       mask(g);
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, G2, scratch, masked ? (const int*)ok : nullptr, img_status, st)) != hipSuccess) return e;
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, G2, scratch, masked ? (const int*)ok : (const int*)slow, img_status, st)) != hipSuccess) return e;
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;
@@ -550,7 +585,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       mask(g);
       if ((e = launch_gemm64_rownorm_dual(g, st)) != hipSuccess) return e;
     }
-    return launch_split_finish(H, Pi, rnorm, nP / NB, cpart, P / NB, B, P, n, nP, r, kRitzTol, scratch, ok, pass_no, c, st);
+    return launch_split_finish(H, Pi, rnorm, nP / NB, cpart, P / NB, B, P, n, nP, r, kRitzTol, scratch, slow, ok, pass_no, c, st);
   };
 
   // G^2 (symmetric: tiles on and below the diagonal, mirrored)
@@ -574,12 +609,13 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
   }
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
-  if ((e = launch_fill_int(skip_until, 2 * B, -1, st)) != hipSuccess) return e;
+  if ((e = launch_fill_int(skip_until, 3 * B, -1, st)) != hipSuccess) return e;
+  if ((e = launch_fill_int(slow, B, 0, st)) != hipSuccess) return e;
   if ((e = pass(iters / 3, iters / 3, 1)) != hipSuccess) return e;
   // images whose subspace is not there yet (slower spectral decay than the first pass allows for) go on from Q^T G
   // for a few more steps; for the others every kernel of this pass returns at once
   masked = true;
-  hipLaunchKernelGGL(mask_passed_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, (const int*)ok, skip_until, last_orth, B);
+  hipLaunchKernelGGL(mask_passed_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, (const int*)ok, skip_until, last_orth, hold, slow, B);
   return pass(0, more_iters, 2);
 }
 
