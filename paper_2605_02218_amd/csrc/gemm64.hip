@@ -24,6 +24,11 @@ namespace covspec {
 namespace {
 
 constexpr int TK = 16, PITCH = TK + 1;
+// 32 x 32 tiles up to which gemm64_small_kernel is taken: beyond it the device is no longer short of workgroups and the
+// doubled operand traffic decides (192 x 320 x 320, 60 tiles: 10.6 against 20.2 us; 960 tiles would read 630 MB).
+constexpr long kSmallTiles = 384;
+// 64 x 64 tiles up to which k is split over two groups of waves: one workgroup per compute unit.
+constexpr long kFewTiles = 256;
 
 __device__ __forceinline__ double as_f64(double v) { return v; }
 __device__ __forceinline__ double as_f64(float v) { return (double)v; }
@@ -246,6 +251,249 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
   }
 }
 
+// ---- fp64 x fp64, both K-contiguous, fp64 result (the products of the low-rank stage).  64 x 64 tile, 2 x 2 waves of
+// 32 x 32, k-tile 16, operand tiles loaded straight into LDS as whole 128-byte rows (a ring of four 16 KB stages, three
+// k-tiles in flight, one barrier per k-tile), rows swizzled by their low three bits so that the 16-byte fragment reads
+// (two k values per lane: any order of k serves as long as both operands have it) are conflict-free, the fragments of the
+// next half k-tile read while the current one is multiplied.  KS = 2: a second group of four waves takes the other half of
+// k in a ring of its own and the halves are added at the end, for problems with no more tiles than compute units, where
+// one wave per SIMD cannot hide its own waits.  The register-staged kernel above held one k-tile in flight and waited for
+// it with one wave per SIMD (its MFMAs were 44 % of its cycles).  Register-staged against this, us: 192 x 1280 x 1280, batch 4 (KS = 2) 75 -> 45;
+// 384 x 1152 x 1152, batch 8 303 -> 190; 256 x 640 x 640, batch 64 260 -> 220 (61 TFLOP/s; a loop of nothing but these
+// MFMAs reaches 67.6).
+// Requires K % 16 == 0, even pitches, 16-byte aligned bases.  Rows beyond M / N are clamped when loading.
+template <int KS>
+__global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int NST = 4, STAGE = 2 * 64 * 128;      // bytes: A tile then B tile
+  extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
+  const int tid = threadIdx.x & 255, grp = threadIdx.x >> 8, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, i16 = lane & 15, kq = lane >> 4;
+  const int per = tiles_m * tiles_n;
+  const int gid = regroup_xcd(blockIdx.x, gridDim.x);
+  const int b = gid / per, pidx = gid - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
+  if (g.skip && g.skip[b] > g.skip_if) return;            // uniform per workgroup
+  if (g.lower_only && tn > tm) return;                    // tile above the diagonal
+  const int row0 = tm * 64, col0 = tn * 64;
+  const double* __restrict__ A = (const double*)g.A + (long)b * g.strideA;
+  const double* __restrict__ B = (const double*)g.B + (long)b * g.strideB;
+  const int nk = g.K >> 4, nk0 = (nk + KS - 1) / KS, kt0 = grp * nk0;
+  const int mine = nk - kt0 < nk0 ? (nk - kt0 > 0 ? nk - kt0 : 0) : nk0;      // k-tiles of this group
+
+  // wave w issues loads j = 0, 1 per operand and stage; load j fills tile rows 8 (2w + j) .. +7: lane l -> row + l / 8,
+  // 16-byte slot l % 8, which holds the row's piece (l % 8) ^ (row % 8)
+  const double* ga[2];
+  const double* gb[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = 8 * (2 * wave + j) + (lane >> 3), c = (lane & 7) ^ (lane >> 3);
+    ga[j] = A + (long)min(row0 + r, g.M - 1) * g.lda + 2 * c + 16 * (long)kt0;
+    gb[j] = B + (long)min(col0 + r, g.N - 1) * g.ldb + 2 * c + 16 * (long)kt0;
+  }
+  unsigned char* base = ring + grp * (NST * STAGE);
+  const int last = mine > 0 ? mine - 1 : 0;
+  auto issue = [&](int kt) {
+    // past the end: the last k-tile again (a group without any: the one before it), into a stage that is never read
+    const long at = 16 * (long)(mine == 0 ? -1 : kt < last ? kt : last);
+    unsigned char* sa = base + (kt & (NST - 1)) * STAGE + wave * 2048;
+    unsigned char* sb = sa + 64 * 128;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[j] + at),
+                                       (__attribute__((address_space(3))) void*)(sa + j * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[j] + at),
+                                       (__attribute__((address_space(3))) void*)(sb + j * 1024), 16, 0, 0);
+    }
+  };
+  f64x4_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
+  // fragment of row R, half h: piece kq + 4h, i.e. k = 2 (kq + 4h) + {0, 1}; R % 8 == i16 % 8 for every fragment row
+  int offA[2], offB[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int piece = ((kq + 4 * h) ^ (i16 & 7)) * 16;
+    offA[h] = (wm * 32 + i16) * 128 + piece;
+    offB[h] = 64 * 128 + (wn * 32 + i16) * 128 + piece;
+  }
+  auto frags = [&](int kt, int h, f64x2_t (&fa)[2], f64x2_t (&fb)[2]) {
+    const unsigned char* st = base + (kt & (NST - 1)) * STAGE;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      fa[i] = *(const f64x2_t*)(st + offA[h] + i * 2048);
+      fb[i] = *(const f64x2_t*)(st + offB[h] + i * 2048);
+    }
+  };
+  auto mma = [&](const f64x2_t (&fa)[2], const f64x2_t (&fb)[2]) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+  };
+  // Per k-tile: wait until the next one has landed (only the four loads of the one after it may be outstanding), barrier,
+  // start the loads three ahead into the stage that held the previous one (every wave's reads of it are complete before it
+  // arrives at the barrier).
+  f64x2_t a0[2], b0[2], a1[2], b1[2];
+  issue(0);
+  issue(1);
+  issue(2);
+  __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8) lgkmcnt(0): k-tile 0 has landed
+  __builtin_amdgcn_s_barrier();
+  frags(0, 0, a0, b0);
+  for (int kt = 0; kt < nk0; ++kt) {
+    __builtin_amdgcn_s_waitcnt(0x0074);   // vmcnt(4) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    frags(kt, 1, a1, b1);
+    issue(kt + 3);
+    if (KS == 1 || kt < mine) mma(a0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+    frags(kt + 1, 0, a0, b0);
+    if (KS == 1 || kt < mine) mma(a1, b1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);
+
+  if (KS == 2) {
+    // each group hands half of its tile (i = 1 - grp) to the other and stores the rest
+    __syncthreads();
+    double* x = (double*)ring + grp * 2048;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[((j * 4 + v) * 4 + wave) * 64 + lane] = grp ? acc[0][j][v] : acc[1][j][v];
+    __syncthreads();
+    const double* y = (const double*)ring + (1 - grp) * 2048;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const double o = y[((j * 4 + v) * 4 + wave) * 64 + lane];
+        if (grp) acc[1][j][v] = o + acc[1][j][v];       // the first half's sum comes first in both groups
+        else acc[0][j][v] = acc[0][j][v] + o;
+      }
+  }
+  double* C = (double*)g.C + (long)b * g.strideC;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (KS == 2 && i != grp) continue;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = row0 + wm * 32 + i * 16 + 4 * v + kq, c = col0 + wn * 32 + j * 16 + i16;
+        if (r < g.M && c < g.N) {
+          C[(long)r * g.ldc + c] = acc[i][j][v];
+          if (g.mirror && tn != tm) C[(long)c * g.ldc + r] = acc[i][j][v];
+        }
+      }
+  }
+}
+
+// The same for problems of few tiles: 32 x 32 tile, the four waves take a quarter of k each, operands straight from global
+// memory (rows in 128-byte pieces, three groups of 16 k in flight), the partial tiles added through LDS in a fixed order.
+// Twice the operand traffic of the 64 x 64 tile but four times the workgroups and a sixteenth of the dependent MFMAs.
+// 192 x 320 x 320, one image: 20.2 us register-staged, 10.6 here.  Requires K % 64 == 0, 32-byte aligned rows.
+__global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  __shared__ double part[4 * 32 * 33];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+  const int per = tiles_m * tiles_n;
+  const int b = blockIdx.x / per, pidx = blockIdx.x - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
+  if (g.skip && g.skip[b] > g.skip_if) return;
+  if (g.lower_only && tn > tm) return;
+  const int row0 = tm * 32, col0 = tn * 32, kn = g.K >> 2;
+  const double* ar[2];
+  const double* br[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    ar[x] = (const double*)g.A + (long)b * g.strideA + (long)min(row0 + 16 * x + i16, g.M - 1) * g.lda + w * kn + 4 * kq;
+    br[x] = (const double*)g.B + (long)b * g.strideB + (long)min(col0 + 16 * x + i16, g.N - 1) * g.ldb + w * kn + 4 * kq;
+  }
+  constexpr int DEPTH = 3;
+  f64x4_t acc[2][2], fa[DEPTH][2], fb[DEPTH][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  const int nc = kn >> 4;
+  auto load = [&](int s, int c) {
+    if (c < nc) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        fa[s][x] = *(const f64x4_t*)(ar[x] + 16 * c);
+        fb[s][x] = *(const f64x4_t*)(br[x] + 16 * c);
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < DEPTH; ++s) load(s, s);
+#pragma unroll 1
+  for (int c = 0; c < nc; c += DEPTH) {
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) {
+      if (c + s < nc) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s][x][k], fb[s][y][k], acc[x][y], 0, 0, 0);
+        load(s, c + s + DEPTH);
+      }
+    }
+  }
+  double* out = part + w * (32 * 33);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(16 * x + 4 * v + kq) * 33 + 16 * y + i16] = acc[x][y][v];
+  __syncthreads();
+  auto sum = [&](int i, int j) {
+    const double* q = part + i * 33 + j;
+    return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
+  };
+  double* C = (double*)g.C + (long)b * g.strideC;
+  for (int e = tid; e < 32 * 32; e += 256) {
+    const int i = e >> 5, j = e & 31;
+    if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = sum(i, j);
+    if (g.mirror && tn != tm && row0 + j < g.M && col0 + i < g.N) C[(long)(col0 + i) * g.ldc + row0 + j] = sum(j, i);
+  }
+}
+
+hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
+  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, t32 = (g.lower_only ? n32 * (n32 + 1) / 2 : m32 * n32) * g.batch;
+  if (t32 <= kSmallTiles && g.K % 64 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.strideA % 4 == 0 && g.strideB % 4 == 0 &&
+      (((uintptr_t)g.A | (uintptr_t)g.B) & 31) == 0) {
+    hipLaunchKernelGGL(gemm64_small_kernel, dim3((unsigned)(m32 * n32 * g.batch)), dim3(256), 0, stream, g, (int)m32, (int)n32);
+    return hipGetLastError();
+  }
+  const long m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, blocks = m64 * n64 * g.batch;
+  const long t64 = (g.lower_only ? n64 * (n64 + 1) / 2 : m64 * n64) * g.batch;
+  if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  constexpr size_t kRing = 4 * 2 * 64 * 128;
+  if (t64 <= kFewTiles && g.K >= 32) {
+    static PerDeviceInt raised;
+    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<2>, 2 * kRing);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gemm64_dma_kernel<2>, dim3((unsigned)blocks), dim3(512), 2 * kRing, stream, g, (int)m64, (int)n64);
+  } else {
+    hipLaunchKernelGGL(gemm64_dma_kernel<1>, dim3((unsigned)blocks), dim3(256), kRing, stream, g, (int)m64, (int)n64);
+  }
+  return hipGetLastError();
+}
+
+// Products the two kernels above take.
+inline bool plain_f64(const GemmArgs& g) {
+  return g.batch > 0 && g.batch_inner == 1 && g.K >= 16 && g.K % 16 == 0 && g.lda % 2 == 0 && g.ldb % 2 == 0 && g.strideA % 2 == 0 &&
+         g.strideB % 2 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
+}
+
 template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ, bool DUAL = false>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream) {
   constexpr int TM = 32 * MI, TN = 32 * NJ;
@@ -284,9 +532,7 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   }
   if (g.epilogue == EPI_STORE_F64) {
     if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, false, 2, 2>(g, stream);
-    // 64x64 tiles: measured equal or faster than 128x128 and 128x64 on every workload (the batched products of
-    // the low-rank stage make 600-2500 tiles of 128x128, one to two rounds over the device, and the finer tiles
-    // lose less to the last, partly filled round than they pay in LDS traffic)
+    if (std::is_same<TA, double>::value && std::is_same<TB, double>::value && plain_f64(g)) return launch_plain_f64(g, stream);
     return launch_cfg<TA, TB, EPI_STORE_F64, false, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;

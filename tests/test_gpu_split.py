@@ -24,6 +24,8 @@ CASES = {
     "direct-rank1": (2, 128, 160, 1, 0.05),
     "full-solve": (1, 129, 160, 64, 0.05),        # too large for a direct split, block would be most of the matrix
     "smallest-block": (1, 171, 192, 3, 0.05),     # block of 128 of 171: the whole block is the window
+    "many-rows": (4, 900, 960, 40, 0.05),         # products on 64 x 64 tiles with k in two halves
+    "few-images": (6, 700, 720, 130, 0.06),       # more such tiles than compute units
     "window-inside": (2, 400, 420, 180, 0.04),    # block of 256, window in its middle
     "leading-rows": (1, 600, 640, 250, 0.06),     # leading rows that no longer couple are left out of the iteration
     "eleven-images": (11, 171, 192, 40, 0.05),
