@@ -15,6 +15,22 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
 
+// Fragment order of a 16 x 16 fp64 tile: lane l of a wave (i = l % 16, q = l / 16) owns the elements (row i, column 4v + q),
+// v = 0..3, which is what an operand of v_mfma_f64_16x16x4_f64 wants of it in four steps, and (with rows and columns
+// swapped) what a product leaves in it.  The four go out as two 16-byte pieces, each a contiguous kilobyte of the wave.
+// Row-major tiles cost a wave 64 cache lines per 16-byte load, one per lane (consecutive lanes are consecutive rows).
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+constexpr int kFragTile = 256;
+__device__ __forceinline__ int frag_at(int i, int k) { return ((k >> 3) * 64 + (k & 3) * 16 + i) * 2 + ((k >> 2) & 1); }
+__device__ __forceinline__ f64x4_t frag_load(const double* tile, int lane) {
+  const f64x2_t a = *(const f64x2_t*)(tile + 2 * lane), b = *(const f64x2_t*)(tile + 128 + 2 * lane);
+  return (f64x4_t){a[0], a[1], b[0], b[1]};
+}
+__device__ __forceinline__ void frag_store(double* tile, int lane, const f64x4_t& v) {
+  *(f64x2_t*)(tile + 2 * lane) = (f64x2_t){v[0], v[1]};
+  *(f64x2_t*)(tile + 128 + 2 * lane) = (f64x2_t){v[2], v[3]};
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ float bf16lo_to_f32(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float bf16hi_to_f32(uint32_t packed) { return __uint_as_float(packed & 0xFFFF0000u); }

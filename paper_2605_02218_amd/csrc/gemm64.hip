@@ -273,6 +273,7 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   const int b = gid / per, pidx = gid - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
   if (g.skip && g.skip[b] > g.skip_if) return;            // uniform per workgroup
   if (g.lower_only && tn > tm) return;                    // tile above the diagonal
+  if (g.frag && tn < tm) return;                          // see the store
   const int row0 = tm * 64, col0 = tn * 64;
   const double* __restrict__ A = (const double*)g.A + (long)b * g.strideA;
   const double* __restrict__ B = (const double*)g.B + (long)b * g.strideB;
@@ -309,7 +310,6 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-  typedef double f64x2_t __attribute__((ext_vector_type(2)));
   // fragment of row R, half h: piece kq + 4h, i.e. k = 2 (kq + 4h) + {0, 1}; R % 8 == i16 % 8 for every fragment row
   int offA[2], offB[2];
 #pragma unroll
@@ -381,6 +381,13 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (KS == 2 && i != grp) continue;
+    if (g.frag) {
+      // the product is symmetric: what this lane holds of tile (row, column) is the fragment of tile (column, row)
+      const int per16 = g.N >> 4, ct = (row0 + wm * 32) / 16 + i;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) frag_store(C + ((long)((col0 + wn * 32) / 16 + j) * per16 + ct) * kFragTile, lane, acc[i][j]);
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -405,6 +412,7 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
   const int b = blockIdx.x / per, pidx = blockIdx.x - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
   if (g.skip && g.skip[b] > g.skip_if) return;
   if (g.lower_only && tn > tm) return;
+  if (g.frag && tn < tm) return;
   const int row0 = tm * 32, col0 = tn * 32, kn = g.K >> 2;
   const double* ar[2];
   const double* br[2];
@@ -459,6 +467,14 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
   };
   double* C = (double*)g.C + (long)b * g.strideC;
+  if (g.frag) {                                           // wave w: 16 x 16 tile (w / 2, w % 2) of the transposed product
+    const int sr = w >> 1, sc = w & 1;
+    f64x4_t v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = sum(16 * sc + 4 * q + kq, 16 * sr + i16);
+    frag_store(C + ((long)(col0 / 16 + sr) * (g.N >> 4) + row0 / 16 + sc) * kFragTile, lane, v);
+    return;
+  }
   for (int e = tid; e < 32 * 32; e += 256) {
     const int i = e >> 5, j = e & 31;
     if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = sum(i, j);
@@ -467,14 +483,15 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
 }
 
 hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
-  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, t32 = (g.lower_only ? n32 * (n32 + 1) / 2 : m32 * n32) * g.batch;
+  if (g.frag && (g.M != g.N || g.N % 64 != 0)) return hipErrorInvalidValue;
+  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, t32 = (g.lower_only || g.frag ? n32 * (n32 + 1) / 2 : m32 * n32) * g.batch;
   if (t32 <= kSmallTiles && g.K % 64 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.strideA % 4 == 0 && g.strideB % 4 == 0 &&
       (((uintptr_t)g.A | (uintptr_t)g.B) & 31) == 0) {
     hipLaunchKernelGGL(gemm64_small_kernel, dim3((unsigned)(m32 * n32 * g.batch)), dim3(256), 0, stream, g, (int)m32, (int)n32);
     return hipGetLastError();
   }
   const long m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, blocks = m64 * n64 * g.batch;
-  const long t64 = (g.lower_only ? n64 * (n64 + 1) / 2 : m64 * n64) * g.batch;
+  const long t64 = (g.lower_only || g.frag ? n64 * (n64 + 1) / 2 : m64 * n64) * g.batch;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
   constexpr size_t kRing = 4 * 2 * 64 * 128;
   if (t64 <= kFewTiles && g.K >= 32) {
@@ -533,6 +550,7 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   if (g.epilogue == EPI_STORE_F64) {
     if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, false, 2, 2>(g, stream);
     if (std::is_same<TA, double>::value && std::is_same<TB, double>::value && plain_f64(g)) return launch_plain_f64(g, stream);
+    if (g.frag) return hipErrorInvalidValue;
     return launch_cfg<TA, TB, EPI_STORE_F64, false, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;

@@ -38,6 +38,8 @@ struct GemmArgs {
   bool mirror = false;                         // with lower_only, square tiles and a symmetric product (A = B): tiles below the
                                                // diagonal are also stored transposed, so that C comes out full
   bool transB = false;                         // B is stored [K][N] (row pitch ldb), i.e. C = A * B
+  bool frag = false;                           // square symmetric product (A = B, N % 64 == 0): C as [N/16][N/16] tiles in fragment
+                                               // order (common.h), those on and below the diagonal; ldc unused
   const int* skip = nullptr;                   // per outer batch: the work is skipped while skip[b] > skip_if
   int skip_if = 1;
   const void* A2 = nullptr;                    // launch_gemm64_rownorm_dual: second operands, laid out like A and B

@@ -145,18 +145,20 @@ __device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* 
   }
 }
 
-// Cholesky factorisation S[b] = L L^T (P x P, pitch P, P % 64 == 0; only the lower triangle is read), one
-// 512-thread workgroup per image, right-looking over 64-wide panels:
-//   diagonal block: factored and inverted by one wave (factor_invert_wave); the inverse goes to Dinv[b][J] (64 x 64);
+// Cholesky factorisation S[b] = L L^T (P x P, P % 64 == 0, [P/16][P/16] tiles in fragment order, those on and below the
+// diagonal), one 512-thread workgroup per image, right-looking over 64-wide panels:
+//   diagonal block: factored and inverted by one wave (factor_invert_wave); the inverse goes to Dinv[b][J] (its 16 tiles);
 //   panel below:    X = S[I,J] inv(L_JJ)^T on the MFMA, in place (these blocks are L[I,J]);
 //   next diagonal block: updated by all waves, into LDS; then one wave factors it while the others do the
-//   trailing part:  S[I,I'] -= X_I X_I'^T for I' <= I on the MFMA, 16 x 32 units.
+//   trailing part:  S[I,I'] -= X_I X_I'^T for I' <= I on the MFMA, units of 16 x 32.
+// Every product is formed transposed, so that its result is the fragment of the tile it goes to.
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
 // Pivots are floored at 1e-28 * trace(first block) so that a numerically rank-deficient block cannot
 // produce NaNs (the residual check afterwards decides whether the result is usable).
 // Bound by the chain of panels (and, from order 384 on, by one compute unit's MFMA rate in the trailing part).  One image of
-// order 192 168 -> 76 us, eight of 384 448 -> 220, sixty-four of 256 257 -> 115 (before: the block factored column by column,
-// its inverse formed by the workgroup, the next diagonal block updated by the wave that factors it, spilled registers).
+// order 192 / eight of 384 / sixty-four of 256, us: 168 / 448 / 257 with the block factored column by column, its inverse
+// formed by the workgroup, the next diagonal block updated by the wave that factors it and spilled registers; 76 / 220 / 115
+// without; 69 / 172 / 107 with the tiles in fragment order.
 // Dynamic LDS: 2 * 64 * 65 + 64 + P doubles.
 __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, int* skip_until, int* last_orth, int step,
                                                    int last_free_step, int next_weight, int r, int n_sq, int* hold, int* slow) {
@@ -170,13 +172,16 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
   double* Sb = S + (long)b * P * P;
   double dmin = 1e300, dmax = 0.0, pmin = 1.0;   // extremes of the factor's diagonal, smallest scaled pivot (wave 0, by lane)
   double d0 = 0.0, dr = 0.0, dP = 0.0;           // diagonal of the factor at rows 0, r - 1 and P - 1 (wave 0)
-  const int nblk = P / NB;
+  const int nblk = P / NB, per16 = P / 16;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
-  for (int k = tid; k < P; k += 512) diag0[k] = Sb[(long)k * P + k];
-  for (int e = tid; e < NB * NB; e += 512) {
-    const int i = e >> 6, j = e & 63;
-    a[i * NBP + j] = (j <= i) ? Sb[(long)i * P + j] : 0.0;
-    inv[i * NBP + j] = 0.0;
+  auto tile = [&](int rt, int ct) -> double* { return Sb + ((long)rt * per16 + ct) * kFragTile; };
+  for (int k = tid; k < P; k += 512) diag0[k] = tile(k >> 4, k >> 4)[frag_at(k & 15, k & 15)];
+  for (int e = tid; e < NB * NB; e += 512) inv[(e >> 6) * NBP + (e & 63)] = 0.0;
+  for (int t = w; t < 10; t += 8) {                     // t-th tile of a block on or below its diagonal
+    const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
+    const f64x4_t c = frag_load(tile(x, y), lane);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v];
   }
   __syncthreads();
   double floor_ = 0.0;
@@ -186,7 +191,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
   __syncthreads();
 
   for (int J = 0; J < nblk; ++J) {
-    const int j0 = J * NB;
+    const int j0 = J * NB, jt = 4 * J;
     // here `inv` holds the inverse of the factor of diagonal block J
     if (w == 0) {
       const double d = dl[lane], s0 = diag0[j0 + lane];
@@ -197,56 +202,51 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
       if (J == 0) d0 = __shfl(d, 0, 64);
       if (J == nblk - 1) dP = __shfl(d, NB - 1, 64);
     }
-    {
-      double* Db = Dinv + ((long)b * nblk + J) * NB * NB;
-      // stored with the columns of every group of 16 permuted, 16x + 4v + q -> 16x + 4q + v: trsm_kernel's lane
-      // of quarter q contracts the columns 16x + 4v + q, v = 0..3, of a step group and reads them as one 32-byte piece
-      for (int e = tid; e < NB * NB; e += 512) {
-        const int c = e & 63;
-        Db[(e & ~63) | (c & 48) | ((c & 3) << 2) | ((c >> 2) & 3)] = inv[(e >> 6) * NBP + c];
-      }
+    for (int t = w; t < 10; t += 8) {
+      const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
+      f64x4_t c;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) c[v] = inv[(16 * x + i16) * NBP + 16 * y + 4 * v + kq];
+      frag_store(Dinv + ((long)b * nblk + J) * NB * NB + (4 * x + y) * kFragTile, lane, c);
     }
     // ---- panel: X = S[I,J] inv^T, 16-row tiles dealt to the waves; inv is lower triangular
-    const int below = P - j0 - NB;
-    for (int t = w; t < below / 16; t += 8) {
-      const long rb = j0 + NB + 16 * t;
+    const int below = (P - j0 - NB) / 16;
+    for (int t = w; t < below; t += 8) {
+      const int rt = jt + 4 + t;
       f64x4_t f[4], out[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) f[c] = *(const f64x4_t*)(Sb + (rb + i16) * P + j0 + 16 * c + 4 * kq);
+      for (int c = 0; c < 4; ++c) f[c] = frag_load(tile(rt, jt + c), lane);
 #pragma unroll
       for (int y = 0; y < 4; ++y) {
         out[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int c = 0; c <= y; ++c)
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            out[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[c][jj], inv[(16 * y + i16) * NBP + 16 * c + 4 * kq + jj], out[y], 0, 0, 0);
+          for (int v = 0; v < 4; ++v)
+            out[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[(16 * y + i16) * NBP + 16 * c + 4 * v + kq], f[c][v], out[y], 0, 0, 0);
       }
 #pragma unroll
-      for (int y = 0; y < 4; ++y)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Sb[(rb + 4 * v + kq) * P + j0 + 16 * y + i16] = out[y][v];
+      for (int y = 0; y < 4; ++y) frag_store(tile(rt, jt + y), lane, out[y]);
     }
     __syncthreads();     // the panel is complete in global memory and `a`, `inv` are free
     if (below == 0) break;
     // ---- the next diagonal block, into LDS: its ten 16 x 16 tiles on and below the diagonal
     for (int t = w; t < 10; t += 8) {
       const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
-      const long ra = j0 + NB + 16 * x, rc = j0 + NB + 16 * y;
-      f64x4_t fa[4], fb[4], cc, acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+      const int rt = jt + 4 + x, ct = jt + 4 + y;
+      f64x4_t fr[4], fc[4], acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        fa[c] = *(const f64x4_t*)(Sb + (ra + i16) * P + j0 + 16 * c + 4 * kq);
-        fb[c] = *(const f64x4_t*)(Sb + (rc + i16) * P + j0 + 16 * c + 4 * kq);
+        fr[c] = frag_load(tile(rt, jt + c), lane);
+        fc[c] = frag_load(tile(ct, jt + c), lane);
       }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) cc[v] = Sb[(ra + 4 * v + kq) * P + rc + i16];
+      const f64x4_t cc = frag_load(tile(rt, ct), lane);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[c][jj], fb[c][jj], acc, 0, 0, 0);
+        for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fc[c][v], fr[c][v], acc, 0, 0, 0);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) a[(16 * x + 4 * v + kq) * NBP + 16 * y + i16] = cc[v] - acc[v];
+      for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = cc[v] - acc[v];
     }
     __syncthreads();
     // ---- trailing update by waves 1..7, unit = 16 rows of block I x 32 columns of block I' <= I, in contiguous
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     if (w == 0) {
       factor_invert_wave(a, inv, dl, floor_);
     } else {
-      const int nb = below / NB;
+      const int nb = below / 4;
       const int units = 4 * nb * (nb + 1);            // 8 * nb (nb + 1) / 2; units 0..7 are the next diagonal block
       const int u0 = 8 + (int)((long)(units - 8) * (w - 1) / 7), u1 = 8 + (int)((long)(units - 8) * w / 7);
       // unit u -> pair index u / 8 -> (I, I2) with I (I + 1) / 2 + I2 = pair index
@@ -270,34 +270,29 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
 #pragma unroll 1
       for (int u = u0; u < u1; ++u) {
         const int q = u & 3, h = (u >> 2) & 1;
-        const long ra = j0 + NB + (long)I * NB + 16 * q;
-        const long rc = j0 + NB + (long)I2 * NB + 32 * h;
-        const int ylim = I == I2 ? q - 2 * h : 1;     // a diagonal block: no tile above the diagonal
-        if (ylim >= 0) {
-          f64x4_t fa[4], cc[2], acc[2];
+        const int rt = jt + 4 + 4 * I + q, ct = jt + 4 + 4 * I2 + 2 * h;
+        if (ct <= rt) {                               // a diagonal block: no tile above the diagonal
+          f64x4_t fa[4], cc[2];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) fa[c] = *(const f64x4_t*)(Sb + (ra + i16) * P + j0 + 16 * c + 4 * kq);
-          if (have != 2 * I2 + h) {
+          for (int c = 0; c < 4; ++c) fa[c] = frag_load(tile(rt, jt + c), lane);
+          if (have != ct) {
 #pragma unroll
             for (int y = 0; y < 2; ++y)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) fb[y][c] = *(const f64x4_t*)(Sb + (rc + 16 * y + i16) * P + j0 + 16 * c + 4 * kq);
-            have = 2 * I2 + h;
+              for (int c = 0; c < 4; ++c) fb[y][c] = frag_load(tile(ct + y, jt + c), lane);
+            have = ct;
           }
-#pragma unroll
-          for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) cc[y][v] = Sb[(ra + 4 * v + kq) * P + rc + 16 * y + i16];
+          cc[0] = frag_load(tile(rt, ct), lane);
+          if (ct < rt) cc[1] = frag_load(tile(rt, ct + 1), lane);
 #pragma unroll
           for (int y = 0; y < 2; ++y) {
-            acc[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-            if (y <= ylim) {
+            if (ct + y <= rt) {
+              f64x4_t acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
               for (int c = 0; c < 4; ++c)
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[c][jj], fb[y][c][jj], acc[y], 0, 0, 0);
-#pragma unroll
-              for (int v = 0; v < 4; ++v) Sb[(ra + 4 * v + kq) * P + rc + 16 * y + i16] = cc[y][v] - acc[y][v];
+                for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[y][c][v], fa[c][v], acc, 0, 0, 0);
+              frag_store(tile(rt, ct + y), lane, cc[y] - acc);
             }
           }
         }
@@ -368,13 +363,97 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
 }
 
 // Yt[b] <- L^-1 Yt[b] (P x nP, pitch nP) by blocked forward substitution with the factor chol_kernel left
-// in S (strictly-lower blocks) and Dinv (inverted diagonal blocks).  Columns are independent: each wave
+// in S (strictly-lower blocks) and Dinv (inverted diagonal blocks), both tiles in fragment order.  Columns are independent: each wave
 // owns 16 of them and never reads what another wave writes, so the whole solve is one launch.
 //   for block row bi:  T = Yt[bi] - sum_{K<bi} L[bi,K] Yt[K];   Yt[bi] = inv(L_bibi) T
-// T comes out of the MFMA in exactly the layout its B operand wants (lane = column, register = k), so the
-// second product takes the accumulator registers as they are.
-__global__ __launch_bounds__(256) void trsm_kernel(double* Yt, const double* __restrict__ S, const double* __restrict__ Dinv,
-                                                    int P, int nP, int wg_per_image, const int* __restrict__ last_orth, int step) {
+// What the MFMA returns (lane = column, register = k) is exactly the layout its B operand wants, so the solved blocks are
+// kept in registers and are the B operands of the following rows as they are; the A operands are a stream that is known in
+// advance, four groups of 16 k of it in flight.  Nothing waits for memory but the first group: the chain is MFMAs.
+// Written back to memory and read again block by block, with the loads of a block in front of its MFMAs, the solve took,
+// us: 192 x 320 29, 192 x 1280 batch 4 33, 384 x 1152 batch 8 91, 256 x 640 batch 64 145; in registers 26, 30, 83, 127; with
+// the factor in fragment order (row-major, a load touched 64 cache lines) 15, 19, 45, 76.
+// Taken for up to six blocks (the registers of a wave hold no more); larger factors go through trsm_any_kernel.
+template <int N>
+struct TrsmAt {          // group N of the A stream: block row bi takes 4 bi groups of L and 4 of its inverted diagonal block
+  static constexpr int row() { int bi = 0; while (2 * (bi + 1) * (bi + 2) <= N) ++bi; return bi; }
+  static constexpr int bi = row(), at = N - 2 * bi * (bi + 1), K = at >> 2, q = at & 3;
+};
+
+struct TrsmPtr { const double *L, *D; double* Y; long nP; };      // lane offsets included
+
+template <int NBLK, int N>
+__device__ __forceinline__ void trsm_fetch(const TrsmPtr& p, f64x4_t (&f)[4]) {
+  if constexpr (N < 2 * NBLK * (NBLK + 1)) {
+    typedef TrsmAt<N> A;
+#pragma unroll
+    for (int x = A::K < A::bi ? 0 : A::q; x < 4; ++x)     // the inverted block is lower triangular
+      f[x] = A::K < A::bi ? frag_load(p.L + ((long)(4 * A::bi + x) * (4 * NBLK) + 4 * A::K + A::q) * kFragTile, 0)
+                          : frag_load(p.D + (16 * A::bi + 4 * x + A::q) * kFragTile, 0);
+  }
+}
+
+template <int NBLK, int N>
+__device__ __forceinline__ void trsm_steps(const TrsmPtr& p, f64x4_t (&y)[NBLK][4], f64x4_t (&f)[4][4], f64x4_t (&acc)[4], f64x4_t (&rhs)[4]) {
+  if constexpr (N < 2 * NBLK * (NBLK + 1)) {
+    typedef TrsmAt<N> A;
+    if constexpr (A::at == 0) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        acc[x] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) rhs[x][v] = p.Y[(long)(A::bi * NB + 16 * x + 4 * v) * p.nP];
+      }
+    }
+    if constexpr (A::K == A::bi && A::q == 0) {         // T is complete; the inverted block takes it as its B operand
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        rhs[x] = rhs[x] - acc[x];
+        acc[x] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double bv = A::K < A::bi ? y[A::K][A::q][v] : rhs[A::q][v];
+#pragma unroll
+      for (int x = A::K < A::bi ? 0 : A::q; x < 4; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[N & 3][x][v], bv, acc[x], 0, 0, 0);
+    }
+    trsm_fetch<NBLK, N + 4>(p, f[N & 3]);
+    __builtin_amdgcn_sched_barrier(0);                  // the loads stay four groups ahead of their use
+    if constexpr (A::K == A::bi && A::q == 3) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        y[A::bi][x] = acc[x];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) p.Y[(long)(A::bi * NB + 16 * x + 4 * v) * p.nP] = acc[x][v];
+      }
+    }
+    trsm_steps<NBLK, N + 1>(p, y, f, acc, rhs);
+  }
+}
+
+template <int NBLK>
+__global__ __launch_bounds__(256, 1) void trsm_kernel(double* Yt, const double* __restrict__ S, const double* __restrict__ Dinv, int nP,
+                                                      int wg_per_image, const int* __restrict__ last_orth, int step) {
+  const int b = blockIdx.x / wg_per_image, cw = blockIdx.x - b * wg_per_image;
+  if (last_orth && last_orth[b] != step) return;    // the factorisation of this step did not run for this image
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
+  constexpr int P = NBLK * NB;
+  TrsmPtr p;
+  p.L = S + (long)b * P * P + 2 * lane;
+  p.D = Dinv + (long)b * NBLK * NB * NB + 2 * lane;
+  p.Y = Yt + (long)b * P * nP + (long)kq * nP + cw * 64 + w * 16 + i16;     // nP % 64 == 0, so every column exists
+  p.nP = nP;
+  f64x4_t y[NBLK][4], f[4][4], acc[4], rhs[4];
+  trsm_fetch<NBLK, 0>(p, f[0]);
+  trsm_fetch<NBLK, 1>(p, f[1]);
+  trsm_fetch<NBLK, 2>(p, f[2]);
+  trsm_fetch<NBLK, 3>(p, f[3]);
+  trsm_steps<NBLK, 0>(p, y, f, acc, rhs);
+}
+
+// The same for any number of blocks: the solved blocks go through memory.
+__global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, const double* __restrict__ S, const double* __restrict__ Dinv,
+                                                        int P, int nP, int wg_per_image, const int* __restrict__ last_orth, int step) {
   const int b = blockIdx.x / wg_per_image, cw = blockIdx.x - b * wg_per_image;
   if (last_orth && last_orth[b] != step) return;    // the factorisation of this step did not run for this image
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
@@ -390,9 +469,9 @@ __global__ __launch_bounds__(256) void trsm_kernel(double* Yt, const double* __r
       f64x4_t fa[4];
       double fb[4];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) fa[x] = *(const f64x4_t*)(Lb + (long)(bi * NB + 16 * x + i16) * P + kk + 4 * kq);
+      for (int x = 0; x < 4; ++x) fa[x] = frag_load(Lb + ((long)(4 * bi + x) * (P / 16) + kk / 16) * kFragTile, lane);
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) fb[jj] = Yb[(long)(kk + 4 * kq + jj) * nP + col];
+      for (int jj = 0; jj < 4; ++jj) fb[jj] = Yb[(long)(kk + 4 * jj + kq) * nP + col];
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
@@ -406,22 +485,15 @@ __global__ __launch_bounds__(256) void trsm_kernel(double* Yt, const double* __r
     f64x4_t out[4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) out[a] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-    // step (x, v) contracts k = 16x + 4v + kq, the row acc[x][v] holds in this lane; the inverse block is stored
-    // with its columns permuted so that the four v of a group are contiguous.  Two groups of loads in flight.
+    // step (x, v) contracts k = 16x + 4v + kq, the row acc[x][v] holds in this lane; the inverse is lower triangular
 #pragma unroll
-    for (int xh = 0; xh < 4; xh += 2) {
-      f64x4_t da[2][4];
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-      for (int xx = 0; xx < 2; ++xx)
+      for (int a = x; a < 4; ++a) {
+        const f64x4_t da = frag_load(Db + (4 * a + x) * kFragTile, lane);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) da[xx][a] = *(const f64x4_t*)(Db + (16 * a + i16) * NB + 16 * (xh + xx) + 4 * kq);
-#pragma unroll
-      for (int xx = 0; xx < 2; ++xx)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int a = 0; a < 4; ++a) out[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[xx][a][v], acc[xh + xx][v], out[a], 0, 0, 0);
-    }
+        for (int v = 0; v < 4; ++v) out[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[v], acc[x][v], out[a], 0, 0, 0);
+      }
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -526,14 +598,26 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     g.A = X; g.B = X; g.C = S; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
     g.batch = B; g.strideA = (long)P * nP; g.strideB = (long)P * nP; g.strideC = (long)P * P;
     g.epilogue = EPI_STORE_F64;
-    g.lower_only = true;
+    g.frag = true;
     g.skip = skip_until;
     g.skip_if = step;
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(chol_kernel, dim3((unsigned)B), dim3(512), chol_lds, st, S, D, P, skip_until, last_orth, step, last_free_step,
                        next_weight, r, n_sq, hold, slow);
-    hipLaunchKernelGGL(trsm_kernel, dim3((unsigned)(B * (nP / NB))), dim3(256), 0, st, X, (const double*)S, (const double*)D, P, nP,
-                       nP / NB, (const int*)last_orth, step);
+    const dim3 tg((unsigned)(B * (nP / NB)));
+    const double *cS = S, *cD = D;
+    const int* orth = last_orth;
+    switch (P / NB) {
+#define COVSPEC_TRSM(n) \
+  case n: hipLaunchKernelGGL(trsm_kernel<n>, tg, dim3(256), 0, st, X, cS, cD, nP, nP / NB, orth, step); break;
+      COVSPEC_TRSM(2)
+      COVSPEC_TRSM(3)
+      COVSPEC_TRSM(4)
+      COVSPEC_TRSM(5)
+      COVSPEC_TRSM(6)
+#undef COVSPEC_TRSM
+      default: hipLaunchKernelGGL(trsm_any_kernel, tg, dim3(256), 0, st, X, cS, cD, P, nP, nP / NB, orth, step);
+    }
     return hipGetLastError();
   };
   double* cur = Yt;

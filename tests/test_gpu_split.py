@@ -26,6 +26,8 @@ CASES = {
     "smallest-block": (1, 171, 192, 3, 0.05),     # block of 128 of 171: the whole block is the window
     "many-rows": (4, 900, 960, 40, 0.05),         # products on 64 x 64 tiles with k in two halves
     "few-images": (6, 700, 720, 130, 0.06),       # more such tiles than compute units
+    "seven-blocks": (1, 700, 720, 330, 0.02),     # block of 448: the substitution goes through memory
+    "five-blocks": (1, 500, 520, 230, 0.03),
     "window-inside": (2, 400, 420, 180, 0.04),    # block of 256, window in its middle
     "leading-rows": (1, 600, 640, 250, 0.06),     # leading rows that no longer couple are left out of the iteration
     "eleven-images": (11, 171, 192, 40, 0.05),
