@@ -15,8 +15,8 @@
 // Before: the P x P problem was diagonalised by block Jacobi (six sweeps of P/32 - 1 rounds of 32 dependent rotation
 // steps each).  An eigen-decomposition orders every pair of rows; the energies only ask which side of the cut a
 // direction is on, and the products that answer that are matrix-core work without a serial chain of rotations.
-// Jacobi against split + sign, us: one matrix of order 128 2727 -> 143 + 168, one of 192 1482 -> 144 + 292, four of 192
-// 1769 -> 144 + 262, eight of 384 3551 -> 144 + 366, sixty-four of 256 3894 -> 144 + 1530.
+// Jacobi against split + sign, us: one matrix of order 128 2727 -> 143 + 131, one of 192 1482 -> 144 + 197, four of 192
+// 1769 -> 144 + 200, eight of 384 3551 -> 144 + 259, sixty-four of 256 3894 -> 144 + 1061.
 //
 // Leading rows [0, a) of an ordered H that do not couple to the rows around and beyond the cut (kLeadFar) and whose
 // eigenvalues are above mu by their diagonal (row sums of the scaled couplings below 1/2: no eigenvalue of the block is
@@ -300,14 +300,17 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
 constexpr int ST = 32;            // tile of a wave in the sign iteration
 constexpr int STP = ST + 1;
 
-// Tile (r0, c0), 32 x 32, of X Z for symmetric X, Z (pitch P), k over [k0, k0 + kn), kn % 16 == 0: one wave, operands
-// straight from global memory in 128-byte pieces of a row, DEPTH groups of 16 k in flight; the result goes to `out` (LDS).
+// The iterates are kept as [P/16][P/16] tiles in fragment order (common.h), both triangles.
+__device__ __forceinline__ long tile16(int rt, int ct, int P) { return ((long)rt * (P >> 4) + ct) * kFragTile; }
+
+// Tile (r0, c0), 32 x 32, of X Z for symmetric X, Z of order P, k over [k0, k0 + kn), kn % 16 == 0: one wave, operands
+// straight from global memory, DEPTH groups of 16 k in flight; the result goes to `out` (LDS).
 template <int DEPTH>
 __device__ __forceinline__ void tile_product(const double* X, const double* Z, int P, int k0, int kn, int r0, int c0, double* out) {
   const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
-  const double* xr = X + (long)(r0 + i16) * P + k0 + 4 * kq;
-  const double* zr = Z + (long)(c0 + i16) * P + k0 + 4 * kq;
-  const long step = 16 * (long)P;
+  const double* xr = X + tile16(r0 >> 4, k0 >> 4, P);
+  const double* zr = Z + tile16(c0 >> 4, k0 >> 4, P);
+  const long step = tile16(1, 0, P);
   f64x4_t acc[2][2], fx[DEPTH][2], fz[DEPTH][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
@@ -318,8 +321,8 @@ __device__ __forceinline__ void tile_product(const double* X, const double* Z, i
     if (c < nc) {
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
-        fx[s][x] = *(const f64x4_t*)(xr + x * step + 16 * c);
-        fz[s][x] = *(const f64x4_t*)(zr + x * step + 16 * c);
+        fx[s][x] = frag_load(xr + x * step + c * kFragTile, lane);
+        fz[s][x] = frag_load(zr + x * step + c * kFragTile, lane);
       }
     }
   };
@@ -363,7 +366,8 @@ __device__ __forceinline__ void tile_of(int t, int& i, int& j) {      // t-th ti
 // X0, X1, Y: P x P per image; the projector is left in Y.
 // What the workgroups hand one another is stored through the L2 (store_through), which spares the write-back of a whole L2
 // at every meeting: eight images of order 192 to 320 took 553 us with write-backs and 366 us without (a single image of
-// order 192: 259 and 292 us, sixty-four of order 256: 1.70 and 1.53 ms).
+// order 192: 259 and 292 us, sixty-four of order 256: 1.70 and 1.53 ms).  The iterates in fragment order instead of row-major
+// (64 cache lines per load): 366 -> 259, 292 -> 197 us, 1.53 -> 1.06 ms.
 // WIDE = false: a workgroup's tile is 32 x 32, its waves take a quarter of k each; WIDE = true: the tile is 64 x 64, a
 // wave takes a quadrant of it and all of k (a quarter of the workgroups: sixty-four images of order 256 took 3.7 ms on
 // small tiles, whose workgroups the device holds only a quarter of at a time, and 1.7 ms on wide ones).
@@ -373,11 +377,10 @@ template <bool WIDE>
 __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
                                                                  int W, SplitCtl* ctl, int* img_status, long long limit_ticks) {
   constexpr int TT = WIDE ? 2 * ST : ST;             // tile of the workgroup
-  constexpr int ES = WIDE ? 64 : 256;                // threads that store one 32 x 32 tile
   __shared__ double part[4 * ST * STP];
   __shared__ int s_flag;
   __shared__ double s_dev[4];
-  const int tid = threadIdx.x, wv = tid >> 6;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
   if (tid == 0) s_flag = (int)atomicAdd(&ctl[0].ticket, 1u);
   __syncthreads();
   const int ticket = s_flag;
@@ -400,22 +403,27 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
     target += nact;
     alive = image_barrier_wait<false>(&cb->bar, target, &s_flag, limit_ticks);
   };
-  // fn(r0, c0, first element, its LDS tile) on the 32 x 32 tile on or below the diagonal that this thread helps to store
+  // fn(r0, c0, above) on the 32 x 32 tiles on and below the diagonal that this wave helps to store; above: this one is above
+  // the diagonal (and left out)
   auto for_tiles = [&](auto fn) {
     for (int t = slot; t < ntiles; t += W) {
       int ti, tj;
       tile_of(t, ti, tj);
       if (WIDE) {
         const int qi = wv >> 1, qj = wv & 1;
-        fn(a + TT * ti + ST * qi, a + TT * tj + ST * qj, tid & 63, ti == tj && qj > qi);
+        fn(a + TT * ti + ST * qi, a + TT * tj + ST * qj, ti == tj && qj > qi);
       } else {
-        fn(a + TT * ti, a + TT * tj, tid, false);
+        fn(a + TT * ti, a + TT * tj, false);
       }
     }
   };
-  // the same with the tile's product X Z in LDS first
+  // fn(tile row, tile column), in units of 16, on the 16 x 16 tiles of a 32 x 32 tile, dealt to the waves that share it
+  auto for_frags = [&](int r0, int c0, auto fn) {
+    for (int q = WIDE ? 0 : wv; q < 4; q += WIDE ? 1 : 4) fn((r0 >> 4) + (q >> 1), (c0 >> 4) + (q & 1));
+  };
+  // the 32 x 32 tiles of the product X Z in LDS, then fn(r0, c0, sum) with sum(i, j) an element of it
   auto product = [&](const double* Z, auto fn) {
-    for_tiles([&](int r0, int c0, int e0, bool above) {
+    for_tiles([&](int r0, int c0, bool above) {
       double* mine = part + wv * (ST * STP);
       const int kn = WIDE ? P - a : (P - a) >> 2;     // P - a is a multiple of 64
       if (!above) tile_product<WIDE ? 2 : 3>(X, Z, P, WIDE ? a : a + wv * kn, kn, r0, c0, mine);
@@ -424,39 +432,67 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
         const double* q = (WIDE ? mine : part) + i * STP + j;
         return WIDE ? q[0] : (q[0] + q[ST * STP]) + (q[2 * ST * STP] + q[3 * ST * STP]);
       };
-      if (!above)
-        for (int e = e0; e < ST * ST; e += ES) fn(r0, c0, e >> 5, e & 31, sum);
+      if (!above) fn(r0, c0, sum);
       __syncthreads();
     });
   };
-  for_tiles([&](int r0, int c0, int e0, bool above) {
+  // a lane's element v of tile (rt, ct) is (16 rt + i16, 16 ct + 4 v + kq)
+  auto put = [&](double* M, int rt, int ct, const f64x4_t& x) {
+    double* t = M + tile16(rt, ct, P) + 2 * lane;
+    store_through(t, x[0]);
+    store_through(t + 1, x[1]);
+    store_through(t + 128, x[2]);
+    store_through(t + 129, x[3]);
+  };
+  for_tiles([&](int r0, int c0, bool above) {
     if (above) return;
-    for (int e = e0; e < ST * ST; e += ES) {
-      const int i = e >> 5, j = e & 31;
-      const long lo = r0 == c0 && j > i ? (long)(r0 + j) * P + c0 + i : (long)(r0 + i) * P + c0 + j;
-      store_through(&X[(long)(r0 + i) * P + c0 + j], (Hb[lo] - (r0 + i == c0 + j ? mu : 0.0)) * inv);
-      if (r0 != c0) store_through(&X[(long)(c0 + i) * P + r0 + j], Hb[(long)(r0 + j) * P + c0 + i] * inv);
-    }
+    for_frags(r0, c0, [&](int rt, int ct) {
+      f64x4_t x, y;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        // the element above the diagonal serves for both
+        const int i = 16 * rt + i16, j = 16 * ct + 4 * v + kq, i2 = 16 * ct + i16, j2 = 16 * rt + 4 * v + kq;
+        x[v] = ((i < j ? Hb[(long)i * P + j] : Hb[(long)j * P + i]) - (i == j ? mu : 0.0)) * inv;
+        y[v] = Hb[(long)(i2 < j2 ? i2 : j2) * P + (i2 < j2 ? j2 : i2)] * inv;
+      }
+      put(X, rt, ct, x);
+      if (r0 != c0) put(X, ct, rt, y);
+    });
   });
   meet();
   int step = 0;
 #pragma unroll 1
   for (; alive && !done && step < kMaxSignSteps; ++step) {
     const double s = sqrt(3.0 / (1.0 + l + l * l)), c1 = 1.5 * s, c3 = -0.5 * s * s * s;
-    product(X, [&](int r0, int c0, int i, int j, auto sum) {            // Y = X X
-      store_through(&Yb[(long)(r0 + i) * P + c0 + j], sum(i, j));    // a diagonal tile: the same products in the same order
-      if (r0 != c0) store_through(&Yb[(long)(c0 + i) * P + r0 + j], sum(j, i));
+    product(X, [&](int r0, int c0, auto sum) {       // Y = X X (a diagonal tile is symmetric: the same products in the same order)
+      for_frags(r0, c0, [&](int rt, int ct) {
+        const int i = 16 * rt - r0 + i16, j = 16 * ct - c0 + kq, i2 = 16 * ct - c0 + i16, j2 = 16 * rt - r0 + kq;
+        put(Yb, rt, ct, (f64x4_t){sum(i, j), sum(i, j + 4), sum(i, j + 8), sum(i, j + 12)});
+        if (r0 != c0) put(Yb, ct, rt, (f64x4_t){sum(j2, i2), sum(j2 + 4, i2), sum(j2 + 8, i2), sum(j2 + 12, i2)});
+      });
     });
     meet();
     if (!alive) break;
     double dev = 0.0;
-    product(Yb, [&](int r0, int c0, int i, int j, auto sum) {           // Xn = c1 X + c3 X Y
-      const double x = X[(long)(r0 + i) * P + c0 + j];
-      const double xn = fma(c3, r0 == c0 && j > i ? sum(j, i) : sum(i, j), c1 * x);
-      store_through(&Xn[(long)(r0 + i) * P + c0 + j], xn);
-      const double d = fabs(xn - x);
-      dev = d > dev || !(d == d) ? (d == d ? d : INFINITY) : dev;
-      if (r0 != c0) store_through(&Xn[(long)(c0 + i) * P + r0 + j], fma(c3, sum(j, i), c1 * X[(long)(c0 + i) * P + r0 + j]));
+    product(Yb, [&](int r0, int c0, auto sum) {      // Xn = c1 X + c3 X Y
+      for_frags(r0, c0, [&](int rt, int ct) {
+        const int i = 16 * rt - r0 + i16, j = 16 * ct - c0 + kq, i2 = 16 * ct - c0 + i16, j2 = 16 * rt - r0 + kq;
+        const f64x4_t x = frag_load(X + tile16(rt, ct, P), lane);
+        f64x4_t xn;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          xn[v] = fma(c3, r0 == c0 && j + 4 * v > i ? sum(j + 4 * v, i) : sum(i, j + 4 * v), c1 * x[v]);
+          const double d = fabs(xn[v] - x[v]);
+          dev = d > dev || !(d == d) ? (d == d ? d : INFINITY) : dev;
+        }
+        put(Xn, rt, ct, xn);
+        if (r0 != c0) {
+          const f64x4_t y = frag_load(X + tile16(ct, rt, P), lane);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) xn[v] = fma(c3, sum(j2 + 4 * v, i2), c1 * y[v]);
+          put(Xn, ct, rt, xn);
+        }
+      });
     });
     dev = wave_max(dev);
     if ((tid & 63) == 0) s_dev[wv] = dev;
@@ -475,13 +511,18 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
     double* tmp = X; X = Xn; Xn = tmp;
   }
   if (done) {
-    for_tiles([&](int r0, int c0, int e0, bool above) {
+    // the projector, row-major: the fragment of tile (row, column) is stored as tile (column, row)
+    for_tiles([&](int r0, int c0, bool above) {
       if (above) return;
-      for (int e = e0; e < ST * ST; e += ES) {
-        const int i = e >> 5, j = e & 31;
-        Yb[(long)(r0 + i) * P + c0 + j] = 0.5 * (X[(long)(r0 + i) * P + c0 + j] + (r0 + i == c0 + j ? 1.0 : 0.0));
-        if (r0 != c0) Yb[(long)(c0 + i) * P + r0 + j] = 0.5 * X[(long)(c0 + i) * P + r0 + j];
-      }
+      for_frags(r0, c0, [&](int rt, int ct) {
+        const f64x4_t x = frag_load(X + tile16(rt, ct, P), lane), y = frag_load(X + tile16(ct, rt, P), lane);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = 16 * rt + i16, j = 16 * ct + 4 * v + kq, i2 = 16 * ct + i16, j2 = 16 * rt + 4 * v + kq;
+          Yb[(long)j * P + i] = 0.5 * (x[v] + (i == j ? 1.0 : 0.0));
+          if (r0 != c0) Yb[(long)j2 * P + i2] = 0.5 * y[v];
+        }
+      });
     });
     for (int p = slot; p < P; p += nact)             // the rows and columns before a: identity
       for (int q = tid; q < (p < a ? P : a); q += 256) Yb[(long)p * P + q] = p == q ? 1.0 : 0.0;
