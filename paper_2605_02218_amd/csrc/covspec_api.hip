@@ -83,7 +83,7 @@ int make_plan(const covspec_params* p, Plan* pl) {
   q.dtype = p->dtype; q.rel = p->rel_mode; q.lr = p->lr_mode; q.M = M; q.r = r; q.k = k; q.lambda = p->lambda; q.seed = p->seed; q.image0 = 0;
   q.esz = p->dtype == COVSPEC_BF16 ? 2 : 4;
   q.planes = p->dtype == COVSPEC_BF16 ? 3 : 1;
-  q.nparts = p->dtype == COVSPEC_BF16 ? gemm_tiles_n(q.d) : gemm64_tiles_n(q.d);
+  q.nparts = p->dtype == COVSPEC_BF16 ? gemm_tiles_n(q.d) : gemm64_tiles_n((long)q.B * q.N, q.d, q.d);
   const size_t fsz = p->dtype == COVSPEC_BF16 ? 4 : 8;  // bytes per intermediate value
   q.nP = jacobi_pitch(M);
 

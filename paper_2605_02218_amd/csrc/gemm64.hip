@@ -27,6 +27,9 @@ constexpr int TK = 16, PITCH = TK + 1;
 // 32 x 32 tiles up to which gemm64_small_kernel is taken: beyond it the device is no longer short of workgroups and the
 // doubled operand traffic decides (192 x 320 x 320, 60 tiles: 10.6 against 20.2 us; 960 tiles would read 630 MB).
 constexpr long kSmallTiles = 384;
+// The same for operands that are not both fp64 (the alternative is the register-staged kernel, one wave per SIMD), in 64 x 64
+// tiles: up to one workgroup of that kernel per compute unit.
+constexpr long kSmallTiles64 = 256;
 // 64 x 64 tiles up to which k is split over two groups of waves: one workgroup per compute unit.
 constexpr long kFewTiles = 256;
 
@@ -401,10 +404,23 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   }
 }
 
-// The same for problems of few tiles: 32 x 32 tile, the four waves take a quarter of k each, operands straight from global
-// memory (rows in 128-byte pieces, three groups of 16 k in flight), the partial tiles added through LDS in a fixed order.
-// Twice the operand traffic of the 64 x 64 tile but four times the workgroups and a sixteenth of the dependent MFMAs.
-// 192 x 320 x 320, one image: 20.2 us register-staged, 10.6 here.  Requires K % 64 == 0, 32-byte aligned rows.
+// Four consecutive elements as fp64 (aligned to an element; the loads are 16 bytes wide all the same).
+typedef double f64x4_any __attribute__((ext_vector_type(4), aligned(8)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f64x4_t load4_f64(const double* p) { return *(const f64x4_any*)p; }
+__device__ __forceinline__ f64x4_t load4_f64(const float* p) {
+  const f32x4_any v = *(const f32x4_any*)p;
+  return (f64x4_t){(double)v[0], (double)v[1], (double)v[2], (double)v[3]};
+}
+
+// The same for problems of few tiles, fp64 or fp32 operands with optional row lists: 32 x 32 tile, the four waves take a
+// quarter of k each, operands straight from global memory (rows in pieces of 16 elements, three such groups in flight), the
+// partial tiles added through LDS in a fixed order.  Twice the operand traffic of a 64 x 64 tile but four times the
+// workgroups and a sixteenth of the dependent MFMAs.  us, 64 x 64 register-staged -> here: fp64 192 x 320 x 320 20.2 -> 10.6;
+// fp32 16 x 1024 x 1024 106 -> 15.7, 576 x 16 x 1024 96 -> 15.4, 128 x 128 x 1024 with row lists 138 -> 16.6, 576 x 1024 x 1024
+// row norms 145 -> 34.  Requires K % 64 == 0.
+// EPI: EPI_STORE_F64, or EPI_ROWNORM2 with one partial per 32 columns.
+template <typename TA, typename TB, int EPI>
 __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   __shared__ double part[4 * 32 * 33];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
@@ -414,12 +430,15 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
   if (g.lower_only && tn > tm) return;
   if (g.frag && tn < tm) return;
   const int row0 = tm * 32, col0 = tn * 32, kn = g.K >> 2;
-  const double* ar[2];
-  const double* br[2];
+  const TA* ar[2];
+  const TB* br[2];
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
-    ar[x] = (const double*)g.A + (long)b * g.strideA + (long)min(row0 + 16 * x + i16, g.M - 1) * g.lda + w * kn + 4 * kq;
-    br[x] = (const double*)g.B + (long)b * g.strideB + (long)min(col0 + 16 * x + i16, g.N - 1) * g.ldb + w * kn + 4 * kq;
+    long ra = min(row0 + 16 * x + i16, g.M - 1), rb = min(col0 + 16 * x + i16, g.N - 1);
+    if (g.gatherA) ra = g.gatherA[(long)b * g.gstrideA + ra];
+    if (g.gatherB) rb = g.gatherB[(long)b * g.gstrideB + rb];
+    ar[x] = (const TA*)g.A + (long)b * g.strideA + ra * g.lda + w * kn + 4 * kq;
+    br[x] = (const TB*)g.B + (long)b * g.strideB + rb * g.ldb + w * kn + 4 * kq;
   }
   constexpr int DEPTH = 3;
   f64x4_t acc[2][2], fa[DEPTH][2], fb[DEPTH][2];
@@ -432,8 +451,8 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     if (c < nc) {
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
-        fa[s][x] = *(const f64x4_t*)(ar[x] + 16 * c);
-        fb[s][x] = *(const f64x4_t*)(br[x] + 16 * c);
+        fa[s][x] = load4_f64(ar[x] + 16 * c);
+        fb[s][x] = load4_f64(br[x] + 16 * c);
       }
     }
   };
@@ -467,6 +486,17 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
   };
   double* C = (double*)g.C + (long)b * g.strideC;
+  if (EPI == EPI_ROWNORM2) {                              // eight lanes per row, four columns each; columns beyond N count as zero
+    const int i = tid >> 3, j0 = (tid & 7) * 4;
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (col0 + j0 + j < g.N) { const double v = sum(i, j0 + j); s = fma(v, v, s); }
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((tid & 7) == 0 && row0 + i < g.M) C[(long)(row0 + i) * g.ldc + tn] = s;
+    return;
+  }
   if (g.frag) {                                           // wave w: 16 x 16 tile (w / 2, w % 2) of the transposed product
     const int sr = w >> 1, sc = w & 1;
     f64x4_t v;
@@ -482,14 +512,23 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
   }
 }
 
+// Can gemm64_small_kernel take the product?
+inline bool small_fits(const GemmArgs& g) { return g.batch > 0 && g.batch_inner == 1 && !g.transB && g.K >= 64 && g.K % 64 == 0; }
+
+template <typename TA, typename TB, int EPI>
+hipError_t launch_small(const GemmArgs& g, hipStream_t stream) {
+  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, blocks = m32 * n32 * g.batch;
+  if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemm64_small_kernel<TA, TB, EPI>), dim3((unsigned)blocks), dim3(256), 0, stream, g, (int)m32, (int)n32);
+  return hipGetLastError();
+}
+
+inline long tiles64(const GemmArgs& g) { return (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch; }
+
 hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
   if (g.frag && (g.M != g.N || g.N % 64 != 0)) return hipErrorInvalidValue;
   const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, t32 = (g.lower_only || g.frag ? n32 * (n32 + 1) / 2 : m32 * n32) * g.batch;
-  if (t32 <= kSmallTiles && g.K % 64 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.strideA % 4 == 0 && g.strideB % 4 == 0 &&
-      (((uintptr_t)g.A | (uintptr_t)g.B) & 31) == 0) {
-    hipLaunchKernelGGL(gemm64_small_kernel, dim3((unsigned)(m32 * n32 * g.batch)), dim3(256), 0, stream, g, (int)m32, (int)n32);
-    return hipGetLastError();
-  }
+  if (t32 <= kSmallTiles && small_fits(g)) return launch_small<double, double, EPI_STORE_F64>(g, stream);
   const long m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, blocks = m64 * n64 * g.batch;
   const long t64 = (g.lower_only || g.frag ? n64 * (n64 + 1) / 2 : m64 * n64) * g.batch;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
@@ -536,9 +575,16 @@ inline bool big_tiles(const GemmArgs& g) {
   return nb >= 256;
 }
 
+// Row norms are decided by sizes alone: the number of partials is part of a plan.
+inline bool rownorm_small(long M, int N, int K) { return ((M + 63) / 64) * ((N + 63) / 64) <= kSmallTiles64 && K >= 64 && K % 64 == 0; }
+
 template <typename TA, typename TB>
 hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   const bool gather = g.gatherA || g.gatherB;
+  constexpr bool f64x2 = std::is_same<TA, double>::value && std::is_same<TB, double>::value;
+  if constexpr (!f64x2 && !std::is_same<TA, bf16_t>::value) {
+    if (g.epilogue == EPI_STORE_F64 && tiles64(g) <= kSmallTiles64 && small_fits(g)) return launch_small<TA, TB, EPI_STORE_F64>(g, stream);
+  }
   if (g.transB) {
     if (gather) return hipErrorInvalidValue;
     if (g.epilogue == EPI_STORE_F64)
@@ -549,19 +595,24 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   }
   if (g.epilogue == EPI_STORE_F64) {
     if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, false, 2, 2>(g, stream);
-    if (std::is_same<TA, double>::value && std::is_same<TB, double>::value && plain_f64(g)) return launch_plain_f64(g, stream);
+    if (f64x2 && plain_f64(g)) return launch_plain_f64(g, stream);
     if (g.frag) return hipErrorInvalidValue;
     return launch_cfg<TA, TB, EPI_STORE_F64, false, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;
   if (g.epilogue == EPI_SUB_F64) return launch_cfg<TA, TB, EPI_SUB_F64, false, false, 2, 2>(g, stream);
-  if (g.epilogue == EPI_ROWNORM2) return launch_cfg<TA, TB, EPI_ROWNORM2, false, false, 2, 2>(g, stream);
+  if (g.epilogue == EPI_ROWNORM2) {
+    if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value) {
+      if (g.batch == 1 && g.batch_inner == 1 && rownorm_small(g.M, g.N, g.K)) return launch_small<TA, TB, EPI_ROWNORM2>(g, stream);
+    }
+    return launch_cfg<TA, TB, EPI_ROWNORM2, false, false, 2, 2>(g, stream);
+  }
   return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-int gemm64_tiles_n(int N) { return (N + 63) / 64; }   // ROWNORM2 always runs with 64-column tiles
+int gemm64_tiles_n(long M, int N, int K) { return rownorm_small(M, N, K) ? (N + 31) / 32 : (N + 63) / 64; }
 
 hipError_t launch_gemm64_store_dot(const GemmArgs& g, hipStream_t stream) {
   if (!g.transB || !g.D || !g.dots || g.gatherA || g.gatherB) return hipErrorInvalidValue;

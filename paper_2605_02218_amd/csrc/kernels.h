@@ -52,8 +52,8 @@ hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream);
 
 // ---------------------------------------------------------------- gemm64.hip
 // Same contraction entirely in fp64 (v_mfma_f64_16x16x4); A and B are fp32 or fp64, C is fp64.
-// Epilogues: EPI_STORE_F64, EPI_ROWNORM2 (fp64 partials, one per 64-column tile).
-int gemm64_tiles_n(int N);
+// Epilogues: EPI_STORE_F64, EPI_ROWNORM2 (fp64 partials, gemm64_tiles_n(M, N, K) per row, for fp32 operands of one batch).
+int gemm64_tiles_n(long M, int N, int K);
 hipError_t launch_gemm64_nt(const GemmArgs& g, bool a_is_f64, bool b_is_f64, hipStream_t stream);
 // C = A * B (B stored [K][N]), and g.dots: per 64-row tile the column sums of C * D, elementwise.
 hipError_t launch_gemm64_store_dot(const GemmArgs& g, hipStream_t stream);

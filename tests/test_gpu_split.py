@@ -68,3 +68,22 @@ def test_equal_eigenvalues_at_the_cut_still_give_a_result(C):
         c = out["c"].cpu().double()
         assert c.min() > -1e-6 and c.max() < 4.0 + 1e-5 and abs(c.sum() - 80.0) < 1e-4, (n, c.sum())
         assert len(set(out["idx"][0].tolist())) == 10
+
+
+@pytest.mark.parametrize("B,N,d,T", [(1, 33, 64, 1), (1, 65, 320, 5), (2, 128, 192, 33), (1, 1100, 1024, 16), (1, 40, 72, 3), (3, 700, 1024, 8)],
+                         ids=["one-k-step", "remainders", "batch", "row-norms-of-few-tiles", "width-not-64", "row-norms-of-many-tiles"])
+def test_fp32_scores_on_few_tiles_match_the_oracle(C, B, N, d, T):
+    """The fp32 path's products on 32 x 32 tiles and, beyond their range (many tiles, a width that is no multiple of 64),
+    on the 64 x 64 ones; X starts at an odd element, so that no row is aligned to more than four bytes."""
+    import torch
+    g = torch.Generator().manual_seed(N)
+    X0 = torch.randn(B * N * d + 1, generator=g).cuda()
+    X = X0[1:].view(B, N, d)
+    Q = torch.randn(B, T, d, generator=g).cuda()
+    Wq, Wk = (torch.randn(2, d, d, generator=g) / d ** 0.5).cuda()
+    p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=T, dtype=C.FP32, keep_k=4, preselect_m=8, rank_r=2)
+    sq, _, _ = C.score(p, X, None, Q, Wq, Wk)
+    v, q = X.double().cpu() @ Wk.double().cpu(), Q.double().cpu() @ Wq.double().cpu()
+    ref = torch.nn.functional.normalize(v, dim=-1) @ torch.nn.functional.normalize(q, dim=-1).transpose(1, 2)
+    # a maximum over T cosines of N(0, 1/d); everything but the result's rounding to fp32 (6e-8 of 1) is fp64
+    assert (sq.double().cpu() - ref.amax(2)).abs().max() < 1e-7
