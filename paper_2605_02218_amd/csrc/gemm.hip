@@ -738,6 +738,18 @@ hipError_t launch_e(const GemmArgs& g, hipStream_t stream) {
 
 int gemm_tiles_n(int N) { return (N + 127) / 128; }
 
+// A 128 x 128 tile walks over k at about a microsecond per 128-byte step, whatever the rest of the device does, so fewer
+// tiles than compute units are cut along k until there are two per compute unit or a part is four steps long.  Measured, us,
+// with the launch that adds the parts: 32 x 4096 x 4096 (32 tiles, 8 parts) 55 + 22 -> 12 + 13, 576 x 96 x 4096 (5 tiles, 16
+// parts) 55 + 5 -> 9 + 10, 444 x 3584 x 3584 (112 tiles, 4 parts) 70 + 25 -> 31 + 10; 1332 x 3584 x 3584 has 308 tiles and stays
+// whole.
+int gemm_nt_splits(long M, long N, long K, long batch) {
+  const long tiles = ((M + 127) / 128) * ((N + 127) / 128) * batch;
+  if (tiles >= 192) return 1;
+  int s = 1;
+  while (s < 16 && tiles * s * 2 <= 512 && K % (64L * s * 2) == 0 && K / (s * 2) >= 256) s *= 2;
+  return s;
+}
 
 hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream) {
   return dtype == DT_BF16 ? launch_e<bf16_t>(g, stream) : launch_e<float>(g, stream);
