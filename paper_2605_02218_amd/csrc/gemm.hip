@@ -665,6 +665,109 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_gram_dma_kernel(GemmArgs g, i
       }
 }
 
+// The same for products of few tiles (the Gram matrix of one image's or a few images' rows): 32 x 32 tile, four waves that
+// each take a quarter of k in steps of 64, loaded straight into a ring of three 8 KB stages of the wave's own (no barrier in
+// the loop), one MFMA accumulator per wave, flushed into fp64 every 256 k; the four partial tiles are added in a fixed order.
+// A 128 x 128 tile has no more than 6 workgroups for 288 rows and walks all of k in each: 85 us for 288 x 288 x 4096,
+// 10.8 here (four images of 256 x 256 x 1536: 35 -> 7.5).  Requires K % 64 == 0 and 16-byte aligned rows.
+__global__ __launch_bounds__(THREADS) void gemm_gram_small_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int NST = 3, STAGE = 2 * 32 * ROWB;       // bytes: A tile then B tile
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, lh = lane >> 5;
+  const int per = tiles_m * tiles_n;
+  const int b = blockIdx.x / per, pidx = blockIdx.x - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
+  if (g.lower_only && tn > tm) return;
+  const int row0 = tm * 32, col0 = tn * 32;
+  const bf16_t* __restrict__ A = (const bf16_t*)g.A + (long)b * g.strideA;
+  const bf16_t* __restrict__ B = (const bf16_t*)g.B + (long)b * g.strideB;
+  const int nc = g.K >> 6, c0 = nc * wave / 4, c1 = nc * (wave + 1) / 4;     // this wave's steps
+  // load j fills tile rows 8j .. 8j + 7: lane l -> row 8j + l / 8, 16-byte slot l % 8 (see swz)
+  const bf16_t* ga[4];
+  const bf16_t* gb[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    long ra = min(row0 + r, g.M - 1), rb = min(col0 + r, g.N - 1);
+    if (g.gatherA) ra = g.gatherA[(long)b * g.gstrideA + ra];
+    if (g.gatherB) rb = g.gatherB[(long)b * g.gstrideB + rb];
+    ga[j] = A + ra * g.lda + c * 8;
+    gb[j] = B + rb * g.ldb + c * 8;
+  }
+  unsigned char* ring = smem + wave * (NST * STAGE);
+  auto issue = [&](int c, int st) {
+    const long k = 64L * (c < nc ? c : nc - 1);       // past the end: a step whose values are not used
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[j] + k),
+                                       (__attribute__((address_space(3))) void*)(ring + st * STAGE + j * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[j] + k),
+                                       (__attribute__((address_space(3))) void*)(ring + st * STAGE + 32 * ROWB + j * 1024), 16, 0, 0);
+    }
+  };
+  f32x16_t acc;
+  double acc64[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) { acc[v] = 0.f; acc64[v] = 0.0; }
+  issue(c0, 0);
+  issue(c0 + 1, 1);
+  int st = 0;
+#pragma unroll 1
+  for (int c = c0; c < c1; ++c) {
+    issue(c + 2, st == 0 ? 2 : st - 1);               // the stage read in the previous step: those reads fed its MFMAs
+    __builtin_amdgcn_s_waitcnt(0x4070);               // vmcnt(16) lgkmcnt(0): this step has landed, the next two are under way
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned char* sa = ring + st * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(sa + swz(li, 2 * ks + lh)));
+      const bf16x8_t bb = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(sa + 32 * ROWB + swz(li, 2 * ks + lh)));
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, acc, 0, 0, 0);
+    }
+    if (((c - c0) & 3) == 3 || c + 1 == c1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { acc64[v] += (double)acc[v]; acc[v] = 0.f; }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    st = st == 2 ? 0 : st + 1;
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);                 // the loads past the end as well
+  __syncthreads();
+  double* part = (double*)smem;                       // [4][32][33]
+#pragma unroll
+  for (int v = 0; v < 16; ++v) part[wave * (32 * 33) + (8 * (v >> 2) + 4 * lh + (v & 3)) * 33 + li] = acc64[v];
+  __syncthreads();
+  auto sum = [&](int i, int j) {
+    const double* q = part + i * 33 + j;
+    return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
+  };
+  double* C = (double*)g.C + (long)b * g.strideC;
+  for (int e = tid; e < 32 * 32; e += THREADS) {
+    const int i = e >> 5, j = e & 31;
+    if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = sum(i, j);
+    if (g.mirror && tn != tm && row0 + j < g.M && col0 + i < g.N) C[(long)(col0 + i) * g.ldc + row0 + j] = sum(j, i);
+  }
+}
+
+inline hipError_t launch_gram_small(const GemmArgs& g, hipStream_t stream) {
+  constexpr int LDS = 4 * 3 * 2 * 32 * ROWB;
+  const long tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32, nblocks = tiles_m * tiles_n * g.batch;
+  if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
+  static PerDeviceInt raised;
+  const hipError_t attr = ensure_dynamic_lds(raised, (const void*)gemm_gram_small_kernel, LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(gemm_gram_small_kernel, dim3((unsigned)nblocks), dim3(THREADS), LDS, stream, g, (int)tiles_m, (int)tiles_n);
+  return hipGetLastError();
+}
+
+// 32 x 32 tiles of the product that are computed
+inline long tiles32(const GemmArgs& g) {
+  const long m = (g.M + 31) / 32, n = (g.N + 31) / 32;
+  return (g.lower_only ? n * (n + 1) / 2 : m * n) * g.batch;
+}
+
+// Tiles up to which gemm_gram_small_kernel is taken: two rounds of its one workgroup per compute unit.
+constexpr long kGramSmallTiles = 512;
+
 inline hipError_t launch_gram_dma(const GemmArgs& g, hipStream_t stream) {
   constexpr int BT = 128, LDS = 4 * 2 * BT * 64;
   const int tiles_m = (g.M + BT - 1) / BT, tiles_n = (g.N + BT - 1) / BT;
@@ -707,7 +810,9 @@ inline bool aligned16(const GemmArgs& g) {
 template <typename In, int EPI>
 hipError_t launch_t(const GemmArgs& g, hipStream_t stream) {
   if constexpr (std::is_same<In, bf16_t>::value && EPI == EPI_STORE_F64) {
-    // fp64 results from bf16 rows (gathered or not): the direct-to-LDS kernel when the shape allows it
+    // fp64 results from bf16 rows (gathered or not): the direct-to-LDS kernels when the shape allows it
+    if (aligned16(g) && g.K % 64 == 0 && g.K >= 256 && g.M >= 1 && g.N >= 1 && g.batch >= 1 && g.batch_inner == 1 && tiles32(g) <= kGramSmallTiles)
+      return launch_gram_small(g, stream);
     if (aligned16(g) && g.K % 32 == 0 && g.K >= 32 && g.M >= 1 && g.N >= 1 && (long)g.M * g.N * g.batch >= 128L * 128 * 64)
       return launch_gram_dma(g, stream);
   }

@@ -37,3 +37,26 @@ def test_scores_with_k_in_parts(C, mode, B, N, d, T, weights):
         ref = sum(torch.softmax(q[..., a:a + dh] @ v[..., a:a + dh].transpose(1, 2) / dh ** 0.5, 2).mean(1) for a in range(0, d, dh)) / H
         # the same error in a logit of size up to ~ sqrt(dh) (unscaled ~ dh), relative in a probability
         assert ((got - ref).abs() / ref).max() < 4 * d ** 0.5 * 2 ** -24 * max(1.0, dh ** 0.5)
+
+
+@pytest.mark.parametrize("B,N,M,d", [(1, 40, 33, 256), (3, 200, 129, 320), (1, 400, 288, 1088), (2, 600, 600, 512)],
+                         ids=["remainder-tiles", "five-steps-over-four-waves", "one-image", "more-tiles"])
+def test_gram_matrix_of_few_tiles(C, B, N, M, d):
+    """The energies of rank M - 1 ... of the pre-selected rows sum to nearly the trace of their Gram matrix, row by row |z_i|^2
+    less the last eigenpair's part: compared with the fp64 eigen-decomposition."""
+    import torch
+    g = torch.Generator().manual_seed(M)
+    scale = 0.97 ** torch.arange(d, dtype=torch.float32)
+    X = (torch.randn(B, N, d, generator=g) * scale).bfloat16().cuda()
+    s = torch.rand(B, N, generator=g).cuda()
+    r = min(20, M // 2)
+    p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=1, dtype=C.BF16, keep_k=8, preselect_m=M, rank_r=r)
+    out = C.select(p, X, s)
+    for b in range(B):
+        rows = out["idx_m"][b].long()
+        Z = X[b][rows].double().cpu()
+        lam, V = torch.linalg.eigh(Z @ Z.t())
+        ref = (V[:, -r:] ** 2 * lam[-r:]).sum(1)
+        err = (out["c"][b].double().cpu() - ref).abs() / ref.clamp_min(1e-3 * ref.max())
+        # fp32 sums over 256 products (2^-24 each, random walk), magnified by the gap at the cut (relative 1 - 0.97^2, 0.06)
+        assert err.max() < 4 * 16 * 2 ** -24 / 0.06
