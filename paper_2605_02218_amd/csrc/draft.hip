@@ -4,11 +4,15 @@
 // than the drafted token.
 //
 // Scan kernel, one workgroup per chunk of 8192 words of one row: every thread keeps its 32 logits in
-// registers, accumulates the streaming softmax statistics, and the chunk's K = F_0 + 1 largest logits are
+// registers as loaded, accumulates the streaming softmax statistics, and the chunk's K = F_0 + 1 largest logits are
 // found by a threshold instead of K rounds of a block-wide argmax: tau = the K-th largest of the 64 quad
 // maxima, so at least K logits are >= tau and, for continuous data, only about K more; those few go to a list
 // in LDS that one wave ranks by all-pairs comparison.  A list that overflows (many equal logits, or fewer than
 // K quads with data) falls back to K rounds of block-wide argmax over the registers: slower, same result.
+// Bound by the latency of a workgroup's dozen phases, so by how many of them a compute unit holds: with the logits widened to
+// fp32 and the fallback's packed keys formed ahead of its loop the kernel took 87 registers (5 waves per SIMD) and 49 us for
+// 512 rows of 151936 bf16 words; with the logits kept as loaded, one reference per thread instead of a running one and the
+// few candidate threads' logits looked through in LDS it takes 64 registers and 33 us (4.7 TB/s).
 // Merge kernel, one wave per row: combines the chunks' statistics in fp64, merges their candidate lists,
 // evaluates the margin and writes gate and candidates.
 #include "common.h"
@@ -26,6 +30,7 @@ constexpr int EPT = 32;                   // logits per thread
 constexpr int DCL = DTH * EPT;            // words per chunk
 constexpr int KMAX = 33;                  // F_0 <= 32, plus one for the drafted token
 constexpr int LISTCAP = 64;               // threshold list: one entry per lane of the ranking wave
+constexpr int POOL = 64;                  // threads whose logits are looked through one by one
 constexpr int MAXCHUNKS = 64;             // the merge kernel keeps chunks * K keys in LDS
 
 // (order key of the logit, ~word): larger logit first, lower word first among equal logits; never 0 for a real entry
@@ -56,7 +61,7 @@ struct FanTable { unsigned char f[64]; };   // F_j by position inside the drafte
 // stats[(row * chunks + c) * 2 + {0,1}] = reference, sum (base-2 domain); top[(row * chunks + c) * KMAX + r],
 // r < K: the chunk's r-th largest logit as a packed key, 0 where the chunk has fewer.
 template <int DT>
-__global__ __launch_bounds__(DTH) void draft_scan_kernel(const void* __restrict__ zd, int V, int chunks, int K,
+__global__ __launch_bounds__(DTH, DT == DT_F32 ? 6 : 8) void draft_scan_kernel(const void* __restrict__ zd, int V, int chunks, int K,
                                                          double* __restrict__ stats, u64* __restrict__ top) {
   constexpr int N = LogitVec<DT>::N;
   constexpr int NV = EPT / N;
@@ -65,39 +70,68 @@ __global__ __launch_bounds__(DTH) void draft_scan_kernel(const void* __restrict_
   __shared__ u64 wbest[DTH / 64];
   __shared__ double red[DTH / 64][2];
   __shared__ float sh_tau;
-  __shared__ int sh_cnt;
+  __shared__ int sh_cnt, sh_found;
+  __shared__ u32x4_t pool[POOL][NV];      // EPT logits of a thread, as loaded
+  __shared__ int pool_id[POOL];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const long row = blockIdx.y;
   const int c = blockIdx.x;
   const int w0 = c * DCL, w1 = min(V, w0 + DCL);      // V % N == 0: whole vectors only
   const long base = row * (long)V;
 
-  // a slot without a word, or with a NaN logit, compares false against every threshold and is skipped by max
-  float v[EPT];
-  uint32_t valid = 0u;                 // whole vectors: bits i*N .. i*N+N-1
-  float cref = -INFINITY, sum = 0.f, tmax = -INFINITY;
+  // The logits stay as they were loaded (16-bit types: two per register) and are widened where they are used.  A slot without
+  // a word holds NaN: like a NaN logit it compares false against every threshold and is skipped by max.
+  constexpr uint32_t kNoWord = DT == DT_BF16 ? 0x7FC07FC0u : DT == DT_F16 ? 0x7E007E00u : 0x7FC00000u;
+  u32x4_t raw[NV];
+  int nv = 0;                          // vectors with words
+  float vmax[NV];                      // per vector, NaN ignored
+  float tmax = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int w = w0 + (i * DTH + tid) * N;
+    raw[i] = (u32x4_t){kNoWord, kNoWord, kNoWord, kNoWord};
     if (w < w1) {
-      float t[N];
-      LogitVec<DT>::load(zd, base + w, t);
-      tmax = fmaxf(tmax, online_add<N>(cref, sum, t));
-      valid |= ((N == 8 ? 0xFFu : 0xFu) << (i * N));
-#pragma unroll
-      for (int e = 0; e < N; ++e) v[i * N + e] = t[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < N; ++e) v[i * N + e] = __builtin_nanf("");
+      raw[i] = LogitVec<DT>::load_raw(zd, base + w);
+      nv = i + 1;
     }
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    float t[N];
+    LogitVec<DT>::unpack(raw[i], t);
+    vmax[i] = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < N; ++e) vmax[i] = fmaxf(vmax[i], t[e]);
+    tmax = fmaxf(tmax, vmax[i]);
+  }
+  // streaming pair of all the thread's logits at once: they are in registers, so the reference is their maximum and no
+  // partial sum is ever rescaled (see vocab.h for the base-2 domain)
+  const float cref = tmax * kLog2e;
+  float sum = 0.f;
+  {
+    const float cn = cref == -INFINITY ? 0.f : cref;      // only masked words: any finite reference gives zeros
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if (i < nv) {
+        float t[N];
+        LogitVec<DT>::unpack(raw[i], t);
+#pragma unroll
+        for (int e = 0; e < N; e += 2) {
+          s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(t[e], kLog2e, -cn));
+          s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(t[e + 1], kLog2e, -cn));
+        }
+      }
+    sum = s0 + s1;
   }
   auto word_of = [&](int e) { return w0 + ((e / N) * DTH + tid) * N + (e % N); };
 
   // quad maxima -> tau
+  const float own = tmax;
   tmax = fmaxf(tmax, __shfl_xor(tmax, 1, 64));
   tmax = fmaxf(tmax, __shfl_xor(tmax, 2, 64));
   if ((lane & 3) == 0) gkey[tid >> 2] = ((u64)float_order_key(tmax) << 32) | (u64)(63 - (tid >> 2));
-  if (tid == 0) sh_cnt = 0;
+  if (tid == 0) { sh_cnt = 0; sh_found = 0; }
   {
     double mm, ss;
     block_combine<DTH / 64>(cref, sum, red, mm, ss);      // its barrier also publishes gkey and sh_cnt
@@ -112,15 +146,29 @@ __global__ __launch_bounds__(DTH) void draft_scan_kernel(const void* __restrict_
   }
   __syncthreads();
   const float tau = sh_tau;
+  // the few threads that hold a logit of tau or more (K quads and a few) put all of theirs into LDS, where the whole
+  // workgroup looks through them: 32 compare-and-branch steps of every wave cost more than that
+  if (own >= tau) {
+    const int pos = atomicAdd(&sh_cnt, 1);
+    if (pos < POOL) {
+      pool_id[pos] = tid;
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    if (v[e] >= tau) {
-      const int pos = atomicAdd(&sh_cnt, 1);
-      if (pos < LISTCAP) list[pos] = pack_key(v[e], word_of(e));
+      for (int i = 0; i < NV; ++i) pool[pos][i] = raw[i];
     }
   }
   __syncthreads();
-  const int n = sh_cnt;
+  const int holders = sh_cnt;
+  if (holders <= POOL) {
+    for (int i = tid; i < holders * EPT; i += DTH) {
+      const float x = (float)LogitVec<DT>::at(&pool[0][0], i);
+      if (x >= tau) {
+        const int e = i % EPT, pos = atomicAdd(&sh_found, 1);
+        if (pos < LISTCAP) list[pos] = pack_key(x, w0 + ((e / N) * DTH + pool_id[i / EPT]) * N + e % N);
+      }
+    }
+  }
+  __syncthreads();
+  const int n = holders <= POOL ? sh_found : LISTCAP + 1;
   u64* out = top + (row * chunks + c) * KMAX;
   if (n <= LISTCAP) {
     if (wv == ((rw + 2) & 3)) {
@@ -132,14 +180,20 @@ __global__ __launch_bounds__(DTH) void draft_scan_kernel(const void* __restrict_
     return;
   }
   // fallback: K rounds of block-wide argmax over the registers
-  uint32_t alive = valid;
+  uint32_t alive = nv * N >= 32 ? 0xFFFFFFFFu : (1u << (nv * N)) - 1u;      // whole vectors: bits i*N .. i*N+N-1
   for (int r = 0; r < K; ++r) {
     u64 best = 0ull;
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      if (((alive >> e) & 1u) && v[e] == v[e]) {
-        const u64 k = pack_key(v[e], word_of(e));
-        best = k > best ? k : best;
+    for (int i = 0; i < NV; ++i) {
+      float t[N];
+      asm volatile("" : "+v"(raw[i]));      // keeps the 32 packed keys from being formed ahead of the loop, 64 registers
+      LogitVec<DT>::unpack(raw[i], t);
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        if (((alive >> (i * N + e)) & 1u) && t[e] == t[e]) {
+          const u64 k = pack_key(t[e], word_of(i * N + e));
+          best = k > best ? k : best;
+        }
       }
     }
     best = wave_max(best);
