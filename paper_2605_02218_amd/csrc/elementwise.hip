@@ -118,6 +118,35 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
     if (c0 + c < cols && r0 + tx < rows) out[(long)(c0 + c) * rows + r0 + tx] = tile[tx][c];
 }
 
+// The same in 16-byte pieces: a thread loads two pieces of a row into LDS and stores two pieces of a column from it.  64 x 64
+// tiles of E-byte elements, rows and cols multiples of 16 / E, 16-byte aligned.  3584 x 3584 bf16: 27.5 us with an element per
+// access, 11.4 here (51 MB).
+template <typename T>
+__global__ __launch_bounds__(256) void transpose16_kernel(const T* __restrict__ in, T* __restrict__ out, int rows, int cols) {
+  constexpr int N = 16 / sizeof(T), PER = 64 / N;      // elements per piece, pieces per tile row
+  __shared__ T tile[64][64 + 4 / sizeof(T)];           // a row is an odd number of banks
+  typedef T piece_t __attribute__((ext_vector_type(N)));
+  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+  for (int e = threadIdx.x; e < 64 * PER; e += 256) {
+    const int r = e / PER, c = e % PER * N;
+    if (r0 + r < rows && c0 + c < cols) {
+      const piece_t v = *(const piece_t*)(in + (long)(r0 + r) * cols + c0 + c);
+#pragma unroll
+      for (int k = 0; k < N; ++k) tile[r][c + k] = v[k];
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 64 * PER; e += 256) {
+    const int c = e / PER, r = e % PER * N;
+    if (c0 + c < cols && r0 + r < rows) {
+      piece_t v;
+#pragma unroll
+      for (int k = 0; k < N; ++k) v[k] = tile[r + k][c];
+      *(piece_t*)(out + (long)(c0 + c) * rows + r0 + r) = v;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- conversion / splitting
 template <typename In, typename Out>
 __global__ void convert_kernel(const In* __restrict__ src, Out* __restrict__ dst, long n) {
@@ -500,6 +529,12 @@ __global__ void fill_int_kernel(int* __restrict__ p, int n, int value) {
 
 hipError_t launch_transpose(const void* in, void* out, int rows, int cols, int dtype, hipStream_t st) {
   dim3 grid((cols + 63) / 64, (rows + 63) / 64), block(256);
+  const int piece = dtype == DT_BF16 ? 8 : 4;
+  if (rows % piece == 0 && cols % piece == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0) {
+    if (dtype == DT_BF16) hipLaunchKernelGGL((transpose16_kernel<bf16_t>), grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, rows, cols);
+    else hipLaunchKernelGGL((transpose16_kernel<float>), grid, block, 0, st, (const float*)in, (float*)out, rows, cols);
+    return hipGetLastError();
+  }
   if (dtype == DT_BF16) hipLaunchKernelGGL((transpose_kernel<bf16_t>), grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, rows, cols);
   else hipLaunchKernelGGL((transpose_kernel<float>), grid, block, 0, st, (const float*)in, (float*)out, rows, cols);
   return hipGetLastError();
