@@ -15,8 +15,8 @@
 // Before: the P x P problem was diagonalised by block Jacobi (six sweeps of P/32 - 1 rounds of 32 dependent rotation
 // steps each).  An eigen-decomposition orders every pair of rows; the energies only ask which side of the cut a
 // direction is on, and the products that answer that are matrix-core work without a serial chain of rotations.
-// Jacobi against split + sign, us: one matrix of order 128 2727 -> 143 + 131, one of 192 1482 -> 144 + 197, four of 192
-// 1769 -> 144 + 200, eight of 384 3551 -> 144 + 259, sixty-four of 256 3894 -> 144 + 1061.
+// Jacobi against split + sign, us: one matrix of order 128 2727 -> 124 + 131, one of 192 1482 -> 124 + 197, four of 192
+// 1769 -> 124 + 200, eight of 384 3551 -> 124 + 259, sixty-four of 256 3894 -> 124 + 1061.
 //
 // Leading rows [0, a) of an ordered H that do not couple to the rows around and beyond the cut (kLeadFar) and whose
 // eigenvalues are above mu by their diagonal (row sums of the scaled couplings below 1/2: no eigenvalue of the block is
@@ -48,20 +48,28 @@ struct SplitCtl {
   double mu, inv_norm, l0, theta;              // cut, 1 / norm, lower bound on |eigenvalues of X|, r-th eigenvalue
 };
 
-// sum over the 16 lanes of a DPP row, the same in all of them
+// Sums over the 16 lanes of a DPP row, the same in all of them; of X0..7 at once, so that the steps of one fill the waits of
+// the others.
+template <int CTRL>
+__device__ __forceinline__ double row_rotated(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true), __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+template <int FIRST>
+__device__ __forceinline__ void row16_sums(double (&v)[8]) {
+#pragma unroll
+  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x128>(v[x]);
+#pragma unroll
+  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x124>(v[x]);
+#pragma unroll
+  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x122>(v[x]);
+#pragma unroll
+  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x121>(v[x]);
+}
 __device__ __forceinline__ double row16_sum(double v) {
-#define COVSPEC_ROR_ADD(n)                                                                                  \
-  {                                                                                                         \
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + (n), 0xf, 0xf, false);         \
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + (n), 0xf, 0xf, false);         \
-    v += __hiloint2double(hi, lo);                                                                          \
-  }
-  COVSPEC_ROR_ADD(8)
-  COVSPEC_ROR_ADD(4)
-  COVSPEC_ROR_ADD(2)
-  COVSPEC_ROR_ADD(1)
-#undef COVSPEC_ROR_ADD
-  return v;
+  v += row_rotated<0x128>(v);
+  v += row_rotated<0x124>(v);
+  v += row_rotated<0x122>(v);
+  return v + row_rotated<0x121>(v);
 }
 
 // Per row p of H: off[p] = sum over q != p of |H_pq|, and link[p] = the largest coupling to the rows from r - 32 on as a
@@ -129,9 +137,16 @@ __device__ __forceinline__ void reflect_block(double (&A)[8][8], double* xs, dou
 #pragma unroll
     for (int y = a0; y < 8; ++y) ss = fma(v[y], v[y], ss);
     ss = row16_sum(ss);
-    const double nrm = sqrt(ss);
-    const double den = fma(fabs(alpha), nrm, ss);
-    const double hinv = den > 1e-280 ? 1.0 / den : 0.0;      // a row that is zero already needs no reflection
+    // |row|, and 1 / (|row|^2 + |alpha| |row|): estimates refined by Newton steps.  A row that is zero needs no reflection.
+    const bool zero = !(ss > 1e-280);
+    const double rs = __builtin_amdgcn_rsq(zero ? 1.0 : ss);
+    double nrm = zero ? 0.0 : ss * rs;
+    nrm = fma(0.5 * rs, fma(-nrm, nrm, ss), nrm);
+    nrm = fma(0.5 * rs, fma(-nrm, nrm, ss), nrm);
+    const double den = zero ? 1.0 : fma(fabs(alpha), nrm, ss);
+    double hinv = __builtin_amdgcn_rcp(den);
+    hinv = fma(hinv, fma(-den, hinv, 1.0), hinv);
+    hinv = zero ? 0.0 : fma(hinv, fma(-den, hinv, 1.0), hinv);
     const double v1 = alpha + copysign(nrm, alpha);
     if (tid == 0) es[k] = ss;
 #pragma unroll
@@ -141,12 +156,16 @@ __device__ __forceinline__ void reflect_block(double (&A)[8][8], double* xs, dou
     }
 #pragma unroll
     for (int x = a0; x < 8; ++x) {
-      double s = 0.0;
+      p[x] = 0.0;
 #pragma unroll
-      for (int y = a0; y < 8; ++y) s = fma(A[x][y], v[y], s);
-      s = row16_sum(s);
-      p[x] = ti + 16 * x > k ? s * hinv : 0.0;
-      if (tj == 0) ps[ti + 16 * x] = p[x];
+      for (int y = a0; y < 8; ++y) p[x] = fma(A[x][y], v[y], p[x]);
+    }
+    row16_sums<a0>(p);
+#pragma unroll
+    for (int x = a0; x < 8; ++x) p[x] = ti + 16 * x > k ? p[x] * hinv : 0.0;
+    if (tj == 0) {
+#pragma unroll
+      for (int x = a0; x < 8; ++x) ps[ti + 16 * x] = p[x];
     }
     __syncthreads();
     double q[8], dot = 0.0;
@@ -164,7 +183,9 @@ __device__ __forceinline__ void reflect_block(double (&A)[8][8], double* xs, dou
 
 // See the head of the file.  One workgroup of 256 threads per image: thread (ti, tj) = (tid / 16, tid % 16) holds the
 // elements (ti + 16 x, tj + 16 y) of the window, x, y < 8, in registers; a sum over a row is then 16 lanes of one DPP
-// row.  Two barriers per reflection.  Bound by latency (126 dependent reflections, then the Sturm recurrences).
+// row.  Two barriers per reflection.  Bound by instruction issue (one wave per SIMD, some 400 instructions a reflection; one
+// barrier instead of two measured the same): 126 reflections 100 us, a Sturm pass of 128 trial points 6.6.  144 us in all with
+// library square roots and divisions and the row sums one after the other, 124 so.
 __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int r, const double* __restrict__ off,
                                                     const double* __restrict__ link, bool ordered, SplitCtl* ctl,
                                                     const int* __restrict__ skip) {
