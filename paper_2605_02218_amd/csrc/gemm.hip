@@ -9,7 +9,7 @@
 // 2x2 MFMA 32x32 tiles) or, for large problems, 256x256 (wave tile 128x128 = 4x4
 // MFMA tiles, 256 accumulator registers); k-tile of 128 bytes per row.  In gemm_nt_kernel operand
 // tiles go global -> registers -> LDS (double buffered, one barrier per k-tile); the large bf16
-// problems (gemm_nt_ring_kernel) and the gathered fp64-result products (gemm_gram_dma_kernel) load
+// problems (gemm_nt_ring_kernel) and the mid-size ones and the gathered fp64-result products (gemm_dma_kernel) load
 // straight into LDS.  LDS rows are 128 B with the 16-byte chunk index XOR-swizzled by bits 1-3 of
 // the row, so both the 16-byte stores and the MFMA fragment reads are bank-conflict free.
 //   bf16: v_mfma_f32_32x32x16_bf16, lane (i = l%32, h = l/32) holds k = 8h..8h+7.
@@ -525,13 +525,19 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// ---- bf16 products into fp64 with optional row gathers (the Gram matrix of the pre-selected tokens and the rows a
-// streaming step adds to it): 128x128 block tile, wave tile 64x64 (2x2 MFMA tiles), k-tile 32, four LDS stages of
-// 16 KB filled by direct global -> LDS loads whose lanes take their row from the gather list, fp32 partial sums
-// flushed into fp64 accumulators every 256 k, tiles above the diagonal skipped and mirrored on request.  One barrier
-// per k-tile, the fragments of the next k-tile read while the current one is multiplied; two workgroups fit a compute unit, so one's waits are the other's MFMAs.  Rows beyond M / N are
-// clamped when loading and masked in the epilogue; requires K % 32 == 0.
-__global__ __launch_bounds__(THREADS, 2) void gemm_gram_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+// ---- bf16 products on 128 x 128 tiles: fp64 results with optional row gathers (the Gram matrix of the pre-selected tokens
+// and the rows a streaming step adds to it), fp32 results and row norms of products too small for the ring kernel.  Wave tile
+// 64x64 (2x2 MFMA tiles), k-tile 32, four LDS stages of 16 KB filled by direct global -> LDS loads whose lanes take their row
+// from the gather list.  For fp64 the fp32 partial sums are flushed into fp64 accumulators every 256 k, tiles above the
+// diagonal skipped and mirrored on request; fp32 results keep one sum over all of k, in gemm_nt_kernel's order.  One barrier
+// per k-tile, the fragments of the next k-tile read while the current one is multiplied; two workgroups fit a compute unit, so
+// one's waits are the other's MFMAs.  Rows beyond M / N are clamped when loading and masked in the epilogue; requires
+// K % 32 == 0.  Bound by the latency of a k-step where a workgroup has its compute unit to itself.  fp32 results against
+// gemm_nt_kernel, us: 1332 x 3584 x 3584 88 -> 73, twelve of 1601 x 111 x 3584 in two parts of k 50 -> 41, row norms of 576 x 4096 x
+// 4096 65 -> 43.
+template <int EPI>
+__global__ __launch_bounds__(THREADS, 2) void gemm_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr bool F64 = EPI == EPI_STORE_F64;
   constexpr int BT = 128, WT = 64, TW = 2, BK = 32, NST = 4;
   constexpr int STAGE = 2 * BT * 64;  // bytes: A tile then B tile
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -574,13 +580,16 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_gram_dma_kernel(GemmArgs g, i
   };
 
   f32x16_t acc[TW][TW];
-  double acc64[TW * TW * 16];
+  double acc64[F64 ? TW * TW * 16 : 1];
 #pragma unroll
   for (int i = 0; i < TW; ++i)
 #pragma unroll
     for (int j = 0; j < TW; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.f; acc64[(i * TW + j) * 16 + v] = 0.0; }
+      for (int v = 0; v < 16; ++v) {
+        acc[i][j][v] = 0.f;
+        if (F64) acc64[F64 ? (i * TW + j) * 16 + v : 0] = 0.0;
+      }
 
   const int nk = g.K / BK;
   const int li = lane & 31, lh = lane >> 5;
@@ -612,7 +621,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_gram_dma_kernel(GemmArgs g, i
       for (int j = 0; j < TW; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          acc64[(i * TW + j) * 16 + v] += (double)acc[i][j][v];
+          acc64[F64 ? (i * TW + j) * 16 + v : 0] += (double)acc[i][j][v];
           acc[i][j][v] = 0.f;
         }
   };
@@ -643,9 +652,31 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_gram_dma_kernel(GemmArgs g, i
     mma(a1, b1);
     __builtin_amdgcn_sched_barrier(0);
     // the fp32 partial sums go into fp64 every 256 contraction steps (8 k-tiles) and at the end
-    if ((kt & 7) == 7 || kt + 1 == nk) flush();
+    if (F64 && ((kt & 7) == 7 || kt + 1 == nk)) flush();
   }
   __builtin_amdgcn_s_waitcnt(0x0070);
+
+  if (EPI == EPI_ROWNORM2) {
+    // per row the sum over the tile's 128 columns of C^2 (columns beyond N are copies of the last one: left out)
+    __syncthreads();                  // the stages are free
+    float* red = (float*)smem;        // [2][BT]
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < TW; ++j)
+          if (col0 + wn * WT + j * 32 + li < g.N) s = fmaf(acc[i][j][v], acc[i][j][v], s);
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (li == 0) red[wn * BT + wm * WT + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)] = s;
+      }
+    __syncthreads();
+    for (int t = tid; t < BT; t += THREADS)
+      if (row0 + t < g.M) ((float*)g.C)[coff + (long)(row0 + t) * g.ldc + tmap.tn] = red[t] + red[BT + t];
+    return;
+  }
 
 #pragma unroll
   for (int i = 0; i < TW; ++i)
@@ -656,7 +687,11 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_gram_dma_kernel(GemmArgs g, i
         const int r = row0 + wm * WT + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
         const int c = col0 + wn * WT + j * 32 + li;
         if (r < g.M && c < g.N) {
-          const double x = acc64[(i * TW + j) * 16 + v];
+          if (!F64) {
+            ((float*)g.C)[coff + (long)r * g.ldc + c] = acc[i][j][v];
+            continue;
+          }
+          const double x = acc64[F64 ? (i * TW + j) * 16 + v : 0];
           ((double*)g.C)[coff + (long)r * g.ldc + c] = x;
           // symmetric product: the tile below the diagonal is also stored transposed (v & 3 walks four
           // consecutive rows r, so each thread writes 32 contiguous bytes of row c)
@@ -768,13 +803,14 @@ inline long tiles32(const GemmArgs& g) {
 // Tiles up to which gemm_gram_small_kernel is taken: two rounds of its one workgroup per compute unit.
 constexpr long kGramSmallTiles = 512;
 
-inline hipError_t launch_gram_dma(const GemmArgs& g, hipStream_t stream) {
+template <int EPI>
+inline hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
   constexpr int BT = 128, LDS = 4 * 2 * BT * 64;
   const int tiles_m = (g.M + BT - 1) / BT, tiles_n = (g.N + BT - 1) / BT;
   const long nblocks = (long)tiles_m * tiles_n * g.batch;
   if (nblocks <= 0) return hipSuccess;
   if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gemm_gram_dma_kernel, dim3((unsigned)nblocks), dim3(THREADS), LDS, stream, g, tiles_m, tiles_n);
+  hipLaunchKernelGGL(gemm_dma_kernel<EPI>, dim3((unsigned)nblocks), dim3(THREADS), LDS, stream, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
@@ -814,7 +850,7 @@ hipError_t launch_t(const GemmArgs& g, hipStream_t stream) {
     if (aligned16(g) && g.K % 64 == 0 && g.K >= 256 && g.M >= 1 && g.N >= 1 && g.batch >= 1 && g.batch_inner == 1 && tiles32(g) <= kGramSmallTiles)
       return launch_gram_small(g, stream);
     if (aligned16(g) && g.K % 32 == 0 && g.K >= 32 && g.M >= 1 && g.N >= 1 && (long)g.M * g.N * g.batch >= 128L * 128 * 64)
-      return launch_gram_dma(g, stream);
+      return launch_dma<EPI_STORE_F64>(g, stream);
   }
   if (g.gatherA || g.gatherB) return launch_cfg<In, EPI, true, 2>(g, stream);
   if constexpr (std::is_same<In, bf16_t>::value && EPI != EPI_STORE_F64) {
@@ -825,6 +861,8 @@ hipError_t launch_t(const GemmArgs& g, hipStream_t stream) {
         return launch_ring<EPI>(g, stream);
       return launch_cfg<In, EPI, false, 4>(g, stream);
     }
+    // the direct loads were the faster ones at every measured shape they can take (gemm_dma_kernel)
+    if (aligned16(g) && g.K % 32 == 0 && g.K >= 32 && g.M >= 1 && g.N >= 1 && g.batch >= 1) return launch_dma<EPI>(g, stream);
   }
   return launch_cfg<In, EPI, false, 2>(g, stream);
 }

@@ -12,8 +12,8 @@ def C():
 
 
 @pytest.mark.parametrize("weights", ["qk", "q", "k", ""])
-@pytest.mark.parametrize("B,N,d,T", [(1, 300, 1024, 16), (2, 130, 2048, 5), (1, 64, 512, 1), (1, 700, 1536, 33), (3, 90, 520, 2)],
-                         ids=["four-parts", "batch-odd-keywords", "one-keyword", "two-tiles", "width-not-cut"])
+@pytest.mark.parametrize("B,N,d,T", [(1, 300, 1024, 16), (2, 130, 2048, 5), (1, 64, 512, 1), (1, 700, 1536, 33), (3, 90, 520, 2), (2, 200, 544, 3)],
+                         ids=["four-parts", "batch-odd-keywords", "one-keyword", "two-tiles", "width-not-cut", "last-column-tile-a-quarter"])
 @pytest.mark.parametrize("mode", ["cosine", "softmax"])
 def test_scores_with_k_in_parts(C, mode, B, N, d, T, weights):
     import torch
