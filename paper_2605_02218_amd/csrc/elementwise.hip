@@ -549,7 +549,6 @@ hipError_t launch_activity(const void* hidden, float* s_act, int B, int N, int d
 hipError_t launch_row_norm2(const void* x, int in_type, void* out, bool out_f64, long rows, int d, hipStream_t st) {
   dim3 grid(blocks_for(rows, 4)), block(256);
   if (in_type == IN_BF16 && !out_f64) hipLaunchKernelGGL((row_norm2_kernel<bf16_t, float>), grid, block, 0, st, (const bf16_t*)x, (float*)out, rows, d);
-  else if (in_type == IN_F32 && !out_f64) hipLaunchKernelGGL((row_norm2_kernel<float, float>), grid, block, 0, st, (const float*)x, (float*)out, rows, d);
   else if (in_type == IN_F32 && out_f64) hipLaunchKernelGGL((row_norm2_kernel<float, double>), grid, block, 0, st, (const float*)x, (double*)out, rows, d);
   else if (in_type == IN_F64 && out_f64) hipLaunchKernelGGL((row_norm2_kernel<double, double>), grid, block, 0, st, (const double*)x, (double*)out, rows, d);
   else return hipErrorInvalidValue;

@@ -9,7 +9,7 @@
 // on the fp64 Gram matrix is a sequence of fp64 products.
 //
 // Shape: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in
-// each direction (64x64 for <2,2>, 128x128 for <4,4>), k-tile 16.  Operands are converted to
+// each direction (64x64 for <2,2>), k-tile 16.  Operands are converted to
 // fp64 on their way into LDS; the loads of k-tile t+1 are issued before the MFMAs of tile t and
 // parked in registers, LDS is double buffered, one barrier per k-tile.
 // MFMA layouts: operand lane l holds (row|col = l%16, k = l/16); result lane l, register v
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
     __syncthreads();
   }
 
-  if (EPI == EPI_STORE_F64 || EPI == EPI_SUB_F64 || EPI == EPI_STORE_DOT) {
+  if (EPI == EPI_STORE_F64 || EPI == EPI_STORE_DOT) {
     double dot[NJ];                // EPI_STORE_DOT: this lane's part of the column sums of C * D
 #pragma unroll
     for (int j = 0; j < NJ; ++j) dot[j] = 0.0;
@@ -214,8 +214,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
           const int c = col0 + wn * NJ * 16 + j * 16 + i16;
           if (r < g.M && c < g.N) {
             double* out = (double*)g.C + coff + (long)r * g.ldc + c;
-            if (EPI == EPI_SUB_F64) *out -= acc[i][j][v];
-            else *out = acc[i][j][v];
+            *out = acc[i][j][v];
             if (EPI == EPI_STORE_DOT) dot[j] = fma(acc[i][j][v], ((const double*)g.D)[coff + (long)r * g.ldc + c], dot[j]);
             // lanes of equal i16 hold four consecutive rows r: the transposed store goes out in 32-byte pieces
             if (EPI == EPI_STORE_F64 && g.mirror && tn != tm) ((double*)g.C)[coff + (long)c * g.ldc + r] = acc[i][j][v];
@@ -568,13 +567,6 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// (B stored [K][N] only) 128x128 tiles when they still fill the chip, else 64x64.
-inline bool big_tiles(const GemmArgs& g) {
-  if (g.M < 128 || g.N < 128) return false;
-  const long nb = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch;
-  return nb >= 256;
-}
-
 // Row norms are decided by sizes alone: the number of partials is part of a plan.
 inline bool rownorm_small(long M, int N, int K) { return ((M + 63) / 64) * ((N + 63) / 64) <= kSmallTiles64 && K >= 64 && K % 64 == 0; }
 
@@ -585,14 +577,7 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   if constexpr (!f64x2 && !std::is_same<TA, bf16_t>::value) {
     if (g.epilogue == EPI_STORE_F64 && tiles64(g) <= kSmallTiles64 && small_fits(g)) return launch_small<TA, TB, EPI_STORE_F64>(g, stream);
   }
-  if (g.transB) {
-    if (gather) return hipErrorInvalidValue;
-    if (g.epilogue == EPI_STORE_F64)
-      return big_tiles(g) ? launch_cfg<TA, TB, EPI_STORE_F64, false, true, 4, 4>(g, stream)
-                          : launch_cfg<TA, TB, EPI_STORE_F64, false, true, 2, 2>(g, stream);
-    if (g.epilogue == EPI_SUB_F64) return launch_cfg<TA, TB, EPI_SUB_F64, false, true, 2, 2>(g, stream);
-    return hipErrorInvalidValue;
-  }
+  if (g.transB) return hipErrorInvalidValue;   // launch_gemm64_store_dot, launch_gemm64_rownorm_dual
   if (g.epilogue == EPI_STORE_F64) {
     if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, false, 2, 2>(g, stream);
     if (f64x2 && plain_f64(g)) return launch_plain_f64(g, stream);
@@ -600,7 +585,6 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
     return launch_cfg<TA, TB, EPI_STORE_F64, false, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;
-  if (g.epilogue == EPI_SUB_F64) return launch_cfg<TA, TB, EPI_SUB_F64, false, false, 2, 2>(g, stream);
   if (g.epilogue == EPI_ROWNORM2) {
     if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value) {
       if (g.batch == 1 && g.batch_inner == 1 && rownorm_small(g.M, g.N, g.K)) return launch_small<TA, TB, EPI_ROWNORM2>(g, stream);

@@ -15,8 +15,7 @@ enum GemmEpilogue {
   EPI_STORE_F32 = 0,  // C fp32 [M,N]
   EPI_ROWNORM2 = 1,   // C fp32 [M, tiles_n]: per-tile sums over columns of C^2 (C itself is not stored)
   EPI_STORE_F64 = 2,  // C fp64 [M,N]; the fp32 accumulators are flushed into fp64 every 256 k
-  EPI_SUB_F64 = 3,    // C fp64 [M,N] -= A*B^T (fp64 kernel only)
-  EPI_STORE_DOT = 4,  // EPI_STORE_F64, and the column sums of C * D per row tile (fp64 kernel only)
+  EPI_STORE_DOT = 3,  // EPI_STORE_F64, and the column sums of C * D per row tile (fp64 kernel only)
 };
 
 struct GemmArgs {
@@ -37,7 +36,7 @@ struct GemmArgs {
   bool lower_only = false;                     // tiles entirely above the diagonal of C are not computed
   bool mirror = false;                         // with lower_only, square tiles and a symmetric product (A = B): tiles below the
                                                // diagonal are also stored transposed, so that C comes out full
-  bool transB = false;                         // B is stored [K][N] (row pitch ldb), i.e. C = A * B
+  bool transB = false;                         // B is stored [K][N] (row pitch ldb), i.e. C = A * B: the two entries that say so
   bool frag = false;                           // square symmetric product (A = B, N % 64 == 0): C as [N/16][N/16] tiles in fragment
                                                // order (common.h), those on and below the diagonal; ldc unused
   const int* skip = nullptr;                   // per outer batch: the work is skipped while skip[b] > skip_if

@@ -516,7 +516,7 @@ __global__ void mask_passed_kernel(const int* __restrict__ ok, int* __restrict__
 }  // namespace
 
 int subspace_block(int n, int r) {
-  // P = r + 64 rounded up to the panel width: the Ritz problem costs P^3 and each step P^2 n, while a wider
+  // P = r + 64 rounded up to the panel width: the split costs P^3 per step and each iteration P^2 n, while a wider
   // block only buys a better contraction factor lambda_{P+1}/lambda_r per step, so the narrow block with a
   // few more steps is the cheaper trade.  0 = not worthwhile (P would be most of n).
   int P = (r + 64 + NB - 1) / NB * NB;
@@ -629,7 +629,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   // is a fixed perturbation of the operator of relative size 1e-16 (lambda_1 / lambda_r)^2 at the r-th eigenvalue
   // (1e-8 for a spectrum that falls by 1e4 down to r); the products with G itself that follow contract that error
   // like any other, and a CPU model of the workloads' matrices needs three to four of them.  The last product
-  // feeds the Rayleigh-Ritz step and is with G in any case.
+  // feeds the split and the residual check and is with G in any case.
   auto pass = [&](int n_sq, int n_plain, int pass_no) -> hipError_t {
     const int steps = n_sq + n_plain;
     for (int it = 0; it < steps; ++it) {
