@@ -164,7 +164,8 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
 
     Candidates are the kernels that make up (nearly) all of a stage by themselves, with the stage time as the
     launch duration, and the fp64 product of the subspace iteration, timed by the library's probe events
-    around one of its equal launches.  achieved = algorithmic work of one launch / its measured duration.
+    around one of its equal launches (an image takes part in as many of them as its schedule asks for, so their number is an
+    upper bound).  achieved = algorithmic work of one launch / its measured duration.
     """
     import covspec_inputs as I
     B, N, d, T, K = w.batch, w.n_tokens, w.d_model, w.n_query, w.n_act_layers
@@ -182,13 +183,13 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
         "gather": ("gather_rows_kernel", "hbm", PEAK["hbm_GBps"], "GB/s", 2.0 * B * k * d * e / 1e9, 1,
                    stages["gather"]),
         # the Gram matrix is symmetric: only the tiles on and below the diagonal are computed, and only those are counted
-        "gram": ("gemm_gram_dma_kernel (tiles on and below the diagonal)" if (bf and p_modes[1] == 0) else "gemm64_kernel<gather> (tiles on and below the diagonal)",
+        "gram": ("gemm_dma_kernel (tiles on and below the diagonal)" if (bf and p_modes[1] == 0) else "gemm64_kernel<gather> (tiles on and below the diagonal)",
                  "mfma", PEAK["mfma_bf16_TFLOPs"] if (bf and p_modes[1] == 0) else PEAK["mfma_fp64_TFLOPs"],
                  "TFLOP/s", gram_flops(B, M, d, 128 if (bf and p_modes[1] == 0) else 64) / 1e12, 1, stages["gram"]),
     }
     n_probe, pr, pc, pk = C.probe_launches(p)
     if n_probe > 0 and probe_ms > 0:
-        cand["lowrank_product"] = ("gemm64_kernel<f64,f64,store>", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
+        cand["lowrank_product"] = ("gemm64_dma_kernel", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
                                    2.0 * B * pr * pc * pk / 1e12, n_probe, probe_ms)
     elif p_modes[1] == 1:
         cand["lowrank"] = ("greedy_kernel", "alu", PEAK["valu_fp64_TFLOPs"], "TFLOP/s", 1.0 * B * M * k * k / 1e12, 1,
