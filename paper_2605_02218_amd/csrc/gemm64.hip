@@ -44,7 +44,7 @@ __device__ __forceinline__ int regroup_xcd(int bid, int nblocks) {
   return (bid < (per << 3)) ? (bid & 7) * per + (bid >> 3) : bid;
 }
 
-template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ, bool DUAL = false>
+template <typename TA, typename TB, int EPI, bool GATHER, int MI, int NJ>
 __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr int TM = 32 * MI, TN = 32 * NJ;
   constexpr int SA = TM / 16, SBn = TN / 16;       // staged elements per thread and operand
@@ -66,8 +66,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
   const TB* __restrict__ B = (const TB*)g.B + (long)bo * g.strideB + (long)bi * g.strideB2;
   const long coff = (long)bo * g.strideC + (long)bi * g.strideC2;
 
-  // staging slots.  K-contiguous operand: element e = tid + 256*s -> (row e/16, k e%16).
-  // B stored [K][N]: e -> (n = e % TN, k = e / TN), so that a wave reads consecutive n.
+  // staging slots: element e = tid + 256*s -> (row e/16, k e%16).
   long aoff[SA], boff[SBn];
   bool aok[SA], bok[SBn];
   const int lk = tid & 15;
@@ -81,25 +80,18 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
   }
 #pragma unroll
   for (int s = 0; s < SBn; ++s) {
-    if (TRANSB) {
-      const int e = tid + 256 * s;
-      const int n = col0 + (e % TN);
-      bok[s] = n < g.N;
-      boff[s] = (long)(e / TN) * g.ldb + n;
-    } else {
-      const int rb = col0 + (tid >> 4) + 16 * s;
-      bok[s] = rb < g.N;
-      long ib = rb;
-      if (GATHER && g.gatherB && bok[s]) ib = g.gatherB[(long)bo * g.gstrideB + rb];
-      boff[s] = ib * g.ldb + lk;
-    }
+    const int rb = col0 + (tid >> 4) + 16 * s;
+    bok[s] = rb < g.N;
+    long ib = rb;
+    if (GATHER && g.gatherB && bok[s]) ib = g.gatherB[(long)bo * g.gstrideB + rb];
+    boff[s] = ib * g.ldb + lk;
   }
 
   // bf16 x bf16, both K-contiguous, 64 x 64 tiles: a k-tile of an operand is 64 rows x 32 bytes, so the
   // element-wise staging above would issue eight 2-byte loads per thread.  When rows and K allow 16-byte
   // pieces, thread t instead loads ONE piece (operand t / 128, row (t % 128) / 2, half t % 2) and converts its
   // eight values on the way into LDS.
-  constexpr bool WIDE_T = std::is_same<TA, bf16_t>::value && std::is_same<TB, bf16_t>::value && !TRANSB && MI == 2 && NJ == 2;
+  constexpr bool WIDE_T = std::is_same<TA, bf16_t>::value && std::is_same<TB, bf16_t>::value && MI == 2 && NJ == 2;
   const bool wide = WIDE_T && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.K % 8 == 0 && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
   const int wop = tid >> 7, wrow = (tid & 127) >> 1, whalf = tid & 1;
   long woff = 0;
@@ -116,16 +108,6 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 
   double ra_[SA], rb_[SBn];
   auto fetch = [&](int k0) {
-    if (DUAL && k0 >= g.K) {       // second pair of operands, subtracted (K % TK == 0, checked by the launcher)
-      k0 -= g.K;
-      const TA* __restrict__ A2 = (const TA*)g.A2 + (long)bo * g.strideA;
-      const TB* __restrict__ B2 = (const TB*)g.B2 + (long)bo * g.strideB;
-#pragma unroll
-      for (int s = 0; s < SA; ++s) ra_[s] = aok[s] ? -as_f64(A2[aoff[s] + k0]) : 0.0;
-#pragma unroll
-      for (int s = 0; s < SBn; ++s) rb_[s] = bok[s] ? as_f64(B2[boff[s] + (TRANSB ? (long)k0 * g.ldb : (long)k0)]) : 0.0;
-      return;
-    }
     if (WIDE_T && wide) {
       const u32x4_t z = {0u, 0u, 0u, 0u};
       const bf16_t* P = wop ? (const bf16_t*)B : (const bf16_t*)A;
@@ -135,14 +117,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 #pragma unroll
     for (int s = 0; s < SA; ++s) ra_[s] = (aok[s] && k0 + lk < g.K) ? as_f64(A[aoff[s] + k0]) : 0.0;
 #pragma unroll
-    for (int s = 0; s < SBn; ++s) {
-      if (TRANSB) {
-        const int k = k0 + (tid + 256 * s) / TN;
-        rb_[s] = (bok[s] && k < g.K) ? as_f64(B[boff[s] + (long)k0 * g.ldb]) : 0.0;
-      } else {
-        rb_[s] = (bok[s] && k0 + lk < g.K) ? as_f64(B[boff[s] + k0]) : 0.0;
-      }
-    }
+    for (int s = 0; s < SBn; ++s) rb_[s] = (bok[s] && k0 + lk < g.K) ? as_f64(B[boff[s] + k0]) : 0.0;
   };
   auto park = [&](int buf) {
     if (WIDE_T && wide) {
@@ -159,14 +134,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 #pragma unroll
     for (int s = 0; s < SA; ++s) a[((tid >> 4) + 16 * s) * PITCH + lk] = ra_[s];
 #pragma unroll
-    for (int s = 0; s < SBn; ++s) {
-      if (TRANSB) {
-        const int e = tid + 256 * s;
-        b[(e % TN) * PITCH + e / TN] = rb_[s];
-      } else {
-        b[((tid >> 4) + 16 * s) * PITCH + lk] = rb_[s];
-      }
-    }
+    for (int s = 0; s < SBn; ++s) b[((tid >> 4) + 16 * s) * PITCH + lk] = rb_[s];
   };
 
   f64x4_t acc[MI][NJ];
@@ -176,7 +144,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
     for (int j = 0; j < NJ; ++j) acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 
   const int i16 = lane & 15, kq = lane >> 4;
-  const int nt = (DUAL ? 2 : 1) * ((g.K + TK - 1) / TK);
+  const int nt = (g.K + TK - 1) / TK;
   fetch(0);
   park(0);
   __syncthreads();
@@ -200,10 +168,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
     __syncthreads();
   }
 
-  if (EPI == EPI_STORE_F64 || EPI == EPI_STORE_DOT) {
-    double dot[NJ];                // EPI_STORE_DOT: this lane's part of the column sums of C * D
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) dot[j] = 0.0;
+  if (EPI == EPI_STORE_F64) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -215,23 +180,10 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
           if (r < g.M && c < g.N) {
             double* out = (double*)g.C + coff + (long)r * g.ldc + c;
             *out = acc[i][j][v];
-            if (EPI == EPI_STORE_DOT) dot[j] = fma(acc[i][j][v], ((const double*)g.D)[coff + (long)r * g.ldc + c], dot[j]);
             // lanes of equal i16 hold four consecutive rows r: the transposed store goes out in 32-byte pieces
-            if (EPI == EPI_STORE_F64 && g.mirror && tn != tm) ((double*)g.C)[coff + (long)c * g.ldc + r] = acc[i][j][v];
+            if (g.mirror && tn != tm) ((double*)g.C)[coff + (long)c * g.ldc + r] = acc[i][j][v];
           }
         }
-    if (EPI == EPI_STORE_DOT) {
-      double* red = smem;          // [2][TN], as below
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        double s = dot[j];
-        s += __shfl_xor(s, 16, 64);
-        s += __shfl_xor(s, 32, 64);
-        if (kq == 0) red[wm * TN + wn * NJ * 16 + j * 16 + i16] = s;
-      }
-      __syncthreads();
-      if (tid < TN && col0 + tid < g.N) g.dots[((long)bidx * tiles_m + tm) * g.N + col0 + tid] = red[tid] + red[TN + tid];
-    }
   } else {  // EPI_ROWNORM2: per-row sum over this tile's columns of C^2 (fp64)
     double* red = smem;   // [2][TM], reuses the operand buffers (all reads of them are behind the last barrier)
 #pragma unroll
@@ -511,8 +463,106 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
   }
 }
 
+// The products that follow the split (launch_gemm64_store_dot, launch_gemm64_rownorm_dual): 32 x 32 tile, the four
+// waves take a quarter of k each, straight from global memory.  B is stored [K][N] and A is symmetric, so that both operands are
+// read by rows of k, sixteen neighbouring doubles per quarter wave.  DUAL: the second product's k follows the first one's with
+// A2 negated.  All dimensions are multiples of 64.  gemm64_kernel staged B's tiles through registers and walked all of k in
+// every wave; us, residual / energies: one image of P = 192, nP = 320 47 -> 8.8 / 20 -> 6.1, four of 192, 1280 48 -> 23 / 22 -> 15,
+// eight of 384, 1152 215 -> 133 / 85 -> 68, sixty-four of 256, 640 359 -> 276 / 160 -> 155.  Bound by the fp64 MFMA at the large end.
+template <bool DUAL>
+__global__ __launch_bounds__(256) void gemm64_sym_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  __shared__ double part[4 * 32 * 33];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+  const int per = tiles_m * tiles_n;
+  const int b = blockIdx.x / per, pidx = blockIdx.x - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
+  if (g.skip && g.skip[b] > g.skip_if) return;
+  const int row0 = tm * 32, col0 = tn * 32;
+  const int groups = g.K >> 6, total = DUAL ? 2 * groups : groups;      // steps of 16 k per wave
+  const long abase = (long)b * g.strideA + row0 + i16, bbase = (long)b * g.strideB + col0 + i16;
+  f64x4_t acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[x][y][v] = 0.0;
+  double fa[2][4][2], fb[2][4][2];
+  auto load = [&](int t, double (&a)[4][2], double (&bb)[4][2]) {
+    const bool second = DUAL && t >= groups;
+    const double* A = (const double*)(second ? g.A2 : g.A) + abase;
+    const double* B = (const double*)(second ? g.B2 : g.B) + bbase;
+    const long k0 = (long)(second ? t - groups : t) * 64 + 16 * w + kq;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const double av = A[(k0 + 4 * q) * g.lda + 16 * x];
+        a[q][x] = second ? -av : av;
+        bb[q][x] = B[(k0 + 4 * q) * g.ldb + 16 * x];
+      }
+  };
+  auto mul = [&](const double (&a)[4][2], const double (&bb)[4][2]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q][x], bb[q][y], acc[x][y], 0, 0, 0);
+  };
+  load(0, fa[0], fb[0]);
+#pragma unroll 1
+  for (int t = 0; t < total; t += 2) {
+    if (t + 1 < total) load(t + 1, fa[1], fb[1]);
+    mul(fa[0], fb[0]);
+    if (t + 1 >= total) break;
+    if (t + 2 < total) load(t + 2, fa[0], fb[0]);
+    mul(fa[1], fb[1]);
+  }
+  double* out = part + w * (32 * 33);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(16 * x + 4 * v + kq) * 33 + 16 * y + i16] = acc[x][y][v];
+  __syncthreads();
+  auto sum = [&](int i, int j) {
+    const double* q = part + i * 33 + j;
+    return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
+  };
+  const long coff = (long)b * g.strideC;
+  if (DUAL) {                                             // eight lanes per row, four columns each
+    const int i = tid >> 3, j0 = (tid & 7) * 4;
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { const double v = sum(i, j0 + j); s = fma(v, v, s); }
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((tid & 7) == 0) ((double*)g.C)[coff + (long)(row0 + i) * g.ldc + tn] = s;
+    return;
+  }
+  double dot = 0.0;                                       // eight threads per column, four rows each
+  const int j = tid & 31, i0 = tid >> 5;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double v = sum(i0 + 8 * q, j);
+    const long o = coff + (long)(row0 + i0 + 8 * q) * g.ldc + col0 + j;
+    ((double*)g.C)[o] = v;
+    dot = fma(v, ((const double*)g.D)[o], dot);
+  }
+  __syncthreads();
+  part[i0 * 33 + j] = dot;
+  __syncthreads();
+  if (tid < 32) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += part[q * 33 + tid];
+    g.dots[((long)b * tiles_m + tm) * g.N + col0 + tid] = s;
+  }
+}
+
 // Can gemm64_small_kernel take the product?
-inline bool small_fits(const GemmArgs& g) { return g.batch > 0 && g.batch_inner == 1 && !g.transB && g.K >= 64 && g.K % 64 == 0; }
+inline bool small_fits(const GemmArgs& g) { return g.batch > 0 && g.batch_inner == 1 && g.K >= 64 && g.K % 64 == 0; }
 
 template <typename TA, typename TB, int EPI>
 hipError_t launch_small(const GemmArgs& g, hipStream_t stream) {
@@ -549,7 +599,7 @@ inline bool plain_f64(const GemmArgs& g) {
          g.strideB % 2 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
 }
 
-template <typename TA, typename TB, int EPI, bool GATHER, bool TRANSB, int MI, int NJ, bool DUAL = false>
+template <typename TA, typename TB, int EPI, bool GATHER, int MI, int NJ>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream) {
   constexpr int TM = 32 * MI, TN = 32 * NJ;
   const int tiles_m = (g.M + TM - 1) / TM, tiles_n = (g.N + TN - 1) / TN;
@@ -557,7 +607,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t stream) {
   if (nblocks <= 0) return hipSuccess;
   if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
   const size_t lds = (size_t)2 * (TM + TN) * PITCH * sizeof(double);
-  auto kern = gemm64_kernel<TA, TB, EPI, GATHER, TRANSB, MI, NJ, DUAL>;
+  auto kern = gemm64_kernel<TA, TB, EPI, GATHER, MI, NJ>;
   if (lds > 64 * 1024) {
     static PerDeviceInt raised;   // per instantiation
     const hipError_t e = ensure_dynamic_lds(raised, (const void*)kern, lds);
@@ -577,19 +627,18 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   if constexpr (!f64x2 && !std::is_same<TA, bf16_t>::value) {
     if (g.epilogue == EPI_STORE_F64 && tiles64(g) <= kSmallTiles64 && small_fits(g)) return launch_small<TA, TB, EPI_STORE_F64>(g, stream);
   }
-  if (g.transB) return hipErrorInvalidValue;   // launch_gemm64_store_dot, launch_gemm64_rownorm_dual
   if (g.epilogue == EPI_STORE_F64) {
-    if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, false, 2, 2>(g, stream);
+    if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, 2, 2>(g, stream);
     if (f64x2 && plain_f64(g)) return launch_plain_f64(g, stream);
     if (g.frag) return hipErrorInvalidValue;
-    return launch_cfg<TA, TB, EPI_STORE_F64, false, false, 2, 2>(g, stream);
+    return launch_cfg<TA, TB, EPI_STORE_F64, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;
   if (g.epilogue == EPI_ROWNORM2) {
     if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value) {
       if (g.batch == 1 && g.batch_inner == 1 && rownorm_small(g.M, g.N, g.K)) return launch_small<TA, TB, EPI_ROWNORM2>(g, stream);
     }
-    return launch_cfg<TA, TB, EPI_ROWNORM2, false, false, 2, 2>(g, stream);
+    return launch_cfg<TA, TB, EPI_ROWNORM2, false, 2, 2>(g, stream);
   }
   return hipErrorInvalidValue;
 }
@@ -598,14 +647,21 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
 
 int gemm64_tiles_n(long M, int N, int K) { return rownorm_small(M, N, K) ? (N + 31) / 32 : (N + 63) / 64; }
 
+template <bool DUAL>
+static hipError_t launch_sym(const GemmArgs& g, hipStream_t stream) {
+  if (g.gatherA || g.gatherB || g.M != g.K || g.M % 64 != 0 || g.N % 64 != 0 || g.batch < 1 || g.batch_inner != 1) return hipErrorInvalidValue;
+  const long m32 = g.M / 32, n32 = g.N / 32, blocks = m32 * n32 * g.batch;
+  if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gemm64_sym_kernel<DUAL>, dim3((unsigned)blocks), dim3(256), 0, stream, g, (int)m32, (int)n32);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm64_store_dot(const GemmArgs& g, hipStream_t stream) {
-  if (!g.transB || !g.D || !g.dots || g.gatherA || g.gatherB) return hipErrorInvalidValue;
-  return launch_cfg<double, double, EPI_STORE_DOT, false, true, 2, 2>(g, stream);
+  return g.D && g.dots ? launch_sym<false>(g, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm64_rownorm_dual(const GemmArgs& g, hipStream_t stream) {
-  if (!g.transB || !g.A2 || !g.B2 || g.gatherA || g.gatherB || g.K % TK != 0) return hipErrorInvalidValue;
-  return launch_cfg<double, double, EPI_ROWNORM2, false, true, 2, 2, true>(g, stream);
+  return g.A2 && g.B2 ? launch_sym<true>(g, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm64_bf16(const GemmArgs& g, hipStream_t stream) { return launch_ab<bf16_t, bf16_t>(g, stream); }

@@ -15,7 +15,6 @@ enum GemmEpilogue {
   EPI_STORE_F32 = 0,  // C fp32 [M,N]
   EPI_ROWNORM2 = 1,   // C fp32 [M, tiles_n]: per-tile sums over columns of C^2 (C itself is not stored)
   EPI_STORE_F64 = 2,  // C fp64 [M,N]; the fp32 accumulators are flushed into fp64 every 256 k
-  EPI_STORE_DOT = 3,  // EPI_STORE_F64, and the column sums of C * D per row tile (fp64 kernel only)
 };
 
 struct GemmArgs {
@@ -36,7 +35,6 @@ struct GemmArgs {
   bool lower_only = false;                     // tiles entirely above the diagonal of C are not computed
   bool mirror = false;                         // with lower_only, square tiles and a symmetric product (A = B): tiles below the
                                                // diagonal are also stored transposed, so that C comes out full
-  bool transB = false;                         // B is stored [K][N] (row pitch ldb), i.e. C = A * B: the two entries that say so
   bool frag = false;                           // square symmetric product (A = B, N % 64 == 0): C as [N/16][N/16] tiles in fragment
                                                // order (common.h), those on and below the diagonal; ldc unused
   const int* skip = nullptr;                   // per outer batch: the work is skipped while skip[b] > skip_if
@@ -44,7 +42,7 @@ struct GemmArgs {
   const void* A2 = nullptr;                    // launch_gemm64_rownorm_dual: second operands, laid out like A and B
   const void* B2 = nullptr;
   const void* D = nullptr;                     // launch_gemm64_store_dot: laid out like C
-  double* dots = nullptr;                      // [batch][ceil(M / 64)][N]
+  double* dots = nullptr;                      // [batch][M / kSymTile][N]
 };
 int gemm_tiles_n(int N);
 // In how many parts k is best cut so that a product of few tiles fills the device (1: not at all): the parts are batches of
@@ -57,9 +55,11 @@ hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream);
 // Epilogues: EPI_STORE_F64, EPI_ROWNORM2 (fp64 partials, gemm64_tiles_n(M, N, K) per row, for fp32 operands of one batch).
 int gemm64_tiles_n(long M, int N, int K);
 hipError_t launch_gemm64_nt(const GemmArgs& g, bool a_is_f64, bool b_is_f64, hipStream_t stream);
-// C = A * B (B stored [K][N]), and g.dots: per 64-row tile the column sums of C * D, elementwise.
+// C = A * B (A symmetric, B stored [K][N]; dimensions multiples of 64), and g.dots: per row tile the column sums of C * D.
+// Tiles of this and the next one have kSymTile rows and columns.
+constexpr int kSymTile = 32;
 hipError_t launch_gemm64_store_dot(const GemmArgs& g, hipStream_t stream);
-// Squared row lengths, one partial per 64-column tile (EPI_ROWNORM2), of A * B - A2 * B2 (B stored [K][N]; K % 16 == 0).
+// Squared row lengths, one partial per column tile (EPI_ROWNORM2), of A * B - A2 * B2 (A, A2 symmetric, B, B2 stored [K][N]).
 hipError_t launch_gemm64_rownorm_dual(const GemmArgs& g, hipStream_t stream);
 // Both operands bf16: products of bf16 values are exact in fp64 and the sum is fp64, so the result is the
 // exactly rounded contraction to ~1e-16 (used where differences of Gram entries decide a ranking).

@@ -568,10 +568,10 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   int* slow = hold + B;                                                                     // [B] no split at the end of the first pass
   double* G2 = (double*)(((uintptr_t)(slow + B) + 255) & ~(uintptr_t)255);             // [B][nP][nP] G squared
   // after the products with G^2 its place is free: one of the iterates of the split (P <= nP), then U, its partial energies
-  // and the partial row lengths of the residual: nP (P + P / 64 + P / 64) <= nP^2 doubles per image, as P <= 3/4 n
+  // and the partial row lengths of the residual: nP (P + P / 32 + P / 32) <= nP^2 doubles per image, as P <= 3/4 n
   double* U = G2;
-  double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 64][nP]
-  double* rnorm = cpart + (size_t)B * (P / NB) * nP;                                        // [B][P][nP / 64]
+  double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 32][nP]
+  double* rnorm = cpart + (size_t)B * (P / kSymTile) * nP;                                       // [B][P][nP / 32]
   hipError_t e;
 
   // Second pass: images that passed the first check take no further part; the kernels see them as skip_until ==
@@ -656,7 +656,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;
-      g.A = Pi; g.B = oth; g.C = U; g.D = cur; g.dots = cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP; g.transB = true;
+      g.A = Pi; g.B = oth; g.C = U; g.D = cur; g.dots = cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP;
       g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * nP;
       mask(g);
       if ((e = launch_gemm64_store_dot(g, st)) != hipSuccess) return e;
@@ -664,12 +664,12 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     // row lengths of the residual Pi Q^T G - H U
     {
       GemmArgs g;
-      g.A = Pi; g.B = cur; g.A2 = H; g.B2 = U; g.C = rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / NB; g.transB = true;
-      g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * (nP / NB);
+      g.A = Pi; g.B = cur; g.A2 = H; g.B2 = U; g.C = rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / kSymTile;
+      g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * (nP / kSymTile);
       mask(g);
       if ((e = launch_gemm64_rownorm_dual(g, st)) != hipSuccess) return e;
     }
-    return launch_split_finish(H, Pi, rnorm, nP / NB, cpart, P / NB, B, P, n, nP, r, kRitzTol, scratch, slow, ok, pass_no, c, st);
+    return launch_split_finish(H, Pi, rnorm, nP / kSymTile, cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, scratch, slow, ok, pass_no, c, st);
   };
 
   // G^2 (symmetric: tiles on and below the diagonal, mirrored)
