@@ -29,11 +29,10 @@ struct Plan {
   int image0;     // index of the first image in the caller's batch (ragged batches run as several calls)
   int esz;        // bytes per stored element
   int planes;     // bf16: 3 split planes of the folded query matrix, fp32: 1
-  int ksq, ksf, ksl;  // parts in which k is cut for e(q), the folded query matrix and the inner products (bf16 only, else 1)
   int nparts;     // per-token partial sums of |e(v)|^2 written by the projection GEMM
   int nP;         // Gram pitch (padded order of the eigen-solve)
   // workspace offsets (bytes)
-  size_t wqT, wkT, Eq, Eqp, qn2, Eq3, G3raw, G3, vn2p, logits, Ev, S, stats, smean, sq, sa, sf;
+  size_t wqT, wkT, Eq, qn2, Eq3, G3raw, G3, vn2p, logits, Ev, S, stats, smean, sq, sa, sf;
   size_t idxm, Awork, ctl, lam, c, Lt, order, resid, gscr, sub, ok, status;
   int P;          // block size of the subspace iteration (0: full Jacobi solve)
   size_t total;
@@ -91,25 +90,20 @@ int make_plan(const covspec_params* p, Plan* pl) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   const size_t B = q.B, N = q.N, d = q.d, T = q.T, BT = B * T, BN = B * N;
-  q.wqT = q.wkT = q.Eq = q.Eqp = q.qn2 = 0;
+  q.wqT = q.wkT = q.Eq = q.qn2 = 0;
   q.Eq3 = q.G3raw = q.G3 = q.vn2p = q.logits = q.Ev = q.S = q.stats = q.smean = 0;
   // the random-selection ablation uses no scores; covspec_score with that mode still works on its own
   // workspace request, so the score buffers are always part of the plan
   q.wqT = take(d * d * q.esz);
   q.wkT = take(d * d * q.esz);
-  const bool bf = q.dtype == COVSPEC_BF16;
-  q.ksq = bf ? gemm_nt_splits(BT, d, d, 1) : 1;
-  q.ksf = bf ? gemm_nt_splits(3 * BT, d, d, 1) : 1;
-  q.ksl = bf ? gemm_nt_splits(N, 3 * T, d, B) : 1;
   q.Eq = take(BT * d * fsz);
-  q.Eqp = q.ksq > 1 ? take((size_t)q.ksq * BT * d * 4) : q.Eq;
   q.qn2 = take(BT * fsz);
   if (q.rel == COVSPEC_REL_COSINE_MAX) {
     if (q.dtype == COVSPEC_BF16) q.Eq3 = take(3 * BT * d * 2);
-    q.G3raw = take((size_t)q.ksf * q.planes * BT * d * fsz);
+    q.G3raw = take((size_t)q.planes * BT * d * fsz);
     if (q.dtype == COVSPEC_BF16) q.G3 = take(3 * BT * d * 2);
     q.vn2p = take(BN * q.nparts * fsz);
-    q.logits = take((size_t)q.ksl * BN * q.planes * T * fsz);
+    q.logits = take(BN * q.planes * T * fsz);
   } else {
     q.Ev = take(BN * d * fsz);
     q.S = take(B * q.H * T * N * fsz);
@@ -204,15 +198,6 @@ int run_score(const Plan& q, const void* X, const void* hidden, const void* Q, c
     // a_mid / b_mid: operand is an intermediate (fp64 on the fp64 path) rather than a stored input
     return f64 ? launch_gemm64_nt(g, a_mid, b_mid, st) : launch_gemm_nt(g, DT_BF16, st);
   };
-  // cuts k into `parts`: part p of outer batch b stores to C + b * strideC + p * part_stride
-  auto cut_k = [](GemmArgs& g, int parts, long part_stride) {
-    if (parts <= 1) return;
-    g.batch *= parts;
-    g.batch_inner = parts;
-    g.K /= parts;
-    g.strideA2 = g.strideB2 = g.K;
-    g.strideC2 = part_stride;
-  };
 
   // A score whose weight in the fusion is zero is computed only if the caller asked for it (selector ablations,
   // Table II: query-only is lambda = 1, activity-only lambda = 0); 0 * score adds an exact zero for finite scores.
@@ -221,26 +206,18 @@ int run_score(const Plan& q, const void* X, const void* hidden, const void* Q, c
 
   marks.mark(COVSPEC_STAGE_QUERY_SIDE);
   auto query_scores = [&]() -> int {
-  // e(q) = q Wq; on the bf16 path its rows are finished (parts of k added, lengths, bf16 planes) in one launch
+  // e(q) = q Wq; on the bf16 path its rows are finished (lengths, bf16 planes) in one launch
   const bool fold = q.rel == COVSPEC_REL_COSINE_MAX && Wk;
-  float* Eqp = at<float>(ws, q.Eqp);
-  int eq_parts = 1;
   if (Wq) {
     HIPCHK(launch_transpose(Wq, at<void>(ws, q.wqT), q.d, q.d, q.dtype, st));
     GemmArgs g;
-    g.A = Q; g.B = at<void>(ws, q.wqT); g.C = f64 ? Eq : (void*)Eqp; g.M = (int)BT; g.N = q.d; g.K = q.d; g.lda = d; g.ldb = d; g.ldc = d;
+    g.A = Q; g.B = at<void>(ws, q.wqT); g.C = Eq; g.M = (int)BT; g.N = q.d; g.K = q.d; g.lda = d; g.ldb = d; g.ldc = d;
     g.epilogue = f64 ? EPI_STORE_F64 : EPI_STORE_F32;
-    eq_parts = q.ksq;
-    cut_k(g, eq_parts, BT * d);
     HIPCHK(gemm(g, false, false));
   } else {
-    HIPCHK(launch_convert(Q, in_x, f64 ? Eq : (void*)Eqp, f64, BT * d, st));
+    HIPCHK(launch_convert(Q, in_x, Eq, f64, BT * d, st));
   }
-  if (!f64) {
-    // with the fold only the planes and the lengths are read from here on
-    HIPCHK(launch_query_rows(Eqp, eq_parts, BT * d, BT, q.d, !fold && Eqp != Eq ? (float*)Eq : nullptr,
-                             fold ? at<unsigned short>(ws, q.Eq3) : nullptr, (float*)qn2, st));
-  }
+  if (!f64) HIPCHK(launch_query_rows((const float*)Eq, BT, q.d, fold ? at<unsigned short>(ws, q.Eq3) : nullptr, (float*)qn2, st));
   if (Wk) HIPCHK(launch_transpose(Wk, at<void>(ws, q.wkT), q.d, q.d, q.dtype, st));
 
   if (q.rel == COVSPEC_REL_COSINE_MAX) {
@@ -255,9 +232,8 @@ int run_score(const Plan& q, const void* X, const void* hidden, const void* Q, c
       g.B = Wk; g.C = Graw; g.N = q.d; g.K = q.d; g.lda = d; g.ldb = d; g.ldc = d;
       if (!f64) {
         g.A = at<void>(ws, q.Eq3); g.M = (int)(3 * BT);
-        cut_k(g, q.ksf, 3 * BT * d);
         HIPCHK(launch_gemm_nt(g, DT_BF16, st));
-        HIPCHK(launch_sum_split3((const float*)Graw, 3 * q.ksf, BT * d, BT, q.d, T, at<unsigned short>(ws, q.G3), st));
+        HIPCHK(launch_sum_split3((const float*)Graw, 3, BT * d, BT, q.d, T, at<unsigned short>(ws, q.G3), st));
         Gq = at<void>(ws, q.G3);
       } else {
         g.A = Eq; g.M = (int)BT; g.epilogue = EPI_STORE_F64;
@@ -287,9 +263,8 @@ int run_score(const Plan& q, const void* X, const void* hidden, const void* Q, c
     l.A = X; l.B = Gq; l.C = logits; l.M = q.N; l.N = q.planes * q.T; l.K = q.d; l.lda = d; l.ldb = d; l.ldc = q.planes * T;
     l.batch = q.B; l.strideA = N * d; l.strideB = (long)q.planes * T * d; l.strideC = N * q.planes * T;
     l.epilogue = f64 ? EPI_STORE_F64 : EPI_STORE_F32;
-    cut_k(l, q.ksl, BN * q.planes * T);
     HIPCHK(gemm(l, false, true));
-    HIPCHK(launch_cosine_max(logits, q.planes, q.ksl, BN * q.planes * T, vn2, nparts, qn2, f64, sq, q.B, q.N, q.T, st));
+    HIPCHK(launch_cosine_max(logits, q.planes, vn2, nparts, qn2, f64, sq, q.B, q.N, q.T, st));
   } else {
     // variant: e(v) materialised, per-head logits, softmax over the visual tokens
     marks.mark(COVSPEC_STAGE_TOKEN_PROJECTION);

@@ -175,7 +175,6 @@ __global__ __launch_bounds__(256) void sum_split3_kernel(const float* __restrict
     const f32x4_t x = *(const f32x4_t*)(src + i);
 #pragma unroll
     for (int e = 0; e < V; ++e) v[e] = x[e];
-#pragma unroll 8
     for (int p = 1; p < planes; ++p) {
       const f32x4_t y = *(const f32x4_t*)(src + p * plane_stride + i);
 #pragma unroll
@@ -209,43 +208,36 @@ __global__ __launch_bounds__(256) void sum_split3_kernel(const float* __restrict
   }
 }
 
-// e(q_j) from the partial products of a split contraction: row r is the sum of its `planes` partial rows (in plane order, as
-// above), its squared length (fp32 per thread, fp64 across threads) goes to norm2, the row itself to eq and its three bf16
-// planes, as sum_split3_kernel writes them with one group, to eq3 (both optional).  One workgroup per row; d % 4 == 0.
-__global__ __launch_bounds__(256) void query_rows_kernel(const float* __restrict__ src, int planes, long plane_stride, long rows, int d,
-                                                         float* __restrict__ eq, bf16_t* __restrict__ eq3, float* __restrict__ norm2) {
-  __shared__ double red[4];
+// What is left to do for a row of e(q): its squared length to norm2, summed by one wave in row_norm2_kernel's order (the other
+// waves share the rest), and its three bf16 planes, as sum_split3_kernel writes them with one group, to eq3 (optional).  One
+// workgroup per row; d % 4 == 0.
+__global__ __launch_bounds__(256) void query_rows_kernel(const float* __restrict__ src, long rows, int d, bf16_t* __restrict__ eq3,
+                                                         float* __restrict__ norm2) {
   const long r = blockIdx.x;
-  float s = 0.f;
-  for (int c = 4 * threadIdx.x; c < d; c += 1024) {
-    f32x4_t v = *(const f32x4_t*)(src + r * d + c);
+  const float* x = src + r * d;
+  if (threadIdx.x < 64) {
+    float acc = 0.f;
 #pragma unroll 8
-    for (int p = 1; p < planes; ++p) {              // the loads do not wait for one another
-      const f32x4_t y = *(const f32x4_t*)(src + p * plane_stride + r * d + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] += y[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s = fmaf(v[e], v[e], s);
-    if (eq) *(f32x4_t*)(eq + r * d + c) = v;
-    if (eq3) {
-      typedef unsigned short u16x4_t __attribute__((ext_vector_type(4)));
-      u16x4_t o[3];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[0][e] = f32_to_bf16_rne(v[e]);
-        const float r1 = v[e] - bf16_to_f32(o[0][e]);  // exact
-        o[1][e] = f32_to_bf16_rne(r1);
-        o[2][e] = f32_to_bf16_rne(r1 - bf16_to_f32(o[1][e]));
-      }
-#pragma unroll
-      for (int q = 0; q < 3; ++q) *(u16x4_t*)(eq3 + (q * rows + r) * d + c) = o[q];
-    }
+    for (int c = threadIdx.x; c < d; c += 64) acc = fmaf(x[c], x[c], acc);
+    acc = wave_sum(acc);
+    if (threadIdx.x == 0) norm2[r] = acc;
+    return;
   }
-  const double w = wave_sum((double)s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
-  __syncthreads();
-  if (norm2 && threadIdx.x == 0) norm2[r] = (float)(red[0] + red[1] + red[2] + red[3]);
+  if (!eq3) return;
+  for (int c = 4 * (threadIdx.x - 64); c < d; c += 768) {
+    typedef unsigned short u16x4_t __attribute__((ext_vector_type(4)));
+    const f32x4_t v = *(const f32x4_t*)(x + c);
+    u16x4_t o[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[0][e] = f32_to_bf16_rne(v[e]);
+      const float r1 = v[e] - bf16_to_f32(o[0][e]);  // exact
+      o[1][e] = f32_to_bf16_rne(r1);
+      o[2][e] = f32_to_bf16_rne(r1 - bf16_to_f32(o[1][e]));
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *(u16x4_t*)(eq3 + (q * rows + r) * d + c) = o[q];
+  }
 }
 
 // ---------------------------------------------------------------- cosine-max epilogue (paper Sec. III-A.1)
@@ -257,7 +249,7 @@ __global__ __launch_bounds__(256) void query_rows_kernel(const float* __restrict
 // keyword was bound by those: 156 us for workload 5 where its 283 MB of logits are 50 us of HBM time).  Where the
 // floor could bind (|v| |q_j| < 1e-30 for some keyword that is not a zero vector) the token takes the literal formula.
 template <typename F>
-__global__ __launch_bounds__(256) void cosine_max_kernel(const F* __restrict__ logits, int planes, int splits, long split_stride,
+__global__ __launch_bounds__(256) void cosine_max_kernel(const F* __restrict__ logits, int planes,
                                                           const F* __restrict__ vnorm2, int nparts,
                                                           const F* __restrict__ qnorm2, float* __restrict__ s_query,
                                                           int N, int T) {
@@ -287,39 +279,32 @@ __global__ __launch_bounds__(256) void cosine_max_kernel(const F* __restrict__ l
   n2 += __shfl_xor(n2, 2, 64);
   const double nv = sqrt(n2);
   const F* L = logits + token * (long)planes * T;
-  auto dot_of = [&](int j) -> double {
-    double dot = 0.0;
-    for (int s_ = 0; s_ < planes; ++s_) {
-#pragma unroll 8
-      for (int k = 0; k < splits; ++k) dot += (double)L[k * split_stride + (long)s_ * T + j];
-    }
-    return dot;
-  };
   double best = -INFINITY;
   if (nv * smallest >= 1e-30) {
-    if (std::is_same<F, float>::value && (T & 3) == 0 && (split_stride & 3) == 0 && (((uintptr_t)logits) & 15) == 0) {
+    if (std::is_same<F, float>::value && (T & 3) == 0 && (((uintptr_t)logits) & 15) == 0) {
       for (int j0 = 4 * q; j0 < T; j0 += 16) {
-        double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
-        for (int s_ = 0; s_ < planes; ++s_) {
-          const float* at = (const float*)L + (long)s_ * T + j0;
-#pragma unroll 8
-          for (int k = 0; k < splits; ++k) {
-            const f32x4_t x = *(const f32x4_t*)(at + k * split_stride);
-            d0 += x[0]; d1 += x[1]; d2 += x[2]; d3 += x[3];
-          }
+        f32x4_t x = *(const f32x4_t*)((const float*)L + j0);
+        double d0 = x[0], d1 = x[1], d2 = x[2], d3 = x[3];
+        for (int s_ = 1; s_ < planes; ++s_) {
+          x = *(const f32x4_t*)((const float*)L + (long)s_ * T + j0);
+          d0 += x[0]; d1 += x[1]; d2 += x[2]; d3 += x[3];
         }
         best = fmax(best, fmax(fmax(d0 * rq[j0], d1 * rq[j0 + 1]), fmax(d2 * rq[j0 + 2], d3 * rq[j0 + 3])));
       }
     } else {
       for (int j = q; j < T; j += 4) {
-        best = fmax(best, dot_of(j) * rq[j]);
+        double dot = (double)L[j];
+        for (int s_ = 1; s_ < planes; ++s_) dot += (double)L[(long)s_ * T + j];
+        best = fmax(best, dot * rq[j]);
       }
     }
     best = best / nv;     // nv > 0 here
   } else {
     for (int j = q; j < T; j += 4) {
+      double dot = (double)L[j];
+      for (int s_ = 1; s_ < planes; ++s_) dot += (double)L[(long)s_ * T + j];
       const double den = nv * sqrt((double)qnorm2[(long)b * T + j]);
-      best = fmax(best, dot_of(j) / fmax(den, 1e-30));
+      best = fmax(best, dot / fmax(den, 1e-30));
     }
   }
   best = fmax(best, __shfl_xor(best, 1, 64));
@@ -572,22 +557,21 @@ hipError_t launch_sum_split3(const float* src, int planes, long plane_stride, lo
   return hipGetLastError();
 }
 
-hipError_t launch_query_rows(const float* src, int planes, long plane_stride, long rows, int d, float* eq, unsigned short* eq3,
-                             float* norm2, hipStream_t st) {
+hipError_t launch_query_rows(const float* src, long rows, int d, unsigned short* eq3, float* norm2, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
-  if (d % 4 != 0 || plane_stride % 4 != 0 || rows > 0x7fffffffL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(query_rows_kernel, dim3((unsigned)rows), dim3(256), 0, st, src, planes, plane_stride, rows, d, eq, eq3, norm2);
+  if (d % 4 != 0 || rows > 0x7fffffffL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(query_rows_kernel, dim3((unsigned)rows), dim3(256), 0, st, src, rows, d, eq3, norm2);
   return hipGetLastError();
 }
 
-hipError_t launch_cosine_max(const void* logits, int planes, int splits, long split_stride, const void* vnorm2, int nparts, const void* qnorm2, bool f64,
+hipError_t launch_cosine_max(const void* logits, int planes, const void* vnorm2, int nparts, const void* qnorm2, bool f64,
                              float* s_query, int B, int N, int T, hipStream_t st) {
   if (B <= 0 || N <= 0) return hipSuccess;
   dim3 grid((unsigned)((N + 63) / 64), (unsigned)B), block(256);
   const size_t lds = (size_t)(T + 1) * sizeof(double);
   if (lds > 48 * 1024) return hipErrorInvalidValue;     // more than 6143 query keywords
-  if (f64) hipLaunchKernelGGL((cosine_max_kernel<double>), grid, block, lds, st, (const double*)logits, planes, splits, split_stride, (const double*)vnorm2, nparts, (const double*)qnorm2, s_query, N, T);
-  else hipLaunchKernelGGL((cosine_max_kernel<float>), grid, block, lds, st, (const float*)logits, planes, splits, split_stride, (const float*)vnorm2, nparts, (const float*)qnorm2, s_query, N, T);
+  if (f64) hipLaunchKernelGGL((cosine_max_kernel<double>), grid, block, lds, st, (const double*)logits, planes, (const double*)vnorm2, nparts, (const double*)qnorm2, s_query, N, T);
+  else hipLaunchKernelGGL((cosine_max_kernel<float>), grid, block, lds, st, (const float*)logits, planes, (const float*)vnorm2, nparts, (const float*)qnorm2, s_query, N, T);
   return hipGetLastError();
 }
 

@@ -533,8 +533,7 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
 // per k-tile, the fragments of the next k-tile read while the current one is multiplied; two workgroups fit a compute unit, so
 // one's waits are the other's MFMAs.  Rows beyond M / N are clamped when loading and masked in the epilogue; requires
 // K % 32 == 0.  Bound by the latency of a k-step where a workgroup has its compute unit to itself.  fp32 results against
-// gemm_nt_kernel, us: 1332 x 3584 x 3584 88 -> 73, twelve of 1601 x 111 x 3584 in two parts of k 50 -> 41, row norms of 576 x 4096 x
-// 4096 65 -> 43.
+// gemm_nt_kernel, us: 1332 x 3584 x 3584 88 -> 73, row norms of 576 x 4096 x 4096 65 -> 43.
 template <int EPI>
 __global__ __launch_bounds__(THREADS, 2) void gemm_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr bool F64 = EPI == EPI_STORE_F64;
@@ -700,6 +699,130 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_dma_kernel(GemmArgs g, int ti
       }
 }
 
+// The same for fp32 results of few tiles (the query side and the inner products of an image or a small batch): 64 x 64 block
+// tile, a wave has a 32 x 32 quadrant of it and walks over all of k, so that every element is one sum over k in the order of
+// the kernels above, whatever the size of the product.  k-tile 64, a ring of NST 16 KB stages (swz rows) filled NST - 1
+// k-tiles ahead, one barrier per k-tile, the fragments of the next k-tile read while the current one is multiplied.  Bound by
+// the latency of the loads while a workgroup has its compute unit to itself (NST = 10, all of the LDS), else by the LDS and L2
+// traffic of the small tile (NST = 5, two workgroups per compute unit).  us, 128 x 128 tiles -> here: 32 x 4096 x 4096 36 -> 18,
+// 576 x 96 x 4096 36 -> 18, 444 x 3584 x 3584 48 -> 28.  (With k cut into up to 16 parts of partial products the same took 12
+// to 31 and the launches that added the parts as much again as they saved, and the parts' roundings were others than those of
+// a large product: two tokens with scores 1e-7 apart could change places at a cut.)  Requires K % 64 == 0.
+template <int NST>
+__global__ __launch_bounds__(THREADS, NST <= 5 ? 2 : 1) void gemm_few_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int BT = 64, BK = 64, OPND = BT * ROWB, STAGE = 2 * OPND;      // bytes: A tile then B tile
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, lh = lane >> 5;
+  const int wm = wave >> 1, wn = wave & 1;
+  const TileMap tmap = map_block(blockIdx.x, gridDim.x, tiles_m, tiles_n);
+  const int row0 = tmap.tm * BT, col0 = tmap.tn * BT;
+  const int bo = tmap.b / g.batch_inner, bi = tmap.b - bo * g.batch_inner;
+  const bf16_t* __restrict__ A = (const bf16_t*)g.A + (long)bo * g.strideA + (long)bi * g.strideA2;
+  const bf16_t* __restrict__ B = (const bf16_t*)g.B + (long)bo * g.strideB + (long)bi * g.strideB2;
+  // wave w issues loads j = 0, 1 per operand and stage; load j fills tile rows 8 (2w + j) .. +7: lane l -> row + l / 8,
+  // 16-byte slot l % 8 (see swz).  Rows beyond M / N: the last one again, left out when storing.
+  const bf16_t* ga[2];
+  const bf16_t* gb[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = 8 * (2 * wave + j) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    ga[j] = A + (long)min(row0 + r, g.M - 1) * g.lda + c * 8;
+    gb[j] = B + (long)min(col0 + r, g.N - 1) * g.ldb + c * 8;
+  }
+  const int nk = g.K / BK;
+  auto issue = [&](int kt, int st) {
+    const long k = (long)BK * min(kt, nk - 1);        // past the end: into a stage that is not used any more
+    unsigned char* s = smem + st * STAGE + wave * 2048;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[j] + k),
+                                       (__attribute__((address_space(3))) void*)(s + j * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[j] + k),
+                                       (__attribute__((address_space(3))) void*)(s + OPND + j * 1024), 16, 0, 0);
+    }
+  };
+  int offA[4], offB[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    offA[ks] = swz(wm * 32 + li, 2 * ks + lh);
+    offB[ks] = OPND + swz(wn * 32 + li, 2 * ks + lh);
+  }
+  auto frags = [&](int st, bf16x8_t (&fa)[4], bf16x8_t (&fb)[4]) {
+    const unsigned char* s = smem + st * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      fa[ks] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(s + offA[ks]));
+      fb[ks] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(s + offB[ks]));
+    }
+  };
+  f32x16_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  auto mma = [&](const bf16x8_t (&fa)[4], const bf16x8_t (&fb)[4]) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
+  };
+  auto next = [](int st) { return st + 1 == NST ? 0 : st + 1; };
+  // vmcnt(n) lgkmcnt(0), n = 4 loads per stage that may be under way
+  constexpr int kFirst = 4 * (NST - 2), kSteady = 4 * (NST - 3);
+  constexpr int kWaitFirst = 0x0070 | (kFirst & 15) | (kFirst >> 4 << 14), kWaitSteady = 0x0070 | (kSteady & 15) | (kSteady >> 4 << 14);
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s) issue(s, s);
+  __builtin_amdgcn_s_waitcnt(kWaitFirst);             // k-tile 0 has landed
+  __builtin_amdgcn_s_barrier();
+  bf16x8_t a0[4], b0[4], a1[4], b1[4];
+  frags(0, a0, b0);
+  int rd = 1, wr = NST - 1;                           // stage of k-tile kt + 1, of k-tile kt + NST - 1
+  // Per k-tile: wait until the next one has landed, barrier, start the loads NST - 1 ahead into the stage that held the
+  // previous one (every wave's reads of it are complete before it arrives at the barrier).
+  auto step = [&](int kt, bf16x8_t (&fa)[4], bf16x8_t (&fb)[4], bf16x8_t (&na)[4], bf16x8_t (&nb)[4]) {
+    __builtin_amdgcn_s_waitcnt(kWaitSteady);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    frags(rd, na, nb);
+    issue(kt + NST - 1, wr);
+    mma(fa, fb);
+    __builtin_amdgcn_sched_barrier(0);
+    rd = next(rd);
+    wr = next(wr);
+  };
+#pragma unroll 1
+  for (int kt = 0; kt < nk; kt += 2) {
+    step(kt, a0, b0, a1, b1);
+    if (kt + 1 >= nk) break;
+    step(kt + 1, a1, b1, a0, b0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);
+  float* C = (float*)g.C + (long)bo * g.strideC + (long)bi * g.strideC2;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int r = row0 + wm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3), c = col0 + wn * 32 + li;
+    if (r < g.M && c < g.N) C[(long)r * g.ldc + c] = acc[v];
+  }
+}
+
+// 128 x 128 tiles below which gemm_few_kernel is taken.  us, on 128 x 128 tiles / here: 104 tiles (1601 x 111 x 3584, batch 8)
+// 37 / 27, 112 (444 x 3584 x 3584) 48 / 28, 156 44 / 40, 168 (740 x 3584 x 3584) 49 / 44, 180 (576 x 96 x 1024, batch 36) 16.6 / 15.2,
+// 182 45 / 46; 196 (888 x 3584 x 3584) 46 / 49, 216 17 / 20, 240 15.7 / 18.4, 336 67 / 70, 392 67 / 73.  (Here and there the
+// small tiles win beyond it too: 260 of batch 20 88 / 73.)
+constexpr long kFewTiles128 = 192;
+
+inline hipError_t launch_few(const GemmArgs& g, hipStream_t stream) {
+  constexpr int STAGE = 2 * 64 * ROWB;
+  const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
+  const long nblocks = (long)tiles_m * tiles_n * g.batch;
+  if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
+  const bool deep = nblocks <= 256;                   // one workgroup per compute unit
+  const int lds = (deep ? 10 : 5) * STAGE;
+  const void* kern = deep ? (const void*)gemm_few_kernel<10> : (const void*)gemm_few_kernel<5>;
+  static PerDeviceInt raised[2];
+  const hipError_t attr = ensure_dynamic_lds(raised[deep], kern, lds);
+  if (attr != hipSuccess) return attr;
+  if (deep) hipLaunchKernelGGL(gemm_few_kernel<10>, dim3((unsigned)nblocks), dim3(THREADS), lds, stream, g, tiles_m, tiles_n);
+  else hipLaunchKernelGGL(gemm_few_kernel<5>, dim3((unsigned)nblocks), dim3(THREADS), lds, stream, g, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
 // The same for products of few tiles (the Gram matrix of one image's or a few images' rows): 32 x 32 tile, four waves that
 // each take a quarter of k in steps of 64, loaded straight into a ring of three 8 KB stages of the wave's own (no barrier in
 // the loop), one MFMA accumulator per wave, flushed into fp64 every 256 k; the four partial tiles are added in a fixed order.
@@ -861,6 +984,10 @@ hipError_t launch_t(const GemmArgs& g, hipStream_t stream) {
         return launch_ring<EPI>(g, stream);
       return launch_cfg<In, EPI, false, 4>(g, stream);
     }
+    if constexpr (EPI == EPI_STORE_F32) {
+      const long tiles = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch;
+      if (aligned16(g) && g.K % 64 == 0 && g.K >= 64 && tiles >= 1 && tiles < kFewTiles128) return launch_few(g, stream);
+    }
     // the direct loads were the faster ones at every measured shape they can take (gemm_dma_kernel)
     if (aligned16(g) && g.K % 32 == 0 && g.K >= 32 && g.M >= 1 && g.N >= 1 && g.batch >= 1) return launch_dma<EPI>(g, stream);
   }
@@ -880,19 +1007,6 @@ hipError_t launch_e(const GemmArgs& g, hipStream_t stream) {
 }  // namespace
 
 int gemm_tiles_n(int N) { return (N + 127) / 128; }
-
-// A 128 x 128 tile walks over k at about a microsecond per 128-byte step, whatever the rest of the device does, so fewer
-// tiles than compute units are cut along k until there are two per compute unit or a part is four steps long.  Measured, us,
-// with the launch that adds the parts: 32 x 4096 x 4096 (32 tiles, 8 parts) 55 + 22 -> 12 + 13, 576 x 96 x 4096 (5 tiles, 16
-// parts) 55 + 5 -> 9 + 10, 444 x 3584 x 3584 (112 tiles, 4 parts) 70 + 25 -> 31 + 10; 1332 x 3584 x 3584 has 308 tiles and stays
-// whole.
-int gemm_nt_splits(long M, long N, long K, long batch) {
-  const long tiles = ((M + 127) / 128) * ((N + 127) / 128) * batch;
-  if (tiles >= 192) return 1;
-  int s = 1;
-  while (s < 16 && tiles * s * 2 <= 512 && K % (64L * s * 2) == 0 && K / (s * 2) >= 256) s *= 2;
-  return s;
-}
 
 hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream) {
   return dtype == DT_BF16 ? launch_e<bf16_t>(g, stream) : launch_e<float>(g, stream);

@@ -45,9 +45,6 @@ struct GemmArgs {
   double* dots = nullptr;                      // [batch][M / kSymTile][N]
 };
 int gemm_tiles_n(int N);
-// In how many parts k is best cut so that a product of few tiles fills the device (1: not at all): the parts are batches of
-// their own (GemmArgs.batch_inner) that store partial products.
-int gemm_nt_splits(long M, long N, long K, long batch);
 hipError_t launch_gemm_nt(const GemmArgs& g, int dtype, hipStream_t stream);
 
 // ---------------------------------------------------------------- gemm64.hip
@@ -86,16 +83,14 @@ hipError_t launch_convert(const void* src, int in_type, void* dst, bool out_f64,
 hipError_t launch_sum_split3(const float* src, int planes, long plane_stride, long rows, int d, long rows_per_group,
                              unsigned short* out, hipStream_t stream);
 
-// Rows of a split contraction: the sum over the planes (in plane order) to eq, its three bf16 planes [3][rows][d] to eq3,
-// its squared length to norm2 (each optional).  d % 4 == 0, 16-byte aligned.
-hipError_t launch_query_rows(const float* src, int planes, long plane_stride, long rows, int d, float* eq, unsigned short* eq3,
-                             float* norm2, hipStream_t stream);
+// Rows of e(q): the three bf16 planes [3][rows][d] to eq3 (optional), the squared lengths to norm2, summed as
+// launch_row_norm2 does.  d % 4 == 0, 16-byte aligned.
+hipError_t launch_query_rows(const float* src, long rows, int d, unsigned short* eq3, float* norm2, hipStream_t stream);
 
 // Query-aware score (paper Sec. III-A.1): s_query[b,i] = max_j L[b,i,j] / max(|e(v_i)| |e(q_j)|, 1e-30) with
 // L[b,i,j] = sum_{s<planes} logits[b,i,s*T+j], |e(v_i)|^2 = sum_{t<nparts} vnorm2[(b*N+i)*nparts + t],
 // |e(q_j)|^2 = qnorm2[b*T+j].  The three inputs are fp32, or fp64 when f64 is set.
-// splits > 1: logits holds that many partial sums of L, split_stride elements apart.
-hipError_t launch_cosine_max(const void* logits, int planes, int splits, long split_stride, const void* vnorm2, int nparts, const void* qnorm2, bool f64,
+hipError_t launch_cosine_max(const void* logits, int planes, const void* vnorm2, int nparts, const void* qnorm2, bool f64,
                              float* s_query, int B, int N, int T, hipStream_t stream);
 
 // Attention-softmax relevance (variant): S is [B,H,T,N] logits (unscaled; fp32, or fp64 when f64 is set).

@@ -1,0 +1,75 @@
+"""Scores are one sum over the width per element, in one order, whatever the size of the product: an image scores the same
+alone and in any batch, copies of a token score and weigh the same, and the kept tokens are the fp64 oracle's."""
+import numpy as np
+import pytest
+
+import covspec_inputs as I
+import util as U
+from oracle import covspec_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def C():
+    import paper_2605_02218_amd as C
+    C.load_library()
+    return C
+
+
+@pytest.mark.parametrize("mode", ["cosine", "softmax"])
+@pytest.mark.parametrize("N,d,T,weights", [(200, 1024, 16, True), (130, 64, 5, True), (200, 192, 11, True), (190, 320, 33, True), (200, 4096, 16, False)],
+                         ids=["width-1024", "one-k-tile", "three-k-tiles", "remainders", "width-4096"])
+def test_an_image_scores_the_same_alone_and_in_a_batch(C, mode, N, d, T, weights):
+    """1, 80 and 96 images: the inner products are fewer 64 x 64 tiles than compute units, more than that, and enough 128 x 128
+    tiles for those.  Equal to the bit (all row norms stay below the size of the 256 x 256 kernel, which adds rows up in another
+    order).  The softmax variant's inner products are fp32 ones; only its e(q) is at stake."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d + T)
+    X, Q = (torch.randn(96, n, d, generator=g, device="cuda").bfloat16() for n in (N, T))
+    Wq, Wk = [(torch.randn(d, d, generator=g, device="cuda") / d ** 0.5).bfloat16() for _ in range(2)] if weights else (None, None)
+    got = []
+    for B in (1, 80, 96):
+        p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=T, n_heads=2, dtype=C.BF16, keep_k=4, preselect_m=8, rank_r=2,
+                     rel_mode=C.REL_COSINE_MAX if mode == "cosine" else C.REL_ATTN_SOFTMAX)
+        got.append(C.score(p, X[:B].contiguous(), None, Q[:B].contiguous(), Wq, Wk)[0])
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1][:1]) and torch.equal(got[1], got[2][:80])
+
+
+def test_copies_and_kept_tokens_of_a_single_image(C):
+    """576 x 4096 images with exact copies and 20x outliers, one at a time: copies have bit-equal scores and energies, and wherever
+    the fp64 values at both cuts are further apart than rounding can move them the kept tokens are the oracle's."""
+    import torch
+    w = I.small_workload(cid=41, name="single", batch=8, n_tokens=576, d_model=4096, dtype=I.BF16, n_query=32, n_heads=32, keep_k=144,
+                         preselect_m=288, rank_r=72, factor_rank=256, n_act_layers=2, structure="dups+outliers")
+    batch = U.gen_batch(w)
+    dev = U.upload(batch, w.dtype)
+    op, p = U.oracle_params(w), U.lib_params(C, w, 1)
+    decided = pairs = 0
+    for b in range(w.batch):
+        x, h, q = (dev[n][b:b + 1].contiguous() for n in ("X", "hidden", "Q"))
+        sq, sa, sf = C.score(p, x, h, q, dev["Wq"], dev["Wk"])
+        out = C.select(p, x, sf)
+        idx, _ = C.reduce(p, x, h, q, dev["Wq"], dev["Wk"])
+        sq, sf, c, idx_m = (t[0].cpu().numpy() for t in (sq, sf, out["c"], out["idx_m"]))
+        assert torch.equal(idx, out["idx"])
+        groups = np.unique(batch["X"][b], axis=0, return_inverse=True)[1].ravel()
+        for gid in np.flatnonzero(np.bincount(groups) > 1):
+            same = np.flatnonzero(groups == gid)
+            assert len(set(sf[same])) == 1
+            energies = c[np.isin(idx_m, same)]
+            pairs += energies.size > 1
+            assert len(set(energies)) <= 1
+        ref = U.oracle_image(w, batch, b, op)
+        # a cosine: fp32 roundings (2^-24) of d additions, adding up like a random walk; after min-max normalisation relative to
+        # the scores' range; both neighbours at the cut move
+        eps = 2 * w.d_model ** 0.5 * 2.0 ** -24
+        assert np.abs(sq - ref["s_query"]).max() < eps
+        eps *= 2 * w.lam / (ref["s_query"].max() - ref["s_query"].min())
+        v, e = np.sort(ref["s_fused"])[::-1], np.sort(ref["c"])[::-1]
+        # an energy: fp32 sums of 256 products (16 x 2^-24 of |z|^2), tenfold
+        if v[w.preselect_m - 1] - v[w.preselect_m] > eps and e[w.keep_k - 1] - e[w.keep_k] > 1e-5 * e[w.keep_k]:
+            decided += 1
+            np.testing.assert_array_equal(idx[0].cpu().numpy(), ref["idx"])
+    assert decided >= 3 and pairs >= 20

@@ -1,4 +1,4 @@
-"""bf16 scores whose products have so few tiles that k is cut into parts: against the same formulas in fp64."""
+"""bf16 scores and Gram matrices of few tiles (smaller tiles than those of large products): against the same formulas in fp64."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -13,9 +13,9 @@ def C():
 
 @pytest.mark.parametrize("weights", ["qk", "q", "k", ""])
 @pytest.mark.parametrize("B,N,d,T", [(1, 300, 1024, 16), (2, 130, 2048, 5), (1, 64, 512, 1), (1, 700, 1536, 33), (3, 90, 520, 2), (2, 200, 544, 3)],
-                         ids=["four-parts", "batch-odd-keywords", "one-keyword", "two-tiles", "width-not-cut", "last-column-tile-a-quarter"])
+                         ids=["two-row-tiles", "batch-odd-keywords", "one-keyword", "two-tiles", "width-not-64", "width-32"])
 @pytest.mark.parametrize("mode", ["cosine", "softmax"])
-def test_scores_with_k_in_parts(C, mode, B, N, d, T, weights):
+def test_scores_of_few_tiles(C, mode, B, N, d, T, weights):
     import torch
     g = torch.Generator().manual_seed(N + T)
     X, Q = torch.randn(B, N, d, generator=g).bfloat16().cuda(), torch.randn(B, T, d, generator=g).bfloat16().cuda()
