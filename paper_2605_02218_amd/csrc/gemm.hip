@@ -826,6 +826,8 @@ inline hipError_t launch_few(const GemmArgs& g, hipStream_t stream) {
 // The same for products of few tiles (the Gram matrix of one image's or a few images' rows): 32 x 32 tile, four waves that
 // each take a quarter of k in steps of 64, loaded straight into a ring of three 8 KB stages of the wave's own (no barrier in
 // the loop), one MFMA accumulator per wave, flushed into fp64 every 256 k; the four partial tiles are added in a fixed order.
+// A wave's share begins at a multiple of 256 k, so that the fp32 partial sums are those of the kernel above and a result does
+// not depend on how many tiles there are beyond the rounding of fp64 sums.
 // A 128 x 128 tile has no more than 6 workgroups for 288 rows and walks all of k in each: 85 us for 288 x 288 x 4096,
 // 10.8 here (four images of 256 x 256 x 1536: 35 -> 7.5).  Requires K % 64 == 0 and 16-byte aligned rows.
 __global__ __launch_bounds__(THREADS) void gemm_gram_small_kernel(GemmArgs g, int tiles_m, int tiles_n) {
@@ -838,7 +840,8 @@ __global__ __launch_bounds__(THREADS) void gemm_gram_small_kernel(GemmArgs g, in
   const int row0 = tm * 32, col0 = tn * 32;
   const bf16_t* __restrict__ A = (const bf16_t*)g.A + (long)b * g.strideA;
   const bf16_t* __restrict__ B = (const bf16_t*)g.B + (long)b * g.strideB;
-  const int nc = g.K >> 6, c0 = nc * wave / 4, c1 = nc * (wave + 1) / 4;     // this wave's steps
+  const int nc = g.K >> 6, ng = (nc + 3) >> 2;
+  const int c0 = 4 * (ng * wave / 4), c1 = min(4 * (ng * (wave + 1) / 4), nc);     // this wave's steps
   // load j fills tile rows 8j .. 8j + 7: lane l -> row 8j + l / 8, 16-byte slot l % 8 (see swz)
   const bf16_t* ga[4];
   const bf16_t* gb[4];

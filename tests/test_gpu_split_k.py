@@ -60,3 +60,21 @@ def test_gram_matrix_of_few_tiles(C, B, N, M, d):
         err = (out["c"][b].double().cpu() - ref).abs() / ref.clamp_min(1e-3 * ref.max())
         # fp32 sums over 256 products (2^-24 each, random walk), magnified by the gap at the cut (relative 1 - 0.97^2, 0.06)
         assert err.max() < 4 * 16 * 2 ** -24 / 0.06
+
+
+@pytest.mark.parametrize("m,d", [(128, 320), (100, 448), (128, 1088), (128, 1536), (128, 256)])
+def test_gram_matrix_does_not_depend_on_the_number_of_tiles(C, m, d):
+    """One video alone (few tiles) and as one of 64 (many): the same fp32 sums over 256 products each, so that only the order of
+    a handful of fp64 additions differs."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(m + d)
+    X, s = torch.randn(64, 160, d, generator=g, device="cuda").bfloat16(), torch.rand(64, 160, generator=g, device="cuda")
+    got = []
+    for B in (1, 64):
+        p = C.StreamParams(batch=B, n_frame=160, d_model=d, frame_m=m, keep_k=m, rank_r=8, dtype=C.BF16)
+        out = C.stream_alloc_state(p)
+        C.stream_step(p, 0, 0, X[:B].contiguous(), s[:B].contiguous(), None, out)
+        got.append(out[1][0].clone())
+    torch.cuda.synchronize()
+    assert got[0].diagonal().min() > 0
+    assert (got[0] - got[1]).abs().max() < 1e-14 * got[0].max()
