@@ -268,8 +268,8 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
  * paper's Sec. III-A.3 asks for a rank-r SVD and says nothing of how).  path_out: DEVICE int32 [B]:
  *   1  block subspace iteration, converged at the first residual check
  *   2  converged after the additional steps of the second pass
- *   0  the Gram matrix as a whole: full Jacobi solve (fallback, or the block would be most of the matrix), or
- *      split directly at its r-th eigenvalue (order up to 128)
+ *   3  no block: the Gram matrix (order up to 128) split directly at its r-th eigenvalue
+ *   0  full Jacobi solve of the Gram matrix (fallback, or the block would be most of the matrix)
  * Enqueued on `stream` after the call in question; reads the workspace, writes nothing else.
  */
 int covspec_lowrank_path(const covspec_params* p, const void* workspace, int32_t* path_out,

@@ -467,7 +467,8 @@ def reduce_ragged(p: Params, n_tokens, n_query, X, hidden, Q, Wq, Wk, streams=No
 
 
 def lowrank_path(p: Params, workspace):
-    """covspec_lowrank_path: int32 [B] tensor, the eigen-solve path of each image in the last call on `workspace`."""
+    """covspec_lowrank_path: int32 [B] tensor, the eigen-solve path of each image in the last call on `workspace`:
+    1, 2 = block iteration (first, second pass), 3 = direct split, 0 = full solve."""
     import torch
     out = torch.empty(p.batch, dtype=torch.int32, device=workspace.device)
     wp, _ = _ws_args(workspace)

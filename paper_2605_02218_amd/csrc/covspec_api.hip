@@ -605,7 +605,7 @@ int covspec_lowrank_path(const covspec_params* p, const void* workspace, int32_t
   if (!workspace || !path_out || ((uintptr_t)workspace & 255u)) return COVSPEC_INVALID_ARG;
   if (pl.lr != COVSPEC_LR_ENERGY_TOPK) return COVSPEC_INVALID_ARG;
   discard_pending_error();
-  if (pl.P > 0) {
+  if (pl.P > 0 || split_direct(pl.nP)) {
     HIPCHK(hipMemcpyAsync(path_out, (const char*)workspace + pl.ok, (size_t)pl.B * sizeof(int32_t), hipMemcpyDeviceToDevice,
                           (hipStream_t)stream));
   } else {

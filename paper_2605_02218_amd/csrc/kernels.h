@@ -163,7 +163,7 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
                                int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,
                                hipStream_t stream);
-// c[b][i] = (Pi G)_ii, i < n, from the projector of G[b] itself; done[b] = 1 where there is one, else 0 and c[b] untouched.
+// c[b][i] = (Pi G)_ii, i < n, from the projector of G[b] itself; done[b] = 3 where there is one, else 0 and c[b] untouched.
 hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n, int nP, int r, const void* scratch, int* done, float* c,
                                 hipStream_t stream);
 
@@ -171,7 +171,7 @@ hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n,
 // Energies c[b, i], i < n, in the span of the r dominant eigenvectors of G[b] (fp64, n x n, pitch nP, left untouched) by
 // block subspace iteration; for P == 0 and nP <= 128 by the projector of G itself.
 // subspace_block: block size P for (n, r), 0 when the matrix is better split (nP <= 128) or solved as a whole.
-// On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second.
+// On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second, 3 by the projector of G.
 int subspace_block(int n, int r);
 size_t subspace_workspace_bytes(int B, int n, int nP, int P);
 // probe_begin / probe_end (optional): recorded around the first of the subspace_product_launches(iters)

@@ -611,7 +611,7 @@ __global__ __launch_bounds__(1024) void split_finish_kernel(const double* __rest
   }
 }
 
-// c[b][i] = (Pi G)_ii for a projector of the Gram matrix itself; done[b] = 1 where the projector is valid.  One wave per row.
+// c[b][i] = (Pi G)_ii for a projector of the Gram matrix itself; done[b] = 3 where the projector is valid, else 0.  One wave per row.
 __global__ __launch_bounds__(256) void direct_energy_kernel(const double* __restrict__ G, const double* __restrict__ Pi, int n, int nP, int r,
                                                             const SplitCtl* __restrict__ ctl, int* __restrict__ done, float* __restrict__ c) {
   __shared__ double red[4];
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(256) void direct_energy_kernel(const double* __rest
   const long base = (long)b * nP * nP;
   bool good = projector_valid(ctl + b);              // uniform
   if (good) good = trace_minus(Pi + base, nP, r, red, 256) < 1e-3;
-  if (blockIdx.x == 0 && threadIdx.x == 0) done[b] = good ? 1 : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) done[b] = good ? 3 : 0;
   if (!good) return;
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= n) return;
