@@ -8,7 +8,9 @@
 // found by a threshold instead of K rounds of a block-wide argmax: tau = the K-th largest of the 64 quad
 // maxima, so at least K logits are >= tau and, for continuous data, only about K more; those few go to a list
 // in LDS that one wave ranks by all-pairs comparison.  A list that overflows (many equal logits, or fewer than
-// K quads with data) falls back to K rounds of block-wide argmax over the registers: slower, same result.
+// K quads with data) goes another way to the same result: the logits above the K-th largest thread maximum are ranked by
+// the workgroup and the lowest words among those equal to it fill up, or, where more than 256 are above, K rounds of block-wide
+// argmax.
 // Bound by the latency of a workgroup's dozen phases, so by how many of them a compute unit holds: with the logits widened to
 // fp32 and the fallback's packed keys formed ahead of its loop the kernel took 87 registers (5 waves per SIMD) and 49 us for
 // 512 rows of 151936 bf16 words; with the logits kept as loaded, one reference per thread instead of a running one and the
@@ -41,7 +43,7 @@ __device__ __forceinline__ float key_value(u64 k) {
   return __uint_as_float((o & 0x80000000u) ? (o ^ 0x80000000u) : ~o);
 }
 
-// lane's rank among the n <= 64 distinct keys of an LDS array: the number of keys greater than its own
+// rank of a key among the n distinct keys of an LDS array: the number of keys greater than its own
 __device__ __forceinline__ int wave_rank(const u64* keys, int n, u64 mine) {
   int rank = 0;
   int j = 0;
@@ -67,10 +69,10 @@ __global__ __launch_bounds__(DTH, DT == DT_F32 ? 6 : 8) void draft_scan_kernel(c
   constexpr int NV = EPT / N;
   __shared__ u64 gkey[64];
   __shared__ u64 list[LISTCAP];
-  __shared__ u64 wbest[DTH / 64];
+  __shared__ u64 wbest[2][DTH / 64];
   __shared__ double red[DTH / 64][2];
   __shared__ float sh_tau;
-  __shared__ int sh_cnt, sh_found;
+  __shared__ int sh_cnt, sh_found, sh_above, equal[2][DTH / 64];
   __shared__ u32x4_t pool[POOL][NV];      // EPT logits of a thread, as loaded
   __shared__ int pool_id[POOL];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -124,14 +126,13 @@ __global__ __launch_bounds__(DTH, DT == DT_F32 ? 6 : 8) void draft_scan_kernel(c
       }
     sum = s0 + s1;
   }
-  auto word_of = [&](int e) { return w0 + ((e / N) * DTH + tid) * N + (e % N); };
 
   // quad maxima -> tau
   const float own = tmax;
   tmax = fmaxf(tmax, __shfl_xor(tmax, 1, 64));
   tmax = fmaxf(tmax, __shfl_xor(tmax, 2, 64));
   if ((lane & 3) == 0) gkey[tid >> 2] = ((u64)float_order_key(tmax) << 32) | (u64)(63 - (tid >> 2));
-  if (tid == 0) { sh_cnt = 0; sh_found = 0; }
+  if (tid == 0) { sh_cnt = 0; sh_found = 0; sh_above = 0; }
   {
     double mm, ss;
     block_combine<DTH / 64>(cref, sum, red, mm, ss);      // its barrier also publishes gkey and sh_cnt
@@ -179,36 +180,107 @@ __global__ __launch_bounds__(DTH, DT == DT_F32 ? 6 : 8) void draft_scan_kernel(c
     }
     return;
   }
-  // fallback: K rounds of block-wide argmax over the registers
-  uint32_t alive = nv * N >= 32 ? 0xFFFFFFFFu : (1u << (nv * N)) - 1u;      // whole vectors: bits i*N .. i*N+N-1
-  for (int r = 0; r < K; ++r) {
-    u64 best = 0ull;
+  // Many logits of tau or more: equal ones (bf16 rows with a wide candidate list, masked words), or live words in few quads.
+  // Another tau, the K-th largest of the threads' maxima; the logits above it are listed and ranked by the whole workgroup, and
+  // the rest of the K are the lowest words among those equal to it.  The logits are read anew from here on (from the caches), so
+  // that none is live in a register.
+  auto word_at = [&](int i) { return w0 + (i * DTH + tid) * N; };
+  u64* big = (u64*)&pool[0][0];       // DTH keys; the pool has been looked through
+  const u64 own_key = ((u64)float_order_key(own) << 32) | (u64)(DTH - 1 - tid);
+  big[tid] = own_key;
+  __syncthreads();
+  if (wave_rank(big, DTH, own_key) == K - 1) sh_tau = key_value(own_key);
+  __syncthreads();
+  const float tau2 = sh_tau;
+#pragma unroll 1
+  for (int i = 0; i < nv; ++i) {
+    float t[N];
+    LogitVec<DT>::load(zd, base + word_at(i), t);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
+    for (int e = 0; e < N; ++e)
+      if (t[e] > tau2) {
+        const int pos = atomicAdd(&sh_above, 1);
+        if (pos < DTH) big[pos] = pack_key(t[e], word_at(i) + e);
+      }
+  }
+  __syncthreads();
+  const int above = sh_above;
+  if (above <= DTH) {
+    if (tid < above) {
+      const u64 mine = big[tid];
+      const int rank = wave_rank(big, above, mine);
+      if (rank < K) out[rank] = mine;
+    }
+    const int need = K - above;
+    int have = 0;                     // words equal to tau2 in the vectors before i, the same in every thread
+#pragma unroll 1
+    for (int i = 0; i < NV && have < need; ++i) {
       float t[N];
-      asm volatile("" : "+v"(raw[i]));      // keeps the 32 packed keys from being formed ahead of the loop, 64 registers
-      LogitVec<DT>::unpack(raw[i], t);
+      int mine = 0;
+      if (i < nv) {
+        LogitVec<DT>::load(zd, base + word_at(i), t);
 #pragma unroll
-      for (int e = 0; e < N; ++e) {
-        if (((alive >> (i * N + e)) & 1u) && t[e] == t[e]) {
-          const u64 k = pack_key(t[e], word_of(i * N + e));
-          best = k > best ? k : best;
-        }
+        for (int e = 0; e < N; ++e) mine += t[e] == tau2 ? 1 : 0;
+      }
+      int upto = mine;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(upto, o, 64);
+        if (lane >= o) upto += v;
+      }
+      if (lane == 63) equal[i & 1][wv] = upto;
+      __syncthreads();                // the other set of `equal` is free behind the next vector's
+      int pos = have + upto - mine;
+#pragma unroll
+      for (int k = 0; k < DTH / 64; ++k) {
+        const int v = equal[i & 1][k];
+        if (k < wv) pos += v;
+        have += v;
+      }
+      if (mine > 0) {
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+          if (t[e] == tau2) {
+            if (pos < need) out[above + pos] = pack_key(tau2, word_at(i) + e);
+            ++pos;
+          }
       }
     }
-    best = wave_max(best);
-    if (lane == 0) wbest[wv] = best;
-    __syncthreads();
-    u64 b = wbest[0];
+    for (int p = have + tid; p < need; p += DTH) out[above + p] = 0ull;      // fewer than K logits in the chunk
+    return;
+  }
+  // More than DTH above tau2 (in fewer than K threads): K rounds of block-wide argmax.  A thread keeps the key of its largest word that is left, and only
+  // the thread that lost it looks through its words again.
+  uint32_t alive = nv * N >= 32 ? 0xFFFFFFFFu : (1u << (nv * N)) - 1u;      // whole vectors: bits i*N .. i*N+N-1
+  auto largest = [&]() -> u64 {
+    u64 best = 0ull;
+#pragma unroll 1
+    for (int i = 0; i < nv; ++i) {
+      const int w = word_at(i);
+      float t[N];
+      LogitVec<DT>::load(zd, base + w, t);
 #pragma unroll
-    for (int k = 1; k < DTH / 64; ++k) b = wbest[k] > b ? wbest[k] : b;
-    if (b != 0ull) {
-      const int rel = key_word(b) - w0;                   // in [0, DCL)
-      const int vec = rel / N;
-      if ((vec % DTH) == tid) alive &= ~(1u << ((vec / DTH) * N + rel % N));
+      for (int e = 0; e < N; ++e) {
+        const u64 k = pack_key(t[e], w + e);
+        if (((alive >> (i * N + e)) & 1u) && t[e] == t[e] && k > best) best = k;
+      }
     }
+    return best;
+  };
+  u64 mine = largest();
+  for (int r = 0; r < K; ++r) {
+    const u64 best = wave_max(mine);
+    if (lane == 0) wbest[r & 1][wv] = best;
+    __syncthreads();                  // the other set of wbest is free behind the next round's
+    u64 b = wbest[r & 1][0];
+#pragma unroll
+    for (int k = 1; k < DTH / 64; ++k) b = wbest[r & 1][k] > b ? wbest[r & 1][k] : b;
     if (tid == 0) out[r] = b;
-    __syncthreads();
+    if (b != 0ull && b == mine) {     // keys are distinct: one thread
+      const int rel = key_word(b) - w0;                   // in [0, DCL)
+      alive &= ~(1u << ((rel / N / DTH) * N + rel % N));
+      mine = largest();
+    }
   }
 }
 
