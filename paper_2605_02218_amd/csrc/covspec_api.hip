@@ -643,7 +643,7 @@ static int verify_check(const covspec_verify_params* p) {
   if (!p) return COVSPEC_INVALID_ARG;
   if (p->n_seq < 1 || p->n_draft < 1 || p->vocab < 2) return COVSPEC_INVALID_ARG;
   if (p->dtype != COVSPEC_FP32 && p->dtype != COVSPEC_BF16 && p->dtype != COVSPEC_FP16) return COVSPEC_INVALID_ARG;
-  // one lane per drafted position in the acceptance kernel (alpha of every position is written in one pass)
+  // the acceptance kernel keeps a sequence's positions in 64-entry arrays and finds the first rejection with one ballot
   if (p->n_draft > 64 || (long)p->n_seq * p->n_draft > 65535) return COVSPEC_UNSUPPORTED;
   if (p->vocab % (p->dtype == COVSPEC_FP32 ? 4 : 8) != 0) return COVSPEC_UNSUPPORTED;
   return COVSPEC_OK;

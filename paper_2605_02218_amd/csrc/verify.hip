@@ -48,24 +48,27 @@ __global__ __launch_bounds__(VT) void verify_stats_kernel(const void* __restrict
 
 constexpr int AW = 8;              // waves of the acceptance kernel
 
-// One workgroup per sequence; a wave takes the positions w, w + AW, ..., its lanes the position's chunks (at most 64): row
-// statistics from the chunk partials (one exponential per lane against the largest reference, one sum), alpha at the drafted
-// token; then wave 0, lane = position, finds the first rejection.  rowmax[s * 4 + {0,1}] = the rejected row's references
+// One workgroup per sequence; `group` lanes (the smallest power of two that holds a row's chunks, at most 64) take a position, a
+// wave as many positions at once as it has groups: row statistics from the chunk partials (one exponential per lane against the
+// largest reference, one sum), alpha at the drafted token; then wave 0, lane = position, finds the first rejection (L <= 64).  rowmax[s * 4 + {0,1}] = the rejected row's references
 // brought back to the natural domain, i.e. its maximum logits to within rounding: the shift the fp64 passes below use (any
 // value near the maximum serves, as long as every pass uses the same), [2] = the ratio of the two streaming sums; untouched
 // when nothing is rejected.  With one lane per position that folds the chunks one by one, two fp64 exponentials each, one
-// sequence of 5 positions in 64 chunks took 11.5 us; now 3.4.
+// sequence of 5 positions in 64 chunks took 11.5 us; now 3.4.  With a wave per position whatever the number of chunks,
+// sixteen sequences of 64 positions in one chunk took 20 us.
 template <int DT>
 __global__ __launch_bounds__(64 * AW) void verify_accept_kernel(const void* __restrict__ zt, const void* __restrict__ zd,
                                                                 const int32_t* __restrict__ tok, const float* __restrict__ u_acc, int L,
-                                                                int V, int chunks, const double* __restrict__ stats,
+                                                                int V, int chunks, int group, const double* __restrict__ stats,
                                                                 int32_t* __restrict__ n_acc, float* __restrict__ alpha_out,
                                                                 double* __restrict__ rowmax) {
   __shared__ double sh[64][3];       // per position: what rowmax gets
   __shared__ int sh_rej[64];
   const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int t = wv; t < L; t += AW) {
-    const long row = (long)s * L + t;
+  const int c = lane & (group - 1), groups = 64 / group;
+  for (int t0 = wv * groups; t0 < L; t0 += AW * groups) {      // uniform in a wave: every lane takes part in the exchanges
+    const int t = t0 + lane / group;
+    const long row = (long)s * L + (t < L ? t : L - 1);
     int y = tok[row];
     y = y < 0 ? 0 : (y >= V ? V - 1 : y);     // never index outside the row
     const double xt = LogitVec<DT>::at(zt, row * V + y), xd = LogitVec<DT>::at(zd, row * V + y);
@@ -73,20 +76,22 @@ __global__ __launch_bounds__(64 * AW) void verify_accept_kernel(const void* __re
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       double mc = -INFINITY, sc = 0.0;
-      if (lane < chunks) {
-        mc = stats[(row * chunks + lane) * 4 + 2 * q];
-        sc = stats[(row * chunks + lane) * 4 + 2 * q + 1];
+      if (c < chunks) {
+        mc = stats[(row * chunks + c) * 4 + 2 * q];
+        sc = stats[(row * chunks + c) * 4 + 2 * q + 1];
       }
       const bool has = sc > 0.0;              // a chunk of masked words has no sum
-      const double mm = wave_max(has ? mc : -INFINITY);
+      double mm = has ? mc : -INFINITY;
+      for (int o = group >> 1; o > 0; o >>= 1) mm = fmax(mm, __shfl_xor(mm, o, 64));
       m[q] = mm == -INFINITY ? 0.0 : mm;
-      sum[q] = wave_sum(has ? sc * exp2(mc - m[q]) : 0.0);
+      sum[q] = has ? sc * exp2(mc - m[q]) : 0.0;
+      for (int o = group >> 1; o > 0; o >>= 1) sum[q] += __shfl_xor(sum[q], o, 64);
     }
     const double pt = exp2(xt * (double)kLog2e - m[0]) / sum[0];
     const double pd = exp2(xd * (double)kLog2e - m[1]) / sum[1];
     const double a = pd > 0.0 ? fmin(1.0, pt / pd) : 1.0;
     const float af = (float)a;
-    if (lane == 0) {
+    if (c == 0 && t < L) {
       if (alpha_out) alpha_out[row] = af;
       sh_rej[t] = !(u_acc[row] < af) ? 1 : 0;
       sh[t][0] = m[0] / (double)kLog2e;
@@ -103,8 +108,8 @@ __global__ __launch_bounds__(64 * AW) void verify_accept_kernel(const void* __re
   if (lane == 0) n_acc[s] = first;
 }
 
-// e^x for the fp64 passes, x <= 0 to within rounding: x = n ln 2 + f with |f| <= ln 2 / 2, the Taylor polynomial of degree 13
-// (remainder below 5e-18) and a scaling by 2^n.  Beyond -800 the result is 0, a NaN stays one.  About 20 fp64 instructions.
+// e^x for the fp64 passes, x <= 0 to within rounding: x = n ln 2 + f with |f| <= ln 2 / 2 (Cody and Waite's two-part reduction),
+// the Taylor polynomial of degree 13 (remainder below 5e-18) and a scaling by 2^n.  Beyond -800 the result is 0, a NaN stays one.  About 20 fp64 instructions.
 __device__ __forceinline__ double exp_shifted(double x) {
   x = x < -800.0 ? -800.0 : x;
   const double n = rint(x * 1.4426950408889634074);
@@ -149,18 +154,25 @@ __global__ __launch_bounds__(VT) void verify_rowpass64_kernel(const void* __rest
   const double mt = rowmax[s * 4], md = rowmax[s * 4 + 1], kap = rowmax[s * 4 + 2];
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   constexpr int N = LogitVec<DT>::N;
-  for (int w = w0 + threadIdx.x * N; w < w1; w += VT * N) {      // V, rlen % N == 0: whole vectors only
-    float a[N], c[N];
-    LogitVec<DT>::load(zt, base + w, a);
-    LogitVec<DT>::load(zd, base + w, c);
+  auto add = [&](double xt, double xd) {
+    const double et = exp_shifted(xt - mt), ed = exp_shifted(xd - md);
+    acc[0] += et;
+    acc[1] += ed;
+    const bool more = et > kap * ed;                             // equal rows: kap == 1 and et == ed exactly, nothing is picked
+    acc[2] += more ? et : 0.0;
+    acc[3] += more ? ed : 0.0;
+  };
+  if (w1 - w0 <= VT) {
+    // a word per thread: eight of them one after the other in an eighth of the threads take 4.2 us where this takes 3.3
+    const int w = w0 + threadIdx.x;
+    if (w < w1) add(LogitVec<DT>::at(zt, base + w), LogitVec<DT>::at(zd, base + w));
+  } else {
+    for (int w = w0 + threadIdx.x * N; w < w1; w += VT * N) {    // V, rlen % N == 0: whole vectors only
+      float a[N], c[N];
+      LogitVec<DT>::load(zt, base + w, a);
+      LogitVec<DT>::load(zd, base + w, c);
 #pragma unroll
-    for (int e = 0; e < N; ++e) {
-      const double et = exp_shifted((double)a[e] - mt), ed = exp_shifted((double)c[e] - md);
-      acc[0] += et;
-      acc[1] += ed;
-      const bool more = et > kap * ed;                           // equal rows: kap == 1 and et == ed exactly, nothing is picked
-      acc[2] += more ? et : 0.0;
-      acc[3] += more ? ed : 0.0;
+      for (int e = 0; e < N; ++e) add((double)a[e], (double)c[e]);
     }
   }
 #pragma unroll
@@ -211,9 +223,10 @@ __device__ __forceinline__ double residual_of(double zt, double zd, double mt, d
 }
 
 // One 1024-thread workgroup per sequence: inverse CDF of the residual in vocabulary order.  A thread's residuals are kept in
-// registers between the two passes over them (14.7 -> 11.9 us for 64 sequences).
+// registers between the two passes over them (14.7 -> 11.9 us for 64 sequences).  64 registers, so that a compute unit holds
+// two workgroups: with 66 and one, 512 sequences of 8192 words took 20.5 us, 15.4 with two.
 template <int DT>
-__global__ __launch_bounds__(1024) void verify_sample_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int L, int V,
+__global__ __launch_bounds__(1024, 8) void verify_sample_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int L, int V,
                                                              int clen, int chunks, const int32_t* __restrict__ n_acc,
                                                              const double* __restrict__ rowmax, const double* __restrict__ rowsum,
                                                              const float* __restrict__ u_res, int32_t* __restrict__ corr) {
@@ -266,16 +279,22 @@ __global__ __launch_bounds__(1024) void verify_sample_kernel(const void* __restr
     if (tid == 0) corr[s] = (int)(0xFFFFFFFFu - (uint32_t)(sh_best & 0xFFFFFFFFull));
     return;
   }
-  // inside the chunk: thread `tid` owns contiguous words: eight of them, kept in registers, where the chunk has no more
-  // than that per thread, else [w0 + tid*per, w0 + (tid+1)*per), evaluated twice
+  // inside the chunk: thread `tid` owns the words [w0 + tid*per, w0 + (tid+1)*per): one, two or eight of them, kept in registers,
+  // where the chunk has no more than that per thread, else more, evaluated twice.  (Eight by an eighth of the threads took
+  // 13.3 us for 512 chunks of 256 words, one by each 9.4.)
   const int w0 = cs * clen, w1 = min(V, w0 + clen);
   constexpr int N = LogitVec<DT>::N;
-  const bool held = w1 - w0 <= 8 * 1024;
-  const int per = held ? 8 : (w1 - w0 + 1023) / 1024;
+  const int n = w1 - w0, per = n <= 1024 ? 1 : n <= 2048 ? 2 : n <= 8192 ? 8 : (n + 1023) / 1024;
   const int a0 = w0 + tid * per, a1 = min(w1, a0 + per);
   auto residual_at = [&](int w) { return residual_of(LogitVec<DT>::at(zt, base + w), LogitVec<DT>::at(zd, base + w), mt, ist, md, isd); };
   double mine = 0.0, r8[8];
-  if (held) {
+  if (per <= 2) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      r8[e] = e < per && a0 + e < w1 ? residual_at(a0 + e) : 0.0;
+      mine += r8[e];
+    }
+  } else if (per == 8) {
 #pragma unroll
     for (int v = 0; v < 8 / N; ++v) {               // w0, w1 % N == 0: whole vectors only
       float a[N], c[N];
@@ -318,9 +337,12 @@ __global__ __launch_bounds__(1024) void verify_sample_kernel(const void* __restr
     run += r;
     if (hit == 0x7fffffff && run > target && r > 0.0) hit = w;
   };
-  if (held) {
+  if (per <= 2) {
+    step(a0, r8[0]);
+    step(a0 + 1, r8[1]);                                  // no mass where it is another thread's or beyond the chunk
+  } else if (per == 8) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) step(a0 + e, r8[e]);      // beyond the chunk: no mass
+    for (int e = 0; e < 8; ++e) step(a0 + e, r8[e]);
   } else {
     for (int w = a0; w < a1; ++w) step(w, residual_at(w));
   }
@@ -374,9 +396,11 @@ static hipError_t launch_verify_t(const void* zt, const void* zd, const int32_t*
   double* stats = (double*)ws;                               // [S*L][chunks][4]
   double* rowmax = stats + (size_t)S * L * chunks * 4;       // [S][4]
   double* rowsum = rowmax + (size_t)S * 4;                   // [S][rchunks][4]
+  int group = 1;
+  while (group < chunks) group *= 2;                         // chunks <= 64
   hipLaunchKernelGGL((verify_stats_kernel<DT>), dim3(chunks, S * L), dim3(VT), 0, st, zt, zd, V, clen, chunks, stats);
-  hipLaunchKernelGGL((verify_accept_kernel<DT>), dim3(S), dim3(64 * AW), 0, st, zt, zd, tok, u_acc, L, V, chunks, (const double*)stats, n_acc,
-                     alpha, rowmax);
+  hipLaunchKernelGGL((verify_accept_kernel<DT>), dim3(S), dim3(64 * AW), 0, st, zt, zd, tok, u_acc, L, V, chunks, group, (const double*)stats,
+                     n_acc, alpha, rowmax);
   hipLaunchKernelGGL((verify_rowpass64_kernel<DT>), dim3(rchunks, S), dim3(VT), 0, st, zt, zd, L, V, rlen, rchunks, (const int32_t*)n_acc,
                      (const double*)rowmax, rowsum);
   hipLaunchKernelGGL((verify_sample_kernel<DT>), dim3(S), dim3(1024), 0, st, zt, zd, L, V, rlen, rchunks, (const int32_t*)n_acc,

@@ -69,6 +69,50 @@ def test_verify_matches_oracle_small(dtype, V):
     _check(d, dtype, n_acc, corr, alpha)
 
 
+@pytest.mark.parametrize("S,L,V,dtype", [(1, 64, 32000, I.BF16), (1, 25, 2048 * 40 - 8, I.BF16), (40, 60, 2048, I.BF16), (3, 63, 9 * 1024 + 4, I.FP32),
+                                         (64, 1, 32768 - 8, I.BF16), (64, 1, 65536 - 8, I.FP16), (128, 1, 4096, I.BF16), (300, 2, 264, I.FP32)],
+                         ids=["sixteen-chunks", "forty-chunks", "one-chunk", "ragged-chunks", "draw-from-1024", "draw-from-2048", "draw-from-256", "short-chunk"])
+def test_verify_positions_and_chunks(S, L, V, dtype):
+    """The acceptance kernel's groups of lanes (1 to 64 chunks a row, up to 64 positions, several turns of a wave) and the words a
+    thread of the residual passes owns (1, 2, 8)."""
+    d = I.make_verify_batch(S, L, V, dtype, seed=S + 7 * L + V, disagreement=0.3 if L > 8 else 0.9)
+    d["u_acc"][::2, :-1] *= 0.05                           # half of the sequences accept most positions
+    d["u_acc"][:, -1] = 0.9                                # and many of them draw a correction at the last
+    n, c, a = _run(d, dtype)
+    _check(d, dtype, n, c, a)
+
+
+def test_verify_time_does_not_grow_with_the_positions():
+    """The same logits as 16 sequences of 64 positions of 1024 words and of 8 positions of 8192 words: with a wave per position the
+    former took about twice the time, now about the same.  A ratio of two medians of one process."""
+    import torch
+    import paper_2605_02218_amd as C
+    z = torch.randn(2, 1 << 20, device="cuda", generator=torch.Generator(device="cuda").manual_seed(0)).bfloat16()
+    took = []
+    for L in (8, 64):
+        V = (1 << 16) // L
+        zt, zd = z.view(2, 16, L, V)
+        p = C.VerifyParams(n_seq=16, n_draft=L, vocab=V, dtype=C.BF16)
+        args = (torch.zeros(16, L, dtype=torch.int32, device="cuda"), torch.zeros(16, L, device="cuda"), torch.zeros(16, device="cuda"))
+        ws = torch.empty(C.verify_workspace_size(p) + 256, dtype=torch.uint8, device="cuda")
+        C.verify(p, zt, zd, *args, workspace=ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()                     # replayed: the launches from Python would hide the kernels
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                C.verify(p, zt, zd, *args, workspace=ws)
+        times = []
+        for _ in range(15):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        took.append(sorted(times)[7])
+    assert took[1] < 1.4 * took[0], took
+
+
 @pytest.mark.parametrize("S,L", [(1, 1), (1, 8), (37, 3), (300, 1)])
 def test_verify_batch_shapes(S, L):
     """One row (64 chunks of the row), many sequences (one chunk per row), odd counts."""
