@@ -634,11 +634,10 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
     return launch_cfg<TA, TB, EPI_STORE_F64, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;
-  if (g.epilogue == EPI_ROWNORM2) {
-    if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value) {
-      if (g.batch == 1 && g.batch_inner == 1 && rownorm_small(g.M, g.N, g.K)) return launch_small<TA, TB, EPI_ROWNORM2>(g, stream);
-    }
-    return launch_cfg<TA, TB, EPI_ROWNORM2, false, 2, 2>(g, stream);
+  if constexpr (std::is_same<TA, float>::value && std::is_same<TB, float>::value) {
+    // one product of stored rows and weights: the only form whose number of partials gemm64_tiles_n states
+    if (g.epilogue == EPI_ROWNORM2 && g.batch == 1 && g.batch_inner == 1)
+      return rownorm_small(g.M, g.N, g.K) ? launch_small<TA, TB, EPI_ROWNORM2>(g, stream) : launch_cfg<TA, TB, EPI_ROWNORM2, false, 2, 2>(g, stream);
   }
   return hipErrorInvalidValue;
 }
