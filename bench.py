@@ -134,15 +134,20 @@ def stage_times(C, p, dev, ws, steps):
     return out, probe
 
 
-def gram_flops(B, M, d, tile):
-    """Flops the Gram kernel executes: square tiles on and below the diagonal only (the rest is mirrored)."""
-    t = (M + tile - 1) // tile
-    return 2.0 * B * (t * (t + 1) // 2) * tile * tile * d
+def gram_flops(B, M, d):
+    """Flops of the Gram matrix whatever tiles it is computed in: d products and sums per pair on and below the diagonal (the
+    rest is mirrored)."""
+    return 1.0 * B * M * (M + 1) * d
+
+
+def tiles(m, n, t, batch=1):
+    """Square tiles of edge t that cover a batch of m x n products."""
+    return -(-m // t) * -(-n // t) * batch
 
 
 def contraction_fractions(w, modes, stages):
     """Fraction of the MFMA peak of the stages that are contractions, from the stage times of the same run: executed
-    flops (the three bf16 planes of the folded query matrix counted three times, Gram tiles on and below the diagonal
+    flops (the three bf16 planes of the folded query matrix counted three times, Gram pairs on and below the diagonal
     only) over the stage's time, which also holds that stage's small non-MFMA kernels."""
     import covspec_inputs as I
     B, N, d, T = w.batch, w.n_tokens, w.d_model, w.n_query
@@ -153,9 +158,9 @@ def contraction_fractions(w, modes, stages):
     work = {"token_projection": 2.0 * B * N * d * d,
             "query_side (e(q), folded query matrix in 3 planes)": 2.0 * B * T * d * d * (1 + planes),
             "relevance (token x folded query products in 3 planes)": 2.0 * B * N * d * T * planes,
-            "gram (tiles on and below the diagonal)": gram_flops(B, w.preselect_m, d, 128)}
+            "gram (pairs on and below the diagonal)": gram_flops(B, w.preselect_m, d)}
     key = {"token_projection": "token_projection", "query_side (e(q), folded query matrix in 3 planes)": "query_side",
-           "relevance (token x folded query products in 3 planes)": "relevance", "gram (tiles on and below the diagonal)": "gram"}
+           "relevance (token x folded query products in 3 planes)": "relevance", "gram (pairs on and below the diagonal)": "gram"}
     return {k: round(v / (stages[key[k]] * 1e-3) / peak, 4) for k, v in work.items() if stages[key[k]] > 0}
 
 
@@ -172,24 +177,32 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
     M, k = w.preselect_m, w.keep_k
     e = 2 if w.dtype == I.BF16 else 4
     bf = e == 2
+    # which kernel takes a product: the library's dispatch rules (gemm.hip, gemm64.hip) at these sizes
+    big = tiles(B * N, d, 256) >= 512 and d % 64 == 0 and d >= 128
+    proj = "gemm_nt_ring_kernel" if bf and big else "gemm_dma_kernel" if bf else "gemm64_small_kernel" if tiles(B * N, d, 64) <= 256 and d % 64 == 0 else "gemm64_kernel"
+    proj += "<rownorm2>" if p_modes[0] == 0 else "<store>"
+    energy = p_modes[1] == 0
+    m32 = -(-M // 32)
+    if bf and energy:
+        gram = "gemm_gram_small_kernel" if d % 64 == 0 and d >= 256 and B * m32 * (m32 + 1) // 2 <= 512 else "gemm_dma_kernel"
+    else:
+        gram = "gemm64_small_kernel" if not bf and d % 64 == 0 and tiles(M, M, 64, B) <= 256 else "gemm64_kernel"
     # name -> (kernel, bound, peak, unit, algorithmic work per launch, launches per step, ms per launch)
     cand = {
-        "token_projection": ("gemm_nt_ring_kernel<rownorm2>" if (bf and p_modes[0] == 0) else
-                             "gemm_nt_ring_kernel<store>" if bf else "gemm64_kernel<f32>",
-                             "mfma", PEAK["mfma_bf16_TFLOPs"] if bf else PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
+        "token_projection": (proj, "mfma", PEAK["mfma_bf16_TFLOPs"] if bf else PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
                              2.0 * B * N * d * d / 1e12, 1, stages["token_projection"]),
         "activity": ("activity_kernel", "hbm", PEAK["hbm_GBps"], "GB/s", (K + 1) * B * N * d * e / 1e9, 1,
                      stages["activity"]),
         "gather": ("gather_rows_kernel", "hbm", PEAK["hbm_GBps"], "GB/s", 2.0 * B * k * d * e / 1e9, 1,
                    stages["gather"]),
-        # the Gram matrix is symmetric: only the tiles on and below the diagonal are computed, and only those are counted
-        "gram": ("gemm_dma_kernel (tiles on and below the diagonal)" if (bf and p_modes[1] == 0) else "gemm64_kernel<gather> (tiles on and below the diagonal)",
-                 "mfma", PEAK["mfma_bf16_TFLOPs"] if (bf and p_modes[1] == 0) else PEAK["mfma_fp64_TFLOPs"],
-                 "TFLOP/s", gram_flops(B, M, d, 128 if (bf and p_modes[1] == 0) else 64) / 1e12, 1, stages["gram"]),
+        # the Gram matrix is symmetric: only the pairs on and below the diagonal are counted
+        "gram": (gram, "mfma", PEAK["mfma_bf16_TFLOPs"] if bf and energy else PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
+                 gram_flops(B, M, d) / 1e12, 1, stages["gram"]),
     }
     n_probe, pr, pc, pk = C.probe_launches(p)
     if n_probe > 0 and probe_ms > 0:
-        cand["lowrank_product"] = ("gemm64_dma_kernel", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
+        product = "gemm64_small_kernel" if tiles(pr, pc, 32, B) <= 384 and pk % 64 == 0 else "gemm64_dma_kernel"
+        cand["lowrank_product"] = (product, "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
                                    2.0 * B * pr * pc * pk / 1e12, n_probe, probe_ms)
     elif p_modes[1] == 1:
         cand["lowrank"] = ("greedy_kernel", "alu", PEAK["valu_fp64_TFLOPs"], "TFLOP/s", 1.0 * B * M * k * k / 1e12, 1,
@@ -235,7 +248,7 @@ def verify_bench(a):
 
     A step is one covspec_verify call: 64 sequences x 8 drafted positions x 151,936 words, bf16 logits resident in
     HBM.  Algorithmic bytes per call = both logit tensors read once (2 S L V e) plus the small per-position
-    inputs and outputs; `achieved` is that figure over the WHOLE call's time (five kernels), so it understates
+    inputs and outputs; `achieved` is that figure over the WHOLE call's time (four kernels), so it understates
     the streaming kernel's own rate.
     """
     import numpy as np

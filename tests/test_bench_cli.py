@@ -36,3 +36,27 @@ def test_roofline_traffic_is_read_from_the_tracked_counter_summaries():
     assert got == nums[1] * 1024 * 2.0 + nums[2] * 1024 * 1.0        # the factors of the summary's calibration line
     assert bench.counter_traffic("reduce5", ["a_kernel_that_does_not_exist"]) is None
     assert bench.counter_traffic("vocab", ["draft_scan_kernel", "draft_merge_kernel"]) > 150e6
+
+
+def test_gram_work_does_not_depend_on_the_tiles():
+    """One image's Gram matrix runs on 32 x 32 tiles, a batch's on 128 x 128 ones: the same work per image is counted."""
+    import bench
+    assert bench.gram_flops(1, 288, 4096) == 288 * 289 * 4096
+    assert bench.gram_flops(64, 288, 4096) == 64 * bench.gram_flops(1, 288, 4096)
+
+
+def test_roofline_names_the_kernel_that_runs():
+    """The kernels of the Gram matrix follow the library's rule: few tiles, many tiles, fp64 products."""
+    import bench
+    import covspec_inputs as I
+    import paper_2605_02218_amd as C
+
+    class Probe:
+        probe_launches = staticmethod(lambda p: (0, 0, 0, 0))
+    stages = {s: 0.0 for s in C.STAGES}
+    stages["gram"] = 1.0
+    for kw, modes, kernel in ((dict(batch=1, dtype=I.BF16), (0, 0), "gemm_gram_small_kernel"), (dict(batch=64, dtype=I.BF16), (0, 0), "gemm_dma_kernel"),
+                              (dict(batch=1, dtype=I.FP32), (0, 0), "gemm64_small_kernel"), (dict(batch=1, dtype=I.BF16), (1, 1), "gemm64_kernel")):
+        w = I.small_workload(n_tokens=576, d_model=4096, n_query=32, n_heads=32, keep_k=144, preselect_m=288, rank_r=72, n_act_layers=4, **kw)
+        got = bench.roofline_for(w, None, modes, dict(stages, activity=1e-9, gather=1e-9, token_projection=1e-9, lowrank=1e-9), 0.0, Probe)
+        assert got["kernel"] == kernel
