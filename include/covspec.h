@@ -185,7 +185,9 @@ int covspec_reduce_staged(const covspec_params* p, const void* X, const void* hi
 /*
  * Ragged batches: images of different token and keyword counts in one call (not in the paper, whose
  * Sec. III-A treats one image; dynamic-resolution serving batches such images).  Image b of the batch
- * gives exactly the result of covspec_reduce on that image alone, with n_tokens[b] and n_query[b] in
+ * gives the result of covspec_reduce on that image alone (kernels are chosen by the size of a run, and
+ * some add up a sum in another order: tokens whose values are closer than that rounding, 1e-6 of the
+ * scores' range, may change places at a cut), with n_tokens[b] and n_query[b] in
  * place of the template's n_tokens and n_query, k / M / r resolved for that image (from keep_ratio
  * unless the template fixes them), and, for COVSPEC_LR_RANDOM, the draw of image b.
  * `p` is the template: batch, n_tokens and n_query are ignored.  `r` and its arrays are HOST memory.

@@ -11,10 +11,12 @@
 // K quads with data) goes another way to the same result: the logits above the K-th largest thread maximum are ranked by
 // the workgroup and the lowest words among those equal to it fill up, or, where more than 256 are above, K rounds of block-wide
 // argmax.
-// Bound by the latency of a workgroup's dozen phases, so by how many of them a compute unit holds: with the logits widened to
-// fp32 and the fallback's packed keys formed ahead of its loop the kernel took 87 registers (5 waves per SIMD) and 49 us for
-// 512 rows of 151936 bf16 words; with the logits kept as loaded, one reference per thread instead of a running one and the
-// few candidate threads' logits looked through in LDS it takes 64 registers and 33 us (4.7 TB/s).
+// Bound by its vector instructions, 12 per logit, which keep the VALUs busy in two thirds or more of its cycles now that eight
+// waves per SIMD cover the latencies of a workgroup's dozen phases: with the logits widened to fp32 and the overflowing
+// chunks' packed keys formed ahead of their loop the kernel took 87 registers (5 waves per SIMD) and 49 us for 512 rows of 151936
+// bf16 words; with the logits kept as loaded, one reference per thread instead of a running one and the few candidate
+// threads' logits looked through in LDS it takes 64 registers, none spilled, and 33.6 us (4.6 TB/s; six inputs in turn, 0.93 GB.
+// The same input again and again, part of which the 256 MB cache keeps: 31.8).
 // Merge kernel, one wave per row: combines the chunks' statistics in fp64, merges their candidate lists,
 // evaluates the margin and writes gate and candidates.
 #include "common.h"

@@ -1,17 +1,21 @@
-// fp64 MFMA GEMM:  C[M,N] (fp64) = A[M,K] * B[N,K]^T (or A * B with B stored [K][N]) with
-// A, B stored as fp64, fp32 or bf16 and every product and sum taken in fp64.
+// fp64 MFMA GEMM:  C[M,N] (fp64) = A[M,K] * B[N,K]^T with A, B stored as fp64, fp32 or bf16 and every product and sum
+// taken in fp64 on v_mfma_f64_16x16x4_f64.
 //
-// Two users.  (1) The fp32-input path: fp32 inputs carry 24-bit mantissas, so an
-// fp32-accumulated contraction cannot deliver cosine scores to 1e-5 relative once the cosine
-// is small against its natural scale; that workload is small, so its whole chain (embeddings,
-// folded query matrix, inner products, norms, Gram matrix) runs on v_mfma_f64_16x16x4_f64 and
-// the fp32 storage is the only rounding left.  (2) The low-rank stage, whose block iteration
-// on the fp64 Gram matrix is a sequence of fp64 products.
+// Two users.  (1) The fp32-input path: fp32 inputs carry 24-bit mantissas, so an fp32-accumulated contraction cannot deliver
+// cosine scores to 1e-5 relative once the cosine is small against its natural scale; that workload is small, so its whole
+// chain (embeddings, folded query matrix, inner products, norms, Gram matrix) runs here and the fp32 storage is the only
+// rounding left; so does the Gram matrix of the greedy picks from bf16 rows.  (2) The low-rank stage, whose block iteration on
+// the fp64 Gram matrix is a sequence of fp64 products.
 //
-// Shape: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in
-// each direction (64x64 for <2,2>), k-tile 16.  Operands are converted to
-// fp64 on their way into LDS; the loads of k-tile t+1 are issued before the MFMAs of tile t and
-// parked in registers, LDS is double buffered, one barrier per k-tile.
+// Four kernels:
+//   gemm64_kernel        any of the storage types, row lists, any K and alignment: 64 x 64 tiles, operands converted to fp64 on
+//                        their way through registers into LDS.
+//   gemm64_dma_kernel    fp64 x fp64 of many tiles (the block iteration on large or many images): direct-to-LDS loads.
+//   gemm64_small_kernel  few tiles, fp64 or fp32, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
+//   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
+// gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
+// for <2,2>), k-tile 16; the loads of k-tile t+1 are issued before the MFMAs of tile t and parked in registers, LDS is double
+// buffered, one barrier per k-tile.
 // MFMA layouts: operand lane l holds (row|col = l%16, k = l/16); result lane l, register v
 // holds (row 4v + l/16, col l%16).
 #include <type_traits>
@@ -25,12 +29,17 @@ namespace {
 
 constexpr int TK = 16, PITCH = TK + 1;
 // 32 x 32 tiles up to which gemm64_small_kernel is taken: beyond it the device is no longer short of workgroups and the
-// doubled operand traffic decides (192 x 320 x 320, 60 tiles: 10.6 against 20.2 us; 960 tiles would read 630 MB).
+// doubled operand traffic decides.  us, gemm64_dma_kernel / here: 240 tiles of K = 320 15.3 / 8.6, 320 of K = 640 26 / 22, 360 of
+// K = 320 15.5 / 13.6, 384 of K = 192 10.9 / 12.4; 432 of K = 1152 44 / 38, 480 of K = 640 27 / 23, 640 of K = 640 27 / 31, 720 of
+// K = 320 15.9 / 18.8, 864 of K = 1152 45 / 69: the curves cross between 380 and 600 tiles, later for the longer k.
 constexpr long kSmallTiles = 384;
-// The same for operands that are not both fp64 (the alternative is the register-staged kernel, one wave per SIMD), in 64 x 64
-// tiles: up to one workgroup of that kernel per compute unit.
+// The same for operands that are not both fp64, in 64 x 64 tiles: up to one workgroup per compute unit of the alternative, the
+// register-staged kernel with one wave per SIMD.  us, gemm64_kernel / here: row norms of 144 tiles (576 x 1024 x 1024) 136 / 34, 256
+// (2000 x 512 x 512) 64 / 30, 288 (1100 x 1024 x 1024) 148 / 52, 864 of K = 256 57 / 57, 1008 59 / 68: the small tiles would still
+// win up to some 800; the line is where the sums' order was drawn.
 constexpr long kSmallTiles64 = 256;
-// 64 x 64 tiles up to which k is split over two groups of waves: one workgroup per compute unit.
+// 64 x 64 tiles up to which k is split over two groups of waves: one workgroup of eight waves per compute unit, where one of
+// four leaves each SIMD a single wave (75 -> 45 us, see the kernel); with more tiles than that two workgroups share a unit.
 constexpr long kFewTiles = 256;
 
 __device__ __forceinline__ double as_f64(double v) { return v; }

@@ -26,7 +26,9 @@ namespace {
 constexpr int NB = 64;        // panel width of Cholesky / substitution
 constexpr int NBP = NB + 1;   // LDS pitch
 // Relative residual accepted for the dominant subspace, row by row (split_finish_kernel).  It perturbs an energy by at
-// most 1e-9 / (relative gap at r) relative; converged blocks sit at 1e-11..1e-13, unconverged ones orders above.
+// most 1e-9 / (relative gap at r) relative.  A block that took the steps planned for it sits at 2e-10 (kPlanTol) or below,
+// one that took all of the first pass at 1e-11..1e-13, unconverged ones orders above.  (Energies as returned, in fp32, are
+// 2.6e-8 off their 64-bit values with either, the rounding to fp32.)
 constexpr double kRitzTol = 1e-9;
 // see the end of chol_kernel
 constexpr double kPivotNear = 0.25;   // smallest scaled pivot above this: rows nearly orthogonal, blocks of three steps
@@ -157,8 +159,8 @@ __device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* 
 // produce NaNs (the residual check afterwards decides whether the result is usable).
 // Bound by the chain of panels (and, from order 384 on, by one compute unit's MFMA rate in the trailing part).  One image of
 // order 192 / eight of 384 / sixty-four of 256, us: 168 / 448 / 257 with the block factored column by column, its inverse
-// formed by the workgroup, the next diagonal block updated by the wave that factors it and spilled registers; 76 / 220 / 115
-// without; 69 / 172 / 107 with the tiles in fragment order.
+// formed by the workgroup and the next diagonal block updated by the wave that factors it; 76 / 220 / 115 without; 69 / 172 / 107
+// with the tiles in fragment order.  (256 registers; five are spilled, read back once a panel, outside the loops.)
 // Dynamic LDS: 2 * 64 * 65 + 64 + P doubles.
 __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, int* skip_until, int* last_orth, int step,
                                                    int last_free_step, int next_weight, int r, int n_sq, int* hold, int* slow) {
@@ -372,7 +374,8 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
 // Written back to memory and read again block by block, with the loads of a block in front of its MFMAs, the solve took,
 // us: 192 x 320 29, 192 x 1280 batch 4 33, 384 x 1152 batch 8 91, 256 x 640 batch 64 145; in registers 26, 30, 83, 127; with
 // the factor in fragment order (row-major, a load touched 64 cache lines) 15, 19, 45, 76.
-// Taken for up to six blocks (the registers of a wave hold no more); larger factors go through trsm_any_kernel.
+// Instantiated for up to six blocks (rank 320); larger factors go through trsm_any_kernel.  us, trsm_any_kernel / here: 192 x 320
+// batch 8 37 / 17, 256 x 640 54 / 23, 384 x 1152 99 / 45; seven blocks measured 124 / 57 and eight 151 / 72 (448 x 704, 512 x 832).
 template <int N>
 struct TrsmAt {          // group N of the A stream: block row bi takes 4 bi groups of L and 4 of its inverted diagonal block
   static constexpr int row() { int bi = 0; while (2 * (bi + 1) * (bi + 2) <= N) ++bi; return bi; }
