@@ -151,7 +151,7 @@ __global__ __launch_bounds__(DTH, DT == DT_F32 ? 6 : 8) void draft_scan_kernel(c
   const float tau = sh_tau;
   // the few threads that hold a logit of tau or more (K quads and a few) put all of theirs into LDS, where the whole
   // workgroup looks through them: 32 compare-and-branch steps of every wave cost more than that
-  if (own >= tau) {
+  if (nv > 0 && own >= tau) {       // a thread without words has -inf, which is tau where few quads have data
     const int pos = atomicAdd(&sh_cnt, 1);
     if (pos < POOL) {
       pool_id[pos] = tid;

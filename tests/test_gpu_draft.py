@@ -148,6 +148,36 @@ def test_draft_gate_rows_of_equal_logits_stay_within_reach_of_others():
     assert took[1] < 8 * took[0], took
 
 
+def test_draft_gate_of_a_few_words_takes_no_longer_than_of_many():
+    """Chunks with fewer words than threads (small vocabularies, a short last chunk) fit the threshold list; threads without words
+    once counted as holders of candidates and sent them the long way, 57 us against 17 here.  A ratio of two medians, replayed
+    from a graph because the launches from Python would hide the kernels."""
+    import torch
+    import paper_2605_02218_amd as C
+    took = []
+    for V in (2688, 40):
+        p = C.DraftParams(n_seq=64, n_draft=8, vocab=V, dtype=C.BF16, fanout0=16, rho=0.7, gamma=0.5)
+        z = torch.randn(64, 8, V, generator=torch.Generator(device="cuda").manual_seed(0), device="cuda").bfloat16()
+        tok = torch.zeros(64, 8, dtype=torch.int32, device="cuda")
+        ws = torch.empty(C.draft_workspace_size(p) + 256, dtype=torch.uint8, device="cuda")
+        C.draft_gate(p, z, tok, workspace=ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                C.draft_gate(p, z, tok, workspace=ws)
+        times = []
+        for _ in range(15):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        took.append(sorted(times)[7])
+    assert took[1] < 1.6 * took[0], took
+
+
 def test_draft_gate_full_vocabulary_batch():
     """The benchmark's shape (64 x 8 positions over 151,936 words, bf16); every fourth sequence against the oracle."""
     dtype = I.BF16
