@@ -17,8 +17,6 @@ namespace {
 constexpr int kMaxTokens = 16384;
 constexpr int kMaxPreselect = 4096;
 constexpr int kMaxActLayers = 8;
-constexpr int kSubspaceIters = 12;       // steps before the first residual check (the workloads pass it with a factor >= 10 to spare)
-constexpr int kSubspaceMoreIters = 4;    // further steps for the images that fail it, before the full solve
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -372,7 +370,7 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
     int* ok = nullptr;
     if (q.P > 0 || split_direct(q.nP)) {
       ok = at<int>(ws, q.ok);
-      HIPCHK(launch_subspace_eigen(A, q.B, q.M, q.nP, q.r, q.P, kSubspaceIters, kSubspaceMoreIters, at<void>(ws, q.sub), ok, c, img_status,
+      HIPCHK(launch_subspace_eigen(A, q.B, q.M, q.nP, q.r, q.P, at<void>(ws, q.sub), ok, c, img_status,
                                    marks.ev ? marks.ev[COVSPEC_PROBE_BEGIN] : nullptr, marks.ev ? marks.ev[COVSPEC_PROBE_END] : nullptr, st));
       probed = q.P > 0;
     }
@@ -636,7 +634,7 @@ int covspec_probe_launches(const covspec_params* p, int32_t* rows, int32_t* cols
   if (rows) *rows = pl.P;
   if (cols) *cols = pl.nP;
   if (inner) *inner = pl.nP;
-  return subspace_product_launches(kSubspaceIters);
+  return subspace_product_launches();
 }
 
 static int verify_check(const covspec_verify_params* p) {
@@ -841,7 +839,7 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
     int* ok = nullptr;
     if (P > 0 || split_direct(q.nP)) {
       ok = at<int>(ws, q.ok);
-      HIPCHK(launch_subspace_eigen(A, q.B, nC, q.nP, q.r, P, kSubspaceIters, kSubspaceMoreIters, at<void>(ws, q.sub), ok, c, nullptr, nullptr,
+      HIPCHK(launch_subspace_eigen(A, q.B, nC, q.nP, q.r, P, at<void>(ws, q.sub), ok, c, nullptr, nullptr,
                                    nullptr, st));
     }
     HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, st));

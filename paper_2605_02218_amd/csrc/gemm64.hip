@@ -225,6 +225,14 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 // 384 x 1152 x 1152, batch 8 303 -> 190; 256 x 640 x 640, batch 64 260 -> 220 (61 TFLOP/s; a loop of nothing but these
 // MFMAs reaches 67.6).
 // Requires K % 16 == 0, even pitches, 16-byte aligned bases.  Rows beyond M / N are clamped when loading.
+// A Chebyshev step (GemmArgs::cheb) is scale * (A B + start): the accumulators begin with the terms that are not the product,
+// whose loads are over before the first operands have landed (read behind the product they cost 30 of 260 us, see below).
+__device__ __forceinline__ double cheb_scale(const GemmArgs& g, double t) { return t == 0.0 ? 1.0 : g.cheb_step == 0 ? t : 2.0 * t; }
+__device__ __forceinline__ double cheb_start(const GemmArgs& g, const double* A, const double* C, double rt, int r, int c) {   // rt = 1 / t
+  const double a = A[(long)r * g.lda + c];
+  return -rt * (g.cheb_step == 0 ? a : fma(0.5, C[(long)r * g.ldc + c], a));
+}
+
 template <int KS>
 __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr int NST = 4, STAGE = 2 * 64 * 128;      // bytes: A tile then B tile
@@ -238,8 +246,9 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   if (g.lower_only && tn > tm) return;                    // tile above the diagonal
   if (g.frag && tn < tm) return;                          // see the store
   const int row0 = tm * 64, col0 = tn * 64;
-  const double* __restrict__ A = (const double*)g.A + (long)b * g.strideA;
-  const double* __restrict__ B = (const double*)g.B + (long)b * g.strideB;
+  const bool moved = g.sel && g.sel[b];
+  const double* A = (const double*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
+  const double* B = (const double*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
   const int nk = g.K >> 4, nk0 = (nk + KS - 1) / KS, kt0 = grp * nk0;
   const int mine = nk - kt0 < nk0 ? (nk - kt0 > 0 ? nk - kt0 : 0) : nk0;      // k-tiles of this group
 
@@ -268,11 +277,20 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
                                        (__attribute__((address_space(3))) void*)(sb + j * 1024), 16, 0, 0);
     }
   };
+  double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
+  const double t = g.cheb ? g.cheb[(long)b * g.cheb_stride] : 0.0, scale = cheb_scale(g, t), rt = 1.0 / t;
   f64x4_t acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < 2; ++j) {
+      acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+      if (t != 0.0 && grp == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          acc[i][j][v] = cheb_start(g, A, C, rt, min(row0 + wm * 32 + i * 16 + 4 * v + kq, g.M - 1), min(col0 + wn * 32 + j * 16 + i16, g.N - 1));
+      }
+    }
   // fragment of row R, half h: piece kq + 4h, i.e. k = 2 (kq + 4h) + {0, 1}; R % 8 == i16 % 8 for every fragment row
   int offA[2], offB[2];
 #pragma unroll
@@ -340,7 +358,6 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
         else acc[0][j][v] = acc[0][j][v] + o;
       }
   }
-  double* C = (double*)g.C + (long)b * g.strideC;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (KS == 2 && i != grp) continue;
@@ -357,7 +374,7 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
       for (int v = 0; v < 4; ++v) {
         const int r = row0 + wm * 32 + i * 16 + 4 * v + kq, c = col0 + wn * 32 + j * 16 + i16;
         if (r < g.M && c < g.N) {
-          C[(long)r * g.ldc + c] = acc[i][j][v];
+          C[(long)r * g.ldc + c] = scale * acc[i][j][v];
           if (g.mirror && tn != tm) C[(long)c * g.ldc + r] = acc[i][j][v];
         }
       }
@@ -390,6 +407,9 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
   if (g.lower_only && tn > tm) return;
   if (g.frag && tn < tm) return;
   const int row0 = tm * 32, col0 = tn * 32, kn = g.K >> 2;
+  const bool moved = g.sel && g.sel[b];
+  const TA* Ab = (const TA*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
+  const TB* Bb = (const TB*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
   const TA* ar[2];
   const TB* br[2];
 #pragma unroll
@@ -397,15 +417,30 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     long ra = min(row0 + 16 * x + i16, g.M - 1), rb = min(col0 + 16 * x + i16, g.N - 1);
     if (g.gatherA) ra = g.gatherA[(long)b * g.gstrideA + ra];
     if (g.gatherB) rb = g.gatherB[(long)b * g.gstrideB + rb];
-    ar[x] = (const TA*)g.A + (long)b * g.strideA + ra * g.lda + w * kn + 4 * kq;
-    br[x] = (const TB*)g.B + (long)b * g.strideB + rb * g.ldb + w * kn + 4 * kq;
+    ar[x] = Ab + ra * g.lda + w * kn + 4 * kq;
+    br[x] = Bb + rb * g.ldb + w * kn + 4 * kq;
   }
   constexpr int DEPTH = 3;
+  double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
   f64x4_t acc[2][2], fa[DEPTH][2], fb[DEPTH][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 2; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  double scale = 1.0;
+  double start[4] = {0.0, 0.0, 0.0, 0.0};                 // of the elements this thread stores
+  if constexpr (std::is_same<TA, double>::value) {
+    if (g.cheb) {
+      const double t = g.cheb[(long)b * g.cheb_stride];
+      scale = cheb_scale(g, t);
+      if (t != 0.0) {
+        const double rt = 1.0 / t;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          start[q] = cheb_start(g, Ab, C, rt, min(row0 + ((tid + 256 * q) >> 5), g.M - 1), min(col0 + ((tid + 256 * q) & 31), g.N - 1));
+      }
+    }
+  }
   const int nc = kn >> 4;
   auto load = [&](int s, int c) {
     if (c < nc) {
@@ -445,7 +480,6 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     const double* q = part + i * 33 + j;
     return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
   };
-  double* C = (double*)g.C + (long)b * g.strideC;
   if (EPI == EPI_ROWNORM2) {                              // eight lanes per row, four columns each; columns beyond N count as zero
     const int i = tid >> 3, j0 = (tid & 7) * 4;
     double s = 0.0;
@@ -465,9 +499,10 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     frag_store(C + ((long)(col0 / 16 + sr) * (g.N >> 4) + row0 / 16 + sc) * kFragTile, lane, v);
     return;
   }
-  for (int e = tid; e < 32 * 32; e += 256) {
-    const int i = e >> 5, j = e & 31;
-    if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = sum(i, j);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = tid + 256 * q, i = e >> 5, j = e & 31;
+    if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = scale * (sum(i, j) + start[q]);
     if (g.mirror && tn != tm && row0 + j < g.M && col0 + i < g.N) C[(long)(col0 + i) * g.ldc + row0 + j] = sum(j, i);
   }
 }
@@ -487,7 +522,8 @@ __global__ __launch_bounds__(256) void gemm64_sym_kernel(GemmArgs g, int tiles_m
   if (g.skip && g.skip[b] > g.skip_if) return;
   const int row0 = tm * 32, col0 = tn * 32;
   const int groups = g.K >> 6, total = DUAL ? 2 * groups : groups;      // steps of 16 k per wave
-  const long abase = (long)b * g.strideA + row0 + i16, bbase = (long)b * g.strideB + col0 + i16;
+  const bool moved = g.sel && g.sel[b];
+  const long abase = (long)b * g.strideA + row0 + i16, bbase = (long)b * g.strideB + col0 + i16, bmoved = moved ? g.selB : 0;
   f64x4_t acc[2][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
@@ -499,7 +535,7 @@ __global__ __launch_bounds__(256) void gemm64_sym_kernel(GemmArgs g, int tiles_m
   auto load = [&](int t, double (&a)[4][2], double (&bb)[4][2]) {
     const bool second = DUAL && t >= groups;
     const double* A = (const double*)(second ? g.A2 : g.A) + abase;
-    const double* B = (const double*)(second ? g.B2 : g.B) + bbase;
+    const double* B = second ? (const double*)g.B2 + bbase : (const double*)g.B + bbase + bmoved;
     const long k0 = (long)(second ? t - groups : t) * 64 + 16 * w + kq;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -557,7 +593,7 @@ __global__ __launch_bounds__(256) void gemm64_sym_kernel(GemmArgs g, int tiles_m
     const double v = sum(i0 + 8 * q, j);
     const long o = coff + (long)(row0 + i0 + 8 * q) * g.ldc + col0 + j;
     ((double*)g.C)[o] = v;
-    dot = fma(v, ((const double*)g.D)[o], dot);
+    dot = fma(v, ((const double*)g.D)[o + (moved ? g.selD : 0)], dot);
   }
   __syncthreads();
   part[i0 * 33 + j] = dot;
@@ -639,7 +675,7 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
   if (g.epilogue == EPI_STORE_F64) {
     if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, 2, 2>(g, stream);
     if (f64x2 && plain_f64(g)) return launch_plain_f64(g, stream);
-    if (g.frag) return hipErrorInvalidValue;
+    if (g.frag || g.sel || g.cheb) return hipErrorInvalidValue;
     return launch_cfg<TA, TB, EPI_STORE_F64, false, 2, 2>(g, stream);
   }
   if (gather) return hipErrorInvalidValue;

@@ -39,6 +39,13 @@ struct GemmArgs {
                                                // order (common.h), those on and below the diagonal; ldc unused
   const int* skip = nullptr;                   // per outer batch: the work is skipped while skip[b] > skip_if
   int skip_if = 1;
+  const int* sel = nullptr;                    // per outer batch: where non-zero, these many elements are added to the operands
+  long selA = 0, selB = 0, selC = 0, selD = 0;
+  // fp64 x fp64 only, M x K times K x K: one step of a Chebyshev recurrence instead of C = A B.  With t = *(cheb + b cheb_stride):
+  // step 0: C = t A B - A, later ones: C = 2 (t A B - A) - C; t = 0: C = A B.
+  const double* cheb = nullptr;
+  long cheb_stride = 0;
+  int cheb_step = 0;
   const void* A2 = nullptr;                    // launch_gemm64_rownorm_dual: second operands, laid out like A and B
   const void* B2 = nullptr;
   const void* D = nullptr;                     // launch_gemm64_store_dot: laid out like C
@@ -174,10 +181,10 @@ hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n,
 // On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second, 3 by the projector of G.
 int subspace_block(int n, int r);
 size_t subspace_workspace_bytes(int B, int n, int nP, int P);
-// probe_begin / probe_end (optional): recorded around the first of the subspace_product_launches(iters)
-// equal launches of the product Yt G (P x nP x nP per image).
-int subspace_product_launches(int iters);
-hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, int iters, int more_iters, void* ws, int* ok,
+// probe_begin / probe_end (optional): recorded around the first of the subspace_product_launches()
+// launches of the product Yt G (P x nP x nP per image).
+int subspace_product_launches();
+hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, void* ws, int* ok,
                                  float* c, int* img_status, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t stream);
 
 // ---------------------------------------------------------------- greedy.hip

@@ -8,14 +8,18 @@
 //     enters an eigenvalue squared.  The window is brought to tridiagonal form by Householder reflections with the
 //     matrix in the registers of one workgroup, and the two eigenvalues are cut out of it by Sturm counts, 128 trial
 //     points per pass and eigenvalue.  A matrix of order <= 128 is its own window, whatever the order of its rows.
-//   sign_kernel iterates X <- 1.5 s X - 0.5 s^3 X^3 from X = (H - mu I) / |H - mu I| (Newton-Schulz; s is the factor
-//     for which the image of [l, 1] has the largest lower end, l the known lower bound on |eigenvalues of X|: a step
+//   sign_kernel first lifts the cut: H is positive semidefinite and mu far below its norm, so X <- alpha X - beta X^2 with the
+//     largest alpha that keeps X in [0, 1] and its top above the image of mu multiplies mu, and the gap around it, by almost 4
+//     per product; it ends with mu in [0.1, 0.4] of the norm.  Then X <- 1.5 s X - 0.5 s^3 X^3 from the shifted X (Newton-Schulz;
+//     s is the factor for which the image of [l, 1] has the largest lower end, l the known lower bound on |eigenvalues of X|: a step
 //     then multiplies a small l by 2.6, against 1.5 without), two symmetric products per step on the fp64 MFMA, until
-//     X no longer changes.  12 to 21 steps for the spectra of the token matrices.
+//     X no longer changes.
 // Before: the P x P problem was diagonalised by block Jacobi (six sweeps of P/32 - 1 rounds of 32 dependent rotation
 // steps each).  An eigen-decomposition orders every pair of rows; the energies only ask which side of the cut a
 // direction is on, and the products that answer that are matrix-core work without a serial chain of rotations.
-// Jacobi against split + sign, us: one matrix of order 128 2727 -> 124 + 131, one of 192 1482 -> 124 + 197, four of 192
+// Without the lift (Newton-Schulz from the unlifted cut, mu / norm = 2e-5 to 3e-2) the iteration took 15 to 20 steps, so 10 to 11 and
+// 2 to 7 single products: one matrix of order 192 193 -> 160 us, one of 128 127 -> 104.
+// Jacobi against split + sign before that, us: one matrix of order 128 2727 -> 124 + 131, one of 192 1482 -> 124 + 197, four of 192
 // 1769 -> 124 + 200, eight of 384 3551 -> 124 + 259, sixty-four of 256 3894 -> 124 + 1061.
 //
 // Leading rows [0, a) of an ordered H that do not couple to the rows around and beyond the cut (kLeadFar) and whose
@@ -34,6 +38,7 @@ namespace {
 constexpr int SN = 128;              // order of the window
 constexpr int kMaxSignSteps = 40;    // 25 take the smallest admitted l to 1 / 2.6, a handful more to 1
 constexpr double kMinGap = 1e-10;    // smallest half gap at the cut, relative to the norm, that is iterated on
+constexpr double kLiftTo = 0.1;      // the cut is lifted until it is at least this part of the norm
 // Couplings |H_pq| / H_rr below which a leading row p is left out of the iteration: to rows beyond the cut (they go into
 // the residual as they are, in quadrature over the rows left out) and to the 32 rows before it (they meet the unwanted
 // directions only through these directions' tails).
@@ -45,7 +50,7 @@ struct SplitCtl {
   unsigned int ticket;                         // ctl[0] only: next (image, slot) to hand to a starting workgroup
   int state;                                   // 0: to be iterated, 1: left alone (no usable gap, or not asked for), 2: projector valid, 3: gave up
   int first;                                   // a: rows before it are wanted as they are
-  double mu, inv_norm, l0, theta;              // cut, 1 / norm, lower bound on |eigenvalues of X|, r-th eigenvalue
+  double mu, norm, half, theta;                // cut, bound on the eigenvalues, half gap at the cut, r-th eigenvalue
 };
 
 // Sums over the 16 lanes of a DPP row, the same in all of them; of X0..7 at once, so that the steps of one fill the waits of
@@ -302,19 +307,19 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
   if (bad > r - 32) bad = r - 32;
   const int a = !ordered || bad < 64 ? 0 : bad / 64 * 64;
   double nrm = 0.0;
-  for (int p = a + tid; p < P; p += 256) nrm = fmax(nrm, fabs(Hb[(long)p * P + p] - mu) + offb[p]);
+  for (int p = a + tid; p < P; p += 256) nrm = fmax(nrm, fabs(Hb[(long)p * P + p]) + offb[p]);
   nrm = wave_max(nrm);
   if (lane == 0) red[wv] = nrm;
   __syncthreads();
   nrm = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
   if (tid == 0) {
-    const double l0 = 0.45 * gap / nrm;            // a tenth off the half gap for what the window leaves out
+    const double half = 0.45 * gap;                // a tenth off the half gap for what the window leaves out
     cb->first = a;
     cb->mu = mu;
-    cb->inv_norm = 1.0 / nrm;
-    cb->l0 = l0;
+    cb->norm = nrm;
+    cb->half = half;
     cb->theta = lo[0] * big;
-    cb->state = l0 > kMinGap && nrm < 1e300 ? 0 : 1;
+    cb->state = half > kMinGap * nrm && mu > 0.0 && nrm < 1e300 ? 0 : 1;
   }
 }
 
@@ -390,18 +395,19 @@ __device__ __forceinline__ void tile_of(int t, int& i, int& j) {      // t-th ti
 // order 192: 259 and 292 us, sixty-four of order 256: 1.70 and 1.53 ms).  The iterates in fragment order instead of row-major
 // (64 cache lines per load): 366 -> 259, 292 -> 197 us, 1.53 -> 1.06 ms.
 // WIDE = false: a workgroup's tile is 32 x 32, its waves take a quarter of k each; WIDE = true: the tile is 64 x 64, a
-// wave takes a quadrant of it and all of k (a quarter of the workgroups: sixty-four images of order 256 took 3.7 ms on
-// small tiles, whose workgroups the device holds only a quarter of at a time, and 1.7 ms on wide ones).
+// wave takes a quadrant of it and all of k, or half of it with KS = 2 (a quarter of the workgroups: sixty-four images of order
+// 256 took 3.7 ms on small tiles, whose workgroups the device holds only a quarter of at a time, and 1.7 ms on wide ones).
 // Everything is kept symmetric to the bit (the elements above the diagonal are those below it): rounding that differs
 // between the two would be a skew perturbation, which the iteration magnifies by 1 / l0.
-template <bool WIDE>
-__global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
+template <bool WIDE, int KS>
+__global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : 3) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
                                                                  int W, SplitCtl* ctl, int* img_status, long long limit_ticks) {
+  static_assert(WIDE || KS == 1, "");
   constexpr int TT = WIDE ? 2 * ST : ST;             // tile of the workgroup
-  __shared__ double part[4 * ST * STP];
+  extern __shared__ double part[];                   // [4 KS][ST][STP], one tile of 32 x 32 per wave
   __shared__ int s_flag;
-  __shared__ double s_dev[4];
-  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
+  __shared__ double s_dev[4 * KS];
+  const int tid = threadIdx.x, wv = tid >> 6, grp = wv >> 2, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
   if (tid == 0) s_flag = (int)atomicAdd(&ctl[0].ticket, 1u);
   __syncthreads();
   const int ticket = s_flag;
@@ -413,8 +419,12 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
   const int ns = (P - a) / TT, ntiles = ns * (ns + 1) / 2;
   const int nact = ntiles < W ? ntiles : W;
   if (slot >= nact) return;
-  const double mu = cb->mu, inv = cb->inv_norm;
-  double l = cb->l0;
+  // cut and half gap as parts of the norm, and the number of lifting steps that follows from them
+  const double norm = cb->norm;
+  double m = cb->mu / norm, l = cb->half / norm;
+  const bool lift = m < kLiftTo;
+  const double mu = lift ? 0.0 : cb->mu, inv = 1.0 / (lift ? norm : fmax(norm - mu, mu));
+  if (!lift) l = cb->half * inv;
   const long pp = (long)P * P;
   const double* Hb = H + b * pp;
   double *X = X0 + b * pp, *Xn = X1 + b * pp, *Yb = Y + b * pp;
@@ -431,7 +441,7 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
       int ti, tj;
       tile_of(t, ti, tj);
       if (WIDE) {
-        const int qi = wv >> 1, qj = wv & 1;
+        const int qi = (wv >> 1) & 1, qj = wv & 1;
         fn(a + TT * ti + ST * qi, a + TT * tj + ST * qj, ti == tj && qj > qi);
       } else {
         fn(a + TT * ti, a + TT * tj, false);
@@ -440,18 +450,18 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
   };
   // fn(tile row, tile column), in units of 16, on the 16 x 16 tiles of a 32 x 32 tile, dealt to the waves that share it
   auto for_frags = [&](int r0, int c0, auto fn) {
-    for (int q = WIDE ? 0 : wv; q < 4; q += WIDE ? 1 : 4) fn((r0 >> 4) + (q >> 1), (c0 >> 4) + (q & 1));
+    for (int q = WIDE ? grp : wv; q < 4; q += WIDE ? KS : 4) fn((r0 >> 4) + (q >> 1), (c0 >> 4) + (q & 1));
   };
   // the 32 x 32 tiles of the product X Z in LDS, then fn(r0, c0, sum) with sum(i, j) an element of it
   auto product = [&](const double* Z, auto fn) {
     for_tiles([&](int r0, int c0, bool above) {
       double* mine = part + wv * (ST * STP);
-      const int kn = WIDE ? P - a : (P - a) >> 2;     // P - a is a multiple of 64
-      if (!above) tile_product<WIDE ? 2 : 3>(X, Z, P, WIDE ? a : a + wv * kn, kn, r0, c0, mine);
+      const int kn = WIDE ? (P - a) / KS : (P - a) >> 2;     // P - a is a multiple of 64
+      if (!above) tile_product<WIDE ? 2 : 3>(X, Z, P, a + (WIDE ? grp : wv) * kn, kn, r0, c0, mine);
       __syncthreads();
       auto sum = [&](int i, int j) {
-        const double* q = (WIDE ? mine : part) + i * STP + j;
-        return WIDE ? q[0] : (q[0] + q[ST * STP]) + (q[2 * ST * STP] + q[3 * ST * STP]);
+        const double* q = part + (WIDE ? (wv & 3) * (ST * STP) : 0) + i * STP + j;
+        return WIDE ? (KS == 2 ? q[0] + q[4 * ST * STP] : q[0]) : (q[0] + q[ST * STP]) + (q[2 * ST * STP] + q[3 * ST * STP]);
       };
       if (!above) fn(r0, c0, sum);
       __syncthreads();
@@ -481,6 +491,34 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
     });
   });
   meet();
+#pragma unroll 1
+  while (alive && m < kLiftTo) {
+    // y = alpha x - beta x^2 is at most 1, and y(1) = y(3 m): what is wanted stays above the image of the cut
+    const double top = 3.0 * m, al = 4.0 / (1.0 + top), be = al / (1.0 + top);
+    const double cut = m * (al - be * m), gap = l * (al - be * (2.0 * m + l));
+    const bool last = cut >= kLiftTo;                // then also shifted and scaled to [-1, 1]
+    const double shift = last ? cut : 0.0, sc = last ? 1.0 / (1.0 - cut) : 1.0;
+    product(X, [&](int r0, int c0, auto sum) {
+      for_frags(r0, c0, [&](int rt, int ct) {
+        const int i = 16 * rt - r0 + i16, j = 16 * ct - c0 + kq, i2 = 16 * ct - c0 + i16, j2 = 16 * rt - r0 + kq;
+        f64x4_t x = frag_load(X + tile16(rt, ct, P), lane);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          x[v] = (fma(al, x[v], -be * sum(i, j + 4 * v)) - (16 * rt + i16 == 16 * ct + 4 * v + kq ? shift : 0.0)) * sc;
+        put(Xn, rt, ct, x);
+        if (r0 != c0) {
+          f64x4_t y = frag_load(X + tile16(ct, rt, P), lane);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[v] = fma(al, y[v], -be * sum(j2 + 4 * v, i2)) * sc;
+          put(Xn, ct, rt, y);
+        }
+      });
+    });
+    meet();
+    m = cut;
+    l = gap * sc;
+    double* tmp = X; X = Xn; Xn = tmp;
+  }
   int step = 0;
 #pragma unroll 1
   for (; alive && !done && step < kMaxSignSteps; ++step) {
@@ -519,7 +557,9 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
     if ((tid & 63) == 0) s_dev[wv] = dev;
     __syncthreads();
     if (tid == 0) {
-      const double m = fmax(fmax(s_dev[0], s_dev[1]), fmax(s_dev[2], s_dev[3]));
+      double m = s_dev[0];
+#pragma unroll
+      for (int w = 1; w < 4 * KS; ++w) m = fmax(m, s_dev[w]);
       atomicMax(&cb->dev[step], (unsigned long long)__double_as_longlong(m));
     }
     meet();
@@ -546,7 +586,7 @@ __global__ __launch_bounds__(256, WIDE ? 3 : 2) void sign_kernel(const double* _
       });
     });
     for (int p = slot; p < P; p += nact)             // the rows and columns before a: identity
-      for (int q = tid; q < (p < a ? P : a); q += 256) Yb[(long)p * P + q] = p == q ? 1.0 : 0.0;
+      for (int q = tid; q < (p < a ? P : a); q += 256 * KS) Yb[(long)p * P + q] = p == q ? 1.0 : 0.0;
   }
   if (slot == 0 && tid == 0) cb->state = done ? 2 : 3;   // every workgroup of the image has read it (behind a barrier, or gave up)
   if (!alive && img_status && tid == 0) img_status[b] = 1;
@@ -639,27 +679,30 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   SplitCtl* ctl = (SplitCtl*)scratch;
   double* off = (double*)((char*)scratch + (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256);
   double* link = off + (size_t)B * P;
-  static PerDeviceInt cache_narrow, cache_wide;
-  int cap_narrow = 0, cap_wide = 0;
-  hipError_t e = resident_workgroups(cache_narrow, sign_kernel<false>, 256, 0, &cap_narrow);
-  if (e != hipSuccess) return e;
-  if ((e = resident_workgroups(cache_wide, sign_kernel<true>, 256, 0, &cap_wide)) != hipSuccess) return e;
   const long n32 = P / 32, n64 = P / 64;
   const long t32 = n32 * (n32 + 1) / 2, t64 = n64 * (n64 + 1) / 2;
-  // small tiles while the device holds the workgroups of all images at once
-  const bool wide = B * t32 > 2 * cap_narrow;
-  const int capacity = wide ? cap_wide : cap_narrow;
+  // Small tiles while a compute unit gets one at most; then 64 x 64 tiles, k in two halves while a compute unit gets one of those.
+  // us per product: eight images of order 384 30 on small tiles (2.4 a unit), 13 on wide ones with k in halves.
+  constexpr long kUnits = 256;
+  const int form = B * t32 <= kUnits ? 0 : B * t64 <= kUnits ? 1 : 2;
+  const size_t lds = (form == 1 ? 8 : 4) * ST * STP * sizeof(double);
+  static PerDeviceInt raised, cache[3];
+  auto kern = form == 0 ? sign_kernel<false, 1> : form == 1 ? sign_kernel<true, 2> : sign_kernel<true, 1>;
+  hipError_t e;
+  if (form == 1 && (e = ensure_dynamic_lds(raised, (const void*)kern, lds)) != hipSuccess) return e;
+  int capacity = 0;
+  if ((e = resident_workgroups(cache[form], kern, form == 1 ? 512 : 256, lds, &capacity)) != hipSuccess) return e;
   // An image of more tiles than its workgroups deals them out.  Its workgroups are an eighth of those the device holds at
   // most, so that the partial images of eight concurrent calls never hold all of it while they wait for the rest of theirs.
-  const long most = capacity / 8, tiles = wide ? t64 : t32;
+  const long most = capacity / 8, tiles = form ? t64 : t32;
   const long W = tiles < most ? tiles : most;
   if (W < 1) return hipErrorInvalidValue;
   const long stride = (long)P * P;
   hipLaunchKernelGGL(row_profile_kernel, dim3(P / 16, B), dim3(256), 0, st, H, P, stride, r, off, link, skip);
   hipLaunchKernelGGL(split_kernel, dim3(B), dim3(256), 0, st, H, P, stride, r, (const double*)off, (const double*)link, ordered, ctl,
                      skip);
-  hipLaunchKernelGGL(wide ? sign_kernel<true> : sign_kernel<false>, dim3((unsigned)(B * W)), dim3(256), 0, st, H, X0, Y, X1, P, (int)W, ctl,
-                     img_status, barrier_limit_ticks());
+  hipLaunchKernelGGL(kern, dim3((unsigned)(B * W)), dim3(form == 1 ? 512 : 256), lds, st, H, X0, Y, X1, P, (int)W, ctl, img_status,
+                     barrier_limit_ticks());
   return hipGetLastError();
 }
 

@@ -3,8 +3,16 @@
 //
 // Only the r dominant eigenpairs of G = Z_M^T Z_M enter the energies, so instead of
 // diagonalising all of G, a block of P > r vectors is iterated:
-//     Y <- G Y,  Y <- orthonormalise(Y)          (P = r + 64..127; error shrinks by lambda_{P+1}/lambda_r per step)
-// and the P x P projection Q^T G Q is split at its r-th eigenvalue (split.hip): U = Pi Q^T spans the dominant subspace and
+//     Y <- p(G) Y,  Y <- orthonormalise(Y)       (P = r + 64..127)
+// with p the Chebyshev polynomial of [0, lambda_P]: of all polynomials of m products it grows fastest beyond that interval, so
+// that m products shrink the error by T_m(2 lambda_r / lambda_P - 1), about (4 lambda_r / lambda_P)^m / 2 for a fast decay and
+// 2.4^m where lambda_r is only 1.2 lambda_P, against (lambda_r / lambda_P)^m for m products with G itself.  How many products a
+// block takes and how many blocks there are is decided per image from the factor's diagonal (plan_block).
+// Before: 12 or 16 steps with G or G^2 (formed once per call) and an orthonormalisation after one to three of them.  G^2 costs n / 2P
+// products and loses (lambda_1 / lambda_r)^2 of the 1e-16, which products with G behind it had to contract again.
+// us per covspec_select: four of n = 1638, P = 192 (9 products, G^2, 7 factorisations -> 10 and 4) 2890 -> 2140; a frame of four
+// videos, n = 1280 (second pass, 11 factorisations -> 5) 2590 -> 1800; sixty-four of 640, P = 256 (7 -> 4) 7.0 -> 6.1 ms.
+// The P x P projection Q^T G Q is split at its r-th eigenvalue (split.hip): U = Pi Q^T spans the dominant subspace and
 // c_i = (U (Q^T G))_ii.  All products are fp64 MFMA GEMMs; the cost scales with r, not with M.
 //
 // Storage is transposed (vectors are rows, Yt is P x nP) so that every product is in the
@@ -14,7 +22,7 @@
 // The start block is Omega G with a fixed +-1 pattern Omega, so exact duplicate tokens (equal rows of
 // G) cannot make it rank deficient.
 // The residual of the dominant subspace, Pi Q^T G - H U, is checked; images that fail (slow decay, P too small, no gap
-// at the cut) take four more steps and, if they fail again, the full block Jacobi solve of G.
+// at the cut) take a further block and, if they fail again, the full block Jacobi solve of G.
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"
@@ -26,17 +34,16 @@ namespace {
 constexpr int NB = 64;        // panel width of Cholesky / substitution
 constexpr int NBP = NB + 1;   // LDS pitch
 // Relative residual accepted for the dominant subspace, row by row (split_finish_kernel).  It perturbs an energy by at
-// most 1e-9 / (relative gap at r) relative.  A block that took the steps planned for it sits at 2e-10 (kPlanTol) or below,
-// one that took all of the first pass at 1e-11..1e-13, unconverged ones orders above.  (Energies as returned, in fp32, are
-// 2.6e-8 off their 64-bit values with either, the rounding to fp32.)
+// most 1e-9 / (relative gap at r) relative.  A block that took the products planned for it sits at 2e-10 or below,
+// unconverged ones orders above.  (Energies as returned, in fp32, are 2.6e-8 off their 64-bit values with either, the rounding
+// to fp32.)
 constexpr double kRitzTol = 1e-9;
-// see the end of chol_kernel
-constexpr double kPivotNear = 0.25;   // smallest scaled pivot above this: rows nearly orthogonal, blocks of three steps
-constexpr double kPivotFar = 1e-3;    // above this: blocks of two steps
-constexpr double kGradeDigits = 14.0; // decimal digits a block's grading (lambda_1 / lambda_P)^steps may use up
-constexpr int kMaxBlockSteps = 3;
-constexpr double kPlanTol = 2e-10;     // residual that the planned number of steps has to promise (checked: kRitzTol)
-constexpr double kPivotOnePass = 0.01; // final step: above this one Cholesky-QR pass leaves the rows orthonormal to ~1e-14
+// A last factorisation with a smallest scaled pivot below this leaves rows whose inner products exceed what the residual check
+// would see (about 1e-16 over the pivot); the image goes on in the second pass.
+constexpr double kPivotOnePass = 1e-10;
+constexpr double kPivotFloor = 1e-28;  // see chol_kernel
+constexpr double kLn10 = 2.302585092994046;
+
 constexpr size_t kCholLdsFixed = (size_t)(2 * NB * NBP + NB) * sizeof(double);   // plus P doubles: the diagonal of S
 
 __global__ void omega_kernel(double* __restrict__ om, int P, int n, int nP) {
@@ -46,6 +53,123 @@ __global__ void omega_kernel(double* __restrict__ om, int P, int n, int nP) {
   uint32_t h = (uint32_t)r * 0x9E3779B1u ^ ((uint32_t)c + 0x7F4A7C15u) * 0x85EBCA77u;
   h ^= h >> 15; h *= 0x2C1B3C6Du; h ^= h >> 12; h *= 0x297A2D39u; h ^= h >> 15;
   om[i] = (c < n) ? ((h & 1u) ? 1.0 : -1.0) : 0.0;
+}
+
+// ---- The schedule of an image.  Orthonormalisations are numbered; before orthonormalisation k the kernels read state k of the
+// image, the factorisation writes state k + 1, the products behind it read that.  Four integers per image and state:
+//   ST_REST  0: takes part in the next orthonormalisation, 1: in the last one of the pass only, 2: in none of this pass
+//   ST_IDLE  minus the number of products of the block that follows
+//   ST_SEL, ST_END  the buffer its first operand is in, and the one its result is in (products alternate between the two)
+enum { ST_REST, ST_IDLE, ST_SEL, ST_END, ST_FIELDS };
+struct IterPlan {
+  double tb;      // 2 / beta, beta = the upper end of the damped interval; 0: the block's products are with G itself
+  float l1, s;    // ln(lambda_1 / beta); how far the rows are separated from the leading ones, ln of the growth so far
+  int pw, n, m[4]; // products with G up to the first estimate; Chebyshev blocks so far and their degrees
+  int redo;       // failed the check: the last product was with G, from orthonormal rows
+};
+struct PlanArgs {
+  const int* in;  // states of this orthonormalisation and of the next, [ST_FIELDS][B] each
+  int* out;
+  IterPlan* plan;
+  int* left;      // [B] nothing left to do for the image in this pass
+  int B, r;
+  int slots;      // products that may follow; 0: the last orthonormalisation of the pass
+  int first;      // the very first: nothing is known about the spectrum yet
+  int closing;    // 1: the last block of the first pass follows, 2: of the second
+};
+
+__device__ __forceinline__ float ln_cosh(float t) { return t + log1pf(expf(-2.0f * t)) - 0.6931472f; }
+// acosh(e^v) for v >= 0
+__device__ __forceinline__ float acosh_exp(float v) { return v + logf(1.0f + sqrtf(fmaxf(0.0f, 1.0f - expf(-2.0f * v)))); }
+
+// Decides what follows an orthonormalisation from the diagonal of its factor (rows 0, r - 1 and P - 1: d1, dr, dP) and its smallest
+// scaled pivot (L_kk^2 / S_kk, the squared sine between row k and the rows before it).  The rows are ordered like the
+// eigenvectors, so after m products with G from orthonormal rows the diagonal holds lambda_k^m: within a quarter of lambda_P and a
+// third of lambda_r after the first block on the token matrices of all workloads.  After a Chebyshev block it holds T_m.
+//   products needed: the error, from x^-pw / T_m1 / T_m2 ... with x = lambda_r / beta, has to
+//     come below 2e-10;
+//   products possible in one block: with growth e^b between the first row and the last, a rounding error of the size eps in row
+//     k along row 1 becomes eps e^b of it.  eps is e^-s while the rows are not yet separated any further, else the 1e-16 over the
+//     pivot that the factorisation left.  Cholesky-QR stands eps e^b of 3e4 (a scaled pivot of 1e-9), and 1e3 at the
+//     last one (it is not repeated).
+// Modelled in fp64 on the token matrices and on spectra from x = 1.2 to 1e5, lambda_1 / lambda_P from 2 to 5e7.
+__device__ __forceinline__ void plan_block(const PlanArgs& q, int b, double d1, double dr, double dP, double pmin) {
+  IterPlan& p = q.plan[b];
+  int* out = q.out + b;
+  const int at = q.in[ST_END * q.B + b];          // the trsm works in place
+  int m = 0, rest = 0;
+  const bool sane = dP > 0.0 && d1 < 1e300 && dr > 0.0 && dr < 1e300 && pmin > 0.0;
+  if (q.first) {
+    // The diagonal of a random block's factor spans a tenth of lambda_1 / lambda_P or more; two products while the
+    // pivots they leave (lambda_P / lambda_1)^2 stay above 1e-10.
+    m = d1 <= 1e4 * dP ? 2 : 1;
+    p.tb = 0.0; p.l1 = p.s = 0.0f; p.pw = 1 + m; p.n = 0; p.redo = 0;
+  } else if (q.slots == 0) {
+    if (!(pmin > kPivotOnePass)) q.left[b] = 1;
+  } else if (!sane) {
+    q.left[b] = 1;
+    rest = 2;
+  } else {
+    float a;                                      // acosh(2 lambda_r / beta - 1)
+    if (p.tb == 0.0 || p.redo) {
+      const float per = p.redo ? 1.0f : 1.0f / (float)(p.pw - 1);
+      const float lP = per * (float)log(dP) + 0.18232f;      // the estimate is up to a fifth low
+      p.l1 = fmaxf(0.0f, per * (float)log(d1) - lP);
+      if (p.tb == 0.0) p.s = (float)p.pw * p.l1;
+      p.tb = 2.0 * exp(-(double)lP);
+      a = per * (float)log(dr) - lP;
+    } else {
+      const float t = acosh_exp(fmaxf(0.0f, (float)log(dr))) / (float)p.m[p.n - 1];
+      a = logf(0.5f + 0.5f * coshf(t));
+    }
+    const float x = fmaxf(1.0f + 1e-6f, expf(a)), ax = acoshf(2.0f * x - 1.0f);
+    const float a1 = p.l1 > 10.0f ? p.l1 + 1.3862944f : acoshf(fmaxf(1.0001f, 2.0f * expf(p.l1) - 1.0f));
+    float e = (float)p.pw * logf(x) - 0.7f;       // digits of the error so far, as a natural logarithm
+    for (int k = 0; k < p.n; ++k) e += ln_cosh(ax * (float)p.m[k]);
+    // (at the end of the first pass a factor of two of that is left to the residual check: the estimate is mostly on the safe side)
+    const float missing = (float)((q.closing == 1 ? 9.4 : 9.7) * kLn10) - e;
+    int need = missing <= 0.0f ? 0 : (int)fminf(40.0f, ceilf(acosh_exp(missing) / ax));
+    if (need == 0 && !(pmin > kPivotOnePass)) need = 1;
+    if (p.redo) need = 40;
+    if (need == 0) {
+      rest = 2;
+    } else {
+      const float apart = fmaxf(0.0f, fminf(p.s, (float)log(pmin) + (float)(19.0 * kLn10)));
+      const int most = max(1, min(q.slots, (int)(acosh_exp(apart + (float)(4.5 * kLn10)) / a1)));
+      const int last = max(1, min(q.slots, (int)(acosh_exp(apart + (float)(3.0 * kLn10)) / a1)));
+      if (need <= last) {
+        m = need;
+        rest = 1;
+      } else if (q.closing == 2) {
+        m = last;
+        rest = 1;
+      } else {
+        const int blocks = 1 + (need - last + most - 1) / most;
+        m = min(most, (need + blocks - 1) / blocks);
+        if (q.closing) {                          // not there at the end of this pass: on to the second without a split
+          rest = 2;
+          q.left[b] = 1;
+        }
+      }
+      p.s += ln_cosh(a1 * (float)m);
+      if (p.n < 4) p.m[p.n++] = m;
+    }
+    p.redo = 0;
+  }
+  out[ST_REST * q.B] = rest;
+  out[ST_IDLE * q.B] = -m;
+  out[ST_SEL * q.B] = at;
+  out[ST_END * q.B] = (at + m) & 1;
+}
+
+// An image that takes no part: its block stays as and where it is.
+__device__ __forceinline__ void rest_on(const PlanArgs& q, int b) {
+  int* out = q.out + b;
+  const int at = q.in[ST_END * q.B + b];
+  out[ST_REST * q.B] = q.in[ST_REST * q.B + b];
+  out[ST_IDLE * q.B] = 0;
+  out[ST_SEL * q.B] = at;
+  out[ST_END * q.B] = at;
 }
 
 // value of `v` in lane `l` (compile-time lane), uniform across the wave
@@ -59,14 +183,15 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle: a = L L^T) and inverts the factor, in one wave: inv(L) goes
-// to `inv` (its tiles above the diagonal are zero already), the diagonal of L to dl.  Pivots are floored at `floor_`.
+// to `inv` (its tiles above the diagonal are zero already), the diagonal of L to dl.  The pivot of row k is floored at
+// kPivotFloor diag[k], diag the diagonal of S.
 // By 16 x 16 tiles.  A diagonal tile is eliminated together with a unit matrix, lane = column (lanes 0..15 the tile,
 // 16..31 the unit matrix): step k subtracts a_ik / a_kk times row k from row i, the a_ik being the scalars of lane k, and
 // leaves the inverse of the unit-diagonal factor in the right half, no exchange through LDS and no column to wait for.  The
 // tiles below and the rest of the block follow on the MFMA, then the inverse tile by tile, inv_ts = -inv_tt sum L_tu inv_us:
 // the sum comes out of the MFMA in the layout its B operand wants.  A column by column factorisation by one wave with the
 // inversion after it by the workgroup took 23 + 14 us of a panel, this takes 11.
-__device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* dl, double floor_) {
+__device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* dl, const double* diag) {
   const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4, c = lane & 31;
 #pragma unroll 1
   for (int s = 0; s < 4; ++s) {
@@ -78,9 +203,10 @@ __device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* 
       x[i] = c < 16 ? v : (c - 16 == i ? 1.0 : 0.0);
     }
     double mine = 0.0;
+    const double floor_ = fma(kPivotFloor, diag[16 * s + i16], 1e-300);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-      const double piv = fmax(lane_value(x[k], k), floor_);
+      const double piv = fmax(lane_value(x[k], k), lane_value(floor_, k));
       double rp = __builtin_amdgcn_rcp(piv);
       rp = fma(rp, fma(-piv, rp, 1.0), rp);
       rp = fma(rp, fma(-piv, rp, 1.0), rp);
@@ -155,24 +281,27 @@ __device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* 
 //   trailing part:  S[I,I'] -= X_I X_I'^T for I' <= I on the MFMA, units of 16 x 32.
 // Every product is formed transposed, so that its result is the fragment of the tile it goes to.
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
-// Pivots are floored at 1e-28 * trace(first block) so that a numerically rank-deficient block cannot
-// produce NaNs (the residual check afterwards decides whether the result is usable).
+// A pivot is floored relative to its own row's squared length, so that a numerically rank-deficient block cannot
+// produce NaNs (the residual check afterwards decides whether the result is usable) while rows may differ in length by any
+// number of digits: after a block of products they do, by the growth of the first row over the last.
 // Bound by the chain of panels (and, from order 384 on, by one compute unit's MFMA rate in the trailing part).  One image of
 // order 192 / eight of 384 / sixty-four of 256, us: 168 / 448 / 257 with the block factored column by column, its inverse
 // formed by the workgroup and the next diagonal block updated by the wave that factors it; 76 / 220 / 115 without; 69 / 172 / 107
 // with the tiles in fragment order.  (256 registers; five are spilled, read back once a panel, outside the loops.)
 // Dynamic LDS: 2 * 64 * 65 + 64 + P doubles.
-__global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, int* skip_until, int* last_orth, int step,
-                                                   int last_free_step, int next_weight, int r, int n_sq, int* hold, int* slow) {
+__global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, PlanArgs q) {
   extern __shared__ double lds[];
   double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert_wave (tiles below the diagonal)
   double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor
   double* dl = lds + 2 * NB * NBP;  // [64] diagonal of the factor
   double* diag0 = dl + NB;          // [P] the diagonal of S before any update: squared row lengths
   const int b = blockIdx.x;
-  if (skip_until && skip_until[b] > step) return;   // this image does not orthonormalise at this step
+  if (q.in[ST_REST * q.B + b] > (q.slots == 0 ? 1 : 0)) {      // no part in this orthonormalisation
+    if (threadIdx.x == 0) rest_on(q, b);
+    return;
+  }
   double* Sb = S + (long)b * P * P;
-  double dmin = 1e300, dmax = 0.0, pmin = 1.0;   // extremes of the factor's diagonal, smallest scaled pivot (wave 0, by lane)
+  double pmin = 1.0;                              // smallest scaled pivot (wave 0, by lane)
   double d0 = 0.0, dr = 0.0, dP = 0.0;           // diagonal of the factor at rows 0, r - 1 and P - 1 (wave 0)
   const int nblk = P / NB, per16 = P / 16;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
@@ -186,10 +315,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v];
   }
   __syncthreads();
-  double floor_ = 0.0;
-  for (int i = 0; i < NB; ++i) floor_ += diag0[i];       // the same value in every thread
-  floor_ = 1e-300 + 1e-28 * floor_;
-  if (w == 0) factor_invert_wave(a, inv, dl, floor_);
+  if (w == 0) factor_invert_wave(a, inv, dl, diag0);
   __syncthreads();
 
   for (int J = 0; J < nblk; ++J) {
@@ -197,10 +323,8 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     // here `inv` holds the inverse of the factor of diagonal block J
     if (w == 0) {
       const double d = dl[lane], s0 = diag0[j0 + lane];
-      dmin = fmin(dmin, d);
-      dmax = fmax(dmax, d);
       if (s0 > 0.0) pmin = fmin(pmin, d * d / s0);
-      if (J == (r - 1) / NB) dr = __shfl(d, (r - 1) % NB, 64);
+      if (J == (q.r - 1) / NB) dr = __shfl(d, (q.r - 1) % NB, 64);
       if (J == 0) d0 = __shfl(d, 0, 64);
       if (J == nblk - 1) dP = __shfl(d, NB - 1, 64);
     }
@@ -255,7 +379,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     //      ranges, so that consecutive units mostly share the columns and their fragments stay in registers (64 columns
     //      would not fit the registers).  Wave 0 factors the next diagonal block meanwhile.
     if (w == 0) {
-      factor_invert_wave(a, inv, dl, floor_);
+      factor_invert_wave(a, inv, dl, diag0 + j0 + NB);
     } else {
       const int nb = below / 4;
       const int units = 4 * nb * (nb + 1);            // 8 * nb (nb + 1) / 2; units 0..7 are the next diagonal block
@@ -271,8 +395,8 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
       int have = -1;
 #pragma unroll 1
       for (int u = u0; u < u1; ++u) {
-        const int q = u & 3, h = (u >> 2) & 1;
-        const int rt = jt + 4 + 4 * I + q, ct = jt + 4 + 4 * I2 + 2 * h;
+        const int u4 = u & 3, h = (u >> 2) & 1;
+        const int rt = jt + 4 + 4 * I + u4, ct = jt + 4 + 4 * I2 + 2 * h;
         if (ct <= rt) {                               // a diagonal block: no tile above the diagonal
           f64x4_t fa[4], cc[2];
 #pragma unroll
@@ -306,65 +430,12 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     __syncthreads();
   }
   if (w == 0) {
-    dmin = wave_min(dmin);
-    dmax = wave_max(dmax);
     pmin = wave_min(pmin);
-  }
-  // How many steps (products with G) the image may take before it orthonormalises again.  Two things limit a
-  // block of m steps.  (1) Cholesky-QR needs the SCALED Gram matrix (unit diagonal) to be well conditioned; the raw
-  // grading lambda_1 / lambda_P of the rows is harmless.  The scaled pivots L_kk^2 / S_kk (squared sine of the
-  // angle between row k and the rows before it) say how close to orthogonal the rows were: the iteration orders
-  // the rows like the eigenvectors, and once it has, they stay nearly orthogonal over several steps.  (2) Within a
-  // row the wanted direction must not drown in rounding noise along the dominant one: (lambda_1 / lambda_P)^m has
-  // to stay well inside the 16 digits; the diagonal of L spans that ratio for the steps of the block just closed.
-  if (tid == 0) {
-    int m = 1;
-    const int begun = hold[b] > last_orth[b] ? hold[b] : last_orth[b];    // first product of the block just factored
-    if (step >= 1 && dmin > 0.0) {
-      const int closed = step - begun;                              // steps in the block just factored (>= 1)
-      const double digits_per_step = log10(fmax(dmax / dmin, 10.0)) / (double)(closed < 1 ? 1 : closed);
-      const int by_grade = (int)(kGradeDigits / digits_per_step);
-      const int by_pivot = pmin > kPivotNear ? kMaxBlockSteps : (pmin > kPivotFar ? 2 : 1);
-      // by_pivot counts products with G; the products that follow multiply by G^next_weight.  by_grade is in
-      // products of the block just closed, whose weight is never below that of the next ones.
-      const int by_pivot_products = by_pivot / next_weight;
-      m = by_pivot_products < by_grade ? by_pivot_products : by_grade;
-      if (m < 1) m = 1;
-    }
-    int next = step + m;                      // the next step that orthonormalises
-    if (next > last_free_step) next = last_free_step;     // the final step always does
-    // The final step is followed by a second pass (step + 1) that makes the rows orthonormal to rounding; the
-    // error of one pass is about 1e-16 times the scaled condition number, so with large pivots it is not needed.
-    if (step == last_free_step) next = pmin > kPivotOnePass ? step + 2 : step + 1;
-    // How many steps are needed.  The block just closed multiplied orthonormal rows by G^(2 closed), and the rows are
-    // ordered: the diagonal of L holds lambda_k^(2 closed), which gives the contraction rho = lambda_P / lambda_r and the
-    // grading lambda_1 / lambda_r (within a quarter of the true rho at step 2 on all workloads).  A first pass of s steps
-    // leaves a residual of about 2 rho^s; what the G^2 as formed is off by, 1e-16 (lambda_1 / lambda_r)^2, is contracted by
-    // the g steps with G itself behind it.  With the rows orthonormal an image may wait out an even number of products (the
-    // two blocks swap roles per product) and go on where the pass ends: a decay of 0.01 per step needs 6 steps of the 12.
-    if (n_sq > 0 && step >= 2 && step <= n_sq && last_orth[b] >= 1 && hold[b] < 0) {
-      const double per = 0.5 / (double)(step - begun);
-      const double est = pow(fmax(dP, 1e-300) / fmax(dr, 1e-300), per), grade = pow(d0 / fmax(dr, 1e-300), per);
-      const double rho = fmin(1.25 * est, 1.0);
-      const int total = last_free_step + 1;
-      for (int t = (last_free_step - step) / 2 * 2 + step; t > step; t -= 2) {    // resume at product t
-        const int with_sq = n_sq - t > 0 ? n_sq - t : 0, g = total - (t > n_sq ? t : n_sq);
-        const int steps = 2 * (step + with_sq) + g;
-        if (2.0 * pow(rho, (double)steps) + 1e-16 * grade * grade * pow(rho, (double)g) < kPlanTol) {
-          hold[b] = t;
-          next = t + 1 < last_free_step ? t + 1 : last_free_step;
-          break;
-        }
-      }
-      // an image that this pass cannot bring down to the tolerance skips the split and goes on in the second pass
-      if (2.0 * pow(est, (double)(2 * n_sq + total - n_sq)) > 4.0 * kRitzTol) slow[b] = 1;
-    }
-    skip_until[b] = next;
-    last_orth[b] = step;
+    if (tid == 0) plan_block(q, b, d0, dr, dP, pmin);
   }
 }
 
-// Yt[b] <- L^-1 Yt[b] (P x nP, pitch nP) by blocked forward substitution with the factor chol_kernel left
+// Y <- L^-1 Y (P x nP, pitch nP; Y is the image's block in Yt or `other` doubles behind it) by blocked forward substitution with the factor chol_kernel left
 // in S (strictly-lower blocks) and Dinv (inverted diagonal blocks), both tiles in fragment order.  Columns are independent: each wave
 // owns 16 of them and never reads what another wave writes, so the whole solve is one launch.
 //   for block row bi:  T = Yt[bi] - sum_{K<bi} L[bi,K] Yt[K];   Yt[bi] = inv(L_bibi) T
@@ -435,16 +506,16 @@ __device__ __forceinline__ void trsm_steps(const TrsmPtr& p, f64x4_t (&y)[NBLK][
 }
 
 template <int NBLK>
-__global__ __launch_bounds__(256, 1) void trsm_kernel(double* Yt, const double* __restrict__ S, const double* __restrict__ Dinv, int nP,
-                                                      int wg_per_image, const int* __restrict__ last_orth, int step) {
+__global__ __launch_bounds__(256, 1) void trsm_kernel(double* Yt, long other, const double* __restrict__ S, const double* __restrict__ Dinv, int nP,
+                                                      int wg_per_image, const int* __restrict__ state, int nimg, int rest_max) {
   const int b = blockIdx.x / wg_per_image, cw = blockIdx.x - b * wg_per_image;
-  if (last_orth && last_orth[b] != step) return;    // the factorisation of this step did not run for this image
+  if (state[ST_REST * nimg + b] > rest_max) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
   constexpr int P = NBLK * NB;
   TrsmPtr p;
   p.L = S + (long)b * P * P + 2 * lane;
   p.D = Dinv + (long)b * NBLK * NB * NB + 2 * lane;
-  p.Y = Yt + (long)b * P * nP + (long)kq * nP + cw * 64 + w * 16 + i16;     // nP % 64 == 0, so every column exists
+  p.Y = Yt + (state[ST_END * nimg + b] ? other : 0) + (long)b * P * nP + (long)kq * nP + cw * 64 + w * 16 + i16;     // nP % 64 == 0, so every column exists
   p.nP = nP;
   f64x4_t y[NBLK][4], f[4][4], acc[4], rhs[4];
   trsm_fetch<NBLK, 0>(p, f[0]);
@@ -455,14 +526,14 @@ __global__ __launch_bounds__(256, 1) void trsm_kernel(double* Yt, const double* 
 }
 
 // The same for any number of blocks: the solved blocks go through memory.
-__global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, const double* __restrict__ S, const double* __restrict__ Dinv,
-                                                        int P, int nP, int wg_per_image, const int* __restrict__ last_orth, int step) {
+__global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, long other, const double* __restrict__ S, const double* __restrict__ Dinv,
+                                                        int P, int nP, int wg_per_image, const int* __restrict__ state, int nimg, int rest_max) {
   const int b = blockIdx.x / wg_per_image, cw = blockIdx.x - b * wg_per_image;
-  if (last_orth && last_orth[b] != step) return;    // the factorisation of this step did not run for this image
+  if (state[ST_REST * nimg + b] > rest_max) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
   const int col = cw * 64 + w * 16 + i16;    // nP % 64 == 0, so every column exists
   const int nblk = P / NB;
-  double* Yb = Yt + (long)b * P * nP;
+  double* Yb = Yt + (state[ST_END * nimg + b] ? other : 0) + (long)b * P * nP;
   const double* Lb = S + (long)b * P * P;
   for (int bi = 0; bi < nblk; ++bi) {
     f64x4_t acc[4];
@@ -505,18 +576,35 @@ __global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, const double*
   }
 }
 
-// skip_until[b] = ok[b] ? INT_MAX : -1 (images that passed take no further part), last_orth[b] = hold[b] = -1, slow[b] = 0
-__global__ void mask_passed_kernel(const int* __restrict__ ok, int* __restrict__ skip_until, int* __restrict__ last_orth, int* __restrict__ hold,
-                                   int* __restrict__ slow, int B) {
+// State 0 of a pass.  First: every block is in buffer 0.  Second: images that passed the check rest; one that was left out of the
+// split goes on from its block, one that failed the check from the product with G that followed its last orthonormalisation
+// (in the buffer its rows are not in).
+__global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__ prev, const int* __restrict__ ok, IterPlan* __restrict__ plan,
+                                  int* __restrict__ left, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
-  skip_until[b] = ok[b] ? 0x7fffffff : -1;
-  last_orth[b] = -1;
-  hold[b] = -1;
-  slow[b] = 0;
+  const bool passed = prev && ok[b] != 0, failed = prev && !passed && !left[b];
+  const int at = prev ? (failed ? 1 - prev[ST_SEL * B + b] : prev[ST_END * B + b]) : 0;
+  out[ST_REST * B + b] = passed ? 2 : 0;
+  out[ST_IDLE * B + b] = 0;
+  out[ST_SEL * B + b] = at;
+  out[ST_END * B + b] = at;
+  plan[b].redo = failed;
+  left[b] = passed;
 }
 
 }  // namespace
+
+// Products a block may take: two between the first two orthonormalisations (the spectrum is not known yet), then as
+// many as tell the rows apart, three or four at most (plan_block; a launch that no image needs costs 2 us); kSlots2: the second pass.
+// The slowest decay that converges is lambda_r / lambda_{P+1} = 2.8; what is slower goes to the full solve, 20 ms and more.
+constexpr int kBlocks = 3, kSlots[kBlocks] = {2, 3, 4}, kSlots2 = 3;
+constexpr int kStates = kBlocks + 2 + 3;       // the first pass's and the second's
+
+inline size_t tail_doubles(int B, int P, int nP) {
+  const size_t u = (size_t)nP * (P + 2 * (P / kSymTile)), x1 = (size_t)P * P;
+  return (size_t)B * (u > x1 ? u : x1);
+}
 
 int subspace_block(int n, int r) {
   // P = r + 64 rounded up to the panel width: the split costs P^3 per step and each iteration P^2 n, while a wider
@@ -529,14 +617,18 @@ int subspace_block(int n, int r) {
 size_t subspace_workspace_bytes(int B, int n, int nP, int P) {
   if (P <= 0) return split_direct(nP) ? 3 * (size_t)B * nP * nP * 8 + split_scratch_bytes(B, nP) + 256 : 0;
   const size_t blk = (size_t)B * P * nP * 8;
-  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 + 4 * (size_t)B * 4 + 256 + (size_t)B * nP * nP * 8 /* G^2 */ + 256;
+  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 +
+         (size_t)B * (sizeof(IterPlan) + (kStates * ST_FIELDS + 1) * sizeof(int)) + 256 + tail_doubles(B, P, nP) * 8 + 256;
 }
 
-// The first pass makes iters steps of the iteration as iters / 3 products with G^2 followed by iters / 3 with G.
-// Launches of the probed shape: start block and the products of the first pass.
-int subspace_product_launches(int iters) { return 2 * (iters / 3) + 1; }
+// Launches of the probed shape: start block and the products of the first pass (blocks that take fewer leave the rest out).
+int subspace_product_launches() {
+  int n = 2;
+  for (int k = 0; k < kBlocks; ++k) n += kSlots[k];
+  return n;
+}
 
-hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, int iters, int more_iters, void* ws_, int* ok,
+hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, void* ws_, int* ok,
                                  float* c, int* img_status, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t st) {
   if (P == 0) {
     // the whole matrix is the window
@@ -550,7 +642,6 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   }
   hipError_t e0;
   if (P <= 0 || P % NB != 0 || P > n || P > 4096 || nP % NB != 0) return hipErrorInvalidValue;
-  if (iters < 3 || iters % 3 != 0 || more_iters < 1) return hipErrorInvalidValue;
   {
     static PerDeviceInt raised;
     if ((e0 = ensure_dynamic_lds(raised, (const void*)chol_kernel, kCholLdsFixed + 4096 * sizeof(double))) != hipSuccess) return e0;
@@ -565,126 +656,110 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   double* D = H + (size_t)B * P * P;
   double* Pi = D + (size_t)B * P * NB;                                                      // [B][P][P] the projector
   void* scratch = (void*)(((uintptr_t)(Pi + (size_t)B * P * P) + 255) & ~(uintptr_t)255);
-  int* skip_until = (int*)((char*)scratch + split_scratch_bytes(B, P));                     // [B] next step that orthonormalises
-  int* last_orth = skip_until + B;                                                          // [B] step of the last one
-  int* hold = last_orth + B;                                                                // [B] products before this one are left out
-  int* slow = hold + B;                                                                     // [B] no split at the end of the first pass
-  double* G2 = (double*)(((uintptr_t)(slow + B) + 255) & ~(uintptr_t)255);             // [B][nP][nP] G squared
-  // after the products with G^2 its place is free: one of the iterates of the split (P <= nP), then U, its partial energies
-  // and the partial row lengths of the residual: nP (P + P / 32 + P / 32) <= nP^2 doubles per image, as P <= 3/4 n
-  double* U = G2;
-  double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 32][nP]
-  double* rnorm = cpart + (size_t)B * (P / kSymTile) * nP;                                       // [B][P][nP / 32]
+  IterPlan* plan = (IterPlan*)((char*)scratch + split_scratch_bytes(B, P));                  // [B]
+  int* states = (int*)(plan + B);                                                           // [kStates][ST_FIELDS][B]
+  int* left = states + (size_t)kStates * ST_FIELDS * B;                                     // [B] nothing left to do in this pass
+  double* X1 = (double*)(((uintptr_t)(left + B) + 255) & ~(uintptr_t)255);                  // an iterate of the split, then
+  double* U = X1;                                                                           // [B][P][nP] Pi Q^T,
+  double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 32][nP] partial energies
+  double* rnorm = cpart + (size_t)B * (P / kSymTile) * nP;                                  // [B][P][nP / 32] of the residual's row lengths
   hipError_t e;
 
-  // Second pass: images that passed the first check take no further part; the kernels see them as skip_until ==
-  // INT_MAX (never reached by a step counter), which is what `masked` switches on for the plain products.
-  bool masked = false;
-  auto mask = [&](GemmArgs& g) {
-    if (masked) { g.skip = skip_until; g.skip_if = 0x7ffffffe; }
-    else { g.skip = slow; g.skip_if = 0; }
-  };
-  auto gemm_yt_g = [&](const double* X, double* out, const double* Gop, int it) {   // out = X Gop  (P x nP), Gop = G or G^2; product `it`
-    GemmArgs g;
-    g.A = X; g.B = Gop; g.C = out; g.M = P; g.N = nP; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = nP;
+  const long other = (long)B * P * nP;       // from buffer 0 of the blocks to buffer 1
+  auto state = [&](int k) { return states + (size_t)k * ST_FIELDS * B; };
+  // out = X Gop (P x nP) with X in the buffer that state k names (flip: in the other one), out in the other
+  auto gemm_yt_g = [&](int k, int flip, GemmArgs& g) {
+    g.B = G; g.M = P; g.N = nP; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = nP;
     g.batch = B; g.strideA = (long)P * nP; g.strideB = (long)nP * nP; g.strideC = (long)P * nP;
     g.epilogue = EPI_STORE_F64;
-    if (masked) mask(g);
-    else { g.skip = hold; g.skip_if = it; }
+    g.A = flip ? Zt : Yt; g.C = flip ? Yt : Zt;
+    g.sel = state(k) + ST_SEL * B; g.selA = flip ? -other : other; g.selC = -g.selA;
     return launch_gemm64_nt(g, true, true, st);
   };
-  // X <- L^-1 X with X X^T = L L^T.  Images with skip_until[b] > step leave X alone, and the factorisation decides
-  // how many steps the image takes before the next one (never beyond last_free_step).
+  // X <- L^-1 X with X X^T = L L^T for the images that state k lets take part, and the plan of what follows
   const size_t chol_lds = kCholLdsFixed + (size_t)P * sizeof(double);
-  auto cholqr = [&](double* X, int step, int last_free_step, int next_weight, int n_sq) -> hipError_t {
+  auto cholqr = [&](int k, int slots, bool first, int closing) -> hipError_t {
+    const int rest_max = slots == 0 ? 1 : 0;
     GemmArgs g;
-    g.A = X; g.B = X; g.C = S; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
+    g.A = Yt; g.B = Yt; g.C = S; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
     g.batch = B; g.strideA = (long)P * nP; g.strideB = (long)P * nP; g.strideC = (long)P * P;
     g.epilogue = EPI_STORE_F64;
     g.frag = true;
-    g.skip = skip_until;
-    g.skip_if = step;
+    g.sel = state(k) + ST_END * B; g.selA = g.selB = other;
+    g.skip = state(k) + ST_REST * B; g.skip_if = rest_max;
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(chol_kernel, dim3((unsigned)B), dim3(512), chol_lds, st, S, D, P, skip_until, last_orth, step, last_free_step,
-                       next_weight, r, n_sq, hold, slow);
+    PlanArgs q;
+    q.in = state(k); q.out = state(k + 1); q.plan = plan; q.left = left; q.B = B; q.r = r; q.slots = slots; q.first = first; q.closing = closing;
+    hipLaunchKernelGGL(chol_kernel, dim3((unsigned)B), dim3(512), chol_lds, st, S, D, P, q);
     const dim3 tg((unsigned)(B * (nP / NB)));
     const double *cS = S, *cD = D;
-    const int* orth = last_orth;
+    const int* in = state(k);
     switch (P / NB) {
 #define COVSPEC_TRSM(n) \
-  case n: hipLaunchKernelGGL(trsm_kernel<n>, tg, dim3(256), 0, st, X, cS, cD, nP, nP / NB, orth, step); break;
+  case n: hipLaunchKernelGGL(trsm_kernel<n>, tg, dim3(256), 0, st, Yt, other, cS, cD, nP, nP / NB, in, B, rest_max); break;
       COVSPEC_TRSM(2)
       COVSPEC_TRSM(3)
       COVSPEC_TRSM(4)
       COVSPEC_TRSM(5)
       COVSPEC_TRSM(6)
 #undef COVSPEC_TRSM
-      default: hipLaunchKernelGGL(trsm_any_kernel, tg, dim3(256), 0, st, X, cS, cD, P, nP, nP / NB, orth, step);
+      default: hipLaunchKernelGGL(trsm_any_kernel, tg, dim3(256), 0, st, Yt, other, cS, cD, P, nP, nP / NB, in, B, rest_max);
     }
     return hipGetLastError();
   };
-  double* cur = Yt;
-  double* oth = Zt;
-  // `steps` products from the block in `cur` (each preceded by an orthonormalisation where the image's schedule
-  // asks for one), then the split, the residual check and the energies.
-  // The first n_sq products multiply by G^2: two steps of the iteration at the cost of one (the same subspace as
-  // two products with G and an orthonormalisation between them).  G^2 as formed is off by about 1e-16 |G|^2, which
-  // is a fixed perturbation of the operator of relative size 1e-16 (lambda_1 / lambda_r)^2 at the r-th eigenvalue
-  // (1e-8 for a spectrum that falls by 1e4 down to r); the products with G itself that follow contract that error
-  // like any other, and a CPU model of the workloads' matrices needs three to four of them.  The last product
-  // feeds the split and the residual check and is with G in any case.
-  auto pass = [&](int n_sq, int n_plain, int pass_no) -> hipError_t {
-    const int steps = n_sq + n_plain;
-    for (int it = 0; it < steps; ++it) {
-      // the block of step 0 is not (orthonormal) x G, so its factor says nothing about the next step (the kernel
-      // takes one step after it); the last step always orthonormalises, twice where its pivots ask for it
-      const int w = it < n_sq ? 2 : 1;
-      if ((e = cholqr(cur, it, steps - 1, w, n_sq)) != hipSuccess) return e;
-      if (it + 1 == steps && (e = cholqr(cur, it + 1, steps - 1, 1, 0)) != hipSuccess) return e;
-      if ((e = gemm_yt_g(cur, oth, w == 2 ? G2 : G, it)) != hipSuccess) return e;   // last: oth = Q^T G
-      double* t = cur; cur = oth; oth = t;
+  // products of the block behind state k
+  auto block = [&](int k, int slots) -> hipError_t {
+    for (int i = 0; i < slots; ++i) {
+      GemmArgs g;
+      g.cheb = &plan->tb; g.cheb_stride = sizeof(IterPlan) / sizeof(double); g.cheb_step = i;
+      g.skip = state(k) + ST_IDLE * B; g.skip_if = -(i + 1);
+      if ((e = gemm_yt_g(k, i & 1, g)) != hipSuccess) return e;
     }
-    // now oth = Q^T (orthonormal rows), cur = Q^T G.  H = (Q^T G) Q
+    return hipSuccess;
+  };
+  // the last orthonormalisation of a pass, the split, the residual check and the energies
+  auto finish = [&](int k, int pass_no) -> hipError_t {
+    if ((e = cholqr(k, 0, false, 0)) != hipSuccess) return e;
+    const int* sel = state(k + 1) + ST_SEL * B;      // Q^T is there (orthonormal rows), Q^T G goes into the other buffer
     {
       GemmArgs g;
-      g.A = cur; g.B = oth; g.C = H; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
+      g.skip = left; g.skip_if = 0;
+      if ((e = gemm_yt_g(k + 1, 0, g)) != hipSuccess) return e;
+    }
+    {                                                // H = (Q^T G) Q
+      GemmArgs g;
+      g.A = Zt; g.B = Yt; g.C = H; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
       g.batch = B; g.strideA = (long)P * nP; g.strideB = (long)P * nP; g.strideC = (long)P * P;
+      g.sel = sel; g.selA = -other; g.selB = other;
       g.epilogue = EPI_STORE_F64;
       g.lower_only = true;      // H is symmetric: the tiles below the diagonal are mirrored
       g.mirror = true;
-      mask(g);
+      g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, G2, scratch, masked ? (const int*)ok : (const int*)slow, img_status, st)) != hipSuccess) return e;
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, X1, scratch, left, img_status, st)) != hipSuccess) return e;
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;
-      g.A = Pi; g.B = oth; g.C = U; g.D = cur; g.dots = cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP;
+      g.A = Pi; g.B = Yt; g.C = U; g.D = Zt; g.dots = cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP;
       g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * nP;
-      mask(g);
+      g.sel = sel; g.selB = other; g.selD = -other;
+      g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_store_dot(g, st)) != hipSuccess) return e;
     }
     // row lengths of the residual Pi Q^T G - H U
     {
       GemmArgs g;
-      g.A = Pi; g.B = cur; g.A2 = H; g.B2 = U; g.C = rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / kSymTile;
+      g.A = Pi; g.B = Zt; g.A2 = H; g.B2 = U; g.C = rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / kSymTile;
       g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * (nP / kSymTile);
-      mask(g);
+      g.sel = sel; g.selB = -other;
+      g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_rownorm_dual(g, st)) != hipSuccess) return e;
     }
-    return launch_split_finish(H, Pi, rnorm, nP / kSymTile, cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, scratch, slow, ok, pass_no, c, st);
+    return launch_split_finish(H, Pi, rnorm, nP / kSymTile, cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, scratch, left, ok, pass_no, c, st);
   };
+  const dim3 ig((unsigned)((B + 255) / 256));
 
-  // G^2 (symmetric: tiles on and below the diagonal, mirrored)
-  {
-    GemmArgs g;
-    g.A = G; g.B = G; g.C = G2; g.M = nP; g.N = nP; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = nP;
-    g.batch = B; g.strideA = (long)nP * nP; g.strideB = (long)nP * nP; g.strideC = (long)nP * nP;
-    g.epilogue = EPI_STORE_F64;
-    g.lower_only = true;
-    g.mirror = true;
-    if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
-  }
   // start block: Omega G
   hipLaunchKernelGGL(omega_kernel, dim3((unsigned)(((long)P * nP + 255) / 256)), dim3(256), 0, st, Om, P, n, nP);
   if (probe_begin && (e = hipEventRecord(probe_begin, st)) != hipSuccess) return e;
@@ -696,14 +771,19 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
   }
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
-  if ((e = launch_fill_int(skip_until, 3 * B, -1, st)) != hipSuccess) return e;
-  if ((e = launch_fill_int(slow, B, 0, st)) != hipSuccess) return e;
-  if ((e = pass(iters / 3, iters / 3, 1)) != hipSuccess) return e;
-  // images whose subspace is not there yet (slower spectral decay than the first pass allows for) go on from Q^T G
-  // for a few more steps; for the others every kernel of this pass returns at once
-  masked = true;
-  hipLaunchKernelGGL(mask_passed_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, (const int*)ok, skip_until, last_orth, hold, slow, B);
-  return pass(0, more_iters, 2);
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, B);
+  for (int k = 0; k < kBlocks; ++k) {
+    if ((e = cholqr(k, kSlots[k], k == 0, k == kBlocks - 1 ? 1 : 0)) != hipSuccess) return e;
+    if ((e = block(k + 1, kSlots[k])) != hipSuccess) return e;
+  }
+  if ((e = finish(kBlocks, 1)) != hipSuccess) return e;
+  // images whose subspace is not there yet (slower decay of the spectrum than the blocks of the first pass allow for) take
+  // another block; for the others every kernel of this pass returns at once
+  const int k2 = kBlocks + 2;
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(k2), (const int*)state(k2 - 1), (const int*)ok, plan, left, B);
+  if ((e = cholqr(k2, kSlots2, false, 2)) != hipSuccess) return e;
+  if ((e = block(k2 + 1, kSlots2)) != hipSuccess) return e;
+  return finish(k2 + 1, 2);
 }
 
 }  // namespace covspec

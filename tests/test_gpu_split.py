@@ -61,6 +61,40 @@ def test_energies_match_the_oracle(C, name):
         np.testing.assert_array_equal(idx[b], ref["idx"])
 
 
+# tokens, rank, decay of the singular values per index, factor on the four largest of them, the way the solve has to take; what
+# the block iteration's schedule has to cope with
+SCHEDULES = {
+    "slow": (256, 32, 0.006, 1.0, 2),                 # lambda_r 3.2 times what the block leaves out: every block at its longest
+    "one-block": (300, 72, 0.03, 1.0, 1),             # there after the first two factorisations but for one product
+    "outliers": (300, 72, 0.02, 30.0, 1),             # first row 2e6 above the last: short blocks, rows of very different length
+    "far-outliers": (300, 72, 0.02, 100.0, 1),        # 2e7
+    "few-wanted": (256, 2, 0.02, 1.0, 1),
+    "wanted-to-the-edge": (256, 64, 0.02, 1.0, 1),    # the block ends 64 rows beyond the cut
+}
+
+
+@pytest.mark.parametrize("name", list(SCHEDULES))
+def test_schedules_of_the_block_iteration(C, name):
+    import torch
+    n, r, decay, factor, path = SCHEDULES[name]
+    sigma = np.exp(-decay * np.arange(n))
+    sigma[:4] *= factor
+    B, d = 3, n + 20
+    X = np.stack([I.make_spectrum_tokens(n, d, sigma, seed=b, dtype=I.FP32) for b in range(B)])
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    ws = C.alloc_workspace(p)
+    out = C.select(p, torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda(), workspace=ws)
+    assert C.lowrank_path(p, ws).tolist() == [path] * B
+    c = out["c"].cpu().numpy().astype(np.float64)
+    for b in range(B):
+        ref = O.select(X[b].astype(np.float64), sf[b], O.Params(preselect_m=n, rank_r=r, keep_k=n // 3))
+        # fp32 rounding of c, and the admitted residual over the relative gap exp(2 decay) - 1, twice; energies far below the
+        # largest carry its rounding
+        err = np.abs(c[b] - ref["c"]) / np.maximum(ref["c"], 1e-6 * ref["c"].max())
+        assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1), "%s image %d: %g" % (name, b, err.max())
+
+
 def test_equal_eigenvalues_at_the_cut_still_give_a_result(C):
     """Orthogonal tokens of equal length: no rank-r subspace is better than another, the split has no gap to use and the
     full solve answers.  Every energy lies between 0 and the squared length, and they sum to r of it."""
