@@ -44,7 +44,8 @@ constexpr double kPivotOnePass = 1e-10;
 constexpr double kPivotFloor = 1e-28;  // see chol_kernel
 constexpr double kLn10 = 2.302585092994046;
 
-constexpr size_t kCholLdsFixed = (size_t)(2 * NB * NBP + NB) * sizeof(double);   // plus P doubles: the diagonal of S
+constexpr size_t kCholLds = (size_t)2 * NB * NBP * sizeof(double);
+constexpr int kMaxBlocks = 64;         // block rows: P <= 4096
 
 __global__ void omega_kernel(double* __restrict__ om, int P, int n, int nP) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -172,266 +173,357 @@ __device__ __forceinline__ void rest_on(const PlanArgs& q, int b) {
   out[ST_END * q.B] = at;
 }
 
-// value of `v` in lane `l` (compile-time lane), uniform across the wave
-__device__ __forceinline__ double lane_value(double v, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-  return __hiloint2double(hi, lo);
+// value of `v` in lane k of every row of 16 lanes
+extern "C" __device__ __attribute__((const)) long long covspec_update_dpp_i64(long long, long long, int, int, int, bool) __asm("llvm.amdgcn.update.dpp.i64");
+template <int k>
+__device__ __forceinline__ double row_lane(double v) {
+  return __longlong_as_double(covspec_update_dpp_i64(0ll, __double_as_longlong(v), 0x150 + k, 0xf, 0xf, true));   // row_newbcast:k
 }
 
-// Everything a wave has written to LDS before is read back by it after (its LDS accesses complete in order; this only
-// keeps the compiler from moving one across the other).
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+// Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle: a = L L^T) and inverts the factor, by all eight waves: inv(L) goes
+// to the tiles of `inv` on and below the diagonal, the diagonal of L to dl.  The pivot of row k is floored at
+// kPivotFloor diag[k], diag the diagonal of S.  Ends with a barrier.
+// By 16 x 16 tiles.  A diagonal tile is eliminated together with a unit matrix by wave 0, lane = column of both (the four rows of 16
+// lanes do the same): step k subtracts a_ik / a_kk times row k from row i, the a_ik coming from lane k of the row in one move,
+// and leaves the inverse of the unit-diagonal factor where the unit matrix was, no exchange through LDS and no column to wait for.
+// (With the a_ik as two scalars from v_readlane and the unit matrix in other lanes a block took 13.4 us, so 11.4.)  The
+// tiles below and the rest of the block follow on the MFMA, a wave per tile, and the inverse tile by tile,
+// inv_ts = -inv_tt sum L_tu inv_us, while wave 0 eliminates the next diagonal tile: the sum comes out of the MFMA in the layout its
+// B operand wants.  
+// Pivot k and its reciprocal: an estimate good to 2^-24, r (1 + e + e^2).  The chain from one pivot to the next is what an elimination
+// takes, so the floor is decided beside it.
+template <int k>
+__device__ __forceinline__ void pivot_of(const double (&x)[16], double floor_, double rfloor, double& piv, double& rp) {
+  const double p = row_lane<k>(x[k]), f = row_lane<k>(floor_), rf = row_lane<k>(rfloor);
+  const double r = __builtin_amdgcn_rcp(p), e = fma(-p, r, 1.0), good = fma(r, fma(e, e, e), r);
+  const bool above = p > f;
+  piv = above ? p : f;
+  rp = above ? good : rf;
+}
+// Step k with its pivot and the reciprocal; the next pivot's is worked out beside the rest of the step.
+template <int k>
+__device__ __forceinline__ void eliminate_step(double (&x)[16], double (&u)[16], double floor_, double rfloor, double piv, double rp, double& mine) {
+  if constexpr (k < 16) {
+    const double row = x[k] * rp, urow = u[k] * rp;
+    double next = 1.0, next_rp = 1.0;
+    if constexpr (k < 15) {
+      const double m = row_lane<k>(x[k + 1]);
+      x[k + 1] = fma(-(m * x[k]), rp, x[k + 1]);
+      u[k + 1] = fma(-m, urow, u[k + 1]);
+      pivot_of<k + 1>(x, floor_, rfloor, next, next_rp);
+    }
+#pragma unroll
+    for (int i = k + 2; i < 16; ++i) {
+      const double m = row_lane<k>(x[i]);
+      x[i] = fma(-m, row, x[i]);
+      u[i] = fma(-m, urow, u[i]);
+    }
+    double rs = __builtin_amdgcn_rsq(piv);
+    rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
+    rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
+    u[k] *= rs;                                  // row k of inv(L_ss)
+    if ((threadIdx.x & 15) == k) mine = piv * rs;
+#pragma unroll
+    for (int i = k + 1; i < 16; ++i) asm volatile("" : "+v"(u[i]));   // or the updates of u pile up behind those of x, and spill
+    eliminate_step<k + 1>(x, u, floor_, rfloor, next, next_rp, mine);
+  }
+}
 
-// Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle: a = L L^T) and inverts the factor, in one wave: inv(L) goes
-// to `inv` (its tiles above the diagonal are zero already), the diagonal of L to dl.  The pivot of row k is floored at
-// kPivotFloor diag[k], diag the diagonal of S.
-// By 16 x 16 tiles.  A diagonal tile is eliminated together with a unit matrix, lane = column (lanes 0..15 the tile,
-// 16..31 the unit matrix): step k subtracts a_ik / a_kk times row k from row i, the a_ik being the scalars of lane k, and
-// leaves the inverse of the unit-diagonal factor in the right half, no exchange through LDS and no column to wait for.  The
-// tiles below and the rest of the block follow on the MFMA, then the inverse tile by tile, inv_ts = -inv_tt sum L_tu inv_us:
-// the sum comes out of the MFMA in the layout its B operand wants.  A column by column factorisation by one wave with the
-// inversion after it by the workgroup took 23 + 14 us of a panel, this takes 11.
-__device__ __noinline__ void factor_invert_wave(double* a, double* inv, double* dl, const double* diag) {
-  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4, c = lane & 31;
+__device__ __forceinline__ void eliminate_tile(double* a, double* inv, double* dl, const double* diag, int s) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15;
+  double x[16], u[16], mine = 0.0, piv, rp;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int hi = i > i16 ? i : i16, lo = i > i16 ? i16 : i;
+    x[i] = a[(16 * s + hi) * NBP + 16 * s + lo];
+    u[i] = i16 == i ? 1.0 : 0.0;
+  }
+  const double floor_ = fma(kPivotFloor, diag[16 * s + i16], 1e-300);
+  const double rfloor = 1.0 / floor_;
+  pivot_of<0>(x, floor_, rfloor, piv, rp);
+  eliminate_step<0>(x, u, floor_, rfloor, piv, rp, mine);
+  if (lane < 16) {
+    dl[16 * s + lane] = mine;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) inv[(16 * s + k) * NBP + 16 * s + i16] = i16 <= k ? u[k] : 0.0;
+  }
+}
+
+// inv_ts = -inv_tt sum over u of L_tu inv_us, one wave
+__device__ __forceinline__ void invert_tile(const double* a, double* inv, int t, int s) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+  f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0}, o = sum;
+#pragma unroll 1
+  for (int u = s; u < t; ++u)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      sum = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * u + 4 * j + kq], inv[(16 * u + 4 * j + kq) * NBP + 16 * s + i16], sum, 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(-inv[(16 * t + i16) * NBP + 16 * t + 4 * j + kq], sum[j], o, 0, 0, 0);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) inv[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
+}
+
+__device__ __forceinline__ void factor_invert(double* a, double* inv, double* dl, const double* diag) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
 #pragma unroll 1
   for (int s = 0; s < 4; ++s) {
-    double x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int hi = i > i16 ? i : i16, lo = i > i16 ? i16 : i;
-      const double v = a[(16 * s + hi) * NBP + 16 * s + lo];
-      x[i] = c < 16 ? v : (c - 16 == i ? 1.0 : 0.0);
-    }
-    double mine = 0.0;
-    const double floor_ = fma(kPivotFloor, diag[16 * s + i16], 1e-300);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const double piv = fmax(lane_value(x[k], k), lane_value(floor_, k));
-      double rp = __builtin_amdgcn_rcp(piv);
-      rp = fma(rp, fma(-piv, rp, 1.0), rp);
-      rp = fma(rp, fma(-piv, rp, 1.0), rp);
-      const double row = x[k] * rp;
-#pragma unroll
-      for (int i = k + 1; i < 16; ++i) x[i] = fma(-lane_value(x[i], k), row, x[i]);
-      double rs = __builtin_amdgcn_rsq(piv);
-      rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
-      rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
-      x[k] *= rs;                                  // lanes 16..31: row k of inv(L_ss)
-      if (lane == k) mine = piv * rs;
-    }
-    if (lane < 16) dl[16 * s + lane] = mine;
-    if (lane >= 16 && lane < 32) {
-#pragma unroll
-      for (int k = 0; k < 16; ++k) inv[(16 * s + k) * NBP + 16 * s + i16] = i16 <= k ? x[k] : 0.0;
-    }
-    wave_lds_fence();
-    double wf[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) wf[j] = inv[(16 * s + i16) * NBP + 16 * s + 4 * j + kq];
-#pragma unroll 1
-    for (int t = s + 1; t < 4; ++t) {              // L_ts = A_ts inv(L_ss)^T
+    if (w == 0) eliminate_tile(a, inv, dl, diag, s);
+    else if (w < s) invert_tile(a, inv, s - 1, w - 1);   // row s - 1 of the inverse, tiles 0 .. s - 2
+    __syncthreads();
+    const int t = s + w;
+    if (w > 0 && t < 4) {                          // L_ts = A_ts inv(L_ss)^T
       f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * s + 4 * j + kq], wf[j], o, 0, 0, 0);
-      wave_lds_fence();
+      for (int j = 0; j < 4; ++j)
+        o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * s + 4 * j + kq], inv[(16 * s + i16) * NBP + 16 * s + 4 * j + kq], o, 0, 0, 0);
 #pragma unroll
       for (int v = 0; v < 4; ++v) a[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
     }
-    wave_lds_fence();
-#pragma unroll 1
-    for (int t = s + 1; t < 4; ++t)                // A_tu -= L_ts L_us^T
-#pragma unroll 1
-      for (int u = s + 1; u <= t; ++u) {
-        f64x4_t o;
+    __syncthreads();
+    const int x = w < 1 ? 0 : w < 3 ? 1 : 2, y = w - x * (x + 1) / 2, r = s + 1 + x, c = s + 1 + y;
+    if (w < 6 && r < 4) {                          // A_rc -= L_rs L_cs^T
+      f64x4_t o;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = a[(16 * t + 4 * v + kq) * NBP + 16 * u + i16];
+      for (int v = 0; v < 4; ++v) o[v] = a[(16 * r + 4 * v + kq) * NBP + 16 * c + i16];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          o = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[(16 * t + i16) * NBP + 16 * s + 4 * j + kq], a[(16 * u + i16) * NBP + 16 * s + 4 * j + kq], o, 0, 0, 0);
+      for (int j = 0; j < 4; ++j)
+        o = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[(16 * r + i16) * NBP + 16 * s + 4 * j + kq], a[(16 * c + i16) * NBP + 16 * s + 4 * j + kq], o, 0, 0, 0);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) a[(16 * t + 4 * v + kq) * NBP + 16 * u + i16] = o[v];
-      }
-    wave_lds_fence();
-  }
-#pragma unroll 1
-  for (int d = 1; d < 4; ++d) {
-#pragma unroll 1
-    for (int t = d; t < 4; ++t) {
-      const int s = t - d;
-      f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0}, o = sum;
-#pragma unroll 1
-      for (int u = s; u < t; ++u)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          sum = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * u + 4 * j + kq], inv[(16 * u + 4 * j + kq) * NBP + 16 * s + i16], sum, 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(-inv[(16 * t + i16) * NBP + 16 * t + 4 * j + kq], sum[j], o, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) inv[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
+      for (int v = 0; v < 4; ++v) a[(16 * r + 4 * v + kq) * NBP + 16 * c + i16] = o[v];
     }
-    wave_lds_fence();
+    __syncthreads();
   }
+  if (w < 3) invert_tile(a, inv, 3, w);
+  __syncthreads();
+}
+
+__device__ __forceinline__ void frag_store_through(double* tile, int lane, const f64x4_t& v) {
+  double* t = tile + 2 * lane;
+  store_through(t, v[0]);
+  store_through(t + 1, v[1]);
+  store_through(t + 128, v[2]);
+  store_through(t + 129, v[3]);
+}
+
+// Progress of the factorisation of one image: written by the workgroup of a block row, polled by those of the rows after it.
+// Cleared at the start of a pass.
+struct CholFlags {
+  unsigned int ticket;          // next block row to hand to a starting workgroup
+  int failed;                   // a workgroup gave up waiting
+  int cols[kMaxBlocks];         // per block row: columns of L that are in memory
+  int done[kMaxBlocks];         // its diagonal block is factored, the inverse is in memory
+};
+
+// Waits until *flag >= value; false when the wait is over its limit or another workgroup has given up.  Everything the other
+// workgroup stored through the L2 before it raised the flag is visible behind it.  Call uniformly.
+__device__ __forceinline__ bool wait_flag(const int* flag, int value, CholFlags* f, int* s_flag, long long limit_ticks) {
+  __syncthreads();                                 // the last wait's result has been read
+  if (threadIdx.x == 0) {
+    int ok = 1;
+    const long long t0 = wall_clock64();
+    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < value) {
+      if (__hip_atomic_load(&f->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > limit_ticks) {
+        ok = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    *s_flag = ok;
+  }
+  __syncthreads();
+  return *s_flag != 0;
+}
+
+// Raises a flag when the stores of all waves have been acknowledged.  Call uniformly.
+__device__ __forceinline__ void raise_flag(int* flag, int value) {
+  __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0) lgkmcnt(0)
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Cholesky factorisation S[b] = L L^T (P x P, P % 64 == 0, [P/16][P/16] tiles in fragment order, those on and below the
-// diagonal), one 512-thread workgroup per image, right-looking over 64-wide panels:
-//   diagonal block: factored and inverted by one wave (factor_invert_wave); the inverse goes to Dinv[b][J] (its 16 tiles);
-//   panel below:    X = S[I,J] inv(L_JJ)^T on the MFMA, in place (these blocks are L[I,J]);
-//   next diagonal block: updated by all waves, into LDS; then one wave factors it while the others do the
-//   trailing part:  S[I,I'] -= X_I X_I'^T for I' <= I on the MFMA, units of 16 x 32.
+// diagonal), one 512-thread workgroup per block row of 64 and image.  The workgroup of block row i:
+//   for K < i:  T = S[i,K] - sum over K' < K of L[i,K'] L[K,K']^T;   L[i,K] = T inv(L_KK)^T, in place;   D += L[i,K] L[i,K]^T
+//   factors and inverts S[i,i] - D (factor_invert); the inverse goes to Dinv[b][i] (its tiles).
+// It waits for row K's columns before the sum and for row K's inverse before the product with it, so that the sum runs while
+// row K is being factored; rows are taken in order (a ticket per image), so that a workgroup only waits for rows that have started
+// before it, whatever else the device is doing; every wait is bounded.  What the rows hand one another is stored through the L2.
 // Every product is formed transposed, so that its result is the fragment of the tile it goes to.
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
 // A pivot is floored relative to its own row's squared length, so that a numerically rank-deficient block cannot
 // produce NaNs (the residual check afterwards decides whether the result is usable) while rows may differ in length by any
 // number of digits: after a block of products they do, by the growth of the first row over the last.
-// Bound by the chain of panels (and, from order 384 on, by one compute unit's MFMA rate in the trailing part).  One image of
-// order 192 / eight of 384 / sixty-four of 256, us: 168 / 448 / 257 with the block factored column by column, its inverse
-// formed by the workgroup and the next diagonal block updated by the wave that factors it; 76 / 220 / 115 without; 69 / 172 / 107
-// with the tiles in fragment order.  (256 registers; five are spilled, read back once a panel, outside the loops.)
-// Dynamic LDS: 2 * 64 * 65 + 64 + P doubles.
-__global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, int P, PlanArgs q) {
+// Bound by the chain of diagonal blocks: factor, flag, product with the inverse, D.  One workgroup per image, which did the
+// trailing updates itself beside the factorisation of the next block by one of its waves, took, us: one image of order 192 67,
+// eight of 384 172, sixty-four of 256 98; this 55, 108 and 80 (eleven of the eighteen a row takes are the elimination).
+// Dynamic LDS: 2 * 64 * 65 doubles.
+__global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, double* __restrict__ diag, double* __restrict__ pivots, int P,
+                                                   PlanArgs q, CholFlags* flags, int* img_status, long long limit_ticks) {
   extern __shared__ double lds[];
-  double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert_wave (tiles below the diagonal)
-  double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor
-  double* dl = lds + 2 * NB * NBP;  // [64] diagonal of the factor
-  double* diag0 = dl + NB;          // [P] the diagonal of S before any update: squared row lengths
-  const int b = blockIdx.x;
+  double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert (tiles below the diagonal)
+  double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor; before: T, then L[i,K]
+  __shared__ double dl[NB], diag0[NB];
+  __shared__ int s_flag;
+  const int b = blockIdx.x % q.B;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
   if (q.in[ST_REST * q.B + b] > (q.slots == 0 ? 1 : 0)) {      // no part in this orthonormalisation
-    if (threadIdx.x == 0) rest_on(q, b);
+    if (tid == 0 && blockIdx.x < (unsigned)q.B) rest_on(q, b);
     return;
   }
+  CholFlags* f = flags + b;
+  if (tid == 0) s_flag = (int)atomicAdd(&f->ticket, 1u);
+  __syncthreads();
+  const int row = s_flag, nblk = P / NB, per16 = P / 16;
   double* Sb = S + (long)b * P * P;
-  double pmin = 1.0;                              // smallest scaled pivot (wave 0, by lane)
-  double d0 = 0.0, dr = 0.0, dP = 0.0;           // diagonal of the factor at rows 0, r - 1 and P - 1 (wave 0)
-  const int nblk = P / NB, per16 = P / 16;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+  double* Db = Dinv + (long)b * nblk * NB * NB;
   auto tile = [&](int rt, int ct) -> double* { return Sb + ((long)rt * per16 + ct) * kFragTile; };
-  for (int k = tid; k < P; k += 512) diag0[k] = tile(k >> 4, k >> 4)[frag_at(k & 15, k & 15)];
-  for (int e = tid; e < NB * NB; e += 512) inv[(e >> 6) * NBP + (e & 63)] = 0.0;
-  for (int t = w; t < 10; t += 8) {                     // t-th tile of a block on or below its diagonal
-    const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
-    const f64x4_t c = frag_load(tile(x, y), lane);
+  if (tid < NB) diag0[tid] = tile(4 * row + (tid >> 4), 4 * row + (tid >> 4))[frag_at(tid & 15, tid & 15)];
+  // t-th tile of a block on or below its diagonal; wave w has the tiles w and, w < 2, w + 8
+  auto low = [](int t, int& x, int& y) { x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3; y = t - x * (x + 1) / 2; };
+  f64x4_t dacc[2];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v];
-  }
-  __syncthreads();
-  if (w == 0) factor_invert_wave(a, inv, dl, diag0);
-  __syncthreads();
-
-  for (int J = 0; J < nblk; ++J) {
-    const int j0 = J * NB, jt = 4 * J;
-    // here `inv` holds the inverse of the factor of diagonal block J
-    if (w == 0) {
-      const double d = dl[lane], s0 = diag0[j0 + lane];
-      if (s0 > 0.0) pmin = fmin(pmin, d * d / s0);
-      if (J == (q.r - 1) / NB) dr = __shfl(d, (q.r - 1) % NB, 64);
-      if (J == 0) d0 = __shfl(d, 0, 64);
-      if (J == nblk - 1) dP = __shfl(d, NB - 1, 64);
-    }
-    for (int t = w; t < 10; t += 8) {
-      const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
-      f64x4_t c;
+  for (int e = 0; e < 2; ++e) dacc[e] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  const int rx = w >> 1;                                        // row tile of this wave, column tiles 2 (w & 1) + 0, 1 of the sum
+  bool alive = true;
+  for (int K = 0; K < row; ++K) {
+    f64x4_t t[2];
+    const int c0 = 2 * (w & 1);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) c[v] = inv[(16 * x + i16) * NBP + 16 * y + 4 * v + kq];
-      frag_store(Dinv + ((long)b * nblk + J) * NB * NB + (4 * x + y) * kFragTile, lane, c);
-    }
-    // ---- panel: X = S[I,J] inv^T, 16-row tiles dealt to the waves; inv is lower triangular
-    const int below = (P - j0 - NB) / 16;
-    for (int t = w; t < below; t += 8) {
-      const int rt = jt + 4 + t;
-      f64x4_t f[4], out[4];
+    for (int y = 0; y < 2; ++y) t[y] = frag_load(tile(4 * row + rx, 4 * K + c0 + y), lane);
+    if (K > 0) {
+      if (!(alive = wait_flag(&f->cols[K], K, f, &s_flag, limit_ticks))) break;
+      f64x4_t acc[2];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) f[c] = frag_load(tile(rt, jt + c), lane);
+      for (int y = 0; y < 2; ++y) acc[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+      for (int k = 0; k < K; ++k) {
+        f64x4_t fa[4], fb[2][4];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        out[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+        for (int c = 0; c < 4; ++c) fa[c] = frag_load(tile(4 * row + rx, 4 * k + c), lane);
 #pragma unroll
-        for (int c = 0; c <= y; ++c)
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) fb[y][c] = frag_load(tile(4 * K + c0 + y, 4 * k + c), lane);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            out[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[(16 * y + i16) * NBP + 16 * c + 4 * v + kq], f[c][v], out[y], 0, 0, 0);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[y][c][v], fa[c][v], acc[y], 0, 0, 0);
       }
 #pragma unroll
-      for (int y = 0; y < 4; ++y) frag_store(tile(rt, jt + y), lane, out[y]);
+      for (int y = 0; y < 2; ++y) t[y] = t[y] - acc[y];
     }
-    __syncthreads();     // the panel is complete in global memory and `a`, `inv` are free
-    if (below == 0) break;
-    // ---- the next diagonal block, into LDS: its ten 16 x 16 tiles on and below the diagonal
-    for (int t = w; t < 10; t += 8) {
-      const int x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3, y = t - x * (x + 1) / 2;
-      const int rt = jt + 4 + x, ct = jt + 4 + y;
-      f64x4_t fr[4], fc[4], acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        fr[c] = frag_load(tile(rt, jt + c), lane);
-        fc[c] = frag_load(tile(ct, jt + c), lane);
-      }
-      const f64x4_t cc = frag_load(tile(rt, ct), lane);
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) inv[(16 * rx + i16) * NBP + 16 * (c0 + y) + 4 * v + kq] = t[y][v];
+    if (!(alive = wait_flag(&f->done[K], 1, f, &s_flag, limit_ticks))) break;
+    // L[i,K]: this wave's column tiles are 0 and 3, or 1 and 2 (five products each)
+    f64x4_t in[4], out[2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) in[c][v] = inv[(16 * rx + i16) * NBP + 16 * c + 4 * v + kq];
+    const int y0 = w & 1, y1 = 3 - (w & 1);
+    {
+      f64x4_t d0[2], d1[4];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) if (c <= y0) d0[c] = frag_load(Db + (long)K * NB * NB + (4 * y0 + c) * kFragTile, lane);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) if (c <= y1) d1[c] = frag_load(Db + (long)K * NB * NB + (4 * y1 + c) * kFragTile, lane);
+      out[0] = out[1] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int c = 0; c < 4; ++c)
+        if (c <= y1) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fc[c][v], fr[c][v], acc, 0, 0, 0);
+          for (int v = 0; v < 4; ++v) out[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d1[c][v], in[c][v], out[1], 0, 0, 0);
+        }
 #pragma unroll
-      for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = cc[v] - acc[v];
+      for (int c = 0; c < 2; ++c)
+        if (c <= y0) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) out[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d0[c][v], in[c][v], out[0], 0, 0, 0);
+        }
+    }
+    __syncthreads();                                            // T has been read
+    frag_store_through(tile(4 * row + rx, 4 * K + y0), lane, out[0]);
+    frag_store_through(tile(4 * row + rx, 4 * K + y1), lane, out[1]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      inv[(16 * rx + i16) * NBP + 16 * y0 + 4 * v + kq] = out[0][v];
+      inv[(16 * rx + i16) * NBP + 16 * y1 + 4 * v + kq] = out[1][v];
     }
     __syncthreads();
-    // ---- trailing update by waves 1..7, unit = 16 rows of block I x 32 columns of block I' <= I, in contiguous
-    //      ranges, so that consecutive units mostly share the columns and their fragments stay in registers (64 columns
-    //      would not fit the registers).  Wave 0 factors the next diagonal block meanwhile.
-    if (w == 0) {
-      factor_invert_wave(a, inv, dl, diag0 + j0 + NB);
-    } else {
-      const int nb = below / 4;
-      const int units = 4 * nb * (nb + 1);            // 8 * nb (nb + 1) / 2; units 0..7 are the next diagonal block
-      const int u0 = 8 + (int)((long)(units - 8) * (w - 1) / 7), u1 = 8 + (int)((long)(units - 8) * w / 7);
-      // unit u -> pair index u / 8 -> (I, I2) with I (I + 1) / 2 + I2 = pair index
-      int I = 0, I2 = 0;
-      {
-        int pi = u0 >> 3;
-        while ((I + 1) * (I + 2) / 2 <= pi) ++I;
-        I2 = pi - I * (I + 1) / 2;
-      }
-      f64x4_t fb[2][4];
-      int have = -1;
-#pragma unroll 1
-      for (int u = u0; u < u1; ++u) {
-        const int u4 = u & 3, h = (u >> 2) & 1;
-        const int rt = jt + 4 + 4 * I + u4, ct = jt + 4 + 4 * I2 + 2 * h;
-        if (ct <= rt) {                               // a diagonal block: no tile above the diagonal
-          f64x4_t fa[4], cc[2];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) fa[c] = frag_load(tile(rt, jt + c), lane);
-          if (have != ct) {
+    for (int e = 0; e < 2; ++e) {
+      const int tt = w + 8 * e;
+      if (tt < 10) {
+        int x, y;
+        low(tt, x, y);
 #pragma unroll
-            for (int y = 0; y < 2; ++y)
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) fb[y][c] = frag_load(tile(ct + y, jt + c), lane);
-            have = ct;
-          }
-          cc[0] = frag_load(tile(rt, ct), lane);
-          if (ct < rt) cc[1] = frag_load(tile(rt, ct + 1), lane);
-#pragma unroll
-          for (int y = 0; y < 2; ++y) {
-            if (ct + y <= rt) {
-              f64x4_t acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-              for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[y][c][v], fa[c][v], acc, 0, 0, 0);
-              frag_store(tile(rt, ct + y), lane, cc[y] - acc);
-            }
-          }
-        }
-        if ((u & 7) == 7) {   // next pair
-          if (I2 == I) { ++I; I2 = 0; } else ++I2;
-        }
+          for (int v = 0; v < 4; ++v)
+            dacc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[(16 * y + i16) * NBP + 16 * c + 4 * v + kq], inv[(16 * x + i16) * NBP + 16 * c + 4 * v + kq], dacc[e], 0, 0, 0);
       }
     }
-    __syncthreads();
+    raise_flag(&f->cols[row], K + 1);                           // and L[i,K] in LDS has been read
   }
-  if (w == 0) {
-    pmin = wave_min(pmin);
-    if (tid == 0) plan_block(q, b, d0, dr, dP, pmin);
+  if (alive) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int tt = w + 8 * e;
+      if (tt < 10) {
+        int x, y;
+        low(tt, x, y);
+        const f64x4_t c = frag_load(tile(4 * row + x, 4 * row + y), lane);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v] - dacc[e][v];
+      }
+    }
+    __syncthreads();
+    factor_invert(a, inv, dl, diag0);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int tt = w + 8 * e;
+      if (tt < 10) {
+        int x, y;
+        low(tt, x, y);
+        f64x4_t c;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) c[v] = inv[(16 * x + i16) * NBP + 16 * y + 4 * v + kq];
+        frag_store_through(Db + (long)row * NB * NB + (4 * x + y) * kFragTile, lane, c);
+      }
+    }
+    if (w == 0) {
+      const double d = dl[lane], s0 = diag0[lane];
+      store_through(diag + (long)b * P + row * NB + lane, d);
+      const double pm = wave_min(s0 > 0.0 ? fmin(1.0, d * d / s0) : 1.0);       // smallest scaled pivot of the rows
+      if (lane == 0) store_through(pivots + (long)b * nblk + row, pm);
+    }
+    raise_flag(&f->done[row], 1);
+  }
+  if (row != nblk - 1) {
+    if (!alive && tid == 0) __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  if (tid != 0) return;
+  if (alive) {                                                  // it has waited for all the other rows
+    double pmin = 1.0;
+    for (int k = 0; k < nblk; ++k) {
+      const double pm = pivots[(long)b * nblk + k];
+      pmin = pm < pmin || !(pm == pm) ? pm : pmin;
+    }
+    plan_block(q, b, diag[(long)b * P], diag[(long)b * P + q.r - 1], diag[(long)b * P + P - 1], pmin);
+  } else {                                                      // no factor: nothing more for the image in this pass
+    __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    rest_on(q, b);
+    q.out[ST_REST * q.B + b] = 2;
+    q.left[b] = 1;
+    if (img_status) img_status[b] = 1;
   }
 }
 
@@ -578,9 +670,11 @@ __global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, long other, c
 
 // State 0 of a pass.  First: every block is in buffer 0.  Second: images that passed the check rest; one that was left out of the
 // split goes on from its block, one that failed the check from the product with G that followed its last orthonormalisation
-// (in the buffer its rows are not in).
+// (in the buffer its rows are not in).  And the flags of the pass's factorisations.
 __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__ prev, const int* __restrict__ ok, IterPlan* __restrict__ plan,
-                                  int* __restrict__ left, int B) {
+                                  int* __restrict__ left, int B, CholFlags* __restrict__ flags, int orths) {
+  int* words = (int*)flags;
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < orths * B * (int)(sizeof(CholFlags) / sizeof(int)); k += gridDim.x * blockDim.x) words[k] = 0;
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   const bool passed = prev && ok[b] != 0, failed = prev && !passed && !left[b];
@@ -600,6 +694,7 @@ __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__
 // The slowest decay that converges is lambda_r / lambda_{P+1} = 2.8; what is slower goes to the full solve, 20 ms and more.
 constexpr int kBlocks = 3, kSlots[kBlocks] = {2, 3, 4}, kSlots2 = 3;
 constexpr int kStates = kBlocks + 2 + 3;       // the first pass's and the second's
+constexpr int kOrths = kBlocks + 1;            // of the first pass; the second has two
 
 inline size_t tail_doubles(int B, int P, int nP) {
   const size_t u = (size_t)nP * (P + 2 * (P / kSymTile)), x1 = (size_t)P * P;
@@ -618,7 +713,7 @@ size_t subspace_workspace_bytes(int B, int n, int nP, int P) {
   if (P <= 0) return split_direct(nP) ? 3 * (size_t)B * nP * nP * 8 + split_scratch_bytes(B, nP) + 256 : 0;
   const size_t blk = (size_t)B * P * nP * 8;
   return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 +
-         (size_t)B * (sizeof(IterPlan) + (kStates * ST_FIELDS + 1) * sizeof(int)) + 256 + tail_doubles(B, P, nP) * 8 + 256;
+         (size_t)B * (sizeof(IterPlan) + (kStates * ST_FIELDS + 1) * sizeof(int) + kOrths * sizeof(CholFlags) + (P + P / NB) * 8) + 512 + tail_doubles(B, P, nP) * 8 + 256;
 }
 
 // Launches of the probed shape: start block and the products of the first pass (blocks that take fewer leave the rest out).
@@ -644,7 +739,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   if (P <= 0 || P % NB != 0 || P > n || P > 4096 || nP % NB != 0) return hipErrorInvalidValue;
   {
     static PerDeviceInt raised;
-    if ((e0 = ensure_dynamic_lds(raised, (const void*)chol_kernel, kCholLdsFixed + 4096 * sizeof(double))) != hipSuccess) return e0;
+    if ((e0 = ensure_dynamic_lds(raised, (const void*)chol_kernel, kCholLds)) != hipSuccess) return e0;
   }
   char* ws = (char*)ws_;
   const size_t blk = (size_t)B * P * nP * 8;
@@ -659,7 +754,10 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   IterPlan* plan = (IterPlan*)((char*)scratch + split_scratch_bytes(B, P));                  // [B]
   int* states = (int*)(plan + B);                                                           // [kStates][ST_FIELDS][B]
   int* left = states + (size_t)kStates * ST_FIELDS * B;                                     // [B] nothing left to do in this pass
-  double* X1 = (double*)(((uintptr_t)(left + B) + 255) & ~(uintptr_t)255);                  // an iterate of the split, then
+  CholFlags* flags = (CholFlags*)(left + B);                                                // [kOrths][B]
+  double* diag = (double*)(((uintptr_t)(flags + (size_t)kOrths * B) + 255) & ~(uintptr_t)255);   // [B][P] diagonal of the factor
+  double* pivots = diag + (size_t)B * P;                                                    // [B][P / 64] smallest scaled pivots
+  double* X1 = (double*)(((uintptr_t)(pivots + (size_t)B * (P / NB)) + 255) & ~(uintptr_t)255);  // an iterate of the split, then
   double* U = X1;                                                                           // [B][P][nP] Pi Q^T,
   double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 32][nP] partial energies
   double* rnorm = cpart + (size_t)B * (P / kSymTile) * nP;                                  // [B][P][nP / 32] of the residual's row lengths
@@ -677,7 +775,6 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     return launch_gemm64_nt(g, true, true, st);
   };
   // X <- L^-1 X with X X^T = L L^T for the images that state k lets take part, and the plan of what follows
-  const size_t chol_lds = kCholLdsFixed + (size_t)P * sizeof(double);
   auto cholqr = [&](int k, int slots, bool first, int closing) -> hipError_t {
     const int rest_max = slots == 0 ? 1 : 0;
     GemmArgs g;
@@ -690,7 +787,9 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     PlanArgs q;
     q.in = state(k); q.out = state(k + 1); q.plan = plan; q.left = left; q.B = B; q.r = r; q.slots = slots; q.first = first; q.closing = closing;
-    hipLaunchKernelGGL(chol_kernel, dim3((unsigned)B), dim3(512), chol_lds, st, S, D, P, q);
+    const int orth = k < kBlocks + 2 ? k : k - (kBlocks + 2);      // of its pass
+    hipLaunchKernelGGL(chol_kernel, dim3((unsigned)(B * (P / NB))), dim3(512), kCholLds, st, S, D, diag, pivots, P, q, flags + (size_t)orth * B,
+                       img_status, barrier_limit_ticks());
     const dim3 tg((unsigned)(B * (nP / NB)));
     const double *cS = S, *cD = D;
     const int* in = state(k);
@@ -758,7 +857,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     }
     return launch_split_finish(H, Pi, rnorm, nP / kSymTile, cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, scratch, left, ok, pass_no, c, st);
   };
-  const dim3 ig((unsigned)((B + 255) / 256));
+  const dim3 ig((unsigned)((B + 3) / 4));          // 130 words of flags per image and factorisation
 
   // start block: Omega G
   hipLaunchKernelGGL(omega_kernel, dim3((unsigned)(((long)P * nP + 255) / 256)), dim3(256), 0, st, Om, P, n, nP);
@@ -771,7 +870,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
   }
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, B);
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, B, flags, kOrths);
   for (int k = 0; k < kBlocks; ++k) {
     if ((e = cholqr(k, kSlots[k], k == 0, k == kBlocks - 1 ? 1 : 0)) != hipSuccess) return e;
     if ((e = block(k + 1, kSlots[k])) != hipSuccess) return e;
@@ -780,7 +879,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   // images whose subspace is not there yet (slower decay of the spectrum than the blocks of the first pass allow for) take
   // another block; for the others every kernel of this pass returns at once
   const int k2 = kBlocks + 2;
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(k2), (const int*)state(k2 - 1), (const int*)ok, plan, left, B);
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(k2), (const int*)state(k2 - 1), (const int*)ok, plan, left, B, flags, 2);
   if ((e = cholqr(k2, kSlots2, false, 2)) != hipSuccess) return e;
   if ((e = block(k2 + 1, kSlots2)) != hipSuccess) return e;
   return finish(k2 + 1, 2);
