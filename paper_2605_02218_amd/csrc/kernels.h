@@ -159,13 +159,14 @@ hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int p
 // ---------------------------------------------------------------- split.hip
 // Projector onto the span of the r dominant eigenvectors of the symmetric positive semidefinite H[b] (P x P, pitch P,
 // P % 64 == 0, r < P), left in Y[b]; X0, X1 are scratch of the same size.  ordered: the rows of H are ordered like its
-// eigenvalues (a block iteration's); required for P > 128 (split_direct).  `scratch`: split_scratch_bytes(B, P) bytes, read
+// eigenvalues (a block iteration's); required for P > 128 (split_direct).  The eigenvalues at the cut are looked for among the
+// 64 rows around it, 128 without `ordered` and for images with again[b] != 0 (optional).  `scratch`: split_scratch_bytes(B, P) bytes, read
 // again by the two launchers below.  skip (optional, [B]): images with a non-zero entry are left out.  img_status as
 // for launch_jacobi_eigen.  Where the eigenvalues at the cut cannot be told apart the image gets no projector.
 size_t split_scratch_bytes(int B, int P);
 bool split_direct(int nP);
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
-                                 const int* skip, int* img_status, hipStream_t stream);
+                                 const int* skip, const int* again, int* img_status, hipStream_t stream);
 // Residual check and energies of a block iteration, see split.hip.  slow[b] != 0: the image was left out of the split.
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
                                int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,

@@ -4,8 +4,10 @@
 //
 // Pi = (I + sign(H - mu I)) / 2 with mu between the r-th and the (r+1)-th eigenvalue.  Two kernels:
 //   split_kernel finds mu.  The rows of H are ordered like its eigenvalues (block iteration, subspace.hip), so the
-//     two eigenvalues at the cut are those of a 128 x 128 window of rows around r: what the rows outside couple to it
-//     enters an eigenvalue squared.  The window is brought to tridiagonal form by Householder reflections with the
+//     two eigenvalues at the cut are those of a 64 x 64 window of rows around r: what the rows outside couple to it
+//     enters an eigenvalue squared (rows p and q couple by (lambda_q / lambda_p)^s after s products; 32 rows apart that shifts
+//     the eigenvalue by less than a tenth of the half gap for every decay the iteration converges on; an image that failed
+//     the check gets 128 rows).  The window is brought to tridiagonal form by Householder reflections with the
 //     matrix in the registers of one workgroup, and the two eigenvalues are cut out of it by Sturm counts, 128 trial
 //     points per pass and eigenvalue.  A matrix of order <= 128 is its own window, whatever the order of its rows.
 //   sign_kernel first lifts the cut: H is positive semidefinite and mu far below its norm, so X <- alpha X - beta X^2 with the
@@ -35,7 +37,7 @@ namespace covspec {
 
 namespace {
 
-constexpr int SN = 128;              // order of the window
+constexpr int SN = 128;              // order of the largest window
 constexpr int kMaxSignSteps = 40;    // 25 take the smallest admitted l to 1 / 2.6, a handful more to 1
 constexpr double kMinGap = 1e-10;    // smallest half gap at the cut, relative to the norm, that is iterated on
 constexpr double kLiftTo = 0.1;      // the cut is lifted until it is at least this part of the norm
@@ -49,8 +51,7 @@ struct SplitCtl {
   ImageBarrier bar;
   unsigned int ticket;                         // ctl[0] only: next (image, slot) to hand to a starting workgroup
   int state;                                   // 0: to be iterated, 1: left alone (no usable gap, or not asked for), 2: projector valid, 3: gave up
-  int first;                                   // a: rows before it are wanted as they are
-  double mu, norm, half, theta;                // cut, bound on the eigenvalues, half gap at the cut, r-th eigenvalue
+  double mu, half, theta;                      // cut, half gap at the cut, r-th eigenvalue
 };
 
 // Sums over the 16 lanes of a DPP row, the same in all of them; of X0..7 at once, so that the steps of one fill the waits of
@@ -59,16 +60,16 @@ template <int CTRL>
 __device__ __forceinline__ double row_rotated(double v) {
   return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true), __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
 }
-template <int FIRST>
-__device__ __forceinline__ void row16_sums(double (&v)[8]) {
+template <int X, int FIRST>
+__device__ __forceinline__ void row16_sums(double (&v)[X]) {
 #pragma unroll
-  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x128>(v[x]);
+  for (int x = FIRST; x < X; ++x) v[x] += row_rotated<0x128>(v[x]);
 #pragma unroll
-  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x124>(v[x]);
+  for (int x = FIRST; x < X; ++x) v[x] += row_rotated<0x124>(v[x]);
 #pragma unroll
-  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x122>(v[x]);
+  for (int x = FIRST; x < X; ++x) v[x] += row_rotated<0x122>(v[x]);
 #pragma unroll
-  for (int x = FIRST; x < 8; ++x) v[x] += row_rotated<0x121>(v[x]);
+  for (int x = FIRST; x < X; ++x) v[x] += row_rotated<0x121>(v[x]);
 }
 __device__ __forceinline__ double row16_sum(double v) {
   v += row_rotated<0x128>(v);
@@ -79,13 +80,10 @@ __device__ __forceinline__ double row16_sum(double v) {
 
 // Per row p of H: off[p] = sum over q != p of |H_pq|, and link[p] = the largest coupling to the rows from r - 32 on as a
 // multiple of what kLeadFar / kLeadNear admit; 1 where the |H_pq| / sqrt(H_pp H_qq) of the row sum to more than 1/2 (no
-// candidate for being left out of the iteration).  One wave per row, 16 rows per workgroup (the diagonal is read once for them).
-__global__ __launch_bounds__(256) void row_profile_kernel(const double* __restrict__ H, int P, long stride, int r, double* __restrict__ off,
-                                                          double* __restrict__ link, const int* __restrict__ skip) {
-  __shared__ double rd[4096];                        // reciprocal square roots of the diagonal, 0 for rows of length zero
-  const int b = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (skip && skip[b]) return;
-  const double* Hb = H + b * stride;
+// candidate for being left out of the iteration).  One wave per row, 16 rows p0 .. per workgroup (the diagonal is read once for them).
+__device__ __forceinline__ void row_profile(const double* __restrict__ Hb, int P, int r, int p0, double* __restrict__ off, double* __restrict__ link,
+                                            double* rd) {   // rd: reciprocal square roots of the diagonal, 0 for rows of length zero
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const double hrr = Hb[(long)(r - 1) * P + r - 1];
   for (int q = threadIdx.x; q < P; q += 256) {
     const double d = Hb[(long)q * P + q];
@@ -94,7 +92,7 @@ __global__ __launch_bounds__(256) void row_profile_kernel(const double* __restri
   __syncthreads();
 #pragma unroll 1
   for (int x = 0; x < 4; ++x) {
-    const int p = blockIdx.x * 16 + 4 * x + wv;      // P % 16 == 0
+    const int p = p0 + 4 * x + wv;                   // P % 16 == 0
     const double rp = rd[p];
     double s = 0.0, t = 0.0, m = 0.0;
     const double far = 1.0 / (kLeadFar * hrr), near = 1.0 / (kLeadNear * hrr);
@@ -110,37 +108,37 @@ __global__ __launch_bounds__(256) void row_profile_kernel(const double* __restri
     t = wave_sum(t);
     m = wave_max(m);
     if (lane == 0) {
-      off[(long)b * P + p] = s;
-      link[(long)b * P + p] = t < 0.5 && rp > 0.0 && m < 1.0 ? m : 1.0;      // NaN: 1
+      off[p] = s;
+      link[p] = t < 0.5 && rp > 0.0 && m < 1.0 ? m : 1.0;      // NaN: 1
     }
   }
 }
 
-// Reflections 16 a0 .. 16 a0 + 15 (to 125) of the Householder reduction of split_kernel's window.  Reflection k takes row k
+// Reflections 16 a0 .. 16 a0 + 15 (to 16 X - 3) of the Householder reduction of split_kernel's window of 16 X rows.  Reflection k takes row k
 // beyond the diagonal to one entry; rows and columns up to k are done.  a0 is a compile-time constant, so that finished
 // blocks of 16 cost nothing and the elements stay in registers.
-template <int a0>
-__device__ __forceinline__ void reflect_block(double (&A)[8][8], double* xs, double* ps, double* dv, double* es) {
+template <int X, int a0>
+__device__ __forceinline__ void reflect_block(double (&A)[X][X], double* xs, double* ps, double* dv, double* es) {
   const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
-  const int kend = a0 == 7 ? 14 : 16;           // k <= 125
+  const int kend = a0 == X - 1 ? 14 : 16;       // k <= 16 X - 3
 #pragma unroll 1
   for (int kk = 0; kk < kend; ++kk) {
     const int k = 16 * a0 + kk;
     if (ti == kk) {                             // the owners of row k
 #pragma unroll
-      for (int y = a0; y < 8; ++y) {
+      for (int y = a0; y < X; ++y) {
         const int j = tj + 16 * y;
         if (j == k) dv[k] = A[a0][y];
         xs[j] = j <= k ? 0.0 : A[a0][y];
       }
     }
     __syncthreads();
-    double v[8], vi[8], p[8], ss = 0.0;
+    double v[X], vi[X], p[X], ss = 0.0;
 #pragma unroll
-    for (int y = a0; y < 8; ++y) { v[y] = xs[tj + 16 * y]; vi[y] = xs[ti + 16 * y]; }
+    for (int y = a0; y < X; ++y) { v[y] = xs[tj + 16 * y]; vi[y] = xs[ti + 16 * y]; }
     const double alpha = xs[k + 1];
 #pragma unroll
-    for (int y = a0; y < 8; ++y) ss = fma(v[y], v[y], ss);
+    for (int y = a0; y < X; ++y) ss = fma(v[y], v[y], ss);
     ss = row16_sum(ss);
     // |row|, and 1 / (|row|^2 + |alpha| |row|): estimates refined by Newton steps.  A row that is zero needs no reflection.
     const bool zero = !(ss > 1e-280);
@@ -155,74 +153,91 @@ __device__ __forceinline__ void reflect_block(double (&A)[8][8], double* xs, dou
     const double v1 = alpha + copysign(nrm, alpha);
     if (tid == 0) es[k] = ss;
 #pragma unroll
-    for (int y = a0; y < (a0 + 2 < 8 ? a0 + 2 : 8); ++y) {
+    for (int y = a0; y < (a0 + 2 < X ? a0 + 2 : X); ++y) {
       if (tj + 16 * y == k + 1) v[y] = v1;
       if (ti + 16 * y == k + 1) vi[y] = v1;
     }
 #pragma unroll
-    for (int x = a0; x < 8; ++x) {
+    for (int x = a0; x < X; ++x) {
       p[x] = 0.0;
 #pragma unroll
-      for (int y = a0; y < 8; ++y) p[x] = fma(A[x][y], v[y], p[x]);
+      for (int y = a0; y < X; ++y) p[x] = fma(A[x][y], v[y], p[x]);
     }
-    row16_sums<a0>(p);
+    row16_sums<X, a0>(p);
 #pragma unroll
-    for (int x = a0; x < 8; ++x) p[x] = ti + 16 * x > k ? p[x] * hinv : 0.0;
+    for (int x = a0; x < X; ++x) p[x] = ti + 16 * x > k ? p[x] * hinv : 0.0;
     if (tj == 0) {
 #pragma unroll
-      for (int x = a0; x < 8; ++x) ps[ti + 16 * x] = p[x];
+      for (int x = a0; x < X; ++x) ps[ti + 16 * x] = p[x];
     }
     __syncthreads();
-    double q[8], dot = 0.0;
+    double q[X], dot = 0.0;
 #pragma unroll
-    for (int y = a0; y < 8; ++y) { q[y] = ps[tj + 16 * y]; dot = fma(q[y], v[y], dot); }
+    for (int y = a0; y < X; ++y) { q[y] = ps[tj + 16 * y]; dot = fma(q[y], v[y], dot); }
     dot = 0.5 * hinv * row16_sum(dot);
 #pragma unroll
-    for (int y = a0; y < 8; ++y) { q[y] = fma(-dot, v[y], q[y]); p[y] = fma(-dot, vi[y], p[y]); }
+    for (int y = a0; y < X; ++y) { q[y] = fma(-dot, v[y], q[y]); p[y] = fma(-dot, vi[y], p[y]); }
 #pragma unroll
-    for (int x = a0; x < 8; ++x)
+    for (int x = a0; x < X; ++x)
 #pragma unroll
-      for (int y = a0; y < 8; ++y) A[x][y] = fma(-p[x], v[y], fma(-vi[x], q[y], A[x][y]));
+      for (int y = a0; y < X; ++y) A[x][y] = fma(-p[x], v[y], fma(-vi[x], q[y], A[x][y]));
   }
 }
 
-// See the head of the file.  One workgroup of 256 threads per image: thread (ti, tj) = (tid / 16, tid % 16) holds the
-// elements (ti + 16 x, tj + 16 y) of the window, x, y < 8, in registers; a sum over a row is then 16 lanes of one DPP
-// row.  Two barriers per reflection.  Bound by instruction issue (one wave per SIMD, some 400 instructions a reflection; one
+template <int X, int a0 = 0>
+__device__ __forceinline__ void reflect_all(double (&A)[X][X], double* xs, double* ps, double* dv, double* es) {
+  if constexpr (a0 < X) {
+    reflect_block<X, a0>(A, xs, ps, dv, es);
+    reflect_all<X, a0 + 1>(A, xs, ps, dv, es);
+  }
+}
+
+// See the head of the file.  Workgroups 0 .. B - 1, of 256 threads, take an image each: thread (ti, tj) = (tid / 16, tid % 16) holds the
+// elements (ti + 16 x, tj + 16 y) of the window of N rows, x, y < N / 16, in registers; a sum over a row is then 16 lanes of one DPP
+// row.  The others profile 16 rows each (a launch of 9 us by itself).  Two barriers per reflection.  Bound by instruction issue (one wave per SIMD, some 400 instructions a reflection; one
 // barrier instead of two measured the same): 126 reflections 100 us, a Sturm pass of 128 trial points 6.6.  144 us in all with
-// library square roots and divisions and the row sums one after the other, 124 so.
-__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int r, const double* __restrict__ off,
-                                                    const double* __restrict__ link, bool ordered, SplitCtl* ctl,
-                                                    const int* __restrict__ skip) {
-  __shared__ double xs[SN], ps[SN], dv[SN], es[SN];   // es: squared off-diagonals
+// library square roots and divisions and the row sums one after the other, 124 so; a window of 64 rows 45.
+template <int N>
+__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int B, int r, double* __restrict__ off,
+                                                    double* __restrict__ link, SplitCtl* ctl, const int* __restrict__ skip,
+                                                    const int* __restrict__ again) {
+  constexpr int X = N / 16;
+  __shared__ double rd[4096];
+  if (blockIdx.x >= (unsigned)B) {
+    const int per = P / 16, at = blockIdx.x - B, img = at / per;
+    if (again && (again[img] != 0) != (N == SN)) return;
+    if (!(skip && skip[img])) row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
+    return;
+  }
+  double *xs = rd, *ps = rd + N, *dv = rd + 2 * N, *es = rd + 3 * N;   // es: squared off-diagonals
   __shared__ double red[4];
   __shared__ int cnt[2][4];
   const int b = blockIdx.x, tid = threadIdx.x, ti = tid >> 4, tj = tid & 15, lane = tid & 63, wv = tid >> 6;
   SplitCtl* cb = ctl + b;
   if (b == 0 && tid == 0) ctl[0].ticket = 0u;
+  if (again && (again[b] != 0) != (N == SN)) return;
   for (int k = tid; k < kMaxSignSteps + 2; k += 256) cb->dev[k] = 0ull;
   if (tid == 0) {
     cb->bar.arrived = 0u;
     cb->bar.failed = 0;
     cb->state = 1;
-    cb->first = 0;
   }
   if (skip && skip[b]) return;
   const double* Hb = H + b * stride;
-  const int w0 = P <= SN ? 0 : (r - SN / 2 < 0 ? 0 : (r - SN / 2 > P - SN ? P - SN : r - SN / 2));
-  const int nw = P - w0 < SN ? P - w0 : SN;
+  const int w0 = P <= N ? 0 : (r - N / 2 < 0 ? 0 : (r - N / 2 > P - N ? P - N : r - N / 2));
+  const int nw = P - w0 < N ? P - w0 : N;
 
-  double A[8][8];
+  double A[X][X];
   double big = 0.0;
 #pragma unroll
-  for (int x = 0; x < 8; ++x)
+  for (int x = 0; x < X; ++x)
 #pragma unroll
-    for (int y = 0; y < 8; ++y) {
+    for (int y = 0; y < X; ++y) {
       const int i = ti + 16 * x, j = tj + 16 * y;
       A[x][y] = (i < nw && j < nw) ? Hb[(long)(w0 + i) * P + w0 + j] : 0.0;
     }
 #pragma unroll
-  for (int x = 0; x < 8; ++x)
+  for (int x = 0; x < X; ++x)
     if (ti == tj) big = fmax(big, A[x][x]);       // H is positive semidefinite: no entry exceeds the largest diagonal entry
   big = wave_max(big);
   if (lane == 0) red[wv] = big;
@@ -231,30 +246,23 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
   if (!(big > 0.0) || !(big < 1e300)) return;     // zero matrix, infinities, NaN: left to the caller's fallback
   const double scale = 1.0 / big;
 #pragma unroll
-  for (int x = 0; x < 8; ++x)
+  for (int x = 0; x < X; ++x)
 #pragma unroll
-    for (int y = 0; y < 8; ++y) A[x][y] *= scale;
+    for (int y = 0; y < X; ++y) A[x][y] *= scale;
 
   // ---- Householder reduction
-  reflect_block<0>(A, xs, ps, dv, es);
-  reflect_block<1>(A, xs, ps, dv, es);
-  reflect_block<2>(A, xs, ps, dv, es);
-  reflect_block<3>(A, xs, ps, dv, es);
-  reflect_block<4>(A, xs, ps, dv, es);
-  reflect_block<5>(A, xs, ps, dv, es);
-  reflect_block<6>(A, xs, ps, dv, es);
-  reflect_block<7>(A, xs, ps, dv, es);
+  reflect_all<X>(A, xs, ps, dv, es);
   if (ti >= 14 && tj >= 14) {
-    if (ti == tj) dv[112 + ti] = A[7][7];
-    else if (ti == 14) es[126] = A[7][7] * A[7][7];
+    if (ti == tj) dv[N - 16 + ti] = A[X - 1][X - 1];
+    else if (ti == 14) es[N - 2] = A[X - 1][X - 1] * A[X - 1][X - 1];
   }
-  if (tid == 0) es[127] = 0.0;
+  if (tid == 0) es[N - 1] = 0.0;
   __syncthreads();
 
   // ---- the m-th and (m+1)-th largest eigenvalue of the window, m = r - w0, by Sturm counts.  Threads 0..127 narrow
   //      the interval of the first, the others that of the second, until both are known to 2 % of what separates them.
   double top = 0.0;
-  if (tid < SN) top = dv[tid] + sqrt(es[tid]) + (tid > 0 ? sqrt(es[tid - 1]) : 0.0);
+  if (tid < N) top = dv[tid] + sqrt(es[tid]) + (tid > 0 ? sqrt(es[tid - 1]) : 0.0);
   top = wave_max(top);
   if (lane == 0) red[wv] = top;
   __syncthreads();
@@ -268,15 +276,15 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
     double q = dv[0] - x;
     int neg = q < 0.0 ? 1 : 0;
 #pragma unroll 8
-    for (int i = 1; i < SN; ++i) {
+    for (int i = 1; i < N; ++i) {
       if (!(fabs(q) > 1e-200)) q = -1e-200;
       double rq = __builtin_amdgcn_rcp(q);
       rq = fma(rq, fma(-q, rq, 1.0), rq);
       q = fma(-es[i - 1], rq, dv[i] - x);
       neg += q < 0.0 ? 1 : 0;
     }
-    // SN - neg eigenvalues lie at x or above: the m-th largest does where that is at least m
-    const unsigned long long yes = __ballot(SN - neg >= m);
+    // N - neg eigenvalues lie at x or above: the m-th largest does where that is at least m
+    const unsigned long long yes = __ballot(N - neg >= m);
     if (lane == 0) cnt[pass & 1][wv] = __popcll(yes);
     __syncthreads();
 #pragma unroll
@@ -284,7 +292,7 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
       const int t = cnt[pass & 1][2 * e] + cnt[pass & 1][2 * e + 1];
       const double w = hi[e] - lo[e], l0 = lo[e], h0 = hi[e];
       if (t > 0) lo[e] = l0 + w * ((double)t * (1.0 / 129.0));
-      if (t < SN) hi[e] = fmin(h0, l0 + w * ((double)(t + 1) * (1.0 / 129.0)));
+      if (t < 128) hi[e] = fmin(h0, l0 + w * ((double)(t + 1) * (1.0 / 129.0)));
     }
     const double gap = lo[0] - hi[1];
     if (fmax(hi[0] - lo[0], hi[1] - lo[1]) <= 0.02 * gap) break;      // the same in every thread
@@ -292,34 +300,11 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
   const double gap = (lo[0] - hi[1]) * big;
   const double mu = 0.25 * (lo[0] + hi[0] + lo[1] + hi[1]) * big;
 
-  // ---- rows that are wanted as they are, and the norm of the rest
-  const double* offb = off + (long)b * P;
-  const double* linkb = link + (long)b * P;
-  int bad = 0x7fffffff;                            // first row that couples across the cut
-  for (int p = tid; p < r; p += 256)
-    if (!(linkb[p] < 1.0 && 0.5 * Hb[(long)p * P + p] > mu)) bad = p < bad ? p : bad;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { const int t = __shfl_xor(bad, o, 64); bad = t < bad ? t : bad; }
-  __syncthreads();
-  if (lane == 0) cnt[0][wv] = bad;
-  __syncthreads();
-  bad = min(min(cnt[0][0], cnt[0][1]), min(cnt[0][2], cnt[0][3]));
-  if (bad > r - 32) bad = r - 32;
-  const int a = !ordered || bad < 64 ? 0 : bad / 64 * 64;
-  double nrm = 0.0;
-  for (int p = a + tid; p < P; p += 256) nrm = fmax(nrm, fabs(Hb[(long)p * P + p]) + offb[p]);
-  nrm = wave_max(nrm);
-  if (lane == 0) red[wv] = nrm;
-  __syncthreads();
-  nrm = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
   if (tid == 0) {
-    const double half = 0.45 * gap;                // a tenth off the half gap for what the window leaves out
-    cb->first = a;
     cb->mu = mu;
-    cb->norm = nrm;
-    cb->half = half;
+    cb->half = 0.45 * gap;                           // a tenth off the half gap for what the window leaves out
     cb->theta = lo[0] * big;
-    cb->state = half > kMinGap * nrm && mu > 0.0 && nrm < 1e300 ? 0 : 1;
+    cb->state = gap > 0.0 && mu > 0.0 ? 0 : 1;
   }
 }
 
@@ -400,7 +385,8 @@ __device__ __forceinline__ void tile_of(int t, int& i, int& j) {      // t-th ti
 // Everything is kept symmetric to the bit (the elements above the diagonal are those below it): rounding that differs
 // between the two would be a skew perturbation, which the iteration magnifies by 1 / l0.
 template <bool WIDE, int KS>
-__global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : 3) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
+__global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
+                                                                 int r, const double* __restrict__ off, const double* __restrict__ link, bool ordered,
                                                                  int W, SplitCtl* ctl, int* img_status, long long limit_ticks) {
   static_assert(WIDE || KS == 1, "");
   constexpr int TT = WIDE ? 2 * ST : ST;             // tile of the workgroup
@@ -415,12 +401,36 @@ __global__ __launch_bounds__(256 * KS, KS == 2 ? 2 : 3) void sign_kernel(const d
   const int b = ticket / W, slot = ticket - b * W;
   SplitCtl* cb = ctl + b;
   if (cb->state != 0) return;                        // set before the launch; nobody of this image writes it before all have read it
-  const int a = cb->first;
+  // rows that are wanted as they are (those before a), and the norm of the rest: the same in every workgroup
+  int a = 0;
+  double norm = 0.0;
+  {
+    const double *Hd = H + b * (long)P * P, *offb = off + (long)b * P, *linkb = link + (long)b * P;
+    if (ordered) {
+      int bad = r - 32;                              // first row that couples across the cut
+      for (int p = tid; p < r - 32; p += 256 * KS)
+        if (!(linkb[p] < 1.0 && 0.5 * Hd[(long)p * P + p] > cb->mu)) bad = p < bad ? p : bad;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) { const int t = __shfl_xor(bad, o, 64); bad = t < bad ? t : bad; }
+      if (lane == 0) s_dev[wv] = (double)bad;
+      __syncthreads();
+      double m = s_dev[0];
+      for (int w = 1; w < 4 * KS; ++w) m = fmin(m, s_dev[w]);
+      a = m < 64.0 ? 0 : (int)m / 64 * 64;
+      __syncthreads();
+    }
+    for (int p = a + tid; p < P; p += 256 * KS) norm = fmax(norm, fabs(Hd[(long)p * P + p]) + offb[p]);
+    norm = wave_max(norm);
+    if (lane == 0) s_dev[wv] = norm;
+    __syncthreads();
+    for (int w = 0; w < 4 * KS; ++w) norm = fmax(norm, s_dev[w]);
+    __syncthreads();
+  }
+  if (!(cb->half > kMinGap * norm && norm < 1e300)) return;      // no usable gap: the image gets no projector
   const int ns = (P - a) / TT, ntiles = ns * (ns + 1) / 2;
   const int nact = ntiles < W ? ntiles : W;
   if (slot >= nact) return;
   // cut and half gap as parts of the norm, and the number of lifting steps that follows from them
-  const double norm = cb->norm;
   double m = cb->mu / norm, l = cb->half / norm;
   const bool lift = m < kLiftTo;
   const double mu = lift ? 0.0 : cb->mu, inv = 1.0 / (lift ? norm : fmax(norm - mu, mu));
@@ -674,7 +684,7 @@ __global__ __launch_bounds__(256) void direct_energy_kernel(const double* __rest
 size_t split_scratch_bytes(int B, int P) { return (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256 + 2 * (size_t)B * P * 8; }
 
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
-                                 const int* skip, int* img_status, hipStream_t st) {
+                                 const int* skip, const int* again, int* img_status, hipStream_t st) {
   if (P < 64 || P % 64 != 0 || P > 4096 || r < 1 || r >= P || (!ordered && P > SN)) return hipErrorInvalidValue;
   SplitCtl* ctl = (SplitCtl*)scratch;
   double* off = (double*)((char*)scratch + (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256);
@@ -684,7 +694,7 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   // Small tiles while a compute unit gets one at most; then 64 x 64 tiles, k in two halves while a compute unit gets one of those.
   // us per product: eight images of order 384 30 on small tiles (2.4 a unit), 13 on wide ones with k in halves.
   constexpr long kUnits = 256;
-  const int form = B * t32 <= kUnits ? 0 : B * t64 <= kUnits ? 1 : 2;
+  const int form = B * t32 <= kUnits && t32 <= kUnits / 4 ? 0 : B * t64 <= kUnits ? 1 : 2;     // t32: see the eighth below
   const size_t lds = (form == 1 ? 8 : 4) * ST * STP * sizeof(double);
   static PerDeviceInt raised, cache[3];
   auto kern = form == 0 ? sign_kernel<false, 1> : form == 1 ? sign_kernel<true, 2> : sign_kernel<true, 1>;
@@ -698,11 +708,11 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   const long W = tiles < most ? tiles : most;
   if (W < 1) return hipErrorInvalidValue;
   const long stride = (long)P * P;
-  hipLaunchKernelGGL(row_profile_kernel, dim3(P / 16, B), dim3(256), 0, st, H, P, stride, r, off, link, skip);
-  hipLaunchKernelGGL(split_kernel, dim3(B), dim3(256), 0, st, H, P, stride, r, (const double*)off, (const double*)link, ordered, ctl,
-                     skip);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(B * W)), dim3(form == 1 ? 512 : 256), lds, st, H, X0, Y, X1, P, (int)W, ctl, img_status,
-                     barrier_limit_ticks());
+  const dim3 sg((unsigned)(B + B * (P / 16)));
+  if (ordered) hipLaunchKernelGGL(split_kernel<64>, sg, dim3(256), 0, st, H, P, stride, B, r, off, link, ctl, skip, again);
+  if (!ordered || again) hipLaunchKernelGGL(split_kernel<SN>, sg, dim3(256), 0, st, H, P, stride, B, r, off, link, ctl, skip, again);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(B * W)), dim3(form == 1 ? 512 : 256), lds, st, H, X0, Y, X1, P, r, (const double*)off, (const double*)link,
+                     ordered, (int)W, ctl, img_status, barrier_limit_ticks());
   return hipGetLastError();
 }
 

@@ -672,7 +672,7 @@ __global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, long other, c
 // split goes on from its block, one that failed the check from the product with G that followed its last orthonormalisation
 // (in the buffer its rows are not in).  And the flags of the pass's factorisations.
 __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__ prev, const int* __restrict__ ok, IterPlan* __restrict__ plan,
-                                  int* __restrict__ left, int B, CholFlags* __restrict__ flags, int orths) {
+                                  int* __restrict__ left, int* __restrict__ failed_before, int B, CholFlags* __restrict__ flags, int orths) {
   int* words = (int*)flags;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < orths * B * (int)(sizeof(CholFlags) / sizeof(int)); k += gridDim.x * blockDim.x) words[k] = 0;
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
@@ -684,6 +684,7 @@ __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__
   out[ST_SEL * B + b] = at;
   out[ST_END * B + b] = at;
   plan[b].redo = failed;
+  failed_before[b] = failed;
   left[b] = passed;
 }
 
@@ -713,7 +714,7 @@ size_t subspace_workspace_bytes(int B, int n, int nP, int P) {
   if (P <= 0) return split_direct(nP) ? 3 * (size_t)B * nP * nP * 8 + split_scratch_bytes(B, nP) + 256 : 0;
   const size_t blk = (size_t)B * P * nP * 8;
   return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 +
-         (size_t)B * (sizeof(IterPlan) + (kStates * ST_FIELDS + 1) * sizeof(int) + kOrths * sizeof(CholFlags) + (P + P / NB) * 8) + 512 + tail_doubles(B, P, nP) * 8 + 256;
+         (size_t)B * (sizeof(IterPlan) + (kStates * ST_FIELDS + 2) * sizeof(int) + kOrths * sizeof(CholFlags) + (P + P / NB) * 8) + 512 + tail_doubles(B, P, nP) * 8 + 256;
 }
 
 // Launches of the probed shape: start block and the products of the first pass (blocks that take fewer leave the rest out).
@@ -732,7 +733,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     double* X0 = (double*)ws_;
     double *Y = X0 + sq, *X1 = Y + sq;
     void* scratch = (void*)(((uintptr_t)(X1 + sq) + 255) & ~(uintptr_t)255);
-    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, img_status, st);
+    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, nullptr, img_status, st);
     return ed != hipSuccess ? ed : launch_direct_energy(G, Y, B, n, nP, r, scratch, ok, c, st);
   }
   hipError_t e0;
@@ -754,7 +755,8 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   IterPlan* plan = (IterPlan*)((char*)scratch + split_scratch_bytes(B, P));                  // [B]
   int* states = (int*)(plan + B);                                                           // [kStates][ST_FIELDS][B]
   int* left = states + (size_t)kStates * ST_FIELDS * B;                                     // [B] nothing left to do in this pass
-  CholFlags* flags = (CholFlags*)(left + B);                                                // [kOrths][B]
+  int* failed = left + B;                                                                   // [B] failed the check of the first pass
+  CholFlags* flags = (CholFlags*)(failed + B);                                              // [kOrths][B]
   double* diag = (double*)(((uintptr_t)(flags + (size_t)kOrths * B) + 255) & ~(uintptr_t)255);   // [B][P] diagonal of the factor
   double* pivots = diag + (size_t)B * P;                                                    // [B][P / 64] smallest scaled pivots
   double* X1 = (double*)(((uintptr_t)(pivots + (size_t)B * (P / NB)) + 255) & ~(uintptr_t)255);  // an iterate of the split, then
@@ -836,7 +838,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, X1, scratch, left, img_status, st)) != hipSuccess) return e;
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, X1, scratch, left, pass_no == 1 ? nullptr : failed, img_status, st)) != hipSuccess) return e;
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;
@@ -870,7 +872,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
   }
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, B, flags, kOrths);
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, failed, B, flags, kOrths);
   for (int k = 0; k < kBlocks; ++k) {
     if ((e = cholqr(k, kSlots[k], k == 0, k == kBlocks - 1 ? 1 : 0)) != hipSuccess) return e;
     if ((e = block(k + 1, kSlots[k])) != hipSuccess) return e;
@@ -879,7 +881,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   // images whose subspace is not there yet (slower decay of the spectrum than the blocks of the first pass allow for) take
   // another block; for the others every kernel of this pass returns at once
   const int k2 = kBlocks + 2;
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(k2), (const int*)state(k2 - 1), (const int*)ok, plan, left, B, flags, 2);
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(k2), (const int*)state(k2 - 1), (const int*)ok, plan, left, failed, B, flags, 2);
   if ((e = cholqr(k2, kSlots2, false, 2)) != hipSuccess) return e;
   if ((e = block(k2 + 1, kSlots2)) != hipSuccess) return e;
   return finish(k2 + 1, 2);
