@@ -201,8 +201,7 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
     }
     n_probe, pr, pc, pk = C.probe_launches(p)
     if n_probe > 0 and probe_ms > 0:
-        product = "gemm64_small_kernel" if tiles(pr, pc, 32, B) <= 384 and pk % 64 == 0 else "gemm64_dma_kernel"
-        cand["lowrank_product"] = (product, "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
+        cand["lowrank_product"] = ("gemm64_dma_kernel", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
                                    2.0 * B * pr * pc * pk / 1e12, n_probe, probe_ms)
     elif p_modes[1] == 1:
         cand["lowrank"] = ("greedy_kernel", "alu", PEAK["valu_fp64_TFLOPs"], "TFLOP/s", 1.0 * B * M * k * k / 1e12, 1,

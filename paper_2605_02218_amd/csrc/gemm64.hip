@@ -10,8 +10,8 @@
 // Four kernels:
 //   gemm64_kernel        any of the storage types, row lists, any K and alignment: 64 x 64 tiles, operands converted to fp64 on
 //                        their way through registers into LDS.
-//   gemm64_dma_kernel    fp64 x fp64 of many tiles (the block iteration on large or many images): direct-to-LDS loads.
-//   gemm64_small_kernel  few tiles, fp64 or fp32, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
+//   gemm64_dma_kernel    fp64 x fp64 (the block iteration): direct-to-LDS loads, tiles of 64 x 64 to 32 x 32.
+//   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
 //   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
 // gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
 // for <2,2>), k-tile 16; the loads of k-tile t+1 are issued before the MFMAs of tile t and parked in registers, LDS is double
@@ -28,19 +28,12 @@ namespace covspec {
 namespace {
 
 constexpr int TK = 16, PITCH = TK + 1;
-// 32 x 32 tiles up to which gemm64_small_kernel is taken: beyond it the device is no longer short of workgroups and the
-// doubled operand traffic decides.  us, gemm64_dma_kernel / here: 240 tiles of K = 320 15.3 / 8.6, 320 of K = 640 26 / 22, 360 of
-// K = 320 15.5 / 13.6, 384 of K = 192 10.9 / 12.4; 432 of K = 1152 44 / 38, 480 of K = 640 27 / 23, 640 of K = 640 27 / 31, 720 of
-// K = 320 15.9 / 18.8, 864 of K = 1152 45 / 69: the curves cross between 380 and 600 tiles, later for the longer k.
-constexpr long kSmallTiles = 384;
-// The same for operands that are not both fp64, in 64 x 64 tiles: up to one workgroup per compute unit of the alternative, the
-// register-staged kernel with one wave per SIMD.  us, gemm64_kernel / here: row norms of 144 tiles (576 x 1024 x 1024) 136 / 34, 256
+// 64 x 64 tiles up to which gemm64_small_kernel is taken for operands that are not both fp64: up to one workgroup per compute unit
+// of the alternative, the register-staged kernel with one wave per SIMD.  us, gemm64_kernel / here: row norms of 144 tiles (576 x 1024 x 1024) 136 / 34, 256
 // (2000 x 512 x 512) 64 / 30, 288 (1100 x 1024 x 1024) 148 / 52, 864 of K = 256 57 / 57, 1008 59 / 68: the small tiles would still
 // win up to some 800; the line is where the sums' order was drawn.
 constexpr long kSmallTiles64 = 256;
-// 64 x 64 tiles up to which k is split over two groups of waves: one workgroup of eight waves per compute unit, where one of
-// four leaves each SIMD a single wave (75 -> 45 us, see the kernel); with more tiles than that two workgroups share a unit.
-constexpr long kFewTiles = 256;
+constexpr int kUnits = 256;      // compute units
 
 __device__ __forceinline__ double as_f64(double v) { return v; }
 __device__ __forceinline__ double as_f64(float v) { return (double)v; }
@@ -214,16 +207,17 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
   }
 }
 
-// ---- fp64 x fp64, both K-contiguous, fp64 result (the products of the low-rank stage).  64 x 64 tile, 2 x 2 waves of
-// 32 x 32, k-tile 16, operand tiles loaded straight into LDS as whole 128-byte rows (a ring of four 16 KB stages, three
-// k-tiles in flight, one barrier per k-tile), rows swizzled by their low three bits so that the 16-byte fragment reads
-// (two k values per lane: any order of k serves as long as both operands have it) are conflict-free, the fragments of the
-// next half k-tile read while the current one is multiplied.  KS = 2: a second group of four waves takes the other half of
-// k in a ring of its own and the halves are added at the end, for problems with no more tiles than compute units, where
-// one wave per SIMD cannot hide its own waits.  The register-staged kernel above held one k-tile in flight and waited for
-// it with one wave per SIMD (its MFMAs were 44 % of its cycles).  Register-staged against this, us: 192 x 1280 x 1280, batch 4 (KS = 2) 75 -> 45;
-// 384 x 1152 x 1152, batch 8 303 -> 190; 256 x 640 x 640, batch 64 260 -> 220 (61 TFLOP/s; a loop of nothing but these
-// MFMAs reaches 67.6).
+// ---- fp64 x fp64, both K-contiguous, fp64 result (the products of the low-rank stage).  TM x TN tile, 2 x 2 waves, k-tile 16,
+// operand tiles loaded straight into LDS as whole 128-byte rows (a ring of four stages, three k-tiles in flight, one barrier per
+// k-tile), rows swizzled by their low three bits so that the 16-byte fragment reads (two k values per lane: any order of k serves as
+// long as both operands have it) are conflict-free, the fragments of the next half k-tile read while the current one is
+// multiplied.  KS = 2: a second group of four waves takes the other half of k in a ring of its own and the halves are added at the
+// end, for problems with no more tiles than compute units, where one wave per SIMD cannot hide its own waits.
+// Bound by the fp64 MFMA: a 64 x 64 tile keeps a compute unit busy for K / 32 us, so what decides is how evenly the tiles go into the
+// compute units (launch_plain_f64).  us, tiles of 64 x 64 / 64 x 32 / 32 x 32, and the time at the rate of a loop of nothing but
+// these MFMAs (67.6 TFLOP/s): 192 x 1664 x 1664, batch 4 114 / 91 / 88 (63); 384 x 1152 x 1152, batch 8 159 / 149 / 166 (121);
+// 256 x 640 x 640, batch 64 235 / 260 / 277 (199); 192 x 1280 x 1280, batch 4 50 / 50 / 54 (37).
+// A symmetric product (lower_only, frag; TM = TN) has a workgroup for each tile on and below its diagonal only.
 // Requires K % 16 == 0, even pitches, 16-byte aligned bases.  Rows beyond M / N are clamped when loading.
 // A Chebyshev step (GemmArgs::cheb) is scale * (A B + start): the accumulators begin with the terms that are not the product,
 // whose loads are over before the first operands have landed (read behind the product they cost 30 of 260 us, see below).
@@ -233,62 +227,74 @@ __device__ __forceinline__ double cheb_start(const GemmArgs& g, const double* A,
   return -rt * (g.cheb_step == 0 ? a : fma(0.5, C[(long)r * g.ldc + c], a));
 }
 
-template <int KS>
+template <int KS, int TM, int TN>
 __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  constexpr int NST = 4, STAGE = 2 * 64 * 128;      // bytes: A tile then B tile
+  constexpr int NST = 4, STAGE = (TM + TN) * 128;   // bytes: A tile then B tile
+  constexpr int MI = TM / 32, NJ = TN / 32;         // 16 x 16 tiles of a wave, and its loads per operand and stage
   extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
   const int tid = threadIdx.x & 255, grp = threadIdx.x >> 8, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, i16 = lane & 15, kq = lane >> 4;
-  const int per = tiles_m * tiles_n;
+  const bool triangle = TM == TN && (g.lower_only || g.frag);
+  const int per = triangle ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int gid = regroup_xcd(blockIdx.x, gridDim.x);
-  const int b = gid / per, pidx = gid - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
+  const int b = gid / per, pidx = gid - b * per;
   if (g.skip && g.skip[b] > g.skip_if) return;            // uniform per workgroup
-  if (g.lower_only && tn > tm) return;                    // tile above the diagonal
-  if (g.frag && tn < tm) return;                          // see the store
-  const int row0 = tm * 64, col0 = tn * 64;
+  int tm, tn;
+  if (triangle) {                                         // tile (x, y <= x) of the triangle; frag: its mirror image, see the store
+    int x = (int)((sqrtf(8.0f * (float)pidx + 1.0f) - 1.0f) * 0.5f);
+    while (x * (x + 1) / 2 > pidx) --x;
+    while ((x + 1) * (x + 2) / 2 <= pidx) ++x;
+    const int y = pidx - x * (x + 1) / 2;
+    tm = g.frag ? y : x;
+    tn = g.frag ? x : y;
+  } else {
+    tm = pidx / tiles_n;
+    tn = pidx - tm * tiles_n;
+  }
+  const int row0 = tm * TM, col0 = tn * TN;
   const bool moved = g.sel && g.sel[b];
   const double* A = (const double*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
   const double* B = (const double*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
   const int nk = g.K >> 4, nk0 = (nk + KS - 1) / KS, kt0 = grp * nk0;
   const int mine = nk - kt0 < nk0 ? (nk - kt0 > 0 ? nk - kt0 : 0) : nk0;      // k-tiles of this group
 
-  // wave w issues loads j = 0, 1 per operand and stage; load j fills tile rows 8 (2w + j) .. +7: lane l -> row + l / 8,
+  // wave w issues MI loads of A and NJ of B per stage; load j of A fills tile rows 8 (MI w + j) .. +7: lane l -> row + l / 8,
   // 16-byte slot l % 8, which holds the row's piece (l % 8) ^ (row % 8)
-  const double* ga[2];
-  const double* gb[2];
+  const double* ga[MI];
+  const double* gb[NJ];
+  const int lr = lane >> 3, lc = 2 * ((lane & 7) ^ (lane >> 3));
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int r = 8 * (2 * wave + j) + (lane >> 3), c = (lane & 7) ^ (lane >> 3);
-    ga[j] = A + (long)min(row0 + r, g.M - 1) * g.lda + 2 * c + 16 * (long)kt0;
-    gb[j] = B + (long)min(col0 + r, g.N - 1) * g.ldb + 2 * c + 16 * (long)kt0;
-  }
+  for (int j = 0; j < MI; ++j) ga[j] = A + (long)min(row0 + 8 * (MI * wave + j) + lr, g.M - 1) * g.lda + lc + 16 * (long)kt0;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) gb[j] = B + (long)min(col0 + 8 * (NJ * wave + j) + lr, g.N - 1) * g.ldb + lc + 16 * (long)kt0;
   unsigned char* base = ring + grp * (NST * STAGE);
   const int last = mine > 0 ? mine - 1 : 0;
   auto issue = [&](int kt) {
     // past the end: the last k-tile again (a group without any: the one before it), into a stage that is never read
     const long at = 16 * (long)(mine == 0 ? -1 : kt < last ? kt : last);
-    unsigned char* sa = base + (kt & (NST - 1)) * STAGE + wave * 2048;
-    unsigned char* sb = sa + 64 * 128;
+    unsigned char* sa = base + (kt & (NST - 1)) * STAGE + wave * (MI * 1024);
+    unsigned char* sb = base + (kt & (NST - 1)) * STAGE + TM * 128 + wave * (NJ * 1024);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < MI; ++j)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[j] + at),
                                        (__attribute__((address_space(3))) void*)(sa + j * 1024), 16, 0, 0);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[j] + at),
                                        (__attribute__((address_space(3))) void*)(sb + j * 1024), 16, 0, 0);
-    }
   };
   double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
   const double t = g.cheb ? g.cheb[(long)b * g.cheb_stride] : 0.0, scale = cheb_scale(g, t), rt = 1.0 / t;
-  f64x4_t acc[2][2];
+  f64x4_t acc[MI][NJ];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
       if (t != 0.0 && grp == 0) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          acc[i][j][v] = cheb_start(g, A, C, rt, min(row0 + wm * 32 + i * 16 + 4 * v + kq, g.M - 1), min(col0 + wn * 32 + j * 16 + i16, g.N - 1));
+          acc[i][j][v] = cheb_start(g, A, C, rt, min(row0 + wm * (16 * MI) + i * 16 + 4 * v + kq, g.M - 1), min(col0 + wn * (16 * NJ) + j * 16 + i16, g.N - 1));
       }
     }
   // fragment of row R, half h: piece kq + 4h, i.e. k = 2 (kq + 4h) + {0, 1}; R % 8 == i16 % 8 for every fragment row
@@ -296,37 +302,36 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int piece = ((kq + 4 * h) ^ (i16 & 7)) * 16;
-    offA[h] = (wm * 32 + i16) * 128 + piece;
-    offB[h] = 64 * 128 + (wn * 32 + i16) * 128 + piece;
+    offA[h] = (wm * (16 * MI) + i16) * 128 + piece;
+    offB[h] = TM * 128 + (wn * (16 * NJ) + i16) * 128 + piece;
   }
-  auto frags = [&](int kt, int h, f64x2_t (&fa)[2], f64x2_t (&fb)[2]) {
+  auto frags = [&](int kt, int h, f64x2_t (&fa)[MI], f64x2_t (&fb)[NJ]) {
     const unsigned char* st = base + (kt & (NST - 1)) * STAGE;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      fa[i] = *(const f64x2_t*)(st + offA[h] + i * 2048);
-      fb[i] = *(const f64x2_t*)(st + offB[h] + i * 2048);
-    }
+    for (int i = 0; i < MI; ++i) fa[i] = *(const f64x2_t*)(st + offA[h] + i * 2048);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) fb[j] = *(const f64x2_t*)(st + offB[h] + j * 2048);
   };
-  auto mma = [&](const f64x2_t (&fa)[2], const f64x2_t (&fb)[2]) {
+  auto mma = [&](const f64x2_t (&fa)[MI], const f64x2_t (&fb)[NJ]) {
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
   };
-  // Per k-tile: wait until the next one has landed (only the four loads of the one after it may be outstanding), barrier,
+  // Per k-tile: wait until the next one has landed (only the loads of the one after it may be outstanding), barrier,
   // start the loads three ahead into the stage that held the previous one (every wave's reads of it are complete before it
   // arrives at the barrier).
-  f64x2_t a0[2], b0[2], a1[2], b1[2];
+  f64x2_t a0[MI], b0[NJ], a1[MI], b1[NJ];
   issue(0);
   issue(1);
   issue(2);
-  __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8) lgkmcnt(0): k-tile 0 has landed
+  __builtin_amdgcn_s_waitcnt(0x0070 + 2 * (MI + NJ));   // vmcnt: the loads of two stages, lgkmcnt(0): k-tile 0 has landed
   __builtin_amdgcn_s_barrier();
   frags(0, 0, a0, b0);
   for (int kt = 0; kt < nk0; ++kt) {
-    __builtin_amdgcn_s_waitcnt(0x0074);   // vmcnt(4) lgkmcnt(0)
+    __builtin_amdgcn_s_waitcnt(0x0070 + MI + NJ);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     frags(kt, 1, a1, b1);
@@ -339,40 +344,40 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   }
   __builtin_amdgcn_s_waitcnt(0x0070);
 
-  if (KS == 2) {
-    // each group hands half of its tile (i = 1 - grp) to the other and stores the rest
+  if constexpr (KS == 2) {                                // the second group's sums come second
     __syncthreads();
-    double* x = (double*)ring + grp * 2048;
+    double* x = (double*)ring + wave * (MI * NJ * 256) + lane;
+    if (grp == 1) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[((j * 4 + v) * 4 + wave) * 64 + lane] = grp ? acc[0][j][v] : acc[1][j][v];
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) x[((i * NJ + j) * 4 + v) * 64] = acc[i][j][v];
+    }
     __syncthreads();
-    const double* y = (const double*)ring + (1 - grp) * 2048;
+    if (grp == 1) return;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const double o = y[((j * 4 + v) * 4 + wave) * 64 + lane];
-        if (grp) acc[1][j][v] = o + acc[1][j][v];       // the first half's sum comes first in both groups
-        else acc[0][j][v] = acc[0][j][v] + o;
-      }
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][j][v] += x[((i * NJ + j) * 4 + v) * 64];
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    if (KS == 2 && i != grp) continue;
+  for (int i = 0; i < MI; ++i) {
     if (g.frag) {
       // the product is symmetric: what this lane holds of tile (row, column) is the fragment of tile (column, row)
-      const int per16 = g.N >> 4, ct = (row0 + wm * 32) / 16 + i;
+      const int per16 = g.N >> 4, ct = (row0 + wm * (16 * MI)) / 16 + i;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) frag_store(C + ((long)((col0 + wn * 32) / 16 + j) * per16 + ct) * kFragTile, lane, acc[i][j]);
+      for (int j = 0; j < NJ; ++j) frag_store(C + ((long)((col0 + wn * (16 * NJ)) / 16 + j) * per16 + ct) * kFragTile, lane, acc[i][j]);
       continue;
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int r = row0 + wm * 32 + i * 16 + 4 * v + kq, c = col0 + wn * 32 + j * 16 + i16;
+        const int r = row0 + wm * (16 * MI) + i * 16 + 4 * v + kq, c = col0 + wn * (16 * NJ) + j * 16 + i16;
         if (r < g.M && c < g.N) {
           C[(long)r * g.ldc + c] = scale * acc[i][j][v];
           if (g.mirror && tn != tm) C[(long)c * g.ldc + r] = acc[i][j][v];
@@ -390,12 +395,11 @@ __device__ __forceinline__ f64x4_t load4_f64(const float* p) {
   return (f64x4_t){(double)v[0], (double)v[1], (double)v[2], (double)v[3]};
 }
 
-// The same for problems of few tiles, fp64 or fp32 operands with optional row lists: 32 x 32 tile, the four waves take a
+// Problems of few tiles with an fp32 operand and optional row lists: 32 x 32 tile, the four waves take a
 // quarter of k each, operands straight from global memory (rows in pieces of 16 elements, three such groups in flight), the
 // partial tiles added through LDS in a fixed order.  Twice the operand traffic of a 64 x 64 tile but four times the
-// workgroups and a sixteenth of the dependent MFMAs.  us, 64 x 64 register-staged -> here: fp64 192 x 320 x 320 20.2 -> 10.6;
-// fp32 16 x 1024 x 1024 106 -> 15.7, 576 x 16 x 1024 96 -> 15.4, 128 x 128 x 1024 with row lists 138 -> 16.6, 576 x 1024 x 1024
-// row norms 145 -> 34.  Requires K % 64 == 0.
+// workgroups and a sixteenth of the dependent MFMAs.  us, 64 x 64 register-staged -> here: 16 x 1024 x 1024 106 -> 15.7,
+// 576 x 16 x 1024 96 -> 15.4, 128 x 128 x 1024 with row lists 138 -> 16.6, 576 x 1024 x 1024 row norms 145 -> 34.  Requires K % 64 == 0.
 // EPI: EPI_STORE_F64, or EPI_ROWNORM2 with one partial per 32 columns.
 template <typename TA, typename TB, int EPI>
 __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles_m, int tiles_n) {
@@ -405,11 +409,9 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
   const int b = blockIdx.x / per, pidx = blockIdx.x - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
   if (g.skip && g.skip[b] > g.skip_if) return;
   if (g.lower_only && tn > tm) return;
-  if (g.frag && tn < tm) return;
   const int row0 = tm * 32, col0 = tn * 32, kn = g.K >> 2;
-  const bool moved = g.sel && g.sel[b];
-  const TA* Ab = (const TA*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
-  const TB* Bb = (const TB*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
+  const TA* Ab = (const TA*)g.A + (long)b * g.strideA;
+  const TB* Bb = (const TB*)g.B + (long)b * g.strideB;
   const TA* ar[2];
   const TB* br[2];
 #pragma unroll
@@ -421,26 +423,12 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     br[x] = Bb + rb * g.ldb + w * kn + 4 * kq;
   }
   constexpr int DEPTH = 3;
-  double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
+  double* C = (double*)g.C + (long)b * g.strideC;
   f64x4_t acc[2][2], fa[DEPTH][2], fb[DEPTH][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 2; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-  double scale = 1.0;
-  double start[4] = {0.0, 0.0, 0.0, 0.0};                 // of the elements this thread stores
-  if constexpr (std::is_same<TA, double>::value) {
-    if (g.cheb) {
-      const double t = g.cheb[(long)b * g.cheb_stride];
-      scale = cheb_scale(g, t);
-      if (t != 0.0) {
-        const double rt = 1.0 / t;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          start[q] = cheb_start(g, Ab, C, rt, min(row0 + ((tid + 256 * q) >> 5), g.M - 1), min(col0 + ((tid + 256 * q) & 31), g.N - 1));
-      }
-    }
-  }
   const int nc = kn >> 4;
   auto load = [&](int s, int c) {
     if (c < nc) {
@@ -491,18 +479,10 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     if ((tid & 7) == 0 && row0 + i < g.M) C[(long)(row0 + i) * g.ldc + tn] = s;
     return;
   }
-  if (g.frag) {                                           // wave w: 16 x 16 tile (w / 2, w % 2) of the transposed product
-    const int sr = w >> 1, sc = w & 1;
-    f64x4_t v;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = sum(16 * sc + 4 * q + kq, 16 * sr + i16);
-    frag_store(C + ((long)(col0 / 16 + sr) * (g.N >> 4) + row0 / 16 + sc) * kFragTile, lane, v);
-    return;
-  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int e = tid + 256 * q, i = e >> 5, j = e & 31;
-    if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = scale * (sum(i, j) + start[q]);
+    if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = sum(i, j);
     if (g.mirror && tn != tm && row0 + j < g.M && col0 + i < g.N) C[(long)(col0 + i) * g.ldc + row0 + j] = sum(j, i);
   }
 }
@@ -619,23 +599,39 @@ hipError_t launch_small(const GemmArgs& g, hipStream_t stream) {
 
 inline long tiles64(const GemmArgs& g) { return (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch; }
 
-hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
-  if (g.frag && (g.M != g.N || g.N % 64 != 0)) return hipErrorInvalidValue;
-  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, t32 = (g.lower_only || g.frag ? n32 * (n32 + 1) / 2 : m32 * n32) * g.batch;
-  if (t32 <= kSmallTiles && small_fits(g)) return launch_small<double, double, EPI_STORE_F64>(g, stream);
-  const long m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, blocks = m64 * n64 * g.batch;
-  const long t64 = (g.lower_only || g.frag ? n64 * (n64 + 1) / 2 : m64 * n64) * g.batch;
+template <int KS, int TM, int TN>
+hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
+  const long tm = (g.M + TM - 1) / TM, tn = (g.N + TN - 1) / TN;
+  const bool triangle = g.lower_only || g.frag;
+  if (triangle && TM != TN) return hipErrorInvalidValue;
+  const long blocks = (triangle ? tm * (tm + 1) / 2 : tm * tn) * g.batch;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  constexpr size_t kRing = 4 * 2 * 64 * 128;
-  if (t64 <= kFewTiles && g.K >= 32) {
+  constexpr size_t kRing = (size_t)KS * 4 * (TM + TN) * 128;
+  if (kRing > 64 * 1024) {
     static PerDeviceInt raised;
-    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<2>, 2 * kRing);
+    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<KS, TM, TN>, kRing);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gemm64_dma_kernel<2>, dim3((unsigned)blocks), dim3(512), 2 * kRing, stream, g, (int)m64, (int)n64);
-  } else {
-    hipLaunchKernelGGL(gemm64_dma_kernel<1>, dim3((unsigned)blocks), dim3(256), kRing, stream, g, (int)m64, (int)n64);
   }
+  hipLaunchKernelGGL((gemm64_dma_kernel<KS, TM, TN>), dim3((unsigned)blocks), dim3(256 * KS), kRing, stream, g, (int)tm, (int)tn);
   return hipGetLastError();
+}
+
+// The tile whose fullest compute unit has the least to do: rounds of tiles over the compute units, times the tile's area, times what a
+// unit of area costs more in smaller tiles (operand reads per MFMA; 1.06 and 1.2 at equal areas, measured with many tiles).  The
+// figures at the kernel and, us, 64 x 64 / 64 x 32 / 32 x 32: 320 x 1024 x 1024, batch 4 73 / 58 / 56; 256 x 832 x 832, batch 16
+// 117 / 109 / 110; 384 x 1280 x 1280, batch 12 260 / 270 / 300; 256 x 1024 x 1024, batch 2 39 / 25 / 26; 192 x 384 x 384, batch 3
+// 17 / 11 / 8; symmetric products 192 x 192 x 1664, batch 4 59 / - / 24; 256 x 256 x 640, batch 64 88 / - / 77.
+hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
+  const bool triangle = g.lower_only || g.frag;
+  if ((triangle && g.M != g.N) || (g.frag && g.N % 64 != 0)) return hipErrorInvalidValue;
+  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64;
+  const auto fullest = [](long tiles) { return (double)((tiles + kUnits - 1) / kUnits); };
+  const long t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
+  const double c64 = 4.0 * fullest((triangle ? m64 * (m64 + 1) / 2 : m64 * n64) * g.batch);
+  const double c32 = 1.2 * fullest(t32), c48 = triangle ? c32 : 2.0 * 1.06 * fullest(m64 * n32 * g.batch);
+  if (c64 <= c32 && c64 <= c48) return launch_dma<1, 64, 64>(g, stream);
+  if (c48 < c32) return launch_dma<1, 64, 32>(g, stream);
+  return t32 <= kUnits && g.K >= 32 ? launch_dma<2, 32, 32>(g, stream) : launch_dma<1, 32, 32>(g, stream);
 }
 
 // Products the two kernels above take.

@@ -26,8 +26,9 @@ CASES = {
     "direct-rank1": (2, 128, 160, 1, 0.05, 3),
     "full-solve": (1, 129, 160, 64, 0.05, 0),        # too large for a direct split, block would be most of the matrix
     "smallest-block": (1, 171, 192, 3, 0.05, 1),     # block of 128 of 171: the whole block is the window
-    "many-rows": (4, 900, 960, 40, 0.05, 1),         # products on 64 x 64 tiles with k in two halves
-    "few-images": (6, 700, 720, 130, 0.02, 1),       # more such tiles than compute units
+    "many-rows": (4, 900, 960, 40, 0.05, 1),         # products on 64 x 32 tiles
+    "few-images": (6, 700, 720, 130, 0.02, 1),       # on 32 x 32 tiles
+    "one-round": (12, 640, 660, 60, 0.05, 1),        # on 64 x 64 tiles
     "steep": (2, 400, 420, 180, 0.04, 0),            # the block's last rows drown in rounding: no split passes the check
     "seven-blocks": (1, 700, 720, 330, 0.01, 1),     # block of 448: the substitution goes through memory
     "five-blocks": (1, 500, 520, 230, 0.015, 1),
