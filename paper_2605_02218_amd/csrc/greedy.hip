@@ -257,40 +257,142 @@ __global__ __launch_bounds__(TPB) void greedy_single_kernel(const double* __rest
 // same decisions: nothing is exchanged), then the workgroups meet at the image's barrier, each brings its own
 // 16-row bands of R up to date, and they meet again before the next block reads rows of R: two barriers per
 // block instead of one per pick, and the device's bandwidth on the update instead of one workgroup's.
-// Dynamic LDS: BK * nP doubles; workgroups take (image, slot) from the ticket counter.
-// Maximum of one 64-bit key per lane over the wave with DPP moves (no LDS round trips): quads, then shifts by 4 and
+// Picks are made in runs.  A residual only ever shrinks, so while the largest residual of the CAND largest ones at the start of the
+// run stays above all the others as they were then, the others need not be looked at: one wave makes the picks from the
+// CAND x CAND submatrix of R in LDS, no barrier and no row of R to wait for, and the columns of the run are formed for all rows
+// behind it, the rows of R requested together.  A run ends when a residual left out could be the largest (8 picks on the
+// average with 64 candidates on the token matrices of the workloads, 5 to 10 over their images), at the end of a block, and
+// before a residual that is not finite.
+// Candidates are the CAND largest of the eight largest of each wave; ordered by (residual rounded to fp32, lower row), so that the
+// first pick of a run is the largest of all whatever ties there are.
+// Bound by the chain of picks: us for 463 picks of 926 rows, six images, with all rows in every step (a maximum over the
+// workgroup, the pivot's row from memory and a barrier per pick) 1842, so 1470 (66 to 73
+// runs of 11 us and 28 updates of R of 20, both bound by latency and the memory-side cache).
+// Dynamic LDS: BK * nP + CAND * (CAND + 1) doubles; workgroups take (image, slot) from the ticket counter.
+
+// Maximum of one 32-bit key per lane over the wave with DPP moves (no LDS round trips): quads, then shifts by 4 and
 // 8 inside a row of 16 lanes, then the last lane of a row broadcast into the next row (rows 1 and 3) and lane 31
 // into rows 2 and 3, which leaves the maximum in lane 63.  Lanes without a source take 0, the identity for keys.
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ unsigned long long dpp_key(unsigned long long v) {
-  const unsigned lo = __builtin_amdgcn_update_dpp(0u, (unsigned)v, CTRL, ROW_MASK, 0xf, false);
-  const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(v >> 32), CTRL, ROW_MASK, 0xf, false);
-  return ((unsigned long long)hi << 32) | lo;
+__device__ __forceinline__ uint32_t max_dpp(uint32_t v) {
+  const uint32_t o = __builtin_amdgcn_update_dpp(0u, v, CTRL, ROW_MASK, 0xf, false);
+  return o > v ? o : v;
 }
-__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
-  unsigned long long o;
-  o = dpp_key<0xb1, 0xf>(v); v = o > v ? o : v;      // quad_perm [1,0,3,2]
-  o = dpp_key<0x4e, 0xf>(v); v = o > v ? o : v;      // quad_perm [2,3,0,1]
-  o = dpp_key<0x114, 0xf>(v); v = o > v ? o : v;     // row_shr:4
-  o = dpp_key<0x118, 0xf>(v); v = o > v ? o : v;     // row_shr:8
-  o = dpp_key<0x142, 0xa>(v); v = o > v ? o : v;     // row_bcast:15 into rows 1 and 3
-  o = dpp_key<0x143, 0xc>(v); v = o > v ? o : v;     // row_bcast:31 into rows 2 and 3
-  const unsigned lo = __builtin_amdgcn_readlane((unsigned)v, 63), hi = __builtin_amdgcn_readlane((unsigned)(v >> 32), 63);
-  return ((unsigned long long)hi << 32) | lo;
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = max_dpp<0xb1, 0xf>(v);       // quad_perm [1,0,3,2]
+  v = max_dpp<0x4e, 0xf>(v);       // quad_perm [2,3,0,1]
+  v = max_dpp<0x114, 0xf>(v);      // row_shr:4
+  v = max_dpp<0x118, 0xf>(v);      // row_shr:8
+  v = max_dpp<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+  v = max_dpp<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+  return __builtin_amdgcn_readlane(v, 63);
+}
+// Lane of the largest key, of the lowest row among equal ones.
+__device__ __forceinline__ int best_lane(uint32_t key, uint32_t best, uint32_t row) {
+  unsigned long long tied = __ballot(key == best);
+  if (__popcll(tied) > 1) {
+    const uint32_t lowest = wave_max_u32(key == best ? 0xFFFFFFFFu - row : 0u);
+    tied = __ballot(key == best && 0xFFFFFFFFu - row == lowest);
+  }
+  return __ffsll((long long)tied) - 1;
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// value of `v` in lane k of every row of 16 lanes
+template <int k>
+__device__ __forceinline__ double row16_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + k, 0xf, 0xf, true), __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + k, 0xf, 0xf, true));
+}
+// Key of an unpicked row; 0 is below all of them.
+__device__ __forceinline__ uint32_t residual_key(double rho) {
+  const uint32_t u = float_order_key((float)rho);
+  return u > 1u ? u : 1u;
+}
+constexpr uint32_t kKeyInf = 0xFF800000u;       // of +infinity; those of NaNs with a clear sign lie above
+constexpr int kWaveBest = 8;                    // keys a wave posts
+
+struct GreedyRun {
+  unsigned long long post[TPB / 64 * kWaveBest];   // per wave its largest keys: (residual, ~row), 0 where there are no more rows
+  double post_rho[TPB / 64 * kWaveBest];
+  int rank[TPB / 64 * kWaveBest];
+  uint32_t left[TPB / 64];                         // per wave the largest key it did not post
+  uint32_t next;                                   // the largest key posted that is no candidate
+  int cand[64];
+  double cand_rho[64];
+  double factor[16 * 16];                          // [q][m]: column q of the run at the row of its pick m
+  double rho[16];                                  // of the picks
+  double inverse[16];                              // of their square roots; -1: nothing left of the row, its column is zero
+  int pick[16];
+  int picks;
+  int flag;
+};
+
+// Pick m of a run and those after it, by one wave; a lane has one candidate.  col[q] is column q of the run at its row.
+template <int BK, int CAND, int M>
+__device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int room, uint32_t bound, uint32_t row, double rho, bool open, double (&col)[BK]) {
+  if constexpr (M < BK) {
+    if (M >= room) return M;
+    const int lane = threadIdx.x & 63;
+    const uint32_t key = open ? residual_key(rho) : 0u;
+    const uint32_t best = wave_max_u32(key);
+    if (best == 0u || (M > 0 && (best <= bound || best >= kKeyInf))) return M;
+    const int at = __builtin_amdgcn_readfirstlane(best_lane(key, best, row));
+    double c = lane < CAND ? S[at * (CAND + 1) + lane] : 0.0;
+    const double piv = lane_value(rho, at);
+    const double inverse = piv > 0.0 ? 1.0 / sqrt(piv) : -1.0;
+    double taken = 0.0;
+#pragma unroll
+    for (int q = 0; q < M; ++q) taken = fma(col[q], lane_value(col[q], at), taken);
+    if (lane == at) {
+      run.pick[M] = (int)row;
+      run.rho[M] = piv;
+      run.inverse[M] = inverse;
+#pragma unroll
+      for (int q = 0; q < M; ++q) run.factor[q * 16 + M] = col[q];
+      open = false;
+    }
+    c -= taken;
+    col[M] = inverse < 0.0 ? 0.0 : c * inverse;
+    rho -= col[M] * col[M];
+    if (best >= kKeyInf) return M + 1;
+    return run_picks<BK, CAND, M + 1>(S, run, room, bound, row, rho, open, col);
+  }
+  return M;
 }
 
-template <int BK, int NR>
+// c[m] -= l factor_m for the picks m of a run, the factors in lane m of every row of 16 lanes; and the columns of the run themselves
+template <int BK, int FROM, int M>
+__device__ __forceinline__ void take_out(double (&c)[BK], double l, double factors) {
+  if constexpr (M < BK) {
+    if constexpr (M >= FROM) c[M] = fma(-l, row16_lane<M>(factors), c[M]);
+    take_out<BK, FROM, M + 1>(c, l, factors);
+  }
+}
+template <int BK, int M>
+__device__ __forceinline__ void run_columns(double (&c)[BK], const GreedyRun& run, int picks, double inverses, double& rho) {
+  if constexpr (M < BK) {
+    if (M >= picks) return;
+    const double inverse = row16_lane<M>(inverses);
+    c[M] = inverse < 0.0 ? 0.0 : c[M] * inverse;
+    rho -= c[M] * c[M];
+    if constexpr (M + 1 < BK) take_out<BK, M + 1, 0>(c, c[M], run.factor[M * 16 + (threadIdx.x & 15)]);
+    run_columns<BK, M + 1>(c, run, picks, inverses, rho);
+  }
+}
+
+template <int BK, int NR, int CAND>
 __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int nP, int k, int W, int32_t* __restrict__ order,
                                                             float* __restrict__ resid, GreedyCtl* ctl, int* img_status,
                                                             long long limit_ticks) {
-  extern __shared__ double Lblk[];        // [BK][nP]
-  __shared__ unsigned long long red[2][16];   // per wave: its best key and that row's residual, double-buffered by
-  __shared__ double red_rho[2][16];           // step parity so that a step needs one barrier only
-  __shared__ int s_flag;
+  extern __shared__ double Lblk[];        // [BK][nP], then [CAND][CAND + 1]
+  __shared__ GreedyRun run;
+  double* S = Lblk + (size_t)BK * nP;
+  constexpr int POSTS = TPB / 64 * kWaveBest;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
-  if (tid == 0) s_flag = (int)atomicAdd(&ctl[0].ticket, 1u);
+  if (tid == 0) run.flag = (int)atomicAdd(&ctl[0].ticket, 1u);
   __syncthreads();
-  const int ticket = s_flag;
+  const int ticket = run.flag;
   __syncthreads();
   const int b = ticket / W, slot = ticket - b * W;
   GreedyCtl* cb = ctl + b;
@@ -308,84 +410,149 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
   unsigned int target = 0;
   bool alive = true;
   // the diagonal is read above and R is first written at the end of block 0, behind a barrier
-  __syncthreads();
 
-  for (int t = 0; t < k; ++t) {
-    const int jj = t % BK, par = t & 1;
-    // ---- argmax over the unpicked rows of float(rho), lowest index on ties.  Keys are distinct, so exactly one
-    //      lane of a wave holds the wave's best and posts it with its residual.  One barrier per step: what a
-    //      step writes besides is read only behind the next step's barrier, and the posts alternate buffers.
-    unsigned long long best = 0ull;
-    double brho = 0.0;
+  int jj = 0;                              // columns of the block so far
+  for (int t = 0; t < k;) {
+    // ---- the largest keys of each wave
+    {
+      uint32_t key[NR];
 #pragma unroll
-    for (int s = 0; s < NR; ++s) {
-      if (!picked[s]) {
-        const unsigned long long key =
-            ((unsigned long long)float_order_key((float)rho[s]) << 32) | (0xFFFFFFFFu - (uint32_t)(tid + TPB * s));
-        if (key > best) { best = key; brho = rho[s]; }
+      for (int s = 0; s < NR; ++s) key[s] = picked[s] ? 0u : residual_key(rho[s]);
+#pragma unroll 1
+      for (int e = 0; e <= kWaveBest; ++e) {
+        uint32_t mine = key[0];
+        int row = tid;
+        double r = rho[0];
+#pragma unroll
+        for (int s = 1; s < NR; ++s)
+          if (key[s] > mine) { mine = key[s]; row = tid + TPB * s; r = rho[s]; }
+        const uint32_t best = wave_max_u32(mine);
+        if (e == kWaveBest) {
+          if (lane == 0) run.left[w] = best;
+        } else if (best == 0u) {
+          if (lane == 0) run.post[kWaveBest * w + e] = 0ull;
+        } else if (lane == best_lane(mine, best, (uint32_t)row)) {
+          run.post[kWaveBest * w + e] = ((unsigned long long)best << 32) | (0xFFFFFFFFu - (uint32_t)row);
+          run.post_rho[kWaveBest * w + e] = r;
+#pragma unroll
+          for (int s = 0; s < NR; ++s)
+            if (row == tid + TPB * s) key[s] = 0u;
+        }
       }
     }
+    if (tid < POSTS) run.rank[tid] = 0;
+    if (tid < CAND) run.cand[tid] = -1;
+    if (tid == 0) run.next = 0u;
+    __syncthreads();
+    // ---- their ranks: eight threads per key, sixteen comparisons each
+    const unsigned long long key = run.post[tid & (POSTS - 1)];
     {
-      const unsigned long long wbest = wave_max_key(best);
-      if (wbest == 0ull) { if (lane == 0) red[par][w] = 0ull; }
-      else if (best == wbest) { red[par][w] = wbest; red_rho[par][w] = brho; }
+      int above = 0;
+#pragma unroll
+      for (int e = 0; e < POSTS / 8; ++e) above += run.post[(tid / POSTS) * (POSTS / 8) + e] > key ? 1 : 0;
+      if (above) atomicAdd(&run.rank[tid & (POSTS - 1)], above);
     }
     __syncthreads();
-    best = red[par][0];
-    int wq = 0;
+    if (tid < POSTS && key != 0ull) {
+      const int rank = run.rank[tid];
+      if (rank < CAND) {
+        run.cand[rank] = (int)(0xFFFFFFFFu - (uint32_t)key);
+        run.cand_rho[rank] = run.post_rho[tid];
+      } else if (rank == CAND) {
+        run.next = (uint32_t)(key >> 32);
+      }
+    }
+    __syncthreads();
+    // ---- R between the candidates: 16 x 16 tiles on and below the diagonal, minus what this block has already taken out
+    {
+      constexpr int PT = CAND / 16;
+      const int ti = w / PT, tj = w % PT;
+      if (w < PT * PT && tj <= ti) {
+        const int cc = run.cand[16 * tj + i16], col = cc < 0 ? 0 : cc, ar = run.cand[16 * ti + i16], arow = ar < 0 ? 0 : ar;
+        double r[4];
 #pragma unroll
-    for (int q = 1; q < TPB / 64; ++q)
-      if (red[par][q] > best) { best = red[par][q]; wq = q; }
-    const double rp = red_rho[par][wq];
-    const int p = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));     // < n: k <= n, so an unpicked row exists
-    if (best == 0ull || (unsigned)p >= (unsigned)n) {   // never index with anything else
+        for (int v = 0; v < 4; ++v) {
+          const int cr = run.cand[16 * ti + 4 * v + kq];
+          r[v] = R[(long)(cr < 0 ? 0 : cr) * nP + col];
+        }
+        f64x4_t d = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s4 = 0; s4 < BK / 4; ++s4)
+          if (4 * s4 < jj) d = __builtin_amdgcn_mfma_f64_16x16x4f64(Lblk[(4 * s4 + kq) * nP + arow], Lblk[(4 * s4 + kq) * nP + col], d, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 16 * ti + 4 * v + kq, c = 16 * tj + i16;
+          S[a * (CAND + 1) + c] = r[v] - d[v];
+          if (ti != tj) S[c * (CAND + 1) + a] = r[v] - d[v];
+        }
+      }
+    }
+    __syncthreads();
+    // ---- the run
+    if (w == 0) {
+      uint32_t bound = lane < TPB / 64 ? run.left[lane] : 0u;
+      bound = run.next > bound ? run.next : bound;
+      bound = wave_max_u32(bound);
+      const int row = lane < CAND ? run.cand[lane] : -1;
+      double col[BK];
+      const int room = BK - jj < k - t ? BK - jj : k - t;
+      const int picks = run_picks<BK, CAND, 0>(S, run, room, bound, (uint32_t)row, row < 0 ? 0.0 : run.cand_rho[lane], row >= 0, col);
+      if (lane == 0) run.picks = picks;
+    }
+    __syncthreads();
+    const int picks = run.picks;
+    if (picks < 1) {                      // no row left: cannot be, k <= n
       if (tid == 0) __hip_atomic_store(&cb->bar.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       alive = false;
       break;
     }
-    if ((p & (TPB - 1)) == tid) {
-#pragma unroll
-      for (int s = 0; s < NR; ++s)
-        if (s == (p >> 10)) picked[s] = true;
+    if (slot == 0 && tid < picks) {
+      order[(long)b * k + t + tid] = run.pick[tid];
+      resid[(long)b * k + t + tid] = (float)run.rho[tid];
     }
-    // ---- the pivot's row of R, minus what this block has already taken out (summed apart, so that the sum
-    //      does not wait for the row)
-    double c[NR];
-#pragma unroll
-    for (int s = 0; s < NR; ++s) {
-      const int i = tid + TPB * s;
-      c[s] = (i < n) ? R[(long)p * nP + i] : 0.0;
-    }
+    // ---- its columns for all rows
     {
-      double taken[NR];
+      const int mine = i16 < picks ? run.pick[i16] : run.pick[0];      // of the run's pick i16
+      const double inverses = i16 < picks ? run.inverse[i16] : -1.0;
+      double c[NR][BK];
 #pragma unroll
-      for (int s = 0; s < NR; ++s) taken[s] = 0.0;
+      for (int s = 0; s < NR; ++s) {
+        const int i = tid + TPB * s;
+#pragma unroll
+        for (int m = 0; m < BK; ++m) {
+          c[s][m] = 0.0;
+          if (m < picks) {
+            const int p = __builtin_amdgcn_readlane(mine, m);
+            if (i < n) c[s][m] = R[(long)p * nP + i];
+            if (p == i) picked[s] = true;
+          }
+        }
+      }
       for (int q = 0; q < jj; ++q) {
-        const double lp = Lblk[q * nP + p];
+        const double factors = Lblk[q * nP + mine];
 #pragma unroll
         for (int s = 0; s < NR; ++s) {
           const int i = tid + TPB * s;
-          if (i < n) taken[s] = fma(Lblk[q * nP + i], lp, taken[s]);
+          take_out<BK, 0, 0>(c[s], i < n ? Lblk[q * nP + i] : 0.0, factors);
         }
       }
 #pragma unroll
-      for (int s = 0; s < NR; ++s) c[s] -= taken[s];
-    }
-    const double piv = rp > 0.0 ? rp : 0.0;
-    const double root = sqrt(piv);
+      for (int s = 0; s < NR; ++s) {
+        const int i = tid + TPB * s;
+        run_columns<BK, 0>(c[s], run, picks, inverses, rho[s]);
 #pragma unroll
-    for (int s = 0; s < NR; ++s) {
-      const int i = tid + TPB * s;
-      const double col = (piv > 0.0 && i < n) ? c[s] / root : 0.0;
-      if (i < nP) Lblk[jj * nP + i] = col;
-      rho[s] -= col * col;
+        for (int m = 0; m < BK; ++m)
+          if (m < picks && i < nP) Lblk[(jj + m) * nP + i] = c[s][m];
+      }
     }
-    if (slot == 0 && tid == 0) { order[(long)b * k + t] = p; resid[(long)b * k + t] = (float)rp; }
-    if (jj == BK - 1 && t + 1 < k) {
+    t += picks;
+    jj += picks;
+    if (jj == BK && t < k) {
+      jj = 0;
       // every workgroup of the image has read its last row of the old R (the wait starts with a barrier of
       // the workgroup, behind which the block's columns are complete in LDS)
       target += (unsigned int)W;
-      alive = image_barrier_wait(&cb->bar, target, &s_flag, limit_ticks);
+      alive = image_barrier_wait<false>(&cb->bar, target, &run.flag, limit_ticks);
       if (!alive) break;
       // ---- R -= Lblk^T Lblk on this workgroup's bands (band ti belongs to slot ti % W); a wave takes four
       //      neighbouring 16 x 16 tiles per trip and requests their 16 values of R before the first MFMA
@@ -416,14 +583,15 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
             d = __builtin_amdgcn_mfma_f64_16x16x4f64(Lblk[(4 * s4 + kq) * nP + 16 * ti[u] + i16], Lblk[(4 * s4 + kq) * nP + 16 * tj[u] + i16], d,
                                                      0, 0, 0);
           if (tile0 + u < ntiles) {
+            // through the L2, so that the barrier has nothing to write back (6 of 26 us per update of six images of 926 rows)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) out[u][(long)(4 * v) * nP] = r[u][v] - d[v];
+            for (int v = 0; v < 4; ++v) store_through(out[u] + (long)(4 * v) * nP, r[u][v] - d[v]);
           }
         }
       }
       // every band is up to date before any workgroup reads a row of R again
       target += (unsigned int)W;
-      alive = image_barrier_wait(&cb->bar, target, &s_flag, limit_ticks);
+      alive = image_barrier_wait<false>(&cb->bar, target, &run.flag, limit_ticks);
       if (!alive) break;
       for (int e = tid; e < BK * nP; e += TPB) Lblk[e] = 0.0;
       __syncthreads();
@@ -469,22 +637,25 @@ size_t greedy_scratch_bytes(int B, int nP) {
   return (size_t)B * sizeof(GreedyCtl) + 256 + (size_t)B * 4 * (nP / GR) * 8;
 }
 
-template <int BK, int NR>
+// Columns of a block of BK picks and the candidates' submatrix, beside the kernel's static words.
+constexpr size_t kPanelLds = 160 * 1024 - sizeof(GreedyRun) - 256;
+static size_t panel_lds(int BK, int cand, int nP) { return ((size_t)BK * nP + (size_t)cand * (cand + 1)) * sizeof(double); }
+
+template <int BK, int NR, int CAND>
 static hipError_t launch_panel(double* G, int B, int n, int nP, int k, int W, int32_t* order, float* resid, GreedyCtl* ctl,
                                int* img_status, hipStream_t st) {
-  const size_t lds = (size_t)BK * nP * sizeof(double);
-  constexpr size_t kLdsMost = 159 * 1024;   // launch_greedy picks BK so that the block's columns stay below this
-  if (lds > kLdsMost) return hipErrorInvalidValue;
+  const size_t lds = panel_lds(BK, CAND, nP);
+  if (lds > kPanelLds || n > TPB * NR) return hipErrorInvalidValue;
   static PerDeviceInt raised, cache;   // per instantiation
-  hipError_t e = ensure_dynamic_lds(raised, (const void*)greedy_panel_kernel<BK, NR>, kLdsMost);
+  hipError_t e = ensure_dynamic_lds(raised, (const void*)greedy_panel_kernel<BK, NR, CAND>, kPanelLds);
   if (e != hipSuccess) return e;
   // the workgroups of one image wait for one another, so one image has to fit the device; counted once per device
   // for the largest LDS request, which never overstates what a smaller one gets
   int capacity = 0;
-  if ((e = resident_workgroups(cache, greedy_panel_kernel<BK, NR>, TPB, kLdsMost, &capacity)) != hipSuccess) return e;
+  if ((e = resident_workgroups(cache, greedy_panel_kernel<BK, NR, CAND>, TPB, kPanelLds, &capacity)) != hipSuccess) return e;
   if (W > capacity) return hipErrorInvalidValue;
   hipLaunchKernelGGL(greedy_init_kernel, dim3((B + 255) / 256), dim3(256), 0, st, ctl, B);
-  hipLaunchKernelGGL((greedy_panel_kernel<BK, NR>), dim3((unsigned)(B * W)), dim3(TPB), lds, st, G, n, nP, k, W, order, resid, ctl,
+  hipLaunchKernelGGL((greedy_panel_kernel<BK, NR, CAND>), dim3((unsigned)(B * W)), dim3(TPB), lds, st, G, n, nP, k, W, order, resid, ctl,
                      img_status, barrier_limit_ticks());
   return hipGetLastError();
 }
@@ -493,10 +664,9 @@ hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int
                          int* img_status, hipStream_t st) {
   if (nP % GR != 0 || n > nP || n > 4096 || k > n || k > 4096) return hipErrorInvalidValue;
   GreedyCtl* ctl = (GreedyCtl*)scratch;
-  // the largest block of picks (a multiple of the MFMA's depth of 4) whose columns fit LDS beside the kernel's few
-  // static words
-  const size_t lds_cap = 159 * 1024;
-  const int BK = (size_t)16 * nP * 8 <= lds_cap ? 16 : (size_t)12 * nP * 8 <= lds_cap ? 12 : (size_t)8 * nP * 8 <= lds_cap ? 8 : 4;
+  // the largest block of picks (a multiple of the MFMA's depth of 4) whose columns fit LDS beside the candidates' submatrix
+  const auto fits = [&](int bk, int cand) { return panel_lds(bk, cand, nP) <= kPanelLds; };
+  const int BK = fits(16, 64) ? 16 : fits(12, 64) ? 12 : fits(8, 32) ? 8 : 4;
   // values moved: the right-looking kernel reads and writes R once per block that is followed by another, the
   // left-looking ones read every earlier column at every step; the former also has far fewer barriers
   const double right = (double)((k - 1) / BK) * 2.0 * n * n, left = 0.5 * k * k * n;
@@ -507,13 +677,14 @@ hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int
     if (Wp < 4) Wp = 256 / B < 4 ? 256 / B : 4;
     Wp = Wp < 1 ? 1 : Wp > 32 ? 32 : Wp;
     Wp = Wp > nt ? nt : Wp;
-    // rows per thread: at most 1216 rows with blocks of 16, 1664 with 12, 2496 with 8
-    if (BK == 16) return n <= TPB ? launch_panel<16, 1>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st)
-                                  : launch_panel<16, 2>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
-    if (BK == 12) return launch_panel<12, 2>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
-    if (BK == 8) return n <= 2 * TPB ? launch_panel<8, 2>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st)
-                                     : launch_panel<8, 4>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
-    return launch_panel<4, 4>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
+    // rows: at most 960 with blocks of 16, 1280 with 12, 1920 with 8 (2304 with 32 candidates), 3840 with 4
+    if (BK == 16) return launch_panel<16, 1, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
+    if (BK == 12) return launch_panel<12, 2, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
+    if (BK == 8)
+      return fits(8, 64) ? launch_panel<8, 2, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st)
+                         : launch_panel<8, 3, 32>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
+    return fits(4, 64) ? launch_panel<4, 4, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st)
+                       : launch_panel<4, 4, 32>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
   }
   const int W = nP / GR;
   // Left-looking: spreading an image over W workgroups costs a device-scope barrier per step; it pays while the

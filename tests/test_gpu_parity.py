@@ -344,8 +344,8 @@ def test_greedy_picks_on_a_large_batch_of_small_images(C, k):
 
 
 @pytest.mark.parametrize("B,n,d,k,why", [
-    (3, 1100, 320, 150, "two rows per thread, blocks of 16 picks, 32 workgroups per image"),
-    (2, 1300, 704, 330, "blocks of 12 picks (16 columns of 1344 rows do not fit LDS)"),
+    (3, 1100, 320, 150, "two rows per thread, 32 workgroups per image"),
+    (2, 1300, 704, 330, "blocks of 8 picks (12 columns of 1344 rows do not fit LDS)"),
     (1, 1700, 896, 430, "blocks of 8 picks"),
     (1, 2500, 2560, 1260, "four rows per thread, blocks of 4 picks"),
     (2, 1500, 256, 40, "few picks out of many rows: the left-looking kernel on several workgroups"),
@@ -368,6 +368,59 @@ def test_greedy_picks_on_large_images(C, B, n, d, k, why):
         np.testing.assert_array_equal(_cpu(out["pick_order"])[b], ref["pick_order"], err_msg="image %d (%s)" % (b, why))
         U.assert_scores_close(_cpu(out["resid"])[b], ref["resid"], I.FP32, "resid[%d]" % b, tol=1e-5)
         np.testing.assert_array_equal(_cpu(out["idx"])[b], ref["idx"])
+
+
+def _greedy_inputs(kind, n, d, seed):
+    g = np.random.default_rng(seed)
+    if kind == "equal":                       # nothing but ties: every pick leaves the others as they were
+        return 2.0 * np.eye(n, d)
+    X = g.standard_normal((n, d)) * 0.98 ** np.arange(d)
+    if kind == "front":                       # the largest rows are neighbours: more of them in one wave than it posts
+        X *= np.where(np.arange(n) < 64, 4.0, 1.0)[:, None]
+    elif kind == "copies":                    # pairs and triples of equal rows
+        X[n // 2:n // 2 + n // 4] = X[:n // 4]
+        X[-(n // 8):] = X[:n // 8]
+    elif kind == "steep":                     # the largest falls below the others with its first pick
+        X *= 0.97 ** np.arange(n)[:, None]
+    return X
+
+
+@pytest.mark.parametrize("n,d,k", [(63, 80, 63), (65, 96, 40), (640, 640, 200), (960, 320, 150), (1024, 512, 200), (1281, 512, 250), (1921, 512, 260),
+                                   (2305, 640, 600)], ids=lambda v: str(v))
+@pytest.mark.parametrize("kind", ["equal", "front", "copies", "steep"])
+def test_greedy_runs_of_picks(C, kind, n, d, k):
+    """Picks made in runs among the largest residuals, at the edges of the block sizes: order and residuals against the oracle
+    as long as the residuals are above the rounding of the products."""
+    import torch
+    if kind == "equal" and d < n:
+        d = (n + 7) // 8 * 8
+    X = _greedy_inputs(kind, n, d, n).astype(np.float32)
+    sf = np.random.default_rng(3).random(n).astype(np.float32)
+    p = C.Params(batch=1, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, lr_mode=C.LR_GREEDY_RESIDUAL, keep_k=k, preselect_m=n, rank_r=1)
+    out = C.select(p, torch.from_numpy(X)[None].cuda(), torch.from_numpy(sf)[None].cuda())
+    if kind == "equal":
+        np.testing.assert_array_equal(_cpu(out["pick_order"])[0], np.arange(k))
+        np.testing.assert_array_equal(_cpu(out["resid"])[0], np.full(k, 4.0, np.float32))
+        return
+    ref = O.select(X.astype(np.float64), sf, O.Params(lr_mode=1, keep_k=k, preselect_m=n, rank_r=1))
+    # residuals carry the rounding of the largest squared length, 1.1e-16 of it per step at most, and are returned in fp32; where that
+    # is not far below them the order is noise
+    sure = int(np.sum(ref["resid"] > 1e-9 * ref["resid"][0]))
+    assert sure >= min(k, n // 4, 200)
+    np.testing.assert_array_equal(_cpu(out["pick_order"])[0][:sure], ref["pick_order"][:sure])
+    np.testing.assert_allclose(_cpu(out["resid"])[0][:sure].astype(np.float64), ref["resid"][:sure], rtol=1e-6, atol=1.1e-16 * k * ref["resid"][0])
+    assert len(set(_cpu(out["idx"])[0].tolist())) == k
+
+
+def test_greedy_picks_with_rows_that_are_not_finite(C):
+    """An infinite token is the largest; whatever its column does to the others, the picks stay distinct positions."""
+    import torch
+    X = torch.randn(1, 300, 64, generator=torch.Generator().manual_seed(5))
+    X[0, 77] = float("inf")
+    p = C.Params(batch=1, n_tokens=300, d_model=64, n_query=1, dtype=C.FP32, lr_mode=C.LR_GREEDY_RESIDUAL, keep_k=50, preselect_m=300, rank_r=1)
+    out = C.select(p, X.cuda(), torch.rand(1, 300, generator=torch.Generator().manual_seed(6)).cuda())
+    picks = _cpu(out["pick_order"])[0]
+    assert picks[0] == 77 and len(set(picks.tolist())) == 50
 
 
 def test_select_ties_and_exact_duplicates(C):
