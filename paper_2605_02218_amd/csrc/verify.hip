@@ -9,6 +9,11 @@
 // masses of max(p_t - p_d, 0), then, inside the one chunk that holds u_res * (total residual mass), for the
 // inverse-CDF search of the correction.  Everything is HBM-bound streaming except the fp64 exponentials of the
 // residual pass (2 per word, one row per sequence).
+// For a few sequences what follows the statistics is one launch (verify_few_kernel): a workgroup per chunk of the rejected row, each of
+// which works out the acceptance for itself, the last one of a sequence draws.  A chain of four launches is bound by the launches
+// there; from some ten sequences on the acceptance is repeated in more workgroups than the device holds at once and the draws come
+// at the end of the longest launch.  us, four launches / two: one sequence of 5 positions and 32000 words 22.8 / 16.5, eight 22.3 / 17.5, sixteen
+// 22.1 / 20.9 (23.7 with 64 registers a thread), thirty-two 25 / 36; eight of 151936 words 26.5 / 25.4.
 #include "common.h"
 #include "kernels.h"
 #include "vocab.h"
@@ -17,18 +22,23 @@ namespace covspec {
 
 namespace {
 
-constexpr int VT = 256;            // threads of the streaming kernels
+constexpr int VT = 256;            // threads of the statistics pass
+constexpr int AW = 8;              // waves of the acceptance kernel
+constexpr int ST = 1024;           // threads of the sampling kernel
+constexpr int FT = 512;            // of the kernel for few sequences
+constexpr long kFewGroups = 512;   // workgroups up to which that is taken: two per compute unit
 
 // stats[(row * chunks + c) * 4 + {0,1,2,3}] = ref_t, sum_t, ref_d, sum_d (base-2 domain) over words [c*clen, min(V, (c+1)*clen))
 template <int DT>
 __global__ __launch_bounds__(VT) void verify_stats_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int V, int clen,
-                                                          int chunks, double* __restrict__ stats) {
+                                                          int chunks, int L, double* __restrict__ stats, int* __restrict__ done) {
   constexpr int N = LogitVec<DT>::N;
   __shared__ double red[2][VT / 64][2];
   const long row = blockIdx.y;
   const int c = blockIdx.x;
   const int w0 = c * clen, w1 = min(V, w0 + clen);
   const long base = row * (long)V;
+  if (c == 0 && threadIdx.x == 0 && row % L == 0) done[row / L] = 0;      // for the residual pass
   float mt = -INFINITY, st = 0.f, md = -INFINITY, sd = 0.f;
   // V, clen % N == 0: whole vectors only.  (Two vectors per trip with all loads issued first, and twice the
   // workgroups, both measured slower: the pass runs at the rate the memory system gives one resident round.)
@@ -46,27 +56,21 @@ __global__ __launch_bounds__(VT) void verify_stats_kernel(const void* __restrict
   if (threadIdx.x == 0) { stats[(row * chunks + c) * 4 + 2] = mm; stats[(row * chunks + c) * 4 + 3] = ss; }
 }
 
-constexpr int AW = 8;              // waves of the acceptance kernel
-
-// One workgroup per sequence; `group` lanes (the smallest power of two that holds a row's chunks, at most 64) take a position, a
-// wave as many positions at once as it has groups: row statistics from the chunk partials (one exponential per lane against the
-// largest reference, one sum), alpha at the drafted token; then wave 0, lane = position, finds the first rejection (L <= 64).  rowmax[s * 4 + {0,1}] = the rejected row's references
-// brought back to the natural domain, i.e. its maximum logits to within rounding: the shift the fp64 passes below use (any
-// value near the maximum serves, as long as every pass uses the same), [2] = the ratio of the two streaming sums; untouched
-// when nothing is rejected.  With one lane per position that folds the chunks one by one, two fp64 exponentials each, one
-// sequence of 5 positions in 64 chunks took 11.5 us; now 3.4.  With a wave per position whatever the number of chunks,
-// sixteen sequences of 64 positions in one chunk took 20 us.
-template <int DT>
-__global__ __launch_bounds__(64 * AW) void verify_accept_kernel(const void* __restrict__ zt, const void* __restrict__ zd,
-                                                                const int32_t* __restrict__ tok, const float* __restrict__ u_acc, int L,
-                                                                int V, int chunks, int group, const double* __restrict__ stats,
-                                                                int32_t* __restrict__ n_acc, float* __restrict__ alpha_out,
-                                                                double* __restrict__ rowmax) {
-  __shared__ double sh[64][3];       // per position: what rowmax gets
-  __shared__ int sh_rej[64];
-  const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// The acceptance of sequence s, by the whole workgroup; `group` lanes (the smallest power of two that holds a row's chunks, at most
+// 64) take a position, a wave as many positions at once as it has groups: row statistics from the chunk partials (one exponential
+// per lane against the largest reference, one sum), alpha at the drafted token.  Returns the first rejected position or L (L <= 64);
+// sh[t * 3 + {0,1}] = the references of row t brought back to the natural domain, i.e. its maximum logits to within rounding: the
+// shift the fp64 passes below use (any value near the maximum serves, as long as every pass uses the same), [2] = the ratio of
+// the two streaming sums.
+// With one lane per position that folds the chunks one by one, two fp64 exponentials each, one sequence of 5 positions in 64 chunks
+// took 11.5 us; now 3.4.  With a wave per position whatever the number of chunks, sixteen sequences of 64 positions in one chunk took 20 us.
+template <int DT, int T>
+__device__ __forceinline__ int accept(const void* __restrict__ zt, const void* __restrict__ zd, const int32_t* __restrict__ tok,
+                                      const float* __restrict__ u_acc, int s, int L, int V, int chunks, int group,
+                                      const double* __restrict__ stats, float* __restrict__ alpha_out, bool write, double* sh, int* sh_rej) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int c = lane & (group - 1), groups = 64 / group;
-  for (int t0 = wv * groups; t0 < L; t0 += AW * groups) {      // uniform in a wave: every lane takes part in the exchanges
+  for (int t0 = wv * groups; t0 < L; t0 += T / 64 * groups) {      // uniform in a wave: every lane takes part in the exchanges
     const int t = t0 + lane / group;
     const long row = (long)s * L + (t < L ? t : L - 1);
     int y = tok[row];
@@ -92,20 +96,32 @@ __global__ __launch_bounds__(64 * AW) void verify_accept_kernel(const void* __re
     const double a = pd > 0.0 ? fmin(1.0, pt / pd) : 1.0;
     const float af = (float)a;
     if (c == 0 && t < L) {
-      if (alpha_out) alpha_out[row] = af;
+      if (write && alpha_out) alpha_out[row] = af;
       sh_rej[t] = !(u_acc[row] < af) ? 1 : 0;
-      sh[t][0] = m[0] / (double)kLog2e;
-      sh[t][1] = m[1] / (double)kLog2e;
+      sh[t * 3] = m[0] / (double)kLog2e;
+      sh[t * 3 + 1] = m[1] / (double)kLog2e;
       // estimate of (sum_w exp(z_t - shift_t)) / (sum_w exp(z_d - shift_d)), good to the ~1e-6 of the streaming sums
-      sh[t][2] = sum[0] / sum[1];
+      sh[t * 3 + 2] = sum[0] / sum[1];
     }
   }
   __syncthreads();
-  if (wv != 0) return;
   const unsigned long long mask = __ballot(lane < L && sh_rej[lane < L ? lane : 0] != 0);
-  const int first = mask != 0ull ? __ffsll((long long)mask) - 1 : L;
-  if (first < L && lane < 3) rowmax[s * 4 + lane] = sh[first][lane];
-  if (lane == 0) n_acc[s] = first;
+  return mask != 0ull ? __ffsll((long long)mask) - 1 : L;
+}
+
+// One workgroup per sequence.  rowmax[s * 4 + {0,1,2}] = what `accept` leaves of the rejected row; untouched when nothing is rejected.
+template <int DT>
+__global__ __launch_bounds__(64 * AW) void verify_accept_kernel(const void* __restrict__ zt, const void* __restrict__ zd,
+                                                                const int32_t* __restrict__ tok, const float* __restrict__ u_acc, int L,
+                                                                int V, int chunks, int group, const double* __restrict__ stats,
+                                                                int32_t* __restrict__ n_acc, float* __restrict__ alpha_out,
+                                                                double* __restrict__ rowmax) {
+  __shared__ double sh[64 * 3];
+  __shared__ int sh_rej[64];
+  const int s = blockIdx.x;
+  const int first = accept<DT, 64 * AW>(zt, zd, tok, u_acc, s, L, V, chunks, group, stats, alpha_out, true, sh, sh_rej);
+  if (first < L && threadIdx.x < 3) rowmax[s * 4 + threadIdx.x] = sh[first * 3 + threadIdx.x];
+  if (threadIdx.x == 0) n_acc[s] = first;
 }
 
 // e^x for the fp64 passes, x <= 0 to within rounding: x = n ln 2 + f with |f| <= ln 2 / 2 (Cody and Waite's two-part reduction),
@@ -141,17 +157,10 @@ __device__ __forceinline__ double exp_shifted(double x) {
 // order (a word that changes sides carries a residual below delta e_d).  So the words are picked with the
 // streaming estimate (delta ~ 1e-6, mass error ~ 1e-12 relative) and A, B are combined with the exact kappa
 // afterwards.  rowsum[(s * rchunks + c) * 4 + {0,1,2,3}] = S_t, S_d, A, B of the chunk.
-template <int DT>
-__global__ __launch_bounds__(VT) void verify_rowpass64_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int L, int V,
-                                                              int rlen, int rchunks, const int32_t* __restrict__ n_acc,
-                                                              const double* __restrict__ rowmax, double* __restrict__ rowsum) {
-  __shared__ double red[4][VT / 64];
-  const int s = blockIdx.y, c = blockIdx.x;
-  const int t = n_acc[s];
-  if (t >= L) return;
-  const long base = ((long)s * L + t) * V;
-  const int w0 = c * rlen, w1 = min(V, w0 + rlen);
-  const double mt = rowmax[s * 4], md = rowmax[s * 4 + 1], kap = rowmax[s * 4 + 2];
+template <int DT, int T>
+__device__ __forceinline__ void residual_masses(const void* __restrict__ zt, const void* __restrict__ zd, long base, int w0, int w1, double mt, double md,
+                                                double kap, double* sums) {
+  __shared__ double red[4][T / 64];
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   constexpr int N = LogitVec<DT>::N;
   auto add = [&](double xt, double xd) {
@@ -162,12 +171,12 @@ __global__ __launch_bounds__(VT) void verify_rowpass64_kernel(const void* __rest
     acc[2] += more ? et : 0.0;
     acc[3] += more ? ed : 0.0;
   };
-  if (w1 - w0 <= VT) {
+  if (w1 - w0 <= T) {
     // a word per thread: eight of them one after the other in an eighth of the threads take 4.2 us where this takes 3.3
     const int w = w0 + threadIdx.x;
     if (w < w1) add(LogitVec<DT>::at(zt, base + w), LogitVec<DT>::at(zd, base + w));
   } else {
-    for (int w = w0 + threadIdx.x * N; w < w1; w += VT * N) {    // V, rlen % N == 0: whole vectors only
+    for (int w = w0 + threadIdx.x * N; w < w1; w += T * N) {     // V, rlen % N == 0: whole vectors only
       float a[N], c[N];
       LogitVec<DT>::load(zt, base + w, a);
       LogitVec<DT>::load(zd, base + w, c);
@@ -184,32 +193,21 @@ __global__ __launch_bounds__(VT) void verify_rowpass64_kernel(const void* __rest
   }
   __syncthreads();
   if (threadIdx.x < 4) {
-    const int q = threadIdx.x;
     double tot = 0.0;
-    for (int k = 0; k < VT / 64; ++k) tot += red[q][k];
-    rowsum[((long)s * rchunks + c) * 4 + q] = tot;
+    for (int k = 0; k < T / 64; ++k) tot += red[threadIdx.x][k];
+    store_through(sums + threadIdx.x, tot);
   }
 }
 
-// wave 0 of a workgroup (all 64 lanes): the row's (max_t, 1/sum_t, max_d, 1/sum_d) from the chunk sums, into
-// LDS.  rchunks <= 64: lane c holds chunk c, butterfly sums (the same order wherever this is called).  Returns
-// the residual mass of chunk `lane`, A / S_t - B / S_d (0 for lanes beyond the chunks).
-__device__ __forceinline__ double combine_rowstat(const double* __restrict__ rowmax, const double* __restrict__ rowsum, int s, int rchunks,
-                                                  double* sh4) {
-  const int lane = threadIdx.x & 63;
-  const double* rs = rowsum + ((long)s * rchunks + lane) * 4;
-  const double st_c = lane < rchunks ? rs[0] : 0.0, sd_c = lane < rchunks ? rs[1] : 0.0;
-  const double a_c = lane < rchunks ? rs[2] : 0.0, b_c = lane < rchunks ? rs[3] : 0.0;
-  const double st = wave_sum(st_c), sd = wave_sum(sd_c);
-  const double ist = 1.0 / st, isd = 1.0 / sd;
-  if (lane == 0) { sh4[0] = rowmax[s * 4]; sh4[1] = ist; sh4[2] = rowmax[s * 4 + 1]; sh4[3] = isd; }
-  double mass;
-  {
-#pragma clang fp contract(off)
-    const double x = a_c * ist, y = b_c * isd;
-    mass = x - y;
-  }
-  return mass > 0.0 ? mass : 0.0;
+template <int DT>
+__global__ __launch_bounds__(VT) void verify_rowpass64_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int L, int V,
+                                                              int rlen, int rchunks, const int32_t* __restrict__ n_acc,
+                                                              const double* __restrict__ rowmax, double* __restrict__ rowsum) {
+  const int s = blockIdx.y, c = blockIdx.x;
+  const int t = n_acc[s];
+  if (t >= L) return;
+  residual_masses<DT, VT>(zt, zd, ((long)s * L + t) * V, c * rlen, min(V, (c + 1) * rlen), rowmax[s * 4], rowmax[s * 4 + 1], rowmax[s * 4 + 2],
+                          rowsum + ((long)s * rchunks + c) * 4);
 }
 
 __device__ __forceinline__ double residual_of(double zt, double zd, double mt, double ist, double md, double isd) {
@@ -222,37 +220,51 @@ __device__ __forceinline__ double residual_of(double zt, double zd, double mt, d
   return d > 0.0 ? d : 0.0;
 }
 
-// One 1024-thread workgroup per sequence: inverse CDF of the residual in vocabulary order.  A thread's residuals are kept in
-// registers between the two passes over them (14.7 -> 11.9 us for 64 sequences).  64 registers, so that a compute unit holds
-// two workgroups: with 66 and one, 512 sequences of 8192 words took 20.5 us, 15.4 with two.
-template <int DT>
-__global__ __launch_bounds__(1024, 8) void verify_sample_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int L, int V,
-                                                             int clen, int chunks, const int32_t* __restrict__ n_acc,
-                                                             const double* __restrict__ rowmax, const double* __restrict__ rowsum,
-                                                             const float* __restrict__ u_res, int32_t* __restrict__ corr) {
-  __shared__ double wsum[16];
-  __shared__ double sh_prefix, sh_target;
-  __shared__ int sh_chunk, sh_found, sh_last;
+// wave 0 of a workgroup (all 64 lanes): the row's 1/sum_t and 1/sum_d from the chunk sums, into LDS.  rchunks <= 64: lane c holds
+// chunk c, butterfly sums.  Returns the residual mass of chunk `lane`, A / S_t - B / S_d (0 for lanes beyond the chunks).
+__device__ __forceinline__ double combine_rowstat(const double* rs, int rchunks, double* sh2) {
+  const int lane = threadIdx.x & 63;
+  rs += lane * 4;
+  const double st_c = lane < rchunks ? rs[0] : 0.0, sd_c = lane < rchunks ? rs[1] : 0.0;
+  const double a_c = lane < rchunks ? rs[2] : 0.0, b_c = lane < rchunks ? rs[3] : 0.0;
+  const double st = wave_sum(st_c), sd = wave_sum(sd_c);
+  const double ist = 1.0 / st, isd = 1.0 / sd;
+  if (lane == 0) { sh2[0] = ist; sh2[1] = isd; }
+  double mass;
+  {
+#pragma clang fp contract(off)
+    const double x = a_c * ist, y = b_c * isd;
+    mass = x - y;
+  }
+  return mass > 0.0 ? mass : 0.0;
+}
+
+// The correction of sequence s, by one workgroup: inverse CDF of the residual in vocabulary order.  A thread sums `per`
+// neighbouring words of the chunk; the words of the one thread whose sum passes the target are evaluated once more, one by a lane.
+// (With all threads walking their words again behind their prefixes, 256 of them, a chunk of 4864 words took 41 us in the kernel for few
+// sequences; so, with 512, 18.)
+template <int DT, int T>
+__device__ __forceinline__ void sample(const void* __restrict__ zt, const void* __restrict__ zd, int s, long base, int V, int clen, int chunks,
+                                       double mt, double md, const double* rowsum, float u, int32_t* __restrict__ corr) {
+  constexpr int N = LogitVec<DT>::N;
+  __shared__ double wsum[T / 64], before[T];
+  __shared__ double sh_prefix, sh_target, sh2[2];
+  __shared__ int sh_chunk, sh_cross, sh_last;
   __shared__ unsigned long long sh_best;
-  const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int t = n_acc[s];
-  if (t >= L) { if (tid == 0) corr[s] = -1; return; }
-  const long base = ((long)s * L + t) * V;
-  __shared__ double sh4[4];
-  double pc = 0.0;
-  if (tid < 64) pc = combine_rowstat(rowmax, rowsum, s, chunks, sh4);     // this lane's chunk mass (wave 0)
-  __syncthreads();
-  const double mt = sh4[0], ist = sh4[1], md = sh4[2], isd = sh4[3];
-  if (tid < 64) {
-    // lane c holds chunk c's residual mass; inclusive scan in lane order, total in lane 63
-    double inc = pc;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // lane c of a wave holds chunk c's residual mass; inclusive scan in lane order, total in lane 63
+  auto scan = [&](double v) {
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const double v = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += v;
+      const double w = __shfl_up(v, o, 64);
+      if (lane >= o) v += w;
     }
+    return v;
+  };
+  if (tid < 64) {
+    const double pc = combine_rowstat(rowsum, chunks, sh2), inc = scan(pc);
     const double R = __shfl(inc, 63, 64);
-    const double target = (double)u_res[s] * R;
+    const double target = (double)u * R;
     // the first chunk whose cumulative mass passes the target; if rounding leaves the target at the total,
     // the last chunk with any mass
     const unsigned long long over = __ballot(pc > 0.0 && inc > target);
@@ -260,7 +272,7 @@ __global__ __launch_bounds__(1024, 8) void verify_sample_kernel(const void* __re
     int cs = -1;
     if (R > 0.0) cs = over ? __ffsll((long long)over) - 1 : 63 - __clzll((long long)mass);
     if (lane == (cs < 0 ? 0 : cs)) {
-      sh_chunk = cs; sh_prefix = inc - pc; sh_target = target; sh_found = 0x7fffffff; sh_last = -1; sh_best = 0ull;
+      sh_chunk = cs; sh_prefix = inc - pc; sh_target = target; sh_cross = T; sh_last = -1; sh_best = 0ull;
     }
   }
   __syncthreads();
@@ -268,10 +280,14 @@ __global__ __launch_bounds__(1024, 8) void verify_sample_kernel(const void* __re
   if (cs < 0) {
     // no residual mass (p_t == p_d): argmax p_t, lowest index on ties
     unsigned long long best = 0ull;
-    for (int w = tid; w < V; w += 1024) {
-      const float z = (float)LogitVec<DT>::at(zt, base + w);   // logits are stored in at most fp32: exact
-      const unsigned long long key = ((unsigned long long)float_order_key(z) << 32) | (0xFFFFFFFFu - (uint32_t)w);
-      best = key > best ? key : best;
+    for (int w = tid * N; w < V; w += T * N) {                // V % N == 0: whole vectors only
+      float a[N];
+      LogitVec<DT>::load(zt, base + w, a);                     // logits are stored in at most fp32: exact
+#pragma unroll
+      for (int e = 0; e < N; ++e) {
+        const unsigned long long key = ((unsigned long long)float_order_key(a[e]) << 32) | (0xFFFFFFFFu - (uint32_t)(w + e));
+        best = key > best ? key : best;
+      }
     }
     best = wave_max(best);
     if (lane == 0) atomicMax(&sh_best, best);
@@ -279,77 +295,107 @@ __global__ __launch_bounds__(1024, 8) void verify_sample_kernel(const void* __re
     if (tid == 0) corr[s] = (int)(0xFFFFFFFFu - (uint32_t)(sh_best & 0xFFFFFFFFull));
     return;
   }
-  // inside the chunk: thread `tid` owns the words [w0 + tid*per, w0 + (tid+1)*per): one, two or eight of them, kept in registers,
-  // where the chunk has no more than that per thread, else more, evaluated twice.  (Eight by an eighth of the threads took
-  // 13.3 us for 512 chunks of 256 words, one by each 9.4.)
-  const int w0 = cs * clen, w1 = min(V, w0 + clen);
-  constexpr int N = LogitVec<DT>::N;
-  const int n = w1 - w0, per = n <= 1024 ? 1 : n <= 2048 ? 2 : n <= 8192 ? 8 : (n + 1023) / 1024;
-  const int a0 = w0 + tid * per, a1 = min(w1, a0 + per);
+  const double ist = sh2[0], isd = sh2[1];
+  const int w0 = cs * clen, w1 = min(V, w0 + clen), n = w1 - w0;
+  const bool vectors = n > 2 * T;                             // one or two words per thread are spread over all of them
+  const int per = vectors ? (n + T * N - 1) / (T * N) * N : (n + T - 1) / T;
+  const int a0 = min(w1, w0 + tid * per), a1 = min(w1, a0 + per);
   auto residual_at = [&](int w) { return residual_of(LogitVec<DT>::at(zt, base + w), LogitVec<DT>::at(zd, base + w), mt, ist, md, isd); };
-  double mine = 0.0, r8[8];
-  if (per <= 2) {
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      r8[e] = e < per && a0 + e < w1 ? residual_at(a0 + e) : 0.0;
-      mine += r8[e];
-    }
-  } else if (per == 8) {
-#pragma unroll
-    for (int v = 0; v < 8 / N; ++v) {               // w0, w1 % N == 0: whole vectors only
+  double mine = 0.0, first = 0.0, second = 0.0;
+  if (vectors) {
+    for (int w = a0; w < a1; w += N) {                         // w0, w1 % N == 0: whole vectors only
       float a[N], c[N];
+      LogitVec<DT>::load(zt, base + w, a);
+      LogitVec<DT>::load(zd, base + w, c);
 #pragma unroll
-      for (int e = 0; e < N; ++e) a[e] = c[e] = 0.f;
-      const bool in = a0 + v * N < w1;
-      if (in) {
-        LogitVec<DT>::load(zt, base + a0 + v * N, a);
-        LogitVec<DT>::load(zd, base + a0 + v * N, c);
-      }
-#pragma unroll
-      for (int e = 0; e < N; ++e) {
-        r8[v * N + e] = in ? residual_of((double)a[e], (double)c[e], mt, ist, md, isd) : 0.0;
-        mine += r8[v * N + e];
-      }
+      for (int e = 0; e < N; ++e) mine += residual_of((double)a[e], (double)c[e], mt, ist, md, isd);
     }
   } else {
-    for (int w = a0; w < a1; ++w) mine += residual_at(w);
+    if (a0 < a1) first = residual_at(a0);
+    if (a0 + 1 < a1) second = residual_at(a0 + 1);
+    mine = first + second;
   }
-  // exclusive prefix over the threads (fp64): wave scan, then the 16 wave totals
-  double inc = mine;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double v = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += v;
-  }
+  // exclusive prefix over the threads (fp64): wave scan, then the wave totals
+  const double inc = scan(mine);
   if (lane == 63) wsum[wv] = inc;
   __syncthreads();
-  double before = sh_prefix;
-  for (int k = 0; k < wv; ++k) before += wsum[k];
-  before += inc - mine;
-  // over the own words again: the first word at which the running sum passes the target, and the last
-  // word with any mass.  A thread that starts beyond the target reports its first word; the minimum over all
-  // threads is the crossing.  If rounding leaves the target just past the chunk, the last word with mass is it.
+  double run = sh_prefix;
+  for (int k = 0; k < wv; ++k) run += wsum[k];
+  run += inc - mine;
+  before[tid] = run;
   const double target = sh_target;
-  double run = before;
-  int hit = 0x7fffffff, last = -1;
-  auto step = [&](int w, double r) {
-    if (r > 0.0) last = w;
-    run += r;
-    if (hit == 0x7fffffff && run > target && r > 0.0) hit = w;
-  };
-  if (per <= 2) {
-    step(a0, r8[0]);
-    step(a0 + 1, r8[1]);                                  // no mass where it is another thread's or beyond the chunk
-  } else if (per == 8) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) step(a0 + e, r8[e]);
-  } else {
-    for (int w = a0; w < a1; ++w) step(w, residual_at(w));
+  if (mine > 0.0) {
+    if (run + mine > target) atomicMin(&sh_cross, tid);
+    atomicMax(&sh_last, tid);
   }
-  if (hit != 0x7fffffff) atomicMin(&sh_found, hit);
-  if (last >= 0) atomicMax(&sh_last, last);
   __syncthreads();
-  if (tid == 0) corr[s] = sh_found != 0x7fffffff ? sh_found : (sh_last >= 0 ? sh_last : w1 - 1);
+  // the first word of the crossing thread at which the running sum passes the target.  If rounding leaves the target just past
+  // the chunk or the thread's words, the last word with any mass before it
+  const int owner = sh_cross < T ? sh_cross : sh_last;
+  if (!vectors) {
+    if (tid == (owner < 0 ? 0 : owner))
+      corr[s] = owner < 0 ? w1 - 1 : second > 0.0 && !(sh_cross < T && first > 0.0 && run + first > target) ? a0 + 1 : a0;
+    return;
+  }
+  if (wv != 0) return;
+  int hit = -1, last = w1 - 1;
+  if (owner >= 0) {
+    const int b0 = w0 + owner * per, b1 = min(w1, b0 + per);
+    double sum = before[owner];
+    for (int w = b0; w < b1 && hit < 0; w += 64) {
+      const double r = w + lane < b1 ? residual_at(w + lane) : 0.0;
+      const double upto = sum + scan(r);
+      const unsigned long long over = __ballot(r > 0.0 && upto > target), mass = __ballot(r > 0.0);
+      if (over) hit = w + __ffsll((long long)over) - 1;
+      if (mass) last = w + 63 - __clzll((long long)mass);
+      sum = __shfl(upto, 63, 64);
+    }
+  }
+  if (lane == 0) corr[s] = hit >= 0 ? hit : last;
+}
+
+// One workgroup per sequence; 64 registers, so that a compute unit holds two of them.
+template <int DT>
+__global__ __launch_bounds__(ST, 8) void verify_sample_kernel(const void* __restrict__ zt, const void* __restrict__ zd, int L, int V,
+                                                              int rlen, int rchunks, const int32_t* __restrict__ n_acc,
+                                                              const double* __restrict__ rowmax, const double* __restrict__ rowsum,
+                                                              const float* __restrict__ u_res, int32_t* __restrict__ corr) {
+  const int s = blockIdx.x, t = n_acc[s];
+  if (t >= L) { if (threadIdx.x == 0) corr[s] = -1; return; }
+  sample<DT, ST>(zt, zd, s, ((long)s * L + t) * V, V, rlen, rchunks, rowmax[s * 4], rowmax[s * 4 + 1], rowsum + (long)s * rchunks * 4, u_res[s], corr);
+}
+
+// All of it for a few sequences, grid (rchunks, S).  The workgroup that finds the others of its sequence done draws the
+// correction; nobody waits.
+template <int DT>
+__global__ __launch_bounds__(FT, 4) void verify_few_kernel(const void* __restrict__ zt, const void* __restrict__ zd, const int32_t* __restrict__ tok,
+                                                           const float* __restrict__ u_acc, const float* __restrict__ u_res, int L, int V,
+                                                           int chunks, int group, const double* __restrict__ stats, int rlen, int rchunks,
+                                                           double* rowsum, int* done, int32_t* __restrict__ n_acc,
+                                                           float* __restrict__ alpha_out, int32_t* __restrict__ corr) {
+  __shared__ double sh[64 * 3];
+  __shared__ int sh_rej[64], sh_last;
+  const int s = blockIdx.y, c = blockIdx.x;
+  const int t = accept<DT, FT>(zt, zd, tok, u_acc, s, L, V, chunks, group, stats, alpha_out, c == 0, sh, sh_rej);
+  if (c == 0 && threadIdx.x == 0) {
+    n_acc[s] = t;
+    if (t >= L) corr[s] = -1;
+  }
+  if (t >= L) return;
+  const long base = ((long)s * L + t) * V;
+  const double mt = sh[t * 3], md = sh[t * 3 + 1];
+  double* sums = rowsum + (long)s * rchunks * 4;
+  residual_masses<DT, FT>(zt, zd, base, c * rlen, min(V, (c + 1) * rlen), mt, md, sh[t * 3 + 2], sums + 4 * c);
+  if (threadIdx.x < 64) {
+    __builtin_amdgcn_s_waitcnt(0x0070);              // this wave's sums are where the others see them before the count says so
+    if (threadIdx.x == 0) {
+      const int before = __hip_atomic_fetch_add(done + s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (before == rchunks - 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      sh_last = before == rchunks - 1 ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  if (sh_last) sample<DT, FT>(zt, zd, s, base, V, rlen, rchunks, mt, md, sums, u_res[s], corr);
 }
 
 }  // namespace
@@ -394,17 +440,22 @@ static hipError_t launch_verify_t(const void* zt, const void* zd, const int32_t*
   verify_plan(S, L, V, DT, &clen, &chunks);
   residual_plan(S, V, &rlen, &rchunks);
   double* stats = (double*)ws;                               // [S*L][chunks][4]
-  double* rowmax = stats + (size_t)S * L * chunks * 4;       // [S][4]
+  double* rowmax = stats + (size_t)S * L * chunks * 4;       // [S][4]; few sequences: [S] workgroups that have their sums in memory
   double* rowsum = rowmax + (size_t)S * 4;                   // [S][rchunks][4]
+  int* done = (int*)rowmax;
+  const double *cstats = stats, *crowmax = rowmax, *crowsum = rowsum;
+  const int32_t* cn = n_acc;
   int group = 1;
   while (group < chunks) group *= 2;                         // chunks <= 64
-  hipLaunchKernelGGL((verify_stats_kernel<DT>), dim3(chunks, S * L), dim3(VT), 0, st, zt, zd, V, clen, chunks, stats);
-  hipLaunchKernelGGL((verify_accept_kernel<DT>), dim3(S), dim3(64 * AW), 0, st, zt, zd, tok, u_acc, L, V, chunks, group, (const double*)stats,
-                     n_acc, alpha, rowmax);
-  hipLaunchKernelGGL((verify_rowpass64_kernel<DT>), dim3(rchunks, S), dim3(VT), 0, st, zt, zd, L, V, rlen, rchunks, (const int32_t*)n_acc,
-                     (const double*)rowmax, rowsum);
-  hipLaunchKernelGGL((verify_sample_kernel<DT>), dim3(S), dim3(1024), 0, st, zt, zd, L, V, rlen, rchunks, (const int32_t*)n_acc,
-                     (const double*)rowmax, (const double*)rowsum, u_res, corr);
+  hipLaunchKernelGGL((verify_stats_kernel<DT>), dim3(chunks, S * L), dim3(VT), 0, st, zt, zd, V, clen, chunks, L, stats, done);
+  if ((long)S * rchunks <= kFewGroups) {
+    hipLaunchKernelGGL((verify_few_kernel<DT>), dim3(rchunks, S), dim3(FT), 0, st, zt, zd, tok, u_acc, u_res, L, V, chunks, group, cstats, rlen,
+                       rchunks, rowsum, done, n_acc, alpha, corr);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((verify_accept_kernel<DT>), dim3(S), dim3(64 * AW), 0, st, zt, zd, tok, u_acc, L, V, chunks, group, cstats, n_acc, alpha, rowmax);
+  hipLaunchKernelGGL((verify_rowpass64_kernel<DT>), dim3(rchunks, S), dim3(VT), 0, st, zt, zd, L, V, rlen, rchunks, cn, crowmax, rowsum);
+  hipLaunchKernelGGL((verify_sample_kernel<DT>), dim3(S), dim3(ST), 0, st, zt, zd, L, V, rlen, rchunks, cn, crowmax, crowsum, u_res, corr);
   return hipGetLastError();
 }
 

@@ -113,6 +113,18 @@ def test_verify_time_does_not_grow_with_the_positions():
     assert took[1] < 1.4 * took[0], took
 
 
+@pytest.mark.parametrize("S,L,V,dtype", [(8, 5, 32768 - 8, I.BF16), (9, 5, 32768 - 8, I.BF16), (3, 64, 4096, I.FP32), (2, 3, 2048 * 64, I.FP16), (5, 1, 8, I.BF16)],
+                         ids=["most-workgroups", "one-more", "many-positions", "vectors-per-thread", "smallest"])
+def test_verify_few_sequences(S, L, V, dtype):
+    """The launch that takes acceptance, masses and draw together, at the edges of its range; a second call on the same buffers
+    counts its workgroups anew."""
+    d = I.make_verify_batch(S, L, V, dtype, seed=3 * S + V, disagreement=0.8)
+    n_acc, corr, alpha = _run(d, dtype)
+    _check(d, dtype, n_acc, corr, alpha)
+    n2, c2, a2 = _run(d, dtype)
+    assert np.array_equal(n2, n_acc) and np.array_equal(c2, corr) and np.array_equal(a2, alpha)
+
+
 @pytest.mark.parametrize("S,L", [(1, 1), (1, 8), (37, 3), (300, 1)])
 def test_verify_batch_shapes(S, L):
     """One row (64 chunks of the row), many sequences (one chunk per row), odd counts."""
