@@ -10,7 +10,7 @@
 // Four kernels:
 //   gemm64_kernel        any of the storage types, row lists, any K and alignment: 64 x 64 tiles, operands converted to fp64 on
 //                        their way through registers into LDS.
-//   gemm64_dma_kernel    fp64 x fp64 (the block iteration): direct-to-LDS loads, tiles of 64 x 64 to 32 x 32.
+//   gemm64_dma_kernel    fp64 x fp64 (the block iteration) and bf16 x bf16: direct-to-LDS loads, tiles of 64 x 64 to 32 x 32.
 //   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
 //   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
 // gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
@@ -214,11 +214,14 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 // multiplied.  KS = 2: a second group of four waves takes the other half of k in a ring of its own and the halves are added at the
 // end, for problems with no more tiles than compute units, where one wave per SIMD cannot hide its own waits.
 // Bound by the fp64 MFMA: a 64 x 64 tile keeps a compute unit busy for K / 32 us, so what decides is how evenly the tiles go into the
-// compute units (launch_plain_f64).  us, tiles of 64 x 64 / 64 x 32 / 32 x 32, and the time at the rate of a loop of nothing but
+// compute units (launch_plain).  us, tiles of 64 x 64 / 64 x 32 / 32 x 32, and the time at the rate of a loop of nothing but
 // these MFMAs (67.6 TFLOP/s): 192 x 1664 x 1664, batch 4 114 / 91 / 88 (63); 384 x 1152 x 1152, batch 8 159 / 149 / 166 (121);
 // 256 x 640 x 640, batch 64 235 / 260 / 277 (199); 192 x 1280 x 1280, batch 4 50 / 50 / 54 (37).
 // A symmetric product (lower_only, frag; TM = TN) has a workgroup for each tile on and below its diagonal only.
-// Requires K % 16 == 0, even pitches, 16-byte aligned bases.  Rows beyond M / N are clamped when loading.
+// TS = bf16 (the Gram matrix of the greedy picks, row lists): the same 128-byte pieces of a row are 64 k, converted between LDS and
+// MFMA, which the MFMAs hide.  Staged through registers and converted into LDS, one k-tile of 16 in flight, six of
+// 926 x 926 x 2048 took 308 us, so 230.
+// Requires whole k-tiles (16 or 64), pitches of whole pieces, 16-byte aligned bases.  Rows beyond M / N are clamped when loading.
 // A Chebyshev step (GemmArgs::cheb) is scale * (A B + start): the accumulators begin with the terms that are not the product,
 // whose loads are over before the first operands have landed (read behind the product they cost 30 of 260 us, see below).
 __device__ __forceinline__ double cheb_scale(const GemmArgs& g, double t) { return t == 0.0 ? 1.0 : g.cheb_step == 0 ? t : 2.0 * t; }
@@ -227,10 +230,24 @@ __device__ __forceinline__ double cheb_start(const GemmArgs& g, const double* A,
   return -rt * (g.cheb_step == 0 ? a : fma(0.5, C[(long)r * g.ldc + c], a));
 }
 
-template <int KS, int TM, int TN>
+// A 16-byte piece of a row and its elements as fp64.
+template <typename TS> struct Piece;
+template <> struct Piece<double> {
+  typedef f64x2_t type;
+  static __device__ __forceinline__ double at(const type& v, int e) { return v[e]; }
+};
+template <> struct Piece<bf16_t> {
+  typedef u32x4_t type;
+  static __device__ __forceinline__ double at(const type& v, int e) { return (double)__uint_as_float(e & 1 ? v[e >> 1] & 0xFFFF0000u : v[e >> 1] << 16); }
+};
+
+template <typename TS, int KS, int TM, int TN>
 __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr int NST = 4, STAGE = (TM + TN) * 128;   // bytes: A tile then B tile
   constexpr int MI = TM / 32, NJ = TN / 32;         // 16 x 16 tiles of a wave, and its loads per operand and stage
+  constexpr int PE = 16 / sizeof(TS), KT = 8 * PE;  // elements of a piece and of a k-tile
+  constexpr bool F64 = std::is_same<TS, double>::value;
+  typedef typename Piece<TS>::type piece_t;
   extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
   const int tid = threadIdx.x & 255, grp = threadIdx.x >> 8, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, i16 = lane & 15, kq = lane >> 4;
@@ -253,25 +270,31 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   }
   const int row0 = tm * TM, col0 = tn * TN;
   const bool moved = g.sel && g.sel[b];
-  const double* A = (const double*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
-  const double* B = (const double*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
-  const int nk = g.K >> 4, nk0 = (nk + KS - 1) / KS, kt0 = grp * nk0;
+  const TS* A = (const TS*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
+  const TS* B = (const TS*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
+  const int nk = g.K / KT, nk0 = (nk + KS - 1) / KS, kt0 = grp * nk0;
   const int mine = nk - kt0 < nk0 ? (nk - kt0 > 0 ? nk - kt0 : 0) : nk0;      // k-tiles of this group
 
   // wave w issues MI loads of A and NJ of B per stage; load j of A fills tile rows 8 (MI w + j) .. +7: lane l -> row + l / 8,
   // 16-byte slot l % 8, which holds the row's piece (l % 8) ^ (row % 8)
-  const double* ga[MI];
-  const double* gb[NJ];
-  const int lr = lane >> 3, lc = 2 * ((lane & 7) ^ (lane >> 3));
+  const TS* ga[MI];
+  const TS* gb[NJ];
+  const int lr = lane >> 3, lc = PE * ((lane & 7) ^ (lane >> 3));
+  auto row_of = [&](int r, int rows, const int32_t* list, long stride) -> long {
+    const int at = min(r, rows - 1);
+    return !F64 && list ? (long)list[(long)b * stride + at] : (long)at;
+  };
 #pragma unroll
-  for (int j = 0; j < MI; ++j) ga[j] = A + (long)min(row0 + 8 * (MI * wave + j) + lr, g.M - 1) * g.lda + lc + 16 * (long)kt0;
+  for (int j = 0; j < MI; ++j)
+    ga[j] = A + row_of(row0 + 8 * (MI * wave + j) + lr, g.M, g.gatherA, g.gstrideA) * g.lda + lc + KT * (long)kt0;
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) gb[j] = B + (long)min(col0 + 8 * (NJ * wave + j) + lr, g.N - 1) * g.ldb + lc + 16 * (long)kt0;
+  for (int j = 0; j < NJ; ++j)
+    gb[j] = B + row_of(col0 + 8 * (NJ * wave + j) + lr, g.N, g.gatherB, g.gstrideB) * g.ldb + lc + KT * (long)kt0;
   unsigned char* base = ring + grp * (NST * STAGE);
   const int last = mine > 0 ? mine - 1 : 0;
   auto issue = [&](int kt) {
     // past the end: the last k-tile again (a group without any: the one before it), into a stage that is never read
-    const long at = 16 * (long)(mine == 0 ? -1 : kt < last ? kt : last);
+    const long at = KT * (long)(mine == 0 ? -1 : kt < last ? kt : last);
     unsigned char* sa = base + (kt & (NST - 1)) * STAGE + wave * (MI * 1024);
     unsigned char* sb = base + (kt & (NST - 1)) * STAGE + TM * 128 + wave * (NJ * 1024);
 #pragma unroll
@@ -284,20 +307,20 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
                                        (__attribute__((address_space(3))) void*)(sb + j * 1024), 16, 0, 0);
   };
   double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
-  const double t = g.cheb ? g.cheb[(long)b * g.cheb_stride] : 0.0, scale = cheb_scale(g, t), rt = 1.0 / t;
+  const double t = F64 && g.cheb ? g.cheb[(long)b * g.cheb_stride] : 0.0, scale = cheb_scale(g, t), rt = 1.0 / t;
   f64x4_t acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-      if (t != 0.0 && grp == 0) {
+      if constexpr (F64) if (t != 0.0 && grp == 0) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           acc[i][j][v] = cheb_start(g, A, C, rt, min(row0 + wm * (16 * MI) + i * 16 + 4 * v + kq, g.M - 1), min(col0 + wn * (16 * NJ) + j * 16 + i16, g.N - 1));
       }
     }
-  // fragment of row R, half h: piece kq + 4h, i.e. k = 2 (kq + 4h) + {0, 1}; R % 8 == i16 % 8 for every fragment row
+  // fragment of row R, half h: piece kq + 4h, i.e. k = PE (kq + 4h) + 0 .. PE - 1; R % 8 == i16 % 8 for every fragment row
   int offA[2], offB[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -305,25 +328,26 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
     offA[h] = (wm * (16 * MI) + i16) * 128 + piece;
     offB[h] = TM * 128 + (wn * (16 * NJ) + i16) * 128 + piece;
   }
-  auto frags = [&](int kt, int h, f64x2_t (&fa)[MI], f64x2_t (&fb)[NJ]) {
+  auto frags = [&](int kt, int h, piece_t (&fa)[MI], piece_t (&fb)[NJ]) {
     const unsigned char* st = base + (kt & (NST - 1)) * STAGE;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) fa[i] = *(const f64x2_t*)(st + offA[h] + i * 2048);
+    for (int i = 0; i < MI; ++i) fa[i] = *(const piece_t*)(st + offA[h] + i * 2048);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) fb[j] = *(const f64x2_t*)(st + offB[h] + j * 2048);
+    for (int j = 0; j < NJ; ++j) fb[j] = *(const piece_t*)(st + offB[h] + j * 2048);
   };
-  auto mma = [&](const f64x2_t (&fa)[MI], const f64x2_t (&fb)[NJ]) {
+  auto mma = [&](const piece_t (&fa)[MI], const piece_t (&fb)[NJ]) {
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < PE; ++e)
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(Piece<TS>::at(fa[i], e), Piece<TS>::at(fb[j], e), acc[i][j], 0, 0, 0);
   };
   // Per k-tile: wait until the next one has landed (only the loads of the one after it may be outstanding), barrier,
   // start the loads three ahead into the stage that held the previous one (every wave's reads of it are complete before it
   // arrives at the barrier).
-  f64x2_t a0[MI], b0[NJ], a1[MI], b1[NJ];
+  piece_t a0[MI], b0[NJ], a1[MI], b1[NJ];
   issue(0);
   issue(1);
   issue(2);
@@ -599,7 +623,7 @@ hipError_t launch_small(const GemmArgs& g, hipStream_t stream) {
 
 inline long tiles64(const GemmArgs& g) { return (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch; }
 
-template <int KS, int TM, int TN>
+template <typename TS, int KS, int TM, int TN>
 hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
   const long tm = (g.M + TM - 1) / TM, tn = (g.N + TN - 1) / TN;
   const bool triangle = g.lower_only || g.frag;
@@ -609,10 +633,10 @@ hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
   constexpr size_t kRing = (size_t)KS * 4 * (TM + TN) * 128;
   if (kRing > 64 * 1024) {
     static PerDeviceInt raised;
-    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<KS, TM, TN>, kRing);
+    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<TS, KS, TM, TN>, kRing);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((gemm64_dma_kernel<KS, TM, TN>), dim3((unsigned)blocks), dim3(256 * KS), kRing, stream, g, (int)tm, (int)tn);
+  hipLaunchKernelGGL((gemm64_dma_kernel<TS, KS, TM, TN>), dim3((unsigned)blocks), dim3(256 * KS), kRing, stream, g, (int)tm, (int)tn);
   return hipGetLastError();
 }
 
@@ -621,7 +645,8 @@ hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
 // figures at the kernel and, us, 64 x 64 / 64 x 32 / 32 x 32: 320 x 1024 x 1024, batch 4 73 / 58 / 56; 256 x 832 x 832, batch 16
 // 117 / 109 / 110; 384 x 1280 x 1280, batch 12 260 / 270 / 300; 256 x 1024 x 1024, batch 2 39 / 25 / 26; 192 x 384 x 384, batch 3
 // 17 / 11 / 8; symmetric products 192 x 192 x 1664, batch 4 59 / - / 24; 256 x 256 x 640, batch 64 88 / - / 77.
-hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
+template <typename TS>
+hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
   const bool triangle = g.lower_only || g.frag;
   if ((triangle && g.M != g.N) || (g.frag && g.N % 64 != 0)) return hipErrorInvalidValue;
   const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64;
@@ -629,15 +654,17 @@ hipError_t launch_plain_f64(const GemmArgs& g, hipStream_t stream) {
   const long t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
   const double c64 = 4.0 * fullest((triangle ? m64 * (m64 + 1) / 2 : m64 * n64) * g.batch);
   const double c32 = 1.2 * fullest(t32), c48 = triangle ? c32 : 2.0 * 1.06 * fullest(m64 * n32 * g.batch);
-  if (c64 <= c32 && c64 <= c48) return launch_dma<1, 64, 64>(g, stream);
-  if (c48 < c32) return launch_dma<1, 64, 32>(g, stream);
-  return t32 <= kUnits && g.K >= 32 ? launch_dma<2, 32, 32>(g, stream) : launch_dma<1, 32, 32>(g, stream);
+  if (c64 <= c32 && c64 <= c48) return launch_dma<TS, 1, 64, 64>(g, stream);
+  if (c48 < c32) return launch_dma<TS, 1, 64, 32>(g, stream);
+  return t32 <= kUnits && g.K >= (int)(256 / sizeof(TS)) ? launch_dma<TS, 2, 32, 32>(g, stream) : launch_dma<TS, 1, 32, 32>(g, stream);
 }
 
-// Products the two kernels above take.
-inline bool plain_f64(const GemmArgs& g) {
-  return g.batch > 0 && g.batch_inner == 1 && g.K >= 16 && g.K % 16 == 0 && g.lda % 2 == 0 && g.ldb % 2 == 0 && g.strideA % 2 == 0 &&
-         g.strideB % 2 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
+// Products gemm64_dma_kernel takes.
+template <typename TS>
+inline bool plain(const GemmArgs& g) {
+  constexpr int PE = 16 / sizeof(TS);
+  return g.batch > 0 && g.batch_inner == 1 && g.K >= 8 * PE && g.K % (8 * PE) == 0 && g.lda % PE == 0 && g.ldb % PE == 0 && g.strideA % PE == 0 &&
+         g.strideB % PE == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
 }
 
 template <typename TA, typename TB, int EPI, bool GATHER, int MI, int NJ>
@@ -669,8 +696,13 @@ hipError_t launch_ab(const GemmArgs& g, hipStream_t stream) {
     if (g.epilogue == EPI_STORE_F64 && tiles64(g) <= kSmallTiles64 && small_fits(g)) return launch_small<TA, TB, EPI_STORE_F64>(g, stream);
   }
   if (g.epilogue == EPI_STORE_F64) {
+    if constexpr (std::is_same<TA, bf16_t>::value) {
+      if (plain<bf16_t>(g) && (!g.lower_only || g.M == g.N)) return launch_plain<bf16_t>(g, stream);
+    }
     if (gather) return launch_cfg<TA, TB, EPI_STORE_F64, true, 2, 2>(g, stream);
-    if (f64x2 && plain_f64(g)) return launch_plain_f64(g, stream);
+    if constexpr (f64x2) {
+      if (plain<double>(g)) return launch_plain<double>(g, stream);
+    }
     if (g.frag || g.sel || g.cheb) return hipErrorInvalidValue;
     return launch_cfg<TA, TB, EPI_STORE_F64, false, 2, 2>(g, stream);
   }

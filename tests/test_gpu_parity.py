@@ -412,6 +412,25 @@ def test_greedy_runs_of_picks(C, kind, n, d, k):
     assert len(set(_cpu(out["idx"])[0].tolist())) == k
 
 
+@pytest.mark.parametrize("B,n,d", [(1, 40, 64), (2, 65, 128), (3, 700, 192), (7, 1000, 320), (2, 300, 72), (1, 33, 448)],
+                         ids=["one-k-tile", "k-halves", "small-tiles", "large-tiles", "width-not-64", "odd-k-tiles"])
+def test_greedy_picks_from_bf16_rows(C, B, n, d):
+    """The fp64 Gram matrix of bf16 rows, which the residuals show: its tiles, k-tiles of 64 and the general kernel beyond them."""
+    import torch
+    X = torch.randn(B, n, d, generator=torch.Generator().manual_seed(n)) * 0.97 ** torch.arange(d)
+    X = X.to(torch.bfloat16)
+    sf = np.random.default_rng(3).random((B, n)).astype(np.float32)
+    k = min(n, d) // 2
+    m = n - 3                                              # rows that the Gram matrix leaves out
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.BF16, lr_mode=C.LR_GREEDY_RESIDUAL, keep_k=k, preselect_m=m, rank_r=1)
+    out = C.select(p, X.cuda(), torch.from_numpy(sf).cuda())
+    for b in range(B):
+        ref = O.select(X[b].double().numpy(), sf[b], O.Params(lr_mode=1, keep_k=k, preselect_m=m, rank_r=1))
+        np.testing.assert_array_equal(_cpu(out["pick_order"])[b], ref["pick_order"])
+        # the rounding of the largest squared length once a pick, and of the result to fp32
+        np.testing.assert_allclose(_cpu(out["resid"])[b].astype(np.float64), ref["resid"], rtol=1e-6, atol=1.1e-16 * k * ref["resid"][0])
+
+
 def test_greedy_picks_with_rows_that_are_not_finite(C):
     """An infinite token is the largest; whatever its column does to the others, the picks stay distinct positions."""
     import torch
