@@ -340,7 +340,7 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
   // token Gram matrix of the pre-selected rows, fp64, zero-padded to the pitch
   marks.mark(COVSPEC_STAGE_GRAM);
   double* A = at<double>(ws, q.Awork);
-  HIPCHK(launch_fill_zero(A, (size_t)q.B * q.nP * q.nP * 8, st));
+  HIPCHK(launch_zero_padding(A, q.B, q.M, q.nP, st));
   GemmArgs g;
   g.A = X; g.B = X; g.C = A; g.M = q.M; g.N = q.M; g.K = q.d; g.lda = d; g.ldb = d; g.ldc = q.nP;
   g.batch = q.B; g.strideA = N * d; g.strideB = N * d; g.strideC = (long)q.nP * q.nP;
@@ -807,7 +807,7 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
   HIPCHK(launch_stream_ids(id_in, idxf, idc, q.B, n_keep, q.M, q.k, id_base, st));
 
   // 2. Gram matrix of the candidates: the kept block is carried, the rows of the arriving tokens are computed
-  HIPCHK(launch_fill_zero(Gc, (size_t)q.B * gstride * 8, st));
+  HIPCHK(launch_zero_padding(Gc, q.B, nC, q.nP, st));
   HIPCHK(launch_copy_block(Gc, q.nP, gstride, G_in, q.k, (long)q.k * q.k, n_keep, q.B, st));
   GemmArgs g;
   g.A = X_frame; g.lda = d; g.strideA = (long)q.N * d; g.gatherA = idxf; g.gstrideA = q.M;
@@ -834,14 +834,14 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
   if (nC > q.k) {
     double* A = at<double>(ws, q.A);
     float* c = c_out ? c_out : at<float>(ws, q.c);
-    HIPCHK(hipMemcpyAsync(A, Gc, (size_t)q.B * gstride * 8, hipMemcpyDeviceToDevice, st));   // the solve may overwrite its input
     const int P = subspace_block(nC, q.r);
     int* ok = nullptr;
     if (P > 0 || split_direct(q.nP)) {
       ok = at<int>(ws, q.ok);
-      HIPCHK(launch_subspace_eigen(A, q.B, nC, q.nP, q.r, P, at<void>(ws, q.sub), ok, c, nullptr, nullptr,
+      HIPCHK(launch_subspace_eigen(Gc, q.B, nC, q.nP, q.r, P, at<void>(ws, q.sub), ok, c, nullptr, nullptr,
                                    nullptr, st));
     }
+    HIPCHK(launch_copy_images(A, Gc, q.B, gstride, ok, st));      // the full solve overwrites its input
     HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, st));
     HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, ok, 0, st));
     int32_t* selw = at<int32_t>(ws, q.sel);

@@ -121,7 +121,10 @@ hipError_t launch_fuse(const float* s_query, const float* s_act, float* s_fused,
 hipError_t launch_gather_rows(const void* X, const int32_t* idx, void* out, int B, int N, int k, long row_bytes,
                               hipStream_t stream);
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
+// Zeroes rows and columns n .. pitch - 1 of B matrices (pitch x pitch).
+hipError_t launch_zero_padding(double* A, int B, int n, int pitch, hipStream_t stream);
+// dst[b] = src[b] (`each` doubles, even; 16-byte aligned) but for images b with leave[b] != 0 (leave may be null).
+hipError_t launch_copy_images(double* dst, const double* src, int B, long each, const int* leave, hipStream_t stream);
 hipError_t launch_fill_int(int* p, int n, int value, hipStream_t stream);
 
 // Reproducible uniform scores for the random-selection ablation: out[b, i] = top 24 bits of
