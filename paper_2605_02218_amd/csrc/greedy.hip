@@ -6,8 +6,8 @@
 // argmax rho (decided on the fp32-rounded value, ties -> lower index), forms the new
 // Cholesky column l = (G[:,p] - L L[p,:]^T) / sqrt(rho_p) and updates rho -= l^2.
 //
-// Three kernels, chosen by launch_greedy from the values each would move: the right-looking panel kernel
-// (greedy_panel_kernel, the usual choice), and two left-looking ones for the case that the picks are a small
+// Four kernels, chosen by launch_greedy from the values each would move: the right-looking panel kernels
+// (greedy_panel_kernel, the usual choice, and greedy_step_kernel for many rows), and two left-looking ones for the case that the picks are a small
 // part of the rows, on several workgroups per image (greedy_kernel) or one (greedy_single_kernel).
 //
 // Left-looking on several workgroups (greedy_kernel).  The k steps are dependent, but inside a step the rows are
@@ -247,8 +247,8 @@ __global__ __launch_bounds__(TPB) void greedy_single_kernel(const double* __rest
   }
 }
 
-// Right-looking in blocks of BK picks, an image of up to 4096 rows spread over W workgroups of 1024 threads (thread
-// tid owns the NR rows tid, tid + 1024, ...).  The residual matrix R = G - L L^T is kept in global memory IN PLACE of G and
+// Right-looking in blocks of BK picks, an image of up to 4096 rows spread over W workgroups of 1024 threads (a thread
+// owns NR rows, 1024 apart).  The residual matrix R = G - L L^T is kept in global memory IN PLACE of G and
 // brought up to date once per block by a rank-BK update on the MFMA; inside a block a new column is the pivot's
 // row of R minus the product with the block's earlier columns, which live in LDS.  The left-looking kernels above
 // re-read every earlier column at every step (k^2 n / 2 values); this one reads one row of R per step and reads
@@ -381,6 +381,59 @@ __device__ __forceinline__ void run_columns(double (&c)[BK], const GreedyRun& ru
   }
 }
 
+// End of a block of BK picks: the workgroups of the image meet, each brings its bands of R up to date, R -= Lblk^T Lblk, and they meet
+// again; Lblk is cleared.  False when a wait ran out.
+template <int BK>
+__device__ __forceinline__ bool update_rows(double* R, double* Lblk, int n, int nP, int W, int slot, ImageBarrier* bar, unsigned int& target, int* s_flag,
+                                            long long limit_ticks) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+  // every workgroup of the image has read its last row of the old R (the wait starts with a barrier of
+  // the workgroup, behind which the block's columns are complete in LDS)
+  target += (unsigned int)W;
+  if (!image_barrier_wait<false>(bar, target, s_flag, limit_ticks)) return false;
+  // ---- R -= Lblk^T Lblk on this workgroup's bands (band ti belongs to slot ti % W); a wave takes four
+  //      neighbouring 16 x 16 tiles per trip and requests their 16 values of R before the first MFMA
+  const int nt = (n + 15) >> 4;
+  const int bands = (nt - slot + W - 1) / W;
+  const int ntiles = bands * nt;
+  for (int tile0 = 4 * w; tile0 < ntiles; tile0 += 4 * (TPB / 64)) {
+    double* out[4];
+    double r[4][4];
+    int ti[4], tj[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int tile = tile0 + u;
+      const int tc = tile < ntiles ? tile : tile0;          // a trailing slot repeats the first tile, result unused
+      const int band = tc / nt;
+      ti[u] = slot + band * W;
+      tj[u] = tc - band * nt;
+      // lane (i16, kq), register v: row 16 ti + 4v + kq, column 16 tj + i16 (inside the nP x nP buffer: nP % 64 == 0)
+      out[u] = R + (long)(16 * ti[u] + kq) * nP + 16 * tj[u] + i16;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) r[u][v] = out[u][(long)(4 * v) * nP];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      f64x4_t d = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s4 = 0; s4 < BK / 4; ++s4)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(Lblk[(4 * s4 + kq) * nP + 16 * ti[u] + i16], Lblk[(4 * s4 + kq) * nP + 16 * tj[u] + i16], d,
+                                                 0, 0, 0);
+      if (tile0 + u < ntiles) {
+        // through the L2, so that the barrier has nothing to write back (6 of 26 us per update of six images of 926 rows)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) store_through(out[u] + (long)(4 * v) * nP, r[u][v] - d[v]);
+      }
+    }
+  }
+  // every band is up to date before any workgroup reads a row of R again
+  target += (unsigned int)W;
+  if (!image_barrier_wait<false>(bar, target, s_flag, limit_ticks)) return false;
+  for (int e = tid; e < BK * nP; e += TPB) Lblk[e] = 0.0;
+  __syncthreads();
+  return true;
+}
+
 template <int BK, int NR, int CAND>
 __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int nP, int k, int W, int32_t* __restrict__ order,
                                                             float* __restrict__ resid, GreedyCtl* ctl, int* img_status,
@@ -397,12 +450,15 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
   const int b = ticket / W, slot = ticket - b * W;
   GreedyCtl* cb = ctl + b;
   double* R = G + (long)b * nP * nP;
+  // row0, row0 + 1024, ... are this thread's rows.  Few rows are dealt to all waves, sixteen neighbours (a 128-byte piece of a row of R)
+  // at a time: of the rows of one wave only eight become candidates.
+  const int row0 = n <= TPB / 2 ? (lane >> 4) * (TPB / 4) + 16 * w + i16 : tid;
 
   double rho[NR];
   bool picked[NR];
 #pragma unroll
   for (int s = 0; s < NR; ++s) {
-    const int i = tid + TPB * s;
+    const int i = row0 + TPB * s;
     rho[s] = (i < n) ? R[(long)i * nP + i] : 0.0;
     picked[s] = !(i < n);
   }
@@ -421,11 +477,11 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
 #pragma unroll 1
       for (int e = 0; e <= kWaveBest; ++e) {
         uint32_t mine = key[0];
-        int row = tid;
+        int row = row0;
         double r = rho[0];
 #pragma unroll
         for (int s = 1; s < NR; ++s)
-          if (key[s] > mine) { mine = key[s]; row = tid + TPB * s; r = rho[s]; }
+          if (key[s] > mine) { mine = key[s]; row = row0 + TPB * s; r = rho[s]; }
         const uint32_t best = wave_max_u32(mine);
         if (e == kWaveBest) {
           if (lane == 0) run.left[w] = best;
@@ -436,7 +492,7 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
           run.post_rho[kWaveBest * w + e] = r;
 #pragma unroll
           for (int s = 0; s < NR; ++s)
-            if (row == tid + TPB * s) key[s] = 0u;
+            if (row == row0 + TPB * s) key[s] = 0u;
         }
       }
     }
@@ -517,7 +573,7 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
       double c[NR][BK];
 #pragma unroll
       for (int s = 0; s < NR; ++s) {
-        const int i = tid + TPB * s;
+        const int i = row0 + TPB * s;
 #pragma unroll
         for (int m = 0; m < BK; ++m) {
           c[s][m] = 0.0;
@@ -532,13 +588,13 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
         const double factors = Lblk[q * nP + mine];
 #pragma unroll
         for (int s = 0; s < NR; ++s) {
-          const int i = tid + TPB * s;
+          const int i = row0 + TPB * s;
           take_out<BK, 0, 0>(c[s], i < n ? Lblk[q * nP + i] : 0.0, factors);
         }
       }
 #pragma unroll
       for (int s = 0; s < NR; ++s) {
-        const int i = tid + TPB * s;
+        const int i = row0 + TPB * s;
         run_columns<BK, 0>(c[s], run, picks, inverses, rho[s]);
 #pragma unroll
         for (int m = 0; m < BK; ++m)
@@ -549,52 +605,144 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
     jj += picks;
     if (jj == BK && t < k) {
       jj = 0;
-      // every workgroup of the image has read its last row of the old R (the wait starts with a barrier of
-      // the workgroup, behind which the block's columns are complete in LDS)
-      target += (unsigned int)W;
-      alive = image_barrier_wait<false>(&cb->bar, target, &run.flag, limit_ticks);
+      alive = update_rows<BK>(R, Lblk, n, nP, W, slot, &cb->bar, target, &run.flag, limit_ticks);
       if (!alive) break;
-      // ---- R -= Lblk^T Lblk on this workgroup's bands (band ti belongs to slot ti % W); a wave takes four
-      //      neighbouring 16 x 16 tiles per trip and requests their 16 values of R before the first MFMA
-      const int nt = (n + 15) >> 4;
-      const int bands = (nt - slot + W - 1) / W;
-      const int ntiles = bands * nt;
-      for (int tile0 = 4 * w; tile0 < ntiles; tile0 += 4 * (TPB / 64)) {
-        double* out[4];
-        double r[4][4];
-        int ti[4], tj[4];
+    }
+  }
+  if (!alive && slot == 0) {
+    // a wait ran out: leave valid (distinct) positions and poisoned residuals behind
+    const float qnan = __uint_as_float(0x7fc00000u);
+    for (int t = tid; t < k; t += TPB) { order[(long)b * k + t] = t; resid[(long)b * k + t] = qnan; }
+    if (img_status && tid == 0) img_status[b] = 1;
+  }
+}
+
+// The same for 64-bit keys.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned long long dpp_key(unsigned long long v) {
+  const unsigned lo = __builtin_amdgcn_update_dpp(0u, (unsigned)v, CTRL, ROW_MASK, 0xf, false);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(v >> 32), CTRL, ROW_MASK, 0xf, false);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
+  unsigned long long o;
+  o = dpp_key<0xb1, 0xf>(v); v = o > v ? o : v;      // quad_perm [1,0,3,2]
+  o = dpp_key<0x4e, 0xf>(v); v = o > v ? o : v;      // quad_perm [2,3,0,1]
+  o = dpp_key<0x114, 0xf>(v); v = o > v ? o : v;     // row_shr:4
+  o = dpp_key<0x118, 0xf>(v); v = o > v ? o : v;     // row_shr:8
+  o = dpp_key<0x142, 0xa>(v); v = o > v ? o : v;     // row_bcast:15 into rows 1 and 3
+  o = dpp_key<0x143, 0xc>(v); v = o > v ? o : v;     // row_bcast:31 into rows 2 and 3
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)v, 63), hi = __builtin_amdgcn_readlane((unsigned)(v >> 32), 63);
+  return ((unsigned long long)hi << 32) | lo;
+}
+
+// The same with all rows in every step (dynamic LDS: BK * nP doubles), for images whose candidates' submatrix would cost LDS that the
+// block's columns need: see launch_greedy.
+template <int BK, int NR>
+__global__ __launch_bounds__(TPB) void greedy_step_kernel(double* G, int n, int nP, int k, int W, int32_t* __restrict__ order,
+                                                            float* __restrict__ resid, GreedyCtl* ctl, int* img_status,
+                                                            long long limit_ticks) {
+  extern __shared__ double Lblk[];        // [BK][nP]
+  __shared__ unsigned long long red[2][16];   // per wave: its best key and that row's residual, double-buffered by
+  __shared__ double red_rho[2][16];           // step parity so that a step needs one barrier only
+  __shared__ int s_flag;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (tid == 0) s_flag = (int)atomicAdd(&ctl[0].ticket, 1u);
+  __syncthreads();
+  const int ticket = s_flag;
+  __syncthreads();
+  const int b = ticket / W, slot = ticket - b * W;
+  GreedyCtl* cb = ctl + b;
+  double* R = G + (long)b * nP * nP;
+
+  double rho[NR];
+  bool picked[NR];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int tile = tile0 + u;
-          const int tc = tile < ntiles ? tile : tile0;          // a trailing slot repeats the first tile, result unused
-          const int band = tc / nt;
-          ti[u] = slot + band * W;
-          tj[u] = tc - band * nt;
-          // lane (i16, kq), register v: row 16 ti + 4v + kq, column 16 tj + i16 (inside the nP x nP buffer: nP % 64 == 0)
-          out[u] = R + (long)(16 * ti[u] + kq) * nP + 16 * tj[u] + i16;
+  for (int s = 0; s < NR; ++s) {
+    const int i = tid + TPB * s;
+    rho[s] = (i < n) ? R[(long)i * nP + i] : 0.0;
+    picked[s] = !(i < n);
+  }
+  for (int e = tid; e < BK * nP; e += TPB) Lblk[e] = 0.0;
+  unsigned int target = 0;
+  bool alive = true;
+  // the diagonal is read above and R is first written at the end of block 0, behind a barrier
+  __syncthreads();
+
+  for (int t = 0; t < k; ++t) {
+    const int jj = t % BK, par = t & 1;
+    // ---- argmax over the unpicked rows of float(rho), lowest index on ties.  Keys are distinct, so exactly one
+    //      lane of a wave holds the wave's best and posts it with its residual.  One barrier per step: what a
+    //      step writes besides is read only behind the next step's barrier, and the posts alternate buffers.
+    unsigned long long best = 0ull;
+    double brho = 0.0;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) r[u][v] = out[u][(long)(4 * v) * nP];
-        }
+    for (int s = 0; s < NR; ++s) {
+      if (!picked[s]) {
+        const unsigned long long key =
+            ((unsigned long long)float_order_key((float)rho[s]) << 32) | (0xFFFFFFFFu - (uint32_t)(tid + TPB * s));
+        if (key > best) { best = key; brho = rho[s]; }
+      }
+    }
+    {
+      const unsigned long long wbest = wave_max_key(best);
+      if (wbest == 0ull) { if (lane == 0) red[par][w] = 0ull; }
+      else if (best == wbest) { red[par][w] = wbest; red_rho[par][w] = brho; }
+    }
+    __syncthreads();
+    best = red[par][0];
+    int wq = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          f64x4_t d = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    for (int q = 1; q < TPB / 64; ++q)
+      if (red[par][q] > best) { best = red[par][q]; wq = q; }
+    const double rp = red_rho[par][wq];
+    const int p = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));     // < n: k <= n, so an unpicked row exists
+    if (best == 0ull || (unsigned)p >= (unsigned)n) {   // never index with anything else
+      if (tid == 0) __hip_atomic_store(&cb->bar.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      alive = false;
+      break;
+    }
+    if ((p & (TPB - 1)) == tid) {
 #pragma unroll
-          for (int s4 = 0; s4 < BK / 4; ++s4)
-            d = __builtin_amdgcn_mfma_f64_16x16x4f64(Lblk[(4 * s4 + kq) * nP + 16 * ti[u] + i16], Lblk[(4 * s4 + kq) * nP + 16 * tj[u] + i16], d,
-                                                     0, 0, 0);
-          if (tile0 + u < ntiles) {
-            // through the L2, so that the barrier has nothing to write back (6 of 26 us per update of six images of 926 rows)
+      for (int s = 0; s < NR; ++s)
+        if (s == (p >> 10)) picked[s] = true;
+    }
+    // ---- the pivot's row of R, minus what this block has already taken out (summed apart, so that the sum
+    //      does not wait for the row)
+    double c[NR];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) store_through(out[u] + (long)(4 * v) * nP, r[u][v] - d[v]);
-          }
+    for (int s = 0; s < NR; ++s) {
+      const int i = tid + TPB * s;
+      c[s] = (i < n) ? R[(long)p * nP + i] : 0.0;
+    }
+    {
+      double taken[NR];
+#pragma unroll
+      for (int s = 0; s < NR; ++s) taken[s] = 0.0;
+      for (int q = 0; q < jj; ++q) {
+        const double lp = Lblk[q * nP + p];
+#pragma unroll
+        for (int s = 0; s < NR; ++s) {
+          const int i = tid + TPB * s;
+          if (i < n) taken[s] = fma(Lblk[q * nP + i], lp, taken[s]);
         }
       }
-      // every band is up to date before any workgroup reads a row of R again
-      target += (unsigned int)W;
-      alive = image_barrier_wait<false>(&cb->bar, target, &run.flag, limit_ticks);
+#pragma unroll
+      for (int s = 0; s < NR; ++s) c[s] -= taken[s];
+    }
+    const double piv = rp > 0.0 ? rp : 0.0;
+    const double root = sqrt(piv);
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+      const int i = tid + TPB * s;
+      const double col = (piv > 0.0 && i < n) ? c[s] / root : 0.0;
+      if (i < nP) Lblk[jj * nP + i] = col;
+      rho[s] -= col * col;
+    }
+    if (slot == 0 && tid == 0) { order[(long)b * k + t] = p; resid[(long)b * k + t] = (float)rp; }
+    if (jj == BK - 1 && t + 1 < k) {
+      alive = update_rows<BK>(R, Lblk, n, nP, W, slot, &cb->bar, target, &s_flag, limit_ticks);
       if (!alive) break;
-      for (int e = tid; e < BK * nP; e += TPB) Lblk[e] = 0.0;
-      __syncthreads();
     }
   }
   if (!alive && slot == 0) {
@@ -638,25 +786,22 @@ size_t greedy_scratch_bytes(int B, int nP) {
 }
 
 // Columns of a block of BK picks and the candidates' submatrix, beside the kernel's static words.
-constexpr size_t kPanelLds = 160 * 1024 - sizeof(GreedyRun) - 256;
-static size_t panel_lds(int BK, int cand, int nP) { return ((size_t)BK * nP + (size_t)cand * (cand + 1)) * sizeof(double); }
+constexpr size_t kRunLds = 160 * 1024 - sizeof(GreedyRun) - 256, kStepLds = 159 * 1024;
+static size_t run_lds(int BK, int cand, int nP) { return ((size_t)BK * nP + (size_t)cand * (cand + 1)) * sizeof(double); }
 
-template <int BK, int NR, int CAND>
-static hipError_t launch_panel(double* G, int B, int n, int nP, int k, int W, int32_t* order, float* resid, GreedyCtl* ctl,
-                               int* img_status, hipStream_t st) {
-  const size_t lds = panel_lds(BK, CAND, nP);
-  if (lds > kPanelLds || n > TPB * NR) return hipErrorInvalidValue;
-  static PerDeviceInt raised, cache;   // per instantiation
-  hipError_t e = ensure_dynamic_lds(raised, (const void*)greedy_panel_kernel<BK, NR, CAND>, kPanelLds);
+template <typename K>
+static hipError_t launch_panel(K kernel, PerDeviceInt& raised, PerDeviceInt& cache, size_t lds, size_t most, double* G, int B, int n, int nP, int k, int W,
+                               int32_t* order, float* resid, GreedyCtl* ctl, int* img_status, hipStream_t st) {
+  if (lds > most) return hipErrorInvalidValue;
+  hipError_t e = ensure_dynamic_lds(raised, (const void*)kernel, most);
   if (e != hipSuccess) return e;
   // the workgroups of one image wait for one another, so one image has to fit the device; counted once per device
   // for the largest LDS request, which never overstates what a smaller one gets
   int capacity = 0;
-  if ((e = resident_workgroups(cache, greedy_panel_kernel<BK, NR, CAND>, TPB, kPanelLds, &capacity)) != hipSuccess) return e;
+  if ((e = resident_workgroups(cache, kernel, TPB, most, &capacity)) != hipSuccess) return e;
   if (W > capacity) return hipErrorInvalidValue;
   hipLaunchKernelGGL(greedy_init_kernel, dim3((B + 255) / 256), dim3(256), 0, st, ctl, B);
-  hipLaunchKernelGGL((greedy_panel_kernel<BK, NR, CAND>), dim3((unsigned)(B * W)), dim3(TPB), lds, st, G, n, nP, k, W, order, resid, ctl,
-                     img_status, barrier_limit_ticks());
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(B * W)), dim3(TPB), lds, st, G, n, nP, k, W, order, resid, ctl, img_status, barrier_limit_ticks());
   return hipGetLastError();
 }
 
@@ -664,9 +809,9 @@ hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int
                          int* img_status, hipStream_t st) {
   if (nP % GR != 0 || n > nP || n > 4096 || k > n || k > 4096) return hipErrorInvalidValue;
   GreedyCtl* ctl = (GreedyCtl*)scratch;
-  // the largest block of picks (a multiple of the MFMA's depth of 4) whose columns fit LDS beside the candidates' submatrix
-  const auto fits = [&](int bk, int cand) { return panel_lds(bk, cand, nP) <= kPanelLds; };
-  const int BK = fits(16, 64) ? 16 : fits(12, 64) ? 12 : fits(8, 32) ? 8 : 4;
+  // the largest block of picks (a multiple of the MFMA's depth of 4) whose columns fit LDS
+  const auto fits = [&](int bk) { return (size_t)bk * nP * sizeof(double) <= kStepLds; };
+  const int BK = fits(16) ? 16 : fits(12) ? 12 : fits(8) ? 8 : 4;
   // values moved: the right-looking kernel reads and writes R once per block that is followed by another, the
   // left-looking ones read every earlier column at every step; the former also has far fewer barriers
   const double right = (double)((k - 1) / BK) * 2.0 * n * n, left = 0.5 * k * k * n;
@@ -677,14 +822,25 @@ hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int
     if (Wp < 4) Wp = 256 / B < 4 ? 256 / B : 4;
     Wp = Wp < 1 ? 1 : Wp > 32 ? 32 : Wp;
     Wp = Wp > nt ? nt : Wp;
-    // rows: at most 960 with blocks of 16, 1280 with 12, 1920 with 8 (2304 with 32 candidates), 3840 with 4
-    if (BK == 16) return launch_panel<16, 1, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
-    if (BK == 12) return launch_panel<12, 2, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
-    if (BK == 8)
-      return fits(8, 64) ? launch_panel<8, 2, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st)
-                         : launch_panel<8, 3, 32>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
-    return fits(4, 64) ? launch_panel<4, 4, 64>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st)
-                       : launch_panel<4, 4, 32>(G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);
+    // Runs of picks up to 960 rows, where the candidates' submatrix fits beside 16 columns.  us per selection of half of the rows, steps (before R was
+    // stored through) / runs, one image and eight: 64 rows 147 / 101 and 152 / 112, 128 228 / 154 and 237 / 176, 512 751 / 567 and 910 / 677,
+    // 900 1544 / 1213 and 2124 / 1594.  Beyond, runs cost the updates that a smaller block adds or most of their candidates: 1000 rows
+    // 1740 / 1760 and 2400 / 2350 with 12 columns, 2160 and 2650 with 32 candidates, 2400 rows 11700 / 18900 with 4 columns.
+#define COVSPEC_PANEL(kernel, lds, most)                                                                                                        \
+  do {                                                                                                                                          \
+    static PerDeviceInt raised, cache;                                                                                                          \
+    return launch_panel(kernel, raised, cache, lds, most, G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);                               \
+  } while (0)
+    if (run_lds(16, 64, nP) <= kRunLds) COVSPEC_PANEL((greedy_panel_kernel<16, 1, 64>), run_lds(16, 64, nP), kRunLds);
+    const size_t lds = (size_t)BK * nP * sizeof(double);
+    // rows per thread: at most 1216 rows with blocks of 16, 1664 with 12, 2496 with 8
+    if (BK == 16 && n <= TPB) COVSPEC_PANEL((greedy_step_kernel<16, 1>), lds, kStepLds);
+    if (BK == 16) COVSPEC_PANEL((greedy_step_kernel<16, 2>), lds, kStepLds);
+    if (BK == 12) COVSPEC_PANEL((greedy_step_kernel<12, 2>), lds, kStepLds);
+    if (BK == 8 && n <= 2 * TPB) COVSPEC_PANEL((greedy_step_kernel<8, 2>), lds, kStepLds);
+    if (BK == 8) COVSPEC_PANEL((greedy_step_kernel<8, 4>), lds, kStepLds);
+    COVSPEC_PANEL((greedy_step_kernel<4, 4>), lds, kStepLds);
+#undef COVSPEC_PANEL
   }
   const int W = nP / GR;
   // Left-looking: spreading an image over W workgroups costs a device-scope barrier per step; it pays while the
