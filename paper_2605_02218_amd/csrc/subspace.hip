@@ -22,7 +22,7 @@
 // The start block is Omega G with a fixed +-1 pattern Omega, so exact duplicate tokens (equal rows of
 // G) cannot make it rank deficient.
 // The residual of the dominant subspace, Pi Q^T G - H U, is checked; images that fail (slow decay, P too small, no gap
-// at the cut) take a further block and, if they fail again, the full block Jacobi solve of G.
+// at the cut) take up to two further blocks and, if they fail again, the full block Jacobi solve of G.
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"
@@ -41,8 +41,9 @@ constexpr double kRitzTol = 1e-9;
 // A last factorisation with a smallest scaled pivot below this leaves rows whose inner products exceed what the residual check
 // would see (about 1e-16 over the pivot); the image goes on in the second pass.
 constexpr double kPivotOnePass = 1e-10;
-constexpr double kPivotFloor = 1e-28;  // see chol_kernel
+constexpr double kPivotFloor = 1e-14;  // see chol_kernel
 constexpr double kLn10 = 2.302585092994046;
+constexpr float kSteep = 9.0f;         // ln(lambda_1 / lambda_P) from which growth and not launches limit a block of three products
 
 constexpr size_t kCholLds = (size_t)2 * NB * NBP * sizeof(double);
 constexpr int kMaxBlocks = 64;         // block rows: P <= 4096
@@ -62,11 +63,14 @@ __global__ void omega_kernel(double* __restrict__ om, int P, int n, int nP) {
 //   ST_IDLE  minus the number of products of the block that follows
 //   ST_SEL, ST_END  the buffer its first operand is in, and the one its result is in (products alternate between the two)
 enum { ST_REST, ST_IDLE, ST_SEL, ST_END, ST_FIELDS };
+constexpr int kMaxDegrees = 6;
 struct IterPlan {
   double tb;      // 2 / beta, beta = the upper end of the damped interval; 0: the block's products are with G itself
   float l1, s;    // ln(lambda_1 / beta); how far the rows are separated from the leading ones, ln of the growth so far
-  int pw, n, m[4]; // products with G up to the first estimate; Chebyshev blocks so far and their degrees
+  float y;        // what lies beyond beta grows like cosh(m y) over m products: acosh(2 lambda_P / beta - 1), 0 where beta is above lambda_P
+  int pw, n, m[kMaxDegrees]; // products with G up to the first estimate; Chebyshev blocks so far and their degrees
   int redo;       // failed the check: the last product was with G, from orthonormal rows
+  int there;      // second pass: with the block under way, by its estimate, the image is there
 };
 struct PlanArgs {
   const int* in;  // states of this orthonormalisation and of the next, [ST_FIELDS][B] each
@@ -74,14 +78,24 @@ struct PlanArgs {
   IterPlan* plan;
   int* left;      // [B] nothing left to do for the image in this pass
   int B, r;
-  int slots;      // products that may follow; 0: the last orthonormalisation of the pass
+  int slots;      // products that may follow; 0: the last orthonormalisation of the pass, Q G follows
   int first;      // the very first: nothing is known about the spectrum yet
-  int closing;    // 1: the last block of the first pass follows, 2: of the second
+  int pass;
+  int closing;    // the last block of the pass follows
 };
+// Products that may follow: two between the first two orthonormalisations (the spectrum is not known yet), then as
+// many as tell the rows apart, three or four at most (plan_block; a launch that no image needs costs 2 us); kSlots2: the second pass.
+constexpr int kBlocks = 3, kSlots[kBlocks] = {2, 3, 4}, kBlocks2 = 2, kSlots2[kBlocks2] = {3, 2};
+constexpr int kStates1 = kBlocks + 2, kStates = kStates1 + kBlocks2 + 2;       // the first pass's and all
+constexpr int kOrths = kBlocks + 1;            // of the first pass; the second has fewer
+static_assert(kBlocks2 <= kBlocks && kBlocks + kBlocks2 <= kMaxDegrees, "");
+
 
 __device__ __forceinline__ float ln_cosh(float t) { return t + log1pf(expf(-2.0f * t)) - 0.6931472f; }
 // acosh(e^v) for v >= 0
 __device__ __forceinline__ float acosh_exp(float v) { return v + logf(1.0f + sqrtf(fmaxf(0.0f, 1.0f - expf(-2.0f * v)))); }
+// ln(lambda / beta) where T_1 of lambda is cosh(t)
+__device__ __forceinline__ float over_beta(float t) { return t > 10.0f ? t - 1.3862944f : logf(0.5f + 0.5f * coshf(t)); }
 
 // Decides what follows an orthonormalisation from the diagonal of its factor (rows 0, r - 1 and P - 1: d1, dr, dP) and its smallest
 // scaled pivot (L_kk^2 / S_kk, the squared sine between row k and the rows before it).  The rows are ordered like the
@@ -90,9 +104,16 @@ __device__ __forceinline__ float acosh_exp(float v) { return v + logf(1.0f + sqr
 //   products needed: the error, from x^-pw / T_m1 / T_m2 ... with x = lambda_r / beta, has to
 //     come below 2e-10;
 //   products possible in one block: with growth e^b between the first row and the last, a rounding error of the size eps in row
-//     k along row 1 becomes eps e^b of it.  eps is e^-s while the rows are not yet separated any further, else the 1e-16 over the
-//     pivot that the factorisation left.  Cholesky-QR stands eps e^b of 3e4 (a scaled pivot of 1e-9), and 1e3 at the
-//     last one (it is not repeated).
+//     k along row 1 becomes eps e^b of it.  eps is e^-s while the rows are not yet separated any further, else what the
+//     factorisation left: 1e-16 over the pivot for the row that has it, taken as 1e-19 over it for the last rows, for steep spectra as 3e-19
+//     and in the second pass, behind which is only the full solve, as 1e-18 (1e-19 for these too: some run out of blocks; 1e-17: more need the
+//     second pass).  Cholesky-QR stands eps e^b of 3e4 (a scaled pivot of 1e-9), and 1e3 (3e2) at the last one, which is not repeated.  A row whose pivot drowns all
+//     the same starts again from what rounding left of it (kPivotFloor).
+// A steep spectrum (kSteep) allows two or three products a block where the launches allow three or four, and needs more blocks than the
+// first pass has.  Its image, if it is further from its end than a block of the second pass reaches, takes the last orthonormalisation of
+// the first too, with one product of a block where the others form Q G, and may take two blocks in the second pass; others take one
+// there.  (With four blocks in all lambda_k = 1 / k^3 of 512 rows, r = 64, ended in the full solve, 22 ms where 2 suffice, and so did one in
+// some four hundred token matrices of 1152 rows, r = 288, 110 ms.)
 // Modelled in fp64 on the token matrices and on spectra from x = 1.2 to 1e5, lambda_1 / lambda_P from 2 to 5e7.
 __device__ __forceinline__ void plan_block(const PlanArgs& q, int b, double d1, double dr, double dP, double pmin) {
   IterPlan& p = q.plan[b];
@@ -101,59 +122,88 @@ __device__ __forceinline__ void plan_block(const PlanArgs& q, int b, double d1, 
   int m = 0, rest = 0;
   const bool sane = dP > 0.0 && d1 < 1e300 && dr > 0.0 && dr < 1e300 && pmin > 0.0;
   if (q.first) {
-    // The diagonal of a random block's factor spans a tenth of lambda_1 / lambda_P or more; two products while the
-    // pivots they leave (lambda_P / lambda_1)^2 stay above 1e-10.
-    m = d1 <= 1e4 * dP ? 2 : 1;
-    p.tb = 0.0; p.l1 = p.s = 0.0f; p.pw = 1 + m; p.n = 0; p.redo = 0;
-  } else if (q.slots == 0) {
-    if (!(pmin > kPivotOnePass)) q.left[b] = 1;
+    // The diagonal of a random block's factor spans a tenth of lambda_1 / lambda_P or more, unless its first row happens to have little of
+    // the first eigenvector, and its pivots are some (lambda_P / lambda_1)^2; two products while those that they leave stay above 1e-10.
+    m = d1 <= 1e4 * dP && pmin > 3e-10 ? 2 : 1;
+    p.tb = 0.0; p.l1 = p.s = p.y = 0.0f; p.pw = 1 + m; p.n = 0; p.redo = 0; p.there = 0;
+  } else if (q.slots == 0 && !q.left[b]) {
+    if (pmin > kPivotOnePass) {
+      m = 1;                                      // Q G
+      p.tb = 0.0;
+    } else {
+      q.left[b] = 1;
+    }
   } else if (!sane) {
     q.left[b] = 1;
     rest = 2;
   } else {
-    float a;                                      // acosh(2 lambda_r / beta - 1)
-    if (p.tb == 0.0 || p.redo) {
+    const int slots = q.slots == 0 ? 1 : q.slots;
+    float a;                                      // ln(lambda_r / beta)
+    if (p.n == 0 || p.redo) {
       const float per = p.redo ? 1.0f : 1.0f / (float)(p.pw - 1);
       const float lP = per * (float)log(dP) + 0.18232f;      // the estimate is up to a fifth low
       p.l1 = fmaxf(0.0f, per * (float)log(d1) - lP);
-      if (p.tb == 0.0) p.s = (float)p.pw * p.l1;
+      if (!p.redo) p.s = (float)p.pw * p.l1;
       p.tb = 2.0 * exp(-(double)lP);
+      p.y = 0.0f;
       a = per * (float)log(dr) - lP;
     } else {
-      const float t = acosh_exp(fmaxf(0.0f, (float)log(dr))) / (float)p.m[p.n - 1];
-      a = logf(0.5f + 0.5f * coshf(t));
+      const float per = 1.0f / (float)p.m[p.n - 1];
+      a = over_beta(acosh_exp(fmaxf(0.0f, (float)log(dr))) * per);
+      if (dP > 1.0) p.y = fmaxf(p.y, acosh_exp((float)log(dP)) * per);
+      p.l1 = fmaxf(p.l1, over_beta(acosh_exp(fmaxf(0.0f, (float)log(d1))) * per));    // row 1 of the first blocks may have little of its eigenvector
     }
     const float x = fmaxf(1.0f + 1e-6f, expf(a)), ax = acoshf(2.0f * x - 1.0f);
     const float a1 = p.l1 > 10.0f ? p.l1 + 1.3862944f : acoshf(fmaxf(1.0001f, 2.0f * expf(p.l1) - 1.0f));
-    float e = (float)p.pw * logf(x) - 0.7f;       // digits of the error so far, as a natural logarithm
-    for (int k = 0; k < p.n; ++k) e += ln_cosh(ax * (float)p.m[k]);
-    // (at the end of the first pass a factor of two of that is left to the residual check: the estimate is mostly on the safe side)
-    const float missing = (float)((q.closing == 1 ? 9.4 : 9.7) * kLn10) - e;
+    // what a block of m products contracts the error by, and the digits of the error so far, as natural logarithms
+    auto gain = [&](int m) { return ln_cosh(ax * (float)m) - (p.y > 0.0f ? ln_cosh(p.y * (float)m) : 0.0f); };
+    float e = (float)p.pw * (logf(x) - (p.y > 0.0f ? over_beta(p.y) : 0.0f)) - 0.7f;
+    for (int k = 0; k < p.n; ++k) e += gain(p.m[k]);
+    // At the end of a pass some of that is left to the residual check where an image would need another block otherwise: the estimate is mostly
+    // on the safe side (modelled: 0.4 to 2.7 digits with lambda_1 / lambda_P below 6e4, -0.2 to 2 below 6e5), but not the first one, from
+    // powers of G, which has been two digits off, nor those of steeper spectra, where rounding counts.
+    const bool steep = p.l1 > kSteep;
+    const double digits = !q.closing ? (q.pass == 2 && steep ? 10.0 : 9.7) : q.pass == 1 ? 9.4 : p.l1 < 13.3f ? 9.1 : 9.7;
+    const float missing = (float)(digits * kLn10) - e;
     int need = missing <= 0.0f ? 0 : (int)fminf(40.0f, ceilf(acosh_exp(missing) / ax));
-    if (need == 0 && !(pmin > kPivotOnePass)) need = 1;
+    while (p.y > 0.0f && need > 0 && need < 40 && gain(need) < missing) ++need;
+    if (need == 0 && (!(pmin > kPivotOnePass) || (p.n == 0 && missing > (float)(-1.5 * kLn10)))) need = 1;
     if (p.redo) need = 40;
+    if (p.there && pmin > kPivotOnePass) need = 0;
+    p.there = 0;
     if (need == 0) {
       rest = 2;
+      if (q.slots == 0) {                         // there after all
+        q.left[b] = 0;
+        m = 1;
+        p.tb = 0.0;
+      }
     } else {
-      const float apart = fmaxf(0.0f, fminf(p.s, (float)log(pmin) + (float)(19.0 * kLn10)));
-      const int most = max(1, min(q.slots, (int)(acosh_exp(apart + (float)(4.5 * kLn10)) / a1)));
-      const int last = max(1, min(q.slots, (int)(acosh_exp(apart + (float)(3.0 * kLn10)) / a1)));
-      if (need <= last) {
+      const float spare = (float)((steep && q.pass == 2 ? 2.5 : 3.0) * kLn10);
+      const float apart = fmaxf(0.0f, fminf(p.s, (float)log(pmin) + (float)((!steep ? 19.0 : q.pass == 1 ? 18.5 : 18.0) * kLn10)));
+      const int most = max(1, min(slots, (int)(acosh_exp(apart + (float)(4.5 * kLn10)) / a1)));
+      const int last = max(1, min(slots, (int)(acosh_exp(apart + spare) / a1)));
+      if (q.pass == 2) {
+        // all images of the pass, done or not, meet at its second orthonormalisation, and the third is left out when all are
+        m = min(need, last);
+        rest = q.closing;
+        p.there = need <= last || !steep;
+      } else if (need <= last) {
         m = need;
-        rest = 1;
-      } else if (q.closing == 2) {
-        m = last;
         rest = 1;
       } else {
         const int blocks = 1 + (need - last + most - 1) / most;
         m = min(most, (need + blocks - 1) / blocks);
         if (q.closing) {                          // not there at the end of this pass: on to the second without a split
-          rest = 2;
           q.left[b] = 1;
+          // what a block there reaches from well separated rows; they are behind a block of less than the most
+          const int reach = max(1, min(kSlots2[0], (int)(acosh_exp((float)(18.5 * kLn10)) / a1)));
+          if (steep) m = min(m, max(need - reach, min(2, last)));
+          if (!steep || need - m <= reach + 1) rest = 2;     // (the one more, by its estimate, is mostly not needed)
         }
       }
       p.s += ln_cosh(a1 * (float)m);
-      if (p.n < 4) p.m[p.n++] = m;
+      if (p.n < kMaxDegrees) p.m[p.n++] = m;
     }
     p.redo = 0;
   }
@@ -163,14 +213,15 @@ __device__ __forceinline__ void plan_block(const PlanArgs& q, int b, double d1, 
   out[ST_END * q.B] = (at + m) & 1;
 }
 
-// An image that takes no part: its block stays as and where it is.
+// An image that takes no part: its block stays as and where it is; at the end of a pass Q G is formed of one that is to be split.
 __device__ __forceinline__ void rest_on(const PlanArgs& q, int b) {
   int* out = q.out + b;
-  const int at = q.in[ST_END * q.B + b];
+  const int at = q.in[ST_END * q.B + b], m = q.slots == 0 && !q.left[b] ? 1 : 0;
+  if (m) q.plan[b].tb = 0.0;
   out[ST_REST * q.B] = q.in[ST_REST * q.B + b];
-  out[ST_IDLE * q.B] = 0;
+  out[ST_IDLE * q.B] = -m;
   out[ST_SEL * q.B] = at;
-  out[ST_END * q.B] = at;
+  out[ST_END * q.B] = (at + m) & 1;
 }
 
 // value of `v` in lane k of every row of 16 lanes
@@ -352,9 +403,10 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
 // before it, whatever else the device is doing; every wait is bounded.  What the rows hand one another is stored through the L2.
 // Every product is formed transposed, so that its result is the fragment of the tile it goes to.
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
-// A pivot is floored relative to its own row's squared length, so that a numerically rank-deficient block cannot
-// produce NaNs (the residual check afterwards decides whether the result is usable) while rows may differ in length by any
-// number of digits: after a block of products they do, by the growth of the first row over the last.
+// A pivot is floored relative to its own row's squared length (rows may differ in length by any number of digits: after a block of
+// products they do, by the growth of the first row over the last), at the rounding of S: what is left of a row below that is noise, which
+// the floor keeps shorter than the other rows, and the next factorisation makes a row of length one of it.  (At 1e-28 such a row came out
+// up to 1e7 long, with as much of the other rows in it, and the image ended in the full solve.)
 // Bound by the chain of diagonal blocks: factor, flag, product with the inverse, D.  One workgroup per image, which did the
 // trailing updates itself beside the factorisation of the next block by one of its waves, took, us: one image of order 192 67,
 // eight of 384 172, sixty-four of 256 98; this 55, 108 and 80 (eleven of the eighteen a row takes are the elimination).
@@ -520,9 +572,9 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     plan_block(q, b, diag[(long)b * P], diag[(long)b * P + q.r - 1], diag[(long)b * P + P - 1], pmin);
   } else {                                                      // no factor: nothing more for the image in this pass
     __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    q.left[b] = 1;
     rest_on(q, b);
     q.out[ST_REST * q.B + b] = 2;
-    q.left[b] = 1;
     if (img_status) img_status[b] = 1;
   }
 }
@@ -669,8 +721,8 @@ __global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, long other, c
 }
 
 // State 0 of a pass.  First: every block is in buffer 0.  Second: images that passed the check rest; one that was left out of the
-// split goes on from its block, one that failed the check from the product with G that followed its last orthonormalisation
-// (in the buffer its rows are not in).  And the flags of the pass's factorisations.
+// split goes on from its block, one that failed the check from the product with G that followed its last orthonormalisation.  And
+// the flags of the pass's factorisations.
 __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__ prev, const int* __restrict__ ok, IterPlan* __restrict__ plan,
                                   int* __restrict__ left, int* __restrict__ failed_before, int B, CholFlags* __restrict__ flags, int orths) {
   int* words = (int*)flags;
@@ -678,7 +730,7 @@ __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   const bool passed = prev && ok[b] != 0, failed = prev && !passed && !left[b];
-  const int at = prev ? (failed ? 1 - prev[ST_SEL * B + b] : prev[ST_END * B + b]) : 0;
+  const int at = prev ? prev[ST_END * B + b] : 0;
   out[ST_REST * B + b] = passed ? 2 : 0;
   out[ST_IDLE * B + b] = 0;
   out[ST_SEL * B + b] = at;
@@ -689,13 +741,6 @@ __global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__
 }
 
 }  // namespace
-
-// Products a block may take: two between the first two orthonormalisations (the spectrum is not known yet), then as
-// many as tell the rows apart, three or four at most (plan_block; a launch that no image needs costs 2 us); kSlots2: the second pass.
-// The slowest decay that converges is lambda_r / lambda_{P+1} = 2.8; what is slower goes to the full solve, 20 ms and more.
-constexpr int kBlocks = 3, kSlots[kBlocks] = {2, 3, 4}, kSlots2 = 3;
-constexpr int kStates = kBlocks + 2 + 3;       // the first pass's and the second's
-constexpr int kOrths = kBlocks + 1;            // of the first pass; the second has two
 
 inline size_t tail_doubles(int B, int P, int nP) {
   const size_t u = (size_t)nP * (P + 2 * (P / kSymTile)), x1 = (size_t)P * P;
@@ -777,7 +822,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     return launch_gemm64_nt(g, true, true, st);
   };
   // X <- L^-1 X with X X^T = L L^T for the images that state k lets take part, and the plan of what follows
-  auto cholqr = [&](int k, int slots, bool first, int closing) -> hipError_t {
+  auto cholqr = [&](int k, int slots, bool first, int pass, bool closing) -> hipError_t {
     const int rest_max = slots == 0 ? 1 : 0;
     GemmArgs g;
     g.A = Yt; g.B = Yt; g.C = S; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
@@ -788,8 +833,8 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     g.skip = state(k) + ST_REST * B; g.skip_if = rest_max;
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     PlanArgs q;
-    q.in = state(k); q.out = state(k + 1); q.plan = plan; q.left = left; q.B = B; q.r = r; q.slots = slots; q.first = first; q.closing = closing;
-    const int orth = k < kBlocks + 2 ? k : k - (kBlocks + 2);      // of its pass
+    q.in = state(k); q.out = state(k + 1); q.plan = plan; q.left = left; q.B = B; q.r = r; q.slots = slots; q.first = first; q.pass = pass; q.closing = closing;
+    const int orth = k < kStates1 ? k : k - kStates1;               // of its pass
     hipLaunchKernelGGL(chol_kernel, dim3((unsigned)(B * (P / NB))), dim3(512), kCholLds, st, S, D, diag, pivots, P, q, flags + (size_t)orth * B,
                        img_status, barrier_limit_ticks());
     const dim3 tg((unsigned)(B * (nP / NB)));
@@ -820,13 +865,9 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   };
   // the last orthonormalisation of a pass, the split, the residual check and the energies
   auto finish = [&](int k, int pass_no) -> hipError_t {
-    if ((e = cholqr(k, 0, false, 0)) != hipSuccess) return e;
+    if ((e = cholqr(k, 0, false, pass_no, false)) != hipSuccess) return e;
     const int* sel = state(k + 1) + ST_SEL * B;      // Q^T is there (orthonormal rows), Q^T G goes into the other buffer
-    {
-      GemmArgs g;
-      g.skip = left; g.skip_if = 0;
-      if ((e = gemm_yt_g(k + 1, 0, g)) != hipSuccess) return e;
-    }
+    if ((e = block(k + 1, 1)) != hipSuccess) return e;
     {                                                // H = (Q^T G) Q
       GemmArgs g;
       g.A = Zt; g.B = Yt; g.C = H; g.M = P; g.N = P; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = P;
@@ -874,17 +915,19 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
   hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, failed, B, flags, kOrths);
   for (int k = 0; k < kBlocks; ++k) {
-    if ((e = cholqr(k, kSlots[k], k == 0, k == kBlocks - 1 ? 1 : 0)) != hipSuccess) return e;
+    if ((e = cholqr(k, kSlots[k], k == 0, 1, k == kBlocks - 1)) != hipSuccess) return e;
     if ((e = block(k + 1, kSlots[k])) != hipSuccess) return e;
   }
   if ((e = finish(kBlocks, 1)) != hipSuccess) return e;
   // images whose subspace is not there yet (slower decay of the spectrum than the blocks of the first pass allow for) take
-  // another block; for the others every kernel of this pass returns at once
-  const int k2 = kBlocks + 2;
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(k2), (const int*)state(k2 - 1), (const int*)ok, plan, left, failed, B, flags, 2);
-  if ((e = cholqr(k2, kSlots2, false, 2)) != hipSuccess) return e;
-  if ((e = block(k2 + 1, kSlots2)) != hipSuccess) return e;
-  return finish(k2 + 1, 2);
+  // one or two more; for the others every kernel of this pass returns at once
+  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(kStates1), (const int*)state(kStates1 - 1), (const int*)ok, plan, left, failed, B,
+                     flags, kBlocks2 + 1);
+  for (int k = 0; k < kBlocks2; ++k) {
+    if ((e = cholqr(kStates1 + k, kSlots2[k], false, 2, k == kBlocks2 - 1)) != hipSuccess) return e;
+    if ((e = block(kStates1 + k + 1, kSlots2[k])) != hipSuccess) return e;
+  }
+  return finish(kStates1 + kBlocks2, 2);
 }
 
 }  // namespace covspec

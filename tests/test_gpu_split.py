@@ -96,6 +96,44 @@ def test_schedules_of_the_block_iteration(C, name):
         assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1), "%s image %d: %g" % (name, b, err.max())
 
 
+# tokens, rank, eigenvalues of the Gram matrix by index, the ways the solve may take: spectra so steep that a block stands two or three
+# products, and one that is there after the first block but for what its first estimate is off
+STEEP = {
+    "cubic": (512, 64, lambda i, r: (i + 1.0) ** -3, (1, 2)),
+    "cubic-short": (256, 64, lambda i, r: (i + 1.0) ** -3, (1, 2)),
+    "power-2.5": (256, 100, lambda i, r: (i + 1.0) ** -2.5, (1, 2)),
+    "power-4": (384, 128, lambda i, r: (i + 10.0) ** -4, (1, 2)),
+    "outliers": (256, 64, lambda i, r: np.exp(-0.02 * i) * np.where(i < 3, 1e4, 1.0), (1, 2)),
+    "outliers-slow": (512, 160, lambda i, r: np.exp(-0.015 * i) * np.where(i < 3, 1e4, 1.0), (1, 2)),
+    "outliers-power": (256, 100, lambda i, r: (i + 1.0) ** -2 * np.where(i < 3, 100.0, 1.0), (1, 2)),
+    "first-estimate": (200, 8, lambda i, r: (i + 10.0) ** -4, (1,)),
+}
+
+
+@pytest.mark.parametrize("name", list(STEEP))
+def test_steep_spectra_stay_on_the_block_iteration(C, name):
+    """A few large tokens above the others, or a fast decay: the block iteration has to finish these (a full solve takes ten
+    times as long)."""
+    import torch
+    n, r, spectrum, paths = STEEP[name]
+    lam = spectrum(np.arange(n), r)
+    B, d = 6, n + 24
+    X = np.stack([I.make_spectrum_tokens(n, d, np.sqrt(lam / lam.max()), seed=20 + b, dtype=I.FP32) for b in range(B)])
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    ws = C.alloc_workspace(p)
+    out = C.select(p, torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda(), workspace=ws)
+    path = C.lowrank_path(p, ws).tolist()
+    c = out["c"].cpu().numpy().astype(np.float64)
+    for b in range(B):
+        ref = O.select(X[b].astype(np.float64), sf[b], O.Params(preselect_m=n, rank_r=r, keep_k=n // 3))
+        # fp32 rounding of c, and the admitted residual over the relative gap at the cut, twice; energies far below the
+        # largest carry its rounding
+        err = np.abs(c[b] - ref["c"]) / np.maximum(ref["c"], 1e-6 * ref["c"].max())
+        assert err.max() < 6e-8 + 2e-9 / (lam[r - 1] / lam[r] - 1), "%s image %d: %g" % (name, b, err.max())
+    assert set(path) <= set(paths), path
+
+
 def test_equal_eigenvalues_at_the_cut_still_give_a_result(C):
     """Orthogonal tokens of equal length: no rank-r subspace is better than another, the split has no gap to use and the
     full solve answers.  Every energy lies between 0 and the squared length, and they sum to r of it."""
