@@ -260,9 +260,10 @@ __global__ __launch_bounds__(TPB) void greedy_single_kernel(const double* __rest
 // Picks are made in runs.  A residual only ever shrinks, so while the largest residual of the CAND largest ones at the start of the
 // run stays above all the others as they were then, the others need not be looked at: one wave makes the picks from the
 // CAND x CAND submatrix of R in LDS, no barrier and no row of R to wait for, and the columns of the run are formed for all rows
-// behind it, the rows of R requested together.  A run ends when a residual left out could be the largest (8 picks on the
+// behind it, the rows of R requested together.  A run ends when a residual left out could be the largest (6.3 to 7 picks on the
 // average with 64 candidates on the token matrices of the workloads, 5 to 10 over their images), at the end of a block, and
-// before a residual that is not finite.
+// before a residual that is not finite.  Residuals are compared with their rows, so that a tie ends no run that goes on in lower rows
+// (300 rows of one length, orthogonal, 150 picks, us: 414 with a step per pick, 1330 with every tie the end of a run, 340 so).
 // Candidates are the CAND largest of the eight largest of each wave; ordered by (residual rounded to fp32, lower row), so that the
 // first pick of a run is the largest of all whatever ties there are.
 // Bound by the chain of picks: us for 463 picks of 926 rows, six images, with all rows in every step (a maximum over the
@@ -316,8 +317,9 @@ struct GreedyRun {
   unsigned long long post[TPB / 64 * kWaveBest];   // per wave its largest keys: (residual, ~row), 0 where there are no more rows
   double post_rho[TPB / 64 * kWaveBest];
   int rank[TPB / 64 * kWaveBest];
-  uint32_t left[TPB / 64];                         // per wave the largest key it did not post
-  uint32_t next;                                   // the largest key posted that is no candidate
+  uint32_t left[TPB / 64];                         // per wave the largest key it did not post, and the lowest row that has it
+  int left_row[TPB / 64];
+  unsigned long long next;                         // the largest key posted that is no candidate
   int cand[64];
   double cand_rho[64];
   double factor[16 * 16];                          // [q][m]: column q of the run at the row of its pick m
@@ -328,7 +330,17 @@ struct GreedyRun {
   int flag;
 };
 
-// Pick m of a run and those after it, by one wave; a lane has one candidate.  col[q] is column q of the run at its row.
+// The lowest row of those left out that have the key `bound`, by one wave.
+__device__ __forceinline__ int lowest_left_out(const GreedyRun& run, uint32_t bound) {
+  const int lane = threadIdx.x & 63;
+  uint32_t after = 0u;                             // all ones minus the row
+  if (lane < TPB / 64 && run.left[lane] == bound) after = 0xFFFFFFFFu - (uint32_t)run.left_row[lane];
+  if (lane == TPB / 64 && (uint32_t)(run.next >> 32) == bound) after = (uint32_t)run.next;
+  return (int)(0xFFFFFFFFu - wave_max_u32(after));
+}
+
+// Pick m of a run and those after it, by one wave; a lane has one candidate.  col[q] is column q of the run at its row.  bound is the
+// largest residual left out; it goes before a candidate of the same residual in a later row.
 template <int BK, int CAND, int M>
 __device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int room, uint32_t bound, uint32_t row, double rho, bool open, double (&col)[BK]) {
   if constexpr (M < BK) {
@@ -336,8 +348,9 @@ __device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int ro
     const int lane = threadIdx.x & 63;
     const uint32_t key = open ? residual_key(rho) : 0u;
     const uint32_t best = wave_max_u32(key);
-    if (best == 0u || (M > 0 && (best <= bound || best >= kKeyInf))) return M;
+    if (best == 0u || (M > 0 && (best < bound || best >= kKeyInf))) return M;
     const int at = __builtin_amdgcn_readfirstlane(best_lane(key, best, row));
+    if (M > 0 && best == bound && __builtin_amdgcn_readlane((int)row, at) > lowest_left_out(run, bound)) return M;
     double c = lane < CAND ? S[at * (CAND + 1) + lane] : 0.0;
     const double piv = lane_value(rho, at);
     const double inverse = piv > 0.0 ? 1.0 / sqrt(piv) : -1.0;
@@ -485,6 +498,7 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
         const uint32_t best = wave_max_u32(mine);
         if (e == kWaveBest) {
           if (lane == 0) run.left[w] = best;
+          if (lane == __ffsll((long long)__ballot(mine == best)) - 1) run.left_row[w] = row;     // lower lanes have lower rows
         } else if (best == 0u) {
           if (lane == 0) run.post[kWaveBest * w + e] = 0ull;
         } else if (lane == best_lane(mine, best, (uint32_t)row)) {
@@ -498,7 +512,7 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
     }
     if (tid < POSTS) run.rank[tid] = 0;
     if (tid < CAND) run.cand[tid] = -1;
-    if (tid == 0) run.next = 0u;
+    if (tid == 0) run.next = 0ull;
     __syncthreads();
     // ---- their ranks: eight threads per key, sixteen comparisons each
     const unsigned long long key = run.post[tid & (POSTS - 1)];
@@ -515,7 +529,7 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
         run.cand[rank] = (int)(0xFFFFFFFFu - (uint32_t)key);
         run.cand_rho[rank] = run.post_rho[tid];
       } else if (rank == CAND) {
-        run.next = (uint32_t)(key >> 32);
+        run.next = key;
       }
     }
     __syncthreads();
@@ -546,8 +560,7 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
     __syncthreads();
     // ---- the run
     if (w == 0) {
-      uint32_t bound = lane < TPB / 64 ? run.left[lane] : 0u;
-      bound = run.next > bound ? run.next : bound;
+      uint32_t bound = lane < TPB / 64 ? run.left[lane] : lane == TPB / 64 ? (uint32_t)(run.next >> 32) : 0u;
       bound = wave_max_u32(bound);
       const int row = lane < CAND ? run.cand[lane] : -1;
       double col[BK];

@@ -431,6 +431,43 @@ def test_greedy_picks_from_bf16_rows(C, B, n, d):
         np.testing.assert_allclose(_cpu(out["resid"])[b].astype(np.float64), ref["resid"], rtol=1e-6, atol=1.1e-16 * k * ref["resid"][0])
 
 
+@pytest.mark.parametrize("n", [64, 130, 512, 513, 960])
+def test_greedy_picks_among_equal_residuals(C, n):
+    """Orthogonal rows of three lengths, so that no pick changes another's residual: the longest first, equal ones by index."""
+    import torch
+    level = np.random.default_rng(n).integers(1, 4, n)
+    d = (n + 7) // 8 * 8
+    X = (np.eye(n, d) * level[:, None]).astype(np.float32)
+    k = n - 3
+    p = C.Params(batch=1, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, lr_mode=C.LR_GREEDY_RESIDUAL, keep_k=k, preselect_m=n, rank_r=1)
+    out = C.select(p, torch.from_numpy(X)[None].cuda(), torch.rand(1, n, generator=torch.Generator().manual_seed(n)).cuda())
+    order = np.argsort(-level, kind="stable")[:k]
+    np.testing.assert_array_equal(_cpu(out["pick_order"])[0], order)
+    np.testing.assert_array_equal(_cpu(out["resid"])[0], (level[order] ** 2).astype(np.float32))
+
+
+def test_greedy_time_does_not_depend_on_ties(C):
+    """Blank regions give tokens that are copies of one another.  Equal residuals take as long as distinct ones in the same order, where
+    the runs are as long (a run that ended at every tie took five times that)."""
+    import torch
+    n, took = 512, []
+    for step in (0.0, 1e-3):
+        X = torch.diag(2.0 - step * torch.arange(n)).float()[None].cuda()
+        p = C.Params(batch=1, n_tokens=n, d_model=n, n_query=1, dtype=C.FP32, lr_mode=C.LR_GREEDY_RESIDUAL, keep_k=n // 2, preselect_m=n, rank_r=1)
+        ws, sf = C.alloc_workspace(p), torch.rand(1, n).cuda()
+        best = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                C.select(p, X, sf, workspace=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best.append(a.elapsed_time(b))
+        took.append(min(best))
+    assert took[0] < 2.0 * took[1], took
+
+
 def test_greedy_picks_with_rows_that_are_not_finite(C):
     """An infinite token is the largest; whatever its column does to the others, the picks stay distinct positions."""
     import torch
