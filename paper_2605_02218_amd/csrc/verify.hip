@@ -11,9 +11,8 @@
 // residual pass (2 per word, one row per sequence).
 // For a few sequences what follows the statistics is one launch (verify_few_kernel): a workgroup per chunk of the rejected row, each of
 // which works out the acceptance for itself, the last one of a sequence draws.  A chain of four launches is bound by the launches
-// there; from some ten sequences on the acceptance is repeated in more workgroups than the device holds at once and the draws come
-// at the end of the longest launch.  us, four launches / two: one sequence of 5 positions and 32000 words 22.8 / 16.5, eight 22.3 / 17.5, sixteen
-// 22.1 / 20.9 (23.7 with 64 registers a thread), thirty-two 25 / 36; eight of 151936 words 26.5 / 25.4.
+// there; beyond, the acceptance is repeated in more workgroups than the device holds at once and the draws come at the end of the longest
+// launch (few_sequences).  One sequence of 5 positions and 32000 words, us: four launches 22.8, two 16.5.
 #include "common.h"
 #include "kernels.h"
 #include "vocab.h"
@@ -26,7 +25,13 @@ constexpr int VT = 256;            // threads of the statistics pass
 constexpr int AW = 8;              // waves of the acceptance kernel
 constexpr int ST = 1024;           // threads of the sampling kernel
 constexpr int FT = 512;            // of the kernel for few sequences
-constexpr long kFewGroups = 512;   // workgroups up to which that is taken: two per compute unit
+// Sequences that kernel is taken for, by the workgroups it makes of them (a chunk of a rejected row each).  The acceptance is worked out in each
+// of them, so the line lies the lower the more chunks a row has.  Device time of the two launches over that of the four, 2 to 64 positions:
+// 60 to 64 chunks 0.90 to 1.01 with three sequences, 0.95 to 1.05 with four, 0.98 to 1.21 with eight; 32 chunks 0.66 to 0.99 with six, 0.91 to
+// 1.04 with eight; 16 chunks 0.87 to 0.99 with twelve, 0.90 to 1.06 with sixteen; 8 chunks 0.90 to 0.96 with 32, 0.94 to 1.05 with 64; four
+// 0.93 to 1.02 with 128, one 0.83 to 1.01 with 512; a single position 0.81 to 1.05, median 0.91, up to 512 workgroups (8 to 151936 words,
+// bf16).
+inline bool few_sequences(long S, int L, int chunks) { return S * chunks <= (L == 1 || chunks <= 4 ? 512 : chunks <= 8 ? 256 : 192); }
 
 // stats[(row * chunks + c) * 4 + {0,1,2,3}] = ref_t, sum_t, ref_d, sum_d (base-2 domain) over words [c*clen, min(V, (c+1)*clen))
 template <int DT>
@@ -448,7 +453,7 @@ static hipError_t launch_verify_t(const void* zt, const void* zd, const int32_t*
   int group = 1;
   while (group < chunks) group *= 2;                         // chunks <= 64
   hipLaunchKernelGGL((verify_stats_kernel<DT>), dim3(chunks, S * L), dim3(VT), 0, st, zt, zd, V, clen, chunks, L, stats, done);
-  if ((long)S * rchunks <= kFewGroups) {
+  if (few_sequences(S, L, rchunks)) {
     hipLaunchKernelGGL((verify_few_kernel<DT>), dim3(rchunks, S), dim3(FT), 0, st, zt, zd, tok, u_acc, u_res, L, V, chunks, group, cstats, rlen,
                        rchunks, rowsum, done, n_acc, alpha, corr);
     return hipGetLastError();

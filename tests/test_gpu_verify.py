@@ -116,13 +116,65 @@ def test_verify_time_does_not_grow_with_the_positions():
 @pytest.mark.parametrize("S,L,V,dtype", [(8, 5, 32768 - 8, I.BF16), (9, 5, 32768 - 8, I.BF16), (3, 64, 4096, I.FP32), (2, 3, 2048 * 64, I.FP16), (5, 1, 8, I.BF16)],
                          ids=["most-workgroups", "one-more", "many-positions", "vectors-per-thread", "smallest"])
 def test_verify_few_sequences(S, L, V, dtype):
-    """The launch that takes acceptance, masses and draw together, at the edges of its range; a second call on the same buffers
-    counts its workgroups anew."""
+    """Few sequences, where one launch may take acceptance, masses and draw together; a second call gives the same.  (The edges of that
+    launch's range and a workspace used again: test_verify_on_a_used_workspace.)"""
     d = I.make_verify_batch(S, L, V, dtype, seed=3 * S + V, disagreement=0.8)
     n_acc, corr, alpha = _run(d, dtype)
     _check(d, dtype, n_acc, corr, alpha)
     n2, c2, a2 = _run(d, dtype)
     assert np.array_equal(n2, n_acc) and np.array_equal(c2, corr) and np.array_equal(a2, alpha)
+
+
+@pytest.mark.parametrize("S,L,V", [(3, 5, 16384), (4, 5, 16384), (32, 3, 2048), (33, 3, 2048), (512, 2, 256), (513, 2, 256), (16, 1, 8192), (17, 1, 8192)],
+                         ids=["long-rows", "long-rows-one-more", "eight-chunks", "eight-chunks-one-more", "one-chunk", "one-chunk-one-more", "one-position", "one-position-one-more"])
+def test_verify_on_a_used_workspace(S, L, V):
+    """Both sides of the lines between one launch behind the statistics and three, twice on one workspace that holds other data: with other
+    uniforms other sequences reject, so that a count left over from the first call would show."""
+    import torch
+    import paper_2605_02218_amd as C
+    d = I.make_verify_batch(S, L, V, I.BF16, seed=S + V, disagreement=0.8)
+    p = C.VerifyParams(n_seq=S, n_draft=L, vocab=V, dtype=I.BF16)
+    ws = torch.full((C.verify_workspace_size(p) + 256,), 255, dtype=torch.uint8, device="cuda")
+    zt, zd, tok = _dev(d["zt"], I.BF16), _dev(d["zd"], I.BF16), _dev(d["tok"])
+    seen = []
+    for u in (d["u_acc"], np.float32(1.0) - d["u_acc"]):
+        d["u_acc"] = np.clip(u, 1e-3, 0.999).astype(np.float32)
+        out = C.verify(p, zt, zd, tok, _dev(d["u_acc"]), _dev(d["u_res"]), workspace=ws)
+        n, c, a = (t.cpu().numpy() for t in out)
+        _check(d, I.BF16, n, c, a, seqs=range(S) if S <= 40 else range(0, S, 16))
+        seen.append(n)
+    assert np.any(seen[0] != seen[1])
+
+
+def test_verify_time_does_not_fall_with_another_sequence():
+    """Eight sequences of 16384 words against nine: one launch for all that follows the statistics, taken for eight, cost a fifth of the
+    call.  A ratio of two medians of one process."""
+    import torch
+    import paper_2605_02218_amd as C
+    took = []
+    for S in (8, 9):
+        g = torch.Generator(device="cuda").manual_seed(1)
+        zt = 2.0 * torch.randn(S, 8, 16384, generator=g, device="cuda")
+        zd = zt + 0.6 * torch.randn(S, 8, 16384, generator=g, device="cuda")
+        p = C.VerifyParams(n_seq=S, n_draft=8, vocab=16384, dtype=C.BF16)
+        args = (zt.bfloat16(), zd.bfloat16(), zd.argmax(2).to(torch.int32), torch.rand(S, 8, generator=g, device="cuda"), torch.rand(S, generator=g, device="cuda"))
+        ws = torch.empty(C.verify_workspace_size(p) + 256, dtype=torch.uint8, device="cuda")
+        C.verify(p, *args, workspace=ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()                     # replayed: the launches from Python would hide the kernels
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                C.verify(p, *args, workspace=ws)
+        times = []
+        for _ in range(25):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        took.append(sorted(times)[12])
+    assert took[0] < 1.1 * took[1], took
 
 
 @pytest.mark.parametrize("S,L", [(1, 1), (1, 8), (37, 3), (300, 1)])
