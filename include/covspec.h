@@ -25,11 +25,14 @@
  *    they use distinct workspaces.
  *  - The eigen-solve and the greedy picks of covspec_select / covspec_reduce spread an image over
  *    several workgroups (at most 64) that wait for one another inside one launch, so such a launch
- *    needs that many workgroup slots of the device at the same time.  Alone on the device it always
- *    has them.  Every such wait is bounded (2 s of wall clock unless covspec_set_wait_limit_us says
- *    otherwise): if other work holds the device for longer, the call still ends, COVSPEC_OK has long been
- *    returned, and the image concerned comes back with NaN energies (or NaN residuals) and valid but
- *    meaningless kept indices; covspec_image_status reports which images these are.  Keep concurrent
+ *    needs that many workgroup slots of the device at the same time (the factorisations of the block
+ *    iteration excepted, where a workgroup only waits for ones that have started before it).  Alone on the
+ *    device it always has them.  Every such wait is bounded (2 s of wall clock unless
+ *    covspec_set_wait_limit_us says otherwise).  If other work holds the device for longer, the call still
+ *    ends, COVSPEC_OK has long been returned, and an image whose block iteration or spectral split gave up
+ *    takes the full eigen-solve.  Where that (or the greedy picks) gives up the image comes back with NaN
+ *    energies (or NaN residuals) and valid but meaningless kept indices; covspec_image_status reports
+ *    which images these are.  Keep concurrent
  *    calls of these two entry points to COVSPEC_MAX_CONCURRENT_CALLS per device.
  *  - Ties in every ranking go to the lower index.  Ranking decisions are taken
  *    on the fp32 score values that the library returns.
@@ -279,11 +282,11 @@ int covspec_lowrank_path(const covspec_params* p, const void* workspace, int32_t
 
 /*
  * Per-image outcome of the LAST covspec_select / covspec_reduce call with these parameters on this workspace:
- * status_out (DEVICE int32 [B]) is 0 for an image whose result is valid and 1 for an image whose eigen-solve or
+ * status_out (DEVICE int32 [B]) is 0 for an image whose result is valid and 1 for an image whose full eigen-solve or
  * greedy picks gave up because a workgroup waited for the others of its image beyond the wait limit (the device
  * was held by other work).  For such an image the kept indices and gathered tokens are meaningless (energies and
  * residuals are NaN) and the call should be repeated.  The status word is cleared at the start of every call and
- * only ever set by the kernels that wait; modes without such kernels (SCORE_TOPK, RANDOM) always report 0.
+ * only ever set by the kernels behind which there is no other way to the result; modes without such kernels (SCORE_TOPK, RANDOM) always report 0.
  * Enqueued on `stream` behind the call in question; reads the workspace, writes nothing else.  (The selection
  * method itself, paper Sec. III-A.3, has no failure case: this reports a property of the execution.)
  * covspec_reduce_ragged keeps one status word per run inside its workspace slices and has no such query.

@@ -370,7 +370,7 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
     int* ok = nullptr;
     if (q.P > 0 || split_direct(q.nP)) {
       ok = at<int>(ws, q.ok);
-      HIPCHK(launch_subspace_eigen(A, q.B, q.M, q.nP, q.r, q.P, at<void>(ws, q.sub), ok, c, img_status,
+      HIPCHK(launch_subspace_eigen(A, q.B, q.M, q.nP, q.r, q.P, at<void>(ws, q.sub), ok, c,
                                    marks.ev ? marks.ev[COVSPEC_PROBE_BEGIN] : nullptr, marks.ev ? marks.ev[COVSPEC_PROBE_END] : nullptr, st));
       probed = q.P > 0;
     }
@@ -838,8 +838,7 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
     int* ok = nullptr;
     if (P > 0 || split_direct(q.nP)) {
       ok = at<int>(ws, q.ok);
-      HIPCHK(launch_subspace_eigen(Gc, q.B, nC, q.nP, q.r, P, at<void>(ws, q.sub), ok, c, nullptr, nullptr,
-                                   nullptr, st));
+      HIPCHK(launch_subspace_eigen(Gc, q.B, nC, q.nP, q.r, P, at<void>(ws, q.sub), ok, c, nullptr, nullptr, st));
     }
     HIPCHK(launch_copy_images(A, Gc, q.B, gstride, ok, st));      // the full solve overwrites its input
     HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, st));

@@ -164,12 +164,12 @@ hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int p
 // P % 64 == 0, r < P), left in Y[b]; X0, X1 are scratch of the same size.  ordered: the rows of H are ordered like its
 // eigenvalues (a block iteration's); required for P > 128 (split_direct).  The eigenvalues at the cut are looked for among the
 // 64 rows around it, 128 without `ordered` and for images with again[b] != 0 (optional).  `scratch`: split_scratch_bytes(B, P) bytes, read
-// again by the two launchers below.  skip (optional, [B]): images with a non-zero entry are left out.  img_status as
-// for launch_jacobi_eigen.  Where the eigenvalues at the cut cannot be told apart the image gets no projector.
+// again by the two launchers below.  skip (optional, [B]): images with a non-zero entry are left out.  Where the eigenvalues at the
+// cut cannot be told apart, or a wait ran out, the image gets no projector.
 size_t split_scratch_bytes(int B, int P);
 bool split_direct(int nP);
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
-                                 const int* skip, const int* again, int* img_status, hipStream_t stream);
+                                 const int* skip, const int* again, hipStream_t stream);
 // Residual check and energies of a block iteration, see split.hip.  slow[b] != 0: the image was left out of the split.
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
                                int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,
@@ -182,14 +182,15 @@ hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n,
 // Energies c[b, i], i < n, in the span of the r dominant eigenvectors of G[b] (fp64, n x n, pitch nP, left untouched) by
 // block subspace iteration; for P == 0 and nP <= 128 by the projector of G itself.
 // subspace_block: block size P for (n, r), 0 when the matrix is better split (nP <= 128) or solved as a whole.
-// On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second, 3 by the projector of G.
+// On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second, 3 by the projector of G.  0 also where a wait of
+// its kernels ran out.
 int subspace_block(int n, int r);
 size_t subspace_workspace_bytes(int B, int n, int nP, int P);
 // probe_begin / probe_end (optional): recorded around the first of the subspace_product_launches()
 // launches of the product Yt G (P x nP x nP per image).
 int subspace_product_launches();
 hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, void* ws, int* ok,
-                                 float* c, int* img_status, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t stream);
+                                 float* c, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t stream);
 
 // ---------------------------------------------------------------- greedy.hip
 // Greedy residual picks (variant): pivoted Cholesky of G[b] (fp64, pitch nP; G may be overwritten with the residual

@@ -387,7 +387,7 @@ __device__ __forceinline__ void tile_of(int t, int& i, int& j) {      // t-th ti
 template <bool WIDE, int KS>
 __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P,
                                                                  int r, const double* __restrict__ off, const double* __restrict__ link, bool ordered,
-                                                                 int W, SplitCtl* ctl, int* img_status, long long limit_ticks) {
+                                                                 int W, SplitCtl* ctl, long long limit_ticks) {
   static_assert(WIDE || KS == 1, "");
   constexpr int TT = WIDE ? 2 * ST : ST;             // tile of the workgroup
   extern __shared__ double part[];                   // [4 KS][ST][STP], one tile of 32 x 32 per wave
@@ -599,7 +599,6 @@ __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel
       for (int q = tid; q < (p < a ? P : a); q += 256 * KS) Yb[(long)p * P + q] = p == q ? 1.0 : 0.0;
   }
   if (slot == 0 && tid == 0) cb->state = done ? 2 : 3;   // every workgroup of the image has read it (behind a barrier, or gave up)
-  if (!alive && img_status && tid == 0) img_status[b] = 1;
 }
 
 // A workgroup that gave up has not stored its part, whatever slot 0 went on to report.
@@ -684,7 +683,7 @@ __global__ __launch_bounds__(256) void direct_energy_kernel(const double* __rest
 size_t split_scratch_bytes(int B, int P) { return (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256 + 2 * (size_t)B * P * 8; }
 
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
-                                 const int* skip, const int* again, int* img_status, hipStream_t st) {
+                                 const int* skip, const int* again, hipStream_t st) {
   if (P < 64 || P % 64 != 0 || P > 4096 || r < 1 || r >= P || (!ordered && P > SN)) return hipErrorInvalidValue;
   SplitCtl* ctl = (SplitCtl*)scratch;
   double* off = (double*)((char*)scratch + (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256);
@@ -712,7 +711,7 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   if (ordered) hipLaunchKernelGGL(split_kernel<64>, sg, dim3(256), 0, st, H, P, stride, B, r, off, link, ctl, skip, again);
   if (!ordered || again) hipLaunchKernelGGL(split_kernel<SN>, sg, dim3(256), 0, st, H, P, stride, B, r, off, link, ctl, skip, again);
   hipLaunchKernelGGL(kern, dim3((unsigned)(B * W)), dim3(form == 1 ? 512 : 256), lds, st, H, X0, Y, X1, P, r, (const double*)off, (const double*)link,
-                     ordered, (int)W, ctl, img_status, barrier_limit_ticks());
+                     ordered, (int)W, ctl, barrier_limit_ticks());
   return hipGetLastError();
 }
 

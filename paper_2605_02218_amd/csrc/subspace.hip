@@ -412,7 +412,7 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
 // eight of 384 172, sixty-four of 256 98; this 55, 108 and 80 (eleven of the eighteen a row takes are the elimination).
 // Dynamic LDS: 2 * 64 * 65 doubles.
 __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, double* __restrict__ diag, double* __restrict__ pivots, int P,
-                                                   PlanArgs q, CholFlags* flags, int* img_status, long long limit_ticks) {
+                                                   PlanArgs q, CholFlags* flags, long long limit_ticks) {
   extern __shared__ double lds[];
   double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert (tiles below the diagonal)
   double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor; before: T, then L[i,K]
@@ -575,7 +575,6 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     q.left[b] = 1;
     rest_on(q, b);
     q.out[ST_REST * q.B + b] = 2;
-    if (img_status) img_status[b] = 1;
   }
 }
 
@@ -770,7 +769,7 @@ int subspace_product_launches() {
 }
 
 hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, void* ws_, int* ok,
-                                 float* c, int* img_status, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t st) {
+                                 float* c, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t st) {
   if (P == 0) {
     // the whole matrix is the window
     if (!split_direct(nP)) return hipErrorInvalidValue;
@@ -778,7 +777,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     double* X0 = (double*)ws_;
     double *Y = X0 + sq, *X1 = Y + sq;
     void* scratch = (void*)(((uintptr_t)(X1 + sq) + 255) & ~(uintptr_t)255);
-    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, nullptr, img_status, st);
+    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, nullptr, st);
     return ed != hipSuccess ? ed : launch_direct_energy(G, Y, B, n, nP, r, scratch, ok, c, st);
   }
   hipError_t e0;
@@ -836,7 +835,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     q.in = state(k); q.out = state(k + 1); q.plan = plan; q.left = left; q.B = B; q.r = r; q.slots = slots; q.first = first; q.pass = pass; q.closing = closing;
     const int orth = k < kStates1 ? k : k - kStates1;               // of its pass
     hipLaunchKernelGGL(chol_kernel, dim3((unsigned)(B * (P / NB))), dim3(512), kCholLds, st, S, D, diag, pivots, P, q, flags + (size_t)orth * B,
-                       img_status, barrier_limit_ticks());
+                       barrier_limit_ticks());
     const dim3 tg((unsigned)(B * (nP / NB)));
     const double *cS = S, *cD = D;
     const int* in = state(k);
@@ -879,7 +878,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, X1, scratch, left, pass_no == 1 ? nullptr : failed, img_status, st)) != hipSuccess) return e;
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, X1, scratch, left, pass_no == 1 ? nullptr : failed, st)) != hipSuccess) return e;
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;

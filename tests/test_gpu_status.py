@@ -61,3 +61,34 @@ def test_status_is_zero_after_a_normal_call_and_one_after_a_starved_wait(C, lr_m
     torch.cuda.synchronize()
     assert st2.cpu().numpy().tolist() == [0] * W.batch
     assert torch.equal(idx2, idx0)
+
+
+@pytest.mark.parametrize("n,r", [(60, 20)], ids=["direct-split"])
+def test_status_one_means_no_result_and_zero_a_valid_one(C, n, r):
+    """An image whose split or block iteration gave up goes on to the full solve.  Of 60 tokens that is one workgroup, which waits for nobody:
+    the result is valid and the status 0.  Of 300 it gives up as well: status 1 and no energy that could pass for one."""
+    import torch
+    B, d = 4, 320
+    X = np.stack([I.make_spectrum_tokens(n, d, np.exp(-0.05 * np.arange(n)), seed=b, dtype=I.FP32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    args = (p, torch.from_numpy(X).cuda(), torch.rand(B, n, generator=torch.Generator().manual_seed(1)).cuda())
+    ws = C.alloc_workspace(p)
+    c0 = C.select(*args, workspace=ws)["c"].clone()
+    assert C.image_status(p, ws).tolist() == [0] * B
+    print("shortening the wait limit to 1 us (%d tokens)" % n, flush=True)
+    C.set_wait_limit_us(1)
+    try:
+        out = C.select(*args, workspace=ws)
+        st = C.image_status(p, ws)
+        torch.cuda.synchronize()
+    finally:
+        C.set_wait_limit_us(0)
+    st = st.tolist()
+    assert sum(st) == (0 if n <= 64 else B), st
+    for b in range(B):
+        idx = out["idx"][b].tolist()
+        assert idx == sorted(set(idx)) and 0 <= idx[0] and idx[-1] < n
+        if st[b]:
+            assert torch.isnan(out["c"][b]).all()
+        else:
+            assert (out["c"][b] - c0[b]).abs().max() < 1e-6 * c0[b].max()
