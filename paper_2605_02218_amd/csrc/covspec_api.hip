@@ -376,7 +376,7 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
     }
     HIPCHK(launch_jacobi_eigen(A, q.B, q.M, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, img_status, st));
     marks.mark(COVSPEC_STAGE_KEEP);
-    HIPCHK(launch_subspace_energy(A, q.B, q.M, q.M, q.nP, (long)q.nP * q.nP, q.r, at<double>(ws, q.lam), c, ok, 0, st));
+    HIPCHK(launch_subspace_energy(A, q.B, q.M, q.M, q.nP, (long)q.nP * q.nP, q.r, at<double>(ws, q.lam), c, ok, 0, img_status, st));
     HIPCHK(launch_select_top(c, q.B, q.M, q.k, idxm, idx_out, st));
   } else {
     int32_t* order = at<int32_t>(ws, q.order);
@@ -842,7 +842,7 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
     }
     HIPCHK(launch_copy_images(A, Gc, q.B, gstride, ok, st));      // the full solve overwrites its input
     HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, st));
-    HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, ok, 0, st));
+    HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, ok, 0, nullptr, st));
     int32_t* selw = at<int32_t>(ws, q.sel);
     HIPCHK(launch_select_top(c, q.B, nC, q.k, nullptr, selw, st));
     sel = selw;

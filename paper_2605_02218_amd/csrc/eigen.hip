@@ -420,11 +420,16 @@ __global__ __launch_bounds__(256) void row_length_kernel(const double* __restric
 // ascending k; i < n.  Images with (flag[b] != 0) != (run_if != 0) are skipped (flag == nullptr: none).
 __global__ __launch_bounds__(256) void energy_kernel(const double* __restrict__ A, int rows, int n, int pitch, long img_stride,
                                                       int r, const double* __restrict__ lam, float* __restrict__ c,
-                                                      const int* __restrict__ flag, int run_if) {
+                                                      const int* __restrict__ flag, int run_if, const int* __restrict__ gave_up) {
   __shared__ double slam[4096];
   __shared__ unsigned char sel[4096];
   const int b = blockIdx.y;
   if (flag && (flag[b] != 0) != (run_if != 0)) return;     // flag: 0 = not converged, any other value = converged
+  if (gave_up && gave_up[b]) {                             // rows without a length are never among the longest: say so here
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) c[(long)b * n + i] = __uint_as_float(0x7fc00000u);
+    return;
+  }
   const double* lb = lam + (long)b * rows;
   for (int k = threadIdx.x; k < rows; k += 256) slam[k] = lb[k];
   __syncthreads();
@@ -491,10 +496,10 @@ hipError_t launch_jacobi_eigen(double* A, int B, int n, int nP, int r, void* ctl
 }
 
 hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int pitch, long img_stride, int r, double* lam,
-                                  float* c, const int* flag, int run_if, hipStream_t st) {
+                                  float* c, const int* flag, int run_if, const int* gave_up, hipStream_t st) {
   if (rows > 4096 || r > rows) return hipErrorInvalidValue;
   hipLaunchKernelGGL(row_length_kernel, dim3((rows + 3) / 4, B), dim3(256), 0, st, A, rows, pitch, img_stride, lam);
-  hipLaunchKernelGGL(energy_kernel, dim3((n + 255) / 256, B), dim3(256), 0, st, A, rows, n, pitch, img_stride, r, lam, c, flag, run_if);
+  hipLaunchKernelGGL(energy_kernel, dim3((n + 255) / 256, B), dim3(256), 0, st, A, rows, n, pitch, img_stride, r, lam, c, flag, run_if, gave_up);
   return hipGetLastError();
 }
 

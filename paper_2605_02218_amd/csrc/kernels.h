@@ -155,9 +155,9 @@ hipError_t launch_jacobi_eigen(double* A, int B, int n, int nP, int r, void* ctl
 // Subspace energy (paper energy equation) from rows of the form lambda_k v_k^T: c[b,i] = sum over the r
 // longest of the `rows` rows of A[b] of A[k][i]^2 / |row k|, i < n.  A[b] starts at b*img_stride, rows have
 // `pitch` doubles.  `lam` is scratch of B*rows doubles.  Images with flag[b] != run_if are skipped
-// (flag == nullptr: none).
+// (flag == nullptr: none), those with gave_up[b] != 0 (optional) get NaN.
 hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int pitch, long img_stride, int r, double* lam,
-                                  float* c, const int* flag, int run_if, hipStream_t stream);
+                                  float* c, const int* flag, int run_if, const int* gave_up, hipStream_t stream);
 
 // ---------------------------------------------------------------- split.hip
 // Projector onto the span of the r dominant eigenvectors of the symmetric positive semidefinite H[b] (P x P, pitch P,

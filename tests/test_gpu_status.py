@@ -63,7 +63,7 @@ def test_status_is_zero_after_a_normal_call_and_one_after_a_starved_wait(C, lr_m
     assert torch.equal(idx2, idx0)
 
 
-@pytest.mark.parametrize("n,r", [(60, 20)], ids=["direct-split"])
+@pytest.mark.parametrize("n,r", [(60, 20), (300, 40)], ids=["direct-split", "block-iteration"])
 def test_status_one_means_no_result_and_zero_a_valid_one(C, n, r):
     """An image whose split or block iteration gave up goes on to the full solve.  Of 60 tokens that is one workgroup, which waits for nobody:
     the result is valid and the status 0.  Of 300 it gives up as well: status 1 and no energy that could pass for one."""
