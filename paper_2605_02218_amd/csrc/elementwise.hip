@@ -655,7 +655,7 @@ hipError_t launch_zero_padding(double* A, int B, int n, int pitch, hipStream_t s
 }
 
 hipError_t launch_copy_images(double* dst, const double* src, int B, long each, const int* leave, hipStream_t st) {
-  if (each % 2 != 0 || B > 65535) return hipErrorInvalidValue;
+  if (each % 2 != 0) return hipErrorInvalidValue;
   const unsigned blocks = blocks_for(each / 2, 256);
   hipLaunchKernelGGL(copy_images_kernel, dim3(blocks < 512u ? blocks : 512u, (unsigned)B), dim3(256), 0, st, (u32x4_t*)dst, (const u32x4_t*)src, each / 2, leave);
   return hipGetLastError();

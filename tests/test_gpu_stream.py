@@ -97,3 +97,24 @@ def test_stream_at_the_benchmark_shape(C):
     # four frames fill the memory, two decide among 1280 candidates (block iteration with a block of 192)
     # (the videos of the benchmark: seeds 0..3)
     assert _run(C, B=4, n_frames=6, n_frame=1024, d=1536, m=256, k=1024, r=128, dtype=I.BF16, seed0=0) == 8
+
+
+def test_stream_takes_as_many_videos_as_a_grid_dimension(C):
+    """65536 tiny videos in one call (11 GB of workspace): as many as the second dimension of a grid holds."""
+    import torch
+    B, d = 65536, 8
+    p = C.StreamParams(batch=B, n_frame=2, d_model=d, frame_m=1, keep_k=2, rank_r=1, dtype=C.FP32)
+    ws = torch.empty(C.stream_workspace_size(p) + 256, dtype=torch.uint8, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(0)
+    Z = torch.randn(B, 2, d, generator=g, device="cuda")
+    G = torch.bmm(Z.double(), Z.double().transpose(1, 2).contiguous())
+    ids = torch.arange(2, device="cuda", dtype=torch.int32).repeat(B, 1)
+    F, s = torch.randn(B, 2, d, generator=g, device="cuda"), torch.rand(B, 2, generator=g, device="cuda")
+    dst = C.stream_alloc_state(p)
+    n, c = C.stream_step(p, 2, 10, F, s, (Z, G, ids), dst, workspace=ws, want_c=True)
+    torch.cuda.synchronize()
+    assert n == 2
+    for b in (0, 1, 40000, B - 1):
+        ref = S.stream_step(S.StreamState(Z[b].double().cpu().numpy(), np.arange(2)), F[b].double().cpu().numpy(), s[b].cpu().numpy(), 10, 1, 2, 1)
+        np.testing.assert_allclose(c[b].cpu().numpy(), ref["c"], rtol=0, atol=1e-6 * ref["c"].max())
+        np.testing.assert_array_equal(dst[2][b].cpu().numpy(), ref["ids"])
