@@ -118,3 +118,41 @@ def test_stream_takes_as_many_videos_as_a_grid_dimension(C):
         ref = S.stream_step(S.StreamState(Z[b].double().cpu().numpy(), np.arange(2)), F[b].double().cpu().numpy(), s[b].cpu().numpy(), 10, 1, 2, 1)
         np.testing.assert_allclose(c[b].cpu().numpy(), ref["c"], rtol=0, atol=1e-6 * ref["c"].max())
         np.testing.assert_array_equal(dst[2][b].cpu().numpy(), ref["ids"])
+
+
+def test_stream_videos_that_need_the_full_solve_beside_others(C):
+    """A batch in which the block iteration answers for some videos and the full solve, on its own copy of the Gram matrix, for the others: the
+    energies and the carried Gram matrix of each against the oracle."""
+    import torch
+    B, n_frame, d, m, k, r = 5, 100, 384, 96, 224, 24
+    rng = np.random.default_rng(11)
+    rows = []
+    for b in range(B):
+        decay = 0.001 if b % 2 else 0.03                   # 0.001: lambda_24 is 1.2 times what the block leaves out
+        sigma = np.exp(-decay * np.arange(k + m))
+        rows.append(I.make_spectrum_tokens(k + m, d, sigma, seed=60 + b, dtype=I.FP32))
+    Z = np.stack([x[:k] for x in rows])
+    F = np.concatenate([np.stack([x[k:] for x in rows]), np.zeros((B, n_frame - m, d), np.float32)], axis=1)
+    s = np.concatenate([1.0 + rng.random((B, m)), rng.random((B, n_frame - m))], axis=1).astype(np.float32)     # the first m are pre-selected
+    Zd = Z.astype(np.float64)
+    G = Zd @ Zd.transpose(0, 2, 1)
+    p = C.StreamParams(batch=B, n_frame=n_frame, d_model=d, frame_m=m, keep_k=k, rank_r=r, dtype=I.FP32)
+    ws = torch.empty(C.stream_workspace_size(p) + 256, dtype=torch.uint8, device="cuda")
+    dst = C.stream_alloc_state(p)
+    ids = torch.arange(k, device="cuda", dtype=torch.int32).repeat(B, 1)
+    src = (_dev(Z, I.FP32), torch.from_numpy(G).cuda(), ids)
+    n, c = C.stream_step(p, k, 1000, _dev(F, I.FP32), torch.from_numpy(s).cuda(), src, dst, workspace=ws, want_c=True)
+    # which way the solve of the same matrices takes
+    q = C.Params(batch=B, n_tokens=k + m, d_model=d, n_query=1, dtype=C.FP32, keep_k=k, preselect_m=k + m, rank_r=r)
+    w2 = C.alloc_workspace(q)
+    C.select(q, _dev(np.stack(rows), I.FP32), torch.rand(B, k + m, generator=torch.Generator().manual_seed(0)).cuda(), workspace=w2)
+    assert C.lowrank_path(q, w2).tolist() == [1, 0, 1, 0, 1]
+    for b in range(B):
+        st = S.StreamState(Zd[b], np.arange(k))
+        ref = S.stream_step(st, F[b].astype(np.float64), s[b], 1000, m, k, r)
+        assert ref["margin_topk"] > 1e-6 and ref["sigma_gap"] > 5e-4, ref
+        got = c[b].cpu().numpy().astype(np.float64)
+        np.testing.assert_allclose(got, ref["c"], rtol=0, atol=1e-6 * ref["c"].max(), err_msg="video %d" % b)
+        np.testing.assert_array_equal(dst[2][b, :n].cpu().numpy(), ref["ids"], err_msg="video %d" % b)
+        Gref = st.rows @ st.rows.T
+        np.testing.assert_allclose(dst[1][b, :n, :n].cpu().numpy(), Gref, rtol=0, atol=1e-12 * Gref.max(), err_msg="video %d" % b)
