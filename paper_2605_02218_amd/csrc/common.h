@@ -90,6 +90,12 @@ __device__ __forceinline__ int block_exscan_1024(int v, int* wsum, int* total) {
   return wsum[w] + inc - v;
 }
 
+// value of `v` in lane k of every row of 16 lanes, in one move
+template <int k>
+__device__ __forceinline__ double row_lane(double v) {
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + k, 0xf, 0xf, true);   // row_newbcast:k
+}
+
 // Barrier in global memory over the workgroups that work on one image.  `arrived` only grows; `target` is the
 // value it reaches when all of them have arrived at this barrier.  Every thread's earlier global writes are
 // visible to every thread of the group behind the barrier (device-scope release before, acquire after: the

@@ -247,8 +247,8 @@ __global__ __launch_bounds__(TPB) void greedy_single_kernel(const double* __rest
   }
 }
 
-// Right-looking in blocks of BK picks, an image of up to 4096 rows spread over W workgroups of 1024 threads (a thread
-// owns NR rows, 1024 apart).  The residual matrix R = G - L L^T is kept in global memory IN PLACE of G and
+// Right-looking in blocks of 16 picks (BK in what both of these kernels use), an image of up to 960 rows spread over W workgroups of 1024 threads
+// (a thread owns a row).  The residual matrix R = G - L L^T is kept in global memory IN PLACE of G and
 // brought up to date once per block by a rank-BK update on the MFMA; inside a block a new column is the pivot's
 // row of R minus the product with the block's earlier columns, which live in LDS.  The left-looking kernels above
 // re-read every earlier column at every step (k^2 n / 2 values); this one reads one row of R per step and reads
@@ -257,19 +257,19 @@ __global__ __launch_bounds__(TPB) void greedy_single_kernel(const double* __rest
 // same decisions: nothing is exchanged), then the workgroups meet at the image's barrier, each brings its own
 // 16-row bands of R up to date, and they meet again before the next block reads rows of R: two barriers per
 // block instead of one per pick, and the device's bandwidth on the update instead of one workgroup's.
-// Picks are made in runs.  A residual only ever shrinks, so while the largest residual of the CAND largest ones at the start of the
+// Picks are made in runs.  A residual only ever shrinks, so while the largest residual of the 64 largest ones at the start of the
 // run stays above all the others as they were then, the others need not be looked at: one wave makes the picks from the
-// CAND x CAND submatrix of R in LDS, no barrier and no row of R to wait for, and the columns of the run are formed for all rows
+// 64 x 64 submatrix of R in LDS, no barrier and no row of R to wait for, and the columns of the run are formed for all rows
 // behind it, the rows of R requested together.  A run ends when a residual left out could be the largest (6.3 to 7 picks on the
-// average with 64 candidates on the token matrices of the workloads, 5 to 10 over their images), at the end of a block, and
+// average on the token matrices of the workloads, 5 to 10 over their images), at the end of a block, and
 // before a residual that is not finite.  Residuals are compared with their rows, so that a tie ends no run that goes on in lower rows
 // (300 rows of one length, orthogonal, 150 picks, us: 414 with a step per pick, 1330 with every tie the end of a run, 340 so).
-// Candidates are the CAND largest of the eight largest of each wave; ordered by (residual rounded to fp32, lower row), so that the
+// Candidates are the 64 largest of the eight largest of each wave; ordered by (residual rounded to fp32, lower row), so that the
 // first pick of a run is the largest of all whatever ties there are.
 // Bound by the chain of picks: us for 463 picks of 926 rows, six images, with all rows in every step (a maximum over the
 // workgroup, the pivot's row from memory and a barrier per pick) 1842, so 1470 (66 to 73
 // runs of 11 us and 28 updates of R of 20, both bound by latency and the memory-side cache).
-// Dynamic LDS: BK * nP + CAND * (CAND + 1) doubles; workgroups take (image, slot) from the ticket counter.
+// Dynamic LDS: 16 * nP + 64 * 65 doubles; workgroups take (image, slot) from the ticket counter.
 
 // Maximum of one 32-bit key per lane over the wave with DPP moves (no LDS round trips): quads, then shifts by 4 and
 // 8 inside a row of 16 lanes, then the last lane of a row broadcast into the next row (rows 1 and 3) and lane 31
@@ -300,11 +300,6 @@ __device__ __forceinline__ int best_lane(uint32_t key, uint32_t best, uint32_t r
 __device__ __forceinline__ double lane_value(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
-// value of `v` in lane k of every row of 16 lanes
-template <int k>
-__device__ __forceinline__ double row16_lane(double v) {
-  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + k, 0xf, 0xf, true), __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + k, 0xf, 0xf, true));
-}
 // Key of an unpicked row; 0 is below all of them.
 __device__ __forceinline__ uint32_t residual_key(double rho) {
   const uint32_t u = float_order_key((float)rho);
@@ -312,6 +307,7 @@ __device__ __forceinline__ uint32_t residual_key(double rho) {
 }
 constexpr uint32_t kKeyInf = 0xFF800000u;       // of +infinity; those of NaNs with a clear sign lie above
 constexpr int kWaveBest = 8;                    // keys a wave posts
+constexpr int kRunBlock = 16, kCand = 64;       // picks of a block, candidates of a run
 
 struct GreedyRun {
   unsigned long long post[TPB / 64 * kWaveBest];   // per wave its largest keys: (residual, ~row), 0 where there are no more rows
@@ -320,12 +316,12 @@ struct GreedyRun {
   uint32_t left[TPB / 64];                         // per wave the largest key it did not post, and the lowest row that has it
   int left_row[TPB / 64];
   unsigned long long next;                         // the largest key posted that is no candidate
-  int cand[64];
-  double cand_rho[64];
-  double factor[16 * 16];                          // [q][m]: column q of the run at the row of its pick m
-  double rho[16];                                  // of the picks
-  double inverse[16];                              // of their square roots; -1: nothing left of the row, its column is zero
-  int pick[16];
+  int cand[kCand];
+  double cand_rho[kCand];
+  double factor[kRunBlock * kRunBlock];            // [q][m]: column q of the run at the row of its pick m
+  double rho[kRunBlock];                           // of the picks
+  double inverse[kRunBlock];                       // of their square roots; -1: nothing left of the row, its column is zero
+  int pick[kRunBlock];
   int picks;
   int flag;
 };
@@ -341,9 +337,9 @@ __device__ __forceinline__ int lowest_left_out(const GreedyRun& run, uint32_t bo
 
 // Pick m of a run and those after it, by one wave; a lane has one candidate.  col[q] is column q of the run at its row.  bound is the
 // largest residual left out; it goes before a candidate of the same residual in a later row.
-template <int BK, int CAND, int M>
-__device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int room, uint32_t bound, uint32_t row, double rho, bool open, double (&col)[BK]) {
-  if constexpr (M < BK) {
+template <int M>
+__device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int room, uint32_t bound, uint32_t row, double rho, bool open, double (&col)[kRunBlock]) {
+  if constexpr (M < kRunBlock) {
     if (M >= room) return M;
     const int lane = threadIdx.x & 63;
     const uint32_t key = open ? residual_key(rho) : 0u;
@@ -351,7 +347,7 @@ __device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int ro
     if (best == 0u || (M > 0 && (best < bound || best >= kKeyInf))) return M;
     const int at = __builtin_amdgcn_readfirstlane(best_lane(key, best, row));
     if (M > 0 && best == bound && __builtin_amdgcn_readlane((int)row, at) > lowest_left_out(run, bound)) return M;
-    double c = lane < CAND ? S[at * (CAND + 1) + lane] : 0.0;
+    double c = S[at * (kCand + 1) + lane];
     const double piv = lane_value(rho, at);
     const double inverse = piv > 0.0 ? 1.0 / sqrt(piv) : -1.0;
     double taken = 0.0;
@@ -369,28 +365,28 @@ __device__ __forceinline__ int run_picks(const double* S, GreedyRun& run, int ro
     col[M] = inverse < 0.0 ? 0.0 : c * inverse;
     rho -= col[M] * col[M];
     if (best >= kKeyInf) return M + 1;
-    return run_picks<BK, CAND, M + 1>(S, run, room, bound, row, rho, open, col);
+    return run_picks<M + 1>(S, run, room, bound, row, rho, open, col);
   }
   return M;
 }
 
 // c[m] -= l factor_m for the picks m of a run, the factors in lane m of every row of 16 lanes; and the columns of the run themselves
-template <int BK, int FROM, int M>
-__device__ __forceinline__ void take_out(double (&c)[BK], double l, double factors) {
-  if constexpr (M < BK) {
-    if constexpr (M >= FROM) c[M] = fma(-l, row16_lane<M>(factors), c[M]);
-    take_out<BK, FROM, M + 1>(c, l, factors);
+template <int FROM, int M>
+__device__ __forceinline__ void take_out(double (&c)[kRunBlock], double l, double factors) {
+  if constexpr (M < kRunBlock) {
+    if constexpr (M >= FROM) c[M] = fma(-l, row_lane<M>(factors), c[M]);
+    take_out<FROM, M + 1>(c, l, factors);
   }
 }
-template <int BK, int M>
-__device__ __forceinline__ void run_columns(double (&c)[BK], const GreedyRun& run, int picks, double inverses, double& rho) {
-  if constexpr (M < BK) {
+template <int M>
+__device__ __forceinline__ void run_columns(double (&c)[kRunBlock], const GreedyRun& run, int picks, double inverses, double& rho) {
+  if constexpr (M < kRunBlock) {
     if (M >= picks) return;
-    const double inverse = row16_lane<M>(inverses);
+    const double inverse = row_lane<M>(inverses);
     c[M] = inverse < 0.0 ? 0.0 : c[M] * inverse;
     rho -= c[M] * c[M];
-    if constexpr (M + 1 < BK) take_out<BK, M + 1, 0>(c, c[M], run.factor[M * 16 + (threadIdx.x & 15)]);
-    run_columns<BK, M + 1>(c, run, picks, inverses, rho);
+    if constexpr (M + 1 < kRunBlock) take_out<M + 1, 0>(c, c[M], run.factor[M * 16 + (threadIdx.x & 15)]);
+    run_columns<M + 1>(c, run, picks, inverses, rho);
   }
 }
 
@@ -447,14 +443,13 @@ __device__ __forceinline__ bool update_rows(double* R, double* Lblk, int n, int 
   return true;
 }
 
-template <int BK, int NR, int CAND>
 __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int nP, int k, int W, int32_t* __restrict__ order,
                                                             float* __restrict__ resid, GreedyCtl* ctl, int* img_status,
                                                             long long limit_ticks) {
-  extern __shared__ double Lblk[];        // [BK][nP], then [CAND][CAND + 1]
+  extern __shared__ double Lblk[];        // [kRunBlock][nP], then [kCand][kCand + 1]
   __shared__ GreedyRun run;
-  double* S = Lblk + (size_t)BK * nP;
-  constexpr int POSTS = TPB / 64 * kWaveBest;
+  double* S = Lblk + (size_t)kRunBlock * nP;
+  constexpr int BK = kRunBlock, CAND = kCand, POSTS = TPB / 64 * kWaveBest;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
   if (tid == 0) run.flag = (int)atomicAdd(&ctl[0].ticket, 1u);
   __syncthreads();
@@ -463,18 +458,12 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
   const int b = ticket / W, slot = ticket - b * W;
   GreedyCtl* cb = ctl + b;
   double* R = G + (long)b * nP * nP;
-  // row0, row0 + 1024, ... are this thread's rows.  Few rows are dealt to all waves, sixteen neighbours (a 128-byte piece of a row of R)
-  // at a time: of the rows of one wave only eight become candidates.
-  const int row0 = n <= TPB / 2 ? (lane >> 4) * (TPB / 4) + 16 * w + i16 : tid;
+  // Row of this thread.  Few rows are dealt to all waves, sixteen neighbours (a 128-byte piece of a row of R) at a time: of the rows of one
+  // wave only eight become candidates.
+  const int i = n <= TPB / 2 ? (lane >> 4) * (TPB / 4) + 16 * w + i16 : tid;
 
-  double rho[NR];
-  bool picked[NR];
-#pragma unroll
-  for (int s = 0; s < NR; ++s) {
-    const int i = row0 + TPB * s;
-    rho[s] = (i < n) ? R[(long)i * nP + i] : 0.0;
-    picked[s] = !(i < n);
-  }
+  double rho = i < n ? R[(long)i * nP + i] : 0.0;
+  bool picked = !(i < n);
   for (int e = tid; e < BK * nP; e += TPB) Lblk[e] = 0.0;
   unsigned int target = 0;
   bool alive = true;
@@ -484,29 +473,19 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
   for (int t = 0; t < k;) {
     // ---- the largest keys of each wave
     {
-      uint32_t key[NR];
-#pragma unroll
-      for (int s = 0; s < NR; ++s) key[s] = picked[s] ? 0u : residual_key(rho[s]);
+      uint32_t key = picked ? 0u : residual_key(rho);
 #pragma unroll 1
       for (int e = 0; e <= kWaveBest; ++e) {
-        uint32_t mine = key[0];
-        int row = row0;
-        double r = rho[0];
-#pragma unroll
-        for (int s = 1; s < NR; ++s)
-          if (key[s] > mine) { mine = key[s]; row = row0 + TPB * s; r = rho[s]; }
-        const uint32_t best = wave_max_u32(mine);
+        const uint32_t best = wave_max_u32(key);
         if (e == kWaveBest) {
           if (lane == 0) run.left[w] = best;
-          if (lane == __ffsll((long long)__ballot(mine == best)) - 1) run.left_row[w] = row;     // lower lanes have lower rows
+          if (lane == __ffsll((long long)__ballot(key == best)) - 1) run.left_row[w] = i;        // lower lanes have lower rows
         } else if (best == 0u) {
           if (lane == 0) run.post[kWaveBest * w + e] = 0ull;
-        } else if (lane == best_lane(mine, best, (uint32_t)row)) {
-          run.post[kWaveBest * w + e] = ((unsigned long long)best << 32) | (0xFFFFFFFFu - (uint32_t)row);
-          run.post_rho[kWaveBest * w + e] = r;
-#pragma unroll
-          for (int s = 0; s < NR; ++s)
-            if (row == row0 + TPB * s) key[s] = 0u;
+        } else if (lane == best_lane(key, best, (uint32_t)i)) {
+          run.post[kWaveBest * w + e] = ((unsigned long long)best << 32) | (0xFFFFFFFFu - (uint32_t)i);
+          run.post_rho[kWaveBest * w + e] = rho;
+          key = 0u;
         }
       }
     }
@@ -562,10 +541,10 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
     if (w == 0) {
       uint32_t bound = lane < TPB / 64 ? run.left[lane] : lane == TPB / 64 ? (uint32_t)(run.next >> 32) : 0u;
       bound = wave_max_u32(bound);
-      const int row = lane < CAND ? run.cand[lane] : -1;
+      const int row = run.cand[lane];
       double col[BK];
       const int room = BK - jj < k - t ? BK - jj : k - t;
-      const int picks = run_picks<BK, CAND, 0>(S, run, room, bound, (uint32_t)row, row < 0 ? 0.0 : run.cand_rho[lane], row >= 0, col);
+      const int picks = run_picks<0>(S, run, room, bound, (uint32_t)row, row < 0 ? 0.0 : run.cand_rho[lane], row >= 0, col);
       if (lane == 0) run.picks = picks;
     }
     __syncthreads();
@@ -583,36 +562,21 @@ __global__ __launch_bounds__(TPB) void greedy_panel_kernel(double* G, int n, int
     {
       const int mine = i16 < picks ? run.pick[i16] : run.pick[0];      // of the run's pick i16
       const double inverses = i16 < picks ? run.inverse[i16] : -1.0;
-      double c[NR][BK];
+      double c[BK];
 #pragma unroll
-      for (int s = 0; s < NR; ++s) {
-        const int i = row0 + TPB * s;
-#pragma unroll
-        for (int m = 0; m < BK; ++m) {
-          c[s][m] = 0.0;
-          if (m < picks) {
-            const int p = __builtin_amdgcn_readlane(mine, m);
-            if (i < n) c[s][m] = R[(long)p * nP + i];
-            if (p == i) picked[s] = true;
-          }
+      for (int m = 0; m < BK; ++m) {
+        c[m] = 0.0;
+        if (m < picks) {
+          const int p = __builtin_amdgcn_readlane(mine, m);
+          if (i < n) c[m] = R[(long)p * nP + i];
+          if (p == i) picked = true;
         }
       }
-      for (int q = 0; q < jj; ++q) {
-        const double factors = Lblk[q * nP + mine];
+      for (int q = 0; q < jj; ++q) take_out<0, 0>(c, i < n ? Lblk[q * nP + i] : 0.0, Lblk[q * nP + mine]);
+      run_columns<0>(c, run, picks, inverses, rho);
 #pragma unroll
-        for (int s = 0; s < NR; ++s) {
-          const int i = row0 + TPB * s;
-          take_out<BK, 0, 0>(c[s], i < n ? Lblk[q * nP + i] : 0.0, factors);
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < NR; ++s) {
-        const int i = row0 + TPB * s;
-        run_columns<BK, 0>(c[s], run, picks, inverses, rho[s]);
-#pragma unroll
-        for (int m = 0; m < BK; ++m)
-          if (m < picks && i < nP) Lblk[(jj + m) * nP + i] = c[s][m];
-      }
+      for (int m = 0; m < BK; ++m)
+        if (m < picks && i < nP) Lblk[(jj + m) * nP + i] = c[m];
     }
     t += picks;
     jj += picks;
@@ -649,8 +613,8 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v)
   return ((unsigned long long)hi << 32) | lo;
 }
 
-// The same with all rows in every step (dynamic LDS: BK * nP doubles), for images whose candidates' submatrix would cost LDS that the
-// block's columns need: see launch_greedy.
+// The same with all rows in every step, in blocks of BK picks (dynamic LDS: BK * nP doubles), for images of up to 4096 rows (a thread owns NR of
+// them, 1024 apart), whose candidates' submatrix would cost LDS that the block's columns need: see launch_greedy.
 template <int BK, int NR>
 __global__ __launch_bounds__(TPB) void greedy_step_kernel(double* G, int n, int nP, int k, int W, int32_t* __restrict__ order,
                                                             float* __restrict__ resid, GreedyCtl* ctl, int* img_status,
@@ -800,7 +764,7 @@ size_t greedy_scratch_bytes(int B, int nP) {
 
 // Columns of a block of BK picks and the candidates' submatrix, beside the kernel's static words.
 constexpr size_t kRunLds = 160 * 1024 - sizeof(GreedyRun) - 256, kStepLds = 159 * 1024;
-static size_t run_lds(int BK, int cand, int nP) { return ((size_t)BK * nP + (size_t)cand * (cand + 1)) * sizeof(double); }
+static size_t run_lds(int nP) { return ((size_t)kRunBlock * nP + (size_t)kCand * (kCand + 1)) * sizeof(double); }
 
 template <typename K>
 static hipError_t launch_panel(K kernel, PerDeviceInt& raised, PerDeviceInt& cache, size_t lds, size_t most, double* G, int B, int n, int nP, int k, int W,
@@ -844,7 +808,7 @@ hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int
     static PerDeviceInt raised, cache;                                                                                                          \
     return launch_panel(kernel, raised, cache, lds, most, G, B, n, nP, k, Wp, order, resid, ctl, img_status, st);                               \
   } while (0)
-    if (run_lds(16, 64, nP) <= kRunLds) COVSPEC_PANEL((greedy_panel_kernel<16, 1, 64>), run_lds(16, 64, nP), kRunLds);
+    if (run_lds(nP) <= kRunLds) COVSPEC_PANEL(greedy_panel_kernel, run_lds(nP), kRunLds);
     const size_t lds = (size_t)BK * nP * sizeof(double);
     // rows per thread: at most 1216 rows with blocks of 16, 1664 with 12, 2496 with 8
     if (BK == 16 && n <= TPB) COVSPEC_PANEL((greedy_step_kernel<16, 1>), lds, kStepLds);

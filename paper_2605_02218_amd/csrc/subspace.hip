@@ -224,13 +224,6 @@ __device__ __forceinline__ void rest_on(const PlanArgs& q, int b) {
   out[ST_END * q.B] = (at + m) & 1;
 }
 
-// value of `v` in lane k of every row of 16 lanes
-extern "C" __device__ __attribute__((const)) long long covspec_update_dpp_i64(long long, long long, int, int, int, bool) __asm("llvm.amdgcn.update.dpp.i64");
-template <int k>
-__device__ __forceinline__ double row_lane(double v) {
-  return __longlong_as_double(covspec_update_dpp_i64(0ll, __double_as_longlong(v), 0x150 + k, 0xf, 0xf, true));   // row_newbcast:k
-}
-
 // Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle: a = L L^T) and inverts the factor, by all eight waves: inv(L) goes
 // to the tiles of `inv` on and below the diagonal, the diagonal of L to dl.  The pivot of row k is floored at
 // kPivotFloor diag[k], diag the diagonal of S.  Ends with a barrier.
