@@ -164,13 +164,23 @@ def contraction_fractions(w, modes, stages):
     return {k: round(v / (stages[key[k]] * 1e-3) / peak, 4) for k, v in work.items() if stages[key[k]] > 0}
 
 
+def greedy_kernel_name(B, M, k):
+    """The greedy picks' kernel by the rule of launch_greedy (greedy.hip): values moved right-looking against left-looking, LDS."""
+    pitch = -(-M // 64) * 64
+    block = next((b for b in (16, 12, 8) if b * pitch * 8 <= 159 * 1024), 4)
+    if (k - 1) // block * 2.0 * M * M <= 1.0 * k * k * M:
+        return "greedy_panel_kernel" if pitch <= 960 else "greedy_step_kernel"
+    return "greedy_single_kernel" if B * pitch // 64 > 256 else "greedy_kernel"
+
+
 def roofline_for(w, p, p_modes, stages, probe_ms, C):
     """Roofline object of the kernel the step spends most of its time in.
 
     Candidates are the kernels that make up (nearly) all of a stage by themselves, with the stage time as the
     launch duration, and the fp64 product of the subspace iteration, timed by the library's probe events
-    around one of its equal launches (an image takes part in as many of them as its schedule asks for, so their number is an
-    upper bound).  achieved = algorithmic work of one launch / its measured duration.
+    around the first of its launches (the others, steps of the Chebyshev recurrence, read two operands more, and an image takes
+    part in as many as its schedule asks for, so launches_per_step is an upper bound there and ms_per_step_in_kernel the
+    first launch's time that often).  achieved = algorithmic work of one launch / its measured duration.
     """
     import covspec_inputs as I
     B, N, d, T, K = w.batch, w.n_tokens, w.d_model, w.n_query, w.n_act_layers
@@ -185,8 +195,10 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
     m32 = -(-M // 32)
     if bf and energy:
         gram = "gemm_gram_small_kernel" if d % 64 == 0 and d >= 256 and B * m32 * (m32 + 1) // 2 <= 512 else "gemm_dma_kernel"
+    elif bf:
+        gram = "gemm64_dma_kernel" if d % 64 == 0 else "gemm64_kernel"
     else:
-        gram = "gemm64_small_kernel" if not bf and d % 64 == 0 and tiles(M, M, 64, B) <= 256 else "gemm64_kernel"
+        gram = "gemm64_small_kernel" if d % 64 == 0 and tiles(M, M, 64, B) <= 256 else "gemm64_kernel"
     # name -> (kernel, bound, peak, unit, algorithmic work per launch, launches per step, ms per launch)
     cand = {
         "token_projection": (proj, "mfma", PEAK["mfma_bf16_TFLOPs"] if bf else PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
@@ -204,7 +216,7 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
         cand["lowrank_product"] = ("gemm64_dma_kernel", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
                                    2.0 * B * pr * pc * pk / 1e12, n_probe, probe_ms)
     elif p_modes[1] == 1:
-        cand["lowrank"] = ("greedy_kernel", "alu", PEAK["valu_fp64_TFLOPs"], "TFLOP/s", 1.0 * B * M * k * k / 1e12, 1,
+        cand["lowrank"] = (greedy_kernel_name(B, M, k), "alu", PEAK["valu_fp64_TFLOPs"], "TFLOP/s", 1.0 * B * M * k * k / 1e12, 1,
                            stages["lowrank"])
     dom = max(cand, key=lambda s: cand[s][5] * cand[s][6])
     kern, bound, peak, unit, work, launches, ms = cand[dom]

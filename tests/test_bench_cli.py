@@ -56,7 +56,16 @@ def test_roofline_names_the_kernel_that_runs():
     stages = {s: 0.0 for s in C.STAGES}
     stages["gram"] = 1.0
     for kw, modes, kernel in ((dict(batch=1, dtype=I.BF16), (0, 0), "gemm_gram_small_kernel"), (dict(batch=64, dtype=I.BF16), (0, 0), "gemm_dma_kernel"),
-                              (dict(batch=1, dtype=I.FP32), (0, 0), "gemm64_small_kernel"), (dict(batch=1, dtype=I.BF16), (1, 1), "gemm64_kernel")):
-        w = I.small_workload(n_tokens=576, d_model=4096, n_query=32, n_heads=32, keep_k=144, preselect_m=288, rank_r=72, n_act_layers=4, **kw)
+                              (dict(batch=1, dtype=I.FP32), (0, 0), "gemm64_small_kernel"), (dict(batch=1, dtype=I.BF16), (1, 1), "gemm64_dma_kernel"),
+                              (dict(batch=1, dtype=I.BF16, d_model=4000), (1, 1), "gemm64_kernel")):
+        w = I.small_workload(n_tokens=576, n_query=32, n_heads=32, keep_k=144, preselect_m=288, rank_r=72, n_act_layers=4, **dict(dict(d_model=4096), **kw))
         got = bench.roofline_for(w, None, modes, dict(stages, activity=1e-9, gather=1e-9, token_projection=1e-9, lowrank=1e-9), 0.0, Probe)
         assert got["kernel"] == kernel
+
+
+def test_roofline_names_the_kernel_of_the_greedy_picks():
+    """All rows are picks; a small part of the rows with a few images or with many; too many rows for runs of picks."""
+    import bench
+    for B, M, k, kernel in ((64, 640, 320, "greedy_panel_kernel"), (1, 960, 480, "greedy_panel_kernel"), (1, 961, 480, "greedy_step_kernel"),
+                            (4, 2304, 1152, "greedy_step_kernel"), (1, 4096, 100, "greedy_kernel"), (64, 4096, 100, "greedy_single_kernel")):
+        assert bench.greedy_kernel_name(B, M, k) == kernel
