@@ -161,8 +161,8 @@ int covspec_reduce(const covspec_params* p, const void* X, const void* hidden, c
  * recorded on `stream` when stage i begins, event COVSPEC_STAGE_END when all work has been enqueued.
  * Stage i lasted from event i to event i+1.  The two probe events bracket ONE launch of the kernel
  * the low-rank stage spends most of its time in (ENERGY_TOPK with the subspace iteration: the fp64
- * product Y^T G of the first iteration, of covspec_probe_launches() equal launches; otherwise they are
- * recorded back to back).  Same results, arguments and errors as covspec_reduce.
+ * product that forms the start block, the first of covspec_probe_launches() of these dimensions; otherwise
+ * they are recorded back to back).  Same results, arguments and errors as covspec_reduce.
  */
 enum {
   COVSPEC_STAGE_QUERY_SIDE = 0,       /* weight transposes, e(q) = q Wq, |e(q)|, folded query matrix    */
@@ -303,8 +303,10 @@ int covspec_image_status(const covspec_params* p, const void* workspace, int32_t
 void covspec_set_wait_limit_us(int64_t microseconds);
 
 /*
- * Description of the probed launch for these parameters: number of equal launches per call (0 when
- * nothing is probed) and, if non-NULL, its dimensions: the product is [rows x inner] * [inner x cols]
+ * Description of the probed launch for these parameters: how many launches of its dimensions a call makes up
+ * to the first residual check (0 when nothing is probed; an upper bound of those that work: an image takes part
+ * in as many as its schedule asks for, and all but two may read two operands more) and, if non-NULL, its
+ * dimensions: the product is [rows x inner] * [inner x cols]
  * per image in fp64 (2*rows*cols*inner flops per image).
  */
 int covspec_probe_launches(const covspec_params* p, int32_t* rows, int32_t* cols, int32_t* inner);

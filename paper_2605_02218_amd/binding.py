@@ -268,7 +268,7 @@ NUM_STAGE_EVENTS = len(STAGES) + 3
 
 
 def probe_launches(p: Params):
-    """covspec_probe_launches: (equal launches per call, rows, cols, inner) of the probed fp64 product."""
+    """covspec_probe_launches: (launches per call up to the first residual check, rows, cols, inner) of the probed fp64 product."""
     cs = p.c_struct()
     r, c, k = ctypes.c_int32(0), ctypes.c_int32(0), ctypes.c_int32(0)
     n = load_library().covspec_probe_launches(ctypes.byref(cs), ctypes.byref(r), ctypes.byref(c), ctypes.byref(k))

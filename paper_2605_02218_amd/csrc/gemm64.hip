@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 // 926 x 926 x 2048 took 308 us, so 230.
 // Requires whole k-tiles (16 or 64), pitches of whole pieces, 16-byte aligned bases.  Rows beyond M / N are clamped when loading.
 // A Chebyshev step (GemmArgs::cheb) is scale * (A B + start): the accumulators begin with the terms that are not the product,
-// whose loads are over before the first operands have landed (read behind the product they cost 30 of 260 us, see below).
+// whose loads are over before the first operands have landed (read behind the product they cost 30 of 260 us).
 __device__ __forceinline__ double cheb_scale(const GemmArgs& g, double t) { return t == 0.0 ? 1.0 : g.cheb_step == 0 ? t : 2.0 * t; }
 __device__ __forceinline__ double cheb_start(const GemmArgs& g, const double* A, const double* C, double rt, int r, int c) {   // rt = 1 / t
   const double a = A[(long)r * g.lda + c];

@@ -17,8 +17,8 @@
 //
 // Storage is transposed (vectors are rows, Yt is P x nP) so that every product is in the
 // K-contiguous "NT" form of the GEMM kernel: (G Y)^T = Yt G^T = Yt G.
-// Orthonormalisation is Cholesky-QR: S = Yt Yt^T = L L^T (blocked right-looking Cholesky, 64-wide
-// panels, trailing update on the MFMA), Yt <- L^-1 Yt (blocked forward substitution).
+// Orthonormalisation is Cholesky-QR: S = Yt Yt^T = L L^T (by block rows of 64, a workgroup each), Yt <- L^-1 Yt (blocked forward
+// substitution).
 // The start block is Omega G with a fixed +-1 pattern Omega, so exact duplicate tokens (equal rows of
 // G) cannot make it rank deficient.
 // The residual of the dominant subspace, Pi Q^T G - H U, is checked; images that fail (slow decay, P too small, no gap
@@ -34,12 +34,13 @@ namespace {
 constexpr int NB = 64;        // panel width of Cholesky / substitution
 constexpr int NBP = NB + 1;   // LDS pitch
 // Relative residual accepted for the dominant subspace, row by row (split_finish_kernel).  It perturbs an energy by at
-// most 1e-9 / (relative gap at r) relative.  A block that took the products planned for it sits at 2e-10 or below,
-// unconverged ones orders above.  (Energies as returned, in fp32, are 2.6e-8 off their 64-bit values with either, the rounding
-// to fp32.)
+// most 1e-9 / (relative gap at r) relative.  Blocks are planned to a residual of 2e-10 (plan_block: to 4e-10 where the first pass ends,
+// 8e-10 to 2e-9 where a steep image's second does) and sit at 1e-14 to 4e-10, unconverged ones orders above.  (Energies as returned, in
+// fp32, are 2.6e-8 off their 64-bit values with either, the rounding to fp32.)
 constexpr double kRitzTol = 1e-9;
-// A last factorisation with a smallest scaled pivot below this leaves rows whose inner products exceed what the residual check
-// would see (about 1e-16 over the pivot); the image goes on in the second pass.
+// A last factorisation leaves rows with inner products of about 1e-16 over its smallest scaled pivot, up to 1e-6 at this line, typically
+// 1e-9 and less.  They enter the residual of the check in full (Q G - H Q is H times them), which refuses what exceeds it; below the line
+// the image is not split and goes on in the second pass.
 constexpr double kPivotOnePass = 1e-10;
 constexpr double kPivotFloor = 1e-14;  // see chol_kernel
 constexpr double kLn10 = 2.302585092994046;

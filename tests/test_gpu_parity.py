@@ -299,11 +299,10 @@ def test_flat_spectrum_takes_the_full_eigen_solve(C):
 
 @pytest.mark.parametrize("decay,path", [(0.03, 1), (0.00775, 2), (0.001, 0)])
 def test_eigen_solve_ladder_by_spectral_decay(C, decay, path):
-    """Tokens with singular values exp(-decay i): the block iteration (r = 32, block of 128 of 256) contracts the
-    error of the 32nd Ritz pair by lambda_129 / lambda_32 = exp(-194 decay) per step.  Fast decay passes the first
-    residual check (12 steps); exp(-1.5) per step needs the 4 further steps of the second pass (the residual is
-    about 0.2 contraction^steps against a tolerance of 1e-9); slow decay ends in the full solve.  Whatever the
-    path, energies and kept indices match the oracle."""
+    """Tokens with singular values exp(-decay i): the block iteration (r = 32, block of 128 of 256) grows the 32nd eigenvector over
+    what the block leaves out by T_m(2 x - 1) in a block of m products, x = lambda_32 / lambda_129 = exp(194 decay).  Fast decay
+    (x = 340) is there in the first pass; x = 4.5 needs the products of the second; slow decay (x = 1.2) ends in the full solve.
+    Whatever the path, energies and kept indices match the oracle."""
     import torch
     n, d, k, r = 256, 384, 64, 32
     sigma = np.exp(-decay * np.arange(n))
