@@ -225,124 +225,6 @@ __device__ __forceinline__ void rest_on(const PlanArgs& q, int b) {
   out[ST_END * q.B] = (at + m) & 1;
 }
 
-// Factors the 64 x 64 block `a` (LDS, pitch NBP, lower triangle: a = L L^T) and inverts the factor, by all eight waves: inv(L) goes
-// to the tiles of `inv` on and below the diagonal, the diagonal of L to dl.  The pivot of row k is floored at
-// kPivotFloor diag[k], diag the diagonal of S.  Ends with a barrier.
-// By 16 x 16 tiles.  A diagonal tile is eliminated together with a unit matrix by wave 0, lane = column of both (the four rows of 16
-// lanes do the same): step k subtracts a_ik / a_kk times row k from row i, the a_ik coming from lane k of the row in one move,
-// and leaves the inverse of the unit-diagonal factor where the unit matrix was, no exchange through LDS and no column to wait for.
-// (With the a_ik as two scalars from v_readlane and the unit matrix in other lanes a block took 13.4 us, so 11.4.)  The
-// tiles below and the rest of the block follow on the MFMA, a wave per tile, and the inverse tile by tile,
-// inv_ts = -inv_tt sum L_tu inv_us, while wave 0 eliminates the next diagonal tile: the sum comes out of the MFMA in the layout its
-// B operand wants.  
-// Pivot k and its reciprocal: an estimate good to 2^-24, r (1 + e + e^2).  The chain from one pivot to the next is what an elimination
-// takes, so the floor is decided beside it.
-template <int k>
-__device__ __forceinline__ void pivot_of(const double (&x)[16], double floor_, double rfloor, double& piv, double& rp) {
-  const double p = row_lane<k>(x[k]), f = row_lane<k>(floor_), rf = row_lane<k>(rfloor);
-  const double r = __builtin_amdgcn_rcp(p), e = fma(-p, r, 1.0), good = fma(r, fma(e, e, e), r);
-  const bool above = p > f;
-  piv = above ? p : f;
-  rp = above ? good : rf;
-}
-// Step k with its pivot and the reciprocal; the next pivot's is worked out beside the rest of the step.
-template <int k>
-__device__ __forceinline__ void eliminate_step(double (&x)[16], double (&u)[16], double floor_, double rfloor, double piv, double rp, double& mine) {
-  if constexpr (k < 16) {
-    const double row = x[k] * rp, urow = u[k] * rp;
-    double next = 1.0, next_rp = 1.0;
-    if constexpr (k < 15) {
-      const double m = row_lane<k>(x[k + 1]);
-      x[k + 1] = fma(-(m * x[k]), rp, x[k + 1]);
-      u[k + 1] = fma(-m, urow, u[k + 1]);
-      pivot_of<k + 1>(x, floor_, rfloor, next, next_rp);
-    }
-#pragma unroll
-    for (int i = k + 2; i < 16; ++i) {
-      const double m = row_lane<k>(x[i]);
-      x[i] = fma(-m, row, x[i]);
-      u[i] = fma(-m, urow, u[i]);
-    }
-    double rs = __builtin_amdgcn_rsq(piv);
-    rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
-    rs = rs * fma(-0.5 * piv, rs * rs, 1.5);
-    u[k] *= rs;                                  // row k of inv(L_ss)
-    if ((threadIdx.x & 15) == k) mine = piv * rs;
-#pragma unroll
-    for (int i = k + 1; i < 16; ++i) asm volatile("" : "+v"(u[i]));   // or the updates of u pile up behind those of x, and spill
-    eliminate_step<k + 1>(x, u, floor_, rfloor, next, next_rp, mine);
-  }
-}
-
-__device__ __forceinline__ void eliminate_tile(double* a, double* inv, double* dl, const double* diag, int s) {
-  const int lane = threadIdx.x & 63, i16 = lane & 15;
-  double x[16], u[16], mine = 0.0, piv, rp;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int hi = i > i16 ? i : i16, lo = i > i16 ? i16 : i;
-    x[i] = a[(16 * s + hi) * NBP + 16 * s + lo];
-    u[i] = i16 == i ? 1.0 : 0.0;
-  }
-  const double floor_ = fma(kPivotFloor, diag[16 * s + i16], 1e-300);
-  const double rfloor = 1.0 / floor_;
-  pivot_of<0>(x, floor_, rfloor, piv, rp);
-  eliminate_step<0>(x, u, floor_, rfloor, piv, rp, mine);
-  if (lane < 16) {
-    dl[16 * s + lane] = mine;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) inv[(16 * s + k) * NBP + 16 * s + i16] = i16 <= k ? u[k] : 0.0;
-  }
-}
-
-// inv_ts = -inv_tt sum over u of L_tu inv_us, one wave
-__device__ __forceinline__ void invert_tile(const double* a, double* inv, int t, int s) {
-  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
-  f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0}, o = sum;
-#pragma unroll 1
-  for (int u = s; u < t; ++u)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      sum = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * u + 4 * j + kq], inv[(16 * u + 4 * j + kq) * NBP + 16 * s + i16], sum, 0, 0, 0);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(-inv[(16 * t + i16) * NBP + 16 * t + 4 * j + kq], sum[j], o, 0, 0, 0);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) inv[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
-}
-
-__device__ __forceinline__ void factor_invert(double* a, double* inv, double* dl, const double* diag) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
-#pragma unroll 1
-  for (int s = 0; s < 4; ++s) {
-    if (w == 0) eliminate_tile(a, inv, dl, diag, s);
-    else if (w < s) invert_tile(a, inv, s - 1, w - 1);   // row s - 1 of the inverse, tiles 0 .. s - 2
-    __syncthreads();
-    const int t = s + w;
-    if (w > 0 && t < 4) {                          // L_ts = A_ts inv(L_ss)^T
-      f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(16 * t + i16) * NBP + 16 * s + 4 * j + kq], inv[(16 * s + i16) * NBP + 16 * s + 4 * j + kq], o, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) a[(16 * t + 4 * v + kq) * NBP + 16 * s + i16] = o[v];
-    }
-    __syncthreads();
-    const int x = w < 1 ? 0 : w < 3 ? 1 : 2, y = w - x * (x + 1) / 2, r = s + 1 + x, c = s + 1 + y;
-    if (w < 6 && r < 4) {                          // A_rc -= L_rs L_cs^T
-      f64x4_t o;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) o[v] = a[(16 * r + 4 * v + kq) * NBP + 16 * c + i16];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        o = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[(16 * r + i16) * NBP + 16 * s + 4 * j + kq], a[(16 * c + i16) * NBP + 16 * s + 4 * j + kq], o, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) a[(16 * r + 4 * v + kq) * NBP + 16 * c + i16] = o[v];
-    }
-    __syncthreads();
-  }
-  if (w < 3) invert_tile(a, inv, 3, w);
-  __syncthreads();
-}
-
 __device__ __forceinline__ void frag_store_through(double* tile, int lane, const f64x4_t& v) {
   double* t = tile + 2 * lane;
   store_through(t, v[0]);
@@ -351,12 +233,224 @@ __device__ __forceinline__ void frag_store_through(double* tile, int lane, const
   store_through(t + 129, v[3]);
 }
 
+// Factors a 64 x 64 block (a = L L^T) and inverts the factor, by all eight waves.  Wave 0 brings tile (0, 0) in registers, element
+// (k, i) in lane (q = k % 4, i), register k / 4; the other tiles on and below the diagonal are in LDS (`a`, pitch NBP), a barrier before
+// they are read.  inv(L) goes through the L2 to Db (its tiles on and below the diagonal, in fragment order), the diagonal of L to dl (valid
+// in wave 0).  The pivot of row k is floored at floors[k].
+// By 16 x 16 tiles.  A diagonal tile stays in the registers of wave 0 from the product that forms it to its inverse, four pivots at a
+// time: the 4 x 4 block at the pivots is read into scalars and factored and inverted by every lane for itself (eliminate_panel), what it
+// does to the other rows is a product of rank 4, one MFMA on the tile and one on the unit matrix that becomes the inverse.  The operand
+// layouts meet: rows 4t .. 4t + 3 of the tile are its register t, which is the B operand of the product with the inverted 4 x 4 block,
+// whose first result register is an operand of the update, and L_ts^T as the MFMA leaves it is both operands of A_tt - L_ts L_ts^T.
+// The tiles below, the rest of the block and the inverse off its diagonal, inv_ts = -inv_tt sum L_tu inv_us, are the other waves', a wave
+// per tile, while wave 0 is at the next diagonal tile; of the last row of the inverse only the products with inv_33 are left at the end.
+// Bound by the chain of 64 pivots, a reciprocal and some five dependent operations each.  (One pivot at a time, the multipliers moved
+// along the rows of 16 lanes, took 32 moves and 32 multiply-adds a pivot, all four rows the same: 11.4 us a block, bound by issue.)
+
+// Scalar from lane l of v.
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// 1 / p: an estimate good to 2^-24, r (1 + e + e^2).
+__device__ __forceinline__ double reciprocal(double p) {
+  const double r = __builtin_amdgcn_rcp(p), e = fma(-p, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// Pivots 4t .. 4t + 3 of the tile x (lane (q, i): rows 4v + q of column i) with the unit matrix u; floors of the tile's 16 pivots in LDS.
+// piv: lane (q, i) gets the pivot of row 4t + q.
+template <int t>
+__device__ __forceinline__ void eliminate_panel(f64x4_t& x, f64x4_t& u, const double* floors, double& piv) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+  auto at = [&](int i, int j) { return lane_value(x[t], 16 * i + 4 * t + j); };
+  const double a00 = at(0, 0), a10 = at(1, 0), a20 = at(2, 0), a30 = at(3, 0);
+  const double a11 = at(1, 1), a21 = at(2, 1), a31 = at(3, 1), a22 = at(2, 2), a32 = at(3, 2), a33 = at(3, 3);
+  // L D L^T of the 4 x 4 block.  From one pivot to the next the chain is the reciprocal and one multiply-add.
+  const double p0 = fmax(a00, floors[4 * t]), r0 = reciprocal(p0);
+  const double b11 = fma(-(a10 * a10), r0, a11), b21 = fma(-(a20 * a10), r0, a21), b31 = fma(-(a30 * a10), r0, a31);
+  const double b22 = fma(-(a20 * a20), r0, a22), b32 = fma(-(a30 * a20), r0, a32), b33 = fma(-(a30 * a30), r0, a33);
+  const double p1 = fmax(b11, floors[4 * t + 1]), r1 = reciprocal(p1);
+  const double c22 = fma(-(b21 * b21), r1, b22), c32 = fma(-(b31 * b21), r1, b32), c33 = fma(-(b31 * b31), r1, b33);
+  const double p2 = fmax(c22, floors[4 * t + 2]), r2 = reciprocal(p2);
+  const double p3 = fmax(fma(-(c32 * c32), r2, c33), floors[4 * t + 3]), r3 = reciprocal(p3);
+  const double l10 = a10 * r0, l20 = a20 * r0, l30 = a30 * r0, l21 = b21 * r1, l31 = b31 * r1, l32 = c32 * r2;
+  // the inverse of its unit-diagonal factor, as the A operand of a product that leaves its rows in the first register
+  const double n20 = fma(l21, l10, -l20), n31 = fma(l32, l21, -l31), n30 = -fma(l31, -l10, fma(l32, n20, l30));
+  double n = i16 == kq ? 1.0 : 0.0;                                  // (kq < 4)
+  if (i16 == 1 && kq == 0) n = -l10;
+  if (i16 == 2 && kq == 0) n = n20;
+  if (i16 == 2 && kq == 1) n = -l21;
+  if (i16 == 3 && kq == 0) n = n30;
+  if (i16 == 3 && kq == 1) n = n31;
+  if (i16 == 3 && kq == 2) n = -l32;
+  const f64x4_t zero = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  const double w = __builtin_amdgcn_mfma_f64_16x16x4f64(n, x[t], zero, 0, 0, 0)[0];
+  const double r = kq == 0 ? r0 : kq == 1 ? r1 : kq == 2 ? r2 : r3;
+  piv = kq == 0 ? p0 : kq == 1 ? p1 : kq == 2 ? p2 : p3;
+  const double below = (i16 > 4 * t + 3 ? -r : 0.0) * w;             // rows above stay: the unit matrix has results there
+  if (t < 3) x = __builtin_amdgcn_mfma_f64_16x16x4f64(below, w, x, 0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);                                 // the products with the unit matrix are not part of the chain
+  const double uw = __builtin_amdgcn_mfma_f64_16x16x4f64(n, u[t], zero, 0, 0, 0)[0];
+  u[t] = uw;
+  if (t < 3) u = __builtin_amdgcn_mfma_f64_16x16x4f64(below, uw, u, 0, 0, 0);
+}
+
+// Wave 0: x <- the inverse of the factor of the tile (its pivots' floors given), piv <- the pivots
+__device__ __forceinline__ void eliminate_tile(f64x4_t& x, double (&piv)[4], const double* floors) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+  f64x4_t u;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) u[v] = i16 == 4 * v + kq ? 1.0 : 0.0;
+  eliminate_panel<0>(x, u, floors, piv[0]);
+  eliminate_panel<1>(x, u, floors, piv[1]);
+  eliminate_panel<2>(x, u, floors, piv[2]);
+  eliminate_panel<3>(x, u, floors, piv[3]);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    double rs = __builtin_amdgcn_rsq(piv[v]);
+    rs = rs * fma(-0.5 * piv[v], rs * rs, 1.5);
+    rs = rs * fma(-0.5 * piv[v], rs * rs, 1.5);
+    x[v] = i16 <= 4 * v + kq ? u[v] * rs : 0.0;
+    piv[v] *= rs;
+  }
+}
+
+// `a` and `inv` of a lane: [0] is its element of an operand by rows (row i, column q of a tile), [1] of one by columns (row q, column i,
+// which is also what a product leaves).
+struct LaneTiles {
+  double *a[2], *inv[2];
+  __device__ __forceinline__ LaneTiles(double* a_, double* inv_) {
+    const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+    int by_row = i16 * NBP + kq, by_col = kq * NBP + i16;
+    asm volatile("" : "+v"(by_row), "+v"(by_col));       // or a register for each tile's address is kept across the loop, and spills
+    a[0] = a_ + by_row; a[1] = a_ + by_col;
+    inv[0] = inv_ + by_row; inv[1] = inv_ + by_col;
+  }
+};
+__device__ __forceinline__ int tile_off(int t, int s) { return 16 * (t * NBP + s); }
+
+// L_ts^T = inv(L_ss) A_ts^T, one wave: lane (q, i) gets the elements (i, 4v + q) of L_ts
+__device__ __forceinline__ f64x4_t solve_tile(const LaneTiles& p, int t, int s) {
+  f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  const double *d = p.inv[0] + tile_off(s, s), *x = p.a[0] + tile_off(t, s);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(d[4 * j], x[4 * j], o, 0, 0, 0);
+  return o;
+}
+
+// A_rc -= L_rs L_cs^T, one wave
+__device__ __forceinline__ void update_tile(const LaneTiles& p, int r, int c, int s) {
+  const double *x = p.a[0] + tile_off(r, s), *y = p.a[0] + tile_off(c, s);
+  double* z = p.a[1] + tile_off(r, c);
+  f64x4_t o;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o[v] = z[4 * v * NBP];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(-x[4 * j], y[4 * j], o, 0, 0, 0);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) z[4 * v * NBP] = o[v];
+}
+
+// sum over u from s to t - 1 of L_tu inv_us, one wave
+__device__ __forceinline__ f64x4_t invert_sum(const LaneTiles& p, int t, int s) {
+  f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int u = s; u < t; ++u) {
+    const double *x = p.a[0] + tile_off(t, u), *y = p.inv[1] + tile_off(u, s);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum = __builtin_amdgcn_mfma_f64_16x16x4f64(x[4 * j], y[4 * j * NBP], sum, 0, 0, 0);
+  }
+  return sum;
+}
+
+// a tile of the inverse from LDS to memory
+__device__ __forceinline__ void hand_on(const LaneTiles& p, double* Db, int t, int s) {
+  const double* d = p.inv[0] + tile_off(t, s);
+  frag_store_through(Db + (4 * t + s) * kFragTile, threadIdx.x & 63, (f64x4_t){d[0], d[4], d[8], d[12]});
+}
+
+// between: called by all waves with their own stores of before acknowledged, one thread of wave 7 raising a flag for it
+template <typename Between>
+__device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv, double* Db, double* dl, const double* floors, Between between) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
+  const int col = 7 - w;                             // waves 7, 6 and 5 have a column of the inverse each
+  f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    const LaneTiles p(a, inv);
+    if (w == 0) {
+      double root[4];
+      eliminate_tile(x, root, floors + 16 * s);
+      if (i16 == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dl[16 * s + 4 * v + kq] = root[v];
+      }
+    } else if (s > 0) {
+      // what step s - 1 left: the tiles beyond (s, s), and row s - 1 of the inverse
+      const int e = w < 3 ? 1 : 2, f = w - e * (e + 1) / 2;
+      if (w < 6 && s + e < 4) update_tile(p, s + e, s + f, s - 1);
+      if (col < s - 1) {
+        const f64x4_t t = invert_sum(p, s - 1, col);
+        const double* d = p.inv[0] + tile_off(s - 1, s - 1);
+        double* z = p.inv[1] + tile_off(s - 1, col);
+        f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(-d[4 * j], t[j], o, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[4 * v * NBP] = o[v];
+      }
+      if (s == 3) {
+        if (w < 4) hand_on(p, Db, w - 1, w - 1);
+        else if (w == 4) hand_on(p, Db, 1, 0);
+        else {
+          if (col < 2) hand_on(p, Db, 2, col);
+          sum = invert_sum(p, 3, col);
+        }
+      }
+    }
+    if (s == 0) between();                           // `inv` has been read, the tiles of `a` are there
+    if (w == 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) p.inv[1][tile_off(s, s) + 4 * v * NBP] = x[v];
+    }
+    __syncthreads();
+    if (s < 3) {
+      const int t = s + 1 + w;
+      if (t < 4) {
+        const f64x4_t l = solve_tile(p, t, s);
+        if (w == 0) {                              // A_tt - L_ts L_ts^T: l^T is both operands
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {            // from its lower triangle
+            const int k = 4 * v + kq, hi = k > i16 ? k : i16, lo = k > i16 ? i16 : k;
+            x[v] = a[tile_off(t, t) + hi * NBP + lo];
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) x = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[v], l[v], x, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) p.a[0][tile_off(t, s) + 4 * v] = l[v];
+      }
+      __syncthreads();
+    }
+  }
+  const LaneTiles p(a, inv);
+  if (w == 0) {
+    hand_on(p, Db, 3, 3);
+  } else if (w > 4) {                                // -inv_33 sum, transposed: in fragment order
+    const double* d = p.inv[0] + tile_off(3, 3);
+    f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(sum[j], -d[4 * j], o, 0, 0, 0);
+    frag_store_through(Db + (12 + col) * kFragTile, lane, o);
+  }
+}
+
 // Progress of the factorisation of one image: written by the workgroup of a block row, polled by those of the rows after it.
 // Cleared at the start of a pass.
 struct CholFlags {
   unsigned int ticket;          // next block row to hand to a starting workgroup
   int failed;                   // a workgroup gave up waiting
-  int cols[kMaxBlocks];         // per block row: columns of L that are in memory
+  int cols[kMaxBlocks];         // per block row: 1 when its part of L is in memory
   int done[kMaxBlocks];         // its diagonal block is factored, the inverse is in memory
 };
 
@@ -401,16 +495,17 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
 // products they do, by the growth of the first row over the last), at the rounding of S: what is left of a row below that is noise, which
 // the floor keeps shorter than the other rows, and the next factorisation makes a row of length one of it.  (At 1e-28 such a row came out
 // up to 1e7 long, with as much of the other rows in it, and the image ended in the full solve.)
-// Bound by the chain of diagonal blocks: factor, flag, product with the inverse, D.  One workgroup per image, which did the
+// Bound by the chain of diagonal blocks: factor (8.8 us), flag, product with the inverse, D.  One workgroup per image, which did the
 // trailing updates itself beside the factorisation of the next block by one of its waves, took, us: one image of order 192 67,
-// eight of 384 172, sixty-four of 256 98; this 55, 108 and 80 (eleven of the eighteen a row takes are the elimination).
+// eight of 384 172; by block rows with one pivot at a time 53 and 109; four at a time, the flag of a row's columns raised beside its
+// first diagonal tile and the inverse handed on as it comes 41 and 87.
 // Dynamic LDS: 2 * 64 * 65 doubles.
 __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, double* __restrict__ diag, double* __restrict__ pivots, int P,
                                                    PlanArgs q, CholFlags* flags, long long limit_ticks) {
   extern __shared__ double lds[];
-  double* a = lds;                  // [64][65] diagonal block, its factor after factor_invert (tiles below the diagonal)
-  double* inv = lds + NB * NBP;     // [64][65] the inverse of the factor; before: T, then L[i,K]
-  __shared__ double dl[NB], diag0[NB];
+  double* a = lds;                  // [64][65] diagonal block, see factor_invert
+  double* inv = lds + NB * NBP;     // [64][65] the inverse of its factor; before: T, then L[i,K]
+  __shared__ double dl[NB], diag0[NB], floors[NB];
   __shared__ int s_flag;
   const int b = blockIdx.x % q.B;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
@@ -425,9 +520,14 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
   double* Sb = S + (long)b * P * P;
   double* Db = Dinv + (long)b * nblk * NB * NB;
   auto tile = [&](int rt, int ct) -> double* { return Sb + ((long)rt * per16 + ct) * kFragTile; };
-  if (tid < NB) diag0[tid] = tile(4 * row + (tid >> 4), 4 * row + (tid >> 4))[frag_at(tid & 15, tid & 15)];
-  // t-th tile of a block on or below its diagonal; wave w has the tiles w and, w < 2, w + 8
+  if (tid < NB) {
+    diag0[tid] = tile(4 * row + (tid >> 4), 4 * row + (tid >> 4))[frag_at(tid & 15, tid & 15)];
+    floors[tid] = fma(kPivotFloor, diag0[tid], 1e-300);
+  }
+  // t-th tile of a block on or below its diagonal; wave w has the tiles w and, w = 2, 3, w + 6 (wave 0, and wave 4 beside it on its
+  // SIMD, one each: the factorisation begins with tile 0)
   auto low = [](int t, int& x, int& y) { x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3; y = t - x * (x + 1) / 2; };
+  auto own = [&](int e) { return e == 0 ? w : w == 2 || w == 3 ? w + 6 : 10; };
   f64x4_t dacc[2];
 #pragma unroll
   for (int e = 0; e < 2; ++e) dacc[e] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
@@ -439,7 +539,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
 #pragma unroll
     for (int y = 0; y < 2; ++y) t[y] = frag_load(tile(4 * row + rx, 4 * K + c0 + y), lane);
     if (K > 0) {
-      if (!(alive = wait_flag(&f->cols[K], K, f, &s_flag, limit_ticks))) break;
+      if (!(alive = wait_flag(&f->cols[K], 1, f, &s_flag, limit_ticks))) break;
       f64x4_t acc[2];
 #pragma unroll
       for (int y = 0; y < 2; ++y) acc[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
@@ -505,7 +605,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const int tt = w + 8 * e;
+      const int tt = own(e);
       if (tt < 10) {
         int x, y;
         low(tt, x, y);
@@ -516,34 +616,31 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
             dacc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[(16 * y + i16) * NBP + 16 * c + 4 * v + kq], inv[(16 * x + i16) * NBP + 16 * c + 4 * v + kq], dacc[e], 0, 0, 0);
       }
     }
-    raise_flag(&f->cols[row], K + 1);                           // and L[i,K] in LDS has been read
+    // the next round writes to LDS behind its first wait
   }
   if (alive) {
+    double* Di = Db + (long)row * NB * NB;
+    f64x4_t x0 = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const int tt = w + 8 * e;
+      const int tt = own(e);
       if (tt < 10) {
         int x, y;
         low(tt, x, y);
         const f64x4_t c = frag_load(tile(4 * row + x, 4 * row + y), lane);
+        if (tt == 0) {
+          x0 = c - dacc[e];
+        } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v] - dacc[e][v];
+          for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v] - dacc[e][v];
+        }
       }
     }
-    __syncthreads();
-    factor_invert(a, inv, dl, diag0);
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int tt = w + 8 * e;
-      if (tt < 10) {
-        int x, y;
-        low(tt, x, y);
-        f64x4_t c;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) c[v] = inv[(16 * x + i16) * NBP + 16 * y + 4 * v + kq];
-        frag_store_through(Db + (long)row * NB * NB + (4 * x + y) * kFragTile, lane, c);
-      }
-    }
+    factor_invert(x0, a, inv, Di, dl, floors, [&]() {
+      __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0): L[row, .] has been stored
+      __syncthreads();
+      if (tid == 7 * kWave) __hip_atomic_store(&f->cols[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
     if (w == 0) {
       const double d = dl[lane], s0 = diag0[lane];
       store_through(diag + (long)b * P + row * NB + lane, d);
