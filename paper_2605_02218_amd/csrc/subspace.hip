@@ -42,7 +42,7 @@ constexpr double kRitzTol = 1e-9;
 // 1e-9 and less.  They enter the residual of the check in full (Q G - H Q is H times them), which refuses what exceeds it; below the line
 // the image is not split and goes on in the second pass.
 constexpr double kPivotOnePass = 1e-10;
-constexpr double kPivotFloor = 1e-14;  // see chol_kernel
+constexpr double kPivotFloor = 1e-14;  // see chol_row
 constexpr double kLn10 = 2.302585092994046;
 constexpr float kSteep = 9.0f;         // ln(lambda_1 / lambda_P) from which growth and not launches limit a block of three products
 
@@ -119,7 +119,7 @@ __device__ __forceinline__ float over_beta(float t) { return t > 10.0f ? t - 1.3
 __device__ __forceinline__ void plan_block(const PlanArgs& q, int b, double d1, double dr, double dP, double pmin) {
   IterPlan& p = q.plan[b];
   int* out = q.out + b;
-  const int at = q.in[ST_END * q.B + b];          // the trsm works in place
+  const int at = q.in[ST_END * q.B + b];          // the substitution works in place
   int m = 0, rest = 0;
   const bool sane = dP > 0.0 && d1 < 1e300 && dr > 0.0 && dr < 1e300 && pmin > 0.0;
   if (q.first) {
@@ -482,8 +482,8 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
   if (threadIdx.x == 0) __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Cholesky factorisation S[b] = L L^T (P x P, P % 64 == 0, [P/16][P/16] tiles in fragment order, those on and below the
-// diagonal), one 512-thread workgroup per block row of 64 and image.  The workgroup of block row i:
+// Block row `row` of the Cholesky factorisation S[b] = L L^T (P x P, P % 64 == 0, [P/16][P/16] tiles in fragment order, those on and below
+// the diagonal), one 512-thread workgroup per block row of 64 and image.  The workgroup of block row i:
 //   for K < i:  T = S[i,K] - sum over K' < K of L[i,K'] L[K,K']^T;   L[i,K] = T inv(L_KK)^T, in place;   D += L[i,K] L[i,K]^T
 //   factors and inverts S[i,i] - D (factor_invert); the inverse goes to Dinv[b][i] (its tiles).
 // It waits for row K's columns before the sum and for row K's inverse before the product with it, so that the sum runs while
@@ -499,24 +499,14 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
 // trailing updates itself beside the factorisation of the next block by one of its waves, took, us: one image of order 192 67,
 // eight of 384 172; by block rows with one pivot at a time 53 and 109; four at a time, the flag of a row's columns raised beside its
 // first diagonal tile and the inverse handed on as it comes 41 and 87.
-// Dynamic LDS: 2 * 64 * 65 doubles.
-__global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict__ Dinv, double* __restrict__ diag, double* __restrict__ pivots, int P,
-                                                   PlanArgs q, CholFlags* flags, long long limit_ticks) {
-  extern __shared__ double lds[];
+// lds: 2 * 64 * 65 doubles.
+__device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, double* __restrict__ Dinv, double* __restrict__ diag, double* __restrict__ pivots,
+                                         int P, int b, int row, const PlanArgs& q, CholFlags* f, long long limit_ticks) {
   double* a = lds;                  // [64][65] diagonal block, see factor_invert
   double* inv = lds + NB * NBP;     // [64][65] the inverse of its factor; before: T, then L[i,K]
   __shared__ double dl[NB], diag0[NB], floors[NB];
-  __shared__ int s_flag;
-  const int b = blockIdx.x % q.B;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
-  if (q.in[ST_REST * q.B + b] > (q.slots == 0 ? 1 : 0)) {      // no part in this orthonormalisation
-    if (tid == 0 && blockIdx.x < (unsigned)q.B) rest_on(q, b);
-    return;
-  }
-  CholFlags* f = flags + b;
-  if (tid == 0) s_flag = (int)atomicAdd(&f->ticket, 1u);
-  __syncthreads();
-  const int row = s_flag, nblk = P / NB, per16 = P / 16;
+  const int nblk = P / NB, per16 = P / 16;
   double* Sb = S + (long)b * P * P;
   double* Db = Dinv + (long)b * nblk * NB * NB;
   auto tile = [&](int rt, int ct) -> double* { return Sb + ((long)rt * per16 + ct) * kFragTile; };
@@ -539,7 +529,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
 #pragma unroll
     for (int y = 0; y < 2; ++y) t[y] = frag_load(tile(4 * row + rx, 4 * K + c0 + y), lane);
     if (K > 0) {
-      if (!(alive = wait_flag(&f->cols[K], 1, f, &s_flag, limit_ticks))) break;
+      if (!(alive = wait_flag(&f->cols[K], 1, f, s_flag, limit_ticks))) break;
       f64x4_t acc[2];
 #pragma unroll
       for (int y = 0; y < 2; ++y) acc[y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
@@ -566,7 +556,7 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
     for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) inv[(16 * rx + i16) * NBP + 16 * (c0 + y) + 4 * v + kq] = t[y][v];
-    if (!(alive = wait_flag(&f->done[K], 1, f, &s_flag, limit_ticks))) break;
+    if (!(alive = wait_flag(&f->done[K], 1, f, s_flag, limit_ticks))) break;
     // L[i,K]: this wave's column tiles are 0 and 3, or 1 and 2 (five products each)
     f64x4_t in[4], out[2];
 #pragma unroll
@@ -669,145 +659,113 @@ __global__ __launch_bounds__(512) void chol_kernel(double* S, double* __restrict
   }
 }
 
-// Y <- L^-1 Y (P x nP, pitch nP; Y is the image's block in Yt or `other` doubles behind it) by blocked forward substitution with the factor chol_kernel left
-// in S (strictly-lower blocks) and Dinv (inverted diagonal blocks), both tiles in fragment order.  Columns are independent: each wave
-// owns 16 of them and never reads what another wave writes, so the whole solve is one launch.
-//   for block row bi:  T = Yt[bi] - sum_{K<bi} L[bi,K] Yt[K];   Yt[bi] = inv(L_bibi) T
-// What the MFMA returns (lane = column, register = k) is exactly the layout its B operand wants, so the solved blocks are
-// kept in registers and are the B operands of the following rows as they are; the A operands are a stream that is known in
-// advance, four groups of 16 k of it in flight.  Nothing waits for memory but the first group: the chain is MFMAs.
-// Written back to memory and read again block by block, with the loads of a block in front of its MFMAs, the solve took,
-// us: 192 x 320 29, 192 x 1280 batch 4 33, 384 x 1152 batch 8 91, 256 x 640 batch 64 145; in registers 26, 30, 83, 127; with
-// the factor in fragment order (row-major, a load touched 64 cache lines) 15, 19, 45, 76.
-// Instantiated for up to six blocks (rank 320); larger factors go through trsm_any_kernel.  us, trsm_any_kernel / here: 192 x 320
-// batch 8 37 / 17, 256 x 640 54 / 23, 384 x 1152 99 / 45; seven blocks measured 124 / 57 and eight 151 / 72 (448 x 704, 512 x 832).
-template <int N>
-struct TrsmAt {          // group N of the A stream: block row bi takes 4 bi groups of L and 4 of its inverted diagonal block
-  static constexpr int row() { int bi = 0; while (2 * (bi + 1) * (bi + 2) <= N) ++bi; return bi; }
-  static constexpr int bi = row(), at = N - 2 * bi * (bi + 1), K = at >> 2, q = at & 3;
-};
-
-struct TrsmPtr { const double *L, *D; double* Y; long nP; };      // lane offsets included
-
-template <int NBLK, int N>
-__device__ __forceinline__ void trsm_fetch(const TrsmPtr& p, f64x4_t (&f)[4]) {
-  if constexpr (N < 2 * NBLK * (NBLK + 1)) {
-    typedef TrsmAt<N> A;
-#pragma unroll
-    for (int x = A::K < A::bi ? 0 : A::q; x < 4; ++x)     // the inverted block is lower triangular
-      f[x] = A::K < A::bi ? frag_load(p.L + ((long)(4 * A::bi + x) * (4 * NBLK) + 4 * A::K + A::q) * kFragTile, 0)
-                          : frag_load(p.D + (16 * A::bi + 4 * x + A::q) * kFragTile, 0);
-  }
-}
-
-template <int NBLK, int N>
-__device__ __forceinline__ void trsm_steps(const TrsmPtr& p, f64x4_t (&y)[NBLK][4], f64x4_t (&f)[4][4], f64x4_t (&acc)[4], f64x4_t (&rhs)[4]) {
-  if constexpr (N < 2 * NBLK * (NBLK + 1)) {
-    typedef TrsmAt<N> A;
-    if constexpr (A::at == 0) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        acc[x] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int v = 0; v < 4; ++v) rhs[x][v] = p.Y[(long)(A::bi * NB + 16 * x + 4 * v) * p.nP];
-      }
-    }
-    if constexpr (A::K == A::bi && A::q == 0) {         // T is complete; the inverted block takes it as its B operand
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        rhs[x] = rhs[x] - acc[x];
-        acc[x] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const double bv = A::K < A::bi ? y[A::K][A::q][v] : rhs[A::q][v];
-#pragma unroll
-      for (int x = A::K < A::bi ? 0 : A::q; x < 4; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[N & 3][x][v], bv, acc[x], 0, 0, 0);
-    }
-    trsm_fetch<NBLK, N + 4>(p, f[N & 3]);
-    __builtin_amdgcn_sched_barrier(0);                  // the loads stay four groups ahead of their use
-    if constexpr (A::K == A::bi && A::q == 3) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        y[A::bi][x] = acc[x];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) p.Y[(long)(A::bi * NB + 16 * x + 4 * v) * p.nP] = acc[x][v];
-      }
-    }
-    trsm_steps<NBLK, N + 1>(p, y, f, acc, rhs);
-  }
-}
-
-template <int NBLK>
-__global__ __launch_bounds__(256, 1) void trsm_kernel(double* Yt, long other, const double* __restrict__ S, const double* __restrict__ Dinv, int nP,
-                                                      int wg_per_image, const int* __restrict__ state, int nimg, int rest_max) {
-  const int b = blockIdx.x / wg_per_image, cw = blockIdx.x - b * wg_per_image;
-  if (state[ST_REST * nimg + b] > rest_max) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
-  constexpr int P = NBLK * NB;
-  TrsmPtr p;
-  p.L = S + (long)b * P * P + 2 * lane;
-  p.D = Dinv + (long)b * NBLK * NB * NB + 2 * lane;
-  p.Y = Yt + (state[ST_END * nimg + b] ? other : 0) + (long)b * P * nP + (long)kq * nP + cw * 64 + w * 16 + i16;     // nP % 64 == 0, so every column exists
-  p.nP = nP;
-  f64x4_t y[NBLK][4], f[4][4], acc[4], rhs[4];
-  trsm_fetch<NBLK, 0>(p, f[0]);
-  trsm_fetch<NBLK, 1>(p, f[1]);
-  trsm_fetch<NBLK, 2>(p, f[2]);
-  trsm_fetch<NBLK, 3>(p, f[3]);
-  trsm_steps<NBLK, 0>(p, y, f, acc, rhs);
-}
-
-// The same for any number of blocks: the solved blocks go through memory.
-__global__ __launch_bounds__(256) void trsm_any_kernel(double* Yt, long other, const double* __restrict__ S, const double* __restrict__ Dinv,
-                                                        int P, int nP, int wg_per_image, const int* __restrict__ state, int nimg, int rest_max) {
-  const int b = blockIdx.x / wg_per_image, cw = blockIdx.x - b * wg_per_image;
-  if (state[ST_REST * nimg + b] > rest_max) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
-  const int col = cw * 64 + w * 16 + i16;    // nP % 64 == 0, so every column exists
+// 16 columns of Y <- L^-1 Y (P x nP, pitch nP, in place), one wave, by blocked forward substitution with the factor chol_row leaves in S
+// (strictly-lower blocks) and Dinv (inverted diagonal blocks), both tiles in fragment order.  Columns are independent: no wave reads what
+// another wrote.  L, D, Y: of the image, lane offsets included.  All waves of the workgroup call it (mine: this one has columns).
+//   for block row bi:  T = Y[bi] - sum_{K<bi} L[bi,K] Y[K];   Y[bi] = inv(L_bibi) T
+// The workgroups of an image's columns are in the launch of its factorisation and follow it block row by block row: the sum as soon as row
+// bi of L is there, the product with the inverted block when that is, so that behind the last flag only that product is left.
+// What the MFMA returns (lane = column, register = k) is exactly the layout its B operand wants; solved blocks are read back by the lane
+// that wrote them, two groups of 16 k ahead, as are those of L.
+// As a launch behind the factorisation, the solved blocks in registers, it took, us: 192 x 320 14.5, 192 x 1664 batch 4 19, 384 x 1152
+// batch 8 44, 256 x 640 batch 64 73; the factorisation by itself 40, 43, 87 and 71, both in one launch 45, 49, 95 and 126.
+__device__ __forceinline__ bool substitute(const double* L, const double* D, double* Y, long nP, int P, bool mine, CholFlags* f, int* s_flag, long long limit_ticks) {
   const int nblk = P / NB;
-  double* Yb = Yt + (state[ST_END * nimg + b] ? other : 0) + (long)b * P * nP;
-  const double* Lb = S + (long)b * P * P;
+  const long row_tiles = (long)(P / 16) * kFragTile;
+#pragma unroll 1
   for (int bi = 0; bi < nblk; ++bi) {
-    f64x4_t acc[4];
-#pragma unroll
-    for (int x = 0; x < 4; ++x) acc[x] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-    for (int kk = 0; kk < bi * NB; kk += 16) {
-      f64x4_t fa[4];
-      double fb[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) fa[x] = frag_load(Lb + ((long)(4 * bi + x) * (P / 16) + kk / 16) * kFragTile, lane);
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) fb[jj] = Yb[(long)(kk + 4 * jj + kq) * nP + col];
+    f64x4_t acc[4], rhs[4];
+    double* Yb = Y + (long)bi * NB * nP;
+    const f64x4_t zero = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    if (mine) {
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[x][jj], fb[jj], acc[x], 0, 0, 0);
+        for (int v = 0; v < 4; ++v) rhs[x][v] = Yb[(long)(16 * x + 4 * v) * nP];
     }
+    if (bi > 0 && !wait_flag(&f->cols[bi], 1, f, s_flag, limit_ticks)) return false;
+    if (bi > 0 && mine) {
+      constexpr int kAhead = 2;
+      const double* Lb = L + 4 * bi * row_tiles;
+      f64x4_t fa[kAhead][4], fb[kAhead];
+      auto fetch = [&](int g, int slot) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+        for (int x = 0; x < 4; ++x) fa[slot][x] = frag_load(Lb + x * row_tiles + g * kFragTile, 0);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) acc[x][v] = Yb[(long)(bi * NB + 16 * x + 4 * v + kq) * nP + col] - acc[x][v];
-    const double* Db = Dinv + ((long)b * nblk + bi) * NB * NB;
-    f64x4_t out[4];
+        for (int v = 0; v < 4; ++v) fb[slot][v] = Y[(long)(16 * g + 4 * v) * nP];
+      };
 #pragma unroll
-    for (int a = 0; a < 4; ++a) out[a] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-    // step (x, v) contracts k = 16x + 4v + kq, the row acc[x][v] holds in this lane; the inverse is lower triangular
+      for (int x = 0; x < 4; ++x) acc[x] = zero;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+      for (int g = 0; g < kAhead; ++g) fetch(g, g);
+#pragma unroll 1
+      for (int g = 0; g < 4 * bi; g += kAhead) {
 #pragma unroll
-      for (int a = x; a < 4; ++a) {
-        const f64x4_t da = frag_load(Db + (4 * a + x) * kFragTile, lane);
+        for (int h = 0; h < kAhead; ++h) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) out[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[v], acc[x][v], out[a], 0, 0, 0);
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[h][x][v], fb[h][v], acc[x], 0, 0, 0);
+          if (g + kAhead < 4 * bi) fetch(g + kAhead + h, h);
+          __builtin_amdgcn_sched_barrier(0);            // the loads stay that far ahead of their use
+        }
       }
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+      for (int x = 0; x < 4; ++x) rhs[x] = rhs[x] - acc[x];
+    }
+    if (!wait_flag(&f->done[bi], 1, f, s_flag, limit_ticks)) return false;
+    if (mine) {
+      const double* Db = D + (long)bi * NB * NB;
+      f64x4_t fd[4][4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) Yb[(long)(bi * NB + 16 * a + 4 * v + kq) * nP + col] = out[a][v];
-    __threadfence_block();   // the rows just written are B operands of the next block rows
+      for (int q = 0; q < 4; ++q)                       // the inverted block is lower triangular
+#pragma unroll
+        for (int x = q; x < 4; ++x) fd[q][x] = frag_load(Db + (4 * x + q) * kFragTile, 0);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[x] = zero;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int x = q; x < 4; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(fd[q][x][v], rhs[q][v], acc[x], 0, 0, 0);
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Yb[(long)(16 * x + 4 * v) * nP] = acc[x][v];
+    }
   }
+  return true;
+}
+
+// The factorisation of all images and the substitution behind it.  Per image the first P / 64 workgroups to start have a block row
+// each, the others 16 columns per wave of their first `waves` (four: a SIMD each, while there are compute units for that).  A workgroup
+// only waits for some that have started before it, in whatever order the device starts them.  Dynamic LDS: 2 * 64 * 65 doubles.
+__global__ __launch_bounds__(512) void orth_kernel(double* S, double* __restrict__ Dinv, double* __restrict__ diag, double* __restrict__ pivots, int P,
+                                                   PlanArgs q, CholFlags* flags, long long limit_ticks, double* Yt, long other, int nP, int waves) {
+  extern __shared__ double lds[];
+  __shared__ int s_flag;
+  const int b = blockIdx.x % q.B, tid = threadIdx.x;
+  if (q.in[ST_REST * q.B + b] > (q.slots == 0 ? 1 : 0)) {      // no part in this orthonormalisation
+    if (tid == 0 && blockIdx.x < (unsigned)q.B) rest_on(q, b);
+    return;
+  }
+  CholFlags* f = flags + b;
+  if (tid == 0) s_flag = (int)atomicAdd(&f->ticket, 1u);
+  __syncthreads();
+  const int ticket = __builtin_amdgcn_readfirstlane(s_flag);
+  __syncthreads();                                   // s_flag is reused by the waits
+  const int nblk = P / NB;
+  if (ticket < nblk) {
+    chol_row(lds, &s_flag, S, Dinv, diag, pivots, P, b, ticket, q, f, limit_ticks);
+    return;
+  }
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), col = ((ticket - nblk) * waves + w) * 16;
+  const bool mine = w < waves && col < nP;           // nP % 64 == 0
+  double* Y = Yt + (q.in[ST_END * q.B + b] ? other : 0) + (long)b * P * nP + (long)(lane >> 4) * nP + (mine ? col : 0) + (lane & 15);
+  // gave up: the image's rows are not orthonormal, which the check of the residual refuses
+  if (!substitute(S + (long)b * P * P + 2 * lane, Dinv + (long)b * nblk * NB * NB + 2 * lane, Y, nP, P, mine, f, &s_flag, limit_ticks) && tid == 0)
+    __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // State 0 of a pass.  First: every block is in buffer 0.  Second: images that passed the check rest; one that was left out of the
@@ -875,7 +833,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   if (P <= 0 || P % NB != 0 || P > n || P > 4096 || nP % NB != 0) return hipErrorInvalidValue;
   {
     static PerDeviceInt raised;
-    if ((e0 = ensure_dynamic_lds(raised, (const void*)chol_kernel, kCholLds)) != hipSuccess) return e0;
+    if ((e0 = ensure_dynamic_lds(raised, (const void*)orth_kernel, kCholLds)) != hipSuccess) return e0;
   }
   char* ws = (char*)ws_;
   const size_t blk = (size_t)B * P * nP * 8;
@@ -925,22 +883,10 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     PlanArgs q;
     q.in = state(k); q.out = state(k + 1); q.plan = plan; q.left = left; q.B = B; q.r = r; q.slots = slots; q.first = first; q.pass = pass; q.closing = closing;
     const int orth = k < kStates1 ? k : k - kStates1;               // of its pass
-    hipLaunchKernelGGL(chol_kernel, dim3((unsigned)(B * (P / NB))), dim3(512), kCholLds, st, S, D, diag, pivots, P, q, flags + (size_t)orth * B,
-                       barrier_limit_ticks());
-    const dim3 tg((unsigned)(B * (nP / NB)));
-    const double *cS = S, *cD = D;
-    const int* in = state(k);
-    switch (P / NB) {
-#define COVSPEC_TRSM(n) \
-  case n: hipLaunchKernelGGL(trsm_kernel<n>, tg, dim3(256), 0, st, Yt, other, cS, cD, nP, nP / NB, in, B, rest_max); break;
-      COVSPEC_TRSM(2)
-      COVSPEC_TRSM(3)
-      COVSPEC_TRSM(4)
-      COVSPEC_TRSM(5)
-      COVSPEC_TRSM(6)
-#undef COVSPEC_TRSM
-      default: hipLaunchKernelGGL(trsm_any_kernel, tg, dim3(256), 0, st, Yt, other, cS, cD, P, nP, nP / NB, in, B, rest_max);
-    }
+    const int nblk = P / NB, n64 = nP / NB;
+    const int waves = B * (nblk + n64) <= 256 ? 4 : 8, parts = waves == 4 ? n64 : (n64 + 1) / 2;
+    hipLaunchKernelGGL(orth_kernel, dim3((unsigned)(B * (nblk + parts))), dim3(512), kCholLds, st, S, D, diag, pivots, P, q, flags + (size_t)orth * B,
+                       barrier_limit_ticks(), Yt, other, nP, waves);
     return hipGetLastError();
   };
   // products of the block behind state k
