@@ -207,7 +207,7 @@ int run_score(const Plan& q, const void* X, const void* hidden, const void* Q, c
   // e(q) = q Wq; on the bf16 path its rows are finished (lengths, bf16 planes) in one launch
   const bool fold = q.rel == COVSPEC_REL_COSINE_MAX && Wk;
   if (Wq) {
-    HIPCHK(launch_transpose(Wq, at<void>(ws, q.wqT), q.d, q.d, q.dtype, st));
+    HIPCHK(launch_transpose(Wq, at<void>(ws, q.wqT), Wk, at<void>(ws, q.wkT), q.d, q.d, q.dtype, st));
     GemmArgs g;
     g.A = Q; g.B = at<void>(ws, q.wqT); g.C = Eq; g.M = (int)BT; g.N = q.d; g.K = q.d; g.lda = d; g.ldb = d; g.ldc = d;
     g.epilogue = f64 ? EPI_STORE_F64 : EPI_STORE_F32;
@@ -216,7 +216,7 @@ int run_score(const Plan& q, const void* X, const void* hidden, const void* Q, c
     HIPCHK(launch_convert(Q, in_x, Eq, f64, BT * d, st));
   }
   if (!f64) HIPCHK(launch_query_rows((const float*)Eq, BT, q.d, fold ? at<unsigned short>(ws, q.Eq3) : nullptr, (float*)qn2, st));
-  if (Wk) HIPCHK(launch_transpose(Wk, at<void>(ws, q.wkT), q.d, q.d, q.dtype, st));
+  if (Wk && !Wq) HIPCHK(launch_transpose(Wk, at<void>(ws, q.wkT), nullptr, nullptr, q.d, q.d, q.dtype, st));
 
   if (q.rel == COVSPEC_REL_COSINE_MAX) {
     if (f64) HIPCHK(launch_row_norm2(Eq, IN_F64, qn2, f64, BT, q.d, st));
@@ -315,8 +315,8 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
   const long N = q.N, d = q.d;
   marks.mark(COVSPEC_STAGE_PRESELECT);
   int* img_status = at<int>(ws, q.status);
-  HIPCHK(launch_fill_int(img_status, q.B, 0, st));
   if (q.lr == COVSPEC_LR_SCORE_TOPK || q.lr == COVSPEC_LR_RANDOM) {
+    HIPCHK(launch_fill_int(img_status, q.B, 0, st));
     // selector ablations (Table II; Sec. III-A.3, first sentence): one ranking, no low-rank stage
     const float* rank_by = s_fused;
     if (q.lr == COVSPEC_LR_RANDOM) {
@@ -334,13 +334,15 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
     marks.mark(COVSPEC_PROBE_END);
     return COVSPEC_OK;
   }
+  double* A = at<double>(ws, q.Awork);
+  const bool greedy = q.lr == COVSPEC_LR_GREEDY_RESIDUAL;
+  HIPCHK(launch_lowrank_prepare(img_status, at<void>(ws, greedy ? q.gscr : q.ctl), (greedy ? greedy_ctl_bytes(q.B) : jacobi_ctl_bytes(q.B)) / sizeof(int), A, q.B, q.M,
+                                q.nP, q.P, at<void>(ws, q.sub), st));
   int32_t* idxm = idx_m_out ? idx_m_out : at<int32_t>(ws, q.idxm);
   HIPCHK(launch_select_top(s_fused, q.B, q.N, q.M, nullptr, idxm, st));
 
   // token Gram matrix of the pre-selected rows, fp64, zero-padded to the pitch
   marks.mark(COVSPEC_STAGE_GRAM);
-  double* A = at<double>(ws, q.Awork);
-  HIPCHK(launch_zero_padding(A, q.B, q.M, q.nP, st));
   GemmArgs g;
   g.A = X; g.B = X; g.C = A; g.M = q.M; g.N = q.M; g.K = q.d; g.lda = d; g.ldb = d; g.ldc = q.nP;
   g.batch = q.B; g.strideA = N * d; g.strideB = N * d; g.strideC = (long)q.nP * q.nP;
@@ -374,9 +376,8 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
                                    marks.ev ? marks.ev[COVSPEC_PROBE_BEGIN] : nullptr, marks.ev ? marks.ev[COVSPEC_PROBE_END] : nullptr, st));
       probed = q.P > 0;
     }
-    HIPCHK(launch_jacobi_eigen(A, q.B, q.M, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, img_status, st));
+    HIPCHK(launch_jacobi_eigen(A, nullptr, q.B, q.M, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, c, img_status, st));
     marks.mark(COVSPEC_STAGE_KEEP);
-    HIPCHK(launch_subspace_energy(A, q.B, q.M, q.M, q.nP, (long)q.nP * q.nP, q.r, at<double>(ws, q.lam), c, ok, 0, img_status, st));
     HIPCHK(launch_select_top(c, q.B, q.M, q.k, idxm, idx_out, st));
   } else {
     int32_t* order = at<int32_t>(ws, q.order);
@@ -807,7 +808,8 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
   HIPCHK(launch_stream_ids(id_in, idxf, idc, q.B, n_keep, q.M, q.k, id_base, st));
 
   // 2. Gram matrix of the candidates: the kept block is carried, the rows of the arriving tokens are computed
-  HIPCHK(launch_zero_padding(Gc, q.B, nC, q.nP, st));
+  const int P = nC > q.k ? subspace_block(nC, q.r) : 0;
+  HIPCHK(launch_lowrank_prepare(nullptr, at<void>(ws, q.ctl), jacobi_ctl_bytes(q.B) / sizeof(int), Gc, q.B, nC, q.nP, P, at<void>(ws, q.sub), st));
   HIPCHK(launch_copy_block(Gc, q.nP, gstride, G_in, q.k, (long)q.k * q.k, n_keep, q.B, st));
   GemmArgs g;
   g.A = X_frame; g.lda = d; g.strideA = (long)q.N * d; g.gatherA = idxf; g.gstrideA = q.M;
@@ -834,15 +836,12 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
   if (nC > q.k) {
     double* A = at<double>(ws, q.A);
     float* c = c_out ? c_out : at<float>(ws, q.c);
-    const int P = subspace_block(nC, q.r);
     int* ok = nullptr;
     if (P > 0 || split_direct(q.nP)) {
       ok = at<int>(ws, q.ok);
       HIPCHK(launch_subspace_eigen(Gc, q.B, nC, q.nP, q.r, P, at<void>(ws, q.sub), ok, c, nullptr, nullptr, st));
     }
-    HIPCHK(launch_copy_images(A, Gc, q.B, gstride, ok, st));      // the full solve overwrites its input
-    HIPCHK(launch_jacobi_eigen(A, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, nullptr, st));
-    HIPCHK(launch_subspace_energy(A, q.B, nC, nC, q.nP, gstride, q.r, at<double>(ws, q.lam), c, ok, 0, nullptr, st));
+    HIPCHK(launch_jacobi_eigen(A, Gc, q.B, nC, q.nP, q.r, at<void>(ws, q.ctl), at<double>(ws, q.lam), ok, c, nullptr, st));   // the matrix is needed below
     int32_t* selw = at<int32_t>(ws, q.sel);
     HIPCHK(launch_select_top(c, q.B, nC, q.k, nullptr, selw, st));
     sel = selw;

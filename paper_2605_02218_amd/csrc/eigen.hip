@@ -41,9 +41,9 @@ struct JacobiCtl {
   ImageBarrier bar;           // barrier of the image's workgroups; bar.failed: a wait ran into its time limit,
                               // the result is invalid (the rows are set to NaN)
   unsigned int ticket;        // ctl[0] only: next (image, slot) to hand to a starting workgroup
+  unsigned int finished;      // workgroups of the image that are through, whatever came of it
   int done;
   int sweeps;
-  double floor2;              // rows with squared norm below this are treated as zero
   double long2;               // squared length of the r-th longest row after the previous sweep
 };
 
@@ -57,30 +57,6 @@ struct JacobiCtl {
 // leaves 1e-10, below what the energies, returned in fp32 (6e-8), can show.
 constexpr double kRotEps = 1e-15;   // rotations below this relative size are skipped
 constexpr double kConvTol = 5e-6;
-
-__global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restrict__ A, int n, int nP, JacobiCtl* ctl,
-                                                             const int* __restrict__ preset_done) {
-  __shared__ double red[4];
-  const int b = blockIdx.x;
-  const double* Ab = A + (long)b * nP * nP;
-  double tr = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) tr += Ab[(long)i * nP + i];
-  tr = wave_sum(tr);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = tr;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = red[0] + red[1] + red[2] + red[3];
-    for (int k = 0; k < kMaxSweeps + 2; ++k) ctl[b].maxoff[k] = 0ull;
-    ctl[b].bar.arrived = 0u;
-    ctl[b].bar.failed = 0;
-    ctl[b].ticket = 0u;
-    ctl[b].done = preset_done ? preset_done[b] : 0;
-    ctl[b].sweeps = 0;
-    double f = 1e-13 * t;
-    ctl[b].floor2 = f * f;
-    ctl[b].long2 = 0.0;       // first sweep: every row counts
-  }
-}
 
 // circle-method tournament over `np` (even) players: pair `m` of round `rd`
 __device__ __forceinline__ void tournament_pair(int np, int rd, int m, int& p, int& q) {
@@ -336,25 +312,92 @@ __device__ __noinline__ double jacobi_visit(double* Ab, double* len2b, int nP, i
   return wave_max(meas2);
 }
 
-// The whole solve of all images: workgroup (image b, slot pr) visits the pair `pr` of every tournament round
-// of every sweep; after a sweep, slot 0 decides convergence and re-measures which rows are the r longest.
-// A and len2 are written and re-read by different workgroups between barriers, hence no __restrict__.
-__global__ __launch_bounds__(JT) void jacobi_solve_kernel(double* A, int n, int nP, int nsb, int r, JacobiCtl* ctl, double* len2,
-                                                              int* img_status, long long limit_ticks) {
+// c[i] = sum over the r longest rows k of A (n x nP, lengths `lam`) of A[k][i]^2 / |row k|, rows added in ascending k, by one workgroup.
+// failed: the rows are no result, and NaN the energies.
+__device__ __noinline__ void energies_of(const double* A, const double* lam, int n, int nP, int r, bool failed, float* c) {
+  const int tid = threadIdx.x;
+  if (failed) {
+    for (int i = tid; i < n; i += JT) c[i] = __uint_as_float(0x7fc00000u);
+    return;
+  }
+  double* slam = Hs;                                       // n <= 4096
+  unsigned char* sel = (unsigned char*)Ws;
+  static_assert(PR * HP >= 4096, "");
+  for (int k = tid; k < n; k += JT) slam[k] = lam[k];
+  __syncthreads();
+  for (int k = tid; k < n; k += JT) {
+    const double v = slam[k];
+    int rank = 0;
+    for (int j = 0; j < n; ++j) {
+      const double w = slam[j];
+      rank += (w > v || (w == v && j < k)) ? 1 : 0;
+    }
+    sel[k] = (rank < r && v > 0.0) ? 1 : 0;
+  }
+  __syncthreads();
+  // the selected rows' reciprocal lengths in place of the lengths: a row then costs a thread one load and two
+  // multiplications, eight rows' loads in flight
+  for (int k = tid; k < n; k += JT) slam[k] = sel[k] ? 1.0 / slam[k] : 0.0;
+  __syncthreads();
+  for (int i = tid; i < n; i += JT) {
+    const double* Ai = A + i;
+    double acc = 0.0;
+    int k = 0;
+    for (; k + 8 <= n; k += 8) {
+      double a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = Ai[(long)(k + u) * nP];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += sel[k + u] ? a[u] * a[u] * slam[k + u] : 0.0;    // an unselected row may hold anything
+    }
+    for (; k < n; ++k) {
+      const double a = Ai[(long)k * nP];
+      acc += sel[k] ? a * a * slam[k] : 0.0;
+    }
+    c[i] = (float)acc;
+  }
+}
+
+// The whole solve of all images that have no energies yet: workgroup (image b, slot pr) visits the pair `pr` of every tournament round
+// of every sweep; after a sweep, slot 0 decides convergence and re-measures which rows are the r longest.  At the end each workgroup
+// measures its rows, and the last one of the image adds up the energies (or says that there are none).  With `src` the matrix is copied
+// from there first.  Where no image is left to solve every workgroup returns at once, in front of the ticket; the start values, the
+// lengths and the energies in launches of their own cost every call three more of these returns, 2 to 4 us each (up to 41 for the lengths of
+// sixty-four images of 640).
+// A and len2 are written and re-read by different workgroups between barriers, hence no __restrict__.  ctl is cleared before the launch.
+__global__ __launch_bounds__(JT) void jacobi_solve_kernel(double* A, const double* __restrict__ src, int n, int nP, int nsb, int r, int B, JacobiCtl* ctl,
+                                                          double* len2, const int* __restrict__ done, float* __restrict__ c, int* img_status,
+                                                          long long limit_ticks) {
   const int npairs = nsb >> 1;
   const int tid = threadIdx.x;
+  if (done) {
+    bool left = false;
+    for (int k = tid; k < B; k += JT) left = left || done[k] == 0;
+    if (!__syncthreads_or(left)) return;
+  }
   if (tid == 0) s_flag = (int)atomicAdd(&ctl[0].ticket, 1u);
   __syncthreads();
   const int ticket = s_flag;
   __syncthreads();   // s_flag is reused by the barriers
   const int b = ticket / npairs, pr = ticket - b * npairs;
   JacobiCtl* cb = ctl + b;
-  if (cb->done) return;   // set before the launch, so the same for every workgroup of the image
+  if (done && done[b]) return;   // set before the launch, so the same for every workgroup of the image
   double* Ab = A + (long)b * nP * nP;
   double* len2b = len2 + (long)b * nP;
-  const double floor2 = cb->floor2;   // written by the init kernel
-  unsigned int target = 0;
-  bool alive = true;
+  const double* Gb = src ? src + (long)b * nP * nP : Ab;
+  // rows with a squared norm below floor2 are treated as zero; the trace is that of the matrix as it came
+  double tr = 0.0;
+  for (int i = tid; i < n; i += JT) tr += Gb[(long)i * nP + i];
+  tr = wave_sum(tr);
+  if ((tid & 63) == 0) Hs[tid >> 6] = tr;
+  __syncthreads();
+  tr = 0.0;
+  for (int w = 0; w < JW; ++w) tr += Hs[w];
+  const double floor2 = (1e-13 * tr) * (1e-13 * tr);
+  if (src)
+    for (long e = tid; e < (long)PR * nP; e += JT) Ab[(long)pr * PR * nP + e] = Gb[(long)pr * PR * nP + e];
+  unsigned int target = npairs;
+  bool alive = image_barrier_wait(&cb->bar, target, &s_flag, limit_ticks);
 #pragma unroll 1
   for (int sweep = 0; sweep < kMaxSweeps && alive; ++sweep) {
     const double long2 = __hip_atomic_load(&cb->long2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -399,71 +442,27 @@ __global__ __launch_bounds__(JT) void jacobi_solve_kernel(double* A, int n, int 
     const double qnan = __longlong_as_double(0x7ff8000000000000LL);
     for (long e = tid; e < (long)PR * nP; e += JT) Ab[(long)pr * PR * nP + e] = qnan;
     if (img_status && tid == 0) img_status[b] = 1;
-  }
-}
-
-// lam[b*rows + k] = |row k of A[b]| (A[b] starts at b*img_stride and has `rows` rows of `pitch`), one wave per row
-__global__ __launch_bounds__(256) void row_length_kernel(const double* __restrict__ A, int rows, int pitch, long img_stride,
-                                                          double* __restrict__ lam) {
-  const int lane = threadIdx.x & 63;
-  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int b = blockIdx.y;
-  if (k >= rows) return;
-  const double* row = A + b * img_stride + (long)k * pitch;
-  double s = 0.0;
-  for (int j = lane; j < pitch; j += 64) s = fma(row[j], row[j], s);
-  s = wave_sum(s);
-  if (lane == 0) lam[(long)b * rows + k] = sqrt(s);
-}
-
-// c[b,i] = sum over the r longest rows k of A[b] (rows x pitch) of A[k][i]^2 / |row k|, rows added in
-// ascending k; i < n.  Images with (flag[b] != 0) != (run_if != 0) are skipped (flag == nullptr: none).
-__global__ __launch_bounds__(256) void energy_kernel(const double* __restrict__ A, int rows, int n, int pitch, long img_stride,
-                                                      int r, const double* __restrict__ lam, float* __restrict__ c,
-                                                      const int* __restrict__ flag, int run_if, const int* __restrict__ gave_up) {
-  __shared__ double slam[4096];
-  __shared__ unsigned char sel[4096];
-  const int b = blockIdx.y;
-  if (flag && (flag[b] != 0) != (run_if != 0)) return;     // flag: 0 = not converged, any other value = converged
-  if (gave_up && gave_up[b]) {                             // rows without a length are never among the longest: say so here
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) c[(long)b * n + i] = __uint_as_float(0x7fc00000u);
-    return;
-  }
-  const double* lb = lam + (long)b * rows;
-  for (int k = threadIdx.x; k < rows; k += 256) slam[k] = lb[k];
-  __syncthreads();
-  for (int k = threadIdx.x; k < rows; k += 256) {
-    const double v = slam[k];
-    int rank = 0;
-    for (int j = 0; j < rows; ++j) {
-      const double w = slam[j];
-      rank += (w > v || (w == v && j < k)) ? 1 : 0;
+  } else {
+    const int lane = tid & 63;
+    for (int k = pr * PR + (tid >> 6); k < (pr + 1) * PR; k += JW) {     // one wave per row
+      double s = 0.0;
+      for (int j = lane; j < nP; j += 64) { const double v = Ab[(long)k * nP + j]; s = fma(v, v, s); }
+      s = wave_sum(s);
+      if (lane == 0) len2b[k] = sqrt(s);
     }
-    sel[k] = (rank < r && v > 0.0) ? 1 : 0;
+  }
+  // the last of the image's workgroups has everybody's rows, and everybody's failures, before it
+  __syncthreads();
+  if (tid == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    const unsigned int at = __hip_atomic_fetch_add(&cb->finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    s_flag = at + 1u == (unsigned int)npairs;
   }
   __syncthreads();
-  // the selected rows' reciprocal lengths in place of the lengths: a row then costs a thread one load and two
-  // multiplications, eight rows' loads in flight (a division per row and one load at a time took 67 us for workload 5)
-  for (int k = threadIdx.x; k < rows; k += 256) slam[k] = sel[k] ? 1.0 / slam[k] : 0.0;
-  __syncthreads();
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const double* Ab = A + b * img_stride + i;
-  double acc = 0.0;
-  int k = 0;
-  for (; k + 8 <= rows; k += 8) {
-    double a[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] = Ab[(long)(k + u) * pitch];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc += sel[k + u] ? a[u] * a[u] * slam[k + u] : 0.0;    // an unselected row may hold anything
-  }
-  for (; k < rows; ++k) {
-    const double a = Ab[(long)k * pitch];
-    acc += sel[k] ? a * a * slam[k] : 0.0;
-  }
-  c[(long)b * n + i] = (float)acc;
+  if (!s_flag) return;
+  const bool failed = __hip_atomic_load(&cb->bar.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+  energies_of(Ab, len2b, n, nP, r, failed, c + (long)b * n);
 }
 
 }  // namespace
@@ -477,7 +476,7 @@ std::atomic<long long> g_barrier_limit{kBarrierLimitTicks};
 void set_barrier_limit_ticks(long long ticks) { g_barrier_limit.store(ticks > 0 ? ticks : kBarrierLimitTicks); }
 long long barrier_limit_ticks() { return g_barrier_limit.load(); }
 
-hipError_t launch_jacobi_eigen(double* A, int B, int n, int nP, int r, void* ctl_, double* len2, const int* preset_done,
+hipError_t launch_jacobi_eigen(double* A, const double* src, int B, int n, int nP, int r, void* ctl_, double* len2, const int* done, float* c,
                                int* img_status, hipStream_t st) {
   if (nP % 64 != 0 || n > nP || n > 4096 || r < 1 || r > n) return hipErrorInvalidValue;
   JacobiCtl* ctl = (JacobiCtl*)ctl_;
@@ -489,17 +488,8 @@ hipError_t launch_jacobi_eigen(double* A, int B, int n, int nP, int r, void* ctl
   const hipError_t ec = resident_workgroups(cache, jacobi_solve_kernel, JT, 0, &capacity);
   if (ec != hipSuccess) return ec;
   if (npairs > capacity) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(jacobi_init_kernel, dim3(B), dim3(256), 0, st, A, n, nP, ctl, preset_done);
-  hipLaunchKernelGGL(jacobi_solve_kernel, dim3((unsigned)(B * npairs)), dim3(JT), 0, st, A, n, nP, nsb, r, ctl, len2,
-                     img_status, barrier_limit_ticks());
-  return hipGetLastError();
-}
-
-hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int pitch, long img_stride, int r, double* lam,
-                                  float* c, const int* flag, int run_if, const int* gave_up, hipStream_t st) {
-  if (rows > 4096 || r > rows) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(row_length_kernel, dim3((rows + 3) / 4, B), dim3(256), 0, st, A, rows, pitch, img_stride, lam);
-  hipLaunchKernelGGL(energy_kernel, dim3((n + 255) / 256, B), dim3(256), 0, st, A, rows, n, pitch, img_stride, r, lam, c, flag, run_if, gave_up);
+  hipLaunchKernelGGL(jacobi_solve_kernel, dim3((unsigned)(B * npairs)), dim3(JT), 0, st, A, src, n, nP, nsb, r, B, ctl, len2, done, c, img_status,
+                     barrier_limit_ticks());
   return hipGetLastError();
 }
 

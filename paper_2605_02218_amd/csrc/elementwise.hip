@@ -107,7 +107,9 @@ __global__ __launch_bounds__(256) void row_norm2_kernel(const In* __restrict__ x
 
 // ---------------------------------------------------------------- transpose
 template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, T* __restrict__ out, int rows, int cols) {
+__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in0, T* __restrict__ out0, const T* __restrict__ in1, T* __restrict__ out1, int rows, int cols) {
+  const T* __restrict__ in = blockIdx.z ? in1 : in0;
+  T* __restrict__ out = blockIdx.z ? out1 : out0;
   __shared__ T tile[64][65];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
@@ -122,7 +124,9 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
 // tiles of E-byte elements, rows and cols multiples of 16 / E, 16-byte aligned.  3584 x 3584 bf16: 27.5 us with an element per
 // access, 11.4 here (51 MB).
 template <typename T>
-__global__ __launch_bounds__(256) void transpose16_kernel(const T* __restrict__ in, T* __restrict__ out, int rows, int cols) {
+__global__ __launch_bounds__(256) void transpose16_kernel(const T* __restrict__ in0, T* __restrict__ out0, const T* __restrict__ in1, T* __restrict__ out1, int rows, int cols) {
+  const T* __restrict__ in = blockIdx.z ? in1 : in0;
+  T* __restrict__ out = blockIdx.z ? out1 : out0;
   constexpr int N = 16 / sizeof(T), PER = 64 / N;      // elements per piece, pieces per tile row
   __shared__ T tile[64][64 + 4 / sizeof(T)];           // a row is an odd number of banks
   typedef T piece_t __attribute__((ext_vector_type(N)));
@@ -485,23 +489,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const unsigned char* _
     *(u32x4_t*)(out + dst + o) = *(const u32x4_t*)(X + src + o);
 }
 
-// Rows and columns n .. pitch - 1 of the matrices A[b] (pitch x pitch).  (Clearing all of the matrices in front of the products that
-// fill them took 16 us for four of 1664 and 13 for four of 1280; the padding takes 3, and nothing where there is none.)
-__global__ __launch_bounds__(256) void zero_padding_kernel(double* __restrict__ A, int n, int pitch, long each, long total) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const long b = i / each, e = i - b * each, right = (long)n * (pitch - n);
-  const int w = pitch - n;
-  A[b * pitch * pitch + (e < right ? (e / w) * pitch + n + e % w : (long)n * pitch + (e - right))] = 0.0;
-}
-
-// Images whose flag is set (null: none) are left out.
-__global__ __launch_bounds__(256) void copy_images_kernel(u32x4_t* __restrict__ dst, const u32x4_t* __restrict__ src, long n16, const int* __restrict__ leave) {
-  const int b = blockIdx.y;
-  if (leave && leave[b] != 0) return;
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n16; i += (long)gridDim.x * 256) dst[b * n16 + i] = src[b * n16 + i];
-}
-
 inline unsigned blocks_for(long n, int per) { return (unsigned)((n + per - 1) / per); }
 
 __global__ __launch_bounds__(256) void random_scores_kernel(float* __restrict__ out, int B, int N, uint32_t seed, int image0) {
@@ -523,16 +510,19 @@ __global__ void fill_int_kernel(int* __restrict__ p, int n, int value) {
 
 }  // namespace
 
-hipError_t launch_transpose(const void* in, void* out, int rows, int cols, int dtype, hipStream_t st) {
-  dim3 grid((cols + 63) / 64, (rows + 63) / 64), block(256);
+hipError_t launch_transpose(const void* in, void* out, const void* in1, void* out1, int rows, int cols, int dtype, hipStream_t st) {
+  dim3 grid((cols + 63) / 64, (rows + 63) / 64, in1 ? 2 : 1), block(256);
   const int piece = dtype == DT_BF16 ? 8 : 4;
-  if (rows % piece == 0 && cols % piece == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0) {
-    if (dtype == DT_BF16) hipLaunchKernelGGL((transpose16_kernel<bf16_t>), grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, rows, cols);
-    else hipLaunchKernelGGL((transpose16_kernel<float>), grid, block, 0, st, (const float*)in, (float*)out, rows, cols);
-    return hipGetLastError();
+  const uintptr_t bits = (uintptr_t)in | (uintptr_t)out | (uintptr_t)in1 | (uintptr_t)out1;
+#define COVSPEC_TRANSPOSE(kernel, T) hipLaunchKernelGGL((kernel<T>), grid, block, 0, st, (const T*)in, (T*)out, (const T*)in1, (T*)out1, rows, cols)
+  if (rows % piece == 0 && cols % piece == 0 && (bits & 15) == 0) {
+    if (dtype == DT_BF16) COVSPEC_TRANSPOSE(transpose16_kernel, bf16_t);
+    else COVSPEC_TRANSPOSE(transpose16_kernel, float);
+  } else {
+    if (dtype == DT_BF16) COVSPEC_TRANSPOSE(transpose_kernel, bf16_t);
+    else COVSPEC_TRANSPOSE(transpose_kernel, float);
   }
-  if (dtype == DT_BF16) hipLaunchKernelGGL((transpose_kernel<bf16_t>), grid, block, 0, st, (const bf16_t*)in, (bf16_t*)out, rows, cols);
-  else hipLaunchKernelGGL((transpose_kernel<float>), grid, block, 0, st, (const float*)in, (float*)out, rows, cols);
+#undef COVSPEC_TRANSPOSE
   return hipGetLastError();
 }
 
@@ -643,21 +633,6 @@ hipError_t launch_random_scores(float* out, int B, int N, uint32_t seed, int ima
 hipError_t launch_fill_int(int* p, int n, int value, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(fill_int_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, n, value);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_padding(double* A, int B, int n, int pitch, hipStream_t st) {
-  const long each = (long)pitch * pitch - (long)n * n, total = each * B;
-  if (each < 0) return hipErrorInvalidValue;
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_padding_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, st, A, n, pitch, each, total);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_images(double* dst, const double* src, int B, long each, const int* leave, hipStream_t st) {
-  if (each % 2 != 0) return hipErrorInvalidValue;
-  const unsigned blocks = blocks_for(each / 2, 256);
-  hipLaunchKernelGGL(copy_images_kernel, dim3(blocks < 512u ? blocks : 512u, (unsigned)B), dim3(256), 0, st, (u32x4_t*)dst, (const u32x4_t*)src, each / 2, leave);
   return hipGetLastError();
 }
 

@@ -37,11 +37,6 @@ struct GreedyCtl {
   unsigned int pad;
 };
 
-__global__ void greedy_init_kernel(GreedyCtl* ctl, int B) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) { ctl[b].bar.arrived = 0u; ctl[b].bar.failed = 0; ctl[b].ticket = 0u; ctl[b].pad = 0u; }
-}
-
 // posts: per image [2][W] keys (u64) then [2][W] rho (fp64), double-buffered by step parity
 __global__ __launch_bounds__(GT) void greedy_kernel(const double* __restrict__ G, int n, int nP, int k, double* Lt, int32_t* __restrict__ order,
                                                      float* __restrict__ resid, GreedyCtl* ctl, unsigned long long* posts,
@@ -758,6 +753,7 @@ __global__ __launch_bounds__(TPB) void greedy_finish_kernel(const int32_t* __res
 
 }  // namespace
 
+size_t greedy_ctl_bytes(int B) { return (size_t)B * sizeof(GreedyCtl); }
 size_t greedy_scratch_bytes(int B, int nP) {
   return (size_t)B * sizeof(GreedyCtl) + 256 + (size_t)B * 4 * (nP / GR) * 8;
 }
@@ -777,7 +773,6 @@ static hipError_t launch_panel(K kernel, PerDeviceInt& raised, PerDeviceInt& cac
   int capacity = 0;
   if ((e = resident_workgroups(cache, kernel, TPB, most, &capacity)) != hipSuccess) return e;
   if (W > capacity) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(greedy_init_kernel, dim3((B + 255) / 256), dim3(256), 0, st, ctl, B);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(B * W)), dim3(TPB), lds, st, G, n, nP, k, W, order, resid, ctl, img_status, barrier_limit_ticks());
   return hipGetLastError();
 }
@@ -833,7 +828,6 @@ hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int
   if (ec != hipSuccess) return ec;
   if (W > capacity) return hipErrorInvalidValue;
   unsigned long long* posts = (unsigned long long*)((char*)scratch + (((size_t)B * sizeof(GreedyCtl) + 255) / 256) * 256);
-  hipLaunchKernelGGL(greedy_init_kernel, dim3((B + 255) / 256), dim3(256), 0, st, ctl, B);
   hipLaunchKernelGGL(greedy_kernel, dim3((unsigned)(B * W)), dim3(GT), 0, st, G, n, nP, k, Lt, order, resid, ctl, posts,
                      img_status, barrier_limit_ticks());
   return hipGetLastError();

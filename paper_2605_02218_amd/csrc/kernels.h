@@ -70,8 +70,8 @@ hipError_t launch_gemm64_rownorm_dual(const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm64_bf16(const GemmArgs& g, hipStream_t stream);
 
 // ---------------------------------------------------------------- elementwise.hip
-// out[c][r] = in[r][c] for a rows x cols matrix of bf16 or fp32 elements.
-hipError_t launch_transpose(const void* in, void* out, int rows, int cols, int dtype, hipStream_t stream);
+// out[c][r] = in[r][c] for a rows x cols matrix of bf16 or fp32 elements; in1 (optional): another one of the same shape to out1.
+hipError_t launch_transpose(const void* in, void* out, const void* in1, void* out1, int rows, int cols, int dtype, hipStream_t stream);
 
 // Token activity (paper Sec. III-A.2): s_act[b,i] = (1/K) sum_l ||hidden[b,l,i,:] - hidden[b,l-1,i,:]||_2.
 hipError_t launch_activity(const void* hidden, float* s_act, int B, int N, int d, int K, int dtype, hipStream_t stream);
@@ -121,10 +121,6 @@ hipError_t launch_fuse(const float* s_query, const float* s_act, float* s_fused,
 hipError_t launch_gather_rows(const void* X, const int32_t* idx, void* out, int B, int N, int k, long row_bytes,
                               hipStream_t stream);
 
-// Zeroes rows and columns n .. pitch - 1 of B matrices (pitch x pitch).
-hipError_t launch_zero_padding(double* A, int B, int n, int pitch, hipStream_t stream);
-// dst[b] = src[b] (`each` doubles, even; 16-byte aligned) but for images b with leave[b] != 0 (leave may be null).
-hipError_t launch_copy_images(double* dst, const double* src, int B, long each, const int* leave, hipStream_t stream);
 hipError_t launch_fill_int(int* p, int n, int value, hipStream_t stream);
 
 // Reproducible uniform scores for the random-selection ablation: out[b, i] = top 24 bits of
@@ -147,17 +143,12 @@ long long barrier_limit_ticks();
 // rows/cols >= n zero).  On return the r longest rows k of A[b] are lambda_k v_k^T (shorter rows only span the rest).  `ctl` is scratch of jacobi_ctl_bytes(B), `len2` scratch of B*nP doubles.
 size_t jacobi_ctl_bytes(int B);
 int jacobi_pitch(int n);      // row pitch (and padded order) the solver needs: n rounded up to 64
-// preset_done (optional, [B]): images whose entry is non-zero are left untouched.
-// img_status (optional, [B]): set to 1 for an image whose workgroups gave up waiting for one another (its rows
-// are then NaN); never cleared here.
-hipError_t launch_jacobi_eigen(double* A, int B, int n, int nP, int r, void* ctl, double* len2, const int* preset_done,
+// done (optional, [B]): images whose entry is non-zero are left untouched.  src (optional): the matrices are there, of the same pitch, and
+// A only takes the rows.  c[b,i], i < n: the subspace energy (paper energy equation), the sum over the r longest rows of A[k][i]^2 / |row k|.
+// img_status (optional, [B]): set to 1 for an image whose workgroups gave up waiting for one another (its energies
+// are then NaN); never cleared here.  ctl is cleared before (launch_lowrank_prepare).
+hipError_t launch_jacobi_eigen(double* A, const double* src, int B, int n, int nP, int r, void* ctl, double* len2, const int* done, float* c,
                                int* img_status, hipStream_t stream);
-// Subspace energy (paper energy equation) from rows of the form lambda_k v_k^T: c[b,i] = sum over the r
-// longest of the `rows` rows of A[b] of A[k][i]^2 / |row k|, i < n.  A[b] starts at b*img_stride, rows have
-// `pitch` doubles.  `lam` is scratch of B*rows doubles.  Images with flag[b] != run_if are skipped
-// (flag == nullptr: none), those with gave_up[b] != 0 (optional) get NaN.
-hipError_t launch_subspace_energy(const double* A, int B, int rows, int n, int pitch, long img_stride, int r, double* lam,
-                                  float* c, const int* flag, int run_if, const int* gave_up, hipStream_t stream);
 
 // ---------------------------------------------------------------- split.hip
 // Projector onto the span of the r dominant eigenvectors of the symmetric positive semidefinite H[b] (P x P, pitch P,
@@ -171,9 +162,17 @@ bool split_direct(int nP);
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
                                  const int* skip, const int* again, hipStream_t stream);
 // Residual check and energies of a block iteration, see split.hip.  slow[b] != 0: the image was left out of the split.
+// next.state != null: state 0 of a further pass, of `fields` integers per image: images that passed the check rest (2); one that was left
+// out of the split goes on from its block, which is in the buffer that state `prev` names last, one that failed the check from the product with
+// G that followed its last orthonormalisation (redo).  And its flags are cleared.
+struct NextPass {
+  int *state, *left, *failed, *redo, *flags;      // [4][B], [B], [B], one per `redo_step` ints, [flag_sets][B][flag_words]
+  const int* prev;
+  int redo_step, flag_sets, flag_words;
+};
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
                                int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,
-                               hipStream_t stream);
+                               const NextPass& next, hipStream_t stream);
 // c[b][i] = (Pi G)_ii, i < n, from the projector of G[b] itself; done[b] = 3 where there is one, else 0 and c[b] untouched.
 hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n, int nP, int r, const void* scratch, int* done, float* c,
                                 hipStream_t stream);
@@ -185,6 +184,9 @@ hipError_t launch_direct_energy(const double* G, const double* Pi, int B, int n,
 // On return ok[b] != 0 where c[b] is valid: 1 after the first pass, 2 after the second, 3 by the projector of G.  0 also where a wait of
 // its kernels ran out.
 int subspace_block(int n, int r);
+// What the low-rank stage finds cleared or laid out, in one launch in front of it: status[b] = 0 and `words` ints at ctl (each optional), rows
+// and columns n .. nP - 1 of the B matrices A (pitch nP), and for P > 0 the start pattern and the first state of the iteration in `ws`.
+hipError_t launch_lowrank_prepare(int* status, void* ctl, size_t words, double* A, int B, int n, int nP, int P, void* ws, hipStream_t stream);
 size_t subspace_workspace_bytes(int B, int n, int nP, int P);
 // probe_begin / probe_end (optional): recorded around the first of the subspace_product_launches()
 // launches of the product Yt G (P x nP x nP per image).
@@ -198,6 +200,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
 // order[b,t] = local position picked at step t, resid[b,t] = residual squared norm at that pick.
 // nP % 64 == 0; `scratch` holds greedy_scratch_bytes(B, nP) bytes (barrier counters and per-step posts).
 size_t greedy_scratch_bytes(int B, int nP);
+size_t greedy_ctl_bytes(int B);     // its first bytes, which are cleared before (launch_lowrank_prepare)
 // img_status (optional, [B]): set to 1 for an image whose workgroups gave up waiting for one another (order[b] is
 // then 0..k-1 and its residuals NaN); never cleared here.
 hipError_t launch_greedy(double* G, int B, int n, int nP, int k, double* Lt, int32_t* order, float* resid, void* scratch,

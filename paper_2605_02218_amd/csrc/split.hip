@@ -198,31 +198,12 @@ __device__ __forceinline__ void reflect_all(double (&A)[X][X], double* xs, doubl
 // barrier instead of two measured the same): 126 reflections 100 us, a Sturm pass of 128 trial points 6.6.  144 us in all with
 // library square roots and divisions and the row sums one after the other, 124 so; a window of 64 rows 45.
 template <int N>
-__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int B, int r, double* __restrict__ off,
-                                                    double* __restrict__ link, SplitCtl* ctl, const int* __restrict__ skip,
-                                                    const int* __restrict__ again) {
+__device__ __forceinline__ void split_window(const double* __restrict__ H, int P, long stride, int r, int b, SplitCtl* cb, double* rd) {
   constexpr int X = N / 16;
-  __shared__ double rd[4096];
-  if (blockIdx.x >= (unsigned)B) {
-    const int per = P / 16, at = blockIdx.x - B, img = at / per;
-    if (again && (again[img] != 0) != (N == SN)) return;
-    if (!(skip && skip[img])) row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
-    return;
-  }
   double *xs = rd, *ps = rd + N, *dv = rd + 2 * N, *es = rd + 3 * N;   // es: squared off-diagonals
   __shared__ double red[4];
   __shared__ int cnt[2][4];
-  const int b = blockIdx.x, tid = threadIdx.x, ti = tid >> 4, tj = tid & 15, lane = tid & 63, wv = tid >> 6;
-  SplitCtl* cb = ctl + b;
-  if (b == 0 && tid == 0) ctl[0].ticket = 0u;
-  if (again && (again[b] != 0) != (N == SN)) return;
-  for (int k = tid; k < kMaxSignSteps + 2; k += 256) cb->dev[k] = 0ull;
-  if (tid == 0) {
-    cb->bar.arrived = 0u;
-    cb->bar.failed = 0;
-    cb->state = 1;
-  }
-  if (skip && skip[b]) return;
+  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15, lane = tid & 63, wv = tid >> 6;
   const double* Hb = H + b * stride;
   const int w0 = P <= N ? 0 : (r - N / 2 < 0 ? 0 : (r - N / 2 > P - N ? P - N : r - N / 2));
   const int nw = P - w0 < N ? P - w0 : N;
@@ -306,6 +287,30 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
     cb->theta = lo[0] * big;
     cb->state = gap > 0.0 && mu > 0.0 ? 0 : 1;
   }
+}
+
+// wide: every image has a window of SN rows; else those with again[b] != 0 (optional), the others 64
+__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int B, int r, bool wide, double* __restrict__ off,
+                                                    double* __restrict__ link, SplitCtl* ctl, const int* __restrict__ skip,
+                                                    const int* __restrict__ again) {
+  __shared__ double rd[4096];
+  if (blockIdx.x >= (unsigned)B) {
+    const int per = P / 16, at = blockIdx.x - B, img = at / per;
+    if (!(skip && skip[img])) row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
+    return;
+  }
+  const int b = blockIdx.x, tid = threadIdx.x;
+  SplitCtl* cb = ctl + b;
+  if (b == 0 && tid == 0) ctl[0].ticket = 0u;
+  for (int k = tid; k < kMaxSignSteps + 2; k += 256) cb->dev[k] = 0ull;
+  if (tid == 0) {
+    cb->bar.arrived = 0u;
+    cb->bar.failed = 0;
+    cb->state = 1;
+  }
+  if (skip && skip[b]) return;
+  if (wide || (again && again[b])) split_window<SN>(H, P, stride, r, b, cb, rd);
+  else split_window<64>(H, P, stride, r, b, cb, rd);
 }
 
 constexpr int ST = 32;            // tile of a wave in the sign iteration
@@ -624,19 +629,21 @@ __device__ __forceinline__ double trace_minus(const double* Pi, int P, int r, do
 __global__ __launch_bounds__(1024) void split_finish_kernel(const double* __restrict__ H, const double* __restrict__ Pi,
                                                             const double* __restrict__ rnorm, int rparts, const double* __restrict__ cpart,
                                                             int cparts, int P, int n, int nP, int r, double tol,
-                                                            const SplitCtl* __restrict__ ctl, const int* __restrict__ slow, int* ok, int pass_no,
-                                                            float* __restrict__ c) {
+                                                            const SplitCtl* __restrict__ ctl, const int* slow, int* ok, int pass_no,
+                                                            float* __restrict__ c, NextPass next) {
   __shared__ double red[16];
   __shared__ int bad;
-  const int b = blockIdx.x;
+  const int b = blockIdx.x, B = gridDim.x;
   if (pass_no > 1 && ok[b]) return;                  // passed an earlier check; its energies are in place
-  if (slow[b]) {                                     // not split in this pass
-    if (threadIdx.x == 0) ok[b] = 0;
-    return;
-  }
+  const bool split = !slow[b];                       // in this pass
   if (threadIdx.x == 0) bad = 0;
+  if (next.state)
+    for (int k = threadIdx.x; k < next.flag_sets * next.flag_words; k += 1024) {
+      const int set = k / next.flag_words;
+      next.flags[((long)set * B + b) * next.flag_words + k - set * next.flag_words] = 0;
+    }
   __syncthreads();
-  const bool valid = projector_valid(ctl + b);
+  const bool valid = split && projector_valid(ctl + b);
   const double theta = ctl[b].theta;
   if (valid) {
     const double off = trace_minus(Pi + (long)b * P * P, P, r, red, 1024);
@@ -651,7 +658,19 @@ __global__ __launch_bounds__(1024) void split_finish_kernel(const double* __rest
   }
   __syncthreads();
   const bool good = valid && bad == 0;
-  if (threadIdx.x == 0) ok[b] = good ? pass_no : 0;
+  if (threadIdx.x == 0) {
+    ok[b] = good ? pass_no : 0;
+    if (next.state) {
+      const int at = next.prev[3 * B + b];
+      next.state[b] = good ? 2 : 0;
+      next.state[B + b] = 0;
+      next.state[2 * B + b] = at;
+      next.state[3 * B + b] = at;
+      next.redo[(long)b * next.redo_step] = !good && split;
+      next.failed[b] = !good && split;
+      next.left[b] = good;
+    }
+  }
   if (!good) return;
   for (int i = threadIdx.x; i < n; i += 1024) {
     double s = 0.0;
@@ -708,8 +727,7 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   if (W < 1) return hipErrorInvalidValue;
   const long stride = (long)P * P;
   const dim3 sg((unsigned)(B + B * (P / 16)));
-  if (ordered) hipLaunchKernelGGL(split_kernel<64>, sg, dim3(256), 0, st, H, P, stride, B, r, off, link, ctl, skip, again);
-  if (!ordered || again) hipLaunchKernelGGL(split_kernel<SN>, sg, dim3(256), 0, st, H, P, stride, B, r, off, link, ctl, skip, again);
+  hipLaunchKernelGGL(split_kernel, sg, dim3(256), 0, st, H, P, stride, B, r, !ordered, off, link, ctl, skip, again);
   hipLaunchKernelGGL(kern, dim3((unsigned)(B * W)), dim3(form == 1 ? 512 : 256), lds, st, H, X0, Y, X1, P, r, (const double*)off, (const double*)link,
                      ordered, (int)W, ctl, barrier_limit_ticks());
   return hipGetLastError();
@@ -717,9 +735,9 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
 
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
                                int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,
-                               hipStream_t st) {
+                               const NextPass& next, hipStream_t st) {
   hipLaunchKernelGGL(split_finish_kernel, dim3(B), dim3(1024), 0, st, H, Pi, rnorm, rparts, cpart, cparts, P, n, nP, r, tol,
-                     (const SplitCtl*)scratch, slow, ok, pass_no, c);
+                     (const SplitCtl*)scratch, slow, ok, pass_no, c, next);
   return hipGetLastError();
 }
 

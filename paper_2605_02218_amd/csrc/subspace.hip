@@ -23,6 +23,7 @@
 // G) cannot make it rank deficient.
 // The residual of the dominant subspace, Pi Q^T G - H U, is checked; images that fail (slow decay, P too small, no gap
 // at the cut) take up to two further blocks and, if they fail again, the full block Jacobi solve of G.
+#include <initializer_list>
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"
@@ -48,15 +49,6 @@ constexpr float kSteep = 9.0f;         // ln(lambda_1 / lambda_P) from which gro
 
 constexpr size_t kCholLds = (size_t)2 * NB * NBP * sizeof(double);
 constexpr int kMaxBlocks = 64;         // block rows: P <= 4096
-
-__global__ void omega_kernel(double* __restrict__ om, int P, int n, int nP) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)P * nP) return;
-  const int r = (int)(i / nP), c = (int)(i - (long)r * nP);
-  uint32_t h = (uint32_t)r * 0x9E3779B1u ^ ((uint32_t)c + 0x7F4A7C15u) * 0x85EBCA77u;
-  h ^= h >> 15; h *= 0x2C1B3C6Du; h ^= h >> 12; h *= 0x297A2D39u; h ^= h >> 15;
-  om[i] = (c < n) ? ((h & 1u) ? 1.0 : -1.0) : 0.0;
-}
 
 // ---- The schedule of an image.  Orthonormalisations are numbered; before orthonormalisation k the kernels read state k of the
 // image, the factorisation writes state k + 1, the products behind it read that.  Four integers per image and state:
@@ -768,25 +760,75 @@ __global__ __launch_bounds__(512) void orth_kernel(double* S, double* __restrict
     __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// State 0 of a pass.  First: every block is in buffer 0.  Second: images that passed the check rest; one that was left out of the
-// split goes on from its block, one that failed the check from the product with G that followed its last orthonormalisation.  And
-// the flags of the pass's factorisations.
-__global__ void begin_pass_kernel(int* __restrict__ out, const int* __restrict__ prev, const int* __restrict__ ok, IterPlan* __restrict__ plan,
-                                  int* __restrict__ left, int* __restrict__ failed_before, int B, CholFlags* __restrict__ flags, int orths) {
-  int* words = (int*)flags;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < orths * B * (int)(sizeof(CholFlags) / sizeof(int)); k += gridDim.x * blockDim.x) words[k] = 0;
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const bool passed = prev && ok[b] != 0, failed = prev && !passed && !left[b];
-  const int at = prev ? prev[ST_END * B + b] : 0;
-  out[ST_REST * B + b] = passed ? 2 : 0;
-  out[ST_IDLE * B + b] = 0;
-  out[ST_SEL * B + b] = at;
-  out[ST_END * B + b] = at;
-  plan[b].redo = failed;
-  failed_before[b] = failed;
-  left[b] = passed;
+// See launch_lowrank_prepare.  One thread per element of the start block Omega, a fixed pattern of +-1, and of the padding; the words with
+// them.  (These were five launches of 2 to 4 us each.  Clearing all of the matrices in front of the products that fill them took 16 us for four of
+// 1664 and 13 for four of 1280.)
+struct PrepareArgs {
+  int *status, *ctl, *flags, *state, *left, *failed;
+  IterPlan* plan;
+  double *A, *om;
+  long words, flag_words, pad, omega;      // numbers of elements; pad: of one matrix
+  int B, n, nP;
+};
+__global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
+  const long at = (long)blockIdx.x * 256 + threadIdx.x, step = (long)gridDim.x * 256;
+  for (long i = at; i < q.omega; i += step) {
+    const int r = (int)(i / q.nP), c = (int)(i - (long)r * q.nP);
+    uint32_t h = (uint32_t)r * 0x9E3779B1u ^ ((uint32_t)c + 0x7F4A7C15u) * 0x85EBCA77u;
+    h ^= h >> 15; h *= 0x2C1B3C6Du; h ^= h >> 12; h *= 0x297A2D39u; h ^= h >> 15;
+    q.om[i] = (c < q.n) ? ((h & 1u) ? 1.0 : -1.0) : 0.0;
+  }
+  const long right = (long)q.n * (q.nP - q.n);
+  const int w = q.nP - q.n;
+  for (long i = at; i < q.pad * q.B; i += step) {
+    const long b = i / q.pad, e = i - b * q.pad;
+    q.A[b * q.nP * q.nP + (e < right ? (e / w) * q.nP + q.n + e % w : (long)q.n * q.nP + (e - right))] = 0.0;
+  }
+  for (long i = at; i < q.words; i += step) q.ctl[i] = 0;
+  for (long i = at; i < q.flag_words; i += step) q.flags[i] = 0;
+  for (long b = at; b < q.B; b += step) {
+    if (q.status) q.status[b] = 0;
+    if (q.state) {                         // every block is in buffer 0
+#pragma unroll
+      for (int k = 0; k < ST_FIELDS; ++k) q.state[k * q.B + b] = 0;
+      q.plan[b].redo = 0;
+      q.left[b] = q.failed[b] = 0;
+    }
+  }
 }
+
+// The workspace of the iteration.
+struct IterBuffers {
+  double *Yt, *Zt, *Om, *S, *H, *D, *Pi;   // Pi: [B][P][P] the projector
+  void* scratch;                           // of the split
+  IterPlan* plan;                          // [B]
+  int *states, *left, *failed;             // [kStates][ST_FIELDS][B]; [B] nothing left to do in this pass; [B] failed the check of the first pass
+  CholFlags* flags;                        // [kOrths][B]
+  double *diag, *pivots;                   // [B][P] diagonal of the factor, [B][P / 64] smallest scaled pivots
+  double* X1;                              // an iterate of the split, then U [B][P][nP] = Pi Q^T,
+  double *cpart, *rnorm;                   // [B][P / 32][nP] partial energies, [B][P][nP / 32] of the residual's row lengths
+  IterBuffers(void* ws_, int B, int nP, int P) {
+    const size_t blk = (size_t)B * P * nP;
+    Yt = (double*)ws_;
+    Zt = Yt + blk;
+    Om = Zt + blk;
+    S = Om + (size_t)P * nP;
+    H = S + (size_t)B * P * P;
+    D = H + (size_t)B * P * P;
+    Pi = D + (size_t)B * P * NB;
+    scratch = (void*)(((uintptr_t)(Pi + (size_t)B * P * P) + 255) & ~(uintptr_t)255);
+    plan = (IterPlan*)((char*)scratch + split_scratch_bytes(B, P));
+    states = (int*)(plan + B);
+    left = states + (size_t)kStates * ST_FIELDS * B;
+    failed = left + B;
+    flags = (CholFlags*)(failed + B);
+    diag = (double*)(((uintptr_t)(flags + (size_t)kOrths * B) + 255) & ~(uintptr_t)255);
+    pivots = diag + (size_t)B * P;
+    X1 = (double*)(((uintptr_t)(pivots + (size_t)B * (P / NB)) + 255) & ~(uintptr_t)255);
+    cpart = X1 + blk;
+    rnorm = cpart + (size_t)B * (P / kSymTile) * nP;
+  }
+};
 
 }  // namespace
 
@@ -817,6 +859,33 @@ int subspace_product_launches() {
   return n;
 }
 
+hipError_t launch_lowrank_prepare(int* status, void* ctl, size_t words, double* A, int B, int n, int nP, int P, void* ws, hipStream_t st) {
+  if (n > nP || B < 1) return hipErrorInvalidValue;
+  PrepareArgs q = {};
+  q.status = status;
+  q.ctl = (int*)ctl;
+  q.words = ctl ? (long)words : 0;
+  q.A = A;
+  q.pad = (long)nP * nP - (long)n * n;
+  q.B = B; q.n = n; q.nP = nP;
+  if (P > 0) {
+    const IterBuffers w(ws, B, nP, P);
+    q.om = w.Om;
+    q.omega = (long)P * nP;
+    q.plan = w.plan;
+    q.state = w.states;
+    q.left = w.left;
+    q.failed = w.failed;
+    q.flags = (int*)w.flags;
+    q.flag_words = (long)kOrths * B * (long)(sizeof(CholFlags) / sizeof(int));
+  }
+  long most = q.pad * B;
+  for (long k : {q.omega, q.words, q.flag_words, (long)B}) most = k > most ? k : most;
+  const long blocks = (most + 255) / 256;
+  hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, q);
+  return hipGetLastError();
+}
+
 hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, int P, void* ws_, int* ok,
                                  float* c, hipEvent_t probe_begin, hipEvent_t probe_end, hipStream_t st) {
   if (P == 0) {
@@ -835,27 +904,11 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     static PerDeviceInt raised;
     if ((e0 = ensure_dynamic_lds(raised, (const void*)orth_kernel, kCholLds)) != hipSuccess) return e0;
   }
-  char* ws = (char*)ws_;
-  const size_t blk = (size_t)B * P * nP * 8;
-  double* Yt = (double*)ws;
-  double* Zt = (double*)(ws + blk);
-  double* Om = (double*)(ws + 2 * blk);
-  double* S = (double*)(ws + 2 * blk + (size_t)P * nP * 8);
-  double* H = S + (size_t)B * P * P;
-  double* D = H + (size_t)B * P * P;
-  double* Pi = D + (size_t)B * P * NB;                                                      // [B][P][P] the projector
-  void* scratch = (void*)(((uintptr_t)(Pi + (size_t)B * P * P) + 255) & ~(uintptr_t)255);
-  IterPlan* plan = (IterPlan*)((char*)scratch + split_scratch_bytes(B, P));                  // [B]
-  int* states = (int*)(plan + B);                                                           // [kStates][ST_FIELDS][B]
-  int* left = states + (size_t)kStates * ST_FIELDS * B;                                     // [B] nothing left to do in this pass
-  int* failed = left + B;                                                                   // [B] failed the check of the first pass
-  CholFlags* flags = (CholFlags*)(failed + B);                                              // [kOrths][B]
-  double* diag = (double*)(((uintptr_t)(flags + (size_t)kOrths * B) + 255) & ~(uintptr_t)255);   // [B][P] diagonal of the factor
-  double* pivots = diag + (size_t)B * P;                                                    // [B][P / 64] smallest scaled pivots
-  double* X1 = (double*)(((uintptr_t)(pivots + (size_t)B * (P / NB)) + 255) & ~(uintptr_t)255);  // an iterate of the split, then
-  double* U = X1;                                                                           // [B][P][nP] Pi Q^T,
-  double* cpart = U + (size_t)B * P * nP;                                                   // [B][P / 32][nP] partial energies
-  double* rnorm = cpart + (size_t)B * (P / kSymTile) * nP;                                  // [B][P][nP / 32] of the residual's row lengths
+  const IterBuffers w(ws_, B, nP, P);
+  double *Yt = w.Yt, *Zt = w.Zt, *S = w.S, *H = w.H, *D = w.D, *Pi = w.Pi, *U = w.X1, *diag = w.diag, *pivots = w.pivots;
+  IterPlan* plan = w.plan;
+  int *states = w.states, *left = w.left;
+  CholFlags* flags = w.flags;
   hipError_t e;
 
   const long other = (long)B * P * nP;       // from buffer 0 of the blocks to buffer 1
@@ -915,11 +968,11 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, X1, scratch, left, pass_no == 1 ? nullptr : failed, st)) != hipSuccess) return e;
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, w.X1, w.scratch, left, pass_no == 1 ? nullptr : w.failed, st)) != hipSuccess) return e;
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;
-      g.A = Pi; g.B = Yt; g.C = U; g.D = Zt; g.dots = cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP;
+      g.A = Pi; g.B = Yt; g.C = U; g.D = Zt; g.dots = w.cpart; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP;
       g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * nP;
       g.sel = sel; g.selB = other; g.selD = -other;
       g.skip = left; g.skip_if = 0;
@@ -928,28 +981,28 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     // row lengths of the residual Pi Q^T G - H U
     {
       GemmArgs g;
-      g.A = Pi; g.B = Zt; g.A2 = H; g.B2 = U; g.C = rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / kSymTile;
+      g.A = Pi; g.B = Zt; g.A2 = H; g.B2 = U; g.C = w.rnorm; g.M = P; g.N = nP; g.K = P; g.lda = P; g.ldb = nP; g.ldc = nP / kSymTile;
       g.batch = B; g.strideA = (long)P * P; g.strideB = (long)P * nP; g.strideC = (long)P * (nP / kSymTile);
       g.sel = sel; g.selB = -other;
       g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_rownorm_dual(g, st)) != hipSuccess) return e;
     }
-    return launch_split_finish(H, Pi, rnorm, nP / kSymTile, cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, scratch, left, ok, pass_no, c, st);
+    NextPass next = {};
+    if (pass_no == 1)
+      next = {state(kStates1), left, w.failed, &plan->redo, (int*)flags, state(kStates1 - 1), (int)(sizeof(IterPlan) / sizeof(int)), kBlocks2 + 1,
+              (int)(sizeof(CholFlags) / sizeof(int))};
+    return launch_split_finish(H, Pi, w.rnorm, nP / kSymTile, w.cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, w.scratch, left, ok, pass_no, c, next, st);
   };
-  const dim3 ig((unsigned)((B + 3) / 4));          // 130 words of flags per image and factorisation
-
   // start block: Omega G
-  hipLaunchKernelGGL(omega_kernel, dim3((unsigned)(((long)P * nP + 255) / 256)), dim3(256), 0, st, Om, P, n, nP);
   if (probe_begin && (e = hipEventRecord(probe_begin, st)) != hipSuccess) return e;
   {
     GemmArgs g;
-    g.A = Om; g.B = G; g.C = Yt; g.M = P; g.N = nP; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = nP;
+    g.A = w.Om; g.B = G; g.C = Yt; g.M = P; g.N = nP; g.K = nP; g.lda = nP; g.ldb = nP; g.ldc = nP;
     g.batch = B; g.strideA = 0; g.strideB = (long)nP * nP; g.strideC = (long)P * nP;
     g.epilogue = EPI_STORE_F64;
     if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
   }
   if (probe_end && (e = hipEventRecord(probe_end, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(0), (const int*)nullptr, (const int*)ok, plan, left, failed, B, flags, kOrths);
   for (int k = 0; k < kBlocks; ++k) {
     if ((e = cholqr(k, kSlots[k], k == 0, 1, k == kBlocks - 1)) != hipSuccess) return e;
     if ((e = block(k + 1, kSlots[k])) != hipSuccess) return e;
@@ -957,8 +1010,6 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   if ((e = finish(kBlocks, 1)) != hipSuccess) return e;
   // images whose subspace is not there yet (slower decay of the spectrum than the blocks of the first pass allow for) take
   // one or two more; for the others every kernel of this pass returns at once
-  hipLaunchKernelGGL(begin_pass_kernel, ig, dim3(256), 0, st, state(kStates1), (const int*)state(kStates1 - 1), (const int*)ok, plan, left, failed, B,
-                     flags, kBlocks2 + 1);
   for (int k = 0; k < kBlocks2; ++k) {
     if ((e = cholqr(kStates1 + k, kSlots2[k], false, 2, k == kBlocks2 - 1)) != hipSuccess) return e;
     if ((e = block(kStates1 + k + 1, kSlots2[k])) != hipSuccess) return e;
