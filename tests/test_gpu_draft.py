@@ -66,6 +66,23 @@ def test_draft_gate_fanouts(f0, rho):
     _check(d["zd"], d["tok"], I.BF16, f0, rho, 0.5, m, g, c)
 
 
+@pytest.mark.parametrize("chunks,f0", [(64, 32), (64, 1), (33, 16), (17, 15), (1, 32)])
+@pytest.mark.parametrize("where", ["one", "spread"])
+def test_draft_gate_merges_the_chunks_lists(chunks, f0, where):
+    """The merge of the chunks' sorted lists at its edges: as many chunks as it has lanes, list lengths about a power of two, one chunk that
+    supplies every candidate and candidates dealt over all chunks."""
+    V, K = 8192 * chunks - 8, f0 + 1
+    d = I.make_verify_batch(1, 2, V, I.FP32, seed=chunks + f0)
+    rng = np.random.default_rng(f0)
+    for t in range(2):
+        first = 8192 * int(rng.integers(chunks)) if where == "one" else 0
+        words = first + np.sort(rng.choice(min(8192, V - first) if where == "one" else V, K, replace=False))
+        top = float(d["zd"][0, t].max()) + 1.0                  # above every other logit, at different distances
+        d["zd"][0, t, rng.permutation(words)] = (top + 0.05 * np.arange(K)).astype(np.float32)
+    m, g, c = _run(d["zd"], d["tok"], I.FP32, f0, 0.9, 0.9)
+    _check(d["zd"], d["tok"], I.FP32, f0, 0.9, 0.9, m, g, c)
+
+
 def test_draft_gate_margin_only():
     d = I.make_verify_batch(4, 3, 8192 + 4096, I.BF16, seed=3)
     m, g, c = _run(d["zd"], d["tok"], I.BF16, 0, 0.5, 0.4)
