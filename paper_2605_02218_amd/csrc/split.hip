@@ -290,13 +290,24 @@ __device__ __forceinline__ void split_window(const double* __restrict__ H, int P
 }
 
 // wide: every image has a window of SN rows; else those with again[b] != 0 (optional), the others 64
+// X0, X1, Y (optional): the buffers of sign_small_kernel, which finds its words at zero.
 __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int B, int r, bool wide, double* __restrict__ off,
                                                     double* __restrict__ link, SplitCtl* ctl, const int* __restrict__ skip,
-                                                    const int* __restrict__ again) {
+                                                    const int* __restrict__ again, double* X0, double* X1, double* Y) {
   __shared__ double rd[4096];
   if (blockIdx.x >= (unsigned)B) {
     const int per = P / 16, at = blockIdx.x - B, img = at / per;
-    if (!(skip && skip[img])) row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
+    if (skip && skip[img]) return;
+    if (X0) {
+      const long from = img * stride + 16l * (at - img * per) * P;
+      const f64x2_t zero = (f64x2_t){0.0, 0.0};
+      for (int k = threadIdx.x; k < 8 * P; k += 256) {
+        *(f64x2_t*)(X0 + from + 2 * k) = zero;
+        *(f64x2_t*)(X1 + from + 2 * k) = zero;
+        *(f64x2_t*)(Y + from + 2 * k) = zero;
+      }
+    }
+    row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
     return;
   }
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -375,6 +386,36 @@ __device__ __forceinline__ void tile_of(int t, int& i, int& j) {      // t-th ti
   j = t - q * (q + 1) / 2;
 }
 
+// Rows that are wanted as they are (those before the returned one, a multiple of 64), and the norm of the rest: the same in every
+// workgroup of the image.  red: WAVES doubles of LDS.
+template <int WAVES>
+__device__ __forceinline__ int leading_rows(const double* __restrict__ Hb, const double* __restrict__ off, const double* __restrict__ link, int P, int r,
+                                            bool ordered, double mu, double* red, double& norm) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  int a = 0;
+  if (ordered) {
+    int bad = r - 32;                                // first row that couples across the cut
+    for (int p = tid; p < r - 32; p += 64 * WAVES)
+      if (!(link[p] < 1.0 && 0.5 * Hb[(long)p * P + p] > mu)) bad = p < bad ? p : bad;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { const int t = __shfl_xor(bad, o, 64); bad = t < bad ? t : bad; }
+    if (lane == 0) red[wv] = (double)bad;
+    __syncthreads();
+    double m = red[0];
+    for (int w = 1; w < WAVES; ++w) m = fmin(m, red[w]);
+    a = m < 64.0 ? 0 : (int)m / 64 * 64;
+    __syncthreads();
+  }
+  norm = 0.0;
+  for (int p = a + tid; p < P; p += 64 * WAVES) norm = fmax(norm, fabs(Hb[(long)p * P + p]) + off[p]);
+  norm = wave_max(norm);
+  if (lane == 0) red[wv] = norm;
+  __syncthreads();
+  for (int w = 0; w < WAVES; ++w) norm = fmax(norm, red[w]);
+  __syncthreads();
+  return a;
+}
+
 // The whole iteration of all images: workgroup (image, slot) owns the tiles slot, slot + W, ... on and below the
 // diagonal and stores each also transposed; the workgroups of an image meet after every product.  (Image, slot)
 // pairs are handed out by a ticket counter, so that resident workgroups always form whole images plus at most one
@@ -406,31 +447,8 @@ __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel
   const int b = ticket / W, slot = ticket - b * W;
   SplitCtl* cb = ctl + b;
   if (cb->state != 0) return;                        // set before the launch; nobody of this image writes it before all have read it
-  // rows that are wanted as they are (those before a), and the norm of the rest: the same in every workgroup
-  int a = 0;
-  double norm = 0.0;
-  {
-    const double *Hd = H + b * (long)P * P, *offb = off + (long)b * P, *linkb = link + (long)b * P;
-    if (ordered) {
-      int bad = r - 32;                              // first row that couples across the cut
-      for (int p = tid; p < r - 32; p += 256 * KS)
-        if (!(linkb[p] < 1.0 && 0.5 * Hd[(long)p * P + p] > cb->mu)) bad = p < bad ? p : bad;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) { const int t = __shfl_xor(bad, o, 64); bad = t < bad ? t : bad; }
-      if (lane == 0) s_dev[wv] = (double)bad;
-      __syncthreads();
-      double m = s_dev[0];
-      for (int w = 1; w < 4 * KS; ++w) m = fmin(m, s_dev[w]);
-      a = m < 64.0 ? 0 : (int)m / 64 * 64;
-      __syncthreads();
-    }
-    for (int p = a + tid; p < P; p += 256 * KS) norm = fmax(norm, fabs(Hd[(long)p * P + p]) + offb[p]);
-    norm = wave_max(norm);
-    if (lane == 0) s_dev[wv] = norm;
-    __syncthreads();
-    for (int w = 0; w < 4 * KS; ++w) norm = fmax(norm, s_dev[w]);
-    __syncthreads();
-  }
+  double norm;
+  const int a = leading_rows<4 * KS>(H + b * (long)P * P, off + (long)b * P, link + (long)b * P, P, r, ordered, cb->mu, s_dev, norm);
   if (!(cb->half > kMinGap * norm && norm < 1e300)) return;      // no usable gap: the image gets no projector
   const int ns = (P - a) / TT, ntiles = ns * (ns + 1) / 2;
   const int nact = ntiles < W ? ntiles : W;
@@ -606,6 +624,201 @@ __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel
   if (slot == 0 && tid == 0) cb->state = done ? 2 : 3;   // every workgroup of the image has read it (behind a barrier, or gave up)
 }
 
+// The iteration of small matrices (P <= 64 kSmallBlocks): a workgroup per 16 x 16 tile on and below the diagonal, its waves a quarter of k
+// each, and no meetings: what a workgroup hands on carries the number of its version in the lowest bit of every element, and the
+// others read an element until it is the one they want.
+//   Version v goes to buffer v % 3, its elements' lowest bits are 1, 0, 1, .. with each use of the buffer (cleared before the launch).  A
+//   workgroup reads version v - 1 of the tiles in its rows (and columns) to form its part of version v; the left operand of the second
+//   product of a step, X, is still in its registers.  So whoever reads a tile's version v - 3 is through with it before version v of
+//   the tile is formed; and a workgroup stores version v when the stores of v - 1 have been acknowledged, so that nobody who has
+//   anything of version v can still find the words of v - 3 elsewhere.  The operands are loaded past the L2s, which are not coherent.
+//   The bit is the rounding of an element to 52 bits, 1e-16 of it; the sums are good to 1e-15.
+// Only the steps that may be the last, by the lower bound l, meet at the barrier: they are when no element moved by more than 1e-7.
+// Bound by latency: store, load, 3 MFMAs a group of 16 k and wave, four partial sums.  us per product with 32 x 32 tiles and a barrier in
+// global memory after each (store, acknowledge, count, see the count, load) and here: one image of order 192 7.0 and 3.4 (155 and 76 in all),
+// four 7.1 and 5.3, one of 128 5 and 2.8 (115 and 63).
+constexpr int kSmallBlocks = 4;
+constexpr int kLoadAgent = 16;                       // buffer loads: sc1, past the L2
+
+__device__ __forceinline__ double tagged(double v, unsigned tag) {
+  return __hiloint2double(__double2hiint(v), (int)(((unsigned)__double2loint(v) & ~1u) | tag));
+}
+
+// BLOCKS = P / 64.
+template <int BLOCKS>
+__global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(const double* __restrict__ H, double* X0, double* Y, double* X1, int P, int r,
+                                                            const double* __restrict__ off, const double* __restrict__ link, bool ordered, int W,
+                                                            SplitCtl* ctl, long long limit_ticks) {
+  __shared__ double part[2][4][16][17];
+  __shared__ double s_dev[4];
+  __shared__ int s_flag, s_fail;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
+  if (tid == 0) { s_flag = (int)atomicAdd(&ctl[0].ticket, 1u); s_fail = 0; }
+  __syncthreads();
+  const int ticket = __builtin_amdgcn_readfirstlane(s_flag);
+  __syncthreads();                                   // s_flag is reused by the barriers
+  const int b = ticket / W, slot = ticket - b * W;
+  SplitCtl* cb = ctl + b;
+  if (cb->state != 0) return;                        // set before the launch; nobody of this image writes it before all have read it
+  const long pp = (long)P * P;
+  const double* Hb = H + b * pp;
+  double norm;
+  const int a = leading_rows<4>(Hb, off + (long)b * P, link + (long)b * P, P, r, ordered, cb->mu, s_dev, norm);
+  if (!(cb->half > kMinGap * norm && norm < 1e300)) return;      // no usable gap: the image gets no projector
+  const int ns = (P - a) >> 4, nact = ns * (ns + 1) / 2;
+  if (slot >= nact) return;
+  int ti, tj;
+  tile_of(slot, ti, tj);
+  const int rt = (a >> 4) + ti, ct = (a >> 4) + tj;
+  // the lift and the steps, as in sign_kernel
+  double m = cb->mu / norm, l = cb->half / norm;
+  const bool lift = m < kLiftTo;
+  const double mu = lift ? 0.0 : cb->mu, inv = 1.0 / (lift ? norm : fmax(norm - mu, mu));
+  if (!lift) l = cb->half * inv;
+  double* buf[3] = {X0 + b * pp, X1 + b * pp, Y + b * pp};       // version v is in buf[0], then they move on
+  __amdgpu_buffer_rsrc_t rs[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) rs[k] = __builtin_amdgcn_make_buffer_rsrc((void*)buf[k], (short)0, (int)(pp * 8), 0x00020000);
+
+  // this thread's element of the tile in fragment order, and the one it has of the tile across the diagonal
+  const int ei = (tid >> 1) & 15, ek = ((tid >> 7) << 3) | ((tid & 1) << 2) | ((tid >> 5) & 3);
+  const bool diagonal = rt == ct;
+  const int ui = diagonal && ek > ei ? ek : ei, uk = diagonal && ek > ei ? ei : ek;      // what is above the diagonal is what is below
+  unsigned version = 0;
+  bool alive = true;
+  auto publish = [&](double& x, double& y) {         // the next version
+    const unsigned tag = ((version / 3) & 1) ^ 1;
+    x = tagged(x, tag);
+    y = tagged(y, tag);
+    double* M = version % 3 == 0 ? buf[0] : version % 3 == 1 ? buf[1] : buf[2];
+    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the version before
+    store_through(M + tile16(rt, ct, P) + tid, x);
+    if (!diagonal) store_through(M + tile16(ct, rt, P) + tid, y);
+    ++version;
+  };
+  const int nc = ns >> 2;                            // groups of 16 k of a wave
+  // The wave's groups of row tiles rt (both: f[0]) and ct (f[1]) of the last version.
+  f64x2_t f[2][BLOCKS][2];
+  auto fetch = [&](bool both) {
+    const unsigned v = version - 1, tag = ((v / 3) & 1) ^ 1;
+    const __amdgpu_buffer_rsrc_t M = v % 3 == 0 ? rs[0] : v % 3 == 1 ? rs[1] : rs[2];
+    const int base[2] = {(int)(tile16(rt, (a >> 4) + wv * nc, P) * 8) + 16 * lane, (int)(tile16(ct, (a >> 4) + wv * nc, P) * 8) + 16 * lane};
+    long long t0 = 0;
+    const unsigned groups = (1u << nc) - 1;
+    unsigned todo = groups << BLOCKS | (both ? groups : 0);
+    for (int tries = 0; todo != 0; ++tries) {
+      asm volatile("" ::: "memory");                 // loads anew
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int c = 0; c < BLOCKS; ++c)
+          if (todo >> (BLOCKS * q + c) & 1) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              f[q][c][h] = __builtin_bit_cast(f64x2_t, __builtin_amdgcn_raw_buffer_load_b128(M, base[q] + c * (kFragTile * 8) + 1024 * h, 0, kLoadAgent));
+          }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int c = 0; c < BLOCKS; ++c)
+          if (todo >> (BLOCKS * q + c) & 1) {
+            const f64x2_t u = f[q][c][0], w = f[q][c][1];
+            const int all = __double2loint(u[0]) & __double2loint(u[1]) & __double2loint(w[0]) & __double2loint(w[1]);
+            const int some = __double2loint(u[0]) | __double2loint(u[1]) | __double2loint(w[0]) | __double2loint(w[1]);
+            if (!__any(((tag ? ~all : some) & 1) != 0)) todo &= ~(1u << (BLOCKS * q + c));
+          }
+      if (todo != 0 && (tries & 63) == 63) {         // 64 tries: some 60 us
+        if (tries == 63) t0 = wall_clock64();
+        if (__hip_atomic_load(&cb->bar.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > limit_ticks) {
+          if (lane == 0) s_fail = 1;
+          break;
+        }
+      }
+    }
+  };
+  int parity = 0;
+  // partial sums of the product of the groups; false: gave up
+  auto product = [&]() {
+    f64x4_t acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < BLOCKS; ++c)
+      if (c < nc) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(f[0][c][k >> 1][k & 1], f[1][c][k >> 1][k & 1], acc, 0, 0, 0);
+      }
+    parity ^= 1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[parity][wv][4 * v + kq][i16] = acc[v];
+    __syncthreads();
+    return s_fail == 0;
+  };
+  auto sum = [&](int i, int k) { return (part[parity][0][i][k] + part[parity][1][i][k]) + (part[parity][2][i][k] + part[parity][3][i][k]); };
+
+  double x, y;                                       // this thread's elements of X
+  {
+    auto start = [&](int i, int j) { return ((i < j ? Hb[(long)i * P + j] : Hb[(long)j * P + i]) - (i == j ? mu : 0.0)) * inv; };
+    x = start(16 * rt + ei, 16 * ct + ek);           // the element above the diagonal serves for both
+    y = start(16 * ct + ei, 16 * rt + ek);
+  }
+  publish(x, y);
+#pragma unroll 1
+  while (alive && m < kLiftTo) {
+    const double top = 3.0 * m, al = 4.0 / (1.0 + top), be = al / (1.0 + top);
+    const double cut = m * (al - be * m), gap = l * (al - be * (2.0 * m + l));
+    const bool last = cut >= kLiftTo;                // then also shifted and scaled to [-1, 1]
+    const double shift = last ? cut : 0.0, sc = last ? 1.0 / (1.0 - cut) : 1.0;
+    fetch(true);
+    if (!(alive = product())) break;
+    x = (fma(al, x, -be * sum(ui, uk)) - (diagonal && ei == ek ? shift : 0.0)) * sc;
+    y = fma(al, y, -be * sum(ek, ei)) * sc;
+    publish(x, y);
+    m = cut;
+    l = gap * sc;
+  }
+  bool done = false;
+  unsigned int target = 0;
+#pragma unroll 1
+  for (int step = 0; alive && !done && step < kMaxSignSteps; ++step) {
+    const double s = sqrt(3.0 / (1.0 + l + l * l)), c1 = 1.5 * s, c3 = -0.5 * s * s * s;
+    fetch(true);
+    if (!(alive = product())) break;
+    double sx = sum(ui, uk), sy = sum(ek, ei);       // Y = X X
+    publish(sx, sy);
+    fetch(false);
+    if (!(alive = product())) break;
+    const double nx = fma(c3, sum(ui, uk), c1 * x), ny = fma(c3, sum(ek, ei), c1 * y);     // c1 X + c3 X Y
+    const double moved = fabs(nx - x);
+    x = nx;
+    y = ny;
+    publish(x, y);
+    l = fmin(1.0, c1 * l + c3 * l * l * l);
+    if (l > 1.0 - 1e-6) {
+      double dev = !(moved == moved) ? INFINITY : moved;
+      dev = wave_max(dev);
+      if (lane == 0) s_dev[wv] = dev;
+      __syncthreads();
+      if (tid == 0)
+        atomicMax(&cb->dev[step], (unsigned long long)__double_as_longlong(fmax(fmax(s_dev[0], s_dev[1]), fmax(s_dev[2], s_dev[3]))));
+      target += nact;
+      if (!(alive = image_barrier_wait<false>(&cb->bar, target, &s_flag, limit_ticks))) break;
+      // near its limit the iteration squares the error: an entry that moved by 1e-7 is 1e-14 away afterwards
+      done = __longlong_as_double((long long)__hip_atomic_load(&cb->dev[step], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < 1e-7;
+    }
+  }
+  if (done) {
+    // the projector, row-major; nobody reads the buffers any more
+    double* Yb = Y + b * pp;
+    const int i = 16 * rt + ei, j = 16 * ct + ek;
+    Yb[(long)i * P + j] = 0.5 * (x + (i == j ? 1.0 : 0.0));
+    if (!diagonal) Yb[(long)(16 * ct + ei) * P + 16 * rt + ek] = 0.5 * y;
+    for (int p = slot; p < P; p += nact)             // the rows and columns before a: identity
+      for (int q = tid; q < (p < a ? P : a); q += 256) Yb[(long)p * P + q] = p == q ? 1.0 : 0.0;
+  } else if (!alive && tid == 0) {
+    __hip_atomic_store(&cb->bar.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (slot == 0 && tid == 0) cb->state = done ? 2 : 3;   // every workgroup of the image has read it (behind a barrier, or gave up)
+}
+
 // A workgroup that gave up has not stored its part, whatever slot 0 went on to report.
 __device__ __forceinline__ bool projector_valid(const SplitCtl* cb) { return cb->state == 2 && cb->bar.failed == 0; }
 
@@ -727,7 +940,26 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   if (W < 1) return hipErrorInvalidValue;
   const long stride = (long)P * P;
   const dim3 sg((unsigned)(B + B * (P / 16)));
-  hipLaunchKernelGGL(split_kernel, sg, dim3(256), 0, st, H, P, stride, B, r, !ordered, off, link, ctl, skip, again);
+  // The small kernel, whose workgroups load two rows of 16 x P each past the L2s: while that is 28 MB a product.  us per call of
+  // covspec_select, sign_kernel / small, by images: order 128 12 278 / 238, 16 274 / 251, 25 295 / 295; order 192 4 534 / 482, 7 574 / 561,
+  // 9 610 / 602, 12 648 / 668; order 256 1 690 / 509 and 2 712 / 577 (with the earlier Cholesky), 4 851 / 902, 7 967 / 1098.  And an
+  // image's workgroups, a tile each, have to be as few as above.
+  const long n16 = P / 16, t16 = n16 * (n16 + 1) / 2;
+  bool small = form == 0 && P <= 64 * kSmallBlocks && B * t16 * 2 * 16 * P * 8 <= 28000000;
+  if (small) {
+    static PerDeviceInt resident;
+    int held = 0;
+    if ((e = resident_workgroups(resident, sign_small_kernel<kSmallBlocks>, 256, 0, &held)) != hipSuccess) return e;      // the others need less
+    small = t16 <= held / 8;
+  }
+  hipLaunchKernelGGL(split_kernel, sg, dim3(256), 0, st, H, P, stride, B, r, !ordered, off, link, ctl, skip, again, small ? X0 : nullptr, X1, Y);
+  if (small) {
+    static_assert(kSmallBlocks == 4, "");
+    auto sk = n64 == 1 ? sign_small_kernel<1> : n64 == 2 ? sign_small_kernel<2> : n64 == 3 ? sign_small_kernel<3> : sign_small_kernel<4>;
+    hipLaunchKernelGGL(sk, dim3((unsigned)(B * t16)), dim3(256), 0, st, H, X0, Y, X1, P, r, (const double*)off, (const double*)link,
+                       ordered, (int)t16, ctl, barrier_limit_ticks());
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(kern, dim3((unsigned)(B * W)), dim3(form == 1 ? 512 : 256), lds, st, H, X0, Y, X1, P, r, (const double*)off, (const double*)link,
                      ordered, (int)W, ctl, barrier_limit_ticks());
   return hipGetLastError();

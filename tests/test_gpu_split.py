@@ -62,6 +62,43 @@ def test_energies_match_the_oracle(C, name):
         np.testing.assert_array_equal(idx[b], ref["idx"])
 
 
+# The sign iteration of small matrices without meetings (split.hip) at its edges, and the one with meetings beyond: batch, tokens,
+# width, rank, decay, way.  Order 64, 128, 192 and 256, each with as many images as it takes and one more.
+SMALL_SIGN = {
+    "order-64": (40, 64, 96, 20, 0.05, 3),
+    "order-128-most": (23, 110, 128, 40, 0.05, 3),
+    "order-128-over": (24, 110, 128, 40, 0.05, 3),
+    "order-192-most": (7, 300, 320, 100, 0.02, 1),
+    "order-192-over": (8, 300, 320, 100, 0.02, 1),
+    "order-256-most": (3, 400, 420, 180, 0.02, 1),
+    "order-256-over": (4, 400, 420, 180, 0.02, 1),
+    "leading-rows-left-out": (2, 600, 640, 190, 0.02, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(SMALL_SIGN))
+def test_small_sign_iteration(C, name):
+    import torch
+    B, n, d, r, decay, path = SMALL_SIGN[name]
+    sigma = np.exp(-decay * np.arange(min(n, d)))
+    X = np.stack([I.make_spectrum_tokens(n, d, sigma, seed=b, dtype=I.FP32) for b in range(B)])
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    ws = C.alloc_workspace(p)
+    Xd, sd = torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda()
+    out = C.select(p, Xd, sd, workspace=ws)
+    assert C.lowrank_path(p, ws).tolist() == [path] * B
+    c = out["c"].cpu().numpy().astype(np.float64)
+    for _ in range(3):                    # whatever order the workgroups ran in, and whatever the buffers held before
+        assert torch.equal(C.select(p, Xd, sd, workspace=ws)["c"], out["c"])
+    for b in (0, B // 2, B - 1):
+        ref = O.select(X[b].astype(np.float64), sf[b], O.Params(preselect_m=n, rank_r=r, keep_k=n // 3))
+        # c is rounded to fp32 (6e-8); a residual of 1e-9 enters an energy at most as 1e-9 over the relative gap (>= 0.039 here), twice;
+        # energies far below the largest carry its rounding
+        err = np.abs(c[b] - ref["c"]) / np.maximum(ref["c"], 1e-6 * ref["c"].max())
+        assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
+
+
 # tokens, rank, decay of the singular values per index, factor on the four largest of them, the way the solve has to take; what
 # the block iteration's schedule has to cope with
 SCHEDULES = {
