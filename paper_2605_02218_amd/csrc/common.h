@@ -111,6 +111,44 @@ __device__ __forceinline__ void store_through(double* p, double v) { __hip_atomi
 
 constexpr long long kBarrierLimitTicks = 200000000LL;   // 2 s, the default of `limit_ticks`
 
+// ---- Handing on without a meeting: every element carries a bit in the lowest place of its mantissa (the rounding of an element to 52
+// bits) which tells whether it is the one that is waited for, and readers load past the L2s, which are not coherent, until it is.  Saves
+// the acknowledgement of the stores and a flag's way in front of the load.
+constexpr int kLoadAgent = 16;                          // buffer loads: sc1, past the L2
+__device__ __forceinline__ double tagged(double v, unsigned tag) {
+  return __hiloint2double(__double2hiint(v), (int)(((unsigned)__double2loint(v) & ~1u) | tag));
+}
+// N tiles in fragment order, tile n at off[n] bytes of `src` (a lane's offset included), as soon as all their elements carry the bit.
+// False: over the limit, or *failed is set; the elements are then whatever there was.  One wave.
+template <int N>
+__device__ __forceinline__ bool fetch_tagged(__amdgpu_buffer_rsrc_t src, const int (&off)[N], unsigned tag, f64x2_t (&out)[N][2], const int* failed,
+                                             long long limit_ticks) {
+  unsigned todo = (1u << N) - 1;
+  long long t0 = 0;
+  for (int tries = 0; todo != 0; ++tries) {
+    asm volatile("" ::: "memory");                      // loads anew
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+      if (todo >> n & 1) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) out[n][h] = __builtin_bit_cast(f64x2_t, __builtin_amdgcn_raw_buffer_load_b128(src, off[n] + 1024 * h, 0, kLoadAgent));
+      }
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+      if (todo >> n & 1) {
+        const f64x2_t u = out[n][0], v = out[n][1];
+        const int all = __double2loint(u[0]) & __double2loint(u[1]) & __double2loint(v[0]) & __double2loint(v[1]);
+        const int some = __double2loint(u[0]) | __double2loint(u[1]) | __double2loint(v[0]) | __double2loint(v[1]);
+        if (!__any(((tag ? ~all : some) & 1) != 0)) todo &= ~(1u << n);
+      }
+    if (todo != 0 && (tries & 63) == 63) {              // 64 tries: some 60 us
+      if (tries == 63) t0 = wall_clock64();
+      if (__hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > limit_ticks) return false;
+    }
+  }
+  return true;
+}
+
 // WRITE_BACK = false: everything the workgroup hands on went out in store_through() and is at the coherence point once
 // the stores are acknowledged, so the caches need no write-back.
 template <bool WRITE_BACK = true>

@@ -164,11 +164,12 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
 // Residual check and energies of a block iteration, see split.hip.  slow[b] != 0: the image was left out of the split.
 // next.state != null: state 0 of a further pass, of `fields` integers per image: images that passed the check rest (2); one that was left
 // out of the split goes on from its block, which is in the buffer that state `prev` names last, one that failed the check from the product with
-// G that followed its last orthonormalisation (redo).  And its flags are cleared.
+// G that followed its last orthonormalisation (redo), and one of which a wait ran out (failed_word of one of the sets before) rests and is not split
+// either: what its workgroups handed on is not all of one turn.  And its flags are cleared.
 struct NextPass {
-  int *state, *left, *failed, *redo, *flags;      // [4][B], [B], [B], one per `redo_step` ints, [flag_sets][B][flag_words]
+  int *state, *left, *failed, *redo, *flags;      // [5][B], [B], [B], one per `redo_step` ints, [flag_sets][B][flag_words]
   const int* prev;
-  int redo_step, flag_sets, flag_words;
+  int redo_step, flag_sets, sets_before, flag_words, failed_word;
 };
 hipError_t launch_split_finish(const double* H, const double* Pi, const double* rnorm, int rparts, const double* cpart, int cparts, int B,
                                int P, int n, int nP, int r, double tol, const void* scratch, const int* slow, int* ok, int pass_no, float* c,

@@ -638,11 +638,6 @@ __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel
 // global memory after each (store, acknowledge, count, see the count, load) and here: one image of order 192 7.0 and 3.4 (155 and 76 in all),
 // four 7.1 and 5.3, one of 128 5 and 2.8 (115 and 63).
 constexpr int kSmallBlocks = 4;
-constexpr int kLoadAgent = 16;                       // buffer loads: sc1, past the L2
-
-__device__ __forceinline__ double tagged(double v, unsigned tag) {
-  return __hiloint2double(__double2hiint(v), (int)(((unsigned)__double2loint(v) & ~1u) | tag));
-}
 
 // BLOCKS = P / 64.
 template <int BLOCKS>
@@ -849,7 +844,13 @@ __global__ __launch_bounds__(1024) void split_finish_kernel(const double* __rest
   const int b = blockIdx.x, B = gridDim.x;
   if (pass_no > 1 && ok[b]) return;                  // passed an earlier check; its energies are in place
   const bool split = !slow[b];                       // in this pass
-  if (threadIdx.x == 0) bad = 0;
+  __shared__ int gave_up;
+  if (threadIdx.x == 0) {
+    bad = gave_up = 0;
+    if (next.state)
+      for (int k = 0; k < next.sets_before; ++k) gave_up |= next.flags[((long)k * B + b) * next.flag_words + next.failed_word];
+  }
+  __syncthreads();
   if (next.state)
     for (int k = threadIdx.x; k < next.flag_sets * next.flag_words; k += 1024) {
       const int set = k / next.flag_words;
@@ -875,13 +876,14 @@ __global__ __launch_bounds__(1024) void split_finish_kernel(const double* __rest
     ok[b] = good ? pass_no : 0;
     if (next.state) {
       const int at = next.prev[3 * B + b];
-      next.state[b] = good ? 2 : 0;
+      next.state[b] = good || gave_up ? 2 : 0;
       next.state[B + b] = 0;
       next.state[2 * B + b] = at;
       next.state[3 * B + b] = at;
+      next.state[4 * B + b] = next.prev[4 * B + b];
       next.redo[(long)b * next.redo_step] = !good && split;
       next.failed[b] = !good && split;
-      next.left[b] = good;
+      next.left[b] = good || gave_up;
     }
   }
   if (!good) return;

@@ -23,6 +23,7 @@
 // G) cannot make it rank deficient.
 // The residual of the dominant subspace, Pi Q^T G - H U, is checked; images that fail (slow decay, P too small, no gap
 // at the cut) take up to two further blocks and, if they fail again, the full block Jacobi solve of G.
+#include <stddef.h>
 #include <initializer_list>
 #include "common.h"
 #include "host_cache.h"
@@ -51,11 +52,12 @@ constexpr size_t kCholLds = (size_t)2 * NB * NBP * sizeof(double);
 constexpr int kMaxBlocks = 64;         // block rows: P <= 4096
 
 // ---- The schedule of an image.  Orthonormalisations are numbered; before orthonormalisation k the kernels read state k of the
-// image, the factorisation writes state k + 1, the products behind it read that.  Four integers per image and state:
+// image, the factorisation writes state k + 1, the products behind it read that.  Five integers per image and state:
 //   ST_REST  0: takes part in the next orthonormalisation, 1: in the last one of the pass only, 2: in none of this pass
 //   ST_IDLE  minus the number of products of the block that follows
 //   ST_SEL, ST_END  the buffer its first operand is in, and the one its result is in (products alternate between the two)
-enum { ST_REST, ST_IDLE, ST_SEL, ST_END, ST_FIELDS };
+//   ST_TURN  factorisations so far: their inverted diagonal blocks carry its lowest bit (see tagged)
+enum { ST_REST, ST_IDLE, ST_SEL, ST_END, ST_TURN, ST_FIELDS };
 constexpr int kMaxDegrees = 6;
 struct IterPlan {
   double tb;      // 2 / beta, beta = the upper end of the damped interval; 0: the block's products are with G itself
@@ -204,6 +206,7 @@ __device__ __forceinline__ void plan_block(const PlanArgs& q, int b, double d1, 
   out[ST_IDLE * q.B] = -m;
   out[ST_SEL * q.B] = at;
   out[ST_END * q.B] = (at + m) & 1;
+  out[ST_TURN * q.B] = q.in[ST_TURN * q.B + b] + 1;
 }
 
 // An image that takes no part: its block stays as and where it is; at the end of a pass Q G is formed of one that is to be split.
@@ -215,6 +218,7 @@ __device__ __forceinline__ void rest_on(const PlanArgs& q, int b) {
   out[ST_IDLE * q.B] = -m;
   out[ST_SEL * q.B] = at;
   out[ST_END * q.B] = (at + m) & 1;
+  out[ST_TURN * q.B] = q.in[ST_TURN * q.B + b];
 }
 
 __device__ __forceinline__ void frag_store_through(double* tile, int lane, const f64x4_t& v) {
@@ -224,11 +228,14 @@ __device__ __forceinline__ void frag_store_through(double* tile, int lane, const
   store_through(t + 128, v[2]);
   store_through(t + 129, v[3]);
 }
+__device__ __forceinline__ f64x4_t tagged(const f64x4_t& v, unsigned tag) {
+  return (f64x4_t){covspec::tagged(v[0], tag), covspec::tagged(v[1], tag), covspec::tagged(v[2], tag), covspec::tagged(v[3], tag)};
+}
 
 // Factors a 64 x 64 block (a = L L^T) and inverts the factor, by all eight waves.  Wave 0 brings tile (0, 0) in registers, element
 // (k, i) in lane (q = k % 4, i), register k / 4; the other tiles on and below the diagonal are in LDS (`a`, pitch NBP), a barrier before
-// they are read.  inv(L) goes through the L2 to Db (its tiles on and below the diagonal, in fragment order), the diagonal of L to dl (valid
-// in wave 0).  The pivot of row k is floored at floors[k].
+// they are read.  inv(L) goes through the L2 to Db (its tiles on and below the diagonal, in fragment order, tagged), the diagonal of L to
+// dl (valid in wave 0).  The pivot of row k is floored at floors[k].
 // By 16 x 16 tiles.  A diagonal tile stays in the registers of wave 0 from the product that forms it to its inverse, four pivots at a
 // time: the 4 x 4 block at the pivots is read into scalars and factored and inverted by every lane for itself (eliminate_panel), what it
 // does to the other rows is a product of rank 4, one MFMA on the tile and one on the unit matrix that becomes the inverse.  The operand
@@ -356,14 +363,14 @@ __device__ __forceinline__ f64x4_t invert_sum(const LaneTiles& p, int t, int s) 
 }
 
 // a tile of the inverse from LDS to memory
-__device__ __forceinline__ void hand_on(const LaneTiles& p, double* Db, int t, int s) {
+__device__ __forceinline__ void hand_on(const LaneTiles& p, double* Db, int t, int s, unsigned tag) {
   const double* d = p.inv[0] + tile_off(t, s);
-  frag_store_through(Db + (4 * t + s) * kFragTile, threadIdx.x & 63, (f64x4_t){d[0], d[4], d[8], d[12]});
+  frag_store_through(Db + (4 * t + s) * kFragTile, threadIdx.x & 63, tagged((f64x4_t){d[0], d[4], d[8], d[12]}, tag));
 }
 
 // between: called by all waves with their own stores of before acknowledged, one thread of wave 7 raising a flag for it
 template <typename Between>
-__device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv, double* Db, double* dl, const double* floors, Between between) {
+__device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv, double* Db, double* dl, const double* floors, unsigned tag, Between between) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
   const int col = 7 - w;                             // waves 7, 6 and 5 have a column of the inverse each
   f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0};
@@ -392,10 +399,10 @@ __device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv,
         for (int v = 0; v < 4; ++v) z[4 * v * NBP] = o[v];
       }
       if (s == 3) {
-        if (w < 4) hand_on(p, Db, w - 1, w - 1);
-        else if (w == 4) hand_on(p, Db, 1, 0);
+        if (w < 4) hand_on(p, Db, w - 1, w - 1, tag);
+        else if (w == 4) hand_on(p, Db, 1, 0, tag);
         else {
-          if (col < 2) hand_on(p, Db, 2, col);
+          if (col < 2) hand_on(p, Db, 2, col, tag);
           sum = invert_sum(p, 3, col);
         }
       }
@@ -427,13 +434,13 @@ __device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv,
   }
   const LaneTiles p(a, inv);
   if (w == 0) {
-    hand_on(p, Db, 3, 3);
+    hand_on(p, Db, 3, 3, tag);
   } else if (w > 4) {                                // -inv_33 sum, transposed: in fragment order
     const double* d = p.inv[0] + tile_off(3, 3);
     f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(sum[j], -d[4 * j], o, 0, 0, 0);
-    frag_store_through(Db + (12 + col) * kFragTile, lane, o);
+    frag_store_through(Db + (12 + col) * kFragTile, lane, tagged(o, tag));
   }
 }
 
@@ -443,7 +450,7 @@ struct CholFlags {
   unsigned int ticket;          // next block row to hand to a starting workgroup
   int failed;                   // a workgroup gave up waiting
   int cols[kMaxBlocks];         // per block row: 1 when its part of L is in memory
-  int done[kMaxBlocks];         // its diagonal block is factored, the inverse is in memory
+  int done[kMaxBlocks];         // its diagonal and smallest pivot are in memory, and everything else of it
 };
 
 // Waits until *flag >= value; false when the wait is over its limit or another workgroup has given up.  Everything the other
@@ -478,8 +485,8 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
 // the diagonal), one 512-thread workgroup per block row of 64 and image.  The workgroup of block row i:
 //   for K < i:  T = S[i,K] - sum over K' < K of L[i,K'] L[K,K']^T;   L[i,K] = T inv(L_KK)^T, in place;   D += L[i,K] L[i,K]^T
 //   factors and inverts S[i,i] - D (factor_invert); the inverse goes to Dinv[b][i] (its tiles).
-// It waits for row K's columns before the sum and for row K's inverse before the product with it, so that the sum runs while
-// row K is being factored; rows are taken in order (a ticket per image), so that a workgroup only waits for rows that have started
+// It waits for row K's columns before the sum and for row K's inverse (its elements carry the bit of this turn) before the product with it, so
+// that the sum runs while row K is being factored; rows are taken in order (a ticket per image), so that a workgroup only waits for rows that have started
 // before it, whatever else the device is doing; every wait is bounded.  What the rows hand one another is stored through the L2.
 // Every product is formed transposed, so that its result is the fragment of the tile it goes to.
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
@@ -497,8 +504,11 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
   double* a = lds;                  // [64][65] diagonal block, see factor_invert
   double* inv = lds + NB * NBP;     // [64][65] the inverse of its factor; before: T, then L[i,K]
   __shared__ double dl[NB], diag0[NB], floors[NB];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+  __shared__ int s_gave_up;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), i16 = lane & 15, kq = lane >> 4;
   const int nblk = P / NB, per16 = P / 16;
+  const unsigned tag = ~q.in[ST_TURN * q.B + b] & 1;
+  if (tid == 0) s_gave_up = 0;                      // (a barrier before it is set)
   double* Sb = S + (long)b * P * P;
   double* Db = Dinv + (long)b * nblk * NB * NB;
   auto tile = [&](int rt, int ct) -> double* { return Sb + ((long)rt * per16 + ct) * kFragTile; };
@@ -510,9 +520,17 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
   // SIMD, one each: the factorisation begins with tile 0)
   auto low = [](int t, int& x, int& y) { x = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3; y = t - x * (x + 1) / 2; };
   auto own = [&](int e) { return e == 0 ? w : w == 2 || w == 3 ? w + 6 : 10; };
-  f64x4_t dacc[2];
+  f64x4_t dacc[2], own_tile[2];
 #pragma unroll
-  for (int e = 0; e < 2; ++e) dacc[e] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  for (int e = 0; e < 2; ++e) {
+    dacc[e] = own_tile[e] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    if (own(e) < 10) {
+      int x, y;
+      low(own(e), x, y);
+      own_tile[e] = frag_load(tile(4 * row + x, 4 * row + y), lane);
+    }
+  }
+  const __amdgpu_buffer_rsrc_t inverses = __builtin_amdgcn_make_buffer_rsrc((void*)Db, (short)0, nblk * NB * NB * 8, 0x00020000);
   const int rx = w >> 1;                                        // row tile of this wave, column tiles 2 (w & 1) + 0, 1 of the sum
   bool alive = true;
   for (int K = 0; K < row; ++K) {
@@ -548,35 +566,44 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
     for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) inv[(16 * rx + i16) * NBP + 16 * (c0 + y) + 4 * v + kq] = t[y][v];
-    if (!(alive = wait_flag(&f->done[K], 1, f, s_flag, limit_ticks))) break;
+    __syncthreads();
     // L[i,K]: this wave's column tiles are 0 and 3, or 1 and 2 (five products each)
     f64x4_t in[4], out[2];
+    f64x2_t d[5][2];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int v = 0; v < 4; ++v) in[c][v] = inv[(16 * rx + i16) * NBP + 16 * c + 4 * v + kq];
-    const int y0 = w & 1, y1 = 3 - (w & 1);
+    const int odd = w & 1, y0 = odd, y1 = 3 - odd;
     {
-      f64x4_t d0[2], d1[4];
+      int at[5];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) if (c <= y0) d0[c] = frag_load(Db + (long)K * NB * NB + (4 * y0 + c) * kFragTile, lane);
+      for (int n = 0; n < 5; ++n) {                             // tiles (y0, 0 .. y0), then (y1, 0 .. y1)
+        const int t = n <= y0 ? 4 * y0 + n : 4 * y1 + n - y0 - 1;
+        at[n] = (K * 16 + t) * (kFragTile * 8) + 16 * lane;
+      }
+      if (!fetch_tagged<5>(inverses, at, tag, d, &f->failed, limit_ticks) && lane == 0) s_gave_up = 1;
+    }
+    out[0] = out[1] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    if (odd) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) if (c <= y1) d1[c] = frag_load(Db + (long)K * NB * NB + (4 * y1 + c) * kFragTile, lane);
-      out[0] = out[1] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          out[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[2 + c][v >> 1][v & 1], in[c][v], out[1], 0, 0, 0);
+          if (c < 2) out[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[c][v >> 1][v & 1], in[c][v], out[0], 0, 0, 0);
+        }
+    } else {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        if (c <= y1) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) out[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d1[c][v], in[c][v], out[1], 0, 0, 0);
-        }
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        if (c <= y0) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) out[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d0[c][v], in[c][v], out[0], 0, 0, 0);
+        for (int v = 0; v < 4; ++v) {
+          out[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[1 + c][v >> 1][v & 1], in[c][v], out[1], 0, 0, 0);
+          if (c < 1) out[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[c][v >> 1][v & 1], in[c][v], out[0], 0, 0, 0);
         }
     }
     __syncthreads();                                            // T has been read
+    if (s_gave_up) { alive = false; break; }
     frag_store_through(tile(4 * row + rx, 4 * K + y0), lane, out[0]);
     frag_store_through(tile(4 * row + rx, 4 * K + y1), lane, out[1]);
 #pragma unroll
@@ -609,16 +636,16 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
       if (tt < 10) {
         int x, y;
         low(tt, x, y);
-        const f64x4_t c = frag_load(tile(4 * row + x, 4 * row + y), lane);
+        const f64x4_t c = own_tile[e] - dacc[e];
         if (tt == 0) {
-          x0 = c - dacc[e];
+          x0 = c;
         } else {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v] - dacc[e][v];
+          for (int v = 0; v < 4; ++v) a[(16 * x + i16) * NBP + 16 * y + 4 * v + kq] = c[v];
         }
       }
     }
-    factor_invert(x0, a, inv, Di, dl, floors, [&]() {
+    factor_invert(x0, a, inv, Di, dl, floors, tag, [&]() {
       __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0): L[row, .] has been stored
       __syncthreads();
       if (tid == 7 * kWave) __hip_atomic_store(&f->cols[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -636,7 +663,12 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
     return;
   }
   if (tid != 0) return;
-  if (alive) {                                                  // it has waited for all the other rows
+  for (int k = 0; alive && k < row; ++k) {
+    const long long t0 = wall_clock64();
+    while (alive && __hip_atomic_load(&f->done[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) alive = wall_clock64() - t0 <= limit_ticks;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (alive) {
     double pmin = 1.0;
     for (int k = 0; k < nblk; ++k) {
       const double pm = pivots[(long)b * nblk + k];
@@ -661,7 +693,10 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
 // that wrote them, two groups of 16 k ahead, as are those of L.
 // As a launch behind the factorisation, the solved blocks in registers, it took, us: 192 x 320 14.5, 192 x 1664 batch 4 19, 384 x 1152
 // batch 8 44, 256 x 640 batch 64 73; the factorisation by itself 40, 43, 87 and 71, both in one launch 45, 49, 95 and 126.
-__device__ __forceinline__ bool substitute(const double* L, const double* D, double* Y, long nP, int P, bool mine, CholFlags* f, int* s_flag, long long limit_ticks) {
+__device__ __forceinline__ bool substitute(const double* L, const double* D, double* Y, long nP, int P, bool mine, unsigned tag, CholFlags* f, int* s_flag,
+                                           long long limit_ticks) {
+  const __amdgpu_buffer_rsrc_t inverses = __builtin_amdgcn_make_buffer_rsrc((void*)D, (short)0, P / NB * NB * NB * 8, 0x00020000);
+  bool alive = true;
   const int nblk = P / NB;
   const long row_tiles = (long)(P / 16) * kFragTile;
 #pragma unroll 1
@@ -705,14 +740,14 @@ __device__ __forceinline__ bool substitute(const double* L, const double* D, dou
 #pragma unroll
       for (int x = 0; x < 4; ++x) rhs[x] = rhs[x] - acc[x];
     }
-    if (!wait_flag(&f->done[bi], 1, f, s_flag, limit_ticks)) return false;
     if (mine) {
-      const double* Db = D + (long)bi * NB * NB;
-      f64x4_t fd[4][4];
+      f64x2_t fd[10][2];                                // the inverted block is lower triangular
+      int at[10];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)                       // the inverted block is lower triangular
+      for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int x = q; x < 4; ++x) fd[q][x] = frag_load(Db + (4 * x + q) * kFragTile, 0);
+        for (int q = 0; q <= x; ++q) at[x * (x + 1) / 2 + q] = (bi * 16 + 4 * x + q) * (kFragTile * 8) + 16 * (threadIdx.x & 63);
+      alive = fetch_tagged<10>(inverses, at, tag, fd, &f->failed, limit_ticks) && alive;
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[x] = zero;
 #pragma unroll
@@ -720,14 +755,14 @@ __device__ __forceinline__ bool substitute(const double* L, const double* D, dou
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
-          for (int x = q; x < 4; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(fd[q][x][v], rhs[q][v], acc[x], 0, 0, 0);
+          for (int x = q; x < 4; ++x) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(fd[x * (x + 1) / 2 + q][v >> 1][v & 1], rhs[q][v], acc[x], 0, 0, 0);
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int v = 0; v < 4; ++v) Yb[(long)(16 * x + 4 * v) * nP] = acc[x][v];
     }
   }
-  return true;
+  return alive;
 }
 
 // The factorisation of all images and the substitution behind it.  Per image the first P / 64 workgroups to start have a block row
@@ -756,7 +791,7 @@ __global__ __launch_bounds__(512) void orth_kernel(double* S, double* __restrict
   const bool mine = w < waves && col < nP;           // nP % 64 == 0
   double* Y = Yt + (q.in[ST_END * q.B + b] ? other : 0) + (long)b * P * nP + (long)(lane >> 4) * nP + (mine ? col : 0) + (lane & 15);
   // gave up: the image's rows are not orthonormal, which the check of the residual refuses
-  if (!substitute(S + (long)b * P * P + 2 * lane, Dinv + (long)b * nblk * NB * NB + 2 * lane, Y, nP, P, mine, f, &s_flag, limit_ticks) && tid == 0)
+  if (!substitute(S + (long)b * P * P + 2 * lane, Dinv + (long)b * nblk * NB * NB, Y, nP, P, mine, ~q.in[ST_TURN * q.B + b] & 1, f, &s_flag, limit_ticks) && lane == 0)
     __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -766,8 +801,8 @@ __global__ __launch_bounds__(512) void orth_kernel(double* S, double* __restrict
 struct PrepareArgs {
   int *status, *ctl, *flags, *state, *left, *failed;
   IterPlan* plan;
-  double *A, *om;
-  long words, flag_words, pad, omega;      // numbers of elements; pad: of one matrix
+  double *A, *om, *inverses;
+  long words, flag_words, pad, omega, blocks;      // numbers of elements; pad: of one matrix
   int B, n, nP;
 };
 __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
@@ -784,6 +819,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
     const long b = i / q.pad, e = i - b * q.pad;
     q.A[b * q.nP * q.nP + (e < right ? (e / w) * q.nP + q.n + e % w : (long)q.n * q.nP + (e - right))] = 0.0;
   }
+  for (long i = at; i < q.blocks; i += step) q.inverses[i] = 0.0;
   for (long i = at; i < q.words; i += step) q.ctl[i] = 0;
   for (long i = at; i < q.flag_words; i += step) q.flags[i] = 0;
   for (long b = at; b < q.B; b += step) {
@@ -872,6 +908,8 @@ hipError_t launch_lowrank_prepare(int* status, void* ctl, size_t words, double* 
     const IterBuffers w(ws, B, nP, P);
     q.om = w.Om;
     q.omega = (long)P * nP;
+    q.inverses = w.D;
+    q.blocks = (long)B * P * NB;
     q.plan = w.plan;
     q.state = w.states;
     q.left = w.left;
@@ -880,7 +918,7 @@ hipError_t launch_lowrank_prepare(int* status, void* ctl, size_t words, double* 
     q.flag_words = (long)kOrths * B * (long)(sizeof(CholFlags) / sizeof(int));
   }
   long most = q.pad * B;
-  for (long k : {q.omega, q.words, q.flag_words, (long)B}) most = k > most ? k : most;
+  for (long k : {q.omega, q.blocks, q.words, q.flag_words, (long)B}) most = k > most ? k : most;
   const long blocks = (most + 255) / 256;
   hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, q);
   return hipGetLastError();
@@ -990,7 +1028,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
     NextPass next = {};
     if (pass_no == 1)
       next = {state(kStates1), left, w.failed, &plan->redo, (int*)flags, state(kStates1 - 1), (int)(sizeof(IterPlan) / sizeof(int)), kBlocks2 + 1,
-              (int)(sizeof(CholFlags) / sizeof(int))};
+              kOrths, (int)(sizeof(CholFlags) / sizeof(int)), (int)(offsetof(CholFlags, failed) / sizeof(int))};
     return launch_split_finish(H, Pi, w.rnorm, nP / kSymTile, w.cpart, P / kSymTile, B, P, n, nP, r, kRitzTol, w.scratch, left, ok, pass_no, c, next, st);
   };
   // start block: Omega G
