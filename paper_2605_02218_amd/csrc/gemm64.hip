@@ -10,7 +10,7 @@
 // Four kernels:
 //   gemm64_kernel        any of the storage types, row lists, any K and alignment: 64 x 64 tiles, operands converted to fp64 on
 //                        their way through registers into LDS.
-//   gemm64_dma_kernel    fp64 x fp64 (the block iteration) and bf16 x bf16: direct-to-LDS loads, tiles of 64 x 64 to 32 x 32.
+//   gemm64_dma_kernel    fp64 x fp64 (the block iteration) and bf16 x bf16: direct-to-LDS loads, tiles of 64 x 96 to 32 x 32.
 //   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
 //   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
 // gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
@@ -214,9 +214,9 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 // multiplied.  KS = 2: a second group of four waves takes the other half of k in a ring of its own and the halves are added at the
 // end, for problems with no more tiles than compute units, where one wave per SIMD cannot hide its own waits.
 // Bound by the fp64 MFMA: a 64 x 64 tile keeps a compute unit busy for K / 32 us, so what decides is how evenly the tiles go into the
-// compute units (launch_plain).  us, tiles of 64 x 64 / 64 x 32 / 32 x 32, and the time at the rate of a loop of nothing but
-// these MFMAs (67.6 TFLOP/s): 192 x 1664 x 1664, batch 4 114 / 91 / 88 (63); 384 x 1152 x 1152, batch 8 159 / 149 / 166 (121);
-// 256 x 640 x 640, batch 64 235 / 260 / 277 (199); 192 x 1280 x 1280, batch 4 50 / 50 / 54 (37).
+// compute units (launch_plain).  us with the tiles chosen there, and the time at the rate of a loop of nothing but these MFMAs (67.6
+// TFLOP/s): 192 x 1664 x 1664, batch 4 72 (63; on tiles of 32 x 32, which read their operands at 20 TB/s from the L2s, 83); 384 x 1152 x
+// 1152, batch 8 139 (121); 256 x 640 x 640, batch 64 213 (199); 192 x 1280 x 1280, batch 4 50 (37).
 // A symmetric product (lower_only, frag; TM = TN) has a workgroup for each tile on and below its diagonal only.
 // TS = bf16 (the Gram matrix of the greedy picks, row lists): the same 128-byte pieces of a row are 64 k, converted between LDS and
 // MFMA, which the MFMAs hide.  Staged through registers and converted into LDS, one k-tile of 16 in flight, six of
@@ -230,6 +230,9 @@ __device__ __forceinline__ double cheb_start(const GemmArgs& g, const double* A,
   return -rt * (g.cheb_step == 0 ? a : fma(0.5, C[(long)r * g.ldc + c], a));
 }
 
+// Bytes of a stage: whole loads of eight rows, as many for each wave.
+constexpr int dma_stage(int TM, int TN) { return ((TM + TN) / 8 + 3) / 4 * 4 * 1024; }
+
 // A 16-byte piece of a row and its elements as fp64.
 template <typename TS> struct Piece;
 template <> struct Piece<double> {
@@ -241,16 +244,19 @@ template <> struct Piece<bf16_t> {
   static __device__ __forceinline__ double at(const type& v, int e) { return (double)__uint_as_float(e & 1 ? v[e >> 1] & 0xFFFF0000u : v[e >> 1] << 16); }
 };
 
-template <typename TS, int KS, int TM, int TN>
+// WM: waves along the rows of the tile (the others along its columns).
+template <typename TS, int KS, int TM, int TN, int WM>
 __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  constexpr int NST = 4, STAGE = (TM + TN) * 128;   // bytes: A tile then B tile
-  constexpr int MI = TM / 32, NJ = TN / 32;         // 16 x 16 tiles of a wave, and its loads per operand and stage
+  constexpr int GROUPS = (TM + TN) / 8, LOADS = (GROUPS + 3) / 4;      // of eight rows, a load each: of a stage, and of a wave
+  constexpr int NST = 4, STAGE = dma_stage(TM, TN);                    // bytes: A tile, then B tile, then what fills up the waves' loads
+  constexpr int WN = 4 / WM, MI = TM / (16 * WM), NJ = TN / (16 * WN); // 16 x 16 tiles of a wave
+  static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && TM % 8 == 0, "");
   constexpr int PE = 16 / sizeof(TS), KT = 8 * PE;  // elements of a piece and of a k-tile
   constexpr bool F64 = std::is_same<TS, double>::value;
   typedef typename Piece<TS>::type piece_t;
   extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
   const int tid = threadIdx.x & 255, grp = threadIdx.x >> 8, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, i16 = lane & 15, kq = lane >> 4;
+  const int wm = wave / WN, wn = wave % WN, i16 = lane & 15, kq = lane >> 4;
   const bool triangle = TM == TN && (g.lower_only || g.frag);
   const int per = triangle ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int gid = regroup_xcd(blockIdx.x, gridDim.x);
@@ -275,36 +281,30 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   const int nk = g.K / KT, nk0 = (nk + KS - 1) / KS, kt0 = grp * nk0;
   const int mine = nk - kt0 < nk0 ? (nk - kt0 > 0 ? nk - kt0 : 0) : nk0;      // k-tiles of this group
 
-  // wave w issues MI loads of A and NJ of B per stage; load j of A fills tile rows 8 (MI w + j) .. +7: lane l -> row + l / 8,
-  // 16-byte slot l % 8, which holds the row's piece (l % 8) ^ (row % 8)
-  const TS* ga[MI];
-  const TS* gb[NJ];
+  // load j of wave w fills the eight rows of group LOADS w + j of the stage: lane l -> row l / 8, 16-byte slot l % 8, which holds the row's
+  // piece (l % 8) ^ (row % 8)
+  const TS* src[LOADS];
   const int lr = lane >> 3, lc = PE * ((lane & 7) ^ (lane >> 3));
   auto row_of = [&](int r, int rows, const int32_t* list, long stride) -> long {
     const int at = min(r, rows - 1);
     return !F64 && list ? (long)list[(long)b * stride + at] : (long)at;
   };
 #pragma unroll
-  for (int j = 0; j < MI; ++j)
-    ga[j] = A + row_of(row0 + 8 * (MI * wave + j) + lr, g.M, g.gatherA, g.gstrideA) * g.lda + lc + KT * (long)kt0;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-    gb[j] = B + row_of(col0 + 8 * (NJ * wave + j) + lr, g.N, g.gatherB, g.gstrideB) * g.ldb + lc + KT * (long)kt0;
+  for (int j = 0; j < LOADS; ++j) {
+    const int r = 8 * (LOADS * wave + j) + lr;
+    src[j] = r < TM ? A + row_of(row0 + r, g.M, g.gatherA, g.gstrideA) * g.lda : B + row_of(col0 + r - TM, g.N, g.gatherB, g.gstrideB) * g.ldb;
+    src[j] += lc + KT * (long)kt0;
+  }
   unsigned char* base = ring + grp * (NST * STAGE);
   const int last = mine > 0 ? mine - 1 : 0;
   auto issue = [&](int kt) {
     // past the end: the last k-tile again (a group without any: the one before it), into a stage that is never read
     const long at = KT * (long)(mine == 0 ? -1 : kt < last ? kt : last);
-    unsigned char* sa = base + (kt & (NST - 1)) * STAGE + wave * (MI * 1024);
-    unsigned char* sb = base + (kt & (NST - 1)) * STAGE + TM * 128 + wave * (NJ * 1024);
+    unsigned char* st = base + (kt & (NST - 1)) * STAGE + wave * (LOADS * 1024);
 #pragma unroll
-    for (int j = 0; j < MI; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[j] + at),
-                                       (__attribute__((address_space(3))) void*)(sa + j * 1024), 16, 0, 0);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[j] + at),
-                                       (__attribute__((address_space(3))) void*)(sb + j * 1024), 16, 0, 0);
+    for (int j = 0; j < LOADS; ++j)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + at),
+                                       (__attribute__((address_space(3))) void*)(st + j * 1024), 16, 0, 0);
   };
   double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
   const double t = F64 && g.cheb ? g.cheb[(long)b * g.cheb_stride] : 0.0, scale = cheb_scale(g, t), rt = 1.0 / t;
@@ -351,11 +351,11 @@ __global__ __launch_bounds__(256 * KS, 2) void gemm64_dma_kernel(GemmArgs g, int
   issue(0);
   issue(1);
   issue(2);
-  __builtin_amdgcn_s_waitcnt(0x0070 + 2 * (MI + NJ));   // vmcnt: the loads of two stages, lgkmcnt(0): k-tile 0 has landed
+  __builtin_amdgcn_s_waitcnt(0x0070 + 2 * LOADS);       // vmcnt: the loads of two stages, lgkmcnt(0): k-tile 0 has landed
   __builtin_amdgcn_s_barrier();
   frags(0, 0, a0, b0);
   for (int kt = 0; kt < nk0; ++kt) {
-    __builtin_amdgcn_s_waitcnt(0x0070 + MI + NJ);
+    __builtin_amdgcn_s_waitcnt(0x0070 + LOADS);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     frags(kt, 1, a1, b1);
@@ -623,28 +623,31 @@ hipError_t launch_small(const GemmArgs& g, hipStream_t stream) {
 
 inline long tiles64(const GemmArgs& g) { return (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch; }
 
-template <typename TS, int KS, int TM, int TN>
+template <typename TS, int KS, int TM, int TN, int WM = 2>
 hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
   const long tm = (g.M + TM - 1) / TM, tn = (g.N + TN - 1) / TN;
   const bool triangle = g.lower_only || g.frag;
   if (triangle && TM != TN) return hipErrorInvalidValue;
   const long blocks = (triangle ? tm * (tm + 1) / 2 : tm * tn) * g.batch;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  constexpr size_t kRing = (size_t)KS * 4 * (TM + TN) * 128;
+  constexpr size_t kRing = (size_t)KS * 4 * dma_stage(TM, TN);
   if (kRing > 64 * 1024) {
     static PerDeviceInt raised;
-    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<TS, KS, TM, TN>, kRing);
+    const hipError_t e = ensure_dynamic_lds(raised, (const void*)gemm64_dma_kernel<TS, KS, TM, TN, WM>, kRing);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((gemm64_dma_kernel<TS, KS, TM, TN>), dim3((unsigned)blocks), dim3(256 * KS), kRing, stream, g, (int)tm, (int)tn);
+  hipLaunchKernelGGL((gemm64_dma_kernel<TS, KS, TM, TN, WM>), dim3((unsigned)blocks), dim3(256 * KS), kRing, stream, g, (int)tm, (int)tn);
   return hipGetLastError();
 }
 
 // The tile whose fullest compute unit has the least to do: rounds of tiles over the compute units, times the tile's area, times what a
-// unit of area costs more in smaller tiles (operand reads per MFMA; 1.06 and 1.2 at equal areas, measured with many tiles).  The
-// figures at the kernel and, us, 64 x 64 / 64 x 32 / 32 x 32: 320 x 1024 x 1024, batch 4 73 / 58 / 56; 256 x 832 x 832, batch 16
-// 117 / 109 / 110; 384 x 1280 x 1280, batch 12 260 / 270 / 300; 256 x 1024 x 1024, batch 2 39 / 25 / 26; 192 x 384 x 384, batch 3
-// 17 / 11 / 8; symmetric products 192 x 192 x 1664, batch 4 59 / - / 24; 256 x 256 x 640, batch 64 88 / - / 77.
+// unit of area costs more or less in such tiles (operand reads per MFMA).  us, 64 x 96 / 80 / 64 / 48 / 32 and 32 x 32:
+//   192 x 1664 x 1664, batch 4 83 / 72 / 109 / 83 / 86 and 83     192 x 1280 x 1280, batch 4 65 / 56 / 50 / 64 / 49 and 49
+//   384 x 1152 x 1152, batch 8 162 / 140 / 151 / 144 / 139, 149   256 x 640 x 640, batch 64 218 / 213 / 218 / 235 / 229 and 247
+//   320 x 1024 x 1024, batch 4 54 / 82 / 69 / 53 / 55 and 52      192 x 960 x 960, batch 7 51 / 44 / 67 / 50 / 53 and 49
+//   384 x 1280 x 1280, batch 12 238 / 253 / 249 / 252 / 260, 269  128 x 512 x 512, batch 10 29 / 25 / 22 / 18 / 22 and 18
+// (64 x 112, 64 x 128, 128 x 64, 128 x 96, 128 x 128 and a second group of waves on 64 x 80 or 64 x 64: never the best by more than 1 %.)
+// Symmetric products and bf16 on 64 x 64 and 32 x 32 only: 192 x 192 x 1664, batch 4 59 and 24; 256 x 256 x 640, batch 64 88 and 77.
 template <typename TS>
 hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
   const bool triangle = g.lower_only || g.frag;
@@ -652,10 +655,31 @@ hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
   const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64;
   const auto fullest = [](long tiles) { return (double)((tiles + kUnits - 1) / kUnits); };
   const long t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
-  const double c64 = 4.0 * fullest((triangle ? m64 * (m64 + 1) / 2 : m64 * n64) * g.batch);
-  const double c32 = 1.2 * fullest(t32), c48 = triangle ? c32 : 2.0 * 1.06 * fullest(m64 * n32 * g.batch);
-  if (c64 <= c32 && c64 <= c48) return launch_dma<TS, 1, 64, 64>(g, stream);
-  if (c48 < c32) return launch_dma<TS, 1, 64, 32>(g, stream);
+  double least = 1.2 * fullest(t32);
+  int width = 0;                                    // 0: 32 x 32
+  const auto consider = [&](int w, long tiles, double per_area) {
+    const double cost = w / 16 * per_area * fullest(tiles);
+    if (cost < least) { least = cost; width = w; }
+  };
+  if (triangle) {
+    if (4.0 * fullest(m64 * (m64 + 1) / 2 * g.batch) <= least) width = 64;
+  } else {
+    const auto tiles = [&](int w) { return m64 * ((g.N + w - 1) / w) * g.batch; };
+    consider(64, m64 * n64 * g.batch, 1.0);
+    if constexpr (std::is_same<TS, double>::value) {
+      consider(96, tiles(96), 1.0);
+      consider(80, tiles(80), 1.0);
+      consider(48, tiles(48), 1.02);
+    }
+    consider(32, m64 * n32 * g.batch, 1.06);
+  }
+  if constexpr (std::is_same<TS, double>::value) {
+    if (width == 96) return launch_dma<TS, 1, 64, 96>(g, stream);
+    if (width == 80) return launch_dma<TS, 1, 64, 80, 4>(g, stream);
+    if (width == 48) return launch_dma<TS, 1, 64, 48, 4>(g, stream);
+  }
+  if (width == 64) return launch_dma<TS, 1, 64, 64>(g, stream);
+  if (width == 32) return launch_dma<TS, 1, 64, 32>(g, stream);
   return t32 <= kUnits && g.K >= (int)(256 / sizeof(TS)) ? launch_dma<TS, 2, 32, 32>(g, stream) : launch_dma<TS, 1, 32, 32>(g, stream);
 }
 

@@ -99,6 +99,34 @@ def test_small_sign_iteration(C, name):
         assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
 
 
+# Batches whose products go on each width of tile of the fp64 kernel (gemm64.hip): images, tokens, rank; the last tile is a partial one.
+TILE_WIDTHS = {"64x80": (7, 950, 100), "64x48": (10, 500, 60), "64x96": (12, 1270, 300), "64x64": (4, 1270, 120), "64x32": (2, 1000, 180), "32x32": (4, 1000, 240)}
+
+
+@pytest.mark.parametrize("name", list(TILE_WIDTHS))
+def test_products_on_every_width_of_tile(C, name):
+    import torch
+    B, n, r = TILE_WIDTHS[name]
+    d, decay = (n + 29) // 4 * 4, 3.0 / r                 # sigma_r is a twentieth of sigma_1
+    sigma = np.exp(-decay * np.arange(n))
+    X = np.stack([I.make_spectrum_tokens(n, d, sigma, seed=b, dtype=I.FP32) if b in (0, B - 1) else np.zeros((n, d), np.float32) for b in range(B)])
+    for b in range(1, B - 1):
+        X[b] = X[0][::-1] if b % 2 else X[B - 1]
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    ws = C.alloc_workspace(p)
+    out = C.select(p, torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda(), workspace=ws)
+    assert set(C.lowrank_path(p, ws).tolist()) <= {1, 2}
+    c = out["c"].cpu().numpy().astype(np.float64)
+    for b in (0, B - 1):
+        ref = O.select(X[b].astype(np.float64), sf[b], O.Params(preselect_m=n, rank_r=r, keep_k=n // 3))["c"]
+        err = np.abs(c[b] - ref) / np.maximum(ref, 1e-6 * ref.max())
+        assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
+    for b in range(1, B - 1):                             # the same tokens, in another place of the batch
+        same = c[0][::-1] if b % 2 else c[B - 1]
+        assert np.abs(c[b] - same).max() < 2e-7 * same.max()
+
+
 # tokens, rank, decay of the singular values per index, factor on the four largest of them, the way the solve has to take; what
 # the block iteration's schedule has to cope with
 SCHEDULES = {
