@@ -655,7 +655,7 @@ hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
   const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64;
   const auto fullest = [](long tiles) { return (double)((tiles + kUnits - 1) / kUnits); };
   const long t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
-  double least = 1.2 * fullest(t32);
+  double least = 1.18 * fullest(t32);
   int width = 0;                                    // 0: 32 x 32
   const auto consider = [&](int w, long tiles, double per_area) {
     const double cost = w / 16 * per_area * fullest(tiles);
@@ -667,7 +667,7 @@ hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
     const auto tiles = [&](int w) { return m64 * ((g.N + w - 1) / w) * g.batch; };
     consider(64, m64 * n64 * g.batch, 1.0);
     if constexpr (std::is_same<TS, double>::value) {
-      consider(96, tiles(96), 1.0);
+      consider(96, tiles(96), 0.99);
       consider(80, tiles(80), 1.0);
       consider(48, tiles(48), 1.02);
     }
