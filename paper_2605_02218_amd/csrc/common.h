@@ -96,6 +96,16 @@ __device__ __forceinline__ double row_lane(double v) {
   return __builtin_amdgcn_mov_dpp(v, 0x150 + k, 0xf, 0xf, true);   // row_newbcast:k
 }
 
+// Scalar from lane l of v.
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// 1 / p: an estimate good to 2^-24, r (1 + e + e^2).
+__device__ __forceinline__ double reciprocal(double p) {
+  const double r = __builtin_amdgcn_rcp(p), e = fma(-p, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
 // Barrier in global memory over the workgroups that work on one image.  `arrived` only grows; `target` is the
 // value it reaches when all of them have arrived at this barrier.  Every thread's earlier global writes are
 // visible to every thread of the group behind the barrier (device-scope release before, acquire after: the

@@ -337,7 +337,7 @@ int run_select(const Plan& q, const void* X, const float* s_fused, int32_t* idx_
   double* A = at<double>(ws, q.Awork);
   const bool greedy = q.lr == COVSPEC_LR_GREEDY_RESIDUAL;
   HIPCHK(launch_lowrank_prepare(img_status, at<void>(ws, greedy ? q.gscr : q.ctl), (greedy ? greedy_ctl_bytes(q.B) : jacobi_ctl_bytes(q.B)) / sizeof(int), A, q.B, q.M,
-                                q.nP, q.P, at<void>(ws, q.sub), st));
+                                q.nP, q.P, greedy ? nullptr : at<void>(ws, q.sub), st));
   int32_t* idxm = idx_m_out ? idx_m_out : at<int32_t>(ws, q.idxm);
   HIPCHK(launch_select_top(s_fused, q.B, q.N, q.M, nullptr, idxm, st));
 
@@ -809,7 +809,7 @@ int covspec_stream_step(const covspec_stream_params* p, int32_t n_keep, int32_t 
 
   // 2. Gram matrix of the candidates: the kept block is carried, the rows of the arriving tokens are computed
   const int P = nC > q.k ? subspace_block(nC, q.r) : 0;
-  HIPCHK(launch_lowrank_prepare(nullptr, at<void>(ws, q.ctl), jacobi_ctl_bytes(q.B) / sizeof(int), Gc, q.B, nC, q.nP, P, at<void>(ws, q.sub), st));
+  HIPCHK(launch_lowrank_prepare(nullptr, at<void>(ws, q.ctl), jacobi_ctl_bytes(q.B) / sizeof(int), Gc, q.B, nC, q.nP, P, nC > q.k ? at<void>(ws, q.sub) : nullptr, st));
   HIPCHK(launch_copy_block(Gc, q.nP, gstride, G_in, q.k, (long)q.k * q.k, n_keep, q.B, st));
   GemmArgs g;
   g.A = X_frame; g.lda = d; g.strideA = (long)q.N * d; g.gatherA = idxf; g.gstrideA = q.M;

@@ -158,9 +158,11 @@ hipError_t launch_jacobi_eigen(double* A, const double* src, int B, int n, int n
 // again by the two launchers below.  skip (optional, [B]): images with a non-zero entry are left out.  Where the eigenvalues at the
 // cut cannot be told apart, or a wait ran out, the image gets no projector.
 size_t split_scratch_bytes(int B, int P);
+// The part of `scratch` that is cleared before the first split of a call (epoch 0, the second one's is 1).
+void* split_cleared(void* scratch, int B, int P, size_t* bytes);
 bool split_direct(int nP);
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
-                                 const int* skip, const int* again, hipStream_t stream);
+                                 const int* skip, const int* again, int epoch, hipStream_t stream);
 // Residual check and energies of a block iteration, see split.hip.  slow[b] != 0: the image was left out of the split.
 // next.state != null: state 0 of a further pass, of `fields` integers per image: images that passed the check rest (2); one that was left
 // out of the split goes on from its block, which is in the buffer that state `prev` names last, one that failed the check from the product with

@@ -2,14 +2,14 @@
 // r dominant eigenvectors (paper Sec. III-A.3: the energies c_i need the rank-r subspace, not its eigenvectors:
 // c_i = (Pi G)_ii).
 //
-// Pi = (I + sign(H - mu I)) / 2 with mu between the r-th and the (r+1)-th eigenvalue.  Two kernels:
-//   split_kernel finds mu.  The rows of H are ordered like its eigenvalues (block iteration, subspace.hip), so the
+// Pi = (I + sign(H - mu I)) / 2 with mu between the r-th and the (r+1)-th eigenvalue.  Two steps:
+//   split_kernel, or cut_kernel for a few images, finds mu.  The rows of H are ordered like its eigenvalues (block iteration, subspace.hip), so the
 //     two eigenvalues at the cut are those of a 64 x 64 window of rows around r: what the rows outside couple to it
 //     enters an eigenvalue squared (rows p and q couple by (lambda_q / lambda_p)^s after s products; 32 rows apart that shifts
 //     the eigenvalue by less than a tenth of the half gap for every decay the iteration converges on; an image that failed
-//     the check gets 128 rows).  The window is brought to tridiagonal form by Householder reflections with the
+//     the check gets 128 rows).  In split_kernel the window is brought to tridiagonal form by Householder reflections with the
 //     matrix in the registers of one workgroup, and the two eigenvalues are cut out of it by Sturm counts, 128 trial
-//     points per pass and eigenvalue.  A matrix of order <= 128 is its own window, whatever the order of its rows.
+//     points per pass and eigenvalue; cut_kernel counts without it.  A matrix of order <= 128 is its own window, whatever the order of its rows.
 //   sign_kernel first lifts the cut: H is positive semidefinite and mu far below its norm, so X <- alpha X - beta X^2 with the
 //     largest alpha that keeps X in [0, 1] and its top above the image of mu multiplies mu, and the gap around it, by almost 4
 //     per product; it ends with mu in [0.1, 0.4] of the norm.  Then X <- 1.5 s X - 0.5 s^3 X^3 from the shifted X (Newton-Schulz;
@@ -289,39 +289,276 @@ __device__ __forceinline__ void split_window(const double* __restrict__ H, int P
   }
 }
 
-// wide: every image has a window of SN rows; else those with again[b] != 0 (optional), the others 64
-// X0, X1, Y (optional): the buffers of sign_small_kernel, which finds its words at zero.
-__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int B, int r, bool wide, double* __restrict__ off,
-                                                    double* __restrict__ link, SplitCtl* ctl, const int* __restrict__ skip,
-                                                    const int* __restrict__ again, double* X0, double* X1, double* Y) {
-  __shared__ double rd[4096];
-  if (blockIdx.x >= (unsigned)B) {
-    const int per = P / 16, at = blockIdx.x - B, img = at / per;
-    if (skip && skip[img]) return;
-    if (X0) {
-      const long from = img * stride + 16l * (at - img * per) * P;
-      const f64x2_t zero = (f64x2_t){0.0, 0.0};
-      for (int k = threadIdx.x; k < 8 * P; k += 256) {
-        *(f64x2_t*)(X0 + from + 2 * k) = zero;
-        *(f64x2_t*)(X1 + from + 2 * k) = zero;
-        *(f64x2_t*)(Y + from + 2 * k) = zero;
-      }
-    }
-    row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
-    return;
-  }
-  const int b = blockIdx.x, tid = threadIdx.x;
-  SplitCtl* cb = ctl + b;
-  if (b == 0 && tid == 0) ctl[0].ticket = 0u;
-  for (int k = tid; k < kMaxSignSteps + 2; k += 256) cb->dev[k] = 0ull;
-  if (tid == 0) {
+// State of an image's split before its cut is known.
+__device__ __forceinline__ void start_ctl(SplitCtl* cb) {
+  for (int k = threadIdx.x; k < kMaxSignSteps + 2; k += 256) cb->dev[k] = 0ull;
+  if (threadIdx.x == 0) {
     cb->bar.arrived = 0u;
     cb->bar.failed = 0;
     cb->state = 1;
   }
+}
+
+// Workgroup `at` of those that profile 16 rows each, P / 16 per image.  X0, X1, Y (optional): the buffers of sign_small_kernel, which finds its
+// words at zero.
+__device__ __forceinline__ void profile_rows(const double* __restrict__ H, int P, long stride, int r, int at, double* __restrict__ off, double* __restrict__ link,
+                                             const int* __restrict__ skip, double* X0, double* X1, double* Y, double* rd) {
+  const int per = P / 16, img = at / per;
+  if (skip && skip[img]) return;
+  if (X0) {
+    const long from = img * stride + 16l * (at - img * per) * P;
+    const f64x2_t zero = (f64x2_t){0.0, 0.0};
+    for (int k = threadIdx.x; k < 8 * P; k += 256) {
+      *(f64x2_t*)(X0 + from + 2 * k) = zero;
+      *(f64x2_t*)(X1 + from + 2 * k) = zero;
+      *(f64x2_t*)(Y + from + 2 * k) = zero;
+    }
+  }
+  row_profile(H + img * stride, P, r, 16 * (at - img * per), off + (long)img * P, link + (long)img * P, rd);
+}
+
+// wide: every image has a window of SN rows; else those with again[b] != 0 (optional), the others 64.  rest: only those are left, what
+// all have in common is done.
+__global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H, int P, long stride, int B, int r, bool wide, double* __restrict__ off,
+                                                    double* __restrict__ link, SplitCtl* ctl, const int* __restrict__ skip,
+                                                    const int* __restrict__ again, bool rest, double* X0, double* X1, double* Y) {
+  __shared__ double rd[4096];
+  if (blockIdx.x >= (unsigned)B) {
+    profile_rows(H, P, stride, r, blockIdx.x - B, off, link, skip, X0, X1, Y, rd);
+    return;
+  }
+  const int b = blockIdx.x, tid = threadIdx.x;
+  SplitCtl* cb = ctl + b;
+  if (rest && !again[b]) return;
+  if (!rest) {
+    if (b == 0 && tid == 0) ctl[0].ticket = 0u;
+    start_ctl(cb);
+  }
   if (skip && skip[b]) return;
   if (wide || (again && again[b])) split_window<SN>(H, P, stride, r, b, cb, rd);
   else split_window<64>(H, P, stride, r, b, cb, rd);
+}
+
+// ---- The cut of a few images by counting: a matrix less x, A - x I = L D L^T without exchanges, has as many eigenvalues below x as D has
+// negative entries, and that is worked out for hundreds of x at once, a wave each.
+// Per image kTrials waves (half as many for windows of 128) try points of an interval, tell one another the counts (each with the
+// number of the pass), and agree on the next interval until eight points lie between the two eigenvalues.  The first interval of an ordered
+// window are the diagonal entries four rows to either side of the cut, otherwise everything.  A wave holds the upper triangle of
+// 16 x 16 tiles in its registers and eliminates four pivots at a time: the 4 x 4 block at the pivots in scalars, as eliminate_panel
+// (subspace.hip) does without its floors, the rest as products of rank 4.  (A pivot of relative size p perturbs the matrix by 1e-16 / p; that
+// this moves an eigenvalue over a trial point, 1e-6 of the norm away and more, takes a pivot below 1e-10, and a count that is
+// wrong shows in the trace of the projector.)
+// Bound by the chain of pivots and the MFMAs of a wave.  us, split_kernel and here: one window of 64 44 and 19 (two 44 and 22), of 128 121 and 83.
+constexpr int kCutImages = 8;        // of windows of 128, half as many of 64: a SIMD gets a wave at most
+constexpr int kTrials = 256;
+constexpr int kCutPasses = 8, kCutPoints = 8;
+struct CutArea {
+  unsigned int ticket[2], pad[62];             // one per split of the call
+  int count[kCutImages][2][kTrials];           // pass << 16 | eigenvalues at the point or above, by turns (who writes the next but one has
+                                               // everybody's next one, so everybody has read this one); cleared before the first split
+};
+
+template <int NT> __device__ constexpr int tri(int s, int t) { return s * NT - s * (s - 1) / 2 + t - s; }
+
+// Pivots 4 PN .. + 3 of diagonal tile S.
+template <int NT, int S, int PN>
+__device__ __forceinline__ void count_panel(f64x4_t (&T)[NT * (NT + 1) / 2], int& neg) {
+  const int lane = threadIdx.x & 63, i16 = lane & 15, kq = lane >> 4;
+  const f64x4_t zero = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  f64x4_t& x = T[tri<NT>(S, S)];
+  auto at = [&](int i, int j) { return lane_value(x[PN], 16 * i + 4 * PN + j); };
+  auto pivot = [&](double p) {
+    p = fabs(p) > 1e-200 ? p : -1e-200;
+    neg += p < 0.0 ? 1 : 0;
+    return p;
+  };
+  const double a10 = at(1, 0), a20 = at(2, 0), a30 = at(3, 0), a21 = at(2, 1), a31 = at(3, 1), a32 = at(3, 2);
+  const double a11 = at(1, 1), a22 = at(2, 2), a33 = at(3, 3), r0 = reciprocal(pivot(at(0, 0)));
+  const double b11 = fma(-(a10 * a10), r0, a11), b21 = fma(-(a20 * a10), r0, a21), b31 = fma(-(a30 * a10), r0, a31);
+  const double b22 = fma(-(a20 * a20), r0, a22), b32 = fma(-(a30 * a20), r0, a32), b33 = fma(-(a30 * a30), r0, a33);
+  const double r1 = reciprocal(pivot(b11));
+  const double c22 = fma(-(b21 * b21), r1, b22), c32 = fma(-(b31 * b21), r1, b32), c33 = fma(-(b31 * b31), r1, b33);
+  const double r2 = reciprocal(pivot(c22));
+  const double r3 = reciprocal(pivot(fma(-(c32 * c32), r2, c33)));
+  if constexpr (S == NT - 1 && PN == 3) return;
+  const double l10 = a10 * r0, l20 = a20 * r0, l30 = a30 * r0, l21 = b21 * r1, l31 = b31 * r1, l32 = c32 * r2;
+  const double n20 = fma(l21, l10, -l20), n31 = fma(l32, l21, -l31), n30 = -fma(l31, -l10, fma(l32, n20, l30));
+  double n = i16 == kq ? 1.0 : 0.0;
+  if (i16 == 1 && kq == 0) n = -l10;
+  if (i16 == 2 && kq == 0) n = n20;
+  if (i16 == 2 && kq == 1) n = -l21;
+  if (i16 == 3 && kq == 0) n = n30;
+  if (i16 == 3 && kq == 1) n = n31;
+  if (i16 == 3 && kq == 2) n = -l32;
+  const double r = kq == 0 ? r0 : kq == 1 ? r1 : kq == 2 ? r2 : r3;
+  double below = 0.0, u[NT], ru[NT];
+  if constexpr (PN < 3) {
+    const double w = __builtin_amdgcn_mfma_f64_16x16x4f64(n, x[PN], zero, 0, 0, 0)[0];
+    below = (i16 > 4 * PN + 3 ? -r : 0.0) * w;
+    x = __builtin_amdgcn_mfma_f64_16x16x4f64(below, w, x, 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = S + 1; t < NT; ++t) {
+    u[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(n, T[tri<NT>(S, t)][PN], zero, 0, 0, 0)[0];
+    ru[t] = -r * u[t];
+    if (PN < 3) T[tri<NT>(S, t)] = __builtin_amdgcn_mfma_f64_16x16x4f64(below, u[t], T[tri<NT>(S, t)], 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = S + 1; t < NT; ++t)
+#pragma unroll
+    for (int v = t; v < NT; ++v) T[tri<NT>(t, v)] = __builtin_amdgcn_mfma_f64_16x16x4f64(ru[t], u[v], T[tri<NT>(t, v)], 0, 0, 0);
+}
+template <int NT, int S>
+__device__ __forceinline__ void count_from(f64x4_t (&T)[NT * (NT + 1) / 2], int& neg) {
+  if constexpr (S < NT) {
+    count_panel<NT, S, 0>(T, neg);
+    count_panel<NT, S, 1>(T, neg);
+    count_panel<NT, S, 2>(T, neg);
+    count_panel<NT, S, 3>(T, neg);
+    count_from<NT, S + 1>(T, neg);
+  }
+}
+
+// Workgroups 0 .. B trials / 4 - 1 try four points of an image each, which image and which points by ticket (so that whoever waits for the
+// counts of others waits for some that have started or start next), the others profile 16 rows each (see split_kernel).  again:
+// images that split_kernel takes instead.  epoch: 0 for the first split of a call, 1 for the second.
+template <int N>
+__global__ __launch_bounds__(256, N == 64 ? 2 : 1) void cut_kernel(const double* __restrict__ H, int P, long stride, int B, int r, bool ordered, int trials,
+                                                                  double* __restrict__ off, double* __restrict__ link, SplitCtl* ctl, CutArea* area, int epoch,
+                                                                  const int* __restrict__ skip, const int* __restrict__ again, double* X0, double* X1, double* Y,
+                                                                  long long limit_ticks) {
+  constexpr int NT = N / 16, PITCH = N + 1;
+  extern __shared__ double lds[];               // [N][N + 1], or the profile's reciprocal square roots
+  __shared__ double red[8];
+  __shared__ int s_ticket;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+  const int per = trials / 4;
+  if (blockIdx.x >= (unsigned)(B * per)) {
+    profile_rows(H, P, stride, r, blockIdx.x - B * per, off, link, skip, X0, X1, Y, lds);
+    return;
+  }
+  if (tid == 0) s_ticket = (int)atomicAdd(&area->ticket[epoch], 1u);
+  __syncthreads();
+  const int ticket = __builtin_amdgcn_readfirstlane(s_ticket), b = ticket / per, slot = ticket - b * per;
+  SplitCtl* cb = ctl + b;
+  if (slot == 0) {
+    if (b == 0 && tid == 0) ctl[0].ticket = 0u;
+    start_ctl(cb);
+  }
+  if ((skip && skip[b]) || (again && again[b])) return;
+  const double* Hb = H + b * stride;
+  const int w0 = P <= N ? 0 : (r - N / 2 < 0 ? 0 : (r - N / 2 > P - N ? P - N : r - N / 2));
+  const int nw = P - w0 < N ? P - w0 : N;
+  {
+    typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+    constexpr int PAIRS = N * N / 512;          // per thread
+    pair_t v[PAIRS];
+#pragma unroll
+    for (int k = 0; k < PAIRS; ++k) {
+      const int e = 2 * (tid + 256 * k), i = e / N, j = e % N;        // nw is even
+      v[k] = i < nw && j < nw ? *(const pair_t*)(Hb + (long)(w0 + i) * P + w0 + j) : (pair_t){0.0, 0.0};
+    }
+#pragma unroll
+    for (int k = 0; k < PAIRS; ++k) {
+      const int e = 2 * (tid + 256 * k), i = e / N, j = e % N;
+      lds[i * PITCH + j] = v[k][0];
+      lds[i * PITCH + j + 1] = v[k][1];
+    }
+  }
+  __syncthreads();
+  double big, top = 0.0;                        // largest diagonal entry (no entry exceeds it), and a bound on the eigenvalues
+  {
+    constexpr int SHARE = 256 / N;              // threads of a row
+    const int i = tid / SHARE, j0 = tid % SHARE * (N / SHARE);
+    big = lds[i * PITCH + i];
+#pragma unroll 16
+    for (int j = 0; j < N / SHARE; ++j) top += fabs(lds[i * PITCH + j0 + j]);
+#pragma unroll
+    for (int o = 1; o < SHARE; o <<= 1) top += __shfl_xor(top, o, 64);
+  }
+  big = wave_max(big);
+  top = wave_max(top);
+  if (lane == 0) { red[wv] = big; red[4 + wv] = top; }
+  __syncthreads();
+  big = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  top = fmax(fmax(red[4], red[5]), fmax(red[6], red[7]));
+  if (!(big > 0.0) || !(top < 1e300)) return;   // zero matrix, infinities, NaN: left to the caller's fallback
+  const double scale = 1.0 / big;
+  top = top * scale * 1.0001 + 1e-12;
+  const int m = r - w0;                         // the m-th largest eigenvalue of the window and the one below it
+  double lo = -1e-3 * top, hi = top;
+  bool ratios = true;                           // points at equal ratios from 1e-6 of the bound to it, for the first pass over everything
+  if (ordered && m >= 5 && m + 4 < nw) {
+    const double d0 = lds[(m + 4) * PITCH + m + 4] * scale, d1 = lds[(m - 5) * PITCH + m - 5] * scale;
+    if (d0 < d1) { lo = d0; hi = d1; ratios = false; }
+  }
+  const int mine = 4 * slot + wv;
+  bool found = false, alive = true;
+  double at0 = 0.0, at1 = 0.0;                  // points between the two eigenvalues, the first and the last
+#pragma unroll 1
+  for (int pass = 1; pass <= kCutPasses && alive && !found; ++pass) {
+    const double dx = (hi - lo) / (double)(trials + 1), l0 = lo;
+    auto point = [&](int j) { return ratios ? top * exp2(20.0 * ((double)(j + 1) / (double)(trials + 1) - 1.0)) : l0 + dx * (double)(j + 1); };
+    const double x = point(mine);
+    f64x4_t T[NT * (NT + 1) / 2];
+#pragma unroll
+    for (int s = 0; s < NT; ++s)
+#pragma unroll
+      for (int t = s; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) T[tri<NT>(s, t)][v] = fma(lds[(16 * s + 4 * v + kq) * PITCH + 16 * t + i16], scale, s == t && 4 * v + kq == i16 ? -x : 0.0);
+    int neg = 0;
+    count_from<NT, 0>(T, neg);
+    const int mark = (epoch * kCutPasses + pass) << 16;
+    int* counts = area->count[b][pass & 1];
+    if (lane == 0) __hip_atomic_store(&counts[mine], mark | (N - neg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // everybody's: lane l looks at l, l + 64, ..
+    int c[kTrials / 64];
+    long long t0 = 0;
+    for (int tries = 0;; ++tries) {
+      bool there = true;
+#pragma unroll
+      for (int q = 0; q < kTrials / 64; ++q) {
+        c[q] = 64 * q < trials ? __hip_atomic_load(&counts[64 * q + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : mark;
+        there = there && (c[q] & ~0xFFFF) == mark;
+      }
+      if (!__any(!there)) break;
+      __builtin_amdgcn_s_sleep(4);
+      if ((tries & 63) == 63) {
+        if (tries == 63) t0 = wall_clock64();
+        if (wall_clock64() - t0 > limit_ticks) { alive = false; break; }
+      }
+    }
+    if (!alive) break;
+    int first = trials, last = -1;              // first point with at most m at it or above, last one with at least m
+#pragma unroll
+    for (int q = 0; q < kTrials / 64; ++q)
+      if (64 * q < trials) {
+        const unsigned long long few = __ballot((c[q] & 0xFFFF) <= m), many = __ballot((c[q] & 0xFFFF) >= m);
+        if (few && first == trials) first = 64 * q + __ffsll((long long)few) - 1;
+        if (many) last = 64 * q + 63 - __clzll((long long)many);
+      }
+    at0 = point(first);
+    at1 = point(last);
+    found = last - first >= kCutPoints || (pass == kCutPasses && last > first);
+    if (last >= first) {                        // some between the two: closer in on them
+      const double l1 = first == 0 ? (pass == 1 ? -1e-3 * top : lo) : point(first - 1);
+      hi = last == trials - 1 ? (pass == 1 ? top : hi) : point(last + 1);
+      lo = l1;
+    } else {                                    // both between two points, or beyond the interval
+      const double l1 = last < 0 ? -1e-3 * top : point(last);
+      hi = first == trials ? top : point(first);
+      lo = l1;
+    }
+    ratios = false;
+  }
+  if (slot == 0 && tid == 0) {
+    const double gap = (at1 - at0) * big;
+    cb->mu = 0.5 * (at0 + at1) * big;
+    cb->half = 0.45 * gap;                           // a tenth off the half gap for what the window leaves out
+    cb->theta = at1 * big;
+    cb->state = found && gap > 0.0 && cb->mu > 0.0 ? 0 : 1;
+  }
 }
 
 constexpr int ST = 32;            // tile of a wave in the sign iteration
@@ -914,10 +1151,17 @@ __global__ __launch_bounds__(256) void direct_energy_kernel(const double* __rest
 
 }  // namespace
 
-size_t split_scratch_bytes(int B, int P) { return (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256 + 2 * (size_t)B * P * 8; }
+namespace {
+inline size_t split_base_bytes(int B, int P) { return (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256 + 2 * (size_t)B * P * 8; }
+}
+size_t split_scratch_bytes(int B, int P) { return split_base_bytes(B, P) + (B <= kCutImages ? sizeof(CutArea) : 0); }
+void* split_cleared(void* scratch, int B, int P, size_t* bytes) {
+  *bytes = B <= kCutImages ? sizeof(CutArea) : 0;
+  return (char*)scratch + split_base_bytes(B, P);
+}
 
 hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool ordered, double* X0, double* Y, double* X1, void* scratch,
-                                 const int* skip, const int* again, hipStream_t st) {
+                                 const int* skip, const int* again, int epoch, hipStream_t st) {
   if (P < 64 || P % 64 != 0 || P > 4096 || r < 1 || r >= P || (!ordered && P > SN)) return hipErrorInvalidValue;
   SplitCtl* ctl = (SplitCtl*)scratch;
   double* off = (double*)((char*)scratch + (sizeof(SplitCtl) * (size_t)B + 255) / 256 * 256);
@@ -954,7 +1198,23 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
     if ((e = resident_workgroups(resident, sign_small_kernel<kSmallBlocks>, 256, 0, &held)) != hipSuccess) return e;      // the others need less
     small = t16 <= held / 8;
   }
-  hipLaunchKernelGGL(split_kernel, sg, dim3(256), 0, st, H, P, stride, B, r, !ordered, off, link, ctl, skip, again, small ? X0 : nullptr, X1, Y);
+  const bool w64 = ordered || P == 64;
+  if (B <= (w64 ? kCutImages / 2 : kCutImages)) {
+    CutArea* area = (CutArea*)((char*)scratch + split_base_bytes(B, P));
+    // A wave per SIMD; an image's workgroups are an eighth of what the device holds at most, as below.  Eight windows of 64: 47 us by
+    // split_kernel, 48 with half the points and 64 with two waves a SIMD.
+    const int trials = w64 ? kTrials : kTrials / 2;
+    const size_t window = w64 ? 64 * 65 * 8 : SN * (SN + 1) * 8, cut_lds = window > (size_t)P * 8 ? window : (size_t)P * 8;
+    static PerDeviceInt grown[2];
+    const dim3 cg((unsigned)(B * (trials / 4) + B * (P / 16)));
+    auto ck = w64 ? cut_kernel<64> : cut_kernel<SN>;
+    if ((e = ensure_dynamic_lds(grown[w64], (const void*)ck, w64 ? 64 * 65 * 8 : SN * (SN + 1) * 8)) != hipSuccess) return e;
+    hipLaunchKernelGGL(ck, cg, dim3(256), cut_lds, st, H, P, stride, B, r, ordered, trials, off, link, ctl, area, epoch, skip, again, small ? X0 : nullptr,
+                       X1, Y, barrier_limit_ticks());
+    if (again) hipLaunchKernelGGL(split_kernel, dim3((unsigned)B), dim3(256), 0, st, H, P, stride, B, r, false, off, link, ctl, skip, again, true, X0, X1, Y);
+  } else {
+    hipLaunchKernelGGL(split_kernel, sg, dim3(256), 0, st, H, P, stride, B, r, !ordered, off, link, ctl, skip, again, false, small ? X0 : nullptr, X1, Y);
+  }
   if (small) {
     static_assert(kSmallBlocks == 4, "");
     auto sk = n64 == 1 ? sign_small_kernel<1> : n64 == 2 ? sign_small_kernel<2> : n64 == 3 ? sign_small_kernel<3> : sign_small_kernel<4>;

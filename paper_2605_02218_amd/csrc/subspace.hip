@@ -246,16 +246,6 @@ __device__ __forceinline__ f64x4_t tagged(const f64x4_t& v, unsigned tag) {
 // Bound by the chain of 64 pivots, a reciprocal and some five dependent operations each.  (One pivot at a time, the multipliers moved
 // along the rows of 16 lanes, took 32 moves and 32 multiply-adds a pivot, all four rows the same: 11.4 us a block, bound by issue.)
 
-// Scalar from lane l of v.
-__device__ __forceinline__ double lane_value(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-// 1 / p: an estimate good to 2^-24, r (1 + e + e^2).
-__device__ __forceinline__ double reciprocal(double p) {
-  const double r = __builtin_amdgcn_rcp(p), e = fma(-p, r, 1.0);
-  return fma(r, fma(e, e, e), r);
-}
-
 // Pivots 4t .. 4t + 3 of the tile x (lane (q, i): rows 4v + q of column i) with the unit matrix u; floors of the tile's 16 pivots in LDS.
 // piv: lane (q, i) gets the pivot of row 4t + q.
 template <int t>
@@ -802,7 +792,8 @@ struct PrepareArgs {
   int *status, *ctl, *flags, *state, *left, *failed;
   IterPlan* plan;
   double *A, *om, *inverses;
-  long words, flag_words, pad, omega, blocks;      // numbers of elements; pad: of one matrix
+  int* cut;
+  long words, flag_words, cut_words, pad, omega, blocks;      // numbers of elements; pad: of one matrix
   int B, n, nP;
 };
 __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
@@ -822,6 +813,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
   for (long i = at; i < q.blocks; i += step) q.inverses[i] = 0.0;
   for (long i = at; i < q.words; i += step) q.ctl[i] = 0;
   for (long i = at; i < q.flag_words; i += step) q.flags[i] = 0;
+  for (long i = at; i < q.cut_words; i += step) q.cut[i] = 0;
   for (long b = at; b < q.B; b += step) {
     if (q.status) q.status[b] = 0;
     if (q.state) {                         // every block is in buffer 0
@@ -832,6 +824,19 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
     }
   }
 }
+
+// The workspace of a direct split.
+struct DirectBuffers {
+  double *X0, *Y, *X1;
+  void* scratch;
+  DirectBuffers(void* ws, int B, int nP) {
+    const size_t sq = (size_t)B * nP * nP;
+    X0 = (double*)ws;
+    Y = X0 + sq;
+    X1 = Y + sq;
+    scratch = (void*)(((uintptr_t)(X1 + sq) + 255) & ~(uintptr_t)255);
+  }
+};
 
 // The workspace of the iteration.
 struct IterBuffers {
@@ -917,8 +922,13 @@ hipError_t launch_lowrank_prepare(int* status, void* ctl, size_t words, double* 
     q.flags = (int*)w.flags;
     q.flag_words = (long)kOrths * B * (long)(sizeof(CholFlags) / sizeof(int));
   }
+  if (ws && (P > 0 || split_direct(nP))) {
+    size_t bytes = 0;
+    q.cut = (int*)(P > 0 ? split_cleared(IterBuffers(ws, B, nP, P).scratch, B, P, &bytes) : split_cleared(DirectBuffers(ws, B, nP).scratch, B, nP, &bytes));
+    q.cut_words = (long)(bytes / sizeof(int));
+  }
   long most = q.pad * B;
-  for (long k : {q.omega, q.blocks, q.words, q.flag_words, (long)B}) most = k > most ? k : most;
+  for (long k : {q.omega, q.blocks, q.words, q.flag_words, q.cut_words, (long)B}) most = k > most ? k : most;
   const long blocks = (most + 255) / 256;
   hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, q);
   return hipGetLastError();
@@ -929,11 +939,10 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
   if (P == 0) {
     // the whole matrix is the window
     if (!split_direct(nP)) return hipErrorInvalidValue;
-    const size_t sq = (size_t)B * nP * nP;
-    double* X0 = (double*)ws_;
-    double *Y = X0 + sq, *X1 = Y + sq;
-    void* scratch = (void*)(((uintptr_t)(X1 + sq) + 255) & ~(uintptr_t)255);
-    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, nullptr, st);
+    const DirectBuffers w(ws_, B, nP);
+    double *X0 = w.X0, *Y = w.Y, *X1 = w.X1;
+    void* scratch = w.scratch;
+    const hipError_t ed = launch_spectral_split(G, B, nP, r, false, X0, Y, X1, scratch, nullptr, nullptr, 0, st);
     return ed != hipSuccess ? ed : launch_direct_energy(G, Y, B, n, nP, r, scratch, ok, c, st);
   }
   hipError_t e0;
@@ -1006,7 +1015,7 @@ hipError_t launch_subspace_eigen(const double* G, int B, int n, int nP, int r, i
       g.skip = left; g.skip_if = 0;
       if ((e = launch_gemm64_nt(g, true, true, st)) != hipSuccess) return e;
     }
-    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, w.X1, w.scratch, left, pass_no == 1 ? nullptr : w.failed, st)) != hipSuccess) return e;
+    if ((e = launch_spectral_split(H, B, P, r, true, S, Pi, w.X1, w.scratch, left, pass_no == 1 ? nullptr : w.failed, pass_no - 1, st)) != hipSuccess) return e;
     // U = Pi Q^T, and the energies (U Q^T G)_ii
     {
       GemmArgs g;

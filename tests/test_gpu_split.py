@@ -99,6 +99,47 @@ def test_small_sign_iteration(C, name):
         assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
 
 
+# The cut by counting (split.hip) at its edges, and by a tridiagonal form beyond: images, tokens, width, rank, decay, way.
+CUT = {
+    "rank-4": (1, 400, 420, 4, 0.05, 1),                  # too near the window's end for a first interval from the diagonal
+    "rank-5": (1, 400, 420, 5, 0.05, 1),
+    "window-inside": (1, 900, 960, 240, 0.015, 1),
+    "four-images": (4, 300, 320, 100, 0.02, 1),           # the most
+    "one-image-more": (5, 300, 320, 100, 0.02, 1),
+    "direct-64": (4, 64, 96, 63, 0.05, 3),
+    "direct-64-five": (5, 50, 96, 1, 0.05, 3),
+    "direct-128": (8, 127, 160, 126, 0.05, 3),
+    "direct-128-more": (9, 127, 160, 126, 0.05, 3),
+    "direct-128-steep": (2, 100, 128, 40, 0.2, 3),        # the cut far below the largest eigenvalue: points in a geometric sequence
+}
+
+
+@pytest.mark.parametrize("name", list(CUT))
+def test_cut_of_few_images(C, name):
+    import torch
+    B, n, d, r, decay, path = CUT[name]
+    sigma = np.exp(-decay * np.arange(min(n, d)))
+    X = np.stack([I.make_spectrum_tokens(n, d, sigma, seed=b, dtype=I.FP32) for b in range(B)])
+    if B > 3:
+        X[1] = 0.0                        # nothing to cut: the others must not wait for it
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    ws = C.alloc_workspace(p)
+    Xd, sd = torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda()
+    out = C.select(p, Xd, sd, workspace=ws)
+    live = [b for b in range(B) if X[b].any()]
+    assert [C.lowrank_path(p, ws).tolist()[b] for b in live] == [path] * len(live)
+    for _ in range(3):
+        assert torch.equal(C.select(p, Xd, sd, workspace=ws)["c"], out["c"])
+    c = out["c"].cpu().numpy().astype(np.float64)
+    assert not c[[b for b in range(B) if b not in live]].any()
+    for b in live[:2] + live[-1:]:
+        ref = O.select(X[b].astype(np.float64), sf[b], O.Params(preselect_m=n, rank_r=r, keep_k=n // 3))
+        # as above: fp32 rounding, a residual of 1e-9 over the relative gap twice, the largest energy's rounding
+        err = np.abs(c[b] - ref["c"]) / np.maximum(ref["c"], 1e-6 * ref["c"].max())
+        assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
+
+
 # Batches whose products go on each width of tile of the fp64 kernel (gemm64.hip): images, tokens, rank; the last tile is a partial one.
 TILE_WIDTHS = {"64x80": (7, 950, 100), "64x48": (10, 500, 60), "64x96": (12, 1270, 300), "64x64": (4, 1270, 120), "64x32": (2, 1000, 180), "32x32": (4, 1000, 240)}
 
