@@ -339,33 +339,44 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const F* __restrict_
   if (lane == 0) stats[row] = make_double2((double)mw, 1.0 / z);
 }
 
-// s_query[b,i] = (1/HT) sum_{row < HT} exp(scale*S[b,row,i] - max_row) / Z_row, rows added in order (four
-// interleaved partial sums, so that four loads are in flight).
+// s_query[b,i] = (1/HT) sum_{row < HT} exp(scale*S[b,row,i] - max_row) / Z_row.  A workgroup has 64 tokens, each of its sixteen waves a
+// sixteenth of the rows (four interleaved partial sums, eight loads in flight), added up in order.
+// Bound by the latency of the loads: with all rows of a token in one thread 384 rows of 1849 tokens, six images, took 45 us on 48
+// workgroups, so 7 (576 fp32 tokens, four images, 512 rows: covspec_score 286, so 222).
+constexpr int kMeanWaves = 16;
 template <typename F>
-__global__ __launch_bounds__(256) void softmax_mean_kernel(const F* __restrict__ S, const double2* __restrict__ stats,
+__global__ __launch_bounds__(64 * kMeanWaves) void softmax_mean_kernel(const F* __restrict__ S, const double2* __restrict__ stats,
                                                             float* __restrict__ s_query, int HT, int N, double scale) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = blockIdx.y;
-  if (i >= N) return;
+  __shared__ double part[kMeanWaves][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = blockIdx.x * 64 + lane, b = blockIdx.y;
+  const int share = (HT + kMeanWaves - 1) / kMeanWaves, end = (w + 1) * share < HT ? (w + 1) * share : HT;
   const F* p = S + (long)b * HT * N + i;
   const double2* st = stats + (long)b * HT;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  int r = 0;
-  for (; r + 4 <= HT; r += 4) {
-    F v[4];
+  int r = w * share;
+  if (i < N) {
+    for (; r + 8 <= end; r += 8) {
+      F v[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = p[(long)(r + u) * N];
+      for (int u = 0; u < 8; ++u) v[u] = p[(long)(r + u) * N];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const double2 mz = st[r + u];
-      acc[u] = fma((double)exp(v[u] * (F)scale - (F)mz.x), mz.y, acc[u]);
+      for (int u = 0; u < 8; ++u) {
+        const double2 mz = st[r + u];
+        acc[u & 3] = fma((double)exp(v[u] * (F)scale - (F)mz.x), mz.y, acc[u & 3]);
+      }
+    }
+    for (; r < end; ++r) {
+      const double2 mz = st[r];
+      acc[0] = fma((double)exp(p[(long)r * N] * (F)scale - (F)mz.x), mz.y, acc[0]);
     }
   }
-  for (; r < HT; ++r) {
-    const double2 mz = st[r];
-    acc[0] = fma((double)exp(p[(long)r * N] * (F)scale - (F)mz.x), mz.y, acc[0]);
-  }
-  s_query[(long)b * N + i] = (float)(((acc[0] + acc[1]) + (acc[2] + acc[3])) / HT);
+  part[w][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  __syncthreads();
+  if (w != 0 || i >= N) return;
+  double sum = 0.0;
+#pragma unroll
+  for (int g = 0; g < kMeanWaves; ++g) sum += part[g][lane];
+  s_query[(long)b * N + i] = (float)(sum / HT);
 }
 
 // fp32 logits with N a multiple of 4 (the bf16 workloads): the same two passes with 16-byte loads, base-2
@@ -606,7 +617,7 @@ hipError_t launch_softmax_mean(const void* S, bool f64, const void* stats, float
     hipLaunchKernelGGL(softmax_mean_finish_kernel, dim3(blocks_for(BN, 256)), dim3(256), 0, st, (const double*)part, s_query, BN, segs, HT);
     return hipGetLastError();
   }
-  dim3 grid((N + 255) / 256, B), block(256);
+  dim3 grid((N + 63) / 64, B), block(64 * kMeanWaves);
   if (f64) hipLaunchKernelGGL((softmax_mean_kernel<double>), grid, block, 0, st, (const double*)S, (const double2*)stats, s_query, HT, N, scale);
   else hipLaunchKernelGGL((softmax_mean_kernel<float>), grid, block, 0, st, (const float*)S, (const double2*)stats, s_query, HT, N, scale);
   return hipGetLastError();

@@ -73,3 +73,26 @@ def test_copies_and_kept_tokens_of_a_single_image(C):
             decided += 1
             np.testing.assert_array_equal(idx[0].cpu().numpy(), ref["idx"])
     assert decided >= 3 and pairs >= 20
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("N,T,H", [(9, 1, 1), (63, 15, 1), (65, 4, 4), (129, 17, 1), (1025, 8, 16), (577, 125, 1)])
+def test_attention_scores_over_few_and_many_rows(C, dtype, N, T, H):
+    """The mean of the softmax over H * T rows, which sixteen waves share: fewer rows than waves, a row more than that, eight rows a
+    wave, a wave left without rows; tokens on both sides of a workgroup's 64.  Odd numbers of tokens: the form of multiples of four
+    is another one for bf16."""
+    import torch
+    d, B = 64, 2
+    rng = np.random.default_rng(N)
+    X, Q = ((0.5 * rng.standard_normal((B, n, d))).astype(np.float32) for n in (N, T))
+    Xd, Qd = (torch.from_numpy(a).cuda() for a in (X, Q))
+    if dtype == "bf16":
+        Xd, Qd = Xd.bfloat16(), Qd.bfloat16()
+    p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=T, n_heads=H, dtype=C.BF16 if dtype == "bf16" else C.FP32, keep_k=1, preselect_m=4, rank_r=2,
+                 rel_mode=C.REL_ATTN_SOFTMAX)
+    sq = C.score(p, Xd, None, Qd, None, None)[0].cpu().numpy()
+    for b in range(B):
+        ref = O.query_score_attention(Xd[b].double().cpu().numpy(), Qd[b].double().cpu().numpy(), H)
+        # fp32: fp64 inside, one rounding of the result and the exponential's.  bf16: a logit is an fp32 sum of d / H products, off by at
+        # most d / H roundings of their absolute sum (below 10 / 8 behind the scale), and its difference from the row's maximum by three
+        np.testing.assert_allclose(sq[b], ref, rtol=2e-7 if dtype == "fp32" else (d / H + 3) * 2.0 ** -24 * 2.5 + 3e-7)
