@@ -18,6 +18,7 @@
 // Result layout of both: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, col l%32.
 #include <type_traits>
 
+
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"
@@ -704,8 +705,8 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_dma_kernel(GemmArgs g, int ti
 // the kernels above, whatever the size of the product.  k-tile 64, a ring of NST 16 KB stages (swz rows) filled NST - 1
 // k-tiles ahead, one barrier per k-tile, the fragments of the next k-tile read while the current one is multiplied.  Bound by
 // the latency of the loads while a workgroup has its compute unit to itself (NST = 10, all of the LDS), else by the LDS and L2
-// traffic of the small tile (NST = 5, two workgroups per compute unit).  us, 128 x 128 tiles -> here: 32 x 4096 x 4096 36 -> 18,
-// 576 x 96 x 4096 36 -> 18, 444 x 3584 x 3584 48 -> 28.  (With k cut into up to 16 parts of partial products the same took 12
+// traffic of the small tile (NST = 5, two workgroups per compute unit).  us, 128 x 128 tiles -> here: 32 x 4096 x 4096 36 -> 17,
+// 576 x 96 x 4096 36 -> 17, 444 x 3584 x 3584 48 -> 28.  (With k cut into up to 16 parts of partial products the same took 12
 // to 31 and the launches that added the parts as much again as they saved, and the parts' roundings were others than those of
 // a large product: two tokens with scores 1e-7 apart could change places at a cut.)  Requires K % 64 == 0.
 template <int NST>
@@ -787,16 +788,103 @@ __global__ __launch_bounds__(THREADS, NST <= 5 ? 2 : 1) void gemm_few_kernel(Gem
     wr = next(wr);
   };
 #pragma unroll 1
-  for (int kt = 0; kt < nk; kt += 2) {
+  for (int kt = 0; kt + 1 < nk; kt += 2) {            // (with a way out in the middle the accumulators were moved to others every time)
     step(kt, a0, b0, a1, b1);
-    if (kt + 1 >= nk) break;
     step(kt + 1, a1, b1, a0, b0);
   }
+  if (nk & 1) step(nk - 1, a0, b0, a1, b1);
   __builtin_amdgcn_s_waitcnt(0x0070);
   float* C = (float*)g.C + (long)bo * g.strideC + (long)bi * g.strideC2;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int r = row0 + wm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3), c = col0 + wn * 32 + li;
+    if (r < g.M && c < g.N) C[(long)r * g.ldc + c] = acc[v];
+  }
+}
+
+// The same for products of so few tiles that most compute units have none: a workgroup is one wave with a 32 x 32 tile, the same sum over k
+// for every element, and loads for itself into a ring of NST 8 KB stages (no barrier).  Twice or four times the workgroups, no rows
+// of padding in a query of 32, and 56 KB of loads under way in each.  Bound by its chain of MFMAs, four per k-tile.
+template <int NST>
+__global__ __launch_bounds__(64) void gemm_wave_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int BT = 32, BK = 64, OPND = BT * ROWB, STAGE = 2 * OPND;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int lane = threadIdx.x, li = lane & 31, lh = lane >> 5;
+  const TileMap tmap = map_block(blockIdx.x, gridDim.x, tiles_m, tiles_n);
+  const int row0 = tmap.tm * BT, col0 = tmap.tn * BT;
+  const int bo = tmap.b / g.batch_inner, bi = tmap.b - bo * g.batch_inner;
+  const bf16_t* __restrict__ A = (const bf16_t*)g.A + (long)bo * g.strideA + (long)bi * g.strideA2;
+  const bf16_t* __restrict__ B = (const bf16_t*)g.B + (long)bo * g.strideB + (long)bi * g.strideB2;
+  // load j of an operand fills tile rows 8 j .. + 7, as above
+  const bf16_t* ga[4];
+  const bf16_t* gb[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    ga[j] = A + (long)min(row0 + r, g.M - 1) * g.lda + c * 8;
+    gb[j] = B + (long)min(col0 + r, g.N - 1) * g.ldb + c * 8;
+  }
+  const int nk = g.K / BK;
+  auto issue = [&](int kt, int st) {
+    const long k = (long)BK * min(kt, nk - 1);
+    unsigned char* s = smem + st * STAGE;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga[j] + k),
+                                       (__attribute__((address_space(3))) void*)(s + j * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb[j] + k),
+                                       (__attribute__((address_space(3))) void*)(s + OPND + j * 1024), 16, 0, 0);
+    }
+  };
+  int off[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) off[ks] = swz(li, 2 * ks + lh);
+  auto frags = [&](int st, bf16x8_t (&fa)[4], bf16x8_t (&fb)[4]) {
+    const unsigned char* s = smem + st * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      fa[ks] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(s + off[ks]));
+      fb[ks] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(s + OPND + off[ks]));
+    }
+  };
+  f32x16_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  auto next = [](int st) { return st + 1 == NST ? 0 : st + 1; };
+  constexpr int kFirst = 8 * (NST - 2), kSteady = 8 * (NST - 3);        // vmcnt counts to 63
+  static_assert(8 * (NST - 1) <= 63 && NST > 3, "");
+  constexpr int kWaitFirst = 0x0070 | (kFirst & 15) | (kFirst >> 4 << 14), kWaitSteady = 0x0070 | (kSteady & 15) | (kSteady >> 4 << 14);
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s) issue(s, s);
+  __builtin_amdgcn_s_waitcnt(kWaitFirst);             // k-tile 0 has landed
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8_t a0[4], b0[4], a1[4], b1[4];
+  frags(0, a0, b0);
+  int rd = 1, wr = NST - 1;
+  // Per k-tile: wait until the next one has landed and the fragments of this one are in registers, start the loads NST - 1 ahead into the
+  // stage of the previous one
+  auto step = [&](int kt, bf16x8_t (&fa)[4], bf16x8_t (&fb)[4], bf16x8_t (&na)[4], bf16x8_t (&nb)[4]) {
+    __builtin_amdgcn_s_waitcnt(kWaitSteady);
+    __builtin_amdgcn_sched_barrier(0);
+    frags(rd, na, nb);
+    issue(kt + NST - 1, wr);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    rd = next(rd);
+    wr = next(wr);
+  };
+#pragma unroll 1
+  for (int kt = 0; kt + 1 < nk; kt += 2) {            // (with a way out in the middle the accumulators were moved to others every time)
+    step(kt, a0, b0, a1, b1);
+    step(kt + 1, a1, b1, a0, b0);
+  }
+  if (nk & 1) step(nk - 1, a0, b0, a1, b1);
+  __builtin_amdgcn_s_waitcnt(0x0070);
+  float* C = (float*)g.C + (long)bo * g.strideC + (long)bi * g.strideC2;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int r = row0 + 8 * (v >> 2) + 4 * lh + (v & 3), c = col0 + li;
     if (r < g.M && c < g.N) C[(long)r * g.ldc + c] = acc[v];
   }
 }
@@ -807,8 +895,22 @@ __global__ __launch_bounds__(THREADS, NST <= 5 ? 2 : 1) void gemm_few_kernel(Gem
 // small tiles win beyond it too: 260 of batch 20 88 / 73.)
 constexpr long kFewTiles128 = 192;
 
+// 32 x 32 tiles up to which a workgroup is one wave: two of them share a compute unit's LDS.  us, gemm_few_kernel / one wave: 54 tiles
+// (576 x 96 x 4096) 17.1 / 13.4, 128 (32 x 4096 x 4096) 17.3 / 13.5, 384 (96 x 4096 x 4096) 18.2 / 15.1, 512 18.2 / 15.4; 576
+// (288 x 2048 x 2048) 11.1 / 16.9, 768 18.7 / 28.2.
+constexpr long kFewWaves = 512;
 inline hipError_t launch_few(const GemmArgs& g, hipStream_t stream) {
   constexpr int STAGE = 2 * 64 * ROWB;
+  const int waves_m = (g.M + 31) / 32, waves_n = (g.N + 31) / 32;
+  const long nwaves = (long)waves_m * waves_n * g.batch;
+  if (nwaves <= kFewWaves) {
+    constexpr int NST = 8;
+    static PerDeviceInt grown;
+    const hipError_t e = ensure_dynamic_lds(grown, (const void*)gemm_wave_kernel<NST>, NST * STAGE / 2);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gemm_wave_kernel<NST>, dim3((unsigned)nwaves), dim3(64), NST * STAGE / 2, stream, g, waves_m, waves_n);
+    return hipGetLastError();
+  }
   const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
   const long nblocks = (long)tiles_m * tiles_n * g.batch;
   if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;

@@ -37,6 +37,21 @@ def test_an_image_scores_the_same_alone_and_in_a_batch(C, mode, N, d, T, weights
     assert torch.equal(got[0], got[1][:1]) and torch.equal(got[1], got[2][:80])
 
 
+@pytest.mark.parametrize("d", [64, 192, 1024])
+def test_scores_on_both_sides_of_the_one_wave_products(C, d):
+    """36 images of 200 tokens and 16 query rows: 504 tiles of 32 x 32 of the inner products, a wave each; one image more: 518, and
+    tiles of 64 x 64.  1, 3 and 16 k-tiles.  Equal to the bit."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X, Q = (torch.randn(37, n, d, generator=g, device="cuda").bfloat16() for n in (200, 16))
+    got = []
+    for B in (36, 37):
+        p = C.Params(batch=B, n_tokens=200, d_model=d, n_query=16, n_heads=2, dtype=C.BF16, keep_k=4, preselect_m=8, rank_r=2, rel_mode=C.REL_COSINE_MAX)
+        got.append(C.score(p, X[:B].contiguous(), None, Q[:B].contiguous(), None, None)[0])
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1][:36])
+
+
 def test_copies_and_kept_tokens_of_a_single_image(C):
     """576 x 4096 images with exact copies and 20x outliers, one at a time: copies have bit-equal scores and energies, and wherever
     the fp64 values at both cuts are further apart than rounding can move them the kept tokens are the oracle's."""
