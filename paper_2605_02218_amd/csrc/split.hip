@@ -1199,16 +1199,23 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
     small = t16 <= held / 8;
   }
   const bool w64 = ordered || P == 64;
-  if (B <= (w64 ? kCutImages / 2 : kCutImages)) {
+  auto ck = w64 ? cut_kernel<64> : cut_kernel<SN>;
+  // A wave per SIMD; an image's workgroups are an eighth of what the device holds at most, as above.  Eight windows of 64: 47 us by
+  // split_kernel, 48 with half the points and 64 with two waves a SIMD.
+  const int trials = w64 ? kTrials : kTrials / 2;
+  const size_t window = w64 ? 64 * 65 * 8 : SN * (SN + 1) * 8;
+  bool count = B <= (w64 ? kCutImages / 2 : kCutImages);
+  if (count) {
+    static PerDeviceInt grown[2], room[2];
+    int held = 0;
+    if ((e = ensure_dynamic_lds(grown[w64], (const void*)ck, window)) != hipSuccess) return e;
+    if ((e = resident_workgroups(room[w64], ck, 256, window, &held)) != hipSuccess) return e;
+    count = trials / 4 <= held / 8;
+  }
+  if (count) {
     CutArea* area = (CutArea*)((char*)scratch + split_base_bytes(B, P));
-    // A wave per SIMD; an image's workgroups are an eighth of what the device holds at most, as below.  Eight windows of 64: 47 us by
-    // split_kernel, 48 with half the points and 64 with two waves a SIMD.
-    const int trials = w64 ? kTrials : kTrials / 2;
-    const size_t window = w64 ? 64 * 65 * 8 : SN * (SN + 1) * 8, cut_lds = window > (size_t)P * 8 ? window : (size_t)P * 8;
-    static PerDeviceInt grown[2];
+    const size_t cut_lds = window > (size_t)P * 8 ? window : (size_t)P * 8;
     const dim3 cg((unsigned)(B * (trials / 4) + B * (P / 16)));
-    auto ck = w64 ? cut_kernel<64> : cut_kernel<SN>;
-    if ((e = ensure_dynamic_lds(grown[w64], (const void*)ck, w64 ? 64 * 65 * 8 : SN * (SN + 1) * 8)) != hipSuccess) return e;
     hipLaunchKernelGGL(ck, cg, dim3(256), cut_lds, st, H, P, stride, B, r, ordered, trials, off, link, ctl, area, epoch, skip, again, small ? X0 : nullptr,
                        X1, Y, barrier_limit_ticks());
     if (again) hipLaunchKernelGGL(split_kernel, dim3((unsigned)B), dim3(256), 0, st, H, P, stride, B, r, false, off, link, ctl, skip, again, true, X0, X1, Y);
