@@ -424,40 +424,43 @@ __device__ __forceinline__ f64x4_t load4_f64(const float* p) {
 // partial tiles added through LDS in a fixed order.  Twice the operand traffic of a 64 x 64 tile but four times the
 // workgroups and a sixteenth of the dependent MFMAs.  us, 64 x 64 register-staged -> here: 16 x 1024 x 1024 106 -> 15.7,
 // 576 x 16 x 1024 96 -> 15.4, 128 x 128 x 1024 with row lists 138 -> 16.6, 576 x 1024 x 1024 row norms 145 -> 34.  Requires K % 64 == 0.
+// A 32 x 32 tile is K / 64 us of its compute unit's MFMAs: where that leaves units idle the tiles are 16 x 16 (X = 1), eight groups in flight, every
+// sum in the same order (128 x 128 x 1024 14.1 -> 7.0).
 // EPI: EPI_STORE_F64, or EPI_ROWNORM2 with one partial per 32 columns.
-template <typename TA, typename TB, int EPI>
+template <typename TA, typename TB, int EPI, int X = 2>
 __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  __shared__ double part[4 * 32 * 33];
+  constexpr int TILE = 16 * X, ROW = TILE + 1, PART = TILE * ROW;
+  __shared__ double part[4 * PART];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i16 = lane & 15, kq = lane >> 4;
   const int per = tiles_m * tiles_n;
   const int b = blockIdx.x / per, pidx = blockIdx.x - b * per, tm = pidx / tiles_n, tn = pidx - tm * tiles_n;
   if (g.skip && g.skip[b] > g.skip_if) return;
   if (g.lower_only && tn > tm) return;
-  const int row0 = tm * 32, col0 = tn * 32, kn = g.K >> 2;
+  const int row0 = tm * TILE, col0 = tn * TILE, kn = g.K >> 2;
   const TA* Ab = (const TA*)g.A + (long)b * g.strideA;
   const TB* Bb = (const TB*)g.B + (long)b * g.strideB;
-  const TA* ar[2];
-  const TB* br[2];
+  const TA* ar[X];
+  const TB* br[X];
 #pragma unroll
-  for (int x = 0; x < 2; ++x) {
+  for (int x = 0; x < X; ++x) {
     long ra = min(row0 + 16 * x + i16, g.M - 1), rb = min(col0 + 16 * x + i16, g.N - 1);
     if (g.gatherA) ra = g.gatherA[(long)b * g.gstrideA + ra];
     if (g.gatherB) rb = g.gatherB[(long)b * g.gstrideB + rb];
     ar[x] = Ab + ra * g.lda + w * kn + 4 * kq;
     br[x] = Bb + rb * g.ldb + w * kn + 4 * kq;
   }
-  constexpr int DEPTH = 3;
+  constexpr int DEPTH = X == 1 ? 8 : 3;
   double* C = (double*)g.C + (long)b * g.strideC;
-  f64x4_t acc[2][2], fa[DEPTH][2], fb[DEPTH][2];
+  f64x4_t acc[X][X], fa[DEPTH][X], fb[DEPTH][X];
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < X; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    for (int y = 0; y < X; ++y) acc[x][y] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
   const int nc = kn >> 4;
   auto load = [&](int s, int c) {
     if (c < nc) {
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
+      for (int x = 0; x < X; ++x) {
         fa[s][x] = load4_f64(ar[x] + 16 * c);
         fb[s][x] = load4_f64(br[x] + 16 * c);
       }
@@ -473,24 +476,24 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-          for (int x = 0; x < 2; ++x)
+          for (int x = 0; x < X; ++x)
 #pragma unroll
-            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s][x][k], fb[s][y][k], acc[x][y], 0, 0, 0);
+            for (int y = 0; y < X; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s][x][k], fb[s][y][k], acc[x][y], 0, 0, 0);
         load(s, c + s + DEPTH);
       }
     }
   }
-  double* out = part + w * (32 * 33);
+  double* out = part + w * PART;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < X; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < X; ++y)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) out[(16 * x + 4 * v + kq) * 33 + 16 * y + i16] = acc[x][y][v];
+      for (int v = 0; v < 4; ++v) out[(16 * x + 4 * v + kq) * ROW + 16 * y + i16] = acc[x][y][v];
   __syncthreads();
   auto sum = [&](int i, int j) {
-    const double* q = part + i * 33 + j;
-    return (q[0] + q[32 * 33]) + (q[2 * 32 * 33] + q[3 * 32 * 33]);
+    const double* q = part + i * ROW + j;
+    return (q[0] + q[PART]) + (q[2 * PART] + q[3 * PART]);
   };
   if (EPI == EPI_ROWNORM2) {                              // eight lanes per row, four columns each; columns beyond N count as zero
     const int i = tid >> 3, j0 = (tid & 7) * 4;
@@ -504,8 +507,8 @@ __global__ __launch_bounds__(256) void gemm64_small_kernel(GemmArgs g, int tiles
     return;
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = tid + 256 * q, i = e >> 5, j = e & 31;
+  for (int q = 0; q < X * X; ++q) {
+    const int e = tid + 256 * q, i = e / TILE, j = e % TILE;
     if (row0 + i < g.M && col0 + j < g.N) C[(long)(row0 + i) * g.ldc + col0 + j] = sum(i, j);
     if (g.mirror && tn != tm && row0 + j < g.M && col0 + i < g.N) C[(long)(col0 + i) * g.ldc + row0 + j] = sum(j, i);
   }
@@ -617,6 +620,16 @@ template <typename TA, typename TB, int EPI>
 hipError_t launch_small(const GemmArgs& g, hipStream_t stream) {
   const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, blocks = m32 * n32 * g.batch;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  if constexpr (EPI == EPI_STORE_F64) {
+    // 16 x 16 tiles while a compute unit gets one.  us, 32 x 32 / here: 36 (576 x 16 x 1024) 13.3 / 8.2, 64 (16 x 1024 x 1024) 13.2 / 8.3, 171 (288 x 288
+    // x 1024, the lower ones) 14.4 / 11.1, 256 (64 x 1024 x 1024) 14.7 / 8.6, 256 of K = 4096 51 / 28; 296 (577 x 32 x 768, batch 4) 12.1 / 11.7, 384
+    // 14.9 / 14.8, 380 (300 x 300 x 1024, batch 2, the lower ones) 14.8 / 16.0, 640 15.2 / 20.6.
+    const long m16 = (g.M + 15) / 16, n16 = (g.N + 15) / 16;
+    if ((g.lower_only ? m16 * (m16 + 1) / 2 : m16 * n16) * g.batch <= kUnits) {
+      hipLaunchKernelGGL((gemm64_small_kernel<TA, TB, EPI, 1>), dim3((unsigned)(m16 * n16 * g.batch)), dim3(256), 0, stream, g, (int)m16, (int)n16);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((gemm64_small_kernel<TA, TB, EPI>), dim3((unsigned)blocks), dim3(256), 0, stream, g, (int)m32, (int)n32);
   return hipGetLastError();
 }

@@ -52,6 +52,25 @@ def test_scores_on_both_sides_of_the_one_wave_products(C, d):
     assert torch.equal(got[0], got[1][:36])
 
 
+@pytest.mark.parametrize("N,d,T", [(100, 320, 20), (97, 64, 17)])
+def test_fp32_scores_on_both_sides_of_the_16_x_16_tiles(C, N, d, T):
+    """fp64 products of 14 tiles of 16 x 16 an image: 252 tiles, one per compute unit, and 266, which are tiles of 32 x 32; alone the
+    query projection is on the small ones too.  Remainders in both directions, 1 and 5 steps of 16 k per wave.  Equal to the bit."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X, Q = (torch.randn(19, n, d, generator=g, device="cuda") for n in (N, T))
+    Wq, Wk = (torch.randn(d, d, generator=g, device="cuda") / d ** 0.5 for _ in range(2))
+    got = []
+    for B in (1, 18, 19):
+        p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=T, n_heads=1, dtype=C.FP32, keep_k=4, preselect_m=8, rank_r=2, rel_mode=C.REL_COSINE_MAX)
+        got.append(C.score(p, X[:B].contiguous(), None, Q[:B].contiguous(), Wq, Wk)[0])
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1][:1]) and torch.equal(got[1], got[2][:18])
+    x, q = X[0].double().cpu().numpy(), Q[0].double().cpu().numpy()
+    ref = O.query_score_cosine(O.embed(x, Wk.double().cpu().numpy()), O.embed(q, Wq.double().cpu().numpy()))
+    np.testing.assert_allclose(got[0][0].cpu().numpy(), ref, rtol=2.0 ** -23)      # fp64 inside, rounded once
+
+
 def test_copies_and_kept_tokens_of_a_single_image(C):
     """576 x 4096 images with exact copies and 20x outliers, one at a time: copies have bit-equal scores and energies, and wherever
     the fp64 values at both cuts are further apart than rounding can move them the kept tokens are the oracle's."""
