@@ -213,7 +213,8 @@ def roofline_for(w, p, p_modes, stages, probe_ms, C):
     }
     n_probe, pr, pc, pk = C.probe_launches(p)
     if n_probe > 0 and probe_ms > 0:
-        cand["lowrank_product"] = ("gemm64_dma_kernel", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
+        small = tiles(pr, pc, 16, B) <= 256 and pk % 64 == 0
+        cand["lowrank_product"] = ("gemm64_tile16_kernel" if small else "gemm64_dma_kernel", "mfma", PEAK["mfma_fp64_TFLOPs"], "TFLOP/s",
                                    2.0 * B * pr * pc * pk / 1e12, n_probe, probe_ms)
     elif p_modes[1] == 1:
         cand["lowrank"] = (greedy_kernel_name(B, M, k), "alu", PEAK["valu_fp64_TFLOPs"], "TFLOP/s", 1.0 * B * M * k * k / 1e12, 1,

@@ -11,6 +11,7 @@
 //   gemm64_kernel        any of the storage types, row lists, any K and alignment: 64 x 64 tiles, operands converted to fp64 on
 //                        their way through registers into LDS.
 //   gemm64_dma_kernel    fp64 x fp64 (the block iteration) and bf16 x bf16: direct-to-LDS loads, tiles of 64 x 96 to 32 x 32.
+//   gemm64_tile16_kernel  the fp64 products of so few 16 x 16 tiles that a compute unit gets one at most
 //   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
 //   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
 // gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
@@ -419,6 +420,87 @@ __device__ __forceinline__ f64x4_t load4_f64(const float* p) {
   return (f64x4_t){(double)v[0], (double)v[1], (double)v[2], (double)v[3]};
 }
 
+// The products of gemm64_dma_kernel where 16 x 16 tiles are one per compute unit at most: the four waves take a quarter of k each, operands straight from global memory, the partial
+// tiles added in order by the first wave.  Bound by latency (192 x 320 x 320 is 0.5 us of MFMAs): no ring to fill, no barriers but one, a quarter of
+// the MFMAs in a chain.
+__global__ __launch_bounds__(256) void gemm64_tile16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int DEPTH = 8;
+  __shared__ double part[3 * 4 * 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), i16 = lane & 15, kq = lane >> 4;
+  const bool triangle = g.lower_only || g.frag;
+  const int per = triangle ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  const int gid = regroup_xcd(blockIdx.x, gridDim.x);
+  const int b = gid / per, pidx = gid - b * per;
+  if (g.skip && g.skip[b] > g.skip_if) return;
+  int tm, tn;
+  if (triangle) {
+    int x = (int)((sqrtf(8.0f * (float)pidx + 1.0f) - 1.0f) * 0.5f);
+    while (x * (x + 1) / 2 > pidx) --x;
+    while ((x + 1) * (x + 2) / 2 <= pidx) ++x;
+    const int y = pidx - x * (x + 1) / 2;
+    tm = g.frag ? y : x;
+    tn = g.frag ? x : y;
+  } else {
+    tm = pidx / tiles_n;
+    tn = pidx - tm * tiles_n;
+  }
+  const int row0 = tm * 16, col0 = tn * 16, kn = g.K >> 2, nc = kn >> 4;
+  const bool moved = g.sel && g.sel[b];
+  const double* A = (const double*)g.A + (long)b * g.strideA + (moved ? g.selA : 0);
+  const double* B = (const double*)g.B + (long)b * g.strideB + (moved ? g.selB : 0);
+  const double* ar = A + (long)min(row0 + i16, g.M - 1) * g.lda + w * kn + 4 * kq;
+  const double* br = B + (long)min(col0 + i16, g.N - 1) * g.ldb + w * kn + 4 * kq;
+  f64x4_t fa[DEPTH], fb[DEPTH];
+  auto load = [&](int s, int c) {
+    if (c < nc) {
+      fa[s] = load4_f64(ar + 16 * c);
+      fb[s] = load4_f64(br + 16 * c);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < DEPTH; ++s) load(s, s);
+  double* C = (double*)g.C + (long)b * g.strideC + (moved ? g.selC : 0);
+  const double t = g.cheb ? g.cheb[(long)b * g.cheb_stride] : 0.0, scale = cheb_scale(g, t), rt = 1.0 / t;
+  f64x4_t acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  if (t != 0.0 && w == 0) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = cheb_start(g, A, C, rt, min(row0 + 4 * v + kq, g.M - 1), min(col0 + i16, g.N - 1));
+  }
+#pragma unroll 1
+  for (int c = 0; c < nc; c += DEPTH) {
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) {
+      if (c + s < nc) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s][k], fb[s][k], acc, 0, 0, 0);
+        load(s, c + s + DEPTH);
+      }
+    }
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[((w - 1) * 4 + v) * 64 + lane] = acc[v];
+  }
+  __syncthreads();
+  if (w > 0) return;
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] += part[(q * 4 + v) * 64 + lane];
+  if (g.frag) {
+    frag_store(C + ((long)tn * (g.N >> 4) + tm) * kFragTile, lane, acc);
+    return;
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int r = row0 + 4 * v + kq, c = col0 + i16;
+    if (r < g.M && c < g.N) {
+      C[(long)r * g.ldc + c] = scale * acc[v];
+      if (g.mirror && tn != tm) C[(long)c * g.ldc + r] = acc[v];
+    }
+  }
+}
+
 // Problems of few tiles with an fp32 operand and optional row lists: 32 x 32 tile, the four waves take a
 // quarter of k each, operands straight from global memory (rows in pieces of 16 elements, three such groups in flight), the
 // partial tiles added through LDS in a fixed order.  Twice the operand traffic of a 64 x 64 tile but four times the
@@ -666,6 +748,15 @@ hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
   const bool triangle = g.lower_only || g.frag;
   if ((triangle && g.M != g.N) || (g.frag && g.N % 64 != 0)) return hipErrorInvalidValue;
   const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64;
+  if constexpr (std::is_same<TS, double>::value) {
+    const long m16 = (g.M + 15) / 16, n16 = (g.N + 15) / 16, t16 = (triangle ? m16 * (m16 + 1) / 2 : m16 * n16) * g.batch;
+    // us, the tiles below / here, back to back: 144 (192 x 192 x 192) 5.5 / 4.6, 240 (192 x 320 x 320) 7.4 / 6.3, 256 (128 x 256 x 256, batch 2) 6.8 / 5.7, 78
+    // (192 x 192 x 1664, the triangle) 20.7 / 14.7; 312 (the same, batch 4) 22.0 / 25.9, 320 18.3 / 21.9, 480 (192 x 320 x 320, batch 2) 7.6 / 8.8.
+    if (t16 >= 1 && t16 <= kUnits && g.K % 64 == 0) {
+      hipLaunchKernelGGL(gemm64_tile16_kernel, dim3((unsigned)t16), dim3(256), 0, stream, g, (int)m16, (int)n16);
+      return hipGetLastError();
+    }
+  }
   const auto fullest = [](long tiles) { return (double)((tiles + kUnits - 1) / kUnits); };
   const long t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
   double least = 1.18 * fullest(t32);

@@ -141,7 +141,9 @@ def test_cut_of_few_images(C, name):
 
 
 # Batches whose products go on each width of tile of the fp64 kernel (gemm64.hip): images, tokens, rank; the last tile is a partial one.
-TILE_WIDTHS = {"64x80": (7, 950, 100), "64x48": (10, 500, 60), "64x96": (12, 1270, 300), "64x64": (4, 1270, 120), "64x32": (2, 1000, 180), "32x32": (4, 1000, 240)}
+TILE_WIDTHS = {"64x80": (7, 950, 100), "64x48": (10, 500, 60), "64x96": (12, 1270, 300), "64x64": (4, 1270, 120), "64x32": (2, 1000, 180), "32x32": (4, 1000, 240),
+               # a 16 x 16 tile per compute unit: 128 x 256 of two images, 192 x 320 of one; and beyond
+               "16x16-most": (2, 250, 60), "16x16": (1, 310, 100), "16x16-over": (2, 310, 100)}
 
 
 @pytest.mark.parametrize("name", list(TILE_WIDTHS))
