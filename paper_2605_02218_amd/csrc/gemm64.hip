@@ -7,11 +7,11 @@
 // rounding left; so does the Gram matrix of the greedy picks from bf16 rows.  (2) The low-rank stage, whose block iteration on
 // the fp64 Gram matrix is a sequence of fp64 products.
 //
-// Four kernels:
+// Five kernels:
 //   gemm64_kernel        any of the storage types, row lists, any K and alignment: 64 x 64 tiles, operands converted to fp64 on
 //                        their way through registers into LDS.
 //   gemm64_dma_kernel    fp64 x fp64 (the block iteration) and bf16 x bf16: direct-to-LDS loads, tiles of 64 x 96 to 32 x 32.
-//   gemm64_tile16_kernel  the fp64 products of so few 16 x 16 tiles that a compute unit gets one at most
+//   gemm64_tile16_kernel fp64 products of so few 16 x 16 tiles that a compute unit gets one at most
 //   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
 //   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
 // gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
