@@ -451,7 +451,10 @@ __global__ __launch_bounds__(JT) void jacobi_solve_kernel(double* A, const doubl
       if (lane == 0) len2b[k] = sqrt(s);
     }
   }
-  // the last of the image's workgroups has everybody's rows, and everybody's failures, before it
+  // The last of the image's workgroups has everybody's rows, and everybody's failures, before it: every wave waits for its own stores,
+  // as in image_barrier_wait (a wait of one thread behind a bare barrier leaves those of the other waves on their way to the L2, and what is
+  // there then is the squared lengths of the last sweep).
+  __builtin_amdgcn_s_waitcnt(0x0070);                  // vmcnt(0) lgkmcnt(0)
   __syncthreads();
   if (tid == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
