@@ -312,55 +312,60 @@ __device__ __noinline__ double jacobi_visit(double* Ab, double* len2b, int nP, i
   return wave_max(meas2);
 }
 
-// c[i] = sum over the r longest rows k of A (n x nP, lengths `lam`) of A[k][i]^2 / |row k|, rows added in ascending k, by one workgroup.
-// failed: the rows are no result, and NaN the energies.
-__device__ __noinline__ void energies_of(const double* A, const double* lam, int n, int nP, int r, bool failed, float* c) {
-  const int tid = threadIdx.x;
-  if (failed) {
-    for (int i = tid; i < n; i += JT) c[i] = __uint_as_float(0x7fc00000u);
-    return;
-  }
-  double* slam = Hs;                                       // n <= 4096
+// c[i] = sum over the r longest rows k of A (n x nP, lengths `lam`) of A[k][i]^2 / |row k| for the columns i0 .. i0 + 63 (below n), by one
+// workgroup: a lane per column, each wave a share of the rows in ascending k, the shares added in order.  Bound by the latency of the
+// loads, eight rows of a wave at a time.  Solves with all columns in the last workgroup of the
+// image, and so, ms: 640 rows 26.1 and 25.9, 1280 75.1 and 74.4, 2500 412.7 and 411.2.
+__device__ __noinline__ void energies_of(const double* A, const double* lam, int n, int nP, int r, int i0, float* c) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  double *slam = Hs, *part = Ws + 512;                     // n <= 4096; [JW][64]
   unsigned char* sel = (unsigned char*)Ws;
-  static_assert(PR * HP >= 4096, "");
+  static_assert(PR * HP >= 4096 && 512 * 8 >= 4096 && 512 + JT <= PR * HP, "");
   for (int k = tid; k < n; k += JT) slam[k] = lam[k];
   __syncthreads();
   for (int k = tid; k < n; k += JT) {
     const double v = slam[k];
     int rank = 0;
     for (int j = 0; j < n; ++j) {
-      const double w = slam[j];
-      rank += (w > v || (w == v && j < k)) ? 1 : 0;
+      const double u = slam[j];
+      rank += (u > v || (u == v && j < k)) ? 1 : 0;
     }
     sel[k] = (rank < r && v > 0.0) ? 1 : 0;
   }
   __syncthreads();
-  // the selected rows' reciprocal lengths in place of the lengths: a row then costs a thread one load and two
-  // multiplications, eight rows' loads in flight
+  // the selected rows' reciprocal lengths in place of the lengths: a row then costs a thread one load and two multiplications
   for (int k = tid; k < n; k += JT) slam[k] = sel[k] ? 1.0 / slam[k] : 0.0;
   __syncthreads();
-  for (int i = tid; i < n; i += JT) {
+  const int share = (n + JW - 1) / JW, end = (w + 1) * share < n ? (w + 1) * share : n, i = i0 + lane;
+  double acc = 0.0;
+  if (i < n) {
     const double* Ai = A + i;
-    double acc = 0.0;
-    int k = 0;
-    for (; k + 8 <= n; k += 8) {
+    int k = w * share;
+    for (; k + 8 <= end; k += 8) {
       double a[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) a[u] = Ai[(long)(k + u) * nP];
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc += sel[k + u] ? a[u] * a[u] * slam[k + u] : 0.0;    // an unselected row may hold anything
     }
-    for (; k < n; ++k) {
+    for (; k < end; ++k) {
       const double a = Ai[(long)k * nP];
       acc += sel[k] ? a * a * slam[k] : 0.0;
     }
-    c[i] = (float)acc;
   }
+  part[tid] = acc;
+  __syncthreads();
+  if (w != 0 || i >= n) return;
+  double sum = 0.0;
+#pragma unroll
+  for (int g = 0; g < JW; ++g) sum += part[64 * g + lane];
+  c[i] = (float)sum;
 }
 
 // The whole solve of all images that have no energies yet: workgroup (image b, slot pr) visits the pair `pr` of every tournament round
 // of every sweep; after a sweep, slot 0 decides convergence and re-measures which rows are the r longest.  At the end each workgroup
-// measures its rows, and the last one of the image adds up the energies (or says that there are none).  With `src` the matrix is copied
+// measures its rows, and when all have, it adds up the energies of its 64 columns; if one of them gave up the last one of the image says that
+// there are none.  With `src` the matrix is copied
 // from there first.  Where no image is left to solve every workgroup returns at once, in front of the ticket; the start values, the
 // lengths and the energies in launches of their own cost every call three more of these returns, 2 to 4 us each (up to 41 for the lengths of
 // sixty-four images of 640).
@@ -450,22 +455,24 @@ __global__ __launch_bounds__(JT) void jacobi_solve_kernel(double* A, const doubl
       s = wave_sum(s);
       if (lane == 0) len2b[k] = sqrt(s);
     }
+    target += npairs;
+    alive = image_barrier_wait(&cb->bar, target, &s_flag, limit_ticks);
+    if (alive) energies_of(Ab, len2b, n, nP, r, pr * PR, c + (long)b * n);
+    else if (img_status && tid == 0) img_status[b] = 1;
   }
-  // The last of the image's workgroups has everybody's rows, and everybody's failures, before it: every wave waits for its own stores,
-  // as in image_barrier_wait (a wait of one thread behind a bare barrier leaves those of the other waves on their way to the L2, and what is
-  // there then is the squared lengths of the last sweep).
+  // The last of the image's workgroups has everybody's energies, and everybody's failures, before it: every wave waits for its own
+  // stores, as in image_barrier_wait (behind a bare barrier those of the other waves may still be on their way to the L2).
   __builtin_amdgcn_s_waitcnt(0x0070);                  // vmcnt(0) lgkmcnt(0)
   __syncthreads();
   if (tid == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     const unsigned int at = __hip_atomic_fetch_add(&cb->finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    s_flag = at + 1u == (unsigned int)npairs;
+    s_flag = at + 1u == (unsigned int)npairs && __hip_atomic_load(&cb->bar.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
   }
   __syncthreads();
   if (!s_flag) return;
-  const bool failed = __hip_atomic_load(&cb->bar.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  energies_of(Ab, len2b, n, nP, r, failed, c + (long)b * n);
+  for (int i = tid; i < n; i += JT) c[(long)b * n + i] = __uint_as_float(0x7fc00000u);
 }
 
 }  // namespace

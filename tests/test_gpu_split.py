@@ -62,6 +62,35 @@ def test_energies_match_the_oracle(C, name):
         np.testing.assert_array_equal(idx[b], ref["idx"])
 
 
+# Full solves: images, tokens, width, rank, decay.  Each workgroup adds up 64 columns, a wave an eighth of the rows: one column beyond two
+# workgroups' columns and a column short, rows that eight do not divide, several images of which one has no tokens of any length.
+FULL = {"129": (1, 129, 160, 64, 0.05), "191": (2, 191, 224, 100, 0.02), "192": (3, 192, 224, 100, 0.02), "577": (2, 577, 608, 420, 0.005)}
+
+
+@pytest.mark.parametrize("name", list(FULL))
+def test_energies_of_a_full_solve(C, name):
+    import torch
+    B, n, d, r, decay = FULL[name]
+    sigma = np.exp(-decay * np.arange(n))
+    X = np.stack([I.make_spectrum_tokens(n, d, sigma, seed=b, dtype=I.FP32) for b in range(B)])
+    if B > 2:
+        X[1] = 0.0
+    sf = np.stack([np.random.default_rng(b).random(n).astype(np.float32) for b in range(B)])
+    p = C.Params(batch=B, n_tokens=n, d_model=d, n_query=1, dtype=C.FP32, keep_k=n // 3, preselect_m=n, rank_r=r)
+    ws = C.alloc_workspace(p)
+    out = C.select(p, torch.from_numpy(X).cuda(), torch.from_numpy(sf).cuda(), workspace=ws)
+    assert C.lowrank_path(p, ws).tolist() == [0] * B and C.image_status(p, ws).tolist() == [0] * B
+    c = out["c"].cpu().numpy().astype(np.float64)
+    for b in range(B):
+        if not X[b].any():
+            assert not c[b].any()
+            continue
+        ref = O.select(X[b].astype(np.float64), sf[b], O.Params(preselect_m=n, rank_r=r, keep_k=n // 3))["c"]
+        # c is rounded to fp32 (6e-8); a converged sweep leaves 1e-10 of a row in the others, over the relative gap
+        err = np.abs(c[b] - ref) / np.maximum(ref, 1e-6 * ref.max())
+        assert err.max() < 6e-8 + 2e-10 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
+
+
 # The sign iteration of small matrices without meetings (split.hip) at its edges, and the one with meetings beyond: batch, tokens,
 # width, rank, decay, way.  Order 64, 128, 192 and 256, each with as many images as it takes and one more.
 SMALL_SIGN = {
