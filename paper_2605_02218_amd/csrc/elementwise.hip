@@ -339,43 +339,96 @@ __global__ __launch_bounds__(256) void softmax_stats_kernel(const F* __restrict_
   if (lane == 0) stats[row] = make_double2((double)mw, 1.0 / z);
 }
 
-// s_query[b,i] = (1/HT) sum_{row < HT} exp(scale*S[b,row,i] - max_row) / Z_row.  A workgroup has 64 tokens, each of its sixteen waves a
-// sixteenth of the rows (four interleaved partial sums, eight loads in flight), added up in order.
-// Bound by the latency of the loads: with all rows of a token in one thread 384 rows of 1849 tokens, six images, took 45 us on 48
-// workgroups, so 7 (576 fp32 tokens, four images, 512 rows: covspec_score 286, so 222).
-constexpr int kMeanWaves = 16;
-template <typename F>
-__global__ __launch_bounds__(64 * kMeanWaves) void softmax_mean_kernel(const F* __restrict__ S, const double2* __restrict__ stats,
-                                                            float* __restrict__ s_query, int HT, int N, double scale) {
-  __shared__ double part[kMeanWaves][64];
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = blockIdx.x * 64 + lane, b = blockIdx.y;
-  const int share = (HT + kMeanWaves - 1) / kMeanWaves, end = (w + 1) * share < HT ? (w + 1) * share : HT;
-  const F* p = S + (long)b * HT * N + i;
-  const double2* st = stats + (long)b * HT;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  int r = w * share;
-  if (i < N) {
-    for (; r + 8 <= end; r += 8) {
-      F v[8];
+// s_query[b,i] = (1/HT) sum_{row < HT} exp(scale*S[b,row,i] - max_row) / Z_row.  The rows of a token are cut into sixteen shares, each added up
+// by itself and the shares in order, so that a token's sum is the same in both of the forms below.
+constexpr int kMeanShares = 16;
+// N rows of a share, all loads in flight, one after the other into acc[0], or (N = 8) into four interleaved sums.
+template <int N, typename F>
+__device__ __forceinline__ void softmax_mean_rows(const F* p, long pitch, const double2* st, F scale, double (&acc)[4]) {
+  F v[N];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(long)(r + u) * N];
+  for (int u = 0; u < N; ++u) v[u] = p[u * pitch];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double2 mz = st[r + u];
-        acc[u & 3] = fma((double)exp(v[u] * (F)scale - (F)mz.x), mz.y, acc[u & 3]);
-      }
-    }
-    for (; r < end; ++r) {
-      const double2 mz = st[r];
-      acc[0] = fma((double)exp(p[(long)r * N] * (F)scale - (F)mz.x), mz.y, acc[0]);
-    }
+  for (int u = 0; u < N; ++u) {
+    const double2 mz = st[u];
+    double& a = acc[N == 8 ? u & 3 : 0];
+    a = fma((double)exp(v[u] * scale - (F)mz.x), mz.y, a);
   }
-  part[w][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+template <typename F>
+__device__ __forceinline__ double softmax_mean_share(const F* p, long pitch, const double2* st, F scale, int r, int end) {
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (; r + 8 <= end; r += 8) softmax_mean_rows<8>(p + r * pitch, pitch, st + r, scale, acc);
+  if (r + 4 <= end) { softmax_mean_rows<4>(p + r * pitch, pitch, st + r, scale, acc); r += 4; }
+  if (r + 2 <= end) { softmax_mean_rows<2>(p + r * pitch, pitch, st + r, scale, acc); r += 2; }
+  if (r < end) softmax_mean_rows<1>(p + r * pitch, pitch, st + r, scale, acc);
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// A workgroup has 64 tokens, each of its sixteen waves a share of the rows.  Bound by the latency of the loads: with all rows of a token in
+// one thread 384 rows of 1849 tokens, six images, took 45 us on 48 workgroups, so 7 (576 fp32 tokens, four images, 512 rows:
+// covspec_score 286, so 222).
+template <typename F>
+__global__ __launch_bounds__(64 * kMeanShares) void softmax_mean_kernel(const F* __restrict__ S, const double2* __restrict__ stats,
+                                                                        float* __restrict__ s_query, int HT, int N, double scale) {
+  __shared__ double part[kMeanShares][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = blockIdx.x * 64 + lane, b = blockIdx.y;
+  const int share = (HT + kMeanShares - 1) / kMeanShares, end = (w + 1) * share < HT ? (w + 1) * share : HT;
+  if (i < N) part[w][lane] = softmax_mean_share(S + (long)b * HT * N + i, (long)N, stats + (long)b * HT, (F)scale, w * share, end);
   __syncthreads();
   if (w != 0 || i >= N) return;
   double sum = 0.0;
 #pragma unroll
-  for (int g = 0; g < kMeanWaves; ++g) sum += part[g][lane];
+  for (int g = 0; g < kMeanShares; ++g) sum += part[g][lane];
+  s_query[(long)b * N + i] = (float)(sum / HT);
+}
+
+// The same with all shares of a token in one thread, 256 tokens a workgroup: for so many tokens, or so few rows, that the sixteen waves of 64
+// tokens are more than it takes to hide the loads (launch_softmax_mean).
+template <typename F>
+__global__ __launch_bounds__(256) void softmax_mean_wide_kernel(const F* __restrict__ S, const double2* __restrict__ stats, float* __restrict__ s_query,
+                                                                int HT, int N, double scale) {
+  const int i = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+  if (i >= N) return;
+  const F* p = S + (long)b * HT * N + i;
+  const double2* st = stats + (long)b * HT;
+  const int share = (HT + kMeanShares - 1) / kMeanShares;
+  double sum = 0.0;
+  // shares of less than eight rows, their length a constant: whole shares at a time, up to eight rows' loads in flight
+  auto few = [&](auto length) {
+    constexpr int LEN = decltype(length)::value, AT_ONCE = 8 / LEN * LEN;
+    auto rows = [&](auto count, int r) {
+      constexpr int C = decltype(count)::value;
+      F v[C];
+#pragma unroll
+      for (int u = 0; u < C; ++u) v[u] = p[(long)(r + u) * N];
+#pragma unroll
+      for (int f = 0; f < C; f += LEN) {
+        double acc = 0.0;
+#pragma unroll
+        for (int u = f; u < C && u < f + LEN; ++u) {
+          const double2 mz = st[r + u];
+          acc = fma((double)exp(v[u] * (F)scale - (F)mz.x), mz.y, acc);
+        }
+        sum += acc;
+      }
+    };
+    int r = 0;
+    for (; r + AT_ONCE <= HT; r += AT_ONCE) rows(std::integral_constant<int, AT_ONCE>{}, r);
+    if (LEN == 1 && r + 4 <= HT) { rows(std::integral_constant<int, 4>{}, r); r += 4; }
+    for (; r < HT; r += LEN) sum += softmax_mean_share(p, (long)N, st, (F)scale, r, r + LEN < HT ? r + LEN : HT);
+  };
+  switch (share) {
+    case 1: few(std::integral_constant<int, 1>{}); break;
+    case 2: few(std::integral_constant<int, 2>{}); break;
+    case 3: few(std::integral_constant<int, 3>{}); break;
+    case 4: few(std::integral_constant<int, 4>{}); break;
+    case 5: few(std::integral_constant<int, 5>{}); break;
+    case 6: few(std::integral_constant<int, 6>{}); break;
+    case 7: few(std::integral_constant<int, 7>{}); break;
+    default:
+      for (int r = 0; r < HT; r += share) sum += softmax_mean_share(p, (long)N, st, (F)scale, r, r + share < HT ? r + share : HT);
+  }
   s_query[(long)b * N + i] = (float)(sum / HT);
 }
 
@@ -617,9 +670,23 @@ hipError_t launch_softmax_mean(const void* S, bool f64, const void* stats, float
     hipLaunchKernelGGL(softmax_mean_finish_kernel, dim3(blocks_for(BN, 256)), dim3(256), 0, st, (const double*)part, s_query, BN, segs, HT);
     return hipGetLastError();
   }
-  dim3 grid((N + 63) / 64, B), block(64 * kMeanWaves);
-  if (f64) hipLaunchKernelGGL((softmax_mean_kernel<double>), grid, block, 0, st, (const double*)S, (const double2*)stats, s_query, HT, N, scale);
-  else hipLaunchKernelGGL((softmax_mean_kernel<float>), grid, block, 0, st, (const float*)S, (const double2*)stats, s_query, HT, N, scale);
+  // A wave has 64 tokens: from two on every SIMD, or half of them where a share is one row, the waves themselves hide the loads.  us of
+  // covspec_score, sixteen waves a workgroup / a thread for all rows, bf16, width 64: 64 images of 2881 tokens (2944 waves) 1 row 95.6 / 91.6, 16 99.0 / 94.3, 64
+  // 108.0 / 105.6, 128 131.5 / 126.4; 16 of 2881 (736) 4 rows 59.8 / 59.4, 16 63.0 / 61.8, 32 64.4 / 65.1, 128 66.3 / 72.2; 128 of 577 (1280) 16
+  // rows 58.0 / 56.8, 64 62.4 / 63.5; 8 of 2881 (368) 16 rows 51.0 / 50.8, 64 55.7 / 62.6; 4 (184) 45.6 / 46.0 with 1 row, 47.4 / 47.8 with 16.
+  const int waves = (N + 63) / 64;
+  const bool wide = (long)waves * B >= (HT <= kMeanShares ? 640 : 2048);
+#define COVSPEC_MEAN(kernel, F, grid, block) hipLaunchKernelGGL((kernel<F>), grid, block, 0, st, (const F*)S, (const double2*)stats, s_query, HT, N, scale)
+  if (wide) {
+    const dim3 grid((N + 255) / 256, B), block(256);
+    if (f64) COVSPEC_MEAN(softmax_mean_wide_kernel, double, grid, block);
+    else COVSPEC_MEAN(softmax_mean_wide_kernel, float, grid, block);
+  } else {
+    const dim3 grid(waves, B), block(64 * kMeanShares);
+    if (f64) COVSPEC_MEAN(softmax_mean_kernel, double, grid, block);
+    else COVSPEC_MEAN(softmax_mean_kernel, float, grid, block);
+  }
+#undef COVSPEC_MEAN
   return hipGetLastError();
 }
 

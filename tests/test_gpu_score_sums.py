@@ -130,3 +130,26 @@ def test_attention_scores_over_few_and_many_rows(C, dtype, N, T, H):
         # fp32: fp64 inside, one rounding of the result and the exponential's.  bf16: a logit is an fp32 sum of d / H products, off by at
         # most d / H roundings of their absolute sum (below 10 / 8 behind the scale), and its difference from the row's maximum by three
         np.testing.assert_allclose(sq[b], ref, rtol=2e-7 if dtype == "fp32" else (d / H + 3) * 2.0 ** -24 * 2.5 + 3e-7)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("T", [1, 3, 7, 16, 17, 33, 47, 48, 64, 65, 79, 96, 111, 112, 113, 128, 150])
+def test_attention_scores_of_few_and_many_images(C, dtype, T):
+    """The mean over the rows: sixteen waves for 64 tokens of one image, a thread for all rows of a token of 330 (660 waves, up to 16 rows) and 1030
+    images (2060 waves).  Shares of 1 to 8 rows and more, whole and cut off.  Equal to the bit, and to the oracle."""
+    import torch
+    N, d = 65, 64
+    g = torch.Generator(device="cuda").manual_seed(T)
+    X, Q = (torch.randn(1030, n, d, generator=g, device="cuda") for n in (N, T))
+    if dtype == "bf16":
+        X, Q = X.bfloat16(), Q.bfloat16()
+    got = []
+    for B in (1, 330, 1030):
+        p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=T, n_heads=1, dtype=C.BF16 if dtype == "bf16" else C.FP32, keep_k=1, preselect_m=4, rank_r=2,
+                     rel_mode=C.REL_ATTN_SOFTMAX)
+        got.append(C.score(p, X[:B].contiguous(), None, Q[:B].contiguous(), None, None)[0])
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1][:1]) and torch.equal(got[1], got[2][:330])
+    ref = O.query_score_attention(X[0].double().cpu().numpy(), Q[0].double().cpu().numpy(), 1)
+    # as above; logits of width 64 are below 5 behind the scale
+    np.testing.assert_allclose(got[0][0].cpu().numpy(), ref, rtol=2e-7 if dtype == "fp32" else (d + 3) * 2.0 ** -24 * 2.5 + 3e-7)
