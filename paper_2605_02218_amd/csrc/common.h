@@ -128,11 +128,17 @@ constexpr int kLoadAgent = 16;                          // buffer loads: sc1, pa
 __device__ __forceinline__ double tagged(double v, unsigned tag) {
   return __hiloint2double(__double2hiint(v), (int)(((unsigned)__double2loint(v) & ~1u) | tag));
 }
-// N tiles in fragment order, tile n at off[n] bytes of `src` (a lane's offset included), as soon as all their elements carry the bit.
+// The same without a bit: an element is there when its upper word is another than kAbsent's, a signalling NaN, which arithmetic does not
+// return; the words are at kAbsent before.
+constexpr int kAbsent = 0x7FF4ADED;
+__device__ __forceinline__ double absent() { return __hiloint2double(kAbsent, 0); }
+__device__ __forceinline__ bool is_absent(double v) { return __double2hiint(v) == kAbsent; }
+// What to store of an element.
+__device__ __forceinline__ double present(double v) { return is_absent(v) ? __hiloint2double(0x7FF80000, 0) : v; }
+// N tiles in fragment order, tile n at off[n] bytes of `src` (a lane's offset included), as soon as all their elements are there.
 // False: over the limit, or *failed is set; the elements are then whatever there was.  One wave.
 template <int N>
-__device__ __forceinline__ bool fetch_tagged(__amdgpu_buffer_rsrc_t src, const int (&off)[N], unsigned tag, f64x2_t (&out)[N][2], const int* failed,
-                                             long long limit_ticks) {
+__device__ __forceinline__ bool fetch_present(__amdgpu_buffer_rsrc_t src, const int (&off)[N], f64x2_t (&out)[N][2], const int* failed, long long limit_ticks) {
   unsigned todo = (1u << N) - 1;
   long long t0 = 0;
   for (int tries = 0; todo != 0; ++tries) {
@@ -147,9 +153,7 @@ __device__ __forceinline__ bool fetch_tagged(__amdgpu_buffer_rsrc_t src, const i
     for (int n = 0; n < N; ++n)
       if (todo >> n & 1) {
         const f64x2_t u = out[n][0], v = out[n][1];
-        const int all = __double2loint(u[0]) & __double2loint(u[1]) & __double2loint(v[0]) & __double2loint(v[1]);
-        const int some = __double2loint(u[0]) | __double2loint(u[1]) | __double2loint(v[0]) | __double2loint(v[1]);
-        if (!__any(((tag ? ~all : some) & 1) != 0)) todo &= ~(1u << n);
+        if (!__any(is_absent(u[0]) || is_absent(u[1]) || is_absent(v[0]) || is_absent(v[1]))) todo &= ~(1u << n);
       }
     if (todo != 0 && (tries & 63) == 63) {              // 64 tries: some 60 us
       if (tries == 63) t0 = wall_clock64();

@@ -56,7 +56,7 @@ constexpr int kMaxBlocks = 64;         // block rows: P <= 4096
 //   ST_REST  0: takes part in the next orthonormalisation, 1: in the last one of the pass only, 2: in none of this pass
 //   ST_IDLE  minus the number of products of the block that follows
 //   ST_SEL, ST_END  the buffer its first operand is in, and the one its result is in (products alternate between the two)
-//   ST_TURN  factorisations so far: their inverted diagonal blocks carry its lowest bit (see tagged)
+//   ST_TURN  factorisations so far: its lowest bit says which of two buffers their inverted diagonal blocks go to
 enum { ST_REST, ST_IDLE, ST_SEL, ST_END, ST_TURN, ST_FIELDS };
 constexpr int kMaxDegrees = 6;
 struct IterPlan {
@@ -228,13 +228,13 @@ __device__ __forceinline__ void frag_store_through(double* tile, int lane, const
   store_through(t + 128, v[2]);
   store_through(t + 129, v[3]);
 }
-__device__ __forceinline__ f64x4_t tagged(const f64x4_t& v, unsigned tag) {
-  return (f64x4_t){covspec::tagged(v[0], tag), covspec::tagged(v[1], tag), covspec::tagged(v[2], tag), covspec::tagged(v[3], tag)};
+__device__ __forceinline__ f64x4_t present(const f64x4_t& v) {
+  return (f64x4_t){covspec::present(v[0]), covspec::present(v[1]), covspec::present(v[2]), covspec::present(v[3])};
 }
 
 // Factors a 64 x 64 block (a = L L^T) and inverts the factor, by all eight waves.  Wave 0 brings tile (0, 0) in registers, element
 // (k, i) in lane (q = k % 4, i), register k / 4; the other tiles on and below the diagonal are in LDS (`a`, pitch NBP), a barrier before
-// they are read.  inv(L) goes through the L2 to Db (its tiles on and below the diagonal, in fragment order, tagged), the diagonal of L to
+// they are read.  inv(L) goes through the L2 to Db (its tiles on and below the diagonal, in fragment order), the diagonal of L to
 // dl (valid in wave 0).  The pivot of row k is floored at floors[k].
 // By 16 x 16 tiles.  A diagonal tile stays in the registers of wave 0 from the product that forms it to its inverse, four pivots at a
 // time: the 4 x 4 block at the pivots is read into scalars and factored and inverted by every lane for itself (eliminate_panel), what it
@@ -353,14 +353,14 @@ __device__ __forceinline__ f64x4_t invert_sum(const LaneTiles& p, int t, int s) 
 }
 
 // a tile of the inverse from LDS to memory
-__device__ __forceinline__ void hand_on(const LaneTiles& p, double* Db, int t, int s, unsigned tag) {
+__device__ __forceinline__ void hand_on(const LaneTiles& p, double* Db, int t, int s) {
   const double* d = p.inv[0] + tile_off(t, s);
-  frag_store_through(Db + (4 * t + s) * kFragTile, threadIdx.x & 63, tagged((f64x4_t){d[0], d[4], d[8], d[12]}, tag));
+  frag_store_through(Db + (4 * t + s) * kFragTile, threadIdx.x & 63, present((f64x4_t){d[0], d[4], d[8], d[12]}));
 }
 
 // between: called by all waves with their own stores of before acknowledged, one thread of wave 7 raising a flag for it
 template <typename Between>
-__device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv, double* Db, double* dl, const double* floors, unsigned tag, Between between) {
+__device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv, double* Db, double* dl, const double* floors, Between between) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i16 = lane & 15, kq = lane >> 4;
   const int col = 7 - w;                             // waves 7, 6 and 5 have a column of the inverse each
   f64x4_t sum = (f64x4_t){0.0, 0.0, 0.0, 0.0};
@@ -389,10 +389,10 @@ __device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv,
         for (int v = 0; v < 4; ++v) z[4 * v * NBP] = o[v];
       }
       if (s == 3) {
-        if (w < 4) hand_on(p, Db, w - 1, w - 1, tag);
-        else if (w == 4) hand_on(p, Db, 1, 0, tag);
+        if (w < 4) hand_on(p, Db, w - 1, w - 1);
+        else if (w == 4) hand_on(p, Db, 1, 0);
         else {
-          if (col < 2) hand_on(p, Db, 2, col, tag);
+          if (col < 2) hand_on(p, Db, 2, col);
           sum = invert_sum(p, 3, col);
         }
       }
@@ -424,13 +424,13 @@ __device__ __forceinline__ void factor_invert(f64x4_t x, double* a, double* inv,
   }
   const LaneTiles p(a, inv);
   if (w == 0) {
-    hand_on(p, Db, 3, 3, tag);
+    hand_on(p, Db, 3, 3);
   } else if (w > 4) {                                // -inv_33 sum, transposed: in fragment order
     const double* d = p.inv[0] + tile_off(3, 3);
     f64x4_t o = (f64x4_t){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) o = __builtin_amdgcn_mfma_f64_16x16x4f64(sum[j], -d[4 * j], o, 0, 0, 0);
-    frag_store_through(Db + (12 + col) * kFragTile, lane, tagged(o, tag));
+    frag_store_through(Db + (12 + col) * kFragTile, lane, present(o));
   }
 }
 
@@ -475,10 +475,11 @@ __device__ __forceinline__ void raise_flag(int* flag, int value) {
 // the diagonal), one 512-thread workgroup per block row of 64 and image.  The workgroup of block row i:
 //   for K < i:  T = S[i,K] - sum over K' < K of L[i,K'] L[K,K']^T;   L[i,K] = T inv(L_KK)^T, in place;   D += L[i,K] L[i,K]^T
 //   factors and inverts S[i,i] - D (factor_invert); the inverse goes to Dinv[b][i] (its tiles).
-// It waits for row K's columns before the sum and for row K's inverse (its elements carry the bit of this turn) before the product with it, so
+// It waits for row K's columns before the sum and for row K's inverse (its elements are there when they are not kAbsent) before the product with it, so
 // that the sum runs while row K is being factored; rows are taken in order (a ticket per image), so that a workgroup only waits for rows that have started
 // before it, whatever else the device is doing; every wait is bounded.  What the rows hand one another is stored through the L2.
 // Every product is formed transposed, so that its result is the fragment of the tile it goes to.
+// The inverses of even and odd turns have a buffer each (orth_kernel clears the other one).
 // On return the strictly-lower blocks of S hold L; its diagonal blocks are represented by their inverses.
 // A pivot is floored relative to its own row's squared length (rows may differ in length by any number of digits: after a block of
 // products they do, by the growth of the first row over the last), at the rounding of S: what is left of a row below that is noise, which
@@ -497,10 +498,10 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
   __shared__ int s_gave_up;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), i16 = lane & 15, kq = lane >> 4;
   const int nblk = P / NB, per16 = P / 16;
-  const unsigned tag = ~q.in[ST_TURN * q.B + b] & 1;
+  const int turn = q.in[ST_TURN * q.B + b] & 1;
   if (tid == 0) s_gave_up = 0;                      // (a barrier before it is set)
   double* Sb = S + (long)b * P * P;
-  double* Db = Dinv + (long)b * nblk * NB * NB;
+  double* Db = Dinv + ((long)turn * q.B + b) * nblk * NB * NB;
   auto tile = [&](int rt, int ct) -> double* { return Sb + ((long)rt * per16 + ct) * kFragTile; };
   if (tid < NB) {
     diag0[tid] = tile(4 * row + (tid >> 4), 4 * row + (tid >> 4))[frag_at(tid & 15, tid & 15)];
@@ -572,7 +573,7 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
         const int t = n <= y0 ? 4 * y0 + n : 4 * y1 + n - y0 - 1;
         at[n] = (K * 16 + t) * (kFragTile * 8) + 16 * lane;
       }
-      if (!fetch_tagged<5>(inverses, at, tag, d, &f->failed, limit_ticks) && lane == 0) s_gave_up = 1;
+      if (!fetch_present<5>(inverses, at, d, &f->failed, limit_ticks) && lane == 0) s_gave_up = 1;
     }
     out[0] = out[1] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
     if (odd) {
@@ -635,7 +636,7 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
         }
       }
     }
-    factor_invert(x0, a, inv, Di, dl, floors, tag, [&]() {
+    factor_invert(x0, a, inv, Di, dl, floors, [&]() {
       __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0): L[row, .] has been stored
       __syncthreads();
       if (tid == 7 * kWave) __hip_atomic_store(&f->cols[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -683,7 +684,7 @@ __device__ __forceinline__ void chol_row(double* lds, int* s_flag, double* S, do
 // that wrote them, two groups of 16 k ahead, as are those of L.
 // As a launch behind the factorisation, the solved blocks in registers, it took, us: 192 x 320 14.5, 192 x 1664 batch 4 19, 384 x 1152
 // batch 8 44, 256 x 640 batch 64 73; the factorisation by itself 40, 43, 87 and 71, both in one launch 45, 49, 95 and 126.
-__device__ __forceinline__ bool substitute(const double* L, const double* D, double* Y, long nP, int P, bool mine, unsigned tag, CholFlags* f, int* s_flag,
+__device__ __forceinline__ bool substitute(const double* L, const double* D, double* Y, long nP, int P, bool mine, CholFlags* f, int* s_flag,
                                            long long limit_ticks) {
   const __amdgpu_buffer_rsrc_t inverses = __builtin_amdgcn_make_buffer_rsrc((void*)D, (short)0, P / NB * NB * NB * 8, 0x00020000);
   bool alive = true;
@@ -737,7 +738,7 @@ __device__ __forceinline__ bool substitute(const double* L, const double* D, dou
       for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int q = 0; q <= x; ++q) at[x * (x + 1) / 2 + q] = (bi * 16 + 4 * x + q) * (kFragTile * 8) + 16 * (threadIdx.x & 63);
-      alive = fetch_tagged<10>(inverses, at, tag, fd, &f->failed, limit_ticks) && alive;
+      alive = fetch_present<10>(inverses, at, fd, &f->failed, limit_ticks) && alive;
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[x] = zero;
 #pragma unroll
@@ -779,9 +780,17 @@ __global__ __launch_bounds__(512) void orth_kernel(double* S, double* __restrict
   }
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), col = ((ticket - nblk) * waves + w) * 16;
   const bool mine = w < waves && col < nP;           // nP % 64 == 0
+  const int turn = q.in[ST_TURN * q.B + b] & 1;
+  // the inverses of the turn before make room for those of the next one, while the first of this one is on its way
+  const int parts = gridDim.x / q.B - nblk;
+  for (int k = ticket - nblk; k < nblk; k += parts) {
+    double* block = Dinv + (((long)(turn ^ 1) * q.B + b) * nblk + k) * (NB * NB);
+    for (int e = tid; e < NB * NB; e += 512)
+      if (e >> 10 >= (e >> 8 & 3)) store_through(block + e, absent());      // tiles on and below the diagonal
+  }
   double* Y = Yt + (q.in[ST_END * q.B + b] ? other : 0) + (long)b * P * nP + (long)(lane >> 4) * nP + (mine ? col : 0) + (lane & 15);
   // gave up: the image's rows are not orthonormal, which the check of the residual refuses
-  if (!substitute(S + (long)b * P * P + 2 * lane, Dinv + (long)b * nblk * NB * NB, Y, nP, P, mine, ~q.in[ST_TURN * q.B + b] & 1, f, &s_flag, limit_ticks) && lane == 0)
+  if (!substitute(S + (long)b * P * P + 2 * lane, Dinv + ((long)turn * q.B + b) * nblk * NB * NB, Y, nP, P, mine, f, &s_flag, limit_ticks) && lane == 0)
     __hip_atomic_store(&f->failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -810,7 +819,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs q) {
     const long b = i / q.pad, e = i - b * q.pad;
     q.A[b * q.nP * q.nP + (e < right ? (e / w) * q.nP + q.n + e % w : (long)q.n * q.nP + (e - right))] = 0.0;
   }
-  for (long i = at; i < q.blocks; i += step) q.inverses[i] = 0.0;
+  for (long i = at; i < q.blocks; i += step) q.inverses[i] = absent();
   for (long i = at; i < q.words; i += step) q.ctl[i] = 0;
   for (long i = at; i < q.flag_words; i += step) q.flags[i] = 0;
   for (long i = at; i < q.cut_words; i += step) q.cut[i] = 0;
@@ -840,7 +849,7 @@ struct DirectBuffers {
 
 // The workspace of the iteration.
 struct IterBuffers {
-  double *Yt, *Zt, *Om, *S, *H, *D, *Pi;   // Pi: [B][P][P] the projector
+  double *Yt, *Zt, *Om, *S, *H, *D, *Pi;   // D: [2][B][P][64] inverted diagonal blocks; Pi: [B][P][P] the projector
   void* scratch;                           // of the split
   IterPlan* plan;                          // [B]
   int *states, *left, *failed;             // [kStates][ST_FIELDS][B]; [B] nothing left to do in this pass; [B] failed the check of the first pass
@@ -856,7 +865,7 @@ struct IterBuffers {
     S = Om + (size_t)P * nP;
     H = S + (size_t)B * P * P;
     D = H + (size_t)B * P * P;
-    Pi = D + (size_t)B * P * NB;
+    Pi = D + 2 * (size_t)B * P * NB;
     scratch = (void*)(((uintptr_t)(Pi + (size_t)B * P * P) + 255) & ~(uintptr_t)255);
     plan = (IterPlan*)((char*)scratch + split_scratch_bytes(B, P));
     states = (int*)(plan + B);
@@ -889,7 +898,7 @@ int subspace_block(int n, int r) {
 size_t subspace_workspace_bytes(int B, int n, int nP, int P) {
   if (P <= 0) return split_direct(nP) ? 3 * (size_t)B * nP * nP * 8 + split_scratch_bytes(B, nP) + 256 : 0;
   const size_t blk = (size_t)B * P * nP * 8;
-  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 +
+  return 2 * blk + (size_t)P * nP * 8 + 3 * (size_t)B * P * P * 8 + 2 * (size_t)B * P * NB * 8 + split_scratch_bytes(B, P) + 256 +
          (size_t)B * (sizeof(IterPlan) + (kStates * ST_FIELDS + 2) * sizeof(int) + kOrths * sizeof(CholFlags) + (P + P / NB) * 8) + 512 + tail_doubles(B, P, nP) * 8 + 256;
 }
 
@@ -914,7 +923,7 @@ hipError_t launch_lowrank_prepare(int* status, void* ctl, size_t words, double* 
     q.om = w.Om;
     q.omega = (long)P * nP;
     q.inverses = w.D;
-    q.blocks = (long)B * P * NB;
+    q.blocks = 2 * (long)B * P * NB;
     q.plan = w.plan;
     q.state = w.states;
     q.left = w.left;
