@@ -121,15 +121,10 @@ __device__ __forceinline__ void store_through(double* p, double v) { __hip_atomi
 
 constexpr long long kBarrierLimitTicks = 200000000LL;   // 2 s, the default of `limit_ticks`
 
-// ---- Handing on without a meeting: every element carries a bit in the lowest place of its mantissa (the rounding of an element to 52
-// bits) which tells whether it is the one that is waited for, and readers load past the L2s, which are not coherent, until it is.  Saves
-// the acknowledgement of the stores and a flag's way in front of the load.
+// ---- Handing on without a meeting: a word is at kAbsent before its element is stored, and readers load past the L2s, which are not coherent,
+// until it is another one.  kAbsent is the upper word of a signalling NaN, which arithmetic does not return.  Saves the acknowledgement of
+// the stores and a flag's way in front of the load.
 constexpr int kLoadAgent = 16;                          // buffer loads: sc1, past the L2
-__device__ __forceinline__ double tagged(double v, unsigned tag) {
-  return __hiloint2double(__double2hiint(v), (int)(((unsigned)__double2loint(v) & ~1u) | tag));
-}
-// The same without a bit: an element is there when its upper word is another than kAbsent's, a signalling NaN, which arithmetic does not
-// return; the words are at kAbsent before.
 constexpr int kAbsent = 0x7FF4ADED;
 __device__ __forceinline__ double absent() { return __hiloint2double(kAbsent, 0); }
 __device__ __forceinline__ bool is_absent(double v) { return __double2hiint(v) == kAbsent; }

@@ -862,19 +862,23 @@ __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel
 }
 
 // The iteration of small matrices (P <= 64 kSmallBlocks): a workgroup per 16 x 16 tile on and below the diagonal, its waves a quarter of k
-// each, and no meetings: what a workgroup hands on carries the number of its version in the lowest bit of every element, and the
-// others read an element until it is the one they want.
-//   Version v goes to buffer v % 3, its elements' lowest bits are 1, 0, 1, .. with each use of the buffer (cleared before the launch).  A
+// each, and no meetings: what a workgroup hands on carries the number of its version in a bit of every element, and the others read an
+// element until it is the one they want.
+//   The bit is the upper one of the exponent, which only numbers from 2 on have: the iterates are symmetric with eigenvalues in [-1, 1], or
+//   their squares, and so are their elements.  (An element that is none of these, NaN included, ends the image's iteration: no projector.)
+//   Version v goes to buffer v % 3, the bits are 1, 0, 1, .. with each use of the buffer (cleared before the launch).  A
 //   workgroup reads version v - 1 of the tiles in its rows (and columns) to form its part of version v; the left operand of the second
 //   product of a step, X, is still in its registers.  So whoever reads a tile's version v - 3 is through with it before version v of
 //   the tile is formed; and a workgroup stores version v when the stores of v - 1 have been acknowledged, so that nobody who has
 //   anything of version v can still find the words of v - 3 elsewhere.  The operands are loaded past the L2s, which are not coherent.
-//   The bit is the rounding of an element to 52 bits, 1e-16 of it; the sums are good to 1e-15.
 // Only the steps that may be the last, by the lower bound l, meet at the barrier: they are when no element moved by more than 1e-7.
 // Bound by latency: store, load, 3 MFMAs a group of 16 k and wave, four partial sums.  us per product with 32 x 32 tiles and a barrier in
 // global memory after each (store, acknowledge, count, see the count, load) and here: one image of order 192 7.0 and 3.4 (155 and 76 in all),
 // four 7.1 and 5.3, one of 128 5 and 2.8 (115 and 63).
 constexpr int kSmallBlocks = 4;
+constexpr int kVersionBit = 0x40000000;              // in the upper word
+__device__ __forceinline__ double with_version(double v, int bit) { return __hiloint2double((__double2hiint(v) & ~kVersionBit) | bit, __double2loint(v)); }
+__device__ __forceinline__ double without_version(double v) { return __hiloint2double(__double2hiint(v) & ~kVersionBit, __double2loint(v)); }
 
 // BLOCKS = P / 64.
 template <int BLOCKS>
@@ -902,6 +906,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
   int ti, tj;
   tile_of(slot, ti, tj);
   const int rt = (a >> 4) + ti, ct = (a >> 4) + tj;
+  norm = lane_value(norm, 0);                        // the same in all lanes: the loops below are those of a wave, the buffers scalars
   // the lift and the steps, as in sign_kernel
   double m = cb->mu / norm, l = cb->half / norm;
   const bool lift = m < kLiftTo;
@@ -918,26 +923,30 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
   const int ui = diagonal && ek > ei ? ek : ei, uk = diagonal && ek > ei ? ei : ek;      // what is above the diagonal is what is below
   unsigned version = 0;
   bool alive = true;
-  auto publish = [&](double& x, double& y) {         // the next version
-    const unsigned tag = ((version / 3) & 1) ^ 1;
-    x = tagged(x, tag);
-    y = tagged(y, tag);
+  auto publish = [&](double x, double y) {           // the next version
+    const int bit = version / 3 % 2 == 0 ? kVersionBit : 0;
+    if (!(fabs(x) < 2.0 && (diagonal || fabs(y) < 2.0))) s_fail = 1;      // (on the diagonal y is not used)
     double* M = version % 3 == 0 ? buf[0] : version % 3 == 1 ? buf[1] : buf[2];
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the version before
-    store_through(M + tile16(rt, ct, P) + tid, x);
-    if (!diagonal) store_through(M + tile16(ct, rt, P) + tid, y);
+    store_through(M + tile16(rt, ct, P) + tid, with_version(x, bit));
+    if (!diagonal) store_through(M + tile16(ct, rt, P) + tid, with_version(y, bit));
     ++version;
   };
   const int nc = ns >> 2;                            // groups of 16 k of a wave
   // The wave's groups of row tiles rt (both: f[0]) and ct (f[1]) of the last version.
   f64x2_t f[2][BLOCKS][2];
   auto fetch = [&](bool both) {
-    const unsigned v = version - 1, tag = ((v / 3) & 1) ^ 1;
+    const unsigned v = version - 1;
+    const bool one = v / 3 % 2 == 0;
     const __amdgpu_buffer_rsrc_t M = v % 3 == 0 ? rs[0] : v % 3 == 1 ? rs[1] : rs[2];
     const int base[2] = {(int)(tile16(rt, (a >> 4) + wv * nc, P) * 8) + 16 * lane, (int)(tile16(ct, (a >> 4) + wv * nc, P) * 8) + 16 * lane};
     long long t0 = 0;
     const unsigned groups = (1u << nc) - 1;
     unsigned todo = groups << BLOCKS | (both ? groups : 0);
+    // What is on its way takes longer than this, and tries that come too early stand in its way.  us of covspec_select without it, and with 8 / 16 / 28 times
+    // 64 clocks: two of order 64 103 and 103 / 106 / 113, eight of 128 192 and 186 / 184 / 187, twenty-three 291 and 280 / 269 / 257, one of 192 373
+    // and 370 / 370 / 375, seven 536 and 526 / 520 / 516, one of 256 597 and 597 / 598 / 606.
+    __builtin_amdgcn_s_sleep(BLOCKS == 1 ? 8 : 16);
     for (int tries = 0; todo != 0; ++tries) {
       asm volatile("" ::: "memory");                 // loads anew
 #pragma unroll
@@ -947,7 +956,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
           if (todo >> (BLOCKS * q + c) & 1) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-              f[q][c][h] = __builtin_bit_cast(f64x2_t, __builtin_amdgcn_raw_buffer_load_b128(M, base[q] + c * (kFragTile * 8) + 1024 * h, 0, kLoadAgent));
+              f[q][c][h] = __builtin_bit_cast(f64x2_t, __builtin_amdgcn_raw_buffer_load_b128(M, base[q], c * (kFragTile * 8) + 1024 * h, kLoadAgent));
           }
 #pragma unroll
       for (int q = 0; q < 2; ++q)
@@ -955,9 +964,13 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
         for (int c = 0; c < BLOCKS; ++c)
           if (todo >> (BLOCKS * q + c) & 1) {
             const f64x2_t u = f[q][c][0], w = f[q][c][1];
-            const int all = __double2loint(u[0]) & __double2loint(u[1]) & __double2loint(w[0]) & __double2loint(w[1]);
-            const int some = __double2loint(u[0]) | __double2loint(u[1]) | __double2loint(w[0]) | __double2loint(w[1]);
-            if (!__any(((tag ? ~all : some) & 1) != 0)) todo &= ~(1u << (BLOCKS * q + c));
+            const int all = __double2hiint(u[0]) & __double2hiint(u[1]) & __double2hiint(w[0]) & __double2hiint(w[1]);
+            const int some = __double2hiint(u[0]) | __double2hiint(u[1]) | __double2hiint(w[0]) | __double2hiint(w[1]);
+            if (!__any(((one ? ~all : some) & kVersionBit) != 0)) {
+              todo &= ~(1u << (BLOCKS * q + c));
+              f[q][c][0] = (f64x2_t){without_version(u[0]), without_version(u[1])};
+              f[q][c][1] = (f64x2_t){without_version(w[0]), without_version(w[1])};
+            }
           }
       if (todo != 0 && (tries & 63) == 63) {         // 64 tries: some 60 us
         if (tries == 63) t0 = wall_clock64();
@@ -982,7 +995,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
 #pragma unroll
     for (int v = 0; v < 4; ++v) part[parity][wv][4 * v + kq][i16] = acc[v];
     __syncthreads();
-    return s_fail == 0;
+    return __builtin_amdgcn_readfirstlane(s_fail) == 0;
   };
   auto sum = [&](int i, int k) { return (part[parity][0][i][k] + part[parity][1][i][k]) + (part[parity][2][i][k] + part[parity][3][i][k]); };
 
@@ -1014,8 +1027,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
     const double s = sqrt(3.0 / (1.0 + l + l * l)), c1 = 1.5 * s, c3 = -0.5 * s * s * s;
     fetch(true);
     if (!(alive = product())) break;
-    double sx = sum(ui, uk), sy = sum(ek, ei);       // Y = X X
-    publish(sx, sy);
+    publish(sum(ui, uk), sum(ek, ei));               // Y = X X
     fetch(false);
     if (!(alive = product())) break;
     const double nx = fma(c3, sum(ui, uk), c1 * x), ny = fma(c3, sum(ek, ei), c1 * y);     // c1 X + c3 X Y
@@ -1032,7 +1044,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
       if (tid == 0)
         atomicMax(&cb->dev[step], (unsigned long long)__double_as_longlong(fmax(fmax(s_dev[0], s_dev[1]), fmax(s_dev[2], s_dev[3]))));
       target += nact;
-      if (!(alive = image_barrier_wait<false>(&cb->bar, target, &s_flag, limit_ticks))) break;
+      if (!(alive = __builtin_amdgcn_readfirstlane(image_barrier_wait<false>(&cb->bar, target, &s_flag, limit_ticks)))) break;
       // near its limit the iteration squares the error: an entry that moved by 1e-7 is 1e-14 away afterwards
       done = __longlong_as_double((long long)__hip_atomic_load(&cb->dev[step], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < 1e-7;
     }

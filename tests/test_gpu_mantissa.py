@@ -22,7 +22,11 @@ def windows_without_a_lowest_bit(words, size=64):
 
 
 # images, tokens, width, rank; what is handed on
-CASES = {"block-rows": (2, 700, 720, 200)}     # the inverted diagonal blocks of the factorisation (a sign iteration with meetings)
+CASES = {
+    "block-rows": (2, 700, 720, 200),     # the inverted diagonal blocks of the factorisation (a sign iteration with meetings)
+    "sign-direct": (1, 100, 128, 40),     # the iterates of the sign iteration without meetings
+    "sign-block": (2, 300, 320, 100),
+}
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -41,4 +45,4 @@ def test_no_place_of_the_mantissa_is_lost(name):
     words = words[(-ws.data_ptr()) % 256:]
     words = words[:len(words) // 8 * 8].view(np.uint64)
     real, lost = windows_without_a_lowest_bit(words)
-    assert real > 1000 and lost == 0, (real, lost)
+    assert real > 100 and lost == 0, (real, lost)
