@@ -32,6 +32,7 @@
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"
+#include "pivots.h"
 
 namespace covspec {
 
@@ -346,8 +347,8 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
 // window are the diagonal entries four rows to either side of the cut, otherwise everything.  A wave holds the upper triangle of
 // 16 x 16 tiles in its registers and eliminates four pivots at a time: the 4 x 4 block at the pivots in scalars, as eliminate_panel
 // (subspace.hip) does without its floors, the rest as products of rank 4.  (A pivot of relative size p perturbs the matrix by 1e-16 / p; that
-// this moves an eigenvalue over a trial point, 1e-6 of the norm away and more, takes a pivot below 1e-10, and a count that is
-// wrong shows in the trace of the projector.)
+// this moves an eigenvalue over a trial point, 1e-6 of the norm away and more, takes a pivot below 1e-10.  An exact zero counts for a matrix
+// 1e-8 away, see pivots.h.  A count that is wrong shows in the trace of the projector.)
 // Bound by the chain of pivots and the MFMAs of a wave.  us, split_kernel and here: one window of 64 44 and 19 (two 44 and 22), of 128 121 and 83.
 constexpr int kCutImages = 8;        // of windows of 128, half as many of 64: a SIMD gets a wave at most
 constexpr int kTrials = 256;
@@ -367,30 +368,16 @@ __device__ __forceinline__ void count_panel(f64x4_t (&T)[NT * (NT + 1) / 2], int
   const f64x4_t zero = (f64x4_t){0.0, 0.0, 0.0, 0.0};
   f64x4_t& x = T[tri<NT>(S, S)];
   auto at = [&](int i, int j) { return lane_value(x[PN], 16 * i + 4 * PN + j); };
-  auto pivot = [&](double p) {
-    p = fabs(p) > 1e-200 ? p : -1e-200;
-    neg += p < 0.0 ? 1 : 0;
-    return p;
-  };
-  const double a10 = at(1, 0), a20 = at(2, 0), a30 = at(3, 0), a21 = at(2, 1), a31 = at(3, 1), a32 = at(3, 2);
-  const double a11 = at(1, 1), a22 = at(2, 2), a33 = at(3, 3), r0 = reciprocal(pivot(at(0, 0)));
-  const double b11 = fma(-(a10 * a10), r0, a11), b21 = fma(-(a20 * a10), r0, a21), b31 = fma(-(a30 * a10), r0, a31);
-  const double b22 = fma(-(a20 * a20), r0, a22), b32 = fma(-(a30 * a20), r0, a32), b33 = fma(-(a30 * a30), r0, a33);
-  const double r1 = reciprocal(pivot(b11));
-  const double c22 = fma(-(b21 * b21), r1, b22), c32 = fma(-(b31 * b21), r1, b32), c33 = fma(-(b31 * b31), r1, b33);
-  const double r2 = reciprocal(pivot(c22));
-  const double r3 = reciprocal(pivot(fma(-(c32 * c32), r2, c33)));
+  const CountedBlock f = count_block(at(0, 0), at(1, 0), at(1, 1), at(2, 0), at(2, 1), at(2, 2), at(3, 0), at(3, 1), at(3, 2), at(3, 3), reciprocal, neg);
   if constexpr (S == NT - 1 && PN == 3) return;
-  const double l10 = a10 * r0, l20 = a20 * r0, l30 = a30 * r0, l21 = b21 * r1, l31 = b31 * r1, l32 = c32 * r2;
-  const double n20 = fma(l21, l10, -l20), n31 = fma(l32, l21, -l31), n30 = -fma(l31, -l10, fma(l32, n20, l30));
   double n = i16 == kq ? 1.0 : 0.0;
-  if (i16 == 1 && kq == 0) n = -l10;
-  if (i16 == 2 && kq == 0) n = n20;
-  if (i16 == 2 && kq == 1) n = -l21;
-  if (i16 == 3 && kq == 0) n = n30;
-  if (i16 == 3 && kq == 1) n = n31;
-  if (i16 == 3 && kq == 2) n = -l32;
-  const double r = kq == 0 ? r0 : kq == 1 ? r1 : kq == 2 ? r2 : r3;
+  if (i16 == 1 && kq == 0) n = f.n10;
+  if (i16 == 2 && kq == 0) n = f.n20;
+  if (i16 == 2 && kq == 1) n = f.n21;
+  if (i16 == 3 && kq == 0) n = f.n30;
+  if (i16 == 3 && kq == 1) n = f.n31;
+  if (i16 == 3 && kq == 2) n = f.n32;
+  const double r = kq == 0 ? f.r0 : kq == 1 ? f.r1 : kq == 2 ? f.r2 : f.r3;
   double below = 0.0, u[NT], ru[NT];
   if constexpr (PN < 3) {
     const double w = __builtin_amdgcn_mfma_f64_16x16x4f64(n, x[PN], zero, 0, 0, 0)[0];
