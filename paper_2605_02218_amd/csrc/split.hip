@@ -874,9 +874,9 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
                                                             SplitCtl* ctl, long long limit_ticks) {
   __shared__ double part[2][4][16][17];
   __shared__ double s_dev[4];
-  __shared__ int s_flag, s_fail;
+  __shared__ int s_flag, s_fail[2];                  // s_fail: of this product and the next, by turns, as part
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
-  if (tid == 0) { s_flag = (int)atomicAdd(&ctl[0].ticket, 1u); s_fail = 0; }
+  if (tid == 0) { s_flag = (int)atomicAdd(&ctl[0].ticket, 1u); s_fail[0] = s_fail[1] = 0; }
   __syncthreads();
   const int ticket = __builtin_amdgcn_readfirstlane(s_flag);
   __syncthreads();                                   // s_flag is reused by the barriers
@@ -910,9 +910,10 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
   const int ui = diagonal && ek > ei ? ek : ei, uk = diagonal && ek > ei ? ei : ek;      // what is above the diagonal is what is below
   unsigned version = 0;
   bool alive = true;
+  int parity = 0;                                    // of the last product
   auto publish = [&](double x, double y) {           // the next version
     const int bit = version / 3 % 2 == 0 ? kVersionBit : 0;
-    if (!(fabs(x) < 2.0 && (diagonal || fabs(y) < 2.0))) s_fail = 1;      // (on the diagonal y is not used)
+    if (!(fabs(x) < 2.0 && (diagonal || fabs(y) < 2.0))) s_fail[parity ^ 1] = 1;     // (on the diagonal y is not used)
     double* M = version % 3 == 0 ? buf[0] : version % 3 == 1 ? buf[1] : buf[2];
     __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the version before
     store_through(M + tile16(rt, ct, P) + tid, with_version(x, bit));
@@ -962,13 +963,12 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
       if (todo != 0 && (tries & 63) == 63) {         // 64 tries: some 60 us
         if (tries == 63) t0 = wall_clock64();
         if (__hip_atomic_load(&cb->bar.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > limit_ticks) {
-          if (lane == 0) s_fail = 1;
+          if (lane == 0) s_fail[parity ^ 1] = 1;
           break;
         }
       }
     }
   };
-  int parity = 0;
   // partial sums of the product of the groups; false: gave up
   auto product = [&]() {
     f64x4_t acc = (f64x4_t){0.0, 0.0, 0.0, 0.0};
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
 #pragma unroll
     for (int v = 0; v < 4; ++v) part[parity][wv][4 * v + kq][i16] = acc[v];
     __syncthreads();
-    return __builtin_amdgcn_readfirstlane(s_fail) == 0;
+    return __builtin_amdgcn_readfirstlane(s_fail[parity]) == 0;
   };
   auto sum = [&](int i, int k) { return (part[parity][0][i][k] + part[parity][1][i][k]) + (part[parity][2][i][k] + part[parity][3][i][k]); };
 
