@@ -1191,10 +1191,12 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   // image's workgroups, a tile each, have to be as few as above.
   const long n16 = P / 16, t16 = n16 * (n16 + 1) / 2;
   bool small = form == 0 && P <= 64 * kSmallBlocks && B * t16 * 2 * 16 * P * 8 <= 28000000;
+  static_assert(kSmallBlocks == 4, "");
+  const auto sk = n64 == 1 ? sign_small_kernel<1> : n64 == 2 ? sign_small_kernel<2> : n64 == 3 ? sign_small_kernel<3> : sign_small_kernel<4>;
   if (small) {
-    static PerDeviceInt resident;
+    static PerDeviceInt resident[kSmallBlocks];
     int held = 0;
-    if ((e = resident_workgroups(resident, sign_small_kernel<kSmallBlocks>, 256, 0, &held)) != hipSuccess) return e;      // the others need less
+    if ((e = resident_workgroups(resident[n64 - 1], sk, 256, 0, &held)) != hipSuccess) return e;
     small = t16 <= held / 8;
   }
   const bool w64 = ordered || P == 64;
@@ -1222,8 +1224,6 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
     hipLaunchKernelGGL(split_kernel, sg, dim3(256), 0, st, H, P, stride, B, r, !ordered, off, link, ctl, skip, again, false, small ? X0 : nullptr, X1, Y);
   }
   if (small) {
-    static_assert(kSmallBlocks == 4, "");
-    auto sk = n64 == 1 ? sign_small_kernel<1> : n64 == 2 ? sign_small_kernel<2> : n64 == 3 ? sign_small_kernel<3> : sign_small_kernel<4>;
     hipLaunchKernelGGL(sk, dim3((unsigned)(B * t16)), dim3(256), 0, st, H, X0, Y, X1, P, r, (const double*)off, (const double*)link,
                        ordered, (int)t16, ctl, barrier_limit_ticks());
     return hipGetLastError();

@@ -56,3 +56,20 @@ def test_every_wave_waits_for_its_stores_in_front_of_a_write_back(tmp_path):
     results = [unguarded_write_backs(a) for a in asm]
     assert sum(n for _, n in results) >= 4
     assert {s: bad for s, (bad, _) in zip(users, results) if bad} == {}
+
+
+@pytest.mark.skipif(not (os.path.exists(B._hipcc()) or shutil.which(B._hipcc())), reason="no hipcc")
+def test_an_image_of_the_small_sign_iteration_is_an_eighth_of_the_device(tmp_path):
+    """What the launcher asks the runtime for each form of the kernel (split.hip), from the registers and the LDS it was compiled to: a
+    workgroup per 16 x 16 tile on and below the diagonal, 256 compute units of four SIMDs with 512 registers and 160 KB."""
+    text = "\n".join(_assembly(os.path.join(B.CSRC, "split.hip"), str(tmp_path / "split.s")))
+    forms = {}
+    for kernel in re.findall(r"\.amdhsa_kernel (\S*sign_small_kernelILi\d\S*)(.*?)\.end_amdhsa_kernel", text, re.S):
+        value = {k: int(re.search(r"\.amdhsa_%s (\d+)" % k, kernel[1]).group(1)) for k in ("next_free_vgpr", "group_segment_fixed_size")}
+        forms[int(re.search(r"ILi(\d)", kernel[0]).group(1))] = value
+    assert sorted(forms) == [1, 2, 3, 4]
+    for blocks, v in forms.items():
+        waves = 512 // ((v["next_free_vgpr"] + 7) // 8 * 8)                    # of a SIMD; a workgroup has one on each
+        held = 256 * min(waves, 8, 160 * 1024 // v["group_segment_fixed_size"])
+        tiles = 4 * blocks * (4 * blocks + 1) // 2
+        assert tiles <= held // 8, (blocks, tiles, held)
