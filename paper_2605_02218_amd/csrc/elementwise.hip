@@ -575,11 +575,16 @@ __global__ void fill_int_kernel(int* __restrict__ p, int n, int value) {
 }  // namespace
 
 hipError_t launch_transpose(const void* in, void* out, const void* in1, void* out1, int rows, int cols, int dtype, hipStream_t st) {
-  dim3 grid((cols + 63) / 64, (rows + 63) / 64, in1 ? 2 : 1), block(256);
   const int piece = dtype == DT_BF16 ? 8 : 4;
-  const uintptr_t bits = (uintptr_t)in | (uintptr_t)out | (uintptr_t)in1 | (uintptr_t)out1;
+  const auto in_pieces = [&](const void* a, const void* b) { return rows % piece == 0 && cols % piece == 0 && (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
+  const bool pieces = in_pieces(in, out);
+  if (in1 && in_pieces(in1, out1) != pieces) {        // a form each
+    const hipError_t e = launch_transpose(in, out, nullptr, nullptr, rows, cols, dtype, st);
+    return e != hipSuccess ? e : launch_transpose(in1, out1, nullptr, nullptr, rows, cols, dtype, st);
+  }
+  dim3 grid((cols + 63) / 64, (rows + 63) / 64, in1 ? 2 : 1), block(256);
 #define COVSPEC_TRANSPOSE(kernel, T) hipLaunchKernelGGL((kernel<T>), grid, block, 0, st, (const T*)in, (T*)out, (const T*)in1, (T*)out1, rows, cols)
-  if (rows % piece == 0 && cols % piece == 0 && (bits & 15) == 0) {
+  if (pieces) {
     if (dtype == DT_BF16) COVSPEC_TRANSPOSE(transpose16_kernel, bf16_t);
     else COVSPEC_TRANSPOSE(transpose16_kernel, float);
   } else {

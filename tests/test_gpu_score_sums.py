@@ -153,3 +153,33 @@ def test_attention_scores_of_few_and_many_images(C, dtype, T):
     ref = O.query_score_attention(X[0].double().cpu().numpy(), Q[0].double().cpu().numpy(), 1)
     # as above; logits of width 64 are below 5 behind the scale
     np.testing.assert_allclose(got[0][0].cpu().numpy(), ref, rtol=2e-7 if dtype == "fp32" else (d + 3) * 2.0 ** -24 * 2.5 + 3e-7)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("mode", ["cosine", "softmax"])
+def test_scores_with_weights_of_any_alignment(C, dtype, mode):
+    """Each weight on a 16-byte boundary and an element behind one: the two are transposed together where they are alike, otherwise each in its own
+    form.  Against the oracle, and the same to rounding in all four."""
+    import torch
+    N, d, T, B = 90, 192, 7, 2
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X, Q = (torch.randn(B, n, d, generator=g, device="cuda") for n in (N, T))
+    W = [torch.randn(d, d, generator=g, device="cuda") / d ** 0.5 for _ in range(2)]
+    if dtype == "bf16":
+        X, Q, W = X.bfloat16(), Q.bfloat16(), [w.bfloat16() for w in W]
+    p = C.Params(batch=B, n_tokens=N, d_model=d, n_query=T, n_heads=2, dtype=C.BF16 if dtype == "bf16" else C.FP32, keep_k=4, preselect_m=8, rank_r=2,
+                 rel_mode=C.REL_COSINE_MAX if mode == "cosine" else C.REL_ATTN_SOFTMAX)
+    x, q, wq, wk = (t.double().cpu().numpy() for t in (X[0], Q[0], W[0], W[1]))
+    score = O.query_score_cosine if mode == "cosine" else lambda v, e: O.query_score_attention(v, e, 2)
+    ref = score(O.embed(x, wk), O.embed(q, wq))
+    for shift in (0, 1, 2, 3):
+        ws = []
+        for i in range(2):
+            base = torch.zeros(d * d + 8, dtype=W[i].dtype, device="cuda")
+            at = base[shift >> i & 1:][:d * d].view(d, d)
+            at.copy_(W[i])
+            assert at.data_ptr() % 16 == (shift >> i & 1) * at.element_size()
+            ws.append(at)
+        got = C.score(p, X, None, Q, ws[0], ws[1])[0][0].cpu().numpy()
+        # fp32: fp64 inside.  bf16: fp32 sums of 192 products twice over, against scores from 0.1 (cosine) and mean softmax weights of 1 / 90
+        np.testing.assert_allclose(got, ref, rtol=3e-7 if dtype == "fp32" else 3e-4, atol=0 if dtype == "fp32" else 2e-6, err_msg="shift %d" % shift)
