@@ -66,27 +66,6 @@ __device__ __forceinline__ float online_add(float& c, float& s, const float (&v)
   return vm;
 }
 
-// combine of two (reference, sum) pairs of the base-2 domain
-__device__ __forceinline__ void combine_pair(double& m, double& s, double m2, double s2) {
-  const double mn = fmax(m, m2);
-  s = (m == mn ? s : s * exp2(m - mn)) + (m2 == mn ? s2 : s2 * exp2(m2 - mn));
-  m = mn;
-}
-
-
-// butterfly combine of (reference, sum) pairs over the wave; every lane ends with the wave's pair
-__device__ __forceinline__ void wave_combine(double& m, double& s) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double m2 = __shfl_xor(m, o, 64), s2 = __shfl_xor(s, o, 64);
-    if (s2 > 0.0) {
-      if (s > 0.0) combine_pair(m, s, m2, s2);
-      else { m = m2; s = s2; }
-    }
-  }
-}
-
-
 // Workgroup combine of the threads' fp32 (reference, sum) pairs: each wave rescales to its largest reference
 // (one fp32 exp2 per lane, relative error ~1e-7, inside the streaming sums' own), adds in fp64, and thread 0
 // folds the waves the same way.  `red` holds 2 doubles per wave.  Contains a barrier: call uniformly; the
