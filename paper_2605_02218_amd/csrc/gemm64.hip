@@ -21,6 +21,7 @@
 // holds (row 4v + l/16, col l%16).
 #include <type_traits>
 #include "common.h"
+#include "gemm64_tiles.h"
 #include "host_cache.h"
 #include "kernels.h"
 
@@ -34,7 +35,6 @@ constexpr int TK = 16, PITCH = TK + 1;
 // (2000 x 512 x 512) 64 / 30, 288 (1100 x 1024 x 1024) 148 / 52, 864 of K = 256 57 / 57, 1008 59 / 68: the small tiles would still
 // win up to some 800; the line is where the sums' order was drawn.
 constexpr long kSmallTiles64 = 256;
-constexpr int kUnits = 256;      // compute units
 
 __device__ __forceinline__ double as_f64(double v) { return v; }
 __device__ __forceinline__ double as_f64(float v) { return (double)v; }
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g, int tiles_m, in
 // Bound by the fp64 MFMA: a 64 x 64 tile keeps a compute unit busy for K / 32 us, so what decides is how evenly the tiles go into the
 // compute units (launch_plain).  us with the tiles chosen there, and the time at the rate of a loop of nothing but these MFMAs (67.6
 // TFLOP/s): 192 x 1664 x 1664, batch 4 72 (63; on tiles of 32 x 32, which read their operands at 20 TB/s from the L2s, 83); 384 x 1152 x
-// 1152, batch 8 139 (121); 256 x 640 x 640, batch 64 213 (199); 192 x 1280 x 1280, batch 4 50 (37).
+// 1152, batch 8 139 (121); 256 x 640 x 640, batch 64 218 (199); 192 x 1280 x 1280, batch 4 50 (37).
 // A symmetric product (lower_only, frag; TM = TN) has a workgroup for each tile on and below its diagonal only.
 // TS = bf16 (the Gram matrix of the greedy picks, row lists): the same 128-byte pieces of a row are 64 k, converted between LDS and
 // MFMA, which the MFMAs hide.  Staged through registers and converted into LDS, one k-tile of 16 in flight, six of
@@ -735,55 +735,26 @@ hipError_t launch_dma(const GemmArgs& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The tile whose fullest compute unit has the least to do: rounds of tiles over the compute units, times the tile's area, times what a
-// unit of area costs more or less in such tiles (operand reads per MFMA).  us, 64 x 96 / 80 / 64 / 48 / 32 and 32 x 32:
-//   192 x 1664 x 1664, batch 4 83 / 72 / 109 / 83 / 86 and 83     192 x 1280 x 1280, batch 4 65 / 56 / 50 / 64 / 49 and 49
-//   384 x 1152 x 1152, batch 8 162 / 140 / 151 / 144 / 139, 149   256 x 640 x 640, batch 64 218 / 213 / 218 / 235 / 229 and 247
-//   320 x 1024 x 1024, batch 4 54 / 82 / 69 / 53 / 55 and 52      192 x 960 x 960, batch 7 51 / 44 / 67 / 50 / 53 and 49
-//   384 x 1280 x 1280, batch 12 238 / 253 / 249 / 252 / 260, 269  128 x 512 x 512, batch 10 29 / 25 / 22 / 18 / 22 and 18
-// (64 x 112, 64 x 128, 128 x 64, 128 x 96, 128 x 128 and a second group of waves on 64 x 80 or 64 x 64: never the best by more than 1 %.)
-// Symmetric products and bf16 on 64 x 64 and 32 x 32 only: 192 x 192 x 1664, batch 4 59 and 24; 256 x 256 x 640, batch 64 88 and 77.
 template <typename TS>
 hipError_t launch_plain(const GemmArgs& g, hipStream_t stream) {
+  constexpr bool F64 = std::is_same<TS, double>::value;
   const bool triangle = g.lower_only || g.frag;
   if ((triangle && g.M != g.N) || (g.frag && g.N % 64 != 0)) return hipErrorInvalidValue;
-  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64;
-  if constexpr (std::is_same<TS, double>::value) {
-    const long m16 = (g.M + 15) / 16, n16 = (g.N + 15) / 16, t16 = (triangle ? m16 * (m16 + 1) / 2 : m16 * n16) * g.batch;
-    // us, the tiles below / here, back to back: 144 (192 x 192 x 192) 5.5 / 4.6, 240 (192 x 320 x 320) 7.4 / 6.3, 256 (128 x 256 x 256, batch 2) 6.8 / 5.7, 78
-    // (192 x 192 x 1664, the triangle) 20.7 / 14.7; 312 (the same, batch 4) 22.0 / 25.9, 320 18.3 / 21.9, 480 (192 x 320 x 320, batch 2) 7.6 / 8.8.
-    if (t16 >= 1 && t16 <= kUnits && g.K % 64 == 0) {
-      hipLaunchKernelGGL(gemm64_tile16_kernel, dim3((unsigned)t16), dim3(256), 0, stream, g, (int)m16, (int)n16);
+  const Gemm64Tile tile = plain_tile(g.M, g.N, g.K, g.batch, triangle, F64);
+  if constexpr (F64) {
+    if (tile == TILE_16x16) {
+      const int m16 = (g.M + 15) / 16, n16 = (g.N + 15) / 16;
+      const unsigned blocks = (triangle ? m16 * (m16 + 1) / 2 : m16 * n16) * g.batch;
+      hipLaunchKernelGGL(gemm64_tile16_kernel, dim3(blocks), dim3(256), 0, stream, g, m16, n16);
       return hipGetLastError();
     }
+    if (tile == TILE_64x96) return launch_dma<TS, 1, 64, 96>(g, stream);
+    if (tile == TILE_64x80) return launch_dma<TS, 1, 64, 80, 4>(g, stream);
+    if (tile == TILE_64x48) return launch_dma<TS, 1, 64, 48, 4>(g, stream);
   }
-  const auto fullest = [](long tiles) { return (double)((tiles + kUnits - 1) / kUnits); };
-  const long t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
-  double least = 1.18 * fullest(t32);
-  int width = 0;                                    // 0: 32 x 32
-  const auto consider = [&](int w, long tiles, double per_area) {
-    const double cost = w / 16 * per_area * fullest(tiles);
-    if (cost < least) { least = cost; width = w; }
-  };
-  if (triangle) {
-    if (4.0 * fullest(m64 * (m64 + 1) / 2 * g.batch) <= least) width = 64;
-  } else {
-    const auto tiles = [&](int w) { return m64 * ((g.N + w - 1) / w) * g.batch; };
-    consider(64, m64 * n64 * g.batch, 1.0);
-    if constexpr (std::is_same<TS, double>::value) {
-      consider(96, tiles(96), 0.99);
-      consider(80, tiles(80), 1.0);
-      consider(48, tiles(48), 1.02);
-    }
-    consider(32, m64 * n32 * g.batch, 1.06);
-  }
-  if constexpr (std::is_same<TS, double>::value) {
-    if (width == 96) return launch_dma<TS, 1, 64, 96>(g, stream);
-    if (width == 80) return launch_dma<TS, 1, 64, 80, 4>(g, stream);
-    if (width == 48) return launch_dma<TS, 1, 64, 48, 4>(g, stream);
-  }
-  if (width == 64) return launch_dma<TS, 1, 64, 64>(g, stream);
-  if (width == 32) return launch_dma<TS, 1, 64, 32>(g, stream);
+  if (tile == TILE_64x64) return launch_dma<TS, 1, 64, 64>(g, stream);
+  if (tile == TILE_64x32) return launch_dma<TS, 1, 64, 32>(g, stream);
+  const long m32 = (g.M + 31) / 32, n32 = (g.N + 31) / 32, t32 = (triangle ? m32 * (m32 + 1) / 2 : m32 * n32) * g.batch;
   return t32 <= kUnits && g.K >= (int)(256 / sizeof(TS)) ? launch_dma<TS, 2, 32, 32>(g, stream) : launch_dma<TS, 1, 32, 32>(g, stream);
 }
 

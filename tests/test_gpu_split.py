@@ -92,9 +92,12 @@ def test_energies_of_a_full_solve(C, name):
 
 
 # The sign iteration of small matrices without meetings (split.hip) at its edges, and the one with meetings beyond: batch, tokens,
-# width, rank, decay, way.  Order 64, 128, 192 and 256, each with as many images as it takes and one more.
+# width, rank, decay, way.  Order 64, 128, 192 and 256, each with as many images as it takes and one more (order 64: while a compute unit gets
+# one of the 32 x 32 tiles of the other form).
 SMALL_SIGN = {
     "order-64": (40, 64, 96, 20, 0.05, 3),
+    "order-64-most": (85, 64, 96, 20, 0.05, 3),
+    "order-64-over": (86, 64, 96, 20, 0.05, 3),
     "order-128-most": (23, 110, 128, 40, 0.05, 3),
     "order-128-over": (24, 110, 128, 40, 0.05, 3),
     "order-192-most": (7, 300, 320, 100, 0.02, 1),
@@ -169,8 +172,10 @@ def test_cut_of_few_images(C, name):
         assert err.max() < 6e-8 + 2e-9 / (np.exp(2 * decay) - 1) + 2e-8, "%s image %d: %g" % (name, b, err.max())
 
 
-# Batches whose products go on each width of tile of the fp64 kernel (gemm64.hip): images, tokens, rank; the last tile is a partial one.
-TILE_WIDTHS = {"64x80": (7, 950, 100), "64x48": (10, 500, 60), "64x96": (12, 1270, 300), "64x64": (4, 1270, 120), "64x32": (2, 1000, 180), "32x32": (4, 1000, 240),
+# Batches whose products go on each width of tile of the fp64 kernel (gemm64.hip): images, tokens, rank; the last tile of 96, 48 and (in one of
+# the two) 80 columns is a partial one.  test_gemm64_tiles.py holds the names against the rule.
+TILE_WIDTHS = {"64x80": (7, 950, 100), "64x80-partial": (4, 1638, 120), "64x48": (10, 500, 60), "64x96": (12, 1270, 300), "64x64": (4, 1270, 120),
+               "64x32": (2, 1000, 180), "32x32": (4, 1000, 240),
                # a 16 x 16 tile per compute unit: 128 x 256 of two images, 192 x 320 of one; and beyond
                "16x16-most": (2, 250, 60), "16x16": (1, 310, 100), "16x16-over": (2, 310, 100)}
 
