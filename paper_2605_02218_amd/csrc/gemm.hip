@@ -18,7 +18,6 @@
 // Result layout of both: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, col l%32.
 #include <type_traits>
 
-
 #include "common.h"
 #include "host_cache.h"
 #include "kernels.h"

@@ -12,7 +12,7 @@
 //                        their way through registers into LDS.
 //   gemm64_dma_kernel    fp64 x fp64 (the block iteration) and bf16 x bf16: direct-to-LDS loads, tiles of 64 x 96 to 32 x 32.
 //   gemm64_tile16_kernel fp64 products of so few 16 x 16 tiles that a compute unit gets one at most
-//   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 tiles, k over the four waves, straight from global memory.
+//   gemm64_small_kernel  few tiles and an fp32 operand, row lists: 32 x 32 or 16 x 16 tiles, k over the four waves, straight from global memory.
 //   gemm64_sym_kernel    the products after the spectral split, whose left operand is symmetric and whose right one is [K][N].
 // gemm64_kernel: 256 threads = 4 waves (2x2); wave tile (MI*16) x (NJ*16), block tile twice that in each direction (64x64
 // for <2,2>), k-tile 16; the loads of k-tile t+1 are issued before the MFMAs of tile t and parked in registers, LDS is double

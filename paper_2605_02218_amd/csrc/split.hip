@@ -350,6 +350,12 @@ __global__ __launch_bounds__(256) void split_kernel(const double* __restrict__ H
 // this moves an eigenvalue over a trial point, 1e-6 of the norm away and more, takes a pivot below 1e-10.  An exact zero counts for a matrix
 // 1e-8 away, see pivots.h.  A count that is wrong shows in the trace of the projector.)
 // Bound by the chain of pivots and the MFMAs of a wave.  us, split_kernel and here: one window of 64 44 and 19 (two 44 and 22), of 128 121 and 83.
+// A window of 128 is 36 tiles, 288 of a wave's 512 registers: half of them are accumulator registers, 2000 moves between the two kinds a pass of
+// 27 us, and 70 others are spilled (84 accesses to scratch memory a pass, 14 of them in the elimination, the rest around the exchange of the
+// counts).  A window of 64 has neither.
+// Where split_kernel takes over, us of covspec_select by counting / by split_kernel: windows of 128 eight images 184 / 214; windows of 64 in blocks of
+// 128 four 306 / 328, five 316 / 330, eight 347 / 352; of 192 three 406 / 425, four 432 / 447, five 477 / 487, eight 560 / 559; of 448 three 1721 / 1736,
+// four 1824 / 1819, five 2080 / 2054, eight 2291 / 2265.  (Order 64 as its own window: four 106 / 185, eight 129 / 185.)
 constexpr int kCutImages = 8;        // of windows of 128, half as many of 64: a SIMD gets a wave at most
 constexpr int kTrials = 256;
 constexpr int kCutPasses = 8, kCutPoints = 8;
@@ -859,7 +865,8 @@ __global__ __launch_bounds__(256 * KS, WIDE && KS == 1 ? 3 : 2) void sign_kernel
 //   the tile is formed; and a workgroup stores version v when the stores of v - 1 have been acknowledged, so that nobody who has
 //   anything of version v can still find the words of v - 3 elsewhere.  The operands are loaded past the L2s, which are not coherent.
 // Only the steps that may be the last, by the lower bound l, meet at the barrier: they are when no element moved by more than 1e-7.
-// Bound by latency: store, load, 3 MFMAs a group of 16 k and wave, four partial sums.  us per product with 32 x 32 tiles and a barrier in
+// Bound by latency: store, load, 3 MFMAs a group of 16 k and wave, four partial sums.  (Five workgroups a compute unit at order 256 leave 96
+// registers a wave: 19 are spilled, 12 accesses to scratch memory a step.)  us per product with 32 x 32 tiles and a barrier in
 // global memory after each (store, acknowledge, count, see the count, load) and here: one image of order 192 7.0 and 3.4 (155 and 76 in all),
 // four 7.1 and 5.3, one of 128 5 and 2.8 (115 and 63).
 constexpr int kSmallBlocks = 4;
@@ -1186,9 +1193,10 @@ hipError_t launch_spectral_split(const double* H, int B, int P, int r, bool orde
   const long stride = (long)P * P;
   const dim3 sg((unsigned)(B + B * (P / 16)));
   // The small kernel, whose workgroups load two rows of 16 x P each past the L2s: while that is 28 MB a product.  us per call of
-  // covspec_select, sign_kernel / small, by images: order 128 12 278 / 238, 16 274 / 251, 25 295 / 295; order 192 4 534 / 482, 7 574 / 561,
-  // 9 610 / 602, 12 648 / 668; order 256 1 690 / 509 and 2 712 / 577 (with the earlier Cholesky), 4 851 / 902, 7 967 / 1098.  And an
-  // image's workgroups, a tile each, have to be as few as above.
+  // covspec_select, sign_kernel / small, by images: order 64 40 228 / 200, 85 246 / 233; order 128 12 259 / 221, 20 277 / 250, 23 282 / 269, 24 283 / 275;
+  // order 192 5 531 / 487, 7 556 / 517, 8 558 / 531, 9 603 / 586, 10 612 / 609, 12 656 / 699; order 256 1 679 / 599, 3 757 / 711, 4 772 / 745, 5 850 / 835, 6 873 /
+  // 891.  (The line was drawn before the pause in its fetches, which moved the meeting points to 40 MB.)  And an image's workgroups, a tile
+  // each, have to be as few as above.
   const long n16 = P / 16, t16 = n16 * (n16 + 1) / 2;
   bool small = form == 0 && P <= 64 * kSmallBlocks && B * t16 * 2 * 16 * P * 8 <= 28000000;
   static_assert(kSmallBlocks == 4, "");
