@@ -906,7 +906,7 @@ __global__ __launch_bounds__(256, BLOCKS == 4 ? 5 : 4) void sign_small_kernel(co
   const bool lift = m < kLiftTo;
   const double mu = lift ? 0.0 : cb->mu, inv = 1.0 / (lift ? norm : fmax(norm - mu, mu));
   if (!lift) l = cb->half * inv;
-  double* buf[3] = {X0 + b * pp, X1 + b * pp, Y + b * pp};       // version v is in buf[0], then they move on
+  double* buf[3] = {X0 + b * pp, X1 + b * pp, Y + b * pp};       // version v is in buf[v % 3]
   __amdgpu_buffer_rsrc_t rs[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) rs[k] = __builtin_amdgcn_make_buffer_rsrc((void*)buf[k], (short)0, (int)(pp * 8), 0x00020000);
